@@ -224,7 +224,8 @@ int lfps_exact_topk(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int3
  *   q_hist [n_queries, B, Hq, D] fp32, q_hist[j-1] = the j-th most recent query (j = 1: the last one).
  * Query j sees rows [0, n_b - j + 1); w = softmax over the offloaded rows it sees of q.K/sqrt(D);
  *   Phi_ver(i) = 1/(2 s (1 - gamma)) sum_j w_j(i),    Phi_sla(i) = 1/(2 s (1 - gamma)) sum_j w_j(i - j + 1)
- * (the paper uses s = 32).  One dense scoring pass per query. */
+ * (the paper uses s = 32).  Two passes over K for every 32 queries (one for a single query); fp32 caches: one scoring
+ * pass per query. */
 int lfps_tables_init(lfps_ctx* ctx, const float* q_hist, int32_t n_queries, const lfps_kv* kv, void* stream);
 /* Set / read the tables as true values per position: phi_ver, phi_sla [B, Hq, max_seq_len], rows
  * [0, seq_lens[b]) used (fp32 in, fp64 out; entries of sink rows and rows >= n_b read as 0). */

@@ -46,6 +46,7 @@ struct lfps_ctx {
   int32_t* x_rank;     // [B] rank of the sample score taken as threshold
   int64_t* x_start;    // [B*Hkv + 1] place of each group on the line of all rows, then the line's length
   float* thr_x;        // [B, Hq] thresholds of the dense filtered pass
+  void* aux;           // partial sums of the prefill calls (priors, table statistics)
   int32_t* flags;      // [0] status flags, [1] part size chosen by the last filtered scoring pass, [2] heads rescored since the last poll
   int64_t ws_bytes;
   // timing
@@ -74,8 +75,11 @@ namespace {
 
 struct Sizes {
   int32_t G, cand_cap, score_stride, n_split_full, nseg, flag_words;
-  int64_t score_b, cand_b, count_b, sel_b, part_b, slot_b, seg_b, thr_b, line_b, tver_b, tsla_b, tstate_b, tflag_b, x_b, total;
+  int64_t score_b, cand_b, count_b, sel_b, part_b, slot_b, seg_b, thr_b, line_b, tver_b, tsla_b, tstate_b, tflag_b, x_b, aux_b, total;
 };
+
+// Key format of the MFMA kernels (16-bit and FP8 keys): 0 bf16, 1 FP8, 2 fp16.
+int key_kind(const lfps_config& c) { return c.k_fp8 ? 1 : (c.kv_dtype == LFPS_F16 ? 2 : 0); }
 
 int64_t align256(int64_t x) { return (x + 255) & ~(int64_t)255; }
 
@@ -153,8 +157,11 @@ int check_config(const lfps_config* c, Sizes* z, char* err, size_t errn) {
   z->tstate_b = c->table_mode ? align256(heads * kTableStateDoubles * 8) : 0;
   z->tflag_b = c->table_mode ? align256(heads * z->flag_words * 4) : 0;
   z->x_b = 3 * z->count_b + 2 * align256((int64_t)c->batch * 4) + align256(((int64_t)c->batch * c->n_kv_heads + 1) * 8) + z->thr_b;
+  z->aux_b = prior_scratch_bytes(s);
+  if (c->table_mode && table_init_scratch_bytes(s) > z->aux_b) z->aux_b = table_init_scratch_bytes(s);
+  z->aux_b = align256(z->aux_b);
   z->total = z->score_b + z->cand_b + z->count_b + z->sel_b + z->part_b + z->slot_b + z->seg_b + z->thr_b +
-             z->line_b + 256 + z->x_b + z->tver_b + z->tsla_b + z->tstate_b + 2 * z->tflag_b + z->thr_b /* gate marks */;
+             z->line_b + 256 + z->x_b + z->aux_b + z->tver_b + z->tsla_b + z->tstate_b + 2 * z->tflag_b + z->thr_b /* gate marks */;
   return LFPS_OK;
 }
 
@@ -337,6 +344,8 @@ int lfps_create(const lfps_config* cfg, lfps_ctx** out) {
     c->thr_x = (float*)(p + 2 * z.count_b + 2 * per_b + align256(((int64_t)cfg->batch * cfg->n_kv_heads + 1) * 8));
     p += z.x_b;
   }
+  c->aux = p;
+  p += z.aux_b;
   if (cfg->table_mode) {
     c->tab_ver = (float*)p;
     p += z.tver_b;
@@ -367,9 +376,10 @@ int lfps_create(const lfps_config* cfg, lfps_ctx** out) {
   if (e == hipSuccess) e = hipMemset(c->gate, 0, (size_t)z.thr_b);
   if (e == hipSuccess) e = configure_candidates(s);
   if (e == hipSuccess) e = configure_select(s);
+  if (e == hipSuccess && cfg->table_mode && cfg->kv_dtype != LFPS_F32) e = configure_table_history(s, key_kind(*cfg));
   // the launch size of the filtered pass is needed whenever that pass can be switched on (lfps_set_filter)
   if (e == hipSuccess && c->slot)
-    e = filter_score_blocks(s, cfg->k_fp8 ? 1 : (cfg->kv_dtype == LFPS_F16 ? 2 : 0), c->filter_blocks);
+    e = filter_score_blocks(s, key_kind(*cfg), c->filter_blocks);
   if (e == hipSuccess && c->slot && (c->filter_blocks[0] < 1 || c->filter_blocks[1] < 1)) e = hipErrorLaunchFailure;
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
@@ -675,16 +685,24 @@ int lfps_tables_init(lfps_ctx* ctx, const float* q_hist, int32_t n_queries, cons
   if (rc != LFPS_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   const Shape& s = ctx->shape;
-  const int64_t q_stride = (int64_t)s.B * s.Hq * kD;
-  for (int j = 1; j <= n_queries; ++j) {
+  hipError_t e = hipSuccess;
+  const bool together = ctx->cfg.kv_dtype != LFPS_F32;   // all queries in one pass over K (fp32 keys: one at a time)
+  if (together) {
     LAUNCH(ctx, LFPS_KERNEL_DENSE_SCORE, st,
-           launch_group_score(s, ctx->cfg.kv_dtype, q_hist + (int64_t)(j - 1) * q_stride, v, nullptr, nullptr, ctx->score,
-                              s.score_stride, ctx->flags, st));
-    hipError_t e = launch_table_init(s, ctx->tab_ver, ctx->tab_sla, v.seq_lens, ctx->score, s.score_stride,
-                                     (double)ctx->cfg.table_decay, j, n_queries, st);
-    if (e != hipSuccess) return fail(ctx, LFPS_EHIP, "lfps_tables_init", e);
+           launch_table_history(s, ctx->tab_ver, ctx->tab_sla, q_hist, n_queries, (double)ctx->cfg.table_decay, v,
+                                ctx->score, s.score_stride, ctx->aux, ctx->flags, st));
+  } else {
+    for (int j = 1; j <= n_queries; ++j) {
+      LAUNCH(ctx, LFPS_KERNEL_DENSE_SCORE, st,
+             launch_group_score(s, ctx->cfg.kv_dtype, q_hist + (int64_t)(j - 1) * s.B * s.Hq * kD, v, nullptr, nullptr,
+                                ctx->score, s.score_stride, ctx->flags, st));
+      e = launch_table_init(s, ctx->tab_ver, ctx->tab_sla, v.seq_lens, ctx->score, s.score_stride,
+                            (double)ctx->cfg.table_decay, j, n_queries, st);
+      if (e != hipSuccess) return fail(ctx, LFPS_EHIP, "lfps_tables_init", e);
+    }
   }
-  hipError_t e = launch_table_finish(s, ctx->tab_ver, ctx->tab_sla, ctx->tab_state, v.seq_lens, st);
+  e = launch_table_state(s, ctx->tab_ver, ctx->tab_sla, ctx->tab_state, v.seq_lens, ctx->aux, together && n_queries == 1,
+                         st);
   if (e != hipSuccess) return fail(ctx, LFPS_EHIP, "lfps_tables_init (statistics)", e);
   ctx->tab_updates = 0;
   ctx->tab_ready = 1;
@@ -791,12 +809,8 @@ int lfps_priors(lfps_ctx* ctx, const float* q, const lfps_kv* kv, float* kbar, f
   if (rc != LFPS_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   const Shape& s = ctx->shape;
-  hipError_t e = launch_prior_means(s, ctx->cfg.kv_dtype, v, kbar, vbar, st);
-  if (e != hipSuccess) return fail(ctx, LFPS_EHIP, "lfps_priors (means)", e);
-  LAUNCH(ctx, LFPS_KERNEL_DENSE_SCORE, st,
-         launch_group_score(s, ctx->cfg.kv_dtype, q, v, nullptr, nullptr, ctx->score, s.score_stride, ctx->flags, st));
-  e = launch_prior_variance(s, q, v.seq_lens, ctx->score, s.score_stride, sigma2_hat, st);
-  if (e != hipSuccess) return fail(ctx, LFPS_EHIP, "lfps_priors (variance)", e);
+  hipError_t e = launch_priors(s, ctx->cfg.kv_dtype, q, v, kbar, vbar, sigma2_hat, ctx->aux, ctx->flags, st);
+  if (e != hipSuccess) return fail(ctx, LFPS_EHIP, "lfps_priors", e);
   return LFPS_OK;
 }
 

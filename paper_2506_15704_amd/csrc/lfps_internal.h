@@ -157,6 +157,16 @@ hipError_t launch_full_merge(const Shape& s, const int32_t* seq_lens, const floa
 // Score tables (Eq. 4, 7-10): see tables.hip.  tab_ver [B*Hq, Lcap], tab_sla [B*Hq, 2*Lcap] unscaled fp32
 // entries; state [B*Hq, kTableStateDoubles]; f0 / fm [B*Hq, flag_words] bitmaps written by the scan.
 constexpr int kTableStateDoubles = 16;
+// head state (doubles): scale, update count, raw moments of both tables, and "the table was flat (every
+// entry equal) when it was imported with N entries" marks.  The thresholds of Eq. 8 are derived from the
+// moments at the start of every scan for the number of rows that scan sees, so a head whose update was
+// skipped (a bypassed head) or a cache that grew by several rows needs no special case: new positions are zeros.
+enum {
+  TS_G = 0, TS_CNT = 1,
+  TS_MV = 2,            // M1..M4 of the vertical table: [2..5]
+  TS_MS = 6,            // M1..M4 of the slash table:    [6..9]
+  TS_FLAT_V = 10, TS_FLAT_S = 11, TS_FLAT_N = 12,
+};
 hipError_t launch_table_flags(const Shape& s, const float* tab_ver, const float* tab_sla, const double* state,
                               const int32_t* seq_lens, uint32_t* f0, uint32_t* fm, int flag_words, double a,
                               const int32_t* gate, hipStream_t st);
@@ -173,8 +183,19 @@ hipError_t launch_table_export(const Shape& s, const float* tab_ver, const float
 hipError_t launch_table_init(const Shape& s, float* tab_ver, float* tab_sla, const int32_t* seq_lens,
                              const float* score, int64_t score_stride, double gamma, int j, int n_queries,
                              hipStream_t st);
-hipError_t launch_table_finish(const Shape& s, const float* tab_ver, const float* tab_sla, double* state,
-                               const int32_t* seq_lens, hipStream_t st);
+// Eq. 4 from n_queries prefill queries, kHistBatch of them per pass over K (prefill.hip; 16-bit and FP8 keys);
+// q_hist[j - 1] = query j, the j-th most recent.  dots [B, Hq, dots_stride]: room for one query's dot products.
+// scratch: table_init_scratch_bytes.
+constexpr int kHistBatch = 32;
+int64_t table_init_scratch_bytes(const Shape& s);
+hipError_t configure_table_history(const Shape& s, int k_kind);
+hipError_t launch_table_history(const Shape& s, float* tab_ver, float* tab_sla, const float* q_hist, int n_queries,
+                                double gamma, const KvView& kv, float* dots, int64_t dots_stride, void* scratch,
+                                int32_t* flags, hipStream_t st);
+// Statistics and head state of freshly written tables; have_moments: launch_table_history was called with one query
+// and has left the moments in scratch.
+hipError_t launch_table_state(const Shape& s, const float* tab_ver, const float* tab_sla, double* state,
+                              const int32_t* seq_lens, void* scratch, bool have_moments, hipStream_t st);
 // Head sparsity (Eq. 5-6) and the prefill priors it needs; gate [B,Hq] marks bypassed heads, whose output
 // row (vbar) and index row (-1) the kernel writes when out != NULL; thr_state (or NULL): the score filter's
 // per-head history, where a bypassed head without history is given +inf.
@@ -182,9 +203,10 @@ hipError_t launch_head_sparsity(const Shape& s, int dtype, const float* q, const
                                 const float* sigma2_hat, int n_local, float eps, float* rho, int32_t* gate,
                                 const float* vbar, int32_t* topk_idx, float* topk_score, float* out, float* thr_state,
                                 hipStream_t st);
-hipError_t launch_prior_means(const Shape& s, int dtype, const KvView& kv, float* kbar, float* vbar, hipStream_t st);
-hipError_t launch_prior_variance(const Shape& s, const float* q, const int32_t* seq_lens, const float* score,
-                                 int64_t score_stride, float* sigma2_hat, hipStream_t st);
+// scratch: prior_scratch_bytes.
+int64_t prior_scratch_bytes(const Shape& s);
+hipError_t launch_priors(const Shape& s, int dtype, const float* q, const KvView& kv, float* kbar, float* vbar,
+                         float* sigma2_hat, void* scratch, int32_t* flags, hipStream_t st);
 
 // ---- small device helpers ------------------------------------------------------------
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -280,6 +302,36 @@ __device__ __forceinline__ int wave_inclusive_sum(int x) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
   x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
   x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+// Sum and maximum over the 16 lanes of a row of lanes, left in every one of them (DPP rotations, no LDS).
+__device__ __forceinline__ float row16_sum(float x) {
+#define LFPS_ROT(v, n) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + (n), 0xf, 0xf, false))
+  x += LFPS_ROT(x, 8);
+  x += LFPS_ROT(x, 4);
+  x += LFPS_ROT(x, 2);
+  x += LFPS_ROT(x, 1);
+  return x;
+}
+__device__ __forceinline__ float row16_max(float x) {
+  x = fmaxf(x, LFPS_ROT(x, 8));
+  x = fmaxf(x, LFPS_ROT(x, 4));
+  x = fmaxf(x, LFPS_ROT(x, 2));
+  x = fmaxf(x, LFPS_ROT(x, 1));
+  return x;
+#undef LFPS_ROT
+}
+template <int kBy>
+__device__ __forceinline__ double row16_rotate(double x) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x120 + kBy, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x120 + kBy, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double row16_sum(double x) {
+  x += row16_rotate<8>(x);
+  x += row16_rotate<4>(x);
+  x += row16_rotate<2>(x);
+  x += row16_rotate<1>(x);
   return x;
 }
 

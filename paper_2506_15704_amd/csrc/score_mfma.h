@@ -111,51 +111,60 @@ __device__ __forceinline__ void report_q_range(bool clipped, int32_t* __restrict
   if (__ballot(clipped) != 0 && (threadIdx.x & 63) == 0) atomicOr(flags, LFPS_FLAG_Q_RANGE);
 }
 
-// The registers a lane (j, kb) holds of one 64-row K tile: its 32 channels [32 kb, 32 kb + 32) of the
-// four rows 16 t + j, in the storage format of K.  operand(t, kk) is the MFMA B operand of step kk, the
-// channels 32 kb + 8 kk .. + 7 as bf16: the value as stored for a bf16 cache, converted (exactly: every
-// E4M3 value is a bf16 value) when it is multiplied for an FP8 cache, so that a tile in flight costs half
-// the registers and half the loads.
+// The registers a lane (j, kb) holds of 16 K rows: its 32 channels [32 kb, 32 kb + 32) of row j, in the storage format
+// of K.  operand(kk) is the MFMA B operand of step kk, the channels 32 kb + 8 kk .. + 7 as bf16: the value as stored for
+// a bf16 cache, converted (exactly: every E4M3 value is a bf16 value) when it is multiplied for an FP8 cache, so that
+// a tile in flight costs half the registers and half the loads.
 template <int kKind>
-struct KTile;
+struct KSub;
 template <>
-struct KTile<kKindBf16> {
+struct KSub<kKindBf16> {
   using Operand = bf16x8;
   static constexpr int kElemBytes = 2;
-  bf16x8 v[4][4];
-  __device__ __forceinline__ void load_row(int t, const char* row, int kb) {
+  bf16x8 v[4];
+  __device__ __forceinline__ void load_row(const char* row, int kb) {
     const bf16x8* p = reinterpret_cast<const bf16x8*>(row) + 4 * kb;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) v[t][kk] = p[kk];
+    for (int kk = 0; kk < 4; ++kk) v[kk] = p[kk];
   }
-  __device__ __forceinline__ bf16x8 operand(int t, int kk) const { return v[t][kk]; }
+  __device__ __forceinline__ bf16x8 operand(int kk) const { return v[kk]; }
 };
 template <>
-struct KTile<kKindF16> {
+struct KSub<kKindF16> {
   using Operand = f16x8;
   static constexpr int kElemBytes = 2;
-  f16x8 v[4][4];
-  __device__ __forceinline__ void load_row(int t, const char* row, int kb) {
+  f16x8 v[4];
+  __device__ __forceinline__ void load_row(const char* row, int kb) {
     const f16x8* p = reinterpret_cast<const f16x8*>(row) + 4 * kb;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) v[t][kk] = p[kk];
+    for (int kk = 0; kk < 4; ++kk) v[kk] = p[kk];
   }
-  __device__ __forceinline__ f16x8 operand(int t, int kk) const { return v[t][kk]; }
+  __device__ __forceinline__ f16x8 operand(int kk) const { return v[kk]; }
 };
 template <>
-struct KTile<kKindFp8> {
+struct KSub<kKindFp8> {
   using Operand = bf16x8;
   static constexpr int kElemBytes = 1;
-  u32x4 v[4][2];
-  __device__ __forceinline__ void load_row(int t, const char* row, int kb) {
+  u32x4 v[2];
+  __device__ __forceinline__ void load_row(const char* row, int kb) {
     const u32x4* p = reinterpret_cast<const u32x4*>(row) + 2 * kb;
-    v[t][0] = p[0];
-    v[t][1] = p[1];
+    v[0] = p[0];
+    v[1] = p[1];
   }
-  __device__ __forceinline__ bf16x8 operand(int t, int kk) const {
-    const u32x4 w = v[t][kk >> 1];
+  __device__ __forceinline__ bf16x8 operand(int kk) const {
+    const u32x4 w = v[kk >> 1];
     return (kk & 1) ? fp8x8_to_bf16x8(w[2], w[3]) : fp8x8_to_bf16x8(w[0], w[1]);
   }
+};
+
+// A 64-row K tile: sub-tile t holds the rows 16 t + j.
+template <int kKind>
+struct KTile {
+  using Operand = typename KSub<kKind>::Operand;
+  static constexpr int kElemBytes = KSub<kKind>::kElemBytes;
+  KSub<kKind> sub[4];
+  __device__ __forceinline__ void load_row(int t, const char* row, int kb) { sub[t].load_row(row, kb); }
+  __device__ __forceinline__ Operand operand(int t, int kk) const { return sub[t].operand(kk); }
 };
 
 // Scores of the slots first .. first+63, first+step .. first+step+63, ... (below count) of one KV group, by one wave:

@@ -27,17 +27,6 @@ constexpr int kTabThreads = 256;
 constexpr int kFlagIters = 8;      // 64-position tests per wave of the scan kernel
 constexpr double kFoldBelow = 1e-20;   // gamma = 0.95 gets here after ~900 updates; stored values stay < 1e20 * Phi
 
-// head state (doubles): scale, update count, raw moments of both tables, and "the table was flat (every
-// entry equal) when it was imported with N entries" marks.  The thresholds of Eq. 8 are derived from the
-// moments at the start of every scan for the number of rows that scan sees, so a head whose update was
-// skipped (a bypassed head) or a cache that grew by several rows needs no special case: new positions are zeros.
-enum {
-  TS_G = 0, TS_CNT = 1,
-  TS_MV = 2,            // M1..M4 of the vertical table: [2..5]
-  TS_MS = 6,            // M1..M4 of the slash table:    [6..9]
-  TS_FLAT_V = 10, TS_FLAT_S = 11, TS_FLAT_N = 12,
-};
-
 // The update count as stored (a double) brought into [0, Lcap - 1]: every slash-frame index formed with
 // it stays inside the table's 2 * Lcap slots (the host refuses updates beyond that count).
 __device__ __forceinline__ int clamp_count(double c, int Lcap) {
@@ -415,7 +404,8 @@ __global__ __launch_bounds__(kTabThreads) void k_table_export(Shape s, const flo
 // recent query (j = 1..s) sees rows [0, n_b - j + 1); its weights w (softmax over the offloaded rows it
 // sees) are added to the vertical table at i and to the slash table at i + j - 1 (Eq. 4's w_{i-j+1}),
 // times 1/(2 s (1 - gamma)).  j = 1 overwrites, later launches accumulate.  score[bh, 0:n_b] holds the
-// scaled scores of query j.  grid B*Hq.  k_table_finish then derives the statistics.
+// scaled scores of query j.  grid B*Hq.  launch_table_state then derives the statistics.
+// Used for fp32 caches; the other formats take all queries together (prefill.hip).
 __global__ __launch_bounds__(1024) void k_table_init(Shape s, float* __restrict__ tab_ver, float* __restrict__ tab_sla,
                                                      const int32_t* __restrict__ seq_lens,
                                                      const float* __restrict__ score, int64_t score_stride, double gamma,
@@ -454,53 +444,6 @@ __global__ __launch_bounds__(1024) void k_table_init(Shape s, float* __restrict_
     const float x = (float)((double)expf(sc[i] - m) * norm);
     ver[i] += x;
     sla[i + j - 1] += x;                                     // i + j - 1 <= n - 1
-  }
-}
-
-// Scale 1, update count 0, raw moments and flat marks of the tables as they stand in the position frame.
-__global__ __launch_bounds__(kTabThreads) void k_table_finish(Shape s, const float* __restrict__ tab_ver,
-                                                              const float* __restrict__ tab_sla,
-                                                              double* __restrict__ state,
-                                                              const int32_t* __restrict__ seq_lens) {
-  __shared__ double red[kTabThreads / 64];
-  __shared__ float redf[kTabThreads / 64];
-  const int bh = blockIdx.x, b = bh / s.Hq, tid = threadIdx.x;
-  int n = seq_lens[b];
-  n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
-  const float* ver = tab_ver + (int64_t)bh * s.Lcap;
-  const float* sla = tab_sla + (int64_t)bh * 2 * s.Lcap + s.Lcap;
-  double mv[4] = {0, 0, 0, 0}, ms[4] = {0, 0, 0, 0};
-  float lo_v = INFINITY, hi_v = -INFINITY, lo_s = INFINITY, hi_s = -INFINITY;
-  for (int i = s.n_sink + tid; i < n; i += kTabThreads) {
-    const float xv = ver[i], xs = sla[i];
-    const double a1 = xv, b1 = xs;
-    mv[0] += a1; mv[1] += a1 * a1; mv[2] += a1 * a1 * a1; mv[3] += a1 * a1 * a1 * a1;
-    ms[0] += b1; ms[1] += b1 * b1; ms[2] += b1 * b1 * b1; ms[3] += b1 * b1 * b1 * b1;
-    lo_v = fminf(lo_v, xv); hi_v = fmaxf(hi_v, xv);
-    lo_s = fminf(lo_s, xs); hi_s = fmaxf(hi_s, xs);
-  }
-  double Mv[4], Ms[4];
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    Mv[p] = block_sum(mv[p], red, tid);
-    Ms[p] = block_sum(ms[p], red, tid);
-  }
-  lo_v = block_min(lo_v, redf, tid);
-  hi_v = -block_min(-hi_v, redf, tid);
-  lo_s = block_min(lo_s, redf, tid);
-  hi_s = -block_min(-hi_s, redf, tid);
-  if (tid == 0) {
-    double* st = state + (int64_t)bh * kTableStateDoubles;
-    st[TS_G] = 1.0;
-    st[TS_CNT] = 0.0;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      st[TS_MV + p] = Mv[p];
-      st[TS_MS + p] = Ms[p];
-    }
-    st[TS_FLAT_V] = hi_v > lo_v ? 0.0 : 1.0;
-    st[TS_FLAT_S] = hi_s > lo_s ? 0.0 : 1.0;
-    st[TS_FLAT_N] = (double)(n - s.n_sink > 0 ? n - s.n_sink : 0);
   }
 }
 
@@ -598,73 +541,6 @@ __global__ __launch_bounds__(64) void k_head_sparsity(Shape s, const float* __re
   }
 }
 
-// ----------------------------------------------------------------------------- prefill priors (Sec. 4.2 "Prefilling")
-// Mean K row and mean V row over rows [n_sink, n_b) of one (b, g).  1024 threads: 64 row slots x 16 lanes
-// of 8 channels; fp32 partial sums per thread, fp64 across the row slots.
-template <typename TK, typename T, bool kPaged>
-__global__ __launch_bounds__(1024) void k_prior_means(Shape s, const TK* __restrict__ K, const T* __restrict__ V,
-                                                      int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage pg,
-                                                      const int32_t* __restrict__ seq_lens, float* __restrict__ kbar,
-                                                      float* __restrict__ vbar) {
-  __shared__ float red[64][16][8];
-  const int bg = blockIdx.x, b = bg / s.Hkv, g = bg % s.Hkv, tid = threadIdx.x;
-  const int slot = tid >> 4, j = tid & 15;
-  int n = seq_lens[b];
-  n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
-  using Rows = RowMap<kPaged>;
-  const int64_t base = Rows::base(b, g, stride_b, stride_h) + 8 * j;
-  for (int which = 0; which < 2; ++which) {
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int r = s.n_sink + slot; r < n; r += 64) {
-      float x[8];
-      const int64_t off = base + Rows::offset(pg, Rows::phys(pg, b, r), stride_b, stride_n);
-      if (which == 0)
-        load8(K + off, x);
-      else
-        load8(V + off, x);
-#pragma unroll
-      for (int c = 0; c < 8; ++c) acc[c] += x[c];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < 8; ++c) red[slot][j][c] = acc[c];
-    __syncthreads();
-    if (tid < kD) {
-      double t = 0.0;
-      for (int sl = 0; sl < 64; ++sl) t += (double)red[sl][tid >> 3][tid & 7];
-      const int cnt = n - s.n_sink;
-      (which == 0 ? kbar : vbar)[(int64_t)bg * kD + tid] = cnt > 0 ? (float)(t / (double)cnt) : 0.f;
-    }
-  }
-}
-
-// sigma2_hat[b, h] = (variance over rows [n_sink, n_b) of score[bh, i]) / |q[b, h]|^2.  grid B*Hq.
-__global__ __launch_bounds__(1024) void k_prior_variance(Shape s, const float* __restrict__ q,
-                                                         const int32_t* __restrict__ seq_lens,
-                                                         const float* __restrict__ score, int64_t score_stride,
-                                                         float* __restrict__ sigma2_hat) {
-  __shared__ double red[16];
-  const int bh = blockIdx.x, b = bh / s.Hq, tid = threadIdx.x;
-  int n = seq_lens[b];
-  n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
-  const float* sc = score + (int64_t)bh * score_stride;
-  const int cnt = n - s.n_sink;
-  double sum = 0.0;
-  for (int i = s.n_sink + tid; i < n; i += 1024) sum += (double)sc[i];
-  sum = block_sum(sum, red, tid);
-  const double mean = cnt > 0 ? sum / (double)cnt : 0.0;
-  double ss = 0.0;
-  for (int i = s.n_sink + tid; i < n; i += 1024) {
-    const double d = (double)sc[i] - mean;
-    ss += d * d;
-  }
-  ss = block_sum(ss, red, tid);
-  double qq = 0.0;
-  for (int c = tid; c < kD; c += 1024) qq += (double)q[(int64_t)bh * kD + c] * (double)q[(int64_t)bh * kD + c];
-  qq = block_sum(qq, red, tid);
-  if (tid == 0) sigma2_hat[bh] = (cnt > 0 && qq > 0.0) ? (float)(ss / (double)cnt / qq) : 0.f;
-}
-
 // ----------------------------------------------------------------------------- launchers
 hipError_t launch_table_flags(const Shape& s, const float* tab_ver, const float* tab_sla, const double* state,
                               const int32_t* seq_lens, uint32_t* f0, uint32_t* fm, int flag_words, double a,
@@ -715,12 +591,6 @@ hipError_t launch_table_init(const Shape& s, float* tab_ver, float* tab_sla, con
   return hipGetLastError();
 }
 
-hipError_t launch_table_finish(const Shape& s, const float* tab_ver, const float* tab_sla, double* state,
-                               const int32_t* seq_lens, hipStream_t st) {
-  hipLaunchKernelGGL(k_table_finish, dim3(s.B * s.Hq), dim3(kTabThreads), 0, st, s, tab_ver, tab_sla, state, seq_lens);
-  return hipGetLastError();
-}
-
 hipError_t launch_head_sparsity(const Shape& s, int dtype, const float* q, const KvView& kv, const float* kbar,
                                 const float* sigma2_hat, int n_local, float eps, float* rho, int32_t* gate,
                                 const float* vbar, int32_t* topk_idx, float* topk_score, float* out, float* thr_state,
@@ -744,42 +614,6 @@ hipError_t launch_head_sparsity(const Shape& s, int dtype, const float* q, const
     else LFPS_LAUNCH_HSP(float, false);
   }
 #undef LFPS_LAUNCH_HSP
-  return hipGetLastError();
-}
-
-hipError_t launch_prior_means(const Shape& s, int dtype, const KvView& kv, float* kbar, float* vbar, hipStream_t st) {
-#define LFPS_LAUNCH_PM(KTYPE, TYPE, PAGED)                                                                        \
-  hipLaunchKernelGGL((k_prior_means<KTYPE, TYPE, PAGED>), dim3(s.B * s.Hkv), dim3(1024), 0, st, s,                  \
-                     (const KTYPE*)kv.k, (const TYPE*)kv.v, kv.stride_b, kv.stride_h, kv.stride_n, kv.page,         \
-                     kv.seq_lens, kbar, vbar)
-  const bool paged = kv.page.table != nullptr;
-  if (dtype == LFPS_BF16 && kv.k_fp8 && kv.v_fp8) {
-    if (paged) LFPS_LAUNCH_PM(uint8_t, uint8_t, true);
-    else LFPS_LAUNCH_PM(uint8_t, uint8_t, false);
-  } else if (dtype == LFPS_BF16 && kv.k_fp8) {
-    if (paged) LFPS_LAUNCH_PM(uint8_t, uint16_t, true);
-    else LFPS_LAUNCH_PM(uint8_t, uint16_t, false);
-  } else if (dtype == LFPS_BF16 && kv.v_fp8) {
-    if (paged) LFPS_LAUNCH_PM(uint16_t, uint8_t, true);
-    else LFPS_LAUNCH_PM(uint16_t, uint8_t, false);
-  } else if (dtype == LFPS_BF16) {
-    if (paged) LFPS_LAUNCH_PM(uint16_t, uint16_t, true);
-    else LFPS_LAUNCH_PM(uint16_t, uint16_t, false);
-  } else if (dtype == LFPS_F16) {
-    if (paged) LFPS_LAUNCH_PM(_Float16, _Float16, true);
-    else LFPS_LAUNCH_PM(_Float16, _Float16, false);
-  } else {
-    if (paged) LFPS_LAUNCH_PM(float, float, true);
-    else LFPS_LAUNCH_PM(float, float, false);
-  }
-#undef LFPS_LAUNCH_PM
-  return hipGetLastError();
-}
-
-hipError_t launch_prior_variance(const Shape& s, const float* q, const int32_t* seq_lens, const float* score,
-                                 int64_t score_stride, float* sigma2_hat, hipStream_t st) {
-  hipLaunchKernelGGL(k_prior_variance, dim3(s.B * s.Hq), dim3(1024), 0, st, s, q, seq_lens, score, score_stride,
-                     sigma2_hat);
   return hipGetLastError();
 }
 

@@ -1,0 +1,102 @@
+"""The prefill hand-over (Eq. 4 from many queries, the priors) at the edges of its kernels' tiles, against the oracle.
+
+Table entries are sums of up to s fp32 weights, each with a relative error of a few 2^-24 (exponential, normalisation,
+rounding): rtol 2e-5 as in test_gpu_tables.  Means are fp32 roundings of sums of fp32 partial sums of at most a few
+hundred unit-variance rows: atol 2e-6; the variance is relative to its own size: rel 2e-5."""
+import numpy as np
+import pytest
+import torch
+
+import gen
+from gen import device as gen_device
+from oracle import lfps_oracle as orc
+from oracle import lfps_tables_oracle as tor
+from tests.harness import DEV, DeviceCase, dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _view(ctx, dc, seq, page):
+    if not page:
+        return ctx.kv_view(dc.K, dc.V, seq)
+    Kp, Vp, table = gen_device.paginate(dc.K, dc.V, page, seed=3)
+    return ctx.paged_kv_view(Kp, Vp, table, seq)
+
+
+def _case(name, L, heads, fmt, B=2):
+    kw = {"fp8": dict(k_dtype="fp8"), "fp8kv": dict(k_dtype="fp8", v_dtype="fp8")}.get(fmt, dict(kv_dtype=fmt))
+    return DeviceCase(gen.tiny_spec(name, B=B, L=L, k=min(16, L), Hq=heads[0], Hkv=heads[1], n_hot=0 if L < 200 else 4,
+                                    recency=min(16, L // 2), **kw))
+
+
+# lengths around the 128-row tiles and the 1024 rows of a workgroup, shorter than the history and than the sinks;
+# histories around the batch of 32 queries
+@pytest.mark.parametrize("L,s,heads,fmt,page", [
+    (127, 32, (8, 2), "bf16", 0), (128, 33, (8, 2), "bf16", 16), (129, 31, (8, 2), "fp8", 0), (1025, 5, (8, 2), "f16", 0),
+    (1024, 65, (4, 2), "bf16", 0), (2111, 32, (4, 2), "fp8", 64), (385, 64, (2, 2), "f16", 16), (20, 32, (8, 2), "bf16", 0),
+    (5, 3, (2, 2), "bf16", 0), (700, 32, (8, 2), "f32", 0)])
+def test_tables_from_many_queries(L, s, heads, fmt, page):
+    dc = _case("hist", L, heads, fmt)
+    spec, case = dc.spec, dc.case
+    n_sink, gamma = 4, 0.95
+    ctx = dc.make_ctx(table_mode=True, table_decay=gamma, n_sink=n_sink)
+    rng = np.random.default_rng(7)
+    q = rng.standard_normal((s, spec.B, spec.Hq, spec.D)).astype(np.float32) * np.float32(1.5)
+    # tables that held a longer sequence before: nothing of it may be left
+    ctx.lfps_tables_init(dev(q[:2]), _view(ctx, dc, dc.seq_lens(spec.T), page))
+    ctx.lfps_tables_init(dev(q), _view(ctx, dc, dc.seq_lens(0), page))
+    ev = torch.zeros((spec.B, spec.Hq, case.Lcap), dtype=torch.float64, device=DEV)
+    es = torch.zeros_like(ev)
+    ctx.lfps_tables_export(ev, es, dc.seq_lens(spec.T))
+    ev, es = ev.cpu().numpy(), es.cpu().numpy()
+    G = spec.G
+    for b, h in ((0, 0), (1, spec.Hq - 1), (1, G - 1)):
+        K, _ = dc.group(b, h // G)
+        n = int(case.seq_lens0[b])
+        w = np.zeros((s, n))
+        for j in range(1, s + 1):
+            seen = n - j + 1
+            if seen > n_sink:
+                sc = orc.scores(q[j - 1, b, h], K[:seen])[n_sink:]
+                e = np.exp(sc - sc.max())
+                w[j - 1, n_sink:seen] = e / e.sum()
+        ver, sla = tor.init_tables(w, gamma, n_sink)
+        np.testing.assert_allclose(ev[b, h, :n], ver, rtol=2e-5, atol=1e-12)
+        np.testing.assert_allclose(es[b, h, :n], sla, rtol=2e-5, atol=1e-12)
+        assert not ev[b, h, n:].any() and not es[b, h, n:].any()
+    # the statistics: candidates from them
+    cand = torch.zeros((spec.B, spec.Hkv, ctx.cand_cap), dtype=torch.int32, device=DEV)
+    cnt = torch.zeros((spec.B, spec.Hkv), dtype=torch.int32, device=DEV)
+    ctx.lfps_table_candidates(dc.seq_lens(0), cand, cnt)
+    n = int(case.seq_lens0[0])
+    t64 = [(ev[0, h, :n], es[0, h, :n]) for h in range(G)]
+    want = tor.group_candidates(t64, n, float(np.float32(0.2)), spec.r, 1, n_sink)
+    got = cand[0, 0, : int(cnt[0, 0])].cpu().numpy()
+    assert len(np.setxor1d(got, want)) <= n // 500        # entries within a rounding of a threshold
+    ctx.close()
+
+
+@pytest.mark.parametrize("L,heads,fmt,page,n_sink", [
+    (255, (8, 2), "bf16", 0, 4), (257, (4, 2), "fp8kv", 16, 0), (1030, (2, 2), "fp8", 0, 4), (777, (8, 2), "f16", 64, 4),
+    (513, (8, 2), "f32", 0, 1), (17, (8, 2), "bf16", 0, 4), (3, (8, 2), "bf16", 0, 4)])
+def test_priors_at_split_edges(L, heads, fmt, page, n_sink):
+    dc = _case("priors", L, heads, fmt)
+    spec, case = dc.spec, dc.case
+    ctx = dc.make_ctx(n_sink=n_sink)
+    kbar = torch.full((spec.B, spec.Hkv, spec.D), 9.0, device=DEV)
+    vbar = torch.full_like(kbar, 9.0)
+    s2 = torch.full((spec.B, spec.Hq), 9.0, device=DEV)
+    ctx.lfps_priors(dc.q(0), _view(ctx, dc, dc.seq_lens(0), page), kbar, vbar, s2)
+    for b in range(spec.B):
+        n = int(case.seq_lens0[b])
+        for g in range(spec.Hkv):
+            K, V = dc.group(b, g)
+            for h in range(spec.G):
+                if n <= n_sink:
+                    ok, ov, os2 = np.zeros(spec.D), np.zeros(spec.D), 0.0
+                else:
+                    ok, ov, os2 = tor.priors(case.q[0, b, spec.G * g + h], K, V, n, n_sink)
+                np.testing.assert_allclose(kbar[b, g].cpu().numpy(), ok, rtol=0, atol=2e-6)
+                np.testing.assert_allclose(vbar[b, g].cpu().numpy(), ov, rtol=0, atol=2e-6)
+                assert float(s2[b, spec.G * g + h]) == pytest.approx(os2, rel=2e-5, abs=1e-9)
+    ctx.close()
