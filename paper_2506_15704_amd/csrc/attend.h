@@ -156,4 +156,70 @@ __device__ __forceinline__ void attend_rows(AttendShared& sm, const T* __restric
   }
 }
 
+// The same sum over the first ksel entries of a list in LDS (physical row, weight relative to the largest score), which
+// the caller has filled up to a multiple of 64 with entries of weight 0, for a head of budget kb: the chunks, the
+// order of the additions and therefore the bits are those of attend_rows.  A wave issues the rows of a whole 64-entry
+// tile (16 loads per lane; 8 for fp32 rows, which take twice the registers) before it uses the first.
+template <typename T, int NW, bool kPaged, typename Entry>
+__device__ __forceinline__ void attend_list(AttendShared& sm, const T* __restrict__ Vbg, const KvPage& pg,
+                                            int64_t stride_b, int64_t stride_n, int kb, int ksel,
+                                            const Entry* list, float* __restrict__ out_row) {
+  constexpr int kPerWave = kAttendChunks / NW;
+  constexpr int kBatch = sizeof(T) == 4 ? 8 : 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int j = lane & 15, rs = lane >> 4;
+  const int chunk = (((kb + kAttendChunks - 1) / kAttendChunks) + 63) & ~63;
+  const T* Vj = Vbg + 8 * j;
+  auto offset = [&](int row) { return RowMap<kPaged>::offset(pg, row, stride_b, stride_n); };
+#pragma unroll 1
+  for (int cc = 0; cc < kPerWave; ++cc) {
+    const int ck = wave * kPerWave + cc;
+    const int c0 = ck * chunk, c1 = c0 + chunk < ksel ? c0 + chunk : ksel;
+    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float l = 0.f;
+    for (int base = c0; base < c1; base += 64) {
+      l += list[base + lane].p;
+#pragma unroll
+      for (int part = 0; part < 16 / kBatch; ++part) {
+        Raw8<T> rw[kBatch];
+        const Entry* e = list + base + 4 * kBatch * part + rs;
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) rw[u].load(Vj + offset(e[4 * u].row));
+        __builtin_amdgcn_sched_barrier(0);                    // keep the batch's loads ahead of its arithmetic
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          const float p = e[4 * u].p;
+          float x[8];
+          rw[u].get(x);
+#pragma unroll
+          for (int c = 0; c < 8; ++c) acc[c] = fmaf(p, x[c], acc[c]);
+        }
+      }
+    }
+    // the chunk's partial sums (zeros for a chunk past the end of the list)
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) l += __shfl_xor(l, d);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      acc[c] += __shfl_xor(acc[c], 16);
+      acc[c] += __shfl_xor(acc[c], 32);
+    }
+    if (rs == 0) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) sm.red[ck][8 * j + c] = acc[c];
+    }
+    if (lane == 0) sm.redl[ck] = l;
+  }
+  __syncthreads();
+  if (tid < kD) {
+    float a = 0.f, ls = 0.f;
+#pragma unroll
+    for (int w = 0; w < kAttendChunks; ++w) {
+      a += sm.red[w][tid];
+      ls += sm.redl[w];
+    }
+    out_row[tid] = ls > 0.f ? a / ls : 0.f;
+  }
+}
+
 }  // namespace lfps

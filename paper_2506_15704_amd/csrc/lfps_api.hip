@@ -375,7 +375,7 @@ int lfps_create(const lfps_config* cfg, lfps_ctx** out) {
     e = hipMemset(c->tab_ver, 0, (size_t)(z.tver_b + z.tsla_b + z.tstate_b + 2 * z.tflag_b));
   if (e == hipSuccess) e = hipMemset(c->gate, 0, (size_t)z.thr_b);
   if (e == hipSuccess) e = configure_candidates(s);
-  if (e == hipSuccess) e = configure_select(s);
+  if (e == hipSuccess) e = configure_select(s, cfg->kv_dtype, cfg->k_fp8 != 0, cfg->v_fp8 != 0);
   if (e == hipSuccess && cfg->table_mode && cfg->kv_dtype != LFPS_F32) e = configure_table_history(s, key_kind(*cfg));
   // the launch size of the filtered pass is needed whenever that pass can be switched on (lfps_set_filter)
   if (e == hipSuccess && c->slot)
@@ -486,8 +486,8 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SELECT_ATTEND, st,
            launch_filter_select_attend(s, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
                                        ctx->flags + 1, ctx->nseg, ctx->cand, ctx->cand_count, ctx->group_start,
-                                       line_total, k, topk_idx, sel, ctx->thr_state, skip_if, ctx->flags + 2, q,
-                                       ctx->flags, v, out, st));
+                                       line_total, k, topk_idx, sel, ctx->thr_state, kFilterMargin, skip_if,
+                                       ctx->flags + 2, q, ctx->flags, v, out, st));
     return LFPS_OK;
   }
   LAUNCH(ctx, LFPS_KERNEL_GATHER_SCORE, st,
@@ -649,8 +649,8 @@ int lfps_exact_topk(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int3
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SELECT_ATTEND, st,
            launch_filter_select_attend(sd, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
                                        ctx->flags + 1, ctx->nseg, nullptr, ctx->x_cnt, ctx->x_start, x_total, k, topk_idx,
-                                       topk_score ? topk_score : ctx->sel_score, ctx->thr_x, nullptr, nullptr, q,
-                                       ctx->flags, v, nullptr, st));
+                                       topk_score ? topk_score : ctx->sel_score, ctx->thr_x, 0.f, nullptr, nullptr,
+                                       q, ctx->flags, v, nullptr, st));
     return LFPS_OK;
   }
   LAUNCH(ctx, LFPS_KERNEL_DENSE_SCORE, st,

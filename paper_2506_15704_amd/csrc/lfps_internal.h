@@ -72,7 +72,7 @@ struct Shape {
 
 // ---- kernel launchers (each enqueues on `st` and returns the launch error) -------------
 hipError_t configure_candidates(const Shape& s);
-hipError_t configure_select(const Shape& s);
+hipError_t configure_select(const Shape& s, int dtype, bool k_fp8, bool v_fp8);
 // group_start [B,Hkv] / line_total [1] (or NULL): every group adds its candidate count to *line_total
 // (zero on entry) and keeps the value before the addition as its place on the line of all candidate slots.
 hipError_t launch_candidates(const Shape& s, const int32_t* prev_topk, const int32_t* k, const int32_t* seq_lens,
@@ -106,13 +106,13 @@ hipError_t launch_filter_score(const Shape& s, const float* q, const KvView& kv,
 // pass: every head gets its Top-k rows (topk_idx, topk_score: both required) and its output row; a head whose list
 // is short or overfull takes the unfiltered pass inside the kernel (counted in *rescored), which needs q, the K rows
 // and the group's candidate list (cand; NULL = all rows 0 .. cand_count-1) and overwrites the head's score row.
-hipError_t configure_select_attend(const Shape& s);
+hipError_t configure_select_attend(const Shape& s, int dtype, bool k_fp8, bool v_fp8);
 hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, const int32_t* slot_in,
                                        int64_t score_stride, const int32_t* seg_count, const int32_t* seg_rows, int nseg,
                                        const int32_t* cand, const int32_t* cand_count, const int64_t* group_start,
                                        int64_t* line_total, const int32_t* k, int32_t* topk_idx, float* topk_score,
-                                       float* thr_state, const int32_t* skip_if, int32_t* rescored, const float* q,
-                                       int32_t* flags, const KvView& kv, float* out,
+                                       float* thr_state, float margin, const int32_t* skip_if, int32_t* rescored,
+                                       const float* q, int32_t* flags, const KvView& kv, float* out,
                                        hipStream_t st);   // out == NULL: select only
 
 // Exact Top-k baseline, set-up of its filtered dense pass (exact_topk.hip): every group's rows 0..n_b-1 laid on the

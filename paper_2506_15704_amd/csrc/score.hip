@@ -51,14 +51,14 @@ __global__ __launch_bounds__(kScoreThreads) void k_group_score_bf16(Shape s, con
 
   using Op = typename KTile<kKind>::Operand;
   Op A[4];
-  report_q_range(load_query_operand<G>(A, q, (int64_t)b * s.Hq + (int64_t)g * G, j, kb), flags);
+  report_q_range(load_query_operand(A, q, (int64_t)b * s.Hq + (int64_t)g * G, G, j, kb), flags);
 
   using Rows = RowMap<kPaged>;
   constexpr int ES = KTile<kKind>::kElemBytes;
   const char* Kbg = static_cast<const char*>(K) + Rows::base(b, g, stride_b, stride_h) * ES;
   const int32_t* cbg = GATHER ? cand + (int64_t)bg * s.cand_cap : nullptr;
   float* sc = score + ((int64_t)b * s.Hq + (int64_t)g * G + kb) * score_stride;   // lane group kb -> head kb
-  score_slots_mfma<G, kPaged, kKind>(A, Kbg, pg, b, stride_b, stride_n, cbg, n, count, first,
+  score_slots_mfma<kPaged, kKind>(A, Kbg, pg, b, stride_b, stride_n, cbg, n, count, first,
                                      (int)gridDim.x * 4 * kRowsPerWaveIter, sc, kb < G, scale);
 }
 
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
       int ids_b = fetch_ids(seg_lo + T);                  // ids of the next odd tile
       int ids_a = fetch_ids(seg_lo + 2 * T);              // ids of the next even tile
       issue(Bt0, rows0, ids_0, 0);
-      report_q_range(load_query_operand<G>(A, q, (int64_t)b * s.Hq + (int64_t)g * G, j, kb), flags);   // overlaps the first tile's latency
+      report_q_range(load_query_operand(A, q, (int64_t)b * s.Hq + (int64_t)g * G, G, j, kb), flags);   // overlaps the first tile's latency
       for (; base_slot + 2 * T < seg_hi; base_slot += 2 * T) {   // at least three tiles left: no conditions inside
         issue(Bt1, rows1, ids_b, 0);
         ids_b = fetch_ids(base_slot + 3 * T);
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
       ids_0 = fetch_ids(seg_lo + 2 * T);
       __builtin_amdgcn_sched_barrier(0);
       fire(Bt0);
-      report_q_range(load_query_operand<G>(A, q, (int64_t)b * s.Hq + (int64_t)g * G, j, kb), flags);
+      report_q_range(load_query_operand(A, q, (int64_t)b * s.Hq + (int64_t)g * G, G, j, kb), flags);
       // here and at the top of every iteration: (ids_1, phys_1) describe the next odd tile, ids_0 the next even one
       for (; base_slot + 2 * T < seg_hi; base_slot += 2 * T) {
         aim(rows1, ids_1, phys_1);

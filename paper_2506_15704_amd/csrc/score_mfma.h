@@ -70,8 +70,8 @@ __device__ __forceinline__ f32x4 mfma16(f16x8 a, f16x8 b, f32x4 c) {
 // loads issued together; a lane-dependent branch here would serialise 32 single loads.
 // Returns true if this lane met a query element beyond the fp16 range (fp16 operands only): the element is
 // clamped to +-65504 so that the scores stay finite, and the caller raises LFPS_FLAG_Q_RANGE.
-template <int G, typename Op>
-__device__ __forceinline__ bool load_query_operand(Op (&A)[4], const float* __restrict__ q, int64_t head0, int j,
+template <typename Op>
+__device__ __forceinline__ bool load_query_operand(Op (&A)[4], const float* __restrict__ q, int64_t head0, int G, int j,
                                                    int kb) {
   const int h = j >> 2, t = j & 3;
   const float4* qh = reinterpret_cast<const float4*>(q + (head0 + (h < G ? h : 0)) * kD);
@@ -173,7 +173,7 @@ struct KTile {
 // position.  A slot whose position lies outside [0, n) reads row 0 and scores -inf: it ranks below every row.
 // The row ids of the next visit are fetched, and the scores of the previous visit stored, right after this visit's
 // loads are issued.  sc: the score row of head kb (ignored by lanes with store == false).
-template <int G, bool kPaged, int kKind>
+template <bool kPaged, int kKind>
 __device__ __forceinline__ void score_slots_mfma(const typename KTile<kKind>::Operand (&A)[4], const char* Kbg,
                                                  const KvPage& pg, int b, int64_t stride_b, int64_t stride_n,
                                                  const int32_t* __restrict__ cbg, int n, int count, int first, int step,

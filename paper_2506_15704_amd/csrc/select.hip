@@ -18,8 +18,8 @@
 //     prefix counts when streaming; no atomics): every row above the k-th value plus as many rows
 //     equal to it as still needed, lowest position first.  The output is ascending in position
 //     and identical from run to run.
-// select_attend.hip applies the same steps to the short (score, position) lists that the filtered scoring
-// pass leaves per head, and runs the attention over the selected rows in the same kernel.
+// select_attend.hip applies the same idea to the short (score, position) lists that the filtered scoring pass leaves per
+// head, with the elements in registers (select_regs.h), and runs the attention over the selected rows in the same kernel.
 #include "select_body.h"
 
 namespace lfps {
@@ -76,22 +76,11 @@ static int select_cache_elems(const Shape& s, bool gather) {
   return (e + 63) & ~63;
 }
 
-int filter_list_cap(const Shape& s) {
-  int cap = 4 * s.kmax;
-  if (cap < 1024) cap = 1024;
-  if (cap > 7680) {             // 60 KB of LDS: two workgroups per CU ...
-    cap = 7680;
-    // ... unless the budget itself needs more room: twice the budget, up to 128 KB (one workgroup per CU)
-    if (2 * s.kmax > cap) cap = 2 * s.kmax < 16384 ? 2 * s.kmax : 16384;
-  }
-  return cap;
-}
-
 // Called once per context at creation: the score cache needs more dynamic LDS than the default limit.
-hipError_t configure_select(const Shape& s) {
+hipError_t configure_select(const Shape& s, int dtype, bool k_fp8, bool v_fp8) {
   hipError_t e = hipFuncSetAttribute((const void*)k_select, hipFuncAttributeMaxDynamicSharedMemorySize, kCacheElems * 4);
   if (e != hipSuccess) return e;
-  return configure_select_attend(s);
+  return configure_select_attend(s, dtype, k_fp8, v_fp8);
 }
 
 hipError_t launch_select(const Shape& s, const float* score, int64_t score_stride, const int32_t* cand,

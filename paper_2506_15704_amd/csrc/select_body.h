@@ -9,7 +9,6 @@
 namespace lfps {
 
 constexpr int kSelThreads = 1024;       // workgroup of the general kernel
-constexpr int kFilterSelThreads = 512;  // workgroup of the kernel that selects from the short survivor lists
 constexpr int kCacheElems = 32768;      // scores of one head kept in LDS (dynamic, 128 KB)
 
 // NT threads: 2*NT histogram bins (two per thread), up to NT members of the threshold bin ranked directly.
@@ -42,16 +41,14 @@ __device__ __forceinline__ void find_bin(SelectShared<NT>& sm, uint32_t need, in
   constexpr int kSelWaves = NT / 64;
   const uint32_t lo = sm.hist[2 * tid], hi = sm.hist[2 * tid + 1];
   const uint32_t mine = lo + hi;
-  uint32_t inc = mine;                       // inclusive suffix sum within the wave
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    uint32_t o = __shfl_down(inc, d);
-    if (lane + d < 64) inc += o;
-  }
-  if (lane == 0) sm.wsum[wv] = inc;
+  const uint32_t upto = (uint32_t)wave_inclusive_sum((int)mine);       // bins of lanes 0 .. lane
+  const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+  const uint32_t inc = all - upto + mine;    // inclusive suffix sum within the wave
+  if (lane == 0) sm.wsum[wv] = all;
   __syncthreads();
   uint32_t above_waves = 0;
-  for (int w = wv + 1; w < kSelWaves; ++w) above_waves += sm.wsum[w];
+#pragma unroll
+  for (int w = 0; w < kSelWaves; ++w) above_waves += w > wv ? sm.wsum[w] : 0u;
   const uint32_t suffix_incl = above_waves + inc;    // count in bins >= 2t
   const uint32_t suffix_excl = suffix_incl - mine;   // count in bins >  2t+1
   if (suffix_incl >= need && suffix_excl < need) {   // exactly one thread

@@ -1,0 +1,165 @@
+// The select for heads whose scored rows fit the registers of one workgroup (up to kRegElems per thread): every element
+// is read once and stays in a register through all passes, so a pass costs no memory traffic and the select is a short
+// chain of LDS round trips (select_body.h keeps the rows in LDS or streams them, for longer lists).
+#pragma once
+#include "select_body.h"
+
+namespace lfps {
+
+constexpr int kRegElems = 16;
+
+// A selected row as the attention reads it: physical row and softmax numerator (a row to skip: row 0, weight 0).
+struct SelRow {
+  int32_t row;
+  float p;
+};
+
+// Histogram bin of score x for a lower bound lo of all scores: 64 bins per octave of x - lo + 1/16, so bins are 1/1024
+// wide at the bound and grow with the distance.  Survivors of a threshold pile up just above it, where the k-th best
+// lies; scores far above share wide bins.  Monotone in x, whatever x and lo are.
+__device__ __forceinline__ int tail_bin(float x, float lo, int bins) {
+  const float t = fmaxf(x - lo, 0.f) + 0.0625f;
+  const int b = (int)((__float_as_uint(t) - 0x3D800000u) >> 17);
+  return b < bins ? b : bins - 1;
+}
+
+// The ksel best of the workgroup's n elements (1 <= ksel <= n): thread t holds the elements u*NT + t (score v[u],
+// sanitised), which ascend in position over u and then t: a wave's loads, and its stores of selected elements, touch
+// consecutive entries.  lo: a lower bound of all scores, or (from_min) ignored and
+// replaced by their minimum.  All threads call, after a barrier behind sm.hist = 0 and sm.list_n = 0.  Calls
+// out(rank, u, top) for every selected element, rank = its place in ascending position, top = the largest score; equal
+// scores at the cut go to the lower position.  *thr_out receives the ksel-th best score.
+template <int NT, int E, typename Out>
+__device__ __forceinline__ void select_registers(SelectShared<NT>& sm, const float (&v)[E], int n, int ksel, float lo,
+                                                 bool from_min, float* __restrict__ thr_out, Out out) {
+  constexpr int kWaves = NT / 64, kBins = 2 * NT, kListCap = NT;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  auto mine = [&](int u) { return u * NT + tid < n; };
+  float hi = -FLT_MAX, mn = FLT_MAX;
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    hi = mine(u) ? fmaxf(hi, v[u]) : hi;
+    mn = mine(u) ? fminf(mn, v[u]) : mn;
+  }
+  hi = row16_max(hi);
+  hi = fmaxf(hi, __shfl_xor(hi, 16));
+  hi = fmaxf(hi, __shfl_xor(hi, 32));
+  if (lane == 0) sm.whi[wv] = hi;
+  if (from_min) {
+    mn = -row16_max(-mn);
+    mn = fminf(mn, __shfl_xor(mn, 16));
+    mn = fminf(mn, __shfl_xor(mn, 32));
+    if (lane == 0) sm.wlo[wv] = mn;
+    __syncthreads();
+    lo = sm.wlo[0];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) lo = fminf(lo, sm.wlo[w]);
+  }
+  // (bins are computed where they are needed: held for all elements they would cost E registers)
+#pragma unroll
+  for (int u = 0; u < E; ++u)
+    if (mine(u)) atomicAdd(&sm.hist[tail_bin(v[u], lo, kBins)], 1u);
+  __syncthreads();
+  float top = sm.whi[0];
+#pragma unroll
+  for (int w = 1; w < kWaves; ++w) top = fmaxf(top, sm.whi[w]);
+  find_bin(sm, (uint32_t)ksel, tid, lane, wv);
+  const int tb = (int)sm.bin;
+  uint32_t need = sm.need;                                 // elements still to take from bin tb (>= 1)
+  const uint32_t m = sm.hist[tb];
+  uint32_t thr_key, need_eq;
+  if (m <= (uint32_t)kListCap) {
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+      const bool hit = mine(u) && tail_bin(v[u], lo, kBins) == tb;
+      const uint64_t mh = __ballot(hit);
+      if (mh) {
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&sm.list_n, (uint32_t)__popcll(mh));
+        at = (uint32_t)__builtin_amdgcn_readlane((int)at, 0);
+        if (hit) sm.list[at + lanes_below(mh)] = f2key(v[u]);
+      }
+    }
+    __syncthreads();
+    // few members (the usual case): every wave ranks them by itself and no further barrier is needed
+    const bool few = m <= 64u;
+    const uint32_t cand = few ? (uint32_t)lane : (uint32_t)tid;
+    const uint32_t key = cand < m ? sm.list[cand] : 0u;
+    uint32_t gt = 0, ge = 0;
+    for (uint32_t i = 0; i < m; ++i) {
+      const uint32_t o = sm.list[i];
+      gt += o > key;
+      ge += o >= key;
+    }
+    const bool is_thr = cand < m && gt < need && need <= ge;       // (equal keys agree)
+    if (few) {
+      const int src = __builtin_ctzll(__ballot(is_thr));
+      thr_key = (uint32_t)__builtin_amdgcn_readlane((int)key, src);
+      need_eq = need - (uint32_t)__builtin_amdgcn_readlane((int)gt, src);
+    } else {
+      if (is_thr) {
+        sm.thr = key;
+        sm.need_eq = need - gt;
+      }
+      __syncthreads();
+      thr_key = sm.thr;
+      need_eq = sm.need_eq;
+    }
+  } else {                                                 // a crowded bin: radix descent over the members' keys
+    uint32_t prefix = 0, mask = 0;
+#pragma unroll 1
+    for (int pass = 0; pass < 4; ++pass) {
+      const int shift = pass < 3 ? 32 - 9 * (pass + 1) : 0;
+      const uint32_t dmask = pass < 3 ? 511u : 31u;
+      __syncthreads();
+      for (int i = tid; i < kBins; i += NT) sm.hist[i] = 0u;
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < E; ++u) {
+        const uint32_t key = f2key(v[u]);
+        if (mine(u) && tail_bin(v[u], lo, kBins) == tb && ((key ^ prefix) & mask) == 0u)
+          atomicAdd(&sm.hist[(key >> shift) & dmask], 1u);
+      }
+      __syncthreads();
+      find_bin(sm, need, tid, lane, wv);
+      prefix |= sm.bin << shift;
+      need = sm.need;
+      mask |= dmask << shift;
+    }
+    thr_key = prefix;
+    need_eq = need;
+  }
+  const float thr = key2f(thr_key);
+  if (thr_out && tid == 0) *thr_out = thr;
+  // ordered compaction: everything above the threshold, and the first need_eq elements equal to it.  Per 64 elements
+  // (u, wave) the counts go to LDS (elements > thr) << 16 | (elements == thr); every wave scans all of them.
+  uint32_t* counts = sm.hist;                              // (not read any more)
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const uint32_t gt = __popcll(__ballot(mine(u) && v[u] > thr)), eq = __popcll(__ballot(mine(u) && v[u] == thr));
+    if (lane == 0) counts[u * kWaves + wv] = gt << 16 | eq;
+  }
+  __syncthreads();
+  constexpr int kRows = (E * kWaves + 63) / 64;
+  uint32_t before[kRows];                                  // exclusive prefix of entry 64 i + lane
+  uint32_t carry = 0;
+#pragma unroll
+  for (int i = 0; i < kRows; ++i) {
+    const uint32_t x = 64 * i + lane < E * kWaves ? counts[64 * i + lane] : 0u;
+    const uint32_t inc = (uint32_t)wave_inclusive_sum((int)x);
+    before[i] = carry + inc - x;
+    carry += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+  }
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const uint64_t gt = __ballot(mine(u) && v[u] > thr), eq = __ballot(mine(u) && v[u] == thr);
+    if (!(gt | eq)) continue;
+    const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)before[u * kWaves / 64], (u * kWaves) % 64 + wv);
+    const uint32_t eq_before = (at & 0xFFFFu) + lanes_below(eq);
+    const bool take = mine(u) && (v[u] > thr || (v[u] == thr && eq_before < need_eq));
+    const uint32_t rank = (at >> 16) + lanes_below(gt) + (eq_before < need_eq ? eq_before : need_eq);
+    if (take && rank < (uint32_t)ksel) out((int)rank, u, top);
+  }
+}
+
+}  // namespace lfps
