@@ -1,8 +1,6 @@
 // S3 — per query head, the k best of the scored rows (Alg. 1 line 8 / Sec. 1 Step 2).
 //
-// One workgroup (16 waves) per (b, h); wave w owns the contiguous slice w of the head's scores.
-// When the head has at most 32768 scores they are read from global memory once and kept in LDS
-// (128 KB) for every later pass; otherwise each pass streams them again (L2).
+// One workgroup (16 waves) per (b, h).
 //
 //  1. block min/max of the scores;
 //  2. one LDS histogram of 2048 bins that are *linear in the score* between min and max.  (Bins
@@ -14,26 +12,34 @@
 //     ranked against the others; if the bin is too full for the list (degenerate inputs: all
 //     scores equal, one huge outlier) an exact most-significant-digit radix descent over the
 //     order-preserving 32-bit keys of the bin's members finds it instead;
-//  5. ordered compaction (per-thread contiguous runs of the LDS copy + one block scan; ballots and
-//     prefix counts when streaming; no atomics): every row above the k-th value plus as many rows
+//  5. ordered compaction (ballots and prefix counts; no atomics): every row above the k-th value plus as many rows
 //     equal to it as still needed, lowest position first.  The output is ascending in position
 //     and identical from run to run.
-// select_attend.hip applies the same idea to the short (score, position) lists that the filtered scoring pass leaves per
-// head, with the elements in registers (select_regs.h), and runs the attention over the selected rows in the same kernel.
-#include "select_body.h"
+//
+// Heads of up to kSelRegMax scores are read from memory once and stay in registers (select_regs.h); only when a row of
+// 16384 to 32768 scores would keep more than the list of select_long holds (budgets of about 16000 and more, crowded
+// bins) is it kept in LDS as a whole, and longer ones are streamed in each pass (L2).  32 heads x 32768 scores, k = 1024:
+// 35 us with the row in LDS, 28 us with select_registers alone (32 elements a thread), 25 us this way (exact Top-k and attention of a 32K request: 57 -> 46 us).
+// select_attend.hip applies the same to the short (score, position) lists that the filtered scoring pass leaves per
+// head, and runs the attention over the selected rows in the same kernel.
+#include "select_regs.h"
 
 namespace lfps {
+
+constexpr int kSelRegMax = 32 * kSelThreads;                // scores of a head that its workgroup's registers hold
+constexpr int kSelListMax = kRegElems * kSelThreads;       // entries of select_long's list: 128 KB
 
 __global__ __launch_bounds__(kSelThreads) void k_select(Shape s, const float* __restrict__ score,
                                                         int64_t score_stride, const int32_t* __restrict__ cand,
                                                         const int32_t* __restrict__ count_arr,
                                                         const int32_t* __restrict__ kk, int32_t* __restrict__ topk_idx,
-                                                        float* __restrict__ topk_score, int cache_elems,
-                                                        float* __restrict__ thr_state,
+                                                        float* __restrict__ topk_score, int list_cap,
+                                                        int cache_elems, float* __restrict__ thr_state,
                                                         const int32_t* __restrict__ skip_if,
                                                         const int32_t* __restrict__ seq_lens) {
-  __shared__ SelectShared<kSelThreads> sm;
-  extern __shared__ float cache[];
+  constexpr int NT = kSelThreads;
+  __shared__ SelectShared<NT> sm;
+  extern __shared__ float dyn[];                    // select_long's list, or the scores of a whole row
   const int bh = blockIdx.x, b = bh / s.Hq, h = bh % s.Hq, g = h / s.G;
   const int tid = threadIdx.x;
   if (skip_if && skip_if[bh] != 0) return;          // bypassed head: its rows were written by the gate
@@ -47,7 +53,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select(Shape s, const float* __
 
   int32_t* oi = topk_idx + (int64_t)bh * s.kmax;
   float* os = topk_score ? topk_score + (int64_t)bh * s.kmax : nullptr;
-  for (int i = ksel + tid; i < s.kmax; i += kSelThreads) {   // padding
+  for (int i = ksel + tid; i < s.kmax; i += NT) {   // padding
     oi[i] = -1;
     if (os) os[i] = 0.f;
   }
@@ -64,21 +70,54 @@ __global__ __launch_bounds__(kSelThreads) void k_select(Shape s, const float* __
     n_valid = seq_lens[b];
     n_valid = n_valid < 0 ? 0 : (n_valid > s.Lcap ? s.Lcap : n_valid);
   }
+  auto put = [&](int rank, int e, float x) {
+    const int p = cbg ? cbg[e] : e;
+    const bool ok = (uint32_t)p < (uint32_t)n_valid;
+    oi[rank] = ok ? p : -1;
+    if (os) os[rank] = ok ? x : 0.f;
+  };
+  if (c <= 8 * NT) {                                // few scores: straight to the end
+    for (int i = tid; i < 2 * NT; i += NT) sm.hist[i] = 0u;
+    if (tid == 0) sm.list_n = 0u;
+    __syncthreads();
+    auto run = [&](auto elems) {
+      constexpr int E = decltype(elems)::value;
+      float v[E];
+#pragma unroll
+      for (int u = 0; u < E; ++u) v[u] = sc[u * NT + tid < c ? u * NT + tid : c - 1];
+#pragma unroll
+      for (int u = 0; u < E; ++u) v[u] = sanitize(v[u]);
+      select_registers<NT, E>(sm, v, c, ksel, 0.f, true, thr_out,
+                              [&](int rank, int u, float) { put(rank, u * NT + tid, v[u]); });
+    };
+    if (c <= 2 * NT) run(std::integral_constant<int, 2>{});
+    else if (c <= 4 * NT) run(std::integral_constant<int, 4>{});
+    else run(std::integral_constant<int, 8>{});
+    return;
+  }
+  bool done = false;
+  float2* list = reinterpret_cast<float2*>(dyn);
+  if (c <= 16 * NT) done = select_long<NT, 16>(sm, sc, c, ksel, list, list_cap, thr_out, put);
+  else if (c <= kSelRegMax) done = select_long<NT, 32>(sm, sc, c, ksel, list, list_cap, thr_out, put);
+  if (done) return;
+  __syncthreads();
   if (c <= cache_elems)
-    select_body<true, kSelThreads>(sm, cache, sc, c, ksel, nullptr, cbg, oi, os, thr_out, FLT_MAX, -FLT_MAX, n_valid);
+    select_body<true, NT>(sm, dyn, sc, c, ksel, nullptr, cbg, oi, os, thr_out, FLT_MAX, -FLT_MAX, n_valid);
   else
     select_stream(sm, sc, c, ksel, cbg, oi, os, thr_out, n_valid);
 }
 
-static int select_cache_elems(const Shape& s, bool gather) {
+// LDS beside SelectShared: select_long's list, or the whole row where that would overflow.  (Rows of up to 8192 scores
+// need neither.)
+static void select_room(const Shape& s, bool gather, int* list_cap, int* cache_elems) {
   const int rows_max = gather ? s.cand_cap : s.Lcap;
-  const int e = rows_max < kCacheElems ? rows_max : kCacheElems;
-  return (e + 63) & ~63;
+  *cache_elems = rows_max <= 8 * kSelThreads ? 0 : (((rows_max < kCacheElems ? rows_max : kCacheElems) + 63) & ~63);
+  *list_cap = rows_max <= 8 * kSelThreads ? 0 : kSelListMax;
 }
 
-// Called once per context at creation: the score cache needs more dynamic LDS than the default limit.
+// Called once per context at creation: the kernel needs more dynamic LDS than the default limit.
 hipError_t configure_select(const Shape& s, int dtype, bool k_fp8, bool v_fp8) {
-  hipError_t e = hipFuncSetAttribute((const void*)k_select, hipFuncAttributeMaxDynamicSharedMemorySize, kCacheElems * 4);
+  hipError_t e = hipFuncSetAttribute((const void*)k_select, hipFuncAttributeMaxDynamicSharedMemorySize, kSelListMax * 8);
   if (e != hipSuccess) return e;
   return configure_select_attend(s, dtype, k_fp8, v_fp8);
 }
@@ -86,9 +125,11 @@ hipError_t configure_select(const Shape& s, int dtype, bool k_fp8, bool v_fp8) {
 hipError_t launch_select(const Shape& s, const float* score, int64_t score_stride, const int32_t* cand,
                          const int32_t* count, const int32_t* k, int32_t* topk_idx, float* topk_score,
                          float* thr_state, const int32_t* skip_if, const int32_t* seq_lens, hipStream_t st) {
-  const int ce = select_cache_elems(s, cand != nullptr);
-  hipLaunchKernelGGL(k_select, dim3(s.B * s.Hq), dim3(kSelThreads), (size_t)ce * 4, st, s, score, score_stride, cand,
-                     count, k, topk_idx, topk_score, ce, thr_state, skip_if, seq_lens);
+  int list_cap, cache_elems;
+  select_room(s, cand != nullptr, &list_cap, &cache_elems);
+  hipLaunchKernelGGL(k_select, dim3(s.B * s.Hq), dim3(kSelThreads), (size_t)(list_cap * 2 > cache_elems ? list_cap * 2 : cache_elems) * 4,
+                     st, s, score, score_stride, cand, count, k, topk_idx, topk_score, list_cap, cache_elems, thr_state,
+                     skip_if, seq_lens);
   return hipGetLastError();
 }
 

@@ -2,6 +2,8 @@
 // is read once and stays in a register through all passes, so a pass costs no memory traffic and the select is a short
 // chain of LDS round trips (select_body.h keeps the rows in LDS or streams them, for longer lists).
 #pragma once
+#include <type_traits>
+
 #include "select_body.h"
 
 namespace lfps {
@@ -160,6 +162,113 @@ __device__ __forceinline__ void select_registers(SelectShared<NT>& sm, const flo
     const uint32_t rank = (at >> 16) + lanes_below(gt) + (eq_before < need_eq ? eq_before : need_eq);
     if (take && rank < (uint32_t)ksel) out((int)rank, u, top);
   }
+}
+
+// The same for long rows.  One workgroup works on a head, so what counts is instructions per element: here about 30 (the
+// select above: about 120).  The n scores of the head (thread t: elements u*NT + t, from memory) are laid on a histogram
+// linear between the smallest and the largest (bins that follow the distance from a bound would pile the bulk of a full
+// row into a few dozen of them); what lies in the bin of the ksel-th best or above, and what reaches a little below it,
+// goes to LDS, ascending in position, as (score, element) pairs, and the select above finishes on those.  False if more
+// than cap elements would go there: nothing has been written then.
+template <int NT, int E, typename Out>
+__device__ __forceinline__ bool select_long(SelectShared<NT>& sm, const float* __restrict__ sc, int n, int ksel,
+                                            float2* list, int cap, float* __restrict__ thr_out, Out out) {
+  constexpr int kWaves = NT / 64, kBins = 2 * NT;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  n = __builtin_amdgcn_readfirstlane(n);
+  auto mine = [&](int u) { return tid < n - u * NT; };
+  float v[E];                                              // (elements past the end: -inf, below every sanitised score)
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const float* at = sc + u * NT;
+    v[u] = mine(u) ? at[tid] : -INFINITY;
+  }
+  float hi = -FLT_MAX, mn = FLT_MAX;
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const bool in = mine(u);
+    v[u] = in ? sanitize(v[u]) : -INFINITY;
+    hi = fmaxf(hi, v[u]);
+    mn = in ? fminf(mn, v[u]) : mn;
+  }
+  hi = row16_max(hi);
+  hi = fmaxf(hi, __shfl_xor(hi, 16));
+  hi = fmaxf(hi, __shfl_xor(hi, 32));
+  mn = -row16_max(-mn);
+  mn = fminf(mn, __shfl_xor(mn, 16));
+  mn = fminf(mn, __shfl_xor(mn, 32));
+  if (lane == 0) {
+    sm.whi[wv] = hi;
+    sm.wlo[wv] = mn;
+  }
+  for (int i = tid; i < kBins; i += NT) sm.hist[i] = 0u;
+  if (tid == 0) sm.list_n = 0u;
+  __syncthreads();
+  float lo = sm.wlo[0], top = sm.whi[0];
+#pragma unroll
+  for (int w = 1; w < kWaves; ++w) {
+    lo = fminf(lo, sm.wlo[w]);
+    top = fmaxf(top, sm.whi[w]);
+  }
+  const float range = top - lo;
+  const float scale = range > 0.f && range < FLT_MAX ? (float)kBins / range : 0.f;
+#pragma unroll
+  for (int u = 0; u < E; ++u)
+    if (mine(u)) atomicAdd(&sm.hist[min((uint32_t)(int)((v[u] - lo) * scale), (uint32_t)(kBins - 1))], 1u);
+  __syncthreads();
+  find_bin(sm, (uint32_t)ksel, tid, lane, wv);
+  // Every score x in the bin or above has (x - lo) * scale >= bin up to two roundings, 2.4e-4 bins: the real number
+  // lo + (bin - 0.01) / scale is below x, and so is the nearest float, x being one.
+  const float cut = scale > 0.f ? fmaxf(lo + ((float)sm.bin - 0.01f) / scale, -FLT_MAX) : -FLT_MAX;
+  auto keep = [&](int u) { return v[u] >= cut; };
+  int my_count = 0;                                        // lane u: what my wave keeps of its elements u
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const int cnt = (int)__popcll(__ballot(keep(u)));
+    my_count = lane == u ? cnt : my_count;
+  }
+  __syncthreads();                                         // everybody has read the histogram
+  if (lane < E) sm.hist[lane * kWaves + wv] = (uint32_t)my_count;
+  __syncthreads();
+  constexpr int kRows = (E * kWaves + 63) / 64;
+  int before[kRows];                                       // exclusive prefix of count 64 i + lane
+  int carry = 0;
+#pragma unroll
+  for (int i = 0; i < kRows; ++i) {
+    const int x = 64 * i + lane < E * kWaves ? (int)sm.hist[64 * i + lane] : 0;
+    const int inc = wave_inclusive_sum(x);
+    before[i] = carry + inc - x;
+    carry += __builtin_amdgcn_readlane(inc, 63);
+  }
+  const int kept = carry;
+  if (kept > cap) return false;                            // (the same for the whole workgroup)
+#pragma unroll
+  for (int u = 0; u < E; ++u) {
+    const bool k = keep(u);
+    const uint64_t m = __ballot(k);
+    const int at = __builtin_amdgcn_readlane(before[u * kWaves / 64], (u * kWaves) % 64 + wv);
+    if (k) list[at + lanes_below(m)] = make_float2(v[u], __int_as_float(u * NT + tid));
+  }
+  __syncthreads();
+  for (int i = tid; i < kBins; i += NT) sm.hist[i] = 0u;
+  __syncthreads();
+  auto finish = [&](auto elems) {
+    constexpr int E2 = decltype(elems)::value;
+    float w[E2];
+    int at[E2];
+#pragma unroll
+    for (int u = 0; u < E2; ++u) {
+      const int e = u * NT + tid < kept ? u * NT + tid : kept - 1;
+      w[u] = list[e].x;
+      at[u] = __float_as_int(list[e].y);
+    }
+    select_registers<NT, E2>(sm, w, kept, ksel, cut, false, thr_out,
+                             [&](int rank, int u, float) { out(rank, at[u], w[u]); });
+  };
+  if (kept <= 2 * NT) finish(std::integral_constant<int, 2>{});
+  else if (kept <= 4 * NT) finish(std::integral_constant<int, 4>{});
+  else finish(std::integral_constant<int, kRegElems>{});
+  return true;
 }
 
 }  // namespace lfps

@@ -65,3 +65,36 @@ def test_step_equals_the_separate_calls(B, Hq, Hkv, L, k, r, dtype, values):
             assert torch.equal(got, ref), (name, t, int((got != ref).sum()))
         prev = idx
     ctx.close()
+
+
+# the stand-alone select: 4, 8, 16 and 32 scores per thread of its 1024, one more, and the streamed form
+@pytest.mark.parametrize("L,k", [(1, 1), (63, 63), (4096, 100), (4097, 4097), (8191, 1), (8193, 700), (16384, 16384),
+                                 (16385, 2000), (32767, 1024), (32768, 1023), (32769, 5000)])
+@pytest.mark.parametrize("values", ["spread", "few", "equal", "outlier"])
+def test_stand_alone_select(L, k, values):
+    """Keys and queries of small whole numbers: dot products are exact, so the selection is fixed (equal scores at the
+    cut go to the lower position)."""
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L + k)
+    ints = lambda lo, hi, shape: torch.randint(lo, hi, shape, device=DEV, generator=g).float()
+    Hq, Hkv = 4, 1
+    K = ints(-3, 4, (1, Hkv, L, 128)) if values == "spread" else ints(-1, 2, (1, Hkv, L, 128))
+    q = ints(-8, 9, (1, Hq, 128))
+    if values == "few":
+        K[..., 2:] = 0
+    if values == "equal":
+        K[:] = 1
+    if values == "outlier":
+        K[0, 0, L // 2] = 100 * q[0, 0]
+    ctx = Lfps(batch=1, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="f32", max_seq_len=L, max_k=k, radius=1)
+    seq, kk = (torch.tensor([x], dtype=torch.int32, device=DEV) for x in (L, k))
+    idx = torch.full((1, Hq, k), -5, dtype=torch.int32, device=DEV)
+    sc = torch.full((1, Hq, k), -5.0, device=DEV)
+    ctx.lfps_exact_topk(q, ctx.kv_view(K, K, seq), kk, idx, sc)
+    dots = (q[0].double() @ K[0, 0].double().T).cpu()
+    order = torch.sort(dots, dim=1, descending=True, stable=True).indices[:, :k].sort(dim=1).values
+    assert torch.equal(idx[0].cpu().long(), order)
+    want = (torch.gather(dots, 1, order).float() * torch.tensor(0.08838834764831845, dtype=torch.float32))
+    assert torch.equal(sc[0].cpu(), want)
+    ctx.close()
