@@ -16,6 +16,15 @@ __device__ __forceinline__ void set_bit_range(uint32_t* bm, int lo, int hi) {  /
   }
 }
 
+// One word of a head's initial candidates (bit 0 = the word's first position), widened by the offsets -r ... r + 1
+// (r <= 30) across the words before and after it.
+__device__ __forceinline__ uint32_t widen_word(uint32_t before, uint32_t mid, uint32_t after, int r) {
+  uint32_t d = mid;
+  for (int e = 1; e <= r + 1; ++e) d |= (mid << e) | (before >> (32 - e));      // j = i + e
+  for (int e = 1; e <= r; ++e) d |= (mid >> e) | (after << (32 - e));            // j = i - e
+  return d;
+}
+
 // Emits the set bits of the LDS bitmap bm[0:W] as ascending positions into cand[bg, :] and leaves the
 // count in cand_count[bg] (truncated to cand_cap with the overflow flag raised).  All threads of the
 // workgroup call it after a barrier that follows the last write to the bitmap.  Emission goes in rounds

@@ -77,12 +77,7 @@ __global__ __launch_bounds__(kCandThreads) void k_table_candidates(Shape s, cons
     }
     uint32_t acc = 0u;
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      uint32_t d = mid[h];
-      for (int e = 1; e <= r + 1; ++e) d |= (mid[h] << e) | (lo[h] >> (32 - e));      // j = i + e
-      for (int e = 1; e <= r; ++e) d |= (mid[h] >> e) | (hi[h] << (32 - e));           // j = i - e
-      acc |= d & mean[h];
-    }
+    for (int h = 0; h < 4; ++h) acc |= widen_word(lo[h], mid[h], hi[h], r) & mean[h];
     bm[w] = acc;
   }
   __syncthreads();

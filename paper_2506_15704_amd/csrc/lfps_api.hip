@@ -23,6 +23,9 @@ struct lfps_ctx {
   int32_t* slot;       // [B, Hq, score_stride] candidate slots of the filtered survivors
   int32_t* seg_count;  // [B, Hq, nseg]
   float* thr_state;    // [B, Hq] k-th best score of the previous step
+  int range[2];        // rows of a range when a step (0 memoryless, 1 table form) takes the range kernel, else 0
+  uint32_t* bitmap;    // [B, Hkv, bitmap_words] the candidates of such a step
+  int bitmap_words;
   int64_t* group_start; // [B, Hkv] place of each group on the line of all candidate slots; [B*Hkv] = the line's length
   // score tables (table_mode)
   float* tab_ver;      // [B, Hq, Lcap]
@@ -74,8 +77,8 @@ static const int64_t kExactFastMinRows = 1 << 20;
 namespace {
 
 struct Sizes {
-  int32_t G, cand_cap, score_stride, n_split_full, nseg, flag_words;
-  int64_t score_b, cand_b, count_b, sel_b, part_b, slot_b, seg_b, thr_b, line_b, tver_b, tsla_b, tstate_b, tflag_b, x_b, aux_b, total;
+  int32_t G, cand_cap, score_stride, n_split_full, nseg, flag_words, range[2], bitmap_words;
+  int64_t score_b, cand_b, count_b, sel_b, part_b, slot_b, seg_b, thr_b, line_b, tver_b, tsla_b, tstate_b, tflag_b, x_b, aux_b, bitmap_b, total;
 };
 
 // Key format of the MFMA kernels (16-bit and FP8 keys): 0 bf16, 1 FP8, 2 fp16.
@@ -132,6 +135,7 @@ int check_config(const lfps_config* c, Sizes* z, char* err, size_t errn) {
   Shape s{};
   s.B = c->batch; s.Hq = c->n_q_heads; s.Hkv = c->n_kv_heads; s.G = G;
   s.Lcap = c->max_seq_len; s.kmax = c->max_k; s.cand_cap = z->cand_cap;
+  s.radius = c->radius; s.n_recent = c->n_recent; s.n_sink = c->n_sink;
   z->n_split_full = full_attn_splits(s);
   z->score_b = align256((int64_t)c->batch * c->n_q_heads * z->score_stride * 4);
   z->cand_b = align256((int64_t)c->batch * c->n_kv_heads * z->cand_cap * 4);
@@ -145,6 +149,16 @@ int check_config(const lfps_config* c, Sizes* z, char* err, size_t errn) {
     sd.cand_cap = s.Lcap;
     const int nd = filter_nseg(sd);
     z->nseg = nd > z->nseg ? nd : z->nseg;
+  }
+  // the range kernel never truncates a candidate set: it is for contexts in which none can exceed cand_cap
+  z->bitmap_words = (s.Lcap + 31) / 32;
+  z->bitmap_b = 0;
+  for (int t = 0; t < 2; ++t) {
+    z->range[t] = filt && z->cand_cap >= bound && (t == 0 || c->table_mode) ? range_rows(s, t == 1) : 0;
+    if (!z->range[t]) continue;
+    const int np = 4 * ((s.Lcap + z->range[t] - 1) / z->range[t]);
+    z->nseg = np > z->nseg ? np : z->nseg;
+    z->bitmap_b = align256((int64_t)c->batch * c->n_kv_heads * z->bitmap_words * 4);
   }
   z->slot_b = filt ? z->score_b : 0;
   z->seg_b = align256((int64_t)c->batch * c->n_q_heads * z->nseg * 4);
@@ -161,7 +175,7 @@ int check_config(const lfps_config* c, Sizes* z, char* err, size_t errn) {
   if (c->table_mode && table_init_scratch_bytes(s) > z->aux_b) z->aux_b = table_init_scratch_bytes(s);
   z->aux_b = align256(z->aux_b);
   z->total = z->score_b + z->cand_b + z->count_b + z->sel_b + z->part_b + z->slot_b + z->seg_b + z->thr_b +
-             z->line_b + 256 + z->x_b + z->aux_b + z->tver_b + z->tsla_b + z->tstate_b + 2 * z->tflag_b + z->thr_b /* gate marks */;
+             z->line_b + 256 + z->x_b + z->aux_b + z->bitmap_b + z->tver_b + z->tsla_b + z->tstate_b + 2 * z->tflag_b + z->thr_b /* gate marks */;
   return LFPS_OK;
 }
 
@@ -346,6 +360,11 @@ int lfps_create(const lfps_config* cfg, lfps_ctx** out) {
   }
   c->aux = p;
   p += z.aux_b;
+  c->range[0] = z.range[0];
+  c->range[1] = z.range[1];
+  c->bitmap = (uint32_t*)p;
+  c->bitmap_words = z.bitmap_words;
+  p += z.bitmap_b;
   if (cfg->table_mode) {
     c->tab_ver = (float*)p;
     p += z.tver_b;
@@ -465,6 +484,8 @@ int lfps_sparse_attn(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int
 // Does the next chained step take the filtered kernels?  (Decides, too, whether its candidates kernel lays the
 // groups on the line: only the filtered select clears the line's length again.)
 static bool next_step_filtered(const lfps_ctx* ctx) { return ctx->filter_on && !ctx->no_history; }
+// ... and with them the kernel that finds the candidates and scores them at once (rows of its ranges, or 0)?
+static int next_step_range(const lfps_ctx* ctx, bool tables) { return next_step_filtered(ctx) ? ctx->range[tables] : 0; }
 
 // S2 + S3 + S4 over ctx->cand / ctx->cand_count inside the chained entry points.  With the score filter on
 // (16-bit and FP8-key caches): survivors of the per-head threshold, then select and attention in one kernel, which
@@ -472,22 +493,31 @@ static bool next_step_filtered(const lfps_ctx* ctx) { return ctx->filter_on && !
 // attention; also for the first step after creation or lfps_reset_history, when no head has a remembered score and
 // the filtered form would send every head through its slower in-kernel fallback.
 // The candidates kernel of the same step has laid the groups on the line (group_start, line_total).
-static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, const int32_t* k, int32_t* topk_idx,
-                               float* sel, float* out, const int32_t* skip_if, hipStream_t st) {
+// from: where the range kernel finds the candidates (steps with a next_step_range; no candidates kernel before it).
+static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, const RangeSource& from,
+                               const int32_t* k, int32_t* topk_idx, float* sel, float* out, const int32_t* skip_if,
+                               hipStream_t st) {
   const Shape& s = ctx->shape;
   int64_t* line_total = ctx->group_start + (int64_t)s.B * s.Hkv;
   const bool filtered = next_step_filtered(ctx);
+  const int range = next_step_range(ctx, from.prev_topk == nullptr);
   ctx->no_history = 0;                       // either form leaves every selecting head's k-th best score behind
-  if (filtered) {
+  if (range) {
+    LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
+           launch_range_score(s, q, v, from, ctx->thr_state, kFilterMargin, ctx->score, ctx->slot, s.score_stride,
+                              ctx->seg_count, ctx->nseg, ctx->bitmap, ctx->bitmap_words, range, ctx->flags, st));
+  } else if (filtered) {
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
            launch_filter_score(s, q, v, ctx->cand, ctx->cand_count, ctx->group_start, line_total, ctx->thr_state,
                                kFilterMargin, ctx->score, ctx->slot, s.score_stride, ctx->seg_count, ctx->flags + 1,
                                ctx->filter_blocks[v.page.table ? 1 : 0], ctx->flags, false, ctx->nseg, st));
+  }
+  if (filtered) {
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SELECT_ATTEND, st,
            launch_filter_select_attend(s, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
                                        ctx->flags + 1, ctx->nseg, ctx->cand, ctx->cand_count, ctx->group_start,
-                                       line_total, k, topk_idx, sel, ctx->thr_state, kFilterMargin, skip_if,
-                                       ctx->flags + 2, q, ctx->flags, v, out, st));
+                                       line_total, range, ctx->bitmap, ctx->bitmap_words, k, topk_idx, sel,
+                                       ctx->thr_state, kFilterMargin, skip_if, ctx->flags + 2, q, ctx->flags, v, out, st));
     return LFPS_OK;
   }
   LAUNCH(ctx, LFPS_KERNEL_GATHER_SCORE, st,
@@ -515,10 +545,14 @@ int lfps_step(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int32_t* p
   hipStream_t st = (hipStream_t)stream;
   float* sel = topk_score ? topk_score : ctx->sel_score;
   int64_t* line_total = ctx->group_start + (int64_t)s.B * s.Hkv;   // zero between steps: the filtered select resets it
-  LAUNCH(ctx, LFPS_KERNEL_CANDIDATES, st,
-         launch_candidates(s, prev_topk, k, v.seq_lens, ctx->cand, ctx->cand_count, ctx->flags,
-                           next_step_filtered(ctx) ? ctx->group_start : nullptr, line_total, st));
-  return score_select_attend(ctx, q, v, k, topk_idx, sel, out, nullptr, st);
+  const RangeSource from{prev_topk, k, s.kmax % 4 == 0 && (uintptr_t)prev_topk % 16 == 0, nullptr, nullptr, 0};
+  if (next_step_range(ctx, false))
+    LAUNCH(ctx, LFPS_KERNEL_CANDIDATES, st, hipSuccess);      // (timing: S1 is part of the filter_score launch)
+  else
+    LAUNCH(ctx, LFPS_KERNEL_CANDIDATES, st,
+           launch_candidates(s, prev_topk, k, v.seq_lens, ctx->cand, ctx->cand_count, ctx->flags,
+                             next_step_filtered(ctx) ? ctx->group_start : nullptr, line_total, st));
+  return score_select_attend(ctx, q, v, from, k, topk_idx, sel, out, nullptr, st);
 }
 
 // ---------------------------------------------------------------------------- allocation-free S4
@@ -648,7 +682,7 @@ int lfps_exact_topk(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int3
                                ctx->filter_blocks[v.page.table ? 1 : 0], ctx->flags, true, ctx->nseg, st));
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SELECT_ATTEND, st,
            launch_filter_select_attend(sd, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
-                                       ctx->flags + 1, ctx->nseg, nullptr, ctx->x_cnt, ctx->x_start, x_total, k, topk_idx,
+                                       ctx->flags + 1, ctx->nseg, nullptr, ctx->x_cnt, ctx->x_start, x_total, 0, nullptr, 0, k, topk_idx,
                                        topk_score ? topk_score : ctx->sel_score, ctx->thr_x, 0.f, nullptr, nullptr,
                                        q, ctx->flags, v, nullptr, st));
     return LFPS_OK;
@@ -740,6 +774,10 @@ static int table_candidates_impl(lfps_ctx* ctx, const int32_t* seq_lens, int32_t
   LAUNCH(ctx, LFPS_KERNEL_TABLE_FLAGS, st,
          launch_table_flags(s, ctx->tab_ver, ctx->tab_sla, ctx->tab_state, seq_lens, ctx->tab_f0, ctx->tab_fm,
                             ctx->flag_words, (double)ctx->cfg.table_a, gate, st));
+  if (for_step && next_step_range(ctx, true)) {
+    LAUNCH(ctx, LFPS_KERNEL_TABLE_CANDIDATES, st, hipSuccess);      // (timing: part of the filter_score launch)
+    return LFPS_OK;
+  }
   LAUNCH(ctx, LFPS_KERNEL_TABLE_CANDIDATES, st,
          launch_table_candidates(s, ctx->tab_f0, ctx->tab_fm, ctx->flag_words, seq_lens, cand, cand_count, ctx->flags,
                                  for_step && next_step_filtered(ctx) ? ctx->group_start : nullptr,
@@ -782,7 +820,8 @@ static int table_step_impl(lfps_ctx* ctx, const float* q, const KvView& v, const
   float* sel = topk_score ? topk_score : ctx->sel_score;
   int rc = table_candidates_impl(ctx, v.seq_lens, ctx->cand, ctx->cand_count, true, gate, st);
   if (rc != LFPS_OK) return rc;
-  rc = score_select_attend(ctx, q, v, k, topk_idx, sel, out, gate, st);
+  const RangeSource from{nullptr, nullptr, 0, ctx->tab_f0, ctx->tab_fm, ctx->flag_words};
+  rc = score_select_attend(ctx, q, v, from, k, topk_idx, sel, out, gate, st);
   if (rc != LFPS_OK) return rc;
   return table_update_impl(ctx, topk_idx, sel, k, v.seq_lens, gate, true, st);   // the select's rows are distinct
 }

@@ -102,15 +102,36 @@ hipError_t launch_filter_score(const Shape& s, const float* q, const KvView& kv,
                                const float* thr_state, float margin, float* score,
                                int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int32_t* seg_rows_out,
                                int n_blocks, int32_t* flags, bool dense, int nseg, hipStream_t st);
+// S1 + S2 of a chained step in one kernel (range_score.hip): candidates from the Top-k of the step before (prev_topk, k) or
+// from the table scan's flags (f0, fm; prev_topk == NULL), scored and filtered as above.  seg_count[b, h, 4 i + w] =
+// candidates << 16 | survivors of piece w of range i; bitmap [B, Hkv, bitmap_words] = the candidates.
+constexpr int kRangeMax = 8192;      // rows of a range at most: a word of bitmap per thread
+struct RangeSource {
+  const int32_t* prev_topk;          // [B, Hq, kmax]
+  const int32_t* k;                  // [B]
+  int vec;                           // rows of prev_topk are 16-byte aligned
+  const uint32_t* f0;                // [B, Hq, flag_words]
+  const uint32_t* fm;
+  int flag_words;
+};
+int range_rows(const Shape& s, bool tables);   // 0: the separate kernels
+hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, const RangeSource& from,
+                              const float* thr_state, float margin, float* score, int32_t* slot_out,
+                              int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words,
+                              int range, int32_t* flags, hipStream_t st);
+
 // S3 + S4 of the chained steps in one kernel (select_attend.hip).  From the survivor lists of the filtered scoring
 // pass: every head gets its Top-k rows (topk_idx, topk_score: both required) and its output row; a head whose list
 // is short or overfull takes the unfiltered pass inside the kernel (counted in *rescored), which needs q, the K rows
 // and the group's candidate list (cand; NULL = all rows 0 .. cand_count-1) and overwrites the head's score row.
+// range > 0: the lists are those of launch_range_score with that range (cand, seg_rows, group_start, line_total unused;
+// the candidates are in bitmap), and cand_count is written.
 hipError_t configure_select_attend(const Shape& s, int dtype, bool k_fp8, bool v_fp8);
-hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, const int32_t* slot_in,
+hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, int32_t* slot,
                                        int64_t score_stride, const int32_t* seg_count, const int32_t* seg_rows, int nseg,
-                                       const int32_t* cand, const int32_t* cand_count, const int64_t* group_start,
-                                       int64_t* line_total, const int32_t* k, int32_t* topk_idx, float* topk_score,
+                                       const int32_t* cand, int32_t* cand_count, const int64_t* group_start,
+                                       int64_t* line_total, int range, const uint32_t* bitmap, int bitmap_words,
+                                       const int32_t* k, int32_t* topk_idx, float* topk_score,
                                        float* thr_state, float margin, const int32_t* skip_if, int32_t* rescored,
                                        const float* q, int32_t* flags, const KvView& kv, float* out,
                                        hipStream_t st);   // out == NULL: select only

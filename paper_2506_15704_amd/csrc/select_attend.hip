@@ -22,6 +22,7 @@
 // room for: 13 us (2.1 + 2.7 + 2.9 + 4.0); 512 heads, k = 2048: 45.8 -> 41 us, 1024 ragged heads: 52.7 -> 39 us (all of them
 // resident at once now).
 #include "attend.h"
+#include "range_geometry.h"
 #include "score_mfma.h"
 #include "select_regs.h"
 
@@ -68,15 +69,18 @@ __device__ __forceinline__ void list_from_global(SelRow* list, const KvPage& pag
 // `sgm` is what wave w_first + sgm took of it, w_first = pg / S: the group's slots [lo, hi).  The piece holds
 // seg_count[bh, sgm] (score, row position) pairs at offset lo of the head's score / position rows, ascending in
 // position within and across pieces.  Workgroup 0 leaves *line_total at zero for the next step.
+// range > 0: the lists of the range kernel instead (range_geometry.h): piece counts are candidates << 16 | survivors, the
+// group's candidate count is their sum (left in cand_count by the group's first head), the candidates are a bitmap.
 // margin: what the scoring pass subtracted from thr_state.
 // The unfiltered pass needs the query, the K rows (format kKind) and the group's candidate list (cand; NULL when the
 // candidates are all rows 0 .. count-1, the exact Top-k baseline's dense pass).
 template <typename T, bool kPaged, int kKind, int NT>
 __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
-    Shape s, float* score, const int32_t* __restrict__ slot_in, int64_t score_stride,
+    Shape s, float* score, int32_t* slot, int64_t score_stride,
     const int32_t* __restrict__ seg_count, const int32_t* __restrict__ seg_rows_in, int nseg,
-    const int32_t* __restrict__ cand, const int32_t* __restrict__ cand_count, const int64_t* __restrict__ group_start,
-    int64_t* __restrict__ line_total, const int32_t* __restrict__ kk, int32_t* topk_idx, float* topk_score,
+    const int32_t* __restrict__ cand, int32_t* __restrict__ cand_count, const int64_t* __restrict__ group_start,
+    int64_t* __restrict__ line_total, int range, const uint32_t* __restrict__ bitmap, int bitmap_words,
+    const int32_t* __restrict__ kk, int32_t* topk_idx, float* topk_score,
     float* __restrict__ thr_state, float margin, const int32_t* __restrict__ skip_if, int32_t* __restrict__ rescored,
     const float* __restrict__ q, const void* __restrict__ K, float scale, int32_t* __restrict__ flags,
     const T* __restrict__ V, int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage page,
@@ -85,16 +89,18 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   constexpr int kPieces = 1024 / NT;               // pieces per thread: nseg <= 1024
   __shared__ SelectShared<NT> sm;
   __shared__ int seg_off[1024];
-  __shared__ int wtot[kWaves];
+  __shared__ int wtot[kWaves], ctot[kWaves];
   extern __shared__ char dyn[];                    // the attention's partial sums, then the list of selected rows
   AttendShared& as = *reinterpret_cast<AttendShared*>(dyn);
   SelRow* list = reinterpret_cast<SelRow*>(dyn + sizeof(AttendShared));
-  if (blockIdx.x == 0 && threadIdx.x == 0) *line_total = 0;   // the scoring pass that read it has finished
+  const bool ranges = range > 0;
+  if (!ranges && blockIdx.x == 0 && threadIdx.x == 0) *line_total = 0;   // the scoring pass that read it has finished
   const int bh = head_of_block(s, blockIdx.x);     // the heads of a KV group on one XCD: they share V rows in its L2
   const int b = bh / s.Hq, h = bh % s.Hq, g = h / s.G;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int bg = b * s.Hkv + g;
-  if (skip_if && skip_if[bh] != 0) return;           // bypassed head: its rows were written by the gate
+  const bool skipped = skip_if && skip_if[bh] != 0;  // bypassed head: its rows were written by the gate
+  if (skipped && !(ranges && h % s.G == 0)) return;
   int raw[kPieces];                                  // piece counts of this head, masked once the geometry is known
 #pragma unroll
   for (int u = 0; u < kPieces; ++u) {
@@ -102,32 +108,37 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     raw[u] = sgm < nseg ? seg_count[(int64_t)bh * nseg + sgm] : 0;
   }
   const float tau = thr_state[bh] - margin;          // what the survivors have reached
-  int c = cand_count[bg];
+  int c = ranges ? 0 : cand_count[bg];
   int kb = kk[b];
   int n = seq_lens[b];
-  int S = *seg_rows_in;                              // chosen by the scoring pass of this step
-  const int64_t pg = group_start[bg];
+  int S = ranges ? 64 : *seg_rows_in;                // chosen by the scoring pass of this step
+  const int64_t pg = ranges ? 0 : group_start[bg];
   c = c < 0 ? 0 : (c > s.cand_cap ? s.cand_cap : c);
   kb = kb < 0 ? 0 : (kb > s.kmax ? s.kmax : kb);
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   S = S < 64 ? 64 : S;
-  const int ksel = kb < c ? kb : c;
   // the group's slots relative to the part it starts in: piece sgm is [sgm * S - r0, (sgm + 1) * S - r0)
   const int r0 = (pg >> 32) == 0 ? (int)((uint32_t)pg % (uint32_t)S) : (int)(pg % S);
-  int np = c > 0 ? (r0 + c - 1) / S + 1 : 0;         // pieces my group was cut into
+  const RangePieces geo(n, ranges ? range : 64);
+  int np = ranges ? geo.count : (c > 0 ? (r0 + c - 1) / S + 1 : 0);         // pieces my group was cut into
   np = np > nseg ? nseg : np;
-  auto piece_lo = [&](int sgm) { return sgm > 0 ? sgm * S - r0 : 0; };
+  auto piece_lo = [&](int sgm) { return ranges ? geo.start(sgm) : (sgm > 0 ? sgm * S - r0 : 0); };
 
   // exclusive prefix of the piece counts (kPieces consecutive pieces per thread)
   for (int i = tid; i < 2 * NT; i += NT) sm.hist[i] = 0u;
   if (tid == 0) sm.list_n = 0u;
   int cntp[kPieces];
-  int cnt = 0;
+  int cnt = 0, cands = 0;
 #pragma unroll
   for (int u = 0; u < kPieces; ++u) {
     const int sgm = kPieces * tid + u;
     cntp[u] = 0;
-    if (sgm < np) {
+    if (sgm < np && ranges) {
+      const int room = range >> 2;                             // rows the piece covers at most
+      const int all = min(raw[u] >> 16 & 0xFFFF, room);
+      cntp[u] = min(raw[u] & 0xFFFF, all);
+      cands += all;
+    } else if (sgm < np) {
       const int hi = (sgm + 1) * S - r0;
       const int room = (hi > c ? c : hi) - piece_lo(sgm);    // rows the piece covers
       cntp[u] = raw[u] < 0 ? 0 : (raw[u] > room ? room : raw[u]);
@@ -136,7 +147,18 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   }
   const int inc = wave_inclusive_sum(cnt);
   if (lane == 63) wtot[wv] = inc;
+  if (ranges) {
+    cands = wave_inclusive_sum(cands);
+    if (lane == 63) ctot[wv] = cands;
+  }
   __syncthreads();
+  if (ranges) {
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) c += ctot[w];
+    if (tid == 0 && h % s.G == 0) cand_count[bg] = c;
+    if (skipped) return;
+  }
+  const int ksel = kb < c ? kb : c;
   int base = 0, n_surv = 0;
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) {
@@ -167,7 +189,24 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     return;
   }
   float* sc = score + (int64_t)bh * score_stride;
-  const int32_t* cbg = cand ? cand + (int64_t)bg * s.cand_cap : nullptr;
+  int32_t* sl = slot + (int64_t)bh * score_stride;
+  const int32_t* cbg = ranges ? sl : (cand ? cand + (int64_t)bg * s.cand_cap : nullptr);
+  if (unfiltered && ranges) {                       // the group's candidates from the bitmap, ascending, over the survivors
+    const uint32_t* bm = bitmap + (int64_t)bg * bitmap_words;
+    const int W = (n + 31) >> 5, per = (W + NT - 1) / NT;
+    const int w0 = tid * per < W ? tid * per : W, w1 = w0 + per < W ? w0 + per : W;
+    int mine = 0;
+    for (int w = w0; w < w1; ++w) mine += __popc(bm[w]);
+    const int upto = wave_inclusive_sum(mine);
+    if (lane == 63) ctot[wv] = upto;                 // (read by nobody since the last barrier but one)
+    __syncthreads();
+    int at = upto - mine;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) at += w < wv ? ctot[w] : 0;
+    for (int w = w0; w < w1; ++w)
+      for (uint32_t bits = bm[w]; bits && at < c; bits &= bits - 1) sl[at++] = (w << 5) + __ffs(bits) - 1;
+    __syncthreads();
+  }
   if (unfiltered) {
     // every candidate slot of the group, 64 per wave and visit, scored for the G heads; my head's lane group stores
     using Rows = RowMap<kPaged>;
@@ -207,7 +246,6 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
             if (mid < np && seg_off[mid] <= u * NT + tid) pc[u] = mid;
           }
         }
-        const int32_t* sl = slot_in + (int64_t)bh * score_stride;
 #pragma unroll
         for (int u = 0; u < E; ++u) {
           const int e = u * NT + tid;
@@ -411,10 +449,11 @@ hipError_t configure_select_attend(const Shape& s, int dtype, bool k_fp8, bool v
   return e;
 }
 
-hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, const int32_t* slot_in,
+hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, int32_t* slot,
                                        int64_t score_stride, const int32_t* seg_count, const int32_t* seg_rows, int nseg,
-                                       const int32_t* cand, const int32_t* cand_count, const int64_t* group_start,
-                                       int64_t* line_total, const int32_t* k, int32_t* topk_idx, float* topk_score,
+                                       const int32_t* cand, int32_t* cand_count, const int64_t* group_start,
+                                       int64_t* line_total, int range, const uint32_t* bitmap, int bitmap_words,
+                                       const int32_t* k, int32_t* topk_idx, float* topk_score,
                                        float* thr_state, float margin, const int32_t* skip_if, int32_t* rescored,
                                        const float* q, int32_t* flags, const KvView& kv, float* out, hipStream_t st) {
   const int nt = filter_select_threads(s);
@@ -436,8 +475,9 @@ hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, 
 #define LFPS_LAUNCH_FSA(TYPE, PAGED, KIND, NT)                                                                          \
   if (!launched && vt == v_type_code<TYPE>() && paged == PAGED && nt == NT && kind == KIND) {                          \
     hipLaunchKernelGGL((k_filter_select_attend<TYPE, PAGED, KIND, NT>), dim3(s.B * s.Hq), dim3(NT),                     \
-                       (size_t)filter_select_attend_lds(s), st, s, score, slot_in, score_stride, seg_count, seg_rows,   \
-                       nseg, cand, cand_count, group_start, line_total, k, topk_idx, topk_score, thr_state, margin,     \
+                       (size_t)filter_select_attend_lds(s), st, s, score, slot, score_stride, seg_count, seg_rows,      \
+                       nseg, cand, cand_count, group_start, line_total, range, bitmap, bitmap_words, k, topk_idx,       \
+                       topk_score, thr_state, margin,                                                                   \
                        skip_if, rescored, q, kv.k, scale, flags, (const TYPE*)kv.v, kv.stride_b, kv.stride_h,           \
                        kv.stride_n, kv.page, kv.seq_lens, out);                                                         \
     launched = true;                                                                                                    \

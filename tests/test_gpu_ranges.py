@@ -1,0 +1,114 @@
+"""Candidates and scores in one kernel (chained steps of up to a million rows): at the edges of its ranges and pieces, from
+the Top-k of the step before and from the table flags, against an unfiltered context, which takes the separate kernels."""
+import pytest
+import torch
+
+from tests.harness import DEV
+
+pytestmark = pytest.mark.gpu
+
+
+def _pair(**kw):
+    from paper_2506_15704_amd.binding import Lfps
+    a, b = Lfps(**kw), Lfps(**kw)
+    b.lfps_set_filter(False)
+    return a, b
+
+
+def _cache(B, Hkv, Lcap, dtype, page, g):
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16, "fp8": torch.bfloat16}[dtype]
+    K, V = (torch.randn((B, Hkv, Lcap, 128), device=DEV, generator=g) for _ in range(2))
+    K, V = K.to(torch.float8_e4m3fn) if dtype == "fp8" else K.to(dt), V.to(dt)
+    if not page:
+        return K, V, None
+    nb = -(-Lcap // page)
+    table = torch.randperm(B * nb, device=DEV, generator=g).view(B, nb)
+    pool = []
+    for x in (K, V):
+        raw = torch.zeros((B, Hkv, nb * page, 128), dtype=x.dtype, device=DEV).view(torch.uint8)
+        raw[:, :, :Lcap] = x.view(torch.uint8)
+        p = torch.empty((B * nb, Hkv, page) + raw.shape[3:], dtype=torch.uint8, device=DEV)
+        p[table.view(-1)] = raw.view(B, Hkv, nb, page, -1).transpose(1, 2).reshape(p.shape)
+        pool.append(p.view(x.dtype))
+    return pool[0], pool[1], table.to(torch.int32)
+
+
+def _view(ctx, cache, seq):
+    K, V, table = cache
+    return ctx.kv_view(K, V, seq) if table is None else ctx.paged_kv_view(K, V, table, seq)
+
+
+# lengths around multiples of a range (512, 1024), a quarter of it and a word; rows of prev_topk with and without 16-byte
+# alignment (k % 4), more than 2048 entries per head, radius 0 and one wider than a range, sinks and recents across ranges
+@pytest.mark.parametrize("B,Hq,Hkv,L,k,r,n_recent,n_sink,dtype,page", [
+    (1, 4, 1, 1, 1, 0, 1, 0, "bf16", 0), (1, 4, 1, 511, 20, 2, 1, 0, "bf16", 0), (2, 8, 2, 1021, 33, 4, 0, 0, "bf16", 0),
+    (1, 4, 4, 2047, 64, 3, 600, 700, "bf16", 0), (3, 8, 4, 3071, 63, 1, 1, 4, "f16", 16),
+    (1, 8, 2, 12000, 2500, 1, 1, 0, "bf16", 0), (2, 4, 1, 1500, 10, 5000, 1, 0, "bf16", 0),
+    (1, 32, 8, 40000, 500, 4, 1, 0, "bf16", 64), (5, 16, 8, 20000, 300, 2, 65, 2, "fp8", 0), (4, 32, 8, 30001, 90, 0, 1, 0, "fp8", 16)])
+def test_memoryless_steps(B, Hq, Hkv, L, k, r, n_recent, n_sink, dtype, page):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L * 7 + k)
+    Lcap = L + 6
+    cache = _cache(B, Hkv, Lcap, dtype, page, g)
+    a, b = _pair(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="bf16" if dtype == "fp8" else dtype, k_fp8=dtype == "fp8",
+                 max_seq_len=Lcap, max_k=k, radius=r, n_recent=n_recent, n_sink=n_sink)
+    lens = [max(1, L - 515 * i) for i in range(B)]
+    ks = torch.tensor([max(1, min(k, n) - i) for i, n in enumerate(lens)], dtype=torch.int32, device=DEV)
+    q = torch.randn((B, Hq, 128), device=DEV, generator=g)
+    prev = torch.full((B, Hq, k), -1, dtype=torch.int32, device=DEV)
+    a.lfps_exact_topk(q, _view(a, cache, torch.tensor(lens, dtype=torch.int32, device=DEV)), ks, prev)
+    for t in range(1, 6):
+        # slowly changing queries; then a useless history: every head takes the unfiltered pass from the bitmap
+        q = q * 0.02 if t == 4 else q + 0.1 * torch.randn((B, Hq, 128), device=DEV, generator=g)
+        if t == 3:      # a caller's list: unsorted, doubled, with entries that are no rows
+            prev = prev.flip(2).contiguous()
+            prev[:, :, ::7] = prev[:, :, :1].clone()
+            for at, entry in ((3, -7), (5, 2**31 - 1), (6, L + 5), (8, -2**31)):
+                prev[:, :, at::23] = entry
+        seq = torch.tensor([n + t for n in lens], dtype=torch.int32, device=DEV)
+        res = []
+        for ctx in (a, b):
+            idx = torch.full((B, Hq, k), -5, dtype=torch.int32, device=DEV)
+            sc, out = torch.full((B, Hq, k), -5.0, device=DEV), torch.full((B, Hq, 128), -5.0, device=DEV)
+            cnt = torch.full((B, Hkv), -5, dtype=torch.int32, device=DEV)
+            ctx.lfps_step(q, _view(ctx, cache, seq), prev, ks, idx, out, sc)
+            ctx.lfps_copy_cand_count(cnt)
+            assert ctx.lfps_poll_status() == 0
+            res.append((idx, sc, out, cnt))
+        for x, y, name in zip(*res, ("index", "score", "output", "candidate count")):
+            assert torch.equal(x, y), (name, t, int((x != y).sum()))
+        prev = res[0][0]
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,k,r,n_sink,dtype,page", [
+    (1, 4, 1, 100, 9, 1, 0, "bf16", 0), (2, 8, 2, 2047, 64, 1, 4, "bf16", 0), (2, 8, 4, 4099, 200, 30, 4, "f16", 64),
+    (3, 8, 8, 9000, 100, 3, 4, "bf16", 16)])
+def test_table_steps(B, Hq, Hkv, L, k, r, n_sink, dtype, page):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L + k)
+    Lcap = L + 8
+    cache = _cache(B, Hkv, Lcap, dtype, page, g)
+    pair = _pair(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype=dtype, max_seq_len=Lcap, max_k=k, radius=r, n_sink=n_sink,
+                 table_mode=True)
+    lens = [max(1, L - 515 * i) for i in range(B)]
+    ks = torch.tensor([min(k, n) for n in lens], dtype=torch.int32, device=DEV)
+    q = 3 * torch.randn((B, Hq, 128), device=DEV, generator=g)
+    for ctx in pair:
+        ctx.lfps_tables_init(q[None].contiguous(), _view(ctx, cache, torch.tensor(lens, dtype=torch.int32, device=DEV)))
+    for t in range(1, 6):
+        q = q + 0.3 * torch.randn((B, Hq, 128), device=DEV, generator=g)
+        seq = torch.tensor([n + t for n in lens], dtype=torch.int32, device=DEV)
+        res = []
+        for ctx in pair:
+            idx = torch.full((B, Hq, k), -5, dtype=torch.int32, device=DEV)
+            sc, out = torch.full((B, Hq, k), -5.0, device=DEV), torch.full((B, Hq, 128), -5.0, device=DEV)
+            cnt = torch.full((B, Hkv), -5, dtype=torch.int32, device=DEV)
+            ctx.lfps_table_step(q, _view(ctx, cache, seq), ks, idx, out, sc)
+            ctx.lfps_copy_cand_count(cnt)
+            res.append((idx, sc, out, cnt))
+        for x, y, name in zip(*res, ("index", "score", "output", "candidate count")):
+            assert torch.equal(x, y), (name, t, int((x != y).sum()))
+    for ctx in pair:
+        ctx.close()
