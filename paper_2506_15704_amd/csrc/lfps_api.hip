@@ -70,6 +70,8 @@ static const char* const kKernelNames[LFPS_N_KERNELS] = {
 
 // Margin below the previous step's k-th best score at which the filtered pass keeps a row.
 static const float kFilterMargin = 0.125f;
+// A head with fewer candidates than this many budgets keeps them all in the next step (memoryless, table form).
+static const int kKeepRatio = 2, kKeepRatioTables = 8;
 // Exact Top-k baseline: rows sampled per KV group for the threshold, and the size from which the filtered form is used.
 static const int kExactSampleRows = 32768;   // at most; the set-up kernel sizes the sample for the budget and the list
 static const int64_t kExactFastMinRows = 1 << 20;
@@ -501,6 +503,7 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
   int64_t* line_total = ctx->group_start + (int64_t)s.B * s.Hkv;
   const bool filtered = next_step_filtered(ctx);
   const int range = next_step_range(ctx, from.prev_topk == nullptr);
+  const int keep_ratio = from.prev_topk ? kKeepRatio : kKeepRatioTables;
   ctx->no_history = 0;                       // either form leaves every selecting head's k-th best score behind
   if (range) {
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
@@ -517,7 +520,7 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
            launch_filter_select_attend(s, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
                                        ctx->flags + 1, ctx->nseg, ctx->cand, ctx->cand_count, ctx->group_start,
                                        line_total, range, ctx->bitmap, ctx->bitmap_words, k, topk_idx, sel,
-                                       ctx->thr_state, kFilterMargin, skip_if, ctx->flags + 2, q, ctx->flags, v, out, st));
+                                       ctx->thr_state, kFilterMargin, keep_ratio, skip_if, ctx->flags + 2, q, ctx->flags, v, out, st));
     return LFPS_OK;
   }
   LAUNCH(ctx, LFPS_KERNEL_GATHER_SCORE, st,
@@ -525,7 +528,7 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
                             ctx->flags, st));
   LAUNCH(ctx, LFPS_KERNEL_SELECT_ATTEND, st,
          launch_select_attend(s, ctx->cfg.kv_dtype, ctx->score, s.score_stride, ctx->cand, ctx->cand_count, k, topk_idx,
-                              sel, ctx->thr_state, skip_if, v, out, st));
+                              sel, ctx->thr_state, keep_ratio, skip_if, v, out, st));
   return LFPS_OK;
 }
 
@@ -683,7 +686,7 @@ int lfps_exact_topk(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int3
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SELECT_ATTEND, st,
            launch_filter_select_attend(sd, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
                                        ctx->flags + 1, ctx->nseg, nullptr, ctx->x_cnt, ctx->x_start, x_total, 0, nullptr, 0, k, topk_idx,
-                                       topk_score ? topk_score : ctx->sel_score, ctx->thr_x, 0.f, nullptr, nullptr,
+                                       topk_score ? topk_score : ctx->sel_score, ctx->thr_x, 0.f, kKeepRatio, nullptr, nullptr,
                                        q, ctx->flags, v, nullptr, st));
     return LFPS_OK;
   }

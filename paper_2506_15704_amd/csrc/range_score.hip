@@ -1,0 +1,301 @@
+// S1 + S2 of a chained step in one kernel: the candidates of a KV group (Alg. 1 lines 6-7; Eq. 7 and 9) and the filtered
+// scores of their rows (Alg. 1 line 8), for 16-bit and FP8 keys.
+//
+// The positions of a group are cut into ranges of `range` rows, one per workgroup.  A workgroup marks its range's
+// candidates in an LDS bitmap (from the Top-k rows of the step before, of which it keeps what touches its range, or from
+// the flag words of the table scan), lists them in LDS and scores their K rows at once, the list in four equal pieces,
+// one per wave.  What reaches a head's threshold (the k-th best score of the step before minus a margin; NaN: no step
+// before, nothing is kept and the select takes its unfiltered pass) goes to the head's score / position rows, ascending
+// in position, with the numbers of survivors and candidates of every piece in seg_count.  The bitmap goes to memory too,
+// for the heads that need that unfiltered pass.
+//
+// Why one kernel: as two, a step of 8 groups x 32K rows spent 7.8 + 14.5 us here, of which the rows themselves are 5 us;
+// the rest is two launches and the round trips
+// candidates -> list -> geometry -> list -> rows.  Together: 14.6 us.
+#include "candidates.h"
+#include "range_geometry.h"
+#include "score_mfma.h"
+
+namespace lfps {
+
+constexpr int kRangeStage = 256;        // survivors a wave holds per head before it writes them out
+
+template <int G, bool kPaged, int kKind, bool kTables>
+__global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
+    Shape s, const float* __restrict__ q, const void* __restrict__ K, int64_t stride_b, int64_t stride_h,
+    int64_t stride_n, KvPage page, const int32_t* __restrict__ seq_lens, RangeSource from,
+    const float* __restrict__ thr_state, float margin, float* __restrict__ score, int32_t* __restrict__ slot_out,
+    int64_t score_stride, int32_t* __restrict__ seg_count, int nseg, uint32_t* __restrict__ bitmap, int bitmap_words,
+    int range, float scale, int32_t* __restrict__ flags) {
+  __shared__ float stage_score[4][G][kRangeStage];
+  __shared__ int32_t stage_slot[4][G][kRangeStage];
+  __shared__ uint32_t bm[kRangeMax / 32];
+  __shared__ int wave_tot[4];
+  extern __shared__ uint16_t list[];                     // the range's candidates, relative to its first row
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = lane & 15, kb = lane >> 4;
+  const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;
+  const int lo = blockIdx.x * range;
+  const int words = range >> 5;
+
+  using Rows = RowMap<kPaged>;
+  using Tile = KTile<kKind>;
+  using Op = typename Tile::Operand;
+
+  // ---- what the workgroup needs is requested before anything is waited for
+  int4 ids[kTables ? 1 : 2][G];
+  const int32_t* pt = kTables ? nullptr : from.prev_topk + ((int64_t)b * s.Hq + (int64_t)g * G) * s.kmax;
+  auto fetch = [&](int j0) {                             // entries j0 + 4 tid .. + 3, and 1024 further on, of every head
+    if constexpr (!kTables) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+          const int at = j0 + 1024 * u + 4 * tid;
+          const int32_t* p = pt + (int64_t)h * s.kmax + at;
+          int4 x = make_int4(-1, -1, -1, -1);
+          if (from.vec) {
+            if (at < s.kmax) x = *reinterpret_cast<const int4*>(p);
+          } else {
+            if (at < s.kmax) x.x = p[0];
+            if (at + 1 < s.kmax) x.y = p[1];
+            if (at + 2 < s.kmax) x.z = p[2];
+            if (at + 3 < s.kmax) x.w = p[3];
+          }
+          ids[u][h] = x;
+        }
+    }
+  };
+  fetch(0);
+  int n = seq_lens[b];
+  const int k_raw = kTables ? 0 : from.k[b];
+  const int64_t head0 = (int64_t)b * s.Hq + (int64_t)g * G;
+  const float thr = thr_state[head0 + (kb < G ? kb : 0)];
+  if (tid < words) bm[tid] = 0u;
+  n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
+  if (lo >= n) return;                                   // (nobody reads the piece counts of such a range)
+  const int hi = n - lo < range ? n : lo + range;
+  const int r = s.radius;
+  Op A[4];
+  report_q_range(load_query_operand(A, q, head0, G, j, kb), flags);
+  __syncthreads();
+
+  // ---- S1: the candidates of [lo, hi) as a bitmap
+  if constexpr (kTables) {
+    const int w = (lo >> 5) + tid, W = (n + 31) >> 5;
+    if (tid < words && w < W) {
+      uint32_t before[G], mid[G], after[G], mean[G];
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        const int64_t row = (head0 + h) * from.flag_words;
+        before[h] = w > 0 ? from.f0[row + w - 1] : 0u;
+        mid[h] = from.f0[row + w];
+        after[h] = w + 1 < W ? from.f0[row + w + 1] : 0u;
+        mean[h] = from.fm[row + w];
+      }
+      uint32_t acc = 0u;
+#pragma unroll
+      for (int h = 0; h < G; ++h) acc |= widen_word(before[h], mid[h], after[h], r) & mean[h];
+      bm[tid] = acc;
+    }
+    __syncthreads();
+  } else {
+    const int k = k_raw < 0 ? 0 : (k_raw > s.kmax ? s.kmax : k_raw);
+    // an entry i touches [lo, hi) with its window [i - r, i + r + 1] when first <= i <= last (r capped: no sum overflows)
+    const int rc = r < s.Lcap ? r : s.Lcap;
+    const int first = lo - 1 - rc > 0 ? lo - 1 - rc : 0, last = hi - 1 + rc < n - 1 ? hi - 1 + rc : n - 1;
+    const uint32_t width = (uint32_t)(last - first);
+    for (int j0 = 0;;) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int left = k - (j0 + 1024 * u + 4 * tid);    // entries of the budget from mine on
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+          const int e[4] = {ids[u][h].x, ids[u][h].y, ids[u][h].z, ids[u][h].w};
+          bool hit[4];
+#pragma unroll
+          for (int c = 0; c < 4; ++c) hit[c] = (uint32_t)(e[c] - first) <= width;
+          if (left > 0 && (hit[0] | hit[1] | hit[2] | hit[3])) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              if (hit[c] && c < left) {
+                const int a = e[c] - rc - lo, z = e[c] + rc + 1 - lo;
+                set_bit_range(bm, a < 0 ? 0 : a, z < hi - lo ? z : hi - 1 - lo);
+              }
+          }
+        }
+      }
+      j0 += 2048;
+      if (j0 >= k) break;
+      fetch(j0);
+    }
+  }
+  if (tid == 0) {
+    const int first = n - s.n_recent < lo ? lo : n - s.n_recent;
+    if (first < hi) set_bit_range(bm, first - lo, hi - 1 - lo);
+    const int sinks = s.n_sink < hi ? s.n_sink : hi;
+    if (sinks > lo) set_bit_range(bm, 0, sinks - 1 - lo);
+  }
+  __syncthreads();
+  if (tid < words && (lo >> 5) + tid < bitmap_words) bitmap[(int64_t)bg * bitmap_words + (lo >> 5) + tid] = bm[tid];
+
+  // ---- the list: thread t owns the bits [t * nb, (t + 1) * nb), nb = range / 256
+  const int nb = range >> 8, bit0 = tid * nb;
+  uint32_t bits = (bm[bit0 >> 5] >> (bit0 & 31)) & (nb == 32 ? 0xFFFFFFFFu : (1u << nb) - 1u);
+  const int mine = __popc(bits);
+  const int inc = wave_inclusive_sum(mine);
+  if (lane == 63) wave_tot[wave] = inc;
+  __syncthreads();
+  int at = inc - mine, total = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const int t = wave_tot[w];
+    at += w < wave ? t : 0;
+    total += t;
+  }
+  while (bits) {
+    list[at++] = (uint16_t)(bit0 + __ffs(bits) - 1);
+    bits &= bits - 1;
+  }
+  __syncthreads();
+
+  // ---- S2: the piece of this wave, entries [c0, c0 + cnt) of the list
+  const RangePieces geo(n, range);
+  const int per = (((total + 3) >> 2) + 15) & ~15;
+  const int c0 = wave * per;
+  const int cnt = __builtin_amdgcn_readfirstlane(total - c0 < per ? (total - c0 > 0 ? total - c0 : 0) : per);
+  const int piece = 4 * (int)blockIdx.x + wave;
+  const int out0 = geo.start(piece);                      // where its survivors go in the heads' rows
+  const int64_t head = head0 + (kb < G ? kb : 0);
+  const uint64_t nans = __ballot(kb < G && isnan(thr));
+  if (cnt == 0 || nans) {
+    if (j == 0 && kb < G) seg_count[head * nseg + piece] = cnt << 16;
+    return;
+  }
+  const float tau = kb < G ? thr - margin : INFINITY;
+  const uint32_t below = (1u << j) - 1u;                 // lanes of my 16-lane group with a lower row
+  float* st_s = stage_score[wave][kb < G ? kb : 0];
+  int32_t* st_i = stage_slot[wave][kb < G ? kb : 0];
+  constexpr int ES = Tile::kElemBytes, T = kRowsPerWaveIter;
+  const char* Kbg = static_cast<const char*>(K) + Rows::base(b, g, stride_b, stride_h) * ES;
+  int run = 0, staged = 0;                               // my head's survivors in global memory, and waiting in LDS
+
+  // (survivors are staged so that the loop holds no global store: a wait for a load would wait for those before it)
+  auto flush = [&]() {
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      const int cnt_h = __shfl(staged, 16 * h);
+      const int run_h = __shfl(run, 16 * h);
+      float* dsc = score + (head0 + h) * score_stride + out0 + run_h;
+      int32_t* dsl = slot_out + (head0 + h) * score_stride + out0 + run_h;
+      for (int e = lane; e < cnt_h; e += 64) {
+        dsc[e] = stage_score[wave][h][e];
+        dsl[e] = stage_slot[wave][h][e];
+      }
+    }
+    run += staged;
+    staged = 0;
+  };
+  // the row of list entry e0 + lane (past the end: the last one, never kept)
+  auto ids_of = [&](int e0) { return lo + list[c0 + (e0 + lane < cnt ? e0 + lane : cnt - 1)]; };
+  auto issue = [&](Tile& Bt, int (&rows)[4], int id, int phys) {
+    int prow[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      rows[t] = __shfl(id, 16 * t + j);
+      prow[t] = kPaged ? __shfl(phys, 16 * t + j) : rows[t];
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) Bt.load_row(t, Kbg + Rows::offset(page, prow[t], stride_b, stride_n) * ES, kb);
+  };
+  auto consume = [&](Tile& Bt, int (&rows)[4], int e0) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) acc = mfma16(A[kk], Bt.operand(t, kk), acc);
+      const float v = Split3<Op>::sum(acc) * scale;
+      const bool pass = kb < G && e0 + 16 * t + j < cnt && v >= tau;
+      const uint32_t gm = (uint32_t)(__ballot(pass) >> (16 * kb)) & 0xFFFFu;   // my head's 16 rows
+      if (pass) {
+        const int o = staged + __popc(gm & below);
+        st_s[o] = v;
+        st_i[o] = rows[t];
+      }
+      staged += __popc(gm);
+    }
+    if (__ballot(staged > kRangeStage - T)) flush();      // no room for one more tile
+  };
+  // One tile in flight per wave and sixteen waves per CU (two tiles in flight do not fit the registers of that many).
+  // Paged cache: the block-table lookup of the next tile is issued before the loads of this one, so that the wait for it
+  // does not wait for them (memory operations complete in order).
+  auto lookup = [&](int id) { return Rows::phys(page, b, id); };
+  Tile Bt;
+  int rows[4];
+  int id = ids_of(0);
+  int phys = lookup(id);
+  for (int e0 = 0; e0 < cnt; e0 += T) {
+    const int id_now = id, phys_now = phys;
+    id = ids_of(e0 + T);
+    if constexpr (kPaged) {
+      asm volatile("" ::"v"(phys_now));
+      phys = lookup(id);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    issue(Bt, rows, id_now, phys_now);
+    consume(Bt, rows, e0);
+  }
+  flush();
+  if (j == 0 && kb < G) seg_count[head * nseg + piece] = cnt << 16 | run;
+}
+
+// ----------------------------------------------------------------------------- launcher
+// Rows per range, or 0 where the separate kernels are faster: they cut all candidates into equal parts for two tiles in
+// flight per wave, which wins once there is enough work to fill the chip.
+//   From the Top-k: every workgroup reads the Top-k rows of its group, 5 us in which it loads no rows, so all of them have
+//   to be resident at once (four per CU) and there may be no more rows than 1024 ranges of 1024.  Steps, separate ->
+//   together: 8 groups x 32K rows 34.6 -> 28 us, 24 x 20K (paged fp16) 31.9 -> 23.6; but 64 x 32K 65.4 -> 69 us, paged FP8
+//   128 x 64K 82 -> 98.  Ranges of 512 rows while that leaves at most 512 of them, else 1024 (512 to 2048 differ by 3 %).
+//   From the table flags, a few words per range: candidates are 4 % of the rows, so ranges of 2048 give a wave 20 rows.
+//   64 x 32K: 23.6 -> 16.1 us for the two kernels.  Up to 4 million rows.
+int range_rows(const Shape& s, bool tables) {
+  const int64_t groups = (int64_t)s.B * s.Hkv;
+  auto ranges = [&](int rows) { return groups * ((s.Lcap + rows - 1) / rows); };
+  int range = tables ? 2048 : (ranges(512) <= 512 ? 512 : 1024);
+  if (groups * s.Lcap > (tables ? 4 << 20 : 1 << 20)) return 0;
+  while ((s.Lcap + range - 1) / range > 256) range *= 2;   // at most 1024 pieces per head
+  return range <= kRangeMax ? range : 0;
+}
+
+hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, const RangeSource& from,
+                              const float* thr_state, float margin, float* score, int32_t* slot_out,
+                              int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words,
+                              int range, int32_t* flags, hipStream_t st) {
+  dim3 grid((s.Lcap + range - 1) / range, s.B * s.Hkv), block(kScoreThreads);
+  const float sc = 0.08838834764831845f;   // 1/sqrt(128)
+  const int kind = kv.k_fp8 ? kKindFp8 : (kv.f16 ? kKindF16 : kKindBf16);
+  const bool paged = kv.page.table != nullptr, tables = from.prev_topk == nullptr;
+  bool launched = false;
+#define LFPS_LAUNCH_RANGE(GG, PAGED, KIND, TABLES)                                                                      \
+  if (!launched && s.G == GG && paged == PAGED && kind == KIND && tables == TABLES) {                                  \
+    hipLaunchKernelGGL((k_range_score<GG, PAGED, KIND, TABLES>), grid, block, (size_t)range * 2, st, s, q, kv.k,        \
+                       kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, from, thr_state, margin, score,    \
+                       slot_out, score_stride, seg_count, nseg, bitmap, bitmap_words, range, sc, flags);                \
+    launched = true;                                                                                                    \
+  }
+#define LFPS_RANGE_KINDS(GG, PAGED, TABLES)          \
+  LFPS_LAUNCH_RANGE(GG, PAGED, kKindBf16, TABLES)    \
+  LFPS_LAUNCH_RANGE(GG, PAGED, kKindFp8, TABLES)     \
+  LFPS_LAUNCH_RANGE(GG, PAGED, kKindF16, TABLES)
+#define LFPS_RANGE_GROUP(GG)                                              \
+  LFPS_RANGE_KINDS(GG, false, false) LFPS_RANGE_KINDS(GG, true, false)    \
+  LFPS_RANGE_KINDS(GG, false, true) LFPS_RANGE_KINDS(GG, true, true)
+  LFPS_RANGE_GROUP(1) LFPS_RANGE_GROUP(2) LFPS_RANGE_GROUP(4)
+#undef LFPS_RANGE_GROUP
+#undef LFPS_RANGE_KINDS
+#undef LFPS_LAUNCH_RANGE
+  return launched ? hipGetLastError() : hipErrorInvalidValue;
+}
+
+}  // namespace lfps

@@ -14,6 +14,12 @@
 //                            launches behind this kernel.
 //   k_select_attend          selects from a head's full score row (all candidates): contexts without the filter.
 //
+// Both leave the k-th best score behind as the next step's threshold, but -inf (keep every candidate) for a head with
+// fewer than keep_ratio * k candidates: there is little to filter then, and one head that the filter leaves short costs the
+// step its unfiltered pass, 25 us.  keep_ratio is 2 for the memoryless form and 8 for the table form, whose candidate sets
+// change in size by a half from one step to the next: table steps of 8 x 32K, k = 1024 of about 1300 candidates: 15 to 60 of
+// 256 heads took the unfiltered pass, and this kernel 44 us instead of 19.
+//
 // For few heads both kernels are a chain of latencies: at 32 heads, k = 1024, the first one took 19.8 us, of which
 // 1.8 us went into the piece counts, 6.3 into finding and fetching the survivors (twelve searches per thread, whatever
 // their number, with 64-bit geometry), 4.4 into the select over LDS and 5.4 into the attention, which fetched the pairs
@@ -29,6 +35,9 @@
 #include <type_traits>
 
 namespace lfps {
+
+// Is the k-th best of c candidates a threshold worth remembering?
+__device__ __forceinline__ bool filter_pays(int c, int ksel, int keep_ratio) { return c / keep_ratio >= ksel; }
 
 constexpr int kSelRowsMax = 16384;    // selected rows of a head that pass through LDS; more go through global memory
 
@@ -81,7 +90,8 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     const int32_t* __restrict__ cand, int32_t* __restrict__ cand_count, const int64_t* __restrict__ group_start,
     int64_t* __restrict__ line_total, int range, const uint32_t* __restrict__ bitmap, int bitmap_words,
     const int32_t* __restrict__ kk, int32_t* topk_idx, float* topk_score,
-    float* __restrict__ thr_state, float margin, const int32_t* __restrict__ skip_if, int32_t* __restrict__ rescored,
+    float* __restrict__ thr_state, float margin, int keep_ratio, const int32_t* __restrict__ skip_if,
+    int32_t* __restrict__ rescored,
     const float* __restrict__ q, const void* __restrict__ K, float scale, int32_t* __restrict__ flags,
     const T* __restrict__ V, int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage page,
     const int32_t* __restrict__ seq_lens, float* __restrict__ out) {
@@ -188,6 +198,8 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     if (out && tid < kD) out[(int64_t)bh * kD + tid] = 0.f;
     return;
   }
+  float* thr_out = filter_pays(c, ksel, keep_ratio) ? thr_state + bh : nullptr;
+  if (!thr_out && tid == 0) thr_state[bh] = -INFINITY;      // (every thread has read it before the barrier)
   float* sc = score + (int64_t)bh * score_stride;
   int32_t* sl = slot + (int64_t)bh * score_stride;
   const int32_t* cbg = ranges ? sl : (cand ? cand + (int64_t)bg * s.cand_cap : nullptr);
@@ -261,7 +273,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
         if constexpr (E <= kRegElems / 2) prow[u] = RowMap<kPaged>::phys(page, b, ok ? pos[u] : 0);
         if (!ok) pos[u] = -1;
       }
-      select_registers<NT, E>(sm, v, n_el, ksel, tau, unfiltered, thr_state + bh, [&](int rank, int u, float top) {
+      select_registers<NT, E>(sm, v, n_el, ksel, tau, unfiltered || tau == -INFINITY, thr_out, [&](int rank, int u, float top) {
         const bool ok = pos[u] >= 0;
         oi[rank] = pos[u];
         os[rank] = ok ? v[u] : 0.f;
@@ -274,7 +286,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     else if (n_el <= 8 * NT) run(std::integral_constant<int, 8>{});
     else run(std::integral_constant<int, kRegElems>{});
   } else {
-    const float top = select_stream<NT>(sm, sc, c, ksel, cbg, oi, os, thr_state + bh, n);
+    const float top = select_stream<NT>(sm, sc, c, ksel, cbg, oi, os, thr_out, n);
     __syncthreads();                                // this workgroup's stores of (position, score) before its loads of them
     if (ksel > kSelRowsMax) {
       if (out)
@@ -298,7 +310,7 @@ template <typename T, bool kPaged>
 __global__ __launch_bounds__(kSelThreads) void k_select_attend(
     Shape s, const float* __restrict__ score, int64_t score_stride, const int32_t* __restrict__ cand,
     const int32_t* __restrict__ cand_count, const int32_t* __restrict__ kk, int32_t* topk_idx, float* topk_score,
-    int cache_elems, float* __restrict__ thr_state,
+    int cache_elems, float* __restrict__ thr_state, int keep_ratio,
     const int32_t* __restrict__ skip_if, const T* __restrict__ V, int64_t stride_b, int64_t stride_h, int64_t stride_n,
     KvPage page, const int32_t* __restrict__ seq_lens, float* __restrict__ out) {
   constexpr int NT = kSelThreads;
@@ -328,6 +340,10 @@ __global__ __launch_bounds__(kSelThreads) void k_select_attend(
     if (thr_out && tid == 0) *thr_out = -INFINITY;
     if (tid < kD) out[(int64_t)bh * kD + tid] = 0.f;
     return;
+  }
+  if (thr_out && !filter_pays(c, ksel, keep_ratio)) {
+    if (tid == 0) *thr_out = -INFINITY;
+    thr_out = nullptr;
   }
   const float* sc = score + (int64_t)bh * score_stride;
   const int32_t* cbg = cand + ((int64_t)b * s.Hkv + g) * s.cand_cap;
@@ -454,7 +470,7 @@ hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, 
                                        const int32_t* cand, int32_t* cand_count, const int64_t* group_start,
                                        int64_t* line_total, int range, const uint32_t* bitmap, int bitmap_words,
                                        const int32_t* k, int32_t* topk_idx, float* topk_score,
-                                       float* thr_state, float margin, const int32_t* skip_if, int32_t* rescored,
+                                       float* thr_state, float margin, int keep_ratio, const int32_t* skip_if, int32_t* rescored,
                                        const float* q, int32_t* flags, const KvView& kv, float* out, hipStream_t st) {
   const int nt = filter_select_threads(s);
   const float scale = 0.08838834764831845f;   // 1/sqrt(128)
@@ -477,7 +493,7 @@ hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, 
     hipLaunchKernelGGL((k_filter_select_attend<TYPE, PAGED, KIND, NT>), dim3(s.B * s.Hq), dim3(NT),                     \
                        (size_t)filter_select_attend_lds(s), st, s, score, slot, score_stride, seg_count, seg_rows,      \
                        nseg, cand, cand_count, group_start, line_total, range, bitmap, bitmap_words, k, topk_idx,       \
-                       topk_score, thr_state, margin,                                                                   \
+                       topk_score, thr_state, margin, keep_ratio,                                                       \
                        skip_if, rescored, q, kv.k, scale, flags, (const TYPE*)kv.v, kv.stride_b, kv.stride_h,           \
                        kv.stride_n, kv.page, kv.seq_lens, out);                                                         \
     launched = true;                                                                                                    \
@@ -491,13 +507,13 @@ hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, 
 template <typename T>
 static hipError_t launch_sa_t(const Shape& s, const float* score, int64_t score_stride, const int32_t* cand,
                               const int32_t* cand_count, const int32_t* k, int32_t* topk_idx, float* topk_score,
-                              float* thr_state, const int32_t* skip_if, const KvView& kv, float* out,
+                              float* thr_state, int keep_ratio, const int32_t* skip_if, const KvView& kv, float* out,
                               hipStream_t st) {
   const int ce = select_attend_cache(s);
   const T* V = (const T*)kv.v;
 #define LFPS_LAUNCH_SA(PAGED)                                                                                         \
   hipLaunchKernelGGL((k_select_attend<T, PAGED>), dim3(s.B * s.Hq), dim3(kSelThreads), (size_t)select_attend_lds(s),  \
-                     st, s, score, score_stride, cand, cand_count, k, topk_idx, topk_score, ce, thr_state, skip_if, V, \
+                     st, s, score, score_stride, cand, cand_count, k, topk_idx, topk_score, ce, thr_state, keep_ratio, skip_if, V, \
                      kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, out)
   if (kv.page.table) {
     LFPS_LAUNCH_SA(true);
@@ -510,9 +526,9 @@ static hipError_t launch_sa_t(const Shape& s, const float* score, int64_t score_
 
 hipError_t launch_select_attend(const Shape& s, int dtype, const float* score, int64_t score_stride, const int32_t* cand,
                                 const int32_t* cand_count, const int32_t* k, int32_t* topk_idx, float* topk_score,
-                                float* thr_state, const int32_t* skip_if, const KvView& kv, float* out,
+                                float* thr_state, int keep_ratio, const int32_t* skip_if, const KvView& kv, float* out,
                                 hipStream_t st) {
-#define LFPS_SA_ARGS s, score, score_stride, cand, cand_count, k, topk_idx, topk_score, thr_state, skip_if, kv, out, st
+#define LFPS_SA_ARGS s, score, score_stride, cand, cand_count, k, topk_idx, topk_score, thr_state, keep_ratio, skip_if, kv, out, st
   if (dtype == LFPS_BF16 && kv.v_fp8) return launch_sa_t<uint8_t>(LFPS_SA_ARGS);
   if (dtype == LFPS_F16) return launch_sa_t<_Float16>(LFPS_SA_ARGS);
   if (dtype == LFPS_BF16) return launch_sa_t<uint16_t>(LFPS_SA_ARGS);

@@ -533,11 +533,10 @@ __global__ __launch_bounds__(64) void k_head_sparsity(Shape s, const float* __re
       topk_idx[(int64_t)bh * s.kmax + i] = -1;
       if (topk_score) topk_score[(int64_t)bh * s.kmax + i] = 0.f;
     }
-    // A head bypassed since the history was reset has no k-th score to remember, and a group with such a
-    // head would be taken as "no previous step" by the filtered scoring pass at every step.  +inf keeps
-    // nothing for this head there (its select is skipped anyway) and lets the group's other heads be
-    // filtered; when the head is no longer bypassed its first select falls back to the unfiltered pass.
-    if (thr_state && lane == 0 && isnan(thr_state[bh])) thr_state[bh] = INFINITY;
+    // A bypassed head has no k-th score to remember, and a group with a NaN there would be taken as "no previous step" by
+    // the filtered scoring pass at every step; -inf keeps all of the group's candidates for this head, which costs little
+    // (its select is skipped) and spares the first step in which it is not bypassed the unfiltered pass.
+    if (thr_state && lane == 0) thr_state[bh] = -INFINITY;
   }
 }
 

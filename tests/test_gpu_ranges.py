@@ -112,3 +112,26 @@ def test_table_steps(B, Hq, Hkv, L, k, r, n_sink, dtype, page):
             assert torch.equal(x, y), (name, t, int((x != y).sum()))
     for ctx in pair:
         ctx.close()
+
+
+@pytest.mark.parametrize("L,k", [(1200, 650), (3000, 1600)])
+def test_a_budget_of_most_candidates_keeps_them_all(L, k):
+    """A head whose budget takes more than half of its candidates remembers no threshold: other queries do not send it
+    through the unfiltered pass."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    cache = _cache(1, 2, L, "bf16", 0, g)
+    a, b = _pair(batch=1, n_q_heads=8, n_kv_heads=2, kv_dtype="bf16", max_seq_len=L, max_k=k, radius=0)
+    seq, ks = (torch.tensor([x], dtype=torch.int32, device=DEV) for x in (L, k))
+    prev = torch.randperm(L, device=DEV, generator=g)[:k].sort().values.to(torch.int32).expand(1, 8, k).contiguous()
+    for t in range(3):
+        q = torch.randn((1, 8, 128), device=DEV, generator=g) * (1.0, 3.0, 0.1)[t]
+        res = []
+        for ctx in (a, b):
+            idx, out = torch.zeros((1, 8, k), dtype=torch.int32, device=DEV), torch.zeros((1, 8, 128), device=DEV)
+            ctx.lfps_step(q, ctx.kv_view(cache[0], cache[1], seq), prev, ks, idx, out)
+            res.append((idx, out))
+        assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+    assert a.lfps_poll_rescored() == 0
+    a.close()
+    b.close()
