@@ -78,12 +78,12 @@ __device__ __forceinline__ void list_from_global(SelRow* list, const KvPage& pag
 // `sgm` is what wave w_first + sgm took of it, w_first = pg / S: the group's slots [lo, hi).  The piece holds
 // seg_count[bh, sgm] (score, row position) pairs at offset lo of the head's score / position rows, ascending in
 // position within and across pieces.  Workgroup 0 leaves *line_total at zero for the next step.
-// range > 0: the lists of the range kernel instead (range_geometry.h): piece counts are candidates << 16 | survivors, the
+// kRanges: the lists of the range kernel instead (range_geometry.h): piece counts are candidates << 16 | survivors, the
 // group's candidate count is their sum (left in cand_count by the group's first head), the candidates are a bitmap.
 // margin: what the scoring pass subtracted from thr_state.
 // The unfiltered pass needs the query, the K rows (format kKind) and the group's candidate list (cand; NULL when the
 // candidates are all rows 0 .. count-1, the exact Top-k baseline's dense pass).
-template <typename T, bool kPaged, int kKind, int NT>
+template <typename T, bool kPaged, int kKind, int NT, bool kRanges>
 __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     Shape s, float* score, int32_t* slot, int64_t score_stride,
     const int32_t* __restrict__ seg_count, const int32_t* __restrict__ seg_rows_in, int nseg,
@@ -103,14 +103,13 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   extern __shared__ char dyn[];                    // the attention's partial sums, then the list of selected rows
   AttendShared& as = *reinterpret_cast<AttendShared*>(dyn);
   SelRow* list = reinterpret_cast<SelRow*>(dyn + sizeof(AttendShared));
-  const bool ranges = range > 0;
-  if (!ranges && blockIdx.x == 0 && threadIdx.x == 0) *line_total = 0;   // the scoring pass that read it has finished
+  if (!kRanges && blockIdx.x == 0 && threadIdx.x == 0) *line_total = 0;   // the scoring pass that read it has finished
   const int bh = head_of_block(s, blockIdx.x);     // the heads of a KV group on one XCD: they share V rows in its L2
   const int b = bh / s.Hq, h = bh % s.Hq, g = h / s.G;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int bg = b * s.Hkv + g;
   const bool skipped = skip_if && skip_if[bh] != 0;  // bypassed head: its rows were written by the gate
-  if (skipped && !(ranges && h % s.G == 0)) return;
+  if (skipped && !(kRanges && h % s.G == 0)) return;
   int raw[kPieces];                                  // piece counts of this head, masked once the geometry is known
 #pragma unroll
   for (int u = 0; u < kPieces; ++u) {
@@ -118,21 +117,21 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     raw[u] = sgm < nseg ? seg_count[(int64_t)bh * nseg + sgm] : 0;
   }
   const float tau = thr_state[bh] - margin;          // what the survivors have reached
-  int c = ranges ? 0 : cand_count[bg];
+  int c = kRanges ? 0 : cand_count[bg];
   int kb = kk[b];
   int n = seq_lens[b];
-  int S = ranges ? 64 : *seg_rows_in;                // chosen by the scoring pass of this step
-  const int64_t pg = ranges ? 0 : group_start[bg];
+  int S = kRanges ? 64 : *seg_rows_in;                // chosen by the scoring pass of this step
+  const int64_t pg = kRanges ? 0 : group_start[bg];
   c = c < 0 ? 0 : (c > s.cand_cap ? s.cand_cap : c);
   kb = kb < 0 ? 0 : (kb > s.kmax ? s.kmax : kb);
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   S = S < 64 ? 64 : S;
   // the group's slots relative to the part it starts in: piece sgm is [sgm * S - r0, (sgm + 1) * S - r0)
   const int r0 = (pg >> 32) == 0 ? (int)((uint32_t)pg % (uint32_t)S) : (int)(pg % S);
-  const RangePieces geo(n, ranges ? range : 64);
-  int np = ranges ? geo.count : (c > 0 ? (r0 + c - 1) / S + 1 : 0);         // pieces my group was cut into
+  const RangePieces geo(n, kRanges ? range : 64);
+  int np = kRanges ? geo.count : (c > 0 ? (r0 + c - 1) / S + 1 : 0);         // pieces my group was cut into
   np = np > nseg ? nseg : np;
-  auto piece_lo = [&](int sgm) { return ranges ? geo.start(sgm) : (sgm > 0 ? sgm * S - r0 : 0); };
+  auto piece_lo = [&](int sgm) { return kRanges ? geo.start(sgm) : (sgm > 0 ? sgm * S - r0 : 0); };
 
   // exclusive prefix of the piece counts (kPieces consecutive pieces per thread)
   for (int i = tid; i < 2 * NT; i += NT) sm.hist[i] = 0u;
@@ -143,7 +142,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   for (int u = 0; u < kPieces; ++u) {
     const int sgm = kPieces * tid + u;
     cntp[u] = 0;
-    if (sgm < np && ranges) {
+    if (sgm < np && kRanges) {
       const int room = range >> 2;                             // rows the piece covers at most
       const int all = min(raw[u] >> 16 & 0xFFFF, room);
       cntp[u] = min(raw[u] & 0xFFFF, all);
@@ -157,12 +156,12 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   }
   const int inc = wave_inclusive_sum(cnt);
   if (lane == 63) wtot[wv] = inc;
-  if (ranges) {
+  if (kRanges) {
     cands = wave_inclusive_sum(cands);
     if (lane == 63) ctot[wv] = cands;
   }
   __syncthreads();
-  if (ranges) {
+  if (kRanges) {
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) c += ctot[w];
     if (tid == 0 && h % s.G == 0) cand_count[bg] = c;
@@ -202,8 +201,8 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   if (!thr_out && tid == 0) thr_state[bh] = -INFINITY;      // (every thread has read it before the barrier)
   float* sc = score + (int64_t)bh * score_stride;
   int32_t* sl = slot + (int64_t)bh * score_stride;
-  const int32_t* cbg = ranges ? sl : (cand ? cand + (int64_t)bg * s.cand_cap : nullptr);
-  if (unfiltered && ranges) {                       // the group's candidates from the bitmap, ascending, over the survivors
+  const int32_t* cbg = kRanges ? sl : (cand ? cand + (int64_t)bg * s.cand_cap : nullptr);
+  if (unfiltered && kRanges) {                       // the group's candidates from the bitmap, ascending, over the survivors
     const uint32_t* bm = bitmap + (int64_t)bg * bitmap_words;
     const int W = (n + 31) >> 5, per = (W + NT - 1) / NT;
     const int w0 = tid * per < W ? tid * per : W, w1 = w0 + per < W ? w0 + per : W;
@@ -420,8 +419,12 @@ static int select_attend_lds(const Shape& s) {
 }
 
 // The instantiations of k_filter_select_attend: V type and K format go together (bf16 V with bf16 or FP8 keys,
-// FP8 V with FP8 keys, fp16 V with fp16 keys), times paged or not, times the threads per head.
-#define LFPS_FSA_FOR_EACH_NT(X, TYPE, PAGED, KIND) X(TYPE, PAGED, KIND, 256) X(TYPE, PAGED, KIND, 512) X(TYPE, PAGED, KIND, 1024)
+// FP8 V with FP8 keys, fp16 V with fp16 keys), times paged or not, times the threads per head, times the form
+// of the lists.
+#define LFPS_FSA_FOR_EACH_NT(X, TYPE, PAGED, KIND)                                \
+  X(TYPE, PAGED, KIND, 256, false) X(TYPE, PAGED, KIND, 256, true)                \
+  X(TYPE, PAGED, KIND, 512, false) X(TYPE, PAGED, KIND, 512, true)                \
+  X(TYPE, PAGED, KIND, 1024, false) X(TYPE, PAGED, KIND, 1024, true)
 #define LFPS_FSA_FOR_EACH(X)                               \
   LFPS_FSA_FOR_EACH_NT(X, uint16_t, false, kKindBf16)      \
   LFPS_FSA_FOR_EACH_NT(X, uint16_t, true, kKindBf16)       \
@@ -448,8 +451,9 @@ hipError_t configure_select_attend(const Shape& s, int dtype, bool k_fp8, bool v
   const int kind = k_fp8 ? kKindFp8 : (dtype == LFPS_F16 ? kKindF16 : kKindBf16);
   const int nt = filter_select_threads(s);
   const int fb = (int)sizeof(AttendShared) + kSelRowsMax * (int)sizeof(SelRow), sb = kCacheElems * 4;
-#define LFPS_RAISE_FSA(TYPE, PAGED, KIND, NT) \
-  if (vt == v_type_code<TYPE>() && kind == KIND && nt == NT) raise((const void*)k_filter_select_attend<TYPE, PAGED, KIND, NT>, fb);
+#define LFPS_RAISE_FSA(TYPE, PAGED, KIND, NT, RANGES)         \
+  if (vt == v_type_code<TYPE>() && kind == KIND && nt == NT)  \
+    raise((const void*)k_filter_select_attend<TYPE, PAGED, KIND, NT, RANGES>, fb);
   LFPS_FSA_FOR_EACH(LFPS_RAISE_FSA)
 #undef LFPS_RAISE_FSA
 #define LFPS_RAISE_SA(TYPE)                                     \
@@ -488,9 +492,9 @@ hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, 
     return hipErrorInvalidValue;              // the filtered pass exists for 16-bit and FP8 caches only
   }
   bool launched = false;
-#define LFPS_LAUNCH_FSA(TYPE, PAGED, KIND, NT)                                                                          \
-  if (!launched && vt == v_type_code<TYPE>() && paged == PAGED && nt == NT && kind == KIND) {                          \
-    hipLaunchKernelGGL((k_filter_select_attend<TYPE, PAGED, KIND, NT>), dim3(s.B * s.Hq), dim3(NT),                     \
+#define LFPS_LAUNCH_FSA(TYPE, PAGED, KIND, NT, RANGES)                                                                  \
+  if (!launched && vt == v_type_code<TYPE>() && paged == PAGED && nt == NT && kind == KIND && (range > 0) == RANGES) { \
+    hipLaunchKernelGGL((k_filter_select_attend<TYPE, PAGED, KIND, NT, RANGES>), dim3(s.B * s.Hq), dim3(NT),             \
                        (size_t)filter_select_attend_lds(s), st, s, score, slot, score_stride, seg_count, seg_rows,      \
                        nseg, cand, cand_count, group_start, line_total, range, bitmap, bitmap_words, k, topk_idx,       \
                        topk_score, thr_state, margin, keep_ratio,                                                       \
