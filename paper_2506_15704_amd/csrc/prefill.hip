@@ -51,32 +51,20 @@ __device__ __forceinline__ bool stage_hist_operands(Op* lds, const float* __rest
   for (int u = threadIdx.x; u < nq * 64; u += kHistWaves * 64) {
     const int jq = u >> 6, h = (u >> 4) & 3, kk = (u >> 2) & 3, kb = u & 3;
     Op* e = lds + (jq * 4 + kk) * 64 + kb * 16 + 4 * h;
-    union {
-      Op v;
-      uint16_t x[8];
-    } a[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) a[t].x[c] = 0;
-    if (h < G) {
-      const float4* p = reinterpret_cast<const float4*>(q0 + jq * q_stride + (head0 + h) * kD) + 2 * (kk + 4 * kb);
-      const float4 lo = p[0], hi = p[1];
-      float f[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    const float4* p = reinterpret_cast<const float4*>(q0 + jq * q_stride + (head0 + (h < G ? h : 0)) * kD) + 2 * (kk + 4 * kb);
+    const float4 lo = p[0], hi = p[1];
+    float f[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    if constexpr (Split3<Op>::kHalf) {
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
-        if constexpr (Split3<Op>::kHalf) {
-          if (fabsf(f[c]) > 65504.0f) {
-            clipped = true;
-            f[c] = copysignf(65504.0f, f[c]);
-          }
+        if (fabsf(f[c]) > 65504.0f) {
+          clipped |= h < G;
+          f[c] = copysignf(65504.0f, f[c]);
         }
-#pragma unroll
-        for (int t = 0; t < 3; ++t) a[t].x[c] = Split3<Op>::term(f[c], t);
       }
     }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) e[t] = a[t].v;
+    for (int t = 0; t < 4; ++t) e[t] = Split3<Op>::terms(f, h < G ? t : 3);
   }
   return clipped;
 }

@@ -13,44 +13,51 @@ constexpr int kRowsPerWaveIter = 64;         // rows a wave scores per loop iter
 // Storage format of the K rows a scoring kernel reads.
 enum { kKindBf16 = 0, kKindFp8 = 1, kKindF16 = 2 };
 
-// Round-to-nearest-even bf16 bits of x (the building block of the three-term split q = q0 + q1 + q2).
-__device__ __forceinline__ uint16_t bf16_rne_bits(float x) {
-  uint32_t u = __float_as_uint(x);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-// Term t (0, 1, 2) of the three-way split of an fp32 query element into the operand's 16-bit format, as bits,
-// and the sum of the three MFMA results that undoes the split.
+// Term t (0, 1, 2; 3: zeros) of the three-way split of eight fp32 query elements into the operand's 16-bit format, and the
+// sum of the three MFMA results that undoes the split.  Every wave of a scoring kernel splits 32 elements per lane before
+// its first product, so this is kept short: two elements per hardware conversion (round to nearest even), and the term is
+// chosen before the last one: 8 instructions an element (rounding in integer arithmetic took about 30: four steps of
+// 8 x 32K 262.5 against 260.2 us, the two passes of a hand-over with 32 queries 50 + 62 against 47 + 60.5 us).
 template <typename Op>
 struct Split3;
 template <>
 struct Split3<bf16x8> {
-  using Elem = uint16_t;
   static constexpr bool kHalf = false;
-  __device__ static __forceinline__ uint16_t term(float f, int t) {
-    const uint16_t t0 = bf16_rne_bits(f);
-    const float r1 = f - __uint_as_float((uint32_t)t0 << 16);
-    const uint16_t t1 = bf16_rne_bits(r1);
-    const float r2 = r1 - __uint_as_float((uint32_t)t1 << 16);
-    const uint16_t t2 = bf16_rne_bits(r2);
-    return t == 0 ? t0 : (t == 1 ? t1 : t2);            // selected without branching
+  __device__ static __forceinline__ bf16x8 terms(const float (&f)[8], int t) {
+    bf16x8 out;
+#pragma unroll
+    for (int c = 0; c < 8; c += 2) {
+      const f32x2 x = {f[c], f[c + 1]};
+      const f32x2 r1 = x - __builtin_convertvector(__builtin_convertvector(x, bf16x2), f32x2);
+      const f32x2 r2 = r1 - __builtin_convertvector(__builtin_convertvector(r1, bf16x2), f32x2);
+      const f32x2 y = t == 0 ? x : (t == 1 ? r1 : (t == 2 ? r2 : f32x2{0.f, 0.f}));
+      const bf16x2 b = __builtin_convertvector(y, bf16x2);
+      out[c] = b[0];
+      out[c + 1] = b[1];
+    }
+    return out;
   }
   __device__ static __forceinline__ float sum(const f32x4& acc) { return (acc[0] + acc[1]) + acc[2]; }
 };
 template <>
 struct Split3<f16x8> {
-  using Elem = _Float16;
   static constexpr bool kHalf = true;
   // q = t0 + t1 / 2^11 + t2 / 2^22 (11 significant bits per term; the scaling keeps t1, t2 normal)
-  __device__ static __forceinline__ uint16_t term(float f, int t) {
-    const _Float16 t0 = (_Float16)f;
-    const float r1 = f - (float)t0;
-    const _Float16 t1 = (_Float16)(r1 * 2048.0f);
-    const float r2 = r1 - (float)t1 * (1.0f / 2048.0f);
-    const _Float16 t2 = (_Float16)(r2 * 4194304.0f);
-    const _Float16 sel = t == 0 ? t0 : (t == 1 ? t1 : t2);
-    return __builtin_bit_cast(uint16_t, sel);
+  __device__ static __forceinline__ f16x8 terms(const float (&f)[8], int t) {
+    f16x8 out;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const _Float16 t0 = (_Float16)f[c];
+      const float r1 = f[c] - (float)t0;
+      const _Float16 t1 = (_Float16)(r1 * 2048.0f);
+      const float r2 = r1 - (float)t1 * (1.0f / 2048.0f);
+      const _Float16 t2 = (_Float16)(r2 * 4194304.0f);
+      out[c] = t == 0 ? t0 : (t == 1 ? t1 : (t == 2 ? t2 : (_Float16)0.0f));
+    }
+    return out;
   }
   __device__ static __forceinline__ float sum(const f32x4& acc) {
     return (acc[0] + acc[1] * (1.0f / 2048.0f)) + acc[2] * (1.0f / 4194304.0f);
@@ -86,7 +93,7 @@ __device__ __forceinline__ bool load_query_operand(Op (&A)[4], const float* __re
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
     float f[8] = {x[kk][0].x, x[kk][0].y, x[kk][0].z, x[kk][0].w, x[kk][1].x, x[kk][1].y, x[kk][1].z, x[kk][1].w};
-    if constexpr (sizeof(typename Split3<Op>::Elem) == sizeof(_Float16) && Split3<Op>::kHalf) {
+    if constexpr (Split3<Op>::kHalf) {
 #pragma unroll
       for (int c = 0; c < 8; ++c) {
         if (fabsf(f[c]) > 65504.0f) {               // also +-inf; a NaN goes through as in the other formats
@@ -95,13 +102,7 @@ __device__ __forceinline__ bool load_query_operand(Op (&A)[4], const float* __re
         }
       }
     }
-    union {
-      Op v;
-      uint16_t h[8];
-    } a;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) a.h[c] = live ? Split3<Op>::term(f[c], t) : (uint16_t)0;
-    A[kk] = a.v;
+    A[kk] = Split3<Op>::terms(f, live ? t : 3);
   }
   return clipped;
 }
