@@ -178,13 +178,35 @@ __global__ __launch_bounds__(kTabThreads) void k_table_flags(Shape s, const floa
   }
 }
 
+// Once the scale has become small it is folded into the stored values (A <- g A, g <- 1; the values g A
+// do not change).  The head decides for itself from its own state, at the end of the update that
+// made the scale small, so no host-side count is involved and a recorded graph folds when an eager run would.
+// This step's additions may have been made in L2 (atomics): they are waited for, and the entries are then read
+// with device-scope loads, which do not look at this CU's vector cache (it may hold the old values).
+__device__ __forceinline__ void fold_scale(const Shape& s, int bh, double g1, float* ver, float* tab_sla, double* st,
+                                           int tid, int threads) {
+  if (g1 < kFoldBelow) {                                     // workgroup-uniform
+    __threadfence();
+    __syncthreads();
+    float* sla_all = tab_sla + (int64_t)bh * 2 * s.Lcap;
+    for (int i = tid; i < s.Lcap; i += threads) {
+      const float x = __hip_atomic_load(&ver[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      ver[i] = (float)(g1 * (double)x);
+    }
+    for (int i = tid; i < 2 * s.Lcap; i += threads) {
+      const float x = __hip_atomic_load(&sla_all[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sla_all[i] = (float)(g1 * (double)x);
+    }
+    __syncthreads();
+    if (tid == 0) st[TS_G] = 1.0;
+  }
+}
+
 // ----------------------------------------------------------------------------- update (Eq. 10)
 // grid B*Hq.  The step saw n rows and selected idx[bh, 0:k_b] with scaled scores sc; entries outside
 // [n_sink, n) are padding.  w = softmax over the valid entries; delta = w - 1/(2 * valid).
-// kDistinct: the positions of a head's list are known to be distinct (the library's own Top-k), so an entry's old
-// value can be read beside the addition; otherwise (a caller's list, where a position may appear twice) every
-// addition returns the value it found, which keeps the moments exact for a repeated position too.
-template <bool kDistinct>
+// The positions are a caller's list, in which one may appear twice: every addition returns the value it found, which keeps
+// the moments exact then too.
 __global__ __launch_bounds__(kTabThreads) void k_table_update(Shape s, float* __restrict__ tab_ver,
                                                               float* __restrict__ tab_sla, double* __restrict__ state,
                                                               const int32_t* __restrict__ seq_lens,
@@ -250,16 +272,8 @@ __global__ __launch_bounds__(kTabThreads) void k_table_update(Shape s, float* __
       const float inc = (float)(delta / g1);
       // (hardware fp32 adds in L2.)  Position p in the next frame (cnt + 1) is the slot of p - 1 in this one (for
       // p = 0 the never-written slot just below the frame).
-      float old_v, old_s = 0.f;
-      if constexpr (kDistinct) {
-        old_v = ver[p];
-        if (p - 1 >= s.n_sink) old_s = sla[p - 1];
-        unsafeAtomicAdd(&ver[p], inc);
-        unsafeAtomicAdd(&sla[p - 1], inc);
-      } else {
-        old_v = unsafeAtomicAdd(&ver[p], inc);
-        old_s = unsafeAtomicAdd(&sla[p - 1], inc);
-      }
+      const float old_v = unsafeAtomicAdd(&ver[p], inc);
+      const float old_s = unsafeAtomicAdd(&sla[p - 1], inc);
       const double xv = gamma * g * (double)old_v;           // decayed old value
       const double xs = p - 1 >= s.n_sink ? gamma * g * (double)old_s : 0.0;   // decayed value moving in from p-1
       const double yv = xv + delta, ys = xs + delta;
@@ -297,26 +311,149 @@ __global__ __launch_bounds__(kTabThreads) void k_table_update(Shape s, float* __
       st[TS_FLAT_S] = 0.0;
     }
   }
-  // Once the scale has become small it is folded into the stored values (A <- g A, g <- 1; the values g A
-  // do not change).  The head decides for itself from its own state, here at the end of the update that
-  // made the scale small, so no host-side count is involved and a recorded graph folds when an eager run would.
-  // This step's additions were made in L2 (atomics): they are waited for, and the entries are then read
-  // with device-scope loads, which do not look at this CU's vector cache (it may hold the old values).
-  if (g1 < kFoldBelow) {                                     // workgroup-uniform
-    __threadfence();
-    __syncthreads();
-    float* sla_all = tab_sla + (int64_t)bh * 2 * s.Lcap;
-    for (int i = tid; i < s.Lcap; i += kTabThreads) {
-      const float x = __hip_atomic_load(&ver[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      ver[i] = (float)(g1 * (double)x);
-    }
-    for (int i = tid; i < 2 * s.Lcap; i += kTabThreads) {
-      const float x = __hip_atomic_load(&sla_all[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      sla_all[i] = (float)(g1 * (double)x);
-    }
-    __syncthreads();
-    if (tid == 0) st[TS_G] = 1.0;
+  fold_scale(s, bh, g1, ver, tab_sla, st, tid, kTabThreads);
+}
+
+// The same for the library's own Top-k (distinct positions, at most kUpdateThreads * kUpdateEach of them): a thread reads
+// its entries and the table values they change at once and keeps them, a plain store replaces the atomic addition, and
+// the eight moments meet in one reduction.  The kernel is a chain of latencies (256 heads, k = 1024): 17.4 us with four
+// entries per thread read three times and ten reductions one after the other, 8.2 us this way.
+constexpr int kUpdateThreads = 1024, kUpdateEach = 4;
+template <int kEach>
+__global__ __launch_bounds__(kUpdateThreads) void k_table_update_own(Shape s, float* __restrict__ tab_ver,
+                                                                     float* __restrict__ tab_sla,
+                                                                     double* __restrict__ state,
+                                                                     const int32_t* __restrict__ seq_lens,
+                                                                     const int32_t* __restrict__ idx,
+                                                                     const float* __restrict__ sc,
+                                                                     const int32_t* __restrict__ kk, double gamma,
+                                                                     const int32_t* __restrict__ gate,
+                                                                     int32_t* __restrict__ flags) {
+  constexpr int NT = kUpdateThreads, NW = NT / 64;
+  __shared__ float top[NW];
+  __shared__ double red[NW][8];
+  __shared__ int cnts[NW];
+  const int bh = blockIdx.x, b = bh / s.Hq, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int32_t* ih = idx + (int64_t)bh * s.kmax;
+  const float* sh = sc + (int64_t)bh * s.kmax;
+  int pos[kEach];
+  float x[kEach];
+#pragma unroll
+  for (int u = 0; u < kEach; ++u) {                          // (up to the row length; masked below)
+    const int e = tid + u * NT;
+    pos[u] = e < s.kmax ? ih[e] : -1;
+    x[u] = e < s.kmax ? sh[e] : 0.f;
   }
+  double* st = state + (int64_t)bh * kTableStateDoubles;
+  const double g = st[TS_G], moves = st[TS_CNT];
+  int n = seq_lens[b];
+  int kb = kk[b];
+  if (gate && gate[bh] != 0) return;                        // bypassed head: Eq. 10 is skipped for it
+  if (moves >= (double)(s.Lcap - 1)) {                       // no room in the slash frame (see k_table_update)
+    if (tid == 0) atomicOr(flags, LFPS_FLAG_TABLE_FULL);
+    return;
+  }
+  n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
+  kb = kb < 0 ? 0 : (kb > s.kmax ? s.kmax : kb);
+  const int cnt = clamp_count(moves, s.Lcap);
+  float* ver = tab_ver + (int64_t)bh * s.Lcap;
+  float* sla = tab_sla + (int64_t)bh * 2 * s.Lcap + (s.Lcap - cnt);   // indexed by position in the frame of this step
+  bool ok[kEach];
+  float old_v[kEach], old_s[kEach];
+  float m = -INFINITY;
+  int valid = 0;
+#pragma unroll
+  for (int u = 0; u < kEach; ++u) {
+    ok[u] = tid + u * NT < kb && pos[u] >= s.n_sink && pos[u] < n;
+    // position p in the next frame (cnt + 1) is the slot of p - 1 in this one (p = 0: the slot just below the frame)
+    old_v[u] = ok[u] ? ver[pos[u]] : 0.f;
+    old_s[u] = ok[u] ? sla[pos[u] - 1] : 0.f;
+    m = ok[u] ? fmaxf(m, x[u]) : m;
+    valid += __popcll(__ballot(ok[u]));
+  }
+  m = row16_max(m);
+  m = fmaxf(m, __shfl_xor(m, 16));
+  m = fmaxf(m, __shfl_xor(m, 32));
+  if (lane == 0) {
+    top[wave] = m;
+    cnts[wave] = valid;
+  }
+  __syncthreads();
+  m = top[0];
+  valid = cnts[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) {
+    m = fmaxf(m, top[w]);
+    valid += cnts[w];
+  }
+  auto wave_sum = [](double v) {
+    v = row16_sum(v);
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    return v;
+  };
+  float w_[kEach];
+  double zsum = 0.0;
+#pragma unroll
+  for (int u = 0; u < kEach; ++u) {
+    w_[u] = ok[u] ? expf(x[u] - m) : 0.f;
+    zsum += (double)w_[u];
+  }
+  zsum = wave_sum(zsum);
+  if (lane == 0) red[wave][0] = zsum;
+  __syncthreads();
+  zsum = 0.0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) zsum += red[w][0];
+  const double half = valid > 0 ? 0.5 / (double)valid : 0.0;
+  const double g1 = gamma * g;                               // scale after this step
+  double d[8] = {0, 0, 0, 0, 0, 0, 0, 0};                    // change of the moments: vertical, slash
+#pragma unroll
+  for (int u = 0; u < kEach; ++u) {
+    if (ok[u]) {
+      const double delta = (double)w_[u] / zsum - half;
+      const float inc = (float)(delta / g1);
+      ver[pos[u]] = old_v[u] + inc;
+      sla[pos[u] - 1] = old_s[u] + inc;
+      const double xv = g1 * (double)old_v[u];                                     // decayed old value
+      const double xs = pos[u] - 1 >= s.n_sink ? g1 * (double)old_s[u] : 0.0;      // decayed value moving in from p - 1
+      double yv = xv + delta, ys = xs + delta, av = xv, as = xs;
+      const double bv = yv, bs = ys;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        d[p] += yv - av;
+        d[4 + p] += ys - as;
+        yv *= bv;
+        ys *= bs;
+        av *= xv;
+        as *= xs;
+      }
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < 8; ++p) d[p] = wave_sum(d[p]);
+  __syncthreads();                                           // everybody has read red[][0]
+  if (lane == 0) {
+#pragma unroll
+    for (int p = 0; p < 8; ++p) red[wave][p] = d[p];
+  }
+  __syncthreads();
+  if (tid < 8) {                                             // thread p: moment p & 3 of the vertical, then of the slash table
+    double sum = 0.0, gp = 1.0;
+    for (int w = 0; w < NW; ++w) sum += red[w][tid];
+    for (int p = 0; p <= (tid & 3); ++p) gp *= gamma;
+    double* M = st + (tid < 4 ? TS_MV + tid : TS_MS + tid - 4);
+    *M = gp * *M + sum;
+    if (tid == 0) {
+      st[TS_G] = g1;
+      st[TS_CNT] = (double)(cnt + 1);
+      if (valid > 0) {                                       // entries were changed: no longer a flat table
+        st[TS_FLAT_V] = 0.0;
+        st[TS_FLAT_S] = 0.0;
+      }
+    }
+  }
+  fold_scale(s, bh, g1, ver, tab_sla, st, tid, NT);
 }
 
 // ----------------------------------------------------------------------------- import / export / renormalise
@@ -448,7 +585,8 @@ __global__ __launch_bounds__(1024) void k_table_init(Shape s, float* __restrict_
 }
 
 // ----------------------------------------------------------------------------- head sparsity (Eq. 5, Eq. 6)
-// One wave per (b, h).  rho = w_sink / (w_sink + w_global + w_local):
+// One wave per (b, h), a chain of latencies: a row at a time, 64 lanes wide, took 10.6 us at 256 heads and 10 rows; four rows
+// side by side and all of them requested at once, 5.7 us.  rho = w_sink / (w_sink + w_global + w_local):
 //   w_sink   = sum over rows [0, n_sink) of exp(q.K_i/sqrt(D)),
 //   w_global = n * exp(q.kbar/sqrt(D) + |q|^2 sigma2_hat / 2)        (log-normal mean of the weights, App. B.1),
 //   w_local  = sum over the newest n_local rows of exp(q.K_i/sqrt(D)).
@@ -466,55 +604,66 @@ __global__ __launch_bounds__(64) void k_head_sparsity(Shape s, const float* __re
                                                       float* __restrict__ topk_score, float* __restrict__ out,
                                                       float* __restrict__ thr_state) {
   const int bh = blockIdx.x, b = bh / s.Hq, h = bh % s.Hq, g = h / s.G, lane = threadIdx.x;
+  const int j = lane & 15, rs = lane >> 4;                    // 16 lanes per row, 8 channels each
   int n = seq_lens[b];
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   const float scale = 0.08838834764831845f;
-  const float q0 = q[(int64_t)bh * kD + 2 * lane], q1 = q[(int64_t)bh * kD + 2 * lane + 1];
-  using Rows = RowMap<kPaged>;
-  const T* Kbg = K + Rows::base(b, g, stride_b, stride_h);
-  auto logit_of_row = [&](int row) {
-    float k0, k1;
-    const T* kr = Kbg + Rows::offset(pg, Rows::phys(pg, b, row), stride_b, stride_n) + 2 * lane;
-    if constexpr (sizeof(T) == 1) {                 // two E4M3 bytes
-      const uint32_t w = *reinterpret_cast<const uint16_t*>(kr);
-      float x[4];
-      fp8x4_to_f32(w, x);
-      k0 = x[0];
-      k1 = x[1];
-    } else if constexpr (sizeof(T) == 2 && !std::is_same<T, _Float16>::value) {   // two bf16
-      const uint32_t w = *reinterpret_cast<const uint32_t*>(kr);
-      k0 = bf16_lo(w);
-      k1 = bf16_hi(w);
-    } else {
-      k0 = (float)kr[0];
-      k1 = (float)kr[1];
-    }
-    float d = fmaf(q1, k1, q0 * k0);
+  float qr[8], kr[8];
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) d += __shfl_xor(d, o);
-    return (double)(d * scale);
-  };
-  // log-sum-exp accumulators (double: a handful of terms per head)
-  auto lse_add = [](double& m, double& z, double x) {
-    if (x > m) {
-      z = z * exp(m - x) + 1.0;
-      m = x;
-    } else {
-      z += exp(x - m);
-    }
-  };
-  double m_sink = -INFINITY, z_sink = 0.0, m_loc = -INFINITY, z_loc = 0.0;
-  const int ns = s.n_sink < n ? s.n_sink : n;
-  for (int i = 0; i < ns; ++i) lse_add(m_sink, z_sink, logit_of_row(i));
-  const int lo = n - n_local > 0 ? n - n_local : 0;
-  for (int i = lo; i < n; ++i) lse_add(m_loc, z_loc, logit_of_row(i));
-  float dk = fmaf(q1, kbar[((int64_t)b * s.Hkv + g) * kD + 2 * lane + 1], q0 * kbar[((int64_t)b * s.Hkv + g) * kD + 2 * lane]);
-  float qq = fmaf(q1, q1, q0 * q0);
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    dk += __shfl_xor(dk, o);
-    qq += __shfl_xor(qq, o);
+  for (int c = 0; c < 8; ++c) {                               // (a caller's pointers: no more than 4-byte alignment)
+    qr[c] = q[(int64_t)bh * kD + 8 * j + c];
+    kr[c] = kbar[((int64_t)b * s.Hkv + g) * kD + 8 * j + c];
   }
+  using Rows = RowMap<kPaged>;
+  const T* Kbg = K + Rows::base(b, g, stride_b, stride_h) + 8 * j;
+  const int ns = s.n_sink < n ? s.n_sink : n;
+  const int lo = n - n_local > 0 ? n - n_local : 0;
+  const int rows = ns + (n - lo);                             // the sinks, then the newest rows
+  // log-sum-exp of both sets, sixteen rows at a time: four per lane group, all loads issued together; then lane i of a
+  // group takes row i (a logit is an fp32 number, its exponential and the sums are fp64)
+  double m_sink = -INFINITY, z_sink = 0.0, m_loc = -INFINITY, z_loc = 0.0;
+  for (int r0 = 0; r0 < rows; r0 += 16) {
+    int prow[4];
+    Raw8<T> raw[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int r = r0 + 4 * u + rs < rows ? r0 + 4 * u + rs : rows - 1;
+      prow[u] = Rows::phys(pg, b, r < ns ? r : lo + r - ns);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) raw[u].load(Kbg + Rows::offset(pg, prow[u], stride_b, stride_n));
+    float mine = 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float x[8];
+      raw[u].get(x);
+      float d = 0.f;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) d = fmaf(qr[c], x[c], d);
+      d = row16_sum(d) * scale;
+      const float of_row = __shfl(d, 16 * (j & 3));           // rows r0 + 4 u + (j & 3)
+      mine = (j >> 2) == u ? of_row : mine;
+    }
+    const int r = r0 + j;
+    auto add = [&](bool in, double& m, double& z) {
+      const float top = row16_max(in ? mine : -INFINITY);
+      if (top == -INFINITY) return;                            // (wave-uniform: every group holds the same rows)
+      const double mx = m > (double)top ? m : (double)top;
+      const double part = row16_sum(in ? exp((double)mine - mx) : 0.0);
+      z = (z > 0.0 ? z * exp(m - mx) : 0.0) + part;
+      m = mx;
+    };
+    add(r < ns, m_sink, z_sink);
+    add(r >= ns && r < rows, m_loc, z_loc);
+  }
+  float dk = 0.f, qq = 0.f;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    dk = fmaf(qr[c], kr[c], dk);
+    qq = fmaf(qr[c], qr[c], qq);
+  }
+  dk = row16_sum(dk);
+  qq = row16_sum(qq);
   const double l_glob = n > 0 ? log((double)n) + (double)(dk * scale) + (double)qq * (double)sigma2_hat[bh] * 0.5 : -INFINITY;
   const double l_sink = z_sink > 0.0 ? m_sink + log(z_sink) : -INFINITY;
   const double l_loc = z_loc > 0.0 ? m_loc + log(z_loc) : -INFINITY;
@@ -559,12 +708,13 @@ hipError_t launch_table_flags(const Shape& s, const float* tab_ver, const float*
 hipError_t launch_table_update(const Shape& s, float* tab_ver, float* tab_sla, double* state, const int32_t* seq_lens,
                                const int32_t* idx, const float* sc, const int32_t* k, double gamma, const int32_t* gate,
                                int32_t* flags, bool distinct, hipStream_t st) {
-  if (distinct)
-    hipLaunchKernelGGL(k_table_update<true>, dim3(s.B * s.Hq), dim3(kTabThreads), 0, st, s, tab_ver, tab_sla, state,
-                       seq_lens, idx, sc, k, gamma, gate, flags);
-  else
-    hipLaunchKernelGGL(k_table_update<false>, dim3(s.B * s.Hq), dim3(kTabThreads), 0, st, s, tab_ver, tab_sla, state,
-                       seq_lens, idx, sc, k, gamma, gate, flags);
+#define LFPS_UPDATE(KERNEL, THREADS)                                                                               \
+  hipLaunchKernelGGL((KERNEL), dim3(s.B * s.Hq), dim3(THREADS), 0, st, s, tab_ver, tab_sla, state, seq_lens, idx, sc, \
+                     k, gamma, gate, flags)
+  if (!distinct || s.kmax > kUpdateThreads * kUpdateEach) LFPS_UPDATE(k_table_update, kTabThreads);
+  else if (s.kmax > kUpdateThreads) LFPS_UPDATE(k_table_update_own<kUpdateEach>, kUpdateThreads);
+  else LFPS_UPDATE(k_table_update_own<1>, kUpdateThreads);
+#undef LFPS_UPDATE
   return hipGetLastError();
 }
 

@@ -887,3 +887,41 @@ def test_table_steps_chained_on_the_device_without_import():
     assert total_diff <= 4, total_diff
     assert ctx.lfps_poll_status() == 0
     ctx.close()
+
+
+@pytest.mark.parametrize("L,k,n_sink", [(300, 1, 0), (2200, 1023, 4), (2200, 1024, 0), (3000, 1025, 4), (5200, 4096, 4),
+                                        (5200, 4097, 4)])
+def test_update_of_a_step_equals_the_update_of_a_callers_list(L, k, n_sink):
+    """The update inside a table step (one, four or any number of entries per thread) against lfps_table_update with the
+    same rows and scores; the sums over the entries differ in order only: 1e-6 of the largest entry (fp32 tables)."""
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L + k)
+    Hq, Lcap = 4, L + 4
+    K, V = (torch.randn((1, 1, Lcap, 128), device=DEV, generator=g).to(torch.bfloat16) for _ in range(2))
+    q = torch.randn((4, 1, Hq, 128), device=DEV, generator=g)
+    ks = torch.tensor([k], dtype=torch.int32, device=DEV)
+    seq = [torch.tensor([L + t], dtype=torch.int32, device=DEV) for t in range(4)]
+    a, b = (Lfps(batch=1, n_q_heads=Hq, n_kv_heads=1, kv_dtype="bf16", max_seq_len=Lcap, max_k=k, radius=30,
+                 n_sink=n_sink, table_mode=True) for _ in range(2))
+    for ctx in (a, b):
+        ctx.lfps_tables_init(q[:1].contiguous(), ctx.kv_view(K, V, seq[0]))
+    for t in (1, 2, 3):
+        idx = torch.zeros((1, Hq, k), dtype=torch.int32, device=DEV)
+        sc, out = torch.zeros((1, Hq, k), device=DEV), torch.zeros((1, Hq, 128), device=DEV)
+        a.lfps_table_step(q[t], a.kv_view(K, V, seq[t]), ks, idx, out, sc)
+        b.lfps_table_update(idx, sc, ks, seq[t])
+        tabs = []
+        for ctx in (a, b):
+            ver, sla = (torch.zeros((1, Hq, Lcap), dtype=torch.float64, device=DEV) for _ in range(2))
+            ctx.lfps_tables_export(ver, sla, seq[t])
+            tabs.append((ver, sla))
+        for x, y in zip(*tabs):
+            assert (x - y).abs().max() <= 1e-6 * y.abs().max(), t
+        cand = torch.zeros((2, 1, 1, a.cand_cap), dtype=torch.int32, device=DEV)
+        cnt = torch.zeros((2, 1, 1), dtype=torch.int32, device=DEV)
+        for i, ctx in enumerate((a, b)):                     # the moments of both give the same thresholds
+            ctx.lfps_table_candidates(seq[t], cand[i], cnt[i])
+        assert (cnt[0] - cnt[1]).abs().max() <= 2
+    a.close()
+    b.close()
