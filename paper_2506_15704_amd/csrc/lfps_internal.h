@@ -344,6 +344,17 @@ __device__ __forceinline__ float row16_max(float x) {
   return x;
 #undef LFPS_ROT
 }
+// The same sum in the order of a butterfly over lane distances 1, 2, 4, 8 (the bits of four xor shuffles), without LDS:
+// lanes of a quad by permutation, then, all lanes of a quad (of a half) being equal, the other one by mirroring.
+__device__ __forceinline__ float row16_butterfly_sum(float x) {
+#define LFPS_DPP(v, ctrl) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false))
+  x += LFPS_DPP(x, 0xB1);     // quad_perm 1 0 3 2
+  x += LFPS_DPP(x, 0x4E);     // quad_perm 2 3 0 1
+  x += LFPS_DPP(x, 0x141);    // row_half_mirror
+  x += LFPS_DPP(x, 0x140);    // row_mirror
+#undef LFPS_DPP
+  return x;
+}
 template <int kBy>
 __device__ __forceinline__ double row16_rotate(double x) {
   return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x120 + kBy, 0xf, 0xf, false),
