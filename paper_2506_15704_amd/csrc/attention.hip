@@ -165,11 +165,9 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
         sc[u][h] = a;
       }
 #pragma unroll
-    for (int d = 1; d < 16; d <<= 1)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int h = 0; h < G; ++h) sc[u][h] += __shfl_xor(sc[u][h], d);
+      for (int h = 0; h < G; ++h) sc[u][h] = row16_butterfly_sum(sc[u][h]);
 #pragma unroll
     for (int h = 0; h < G; ++h) {
       float mx = m[h];

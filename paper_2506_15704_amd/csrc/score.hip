@@ -433,8 +433,7 @@ __global__ __launch_bounds__(256) void k_head_score(Shape s, const float* __rest
     float a = qr[0] * x[0];
 #pragma unroll
     for (int c = 1; c < 8; ++c) a = fmaf(qr[c], x[c], a);
-#pragma unroll
-    for (int d = 1; d < 16; d <<= 1) a += __shfl_xor(a, d);
+    a = row16_butterfly_sum(a);
     int slot = base + 4 * t + rs;
     if (j == 0 && slot < kb) out[(int64_t)bh * s.kmax + slot] = ok ? a * scale : -INFINITY;
   }
