@@ -16,6 +16,15 @@ __device__ __forceinline__ void set_bit_range(uint32_t* bm, int lo, int hi) {  /
   }
 }
 
+// The same for at most 32 positions: at most two words, no loop.  (Every entry of a Top-k list sets such a window; with
+// the loop that was up to 60 instructions an entry: candidates kernel of 128 groups x 128K rows @@C0@@ -> @@C1@@ us.)
+constexpr int kWindowRadius = 15;      // windows of up to 2 * 15 + 2 positions
+__device__ __forceinline__ void set_bit_window(uint32_t* bm, int lo, int hi) {
+  const uint64_t m = ((2ull << (hi - lo)) - 1ull) << (lo & 31);
+  atomicOr(&bm[lo >> 5], (uint32_t)m);
+  if ((uint32_t)(m >> 32)) atomicOr(&bm[(lo >> 5) + 1], (uint32_t)(m >> 32));
+}
+
 // One word of a head's initial candidates (bit 0 = the word's first position), widened by the offsets -r ... r + 1
 // (r <= 30) across the words before and after it.
 __device__ __forceinline__ uint32_t widen_word(uint32_t before, uint32_t mid, uint32_t after, int r) {
@@ -154,8 +163,12 @@ __device__ __forceinline__ void candidates_from_topk(const Shape& s, uint32_t* l
       const int i = (j0 + tid + (e % kU) * NT < kb) ? ids[e] : -1;
       if (i >= 0 && i < n) {
         const int lo = i - r < 0 ? 0 : i - r;
-        const int64_t hi64 = (int64_t)i + r + 1;
-        set_bit_range(bm, lo, hi64 > n - 1 ? n - 1 : (int)hi64);
+        if (r <= kWindowRadius) {
+          set_bit_window(bm, lo, i + r + 1 > n - 1 ? n - 1 : i + r + 1);
+        } else {
+          const int64_t hi64 = (int64_t)i + r + 1;
+          set_bit_range(bm, lo, hi64 > n - 1 ? n - 1 : (int)hi64);
+        }
       }
     }
     j0 += kU * NT;

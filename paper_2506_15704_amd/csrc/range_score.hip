@@ -121,7 +121,8 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
             for (int c = 0; c < 4; ++c)
               if (hit[c] && c < left) {
                 const int a = e[c] - rc - lo, z = e[c] + rc + 1 - lo;
-                set_bit_range(bm, a < 0 ? 0 : a, z < hi - lo ? z : hi - 1 - lo);
+                if (rc <= kWindowRadius) set_bit_window(bm, a < 0 ? 0 : a, z < hi - lo ? z : hi - 1 - lo);
+                else set_bit_range(bm, a < 0 ? 0 : a, z < hi - lo ? z : hi - 1 - lo);
               }
           }
         }
