@@ -507,12 +507,12 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
   ctx->no_history = 0;                       // either form leaves every selecting head's k-th best score behind
   if (range) {
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
-           launch_range_score(s, q, v, from, ctx->thr_state, kFilterMargin, ctx->score, ctx->slot, s.score_stride,
-                              ctx->seg_count, ctx->nseg, ctx->bitmap, ctx->bitmap_words, range, ctx->flags, st));
+           launch_range_score(s, q, v, from, ctx->thr_state, kFilterMargin, skip_if, ctx->score, ctx->slot,
+                              s.score_stride, ctx->seg_count, ctx->nseg, ctx->bitmap, ctx->bitmap_words, range, ctx->flags, st));
   } else if (filtered) {
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
            launch_filter_score(s, q, v, ctx->cand, ctx->cand_count, ctx->group_start, line_total, ctx->thr_state,
-                               kFilterMargin, ctx->score, ctx->slot, s.score_stride, ctx->seg_count, ctx->flags + 1,
+                               kFilterMargin, skip_if, ctx->score, ctx->slot, s.score_stride, ctx->seg_count, ctx->flags + 1,
                                ctx->filter_blocks[v.page.table ? 1 : 0], ctx->flags, false, ctx->nseg, st));
   }
   if (filtered) {
@@ -680,7 +680,7 @@ int lfps_exact_topk(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int3
            launch_select(s, ctx->score, s.score_stride, nullptr, ctx->x_ns, ctx->x_rank, ctx->slot, nullptr, ctx->thr_x,
                          nullptr, nullptr, st));
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
-           launch_filter_score(sd, q, v, nullptr, ctx->x_cnt, ctx->x_start, x_total, ctx->thr_x, 0.f, ctx->score,
+           launch_filter_score(sd, q, v, nullptr, ctx->x_cnt, ctx->x_start, x_total, ctx->thr_x, 0.f, nullptr, ctx->score,
                                ctx->slot, s.score_stride, ctx->seg_count, ctx->flags + 1,
                                ctx->filter_blocks[v.page.table ? 1 : 0], ctx->flags, true, ctx->nseg, st));
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SELECT_ATTEND, st,

@@ -99,7 +99,7 @@ int filter_list_cap(const Shape& s);   // survivors per head the filtered select
 hipError_t filter_score_blocks(const Shape& s, int k_kind, int out[2]);
 hipError_t launch_filter_score(const Shape& s, const float* q, const KvView& kv, const int32_t* cand,
                                const int32_t* cand_count, const int64_t* group_start, const int64_t* line_total,
-                               const float* thr_state, float margin, float* score,
+                               const float* thr_state, float margin, const int32_t* skip_if, float* score,
                                int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int32_t* seg_rows_out,
                                int n_blocks, int32_t* flags, bool dense, int nseg, hipStream_t st);
 // S1 + S2 of a chained step in one kernel (range_score.hip): candidates from the Top-k of the step before (prev_topk, k) or
@@ -116,8 +116,8 @@ struct RangeSource {
 };
 int range_rows(const Shape& s, bool tables);   // 0: the separate kernels
 hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, const RangeSource& from,
-                              const float* thr_state, float margin, float* score, int32_t* slot_out,
-                              int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words,
+                              const float* thr_state, float margin, const int32_t* skip_if, float* score,
+                              int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words,
                               int range, int32_t* flags, hipStream_t st);
 
 // S3 + S4 of the chained steps in one kernel (select_attend.hip).  From the survivor lists of the filtered scoring
@@ -126,7 +126,7 @@ hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, 
 // and the group's candidate list (cand; NULL = all rows 0 .. cand_count-1) and overwrites the head's score row.
 // range > 0: the lists are those of launch_range_score with that range (cand, seg_rows, group_start, line_total unused;
 // the candidates are in bitmap), and cand_count is written.  keep_ratio: a head with fewer than keep_ratio * k candidates
-// leaves -inf in thr_state instead of its k-th best score.
+// (and no more than half of filter_list_cap) leaves -inf in thr_state instead of its k-th best score.
 hipError_t configure_select_attend(const Shape& s, int dtype, bool k_fp8, bool v_fp8);
 hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, int32_t* slot,
                                        int64_t score_stride, const int32_t* seg_count, const int32_t* seg_rows, int nseg,

@@ -24,7 +24,8 @@ template <int G, bool kPaged, int kKind, bool kTables>
 __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
     Shape s, const float* __restrict__ q, const void* __restrict__ K, int64_t stride_b, int64_t stride_h,
     int64_t stride_n, KvPage page, const int32_t* __restrict__ seq_lens, RangeSource from,
-    const float* __restrict__ thr_state, float margin, float* __restrict__ score, int32_t* __restrict__ slot_out,
+    const float* __restrict__ thr_state, float margin, const int32_t* __restrict__ skip_if, float* __restrict__ score,
+    int32_t* __restrict__ slot_out,
     int64_t score_stride, int32_t* __restrict__ seg_count, int nseg, uint32_t* __restrict__ bitmap, int bitmap_words,
     int range, float scale, int32_t* __restrict__ flags) {
   __shared__ float stage_score[4][G][kRangeStage];
@@ -72,6 +73,7 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
   const int k_raw = kTables ? 0 : from.k[b];
   const int64_t head0 = (int64_t)b * s.Hq + (int64_t)g * G;
   const float thr = thr_state[head0 + (kb < G ? kb : 0)];
+  const bool skipped = skip_if && skip_if[head0 + (kb < G ? kb : 0)] != 0;     // bypassed head: nothing is kept for it
   if (tid < words) bm[tid] = 0u;
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   if (lo >= n) return;                                   // (nobody reads the piece counts of such a range)
@@ -174,7 +176,7 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
     if (j == 0 && kb < G) seg_count[head * nseg + piece] = cnt << 16;
     return;
   }
-  const float tau = kb < G ? thr - margin : INFINITY;
+  const float tau = kb < G && !skipped ? thr - margin : INFINITY;
   const uint32_t below = (1u << j) - 1u;                 // lanes of my 16-lane group with a lower row
   float* st_s = stage_score[wave][kb < G ? kb : 0];
   int32_t* st_i = stage_slot[wave][kb < G ? kb : 0];
@@ -270,8 +272,8 @@ int range_rows(const Shape& s, bool tables) {
 }
 
 hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, const RangeSource& from,
-                              const float* thr_state, float margin, float* score, int32_t* slot_out,
-                              int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words,
+                              const float* thr_state, float margin, const int32_t* skip_if, float* score,
+                              int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words,
                               int range, int32_t* flags, hipStream_t st) {
   dim3 grid((s.Lcap + range - 1) / range, s.B * s.Hkv), block(kScoreThreads);
   const float sc = 0.08838834764831845f;   // 1/sqrt(128)
@@ -281,8 +283,8 @@ hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, 
 #define LFPS_LAUNCH_RANGE(GG, PAGED, KIND, TABLES)                                                                      \
   if (!launched && s.G == GG && paged == PAGED && kind == KIND && tables == TABLES) {                                  \
     hipLaunchKernelGGL((k_range_score<GG, PAGED, KIND, TABLES>), grid, block, (size_t)range * 2, st, s, q, kv.k,        \
-                       kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, from, thr_state, margin, score,    \
-                       slot_out, score_stride, seg_count, nseg, bitmap, bitmap_words, range, sc, flags);                \
+                       kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, from, thr_state, margin, skip_if,  \
+                       score, slot_out, score_stride, seg_count, nseg, bitmap, bitmap_words, range, sc, flags);                \
     launched = true;                                                                                                    \
   }
 #define LFPS_RANGE_KINDS(GG, PAGED, TABLES)          \

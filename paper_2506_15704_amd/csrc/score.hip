@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
     int64_t stride_n, KvPage page, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ cand,
     const int32_t* __restrict__ cand_count, const int64_t* __restrict__ group_start,
     const int64_t* __restrict__ line_total, const float* __restrict__ thr_state, float margin,
-    float* __restrict__ score, int32_t* __restrict__ slot_out, int64_t score_stride,
+    const int32_t* __restrict__ skip_if, float* __restrict__ score, int32_t* __restrict__ slot_out, int64_t score_stride,
     int32_t* __restrict__ seg_count, int32_t* __restrict__ seg_rows_out, int min_seg_rows, int nseg, float scale,
     int32_t* __restrict__ flags) {
   __shared__ float stage_score[4][G][kFilterStage];
@@ -151,7 +151,8 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
       if (j == 0 && kb < G) seg_count[head * nseg + seg] = 0;
       continue;
     }
-    const float tau = kb < G ? thr_state[head] - margin : INFINITY;
+    // (a bypassed head keeps nothing)
+    const float tau = kb < G && !(skip_if && skip_if[head] != 0) ? thr_state[head] - margin : INFINITY;
 
     using Rows = RowMap<kPaged>;
     using Tile = KTile<kKind>;
@@ -536,7 +537,7 @@ hipError_t filter_score_blocks(const Shape& s, int k_kind, int out[2]) {
 
 hipError_t launch_filter_score(const Shape& s, const float* q, const KvView& kv, const int32_t* cand,
                                const int32_t* cand_count, const int64_t* group_start, const int64_t* line_total,
-                               const float* thr_state, float margin, float* score,
+                               const float* thr_state, float margin, const int32_t* skip_if, float* score,
                                int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int32_t* seg_rows_out,
                                int n_blocks, int32_t* flags, bool dense, int nseg, hipStream_t st) {
   if (n_blocks < 1) return hipErrorInvalidValue;
@@ -546,7 +547,7 @@ hipError_t launch_filter_score(const Shape& s, const float* q, const KvView& kv,
 #define LFPS_LAUNCH_FILTER_D(GG, PAGED, FP8, DENSE)                                                                \
   hipLaunchKernelGGL((k_filter_score_bf16<GG, PAGED, FP8, DENSE>), grid, block, 0, st, s, q, kv.k, kv.stride_b,    \
                      kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, cand, cand_count, group_start, line_total,    \
-                     thr_state, margin, score, slot_out, score_stride, seg_count, seg_rows_out,                    \
+                     thr_state, margin, skip_if, score, slot_out, score_stride, seg_count, seg_rows_out,                    \
                      filter_min_seg_rows(s), nseg, scale, flags)
 #define LFPS_LAUNCH_FILTER_P(GG, PAGED, FP8)       \
   if (dense) {                                     \

@@ -15,10 +15,11 @@
 //   k_select_attend          selects from a head's full score row (all candidates): contexts without the filter.
 //
 // Both leave the k-th best score behind as the next step's threshold, but -inf (keep every candidate) for a head with
-// fewer than keep_ratio * k candidates: there is little to filter then, and one head that the filter leaves short costs the
-// step its unfiltered pass, 25 us.  keep_ratio is 2 for the memoryless form and 8 for the table form, whose candidate sets
-// change in size by a half from one step to the next: table steps of 8 x 32K, k = 1024 of about 1300 candidates: 15 to 60 of
-// 256 heads took the unfiltered pass, and this kernel 44 us instead of 19.
+// fewer than ratio * k candidates, if they fill no more than half of the next step's list: there is little to filter then,
+// and one head that the filter leaves short costs the step its unfiltered pass, 25 us.  The ratio is 2 for the memoryless
+// form and 8 for the table form, whose candidate sets change in size by a half from one step to the next: table steps of
+// 8 x 32K, k = 1024 of about 1300 candidates: 15 to 60 of 256 heads took the unfiltered pass, and this kernel 44 us instead
+// of 19.  (Half of the list: with 5000 to 14000 candidates for lists of 4096 every head overflowed, 250 instead of 58 us.)
 //
 // For few heads both kernels are a chain of latencies: at 32 heads, k = 1024, the first one took 19.8 us, of which
 // 1.8 us went into the piece counts, 6.3 into finding and fetching the survivors (twelve searches per thread, whatever
@@ -36,8 +37,13 @@
 
 namespace lfps {
 
-// Is the k-th best of c candidates a threshold worth remembering?
-__device__ __forceinline__ bool filter_pays(int c, int ksel, int keep_ratio) { return c / keep_ratio >= ksel; }
+struct KeepAll {
+  int ratio, most;
+};
+// Is the k-th best of c candidates a threshold worth remembering?  (keep: c < keep.ratio * k and c <= keep.most)
+__device__ __forceinline__ bool filter_pays(int c, int ksel, const KeepAll& keep) {
+  return c / keep.ratio >= ksel || c > keep.most;
+}
 
 constexpr int kSelRowsMax = 16384;    // selected rows of a head that pass through LDS; more go through global memory
 
@@ -90,7 +96,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     const int32_t* __restrict__ cand, int32_t* __restrict__ cand_count, const int64_t* __restrict__ group_start,
     int64_t* __restrict__ line_total, int range, const uint32_t* __restrict__ bitmap, int bitmap_words,
     const int32_t* __restrict__ kk, int32_t* topk_idx, float* topk_score,
-    float* __restrict__ thr_state, float margin, int keep_ratio, const int32_t* __restrict__ skip_if,
+    float* __restrict__ thr_state, float margin, KeepAll keep, const int32_t* __restrict__ skip_if,
     int32_t* __restrict__ rescored,
     const float* __restrict__ q, const void* __restrict__ K, float scale, int32_t* __restrict__ flags,
     const T* __restrict__ V, int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage page,
@@ -197,7 +203,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     if (out && tid < kD) out[(int64_t)bh * kD + tid] = 0.f;
     return;
   }
-  float* thr_out = filter_pays(c, ksel, keep_ratio) ? thr_state + bh : nullptr;
+  float* thr_out = filter_pays(c, ksel, keep) ? thr_state + bh : nullptr;
   if (!thr_out && tid == 0) thr_state[bh] = -INFINITY;      // (every thread has read it before the barrier)
   float* sc = score + (int64_t)bh * score_stride;
   int32_t* sl = slot + (int64_t)bh * score_stride;
@@ -309,7 +315,7 @@ template <typename T, bool kPaged>
 __global__ __launch_bounds__(kSelThreads) void k_select_attend(
     Shape s, const float* __restrict__ score, int64_t score_stride, const int32_t* __restrict__ cand,
     const int32_t* __restrict__ cand_count, const int32_t* __restrict__ kk, int32_t* topk_idx, float* topk_score,
-    int cache_elems, float* __restrict__ thr_state, int keep_ratio,
+    int cache_elems, float* __restrict__ thr_state, KeepAll keep,
     const int32_t* __restrict__ skip_if, const T* __restrict__ V, int64_t stride_b, int64_t stride_h, int64_t stride_n,
     KvPage page, const int32_t* __restrict__ seq_lens, float* __restrict__ out) {
   constexpr int NT = kSelThreads;
@@ -340,7 +346,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_attend(
     if (tid < kD) out[(int64_t)bh * kD + tid] = 0.f;
     return;
   }
-  if (thr_out && !filter_pays(c, ksel, keep_ratio)) {
+  if (thr_out && !filter_pays(c, ksel, keep)) {
     if (tid == 0) *thr_out = -INFINITY;
     thr_out = nullptr;
   }
@@ -477,6 +483,7 @@ hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, 
                                        float* thr_state, float margin, int keep_ratio, const int32_t* skip_if, int32_t* rescored,
                                        const float* q, int32_t* flags, const KvView& kv, float* out, hipStream_t st) {
   const int nt = filter_select_threads(s);
+  const KeepAll keep{keep_ratio, filter_list_cap(s) / 2};
   const float scale = 0.08838834764831845f;   // 1/sqrt(128)
   const bool paged = kv.page.table != nullptr;
   // the pair (V type, K format) of this cache
@@ -497,7 +504,7 @@ hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, 
     hipLaunchKernelGGL((k_filter_select_attend<TYPE, PAGED, KIND, NT, RANGES>), dim3(s.B * s.Hq), dim3(NT),             \
                        (size_t)filter_select_attend_lds(s), st, s, score, slot, score_stride, seg_count, seg_rows,      \
                        nseg, cand, cand_count, group_start, line_total, range, bitmap, bitmap_words, k, topk_idx,       \
-                       topk_score, thr_state, margin, keep_ratio,                                                       \
+                       topk_score, thr_state, margin, keep,                                                             \
                        skip_if, rescored, q, kv.k, scale, flags, (const TYPE*)kv.v, kv.stride_b, kv.stride_h,           \
                        kv.stride_n, kv.page, kv.seq_lens, out);                                                         \
     launched = true;                                                                                                    \
@@ -514,10 +521,11 @@ static hipError_t launch_sa_t(const Shape& s, const float* score, int64_t score_
                               float* thr_state, int keep_ratio, const int32_t* skip_if, const KvView& kv, float* out,
                               hipStream_t st) {
   const int ce = select_attend_cache(s);
+  const KeepAll keep{keep_ratio, filter_list_cap(s) / 2};
   const T* V = (const T*)kv.v;
 #define LFPS_LAUNCH_SA(PAGED)                                                                                         \
   hipLaunchKernelGGL((k_select_attend<T, PAGED>), dim3(s.B * s.Hq), dim3(kSelThreads), (size_t)select_attend_lds(s),  \
-                     st, s, score, score_stride, cand, cand_count, k, topk_idx, topk_score, ce, thr_state, keep_ratio, skip_if, V, \
+                     st, s, score, score_stride, cand, cand_count, k, topk_idx, topk_score, ce, thr_state, keep, skip_if, V, \
                      kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, out)
   if (kv.page.table) {
     LFPS_LAUNCH_SA(true);

@@ -683,8 +683,8 @@ __global__ __launch_bounds__(64) void k_head_sparsity(Shape s, const float* __re
       if (topk_score) topk_score[(int64_t)bh * s.kmax + i] = 0.f;
     }
     // A bypassed head has no k-th score to remember, and a group with a NaN there would be taken as "no previous step" by
-    // the filtered scoring pass at every step; -inf keeps all of the group's candidates for this head, which costs little
-    // (its select is skipped) and spares the first step in which it is not bypassed the unfiltered pass.
+    // the filtered scoring pass at every step.  -inf makes the first step in which it is not bypassed keep all candidates
+    // for it (the scoring pass keeps nothing for a bypassed head) and spares that step the unfiltered pass.
     if (thr_state && lane == 0) thr_state[bh] = -INFINITY;
   }
 }
