@@ -192,7 +192,8 @@ int lfps_sparse_attn_noalloc(const lfps_config* cfg, const float* q, const lfps_
  * With a bf16 or fp16 cache the scoring pass keeps, per head, only rows whose score reaches the k-th best
  * score of the PREVIOUS lfps_step call on this context minus a margin (the context remembers one
  * float per head); a head for which that leaves fewer than k rows is rescored without the filter
- * in the same call (by that head's workgroup of the select kernel: no extra launches).  The result is therefore
+ * in the same call (by that head's workgroup of the select kernel: no extra launches); a head with so few candidates that
+ * filtering would save little keeps them all in the next step.  The result is therefore
  * the same exact Top-k over the candidates whatever the remembered value is; only the time differs.  The first
  * chained step after lfps_create or lfps_reset_history has nothing remembered and takes the unfiltered kernels; that
  * is decided on the host, so a HIP graph captured from such a call replays the unfiltered form: capture a later step.  (A context whose max_k exceeds ~13 000 starts with the
@@ -296,7 +297,8 @@ int lfps_poll_rescored(lfps_ctx* ctx, int32_t* n_heads, void* stream);
  * the summed milliseconds to ms[i] and the number of timed launches to launches[i] (host
  * arrays of LFPS_N_KERNELS), then resets the accumulators. */
 enum {
-  LFPS_KERNEL_CANDIDATES = 0,
+  LFPS_KERNEL_CANDIDATES = 0,   /* steps that find their candidates inside the filter_score launch (contexts of up to a million
+                                   rows, table form four million) count it here too, with next to no time; so TABLE_CANDIDATES */
   LFPS_KERNEL_GATHER_SCORE = 1,
   LFPS_KERNEL_SELECT = 2,
   LFPS_KERNEL_SPARSE_ATTN = 3,
