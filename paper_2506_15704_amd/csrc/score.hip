@@ -14,7 +14,7 @@
 //   fp16 cache: the same with v_mfma_f32_16x16x32_f16; the query terms are fp16 too, the second and third
 //     scaled up by 2^11 and 2^22 so that they stay normal numbers, and scaled back when the three
 //     D rows are added (fp16 x fp16 products are exact in fp32 as well).  |q| must stay below 65504.
-//   fp32 cache: 16 lanes per row, 8 channels each, fp32 FMAs and a 4-step xor-shuffle reduce.
+//   fp32 cache: 16 lanes per row, 8 channels each, fp32 FMAs and a reduce by lane permutations.
 #include "lfps_internal.h"
 #include "score_mfma.h"
 
