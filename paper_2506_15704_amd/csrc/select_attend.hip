@@ -106,6 +106,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   __shared__ SelectShared<NT> sm;
   __shared__ int seg_off[1024];
   __shared__ int wtot[kWaves], ctot[kWaves];
+  __shared__ int btot[kWaves];                     // the bitmap scan's: ctot may still be read by a slower wave then
   extern __shared__ char dyn[];                    // the attention's partial sums, then the list of selected rows
   AttendShared& as = *reinterpret_cast<AttendShared*>(dyn);
   SelRow* list = reinterpret_cast<SelRow*>(dyn + sizeof(AttendShared));
@@ -215,11 +216,11 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     int mine = 0;
     for (int w = w0; w < w1; ++w) mine += __popc(bm[w]);
     const int upto = wave_inclusive_sum(mine);
-    if (lane == 63) ctot[wv] = upto;                 // (read by nobody since the last barrier but one)
+    if (lane == 63) btot[wv] = upto;
     __syncthreads();
     int at = upto - mine;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) at += w < wv ? ctot[w] : 0;
+    for (int w = 0; w < kWaves; ++w) at += w < wv ? btot[w] : 0;
     for (int w = w0; w < w1; ++w)
       for (uint32_t bits = bm[w]; bits && at < c; bits &= bits - 1) sl[at++] = (w << 5) + __ffs(bits) - 1;
     __syncthreads();

@@ -135,3 +135,38 @@ def test_a_budget_of_most_candidates_keeps_them_all(L, k):
     assert a.lfps_poll_rescored() == 0
     a.close()
     b.close()
+
+
+# 1024, 512 and 256 threads per head; one to a few dozen words of bitmap, so that most waves own none
+@pytest.mark.parametrize("B,Hq,Hkv,L,k,r,page", [
+    (1, 4, 1, 40, 2, 0, 0), (2, 8, 2, 130, 8, 1, 16), (4, 32, 8, 301, 16, 2, 0), (8, 64, 16, 97, 5, 1, 0),
+    (17, 32, 8, 260, 12, 1, 64), (17, 32, 32, 700, 20, 3, 0)])
+def test_every_head_left_short_in_a_short_context(B, Hq, Hkv, L, k, r, page):
+    """Queries fifty times smaller than the step before: no score reaches the remembered threshold and every head scores the
+    group's candidates from the bitmap."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L + k)
+    Lcap = L + 8
+    cache = _cache(B, Hkv, Lcap, "bf16", page, g)
+    a, b = _pair(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="bf16", max_seq_len=Lcap, max_k=k, radius=r)
+    ks = torch.full((B,), k, dtype=torch.int32, device=DEV)
+    prev = torch.randint(0, L, (B, Hq, k), device=DEV, generator=g).to(torch.int32)
+    for t in range(1, 8):
+        q = torch.randn((B, Hq, 128), device=DEV, generator=g) * (4.0 if t % 2 else 0.02)
+        seq = torch.tensor([L - i % 3 + t for i in range(B)], dtype=torch.int32, device=DEV)
+        res = []
+        for ctx in (a, b):
+            idx = torch.full((B, Hq, k), -5, dtype=torch.int32, device=DEV)
+            sc, out = torch.full((B, Hq, k), -5.0, device=DEV), torch.full((B, Hq, 128), -5.0, device=DEV)
+            cnt = torch.full((B, Hkv), -5, dtype=torch.int32, device=DEV)
+            ctx.lfps_step(q, _view(ctx, cache, seq), prev, ks, idx, out, sc)
+            ctx.lfps_copy_cand_count(cnt)
+            res.append((idx, sc, out, cnt))
+        for x, y, name in zip(*res, ("index", "score", "output", "candidate count")):
+            assert torch.equal(x, y), (name, t, int((x != y).sum()))
+        if t % 2 == 0:
+            assert a.lfps_poll_rescored() > 0.9 * B * Hq, t
+        else:
+            a.lfps_poll_rescored()
+    a.close()
+    b.close()
