@@ -55,6 +55,7 @@ __device__ __forceinline__ void attend_rows(AttendShared& sm, const T* __restric
       if (r >= 0 && r < n) row = Rows::phys(pg, b, r);
     }
   };
+  const int pad_row = Rows::phys(pg, b, 0);   // what is read where there is no row (with weight 0): a row of this request
   int first_row = -1;                 // as a physical row (never negative), or -1 for "no row"
   float first_s = -INFINITY;
   float m = m_known;
@@ -117,7 +118,7 @@ __device__ __forceinline__ void attend_rows(AttendShared& sm, const T* __restric
           const int t = half * kBatch + u;
           const int row = __shfl(cur_row, 4 * t + rs);
           const float p = __shfl(cur_p, 4 * t + rs);
-          rw[u].load(Vbg + Rows::offset(pg, row < 0 ? 0 : row, stride_b, stride_n));
+          rw[u].load(Vbg + Rows::offset(pg, row < 0 ? pad_row : row, stride_b, stride_n));
           pw[u] = row < 0 ? 0.f : p;
         }
         __builtin_amdgcn_sched_barrier(0);                    // keep the batch's loads ahead of its arithmetic
@@ -157,7 +158,7 @@ __device__ __forceinline__ void attend_rows(AttendShared& sm, const T* __restric
 }
 
 // The same sum over the first ksel entries of a list in LDS (physical row, weight relative to the largest score), which
-// the caller has filled up to a multiple of 64 with entries of weight 0, for a head of budget kb: the chunks, the
+// the caller has filled up to a multiple of 64 with entries of weight 0 (pad_list), for a head of budget kb: the chunks, the
 // order of the additions and therefore the bits are those of attend_rows.  A wave issues the rows of a whole 64-entry
 // tile (16 loads per lane; 8 for fp32 rows, which take twice the registers) before it uses the first.
 template <typename T, int NW, bool kPaged, typename Entry>

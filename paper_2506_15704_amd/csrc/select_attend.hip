@@ -66,6 +66,14 @@ static __device__ __noinline__ void attend_global(AttendShared& as, const T* V, 
   attend_rows<T, NW, kPaged>(as, V, stride_b, stride_h, stride_n, page, b, g, n, kb, oi, os, true, top, out_row);
 }
 
+// Entries of weight 0 behind the ksel selected rows of a list, up to a multiple of 64 (and to `room`): the request's own row
+// 0.  (Row 0 of a paged pool may belong to nobody, and 0 times what it holds need not be 0.)
+template <int NT, bool kPaged>
+__device__ __forceinline__ void pad_list(SelRow* list, const KvPage& page, int b, int ksel, int room) {
+  const int end = ((ksel + 63) & ~63) < room ? (ksel + 63) & ~63 : room;
+  for (int i = ksel + threadIdx.x; i < end; i += NT) list[i] = SelRow{RowMap<kPaged>::phys(page, b, 0), 0.f};
+}
+
 // The rows a workgroup has just selected into global memory (oi, os; the caller's barrier has ordered the stores), as
 // the attention's list.
 template <int NT, bool kPaged>
@@ -198,7 +206,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     oi[i] = -1;
     os[i] = 0.f;
   }
-  for (int i = ksel + tid; i < ((ksel + 63) & ~63) && i < kSelRowsMax; i += NT) list[i] = SelRow{0, 0.f};
+  pad_list<NT, kPaged>(list, page, b, ksel, kSelRowsMax);
   if (ksel == 0) {
     if (tid == 0) thr_state[bh] = -INFINITY;
     if (out && tid < kD) out[(int64_t)bh * kD + tid] = 0.f;
@@ -356,7 +364,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_attend(
   if (c <= kRegElems * NT) {
     for (int i = tid; i < 2 * NT; i += NT) sm.hist[i] = 0u;
     if (tid == 0) sm.list_n = 0u;
-    for (int i = ksel + tid; i < ((ksel + 63) & ~63); i += NT) list[i] = SelRow{0, 0.f};
+    pad_list<NT, kPaged>(list, page, b, ksel, kSelRowsMax);
     __syncthreads();
     auto run = [&](auto elems) {
       constexpr int E = decltype(elems)::value;
@@ -400,7 +408,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_attend(
                                         out + (int64_t)bh * kD);
       return;
     }
-    for (int i = ksel + tid; i < ((ksel + 63) & ~63); i += NT) list[i] = SelRow{0, 0.f};
+    pad_list<NT, kPaged>(list, page, b, ksel, kSelRowsMax);
     list_from_global<NT, kPaged>(list, page, b, n, ksel, oi, os, top);
   }
   __syncthreads();

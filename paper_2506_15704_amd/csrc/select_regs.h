@@ -10,7 +10,8 @@ namespace lfps {
 
 constexpr int kRegElems = 16;
 
-// A selected row as the attention reads it: physical row and softmax numerator (a row to skip: row 0, weight 0).
+// A selected row as the attention reads it: physical row and softmax numerator (a row to skip: the request's row 0,
+// weight 0).
 struct SelRow {
   int32_t row;
   float p;

@@ -237,3 +237,48 @@ def test_paged_view_argument_errors(cases):
             ctx.lfps_full_attn_decode(dc.q(0), variant(**kw), out)
         assert text in str(e.value), (kw, str(e.value))
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32", "fp8", "fp8kv", "f16"])
+@pytest.mark.parametrize("budget", [1, 37, 63])
+def test_nothing_of_another_owners_block_reaches_an_output(cases, dtype, budget):
+    """Block 0 of the pool belongs to no request and holds NaN: budgets that do not fill a multiple of 64 entries give, through
+    every entry point that ends in sparse attention, what the contiguous cache gives."""
+    dc = cases[dtype]
+    spec, case = dc.spec, dc.case
+    pools = []
+    *both, table = gen_device.paginate(dc.K, dc.V, 16, seed=21)
+    for p in both:
+        raw = p.view(torch.uint8)
+        nan = torch.full_like(raw[:1], 0x7F if p.dtype == torch.float8_e4m3fn else 0xFF)
+        pools.append(torch.cat([nan, raw]).view(p.dtype))
+        assert pools[-1][0].float().isnan().all()
+    table = torch.where(table >= 0, table + 1, table)
+    ks = torch.full((spec.B,), budget, dtype=torch.int32, device=DEV)
+    bound = 4 * case.kmax * (2 * spec.r + 2) + 1
+    runs = []
+    for paged in (False, True):
+        outs = []
+        for cap in (0, min(bound, case.Lcap) - 1):       # steps through the range kernel, and through the separate ones
+            ctx = dc.make_ctx(cand_cap=cap)
+            view = lambda t: (ctx.paged_kv_view(*pools, table, dc.seq_lens(t)) if paged else
+                              ctx.kv_view(dc.K, dc.V, dc.seq_lens(t)))
+            prev, sc, out = _bufs(dc)
+            ctx.lfps_exact_topk(dc.q(0), view(0), ks, prev)
+            for t in range(1, spec.T + 1):               # the first one from full score rows
+                idx, sc, out = _bufs(dc)
+                ctx.lfps_step(dc.q(t), view(t), prev, ks, idx, out, sc)
+                outs += [idx, sc, out]
+                prev = idx
+            given, scores = idx.clone(), sc.clone()
+            given[:, :, 0] = -1                          # padding inside a list
+            for call in (lambda o: ctx.lfps_sparse_attn(dc.q(t), view(t), given, scores, ks, o),
+                         lambda o: ctx.lfps_sparse_attn(dc.q(t), view(t), given, None, ks, o),
+                         lambda o: ctx.lfps_sparse_attn_noalloc(dc.q(t), view(t), given, ks, o)):
+                outs.append(torch.full_like(out, -7.0))
+                call(outs[-1])
+            ctx.close()
+        runs.append(outs)
+    for i, (x, y) in enumerate(zip(*runs)):
+        assert not y.isnan().any(), i
+        assert torch.equal(x, y), (i, int((x != y).sum()))
