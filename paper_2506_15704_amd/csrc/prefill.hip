@@ -16,6 +16,8 @@
 #include "lfps_internal.h"
 #include "score_mfma.h"
 
+#include <float.h>
+
 #include <type_traits>
 
 namespace lfps {
@@ -23,7 +25,8 @@ namespace lfps {
 constexpr int kHistWaves = 8;          // one workgroup per CU: the query operands fill its LDS, the rows its registers
 constexpr int kHistSub = 8;            // 16-row sub-tiles a wave holds: 128 rows
 constexpr int kHistRows = 16 * kHistSub;
-constexpr float kNoScore = -1e30f;     // stands for "row not seen": below every score, and finite (see exp_scaled)
+constexpr float kNoScore = -FLT_MAX;   // stands for "row not seen"
+constexpr float kLeastMax = -1.7e38f;  // the largest score is taken as at least this: a row not seen weighs 0 beside any
 
 // The value of lane (lane - 1) of my 16 lanes; lane 0 receives lane 15's.
 __device__ __forceinline__ float rotate16(float x) {
@@ -31,10 +34,12 @@ __device__ __forceinline__ float rotate16(float x) {
 }
 
 // exp(y / sqrt(D)) for y <= 0 to about one unit in the last place: exp2 of the rounded product, corrected by the product's
-// rounding error (six instructions; without expf's handling of other ranges: results below 2^-126 are 0, and y is finite).
+// rounding error (seven instructions; without expf's handling of other ranges: results below 2^-126 are 0).  -inf gives 0,
+// a NaN stays one.
 __device__ __forceinline__ float exp_scaled(float y) {
   constexpr double c = 0.08838834764831845 * 1.4426950408889634;            // log2(e) / sqrt(128)
   constexpr float hi = (float)c, lo = (float)(c - (double)hi), ln2 = 0.6931471805599453f;
+  y = __builtin_elementwise_maximum(y, -1e30f);                             // (the correction below needs a finite y)
   const float t = y * hi;
   const float r = fmaf(y, lo, fmaf(y, hi, -t));
   const float e = __builtin_amdgcn_exp2f(t);
@@ -114,7 +119,7 @@ __device__ __forceinline__ void wave_run(int tiles, int w, int waves, int& lo, i
 
 // grid (blocks per group, B*Hkv).  Queries j0 .. j0 + nq - 1 (j = 1: the most recent); query j sees the offloaded rows
 // [n_sink, n - j + 1).  part_m / part_l [bg, block, jq, h]: the largest q . K and the sum of the exponentials relative
-// to it over the rows of the block (kNoScore and 0 when it has none).  dots (or NULL; one query only): every q . K,
+// to it over the rows of the block (kLeastMax and 0 when it has none).  dots (or NULL; one query only): every q . K,
 // [B, Hq, stride].
 template <int G, bool kPaged, int kKind>
 __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
@@ -135,7 +140,7 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   report_q_range(stage_hist_operands<G>(ops, q0, q_stride, (int64_t)b * s.Hq + (int64_t)g * G, nq), flags);
   for (int e = tid; e < kHistWaves * kHistBatch * 4; e += kHistWaves * 64) {
-    (&wm[0][0][0])[e] = kNoScore;
+    (&wm[0][0][0])[e] = kLeastMax;
     (&wl[0][0][0])[e] = 0.0;
   }
   __syncthreads();
@@ -172,7 +177,7 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
         for (int t = 0; t < kHistSub; ++t) l += (double)exp_scaled(v[t] - m);
         l = row16_sum(l);
         if (j == 0) {
-          wl[wave][jq][kb] = m > kNoScore ? wl[wave][jq][kb] * (double)exp_scaled(m_old - m) + l : 0.0;
+          wl[wave][jq][kb] = wl[wave][jq][kb] * (double)exp_scaled(m_old - m) + l;
           wm[wave][jq][kb] = m;
         }
         if (my_dots) {
@@ -190,7 +195,7 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
   __syncthreads();
   for (int e = tid; e < nq * G; e += kHistWaves * 64) {
     const int jq = e / G, h = e % G;
-    float m = kNoScore;
+    float m = kLeastMax;
 #pragma unroll
     for (int w = 0; w < kHistWaves; ++w) m = fmaxf(m, wm[w][jq][h]);
     double l = 0.0;
@@ -207,7 +212,7 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
 template <int kPer>
 __device__ __forceinline__ void merge_hist(const float* part_m, const double* part_l, int64_t o, int64_t step, int blocks,
                                            int sub, double gamma, int n_queries, float& m, double& norm) {
-  m = kNoScore;
+  m = kLeastMax;
 #pragma unroll 8
   for (int k = sub; k < blocks; k += kPer) m = fmaxf(m, part_m[o + k * step]);
 #pragma unroll
@@ -288,8 +293,7 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_apply(
           const int row = base + 16 * t + j;
           v[t] = row >= s.n_sink && row < n - (j0 + jq) + 1 ? v[t] : kNoScore;
         }
-        float w = weigh(exp_scaled(v[t] - m), hi, lo);
-        if constexpr (decltype(masked)::value) w = v[t] > kNoScore ? w : 0.f;
+        const float w = weigh(exp_scaled(v[t] - m), hi, lo);
         av[t] += w;
         const float moved = j != 0 ? up[t] : (t == 0 ? cin : up[t > 0 ? t - 1 : 0]);
         as[t] = moved + w;

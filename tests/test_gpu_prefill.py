@@ -100,3 +100,46 @@ def test_priors_at_split_edges(L, heads, fmt, page, n_sink):
                 np.testing.assert_allclose(vbar[b, g].cpu().numpy(), ov, rtol=0, atol=2e-6)
                 assert float(s2[b, spec.G * g + h]) == pytest.approx(os2, rel=2e-5, abs=1e-9)
     ctx.close()
+
+
+# one query (from stored dot products), one batch of queries, two; rows in whole 128-row tiles and in the ones cut by the
+# sinks and by the end
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("s", [1, 5, 33])
+@pytest.mark.parametrize("bad,value", [((4, 130, 131, 255, 600, 699), -np.inf), ((200,), np.nan), ((5, 690), np.nan),
+                                       ((300,), np.inf)])
+def test_tables_where_scores_are_not_finite(dtype, s, bad, value):
+    """A row that scores -inf weighs nothing.  Where a score is NaN or +inf the softmax has no value: the entries of that row
+    are NaN and the query adds nothing elsewhere."""
+    from paper_2506_15704_amd.binding import Lfps
+    L, n_sink, gamma = 700, 4, 0.95
+    dt = {"bf16": torch.bfloat16, "f32": torch.float32}[dtype]
+    g = torch.Generator(device=DEV)
+    g.manual_seed(s)
+    K = torch.randn((1, 1, L + 8, 128), device=DEV, generator=g).to(dt)
+    q = torch.randn((s, 1, 2, 128), device=DEV, generator=g).to(torch.bfloat16).float()   # (whole in one term of the split)
+    q[..., :2] = 2.0
+    for i in bad:
+        K[0, 0, i] = 0
+        K[0, 0, i, :2] = {-np.inf: -3e38, np.inf: 3e38}.get(value, value)                  # 2 * -3e38 - ... = -inf in fp32
+    ctx = Lfps(batch=1, n_q_heads=2, n_kv_heads=1, kv_dtype=dtype, max_seq_len=L + 8, max_k=16, radius=1, n_sink=n_sink,
+               table_mode=True, table_decay=gamma)
+    seq = torch.tensor([L], dtype=torch.int32, device=DEV)
+    ctx.lfps_tables_init(q.contiguous(), ctx.kv_view(K, K, seq))
+    ver, sla = (torch.zeros((1, 2, L + 8), dtype=torch.float64, device=DEV) for _ in range(2))
+    ctx.lfps_tables_export(ver, sla, seq)
+    for h in range(2):
+        w = np.zeros((s, L))
+        for j in range(1, s + 1):
+            seen = L - j + 1
+            sc = orc.scores(q[j - 1, 0, h].cpu().numpy(), K[0, 0, :seen].float().cpu().numpy())[n_sink:]
+            at = np.array([i - n_sink for i in bad if i < seen], dtype=int)
+            sc[at] = -np.inf
+            w[j - 1, n_sink:seen] = np.exp(sc - sc.max()) / np.exp(sc - sc.max()).sum()
+            if value != -np.inf and len(at):
+                w[j - 1] = 0
+                w[j - 1, at + n_sink] = np.nan
+        want = tor.init_tables(w, gamma, n_sink)
+        for got, ref in zip((ver, sla), want):
+            np.testing.assert_allclose(got[0, h, :L].cpu().numpy(), ref, rtol=2e-5, atol=1e-12)
+    ctx.close()
