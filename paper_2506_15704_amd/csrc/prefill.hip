@@ -805,12 +805,14 @@ hipError_t launch_table_state(const Shape& s, const float* tab_ver, const float*
   return hipGetLastError();
 }
 
-// The rows of a group are cut so that about 1024 workgroups share K and V, each with at least 256 rows.
+// The rows of a group are cut so that about 1024 workgroups share K and V, each with at least 256 rows, but into at least
+// four parts: a lane then adds n / 64 rows in fp32 at most, however many groups there are (8192 rows with a mean of 0.5, RMS
+// error of the mean: 1.7e-8; with one part for each of 1024 groups, n / 16 rows a lane, 3.9e-8).
 static int prior_splits(const Shape& s) {
   const int by_len = (s.Lcap + 255) / 256;
   int n = (1024 + s.B * s.Hkv - 1) / (s.B * s.Hkv);
   n = n < by_len ? n : by_len;
-  return n < 1 ? 1 : n;
+  return n < 4 ? 4 : n;
 }
 
 int64_t prior_scratch_bytes(const Shape& s) {
