@@ -26,8 +26,7 @@
 // their number, with 64-bit geometry), 4.4 into the select over LDS and 5.4 into the attention, which fetched the pairs
 // back from global memory first.  Now the survivors go straight into registers (as many searches as a thread needs,
 // 32-bit geometry) and stay there (select_regs.h), and the workgroup has as many threads as the number of heads leaves
-// room for: 13 us (2.1 + 2.7 + 2.9 + 4.0); 512 heads, k = 2048: 45.8 -> 41 us, 1024 ragged heads: 52.7 -> 39 us (all of them
-// resident at once now).
+// room for: 13 us (2.1 + 2.7 + 2.9 + 4.0); 512 heads, k = 2048: 45.8 -> 41 us, 1024 ragged heads: 52.7 -> 41 us.
 #include "attend.h"
 #include "range_geometry.h"
 #include "score_mfma.h"
@@ -47,13 +46,14 @@ __device__ __forceinline__ bool filter_pays(int c, int ksel, const KeepAll& keep
 
 constexpr int kSelRowsMax = 16384;    // selected rows of a head that pass through LDS; more go through global memory
 
-// Threads per head: every head's workgroup is resident at once (16 waves per CU: the attention's loads in flight set
-// the registers), unless the survivors of the largest budget need the registers of more threads.
+// Threads per head (16 waves per CU: the attention's loads in flight set the registers): 1024 while every head's workgroup is
+// resident at once, else 512, unless the survivors of the largest budget need the registers of more threads.  Not 256, also
+// where that would make more than 512 heads resident at once: whole steps of 1024 heads were then 0 to 2.4 % faster (k = 512
+// 172 -> 168 us, k = 1000 to 2048 within 0.5 %, ragged budgets of 330 to 1311 630 -> 615 for four steps), but those in which a
+// change of the queries leaves 2 to 10 % of the heads short 5 to 28 % slower (k = 512 239 -> 307 us, 1000 399 -> 443, 2048
+// 649 -> 727: the unfiltered pass of a head has half the waves), and the list holds 4096 survivors instead of 8192.
 static int filter_select_threads(const Shape& s) {
-  const int heads = s.B * s.Hq;
-  int nt = heads <= 256 ? 1024 : (heads <= 512 ? 512 : 256);
-  while (nt < 1024 && kRegElems * nt < 2 * s.kmax) nt *= 2;
-  return nt;
+  return s.B * s.Hq <= 256 || kRegElems * 512 < 2 * s.kmax ? 1024 : 512;
 }
 
 int filter_list_cap(const Shape& s) { return kRegElems * filter_select_threads(s); }
@@ -437,7 +437,6 @@ static int select_attend_lds(const Shape& s) {
 // FP8 V with FP8 keys, fp16 V with fp16 keys), times paged or not, times the threads per head, times the form
 // of the lists.
 #define LFPS_FSA_FOR_EACH_NT(X, TYPE, PAGED, KIND)                                \
-  X(TYPE, PAGED, KIND, 256, false) X(TYPE, PAGED, KIND, 256, true)                \
   X(TYPE, PAGED, KIND, 512, false) X(TYPE, PAGED, KIND, 512, true)                \
   X(TYPE, PAGED, KIND, 1024, false) X(TYPE, PAGED, KIND, 1024, true)
 #define LFPS_FSA_FOR_EACH(X)                               \

@@ -24,7 +24,7 @@ def _reference(ctx, q, kv, prev, k, seq):
     return idx, sc, out
 
 
-# heads: up to 256 -> 1024 threads, up to 512 -> 512, more -> 256 (unless the budget needs more); budgets that put the
+# heads: up to 256 -> 1024 threads, more -> 512 (unless the budget needs more); budgets that put the
 # survivors on both sides of 2, 4, 8 and 16 elements per thread; dtype f32 = the select from full score rows
 @pytest.mark.parametrize("B,Hq,Hkv,L,k,r,dtype", [
     (1, 4, 1, 3000, 63, 2, "bf16"), (1, 4, 1, 3001, 1, 0, "bf16"), (2, 8, 2, 6000, 1600, 3, "bf16"),
@@ -98,3 +98,31 @@ def test_stand_alone_select(L, k, values):
     want = (torch.gather(dots, 1, order).float() * torch.tensor(0.08838834764831845, dtype=torch.float32))
     assert torch.equal(sc[0].cpu(), want)
     ctx.close()
+
+
+def test_many_heads_hold_survivors_of_several_budgets():
+    """544 heads, each with more than two budgets of survivors (larger queries than the step before): they fit the select's
+    list, and no head is scored again."""
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    B, Hq, Hkv, L, k = 17, 32, 8, 12000, 2048
+    K = torch.randn((B, Hkv, L + 8, 128), device=DEV, generator=g).to(torch.bfloat16)
+    ctxs = [Lfps(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="bf16", max_seq_len=L + 8, max_k=k, radius=4) for _ in range(2)]
+    ctxs[1].lfps_set_filter(False)
+    ks = torch.full((B,), k, dtype=torch.int32, device=DEV)
+    q = torch.randn((B, Hq, 128), device=DEV, generator=g)
+    prev = torch.zeros((B, Hq, k), dtype=torch.int32, device=DEV)
+    ctxs[0].lfps_exact_topk(q, ctxs[0].kv_view(K, K, torch.full((B,), L, dtype=torch.int32, device=DEV)), ks, prev)
+    ctxs[0].lfps_poll_rescored()
+    for t, scale in ((1, 1.0), (2, 3.0)):
+        seq = torch.full((B,), L + t, dtype=torch.int32, device=DEV)
+        res = []
+        for ctx in ctxs:
+            idx, out = torch.zeros((B, Hq, k), dtype=torch.int32, device=DEV), torch.zeros((B, Hq, 128), device=DEV)
+            ctx.lfps_step(scale * q, ctx.kv_view(K, K, seq), prev, ks, idx, out)
+            res.append((idx, out))
+        assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1]), t
+        assert ctxs[0].lfps_poll_rescored() == 0, t
+    for ctx in ctxs:
+        ctx.close()
