@@ -23,6 +23,7 @@ struct lfps_ctx {
   int32_t* slot;       // [B, Hq, score_stride] candidate slots of the filtered survivors
   int32_t* seg_count;  // [B, Hq, nseg]
   float* thr_state;    // [B, Hq] k-th best score of the previous step
+  int32_t* keep_fits;  // [B, Hq] 1: the candidates of the head's last step fitted half of the select's list (table mode, else NULL)
   int range[2];        // rows of a range when a step (0 memoryless, 1 table form) takes the range kernel, else 0
   uint32_t* bitmap;    // [B, Hkv, bitmap_words] the candidates of such a step
   int bitmap_words;
@@ -177,7 +178,8 @@ int check_config(const lfps_config* c, Sizes* z, char* err, size_t errn) {
   if (c->table_mode && table_init_scratch_bytes(s) > z->aux_b) z->aux_b = table_init_scratch_bytes(s);
   z->aux_b = align256(z->aux_b);
   z->total = z->score_b + z->cand_b + z->count_b + z->sel_b + z->part_b + z->slot_b + z->seg_b + z->thr_b +
-             z->line_b + 256 + z->x_b + z->aux_b + z->bitmap_b + z->tver_b + z->tsla_b + z->tstate_b + 2 * z->tflag_b + z->thr_b /* gate marks */;
+             z->line_b + 256 + z->x_b + z->aux_b + z->bitmap_b + z->tver_b + z->tsla_b + z->tstate_b + 2 * z->tflag_b +
+             z->thr_b /* gate marks */ + (c->table_mode ? z->thr_b : 0) /* keep_fits */;
   return LFPS_OK;
 }
 
@@ -381,6 +383,8 @@ int lfps_create(const lfps_config* cfg, lfps_ctx** out) {
     c->flag_words = z.flag_words;
   }
   c->gate = (int32_t*)p;
+  p += z.thr_b;
+  if (cfg->table_mode) c->keep_fits = (int32_t*)p;
   c->nseg = z.nseg;
   // The filtered pass pays off only if a head's survivors (about 1.25 x its budget) fit the select's list; with a
   // budget too large for that every head would be rescored anyway, so such a context starts with the filter off.
@@ -395,6 +399,7 @@ int lfps_create(const lfps_config* cfg, lfps_ctx** out) {
   if (e == hipSuccess && cfg->table_mode)
     e = hipMemset(c->tab_ver, 0, (size_t)(z.tver_b + z.tsla_b + z.tstate_b + 2 * z.tflag_b));
   if (e == hipSuccess) e = hipMemset(c->gate, 0, (size_t)z.thr_b);
+  if (e == hipSuccess && c->keep_fits) e = hipMemset(c->keep_fits, 0, (size_t)z.thr_b);
   if (e == hipSuccess) e = configure_candidates(s);
   if (e == hipSuccess) e = configure_select(s, cfg->kv_dtype, cfg->k_fp8 != 0, cfg->v_fp8 != 0);
   if (e == hipSuccess && cfg->table_mode && cfg->kv_dtype != LFPS_F32) e = configure_table_history(s, key_kind(*cfg));
@@ -503,7 +508,7 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
   int64_t* line_total = ctx->group_start + (int64_t)s.B * s.Hkv;
   const bool filtered = next_step_filtered(ctx);
   const int range = next_step_range(ctx, from.prev_topk == nullptr);
-  const int keep_ratio = from.prev_topk ? kKeepRatio : kKeepRatioTables;
+  const KeepAll keep{from.prev_topk ? kKeepRatio : kKeepRatioTables, ctx->keep_fits, 0};
   ctx->no_history = 0;                       // either form leaves every selecting head's k-th best score behind
   if (range) {
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
@@ -520,7 +525,7 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
            launch_filter_select_attend(s, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
                                        ctx->flags + 1, ctx->nseg, ctx->cand, ctx->cand_count, ctx->group_start,
                                        line_total, range, ctx->bitmap, ctx->bitmap_words, k, topk_idx, sel,
-                                       ctx->thr_state, kFilterMargin, keep_ratio, skip_if, ctx->flags + 2, q, ctx->flags, v, out, st));
+                                       ctx->thr_state, kFilterMargin, keep, skip_if, ctx->flags + 2, q, ctx->flags, v, out, st));
     return LFPS_OK;
   }
   LAUNCH(ctx, LFPS_KERNEL_GATHER_SCORE, st,
@@ -528,7 +533,7 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
                             ctx->flags, st));
   LAUNCH(ctx, LFPS_KERNEL_SELECT_ATTEND, st,
          launch_select_attend(s, ctx->cfg.kv_dtype, ctx->score, s.score_stride, ctx->cand, ctx->cand_count, k, topk_idx,
-                              sel, ctx->thr_state, keep_ratio, skip_if, v, out, st));
+                              sel, ctx->thr_state, keep, skip_if, v, out, st));
   return LFPS_OK;
 }
 
@@ -686,7 +691,7 @@ int lfps_exact_topk(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int3
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SELECT_ATTEND, st,
            launch_filter_select_attend(sd, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
                                        ctx->flags + 1, ctx->nseg, nullptr, ctx->x_cnt, ctx->x_start, x_total, 0, nullptr, 0, k, topk_idx,
-                                       topk_score ? topk_score : ctx->sel_score, ctx->thr_x, 0.f, kKeepRatio, nullptr, nullptr,
+                                       topk_score ? topk_score : ctx->sel_score, ctx->thr_x, 0.f, KeepAll{kKeepRatio, nullptr, 0}, nullptr, nullptr,
                                        q, ctx->flags, v, nullptr, st));
     return LFPS_OK;
   }
@@ -865,7 +870,7 @@ int lfps_head_sparsity(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const f
   int rc = check_kv(ctx, kv, false, &v);
   if (rc != LFPS_OK) return rc;
   hipError_t e = launch_head_sparsity(ctx->shape, ctx->cfg.kv_dtype, q, v, kbar, sigma2_hat, n_local, eps, rho, gate,
-                                      nullptr, nullptr, nullptr, nullptr, nullptr, (hipStream_t)stream);
+                                      nullptr, nullptr, nullptr, nullptr, (hipStream_t)stream);
   if (e != hipSuccess) return fail(ctx, LFPS_EHIP, "lfps_head_sparsity", e);
   return LFPS_OK;
 }
@@ -885,7 +890,7 @@ int lfps_table_step_gated(lfps_ctx* ctx, const float* q, const lfps_kv* kv, cons
   hipStream_t st = (hipStream_t)stream;
   int32_t* gate = gate_out ? gate_out : ctx->gate;
   hipError_t e = launch_head_sparsity(ctx->shape, ctx->cfg.kv_dtype, q, v, kbar, sigma2_hat, n_local, eps, nullptr,
-                                      gate, vbar, topk_idx, topk_score, out, ctx->filter_on ? ctx->thr_state : nullptr, st);
+                                      gate, vbar, topk_idx, topk_score, out, st);
   if (e != hipSuccess) return fail(ctx, LFPS_EHIP, "lfps_table_step_gated (gate)", e);
   return table_step_impl(ctx, q, v, k, topk_idx, topk_score, out, gate, st);
 }

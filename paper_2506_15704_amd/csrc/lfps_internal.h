@@ -125,15 +125,22 @@ hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, 
 // is short or overfull takes the unfiltered pass inside the kernel (counted in *rescored), which needs q, the K rows
 // and the group's candidate list (cand; NULL = all rows 0 .. cand_count-1) and overwrites the head's score row.
 // range > 0: the lists are those of launch_range_score with that range (cand, seg_rows, group_start, line_total unused;
-// the candidates are in bitmap), and cand_count is written.  keep_ratio: a head with fewer than keep_ratio * k candidates
-// (and no more than half of filter_list_cap) leaves -inf in thr_state instead of its k-th best score.
+// the candidates are in bitmap), and cand_count is written.
+// keep: a head with fewer than keep.ratio * k candidates, and no more than keep.most, leaves -inf in thr_state instead of its
+// k-th best score; keep.fits [B, Hq] (or NULL) receives whether it had no more than keep.most, and a bypassed head (skip_if)
+// leaves -inf unless it has a score and had more.  The launchers set most: half of filter_list_cap.
+struct KeepAll {
+  int ratio;
+  int32_t* fits;
+  int most;
+};
 hipError_t configure_select_attend(const Shape& s, int dtype, bool k_fp8, bool v_fp8);
 hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, int32_t* slot,
                                        int64_t score_stride, const int32_t* seg_count, const int32_t* seg_rows, int nseg,
                                        const int32_t* cand, int32_t* cand_count, const int64_t* group_start,
                                        int64_t* line_total, int range, const uint32_t* bitmap, int bitmap_words,
                                        const int32_t* k, int32_t* topk_idx, float* topk_score,
-                                       float* thr_state, float margin, int keep_ratio, const int32_t* skip_if, int32_t* rescored,
+                                       float* thr_state, float margin, KeepAll keep, const int32_t* skip_if, int32_t* rescored,
                                        const float* q, int32_t* flags, const KvView& kv, float* out,
                                        hipStream_t st);   // out == NULL: select only
 
@@ -149,7 +156,7 @@ hipError_t launch_dense_prep(const Shape& s, const int32_t* seq_lens, const int3
 // From the full score rows [B, Hq, score_stride] over cand, every head.
 hipError_t launch_select_attend(const Shape& s, int dtype, const float* score, int64_t score_stride, const int32_t* cand,
                                 const int32_t* cand_count, const int32_t* k, int32_t* topk_idx, float* topk_score,
-                                float* thr_state, int keep_ratio, const int32_t* skip_if, const KvView& kv, float* out,
+                                float* thr_state, KeepAll keep, const int32_t* skip_if, const KvView& kv, float* out,
                                 hipStream_t st);
 
 // Per (b, h): the k_b best of score[b,h,0:count]; count = cand_count[b, g(h)] when cand != NULL,
@@ -219,11 +226,10 @@ hipError_t launch_table_history(const Shape& s, float* tab_ver, float* tab_sla, 
 hipError_t launch_table_state(const Shape& s, const float* tab_ver, const float* tab_sla, double* state,
                               const int32_t* seq_lens, void* scratch, bool have_moments, hipStream_t st);
 // Head sparsity (Eq. 5-6) and the prefill priors it needs; gate [B,Hq] marks bypassed heads, whose output
-// row (vbar) and index row (-1) the kernel writes when out != NULL; thr_state (or NULL): the score filter's
-// per-head history, where a bypassed head is given -inf.
+// row (vbar) and index row (-1) the kernel writes when out != NULL.
 hipError_t launch_head_sparsity(const Shape& s, int dtype, const float* q, const KvView& kv, const float* kbar,
                                 const float* sigma2_hat, int n_local, float eps, float* rho, int32_t* gate,
-                                const float* vbar, int32_t* topk_idx, float* topk_score, float* out, float* thr_state,
+                                const float* vbar, int32_t* topk_idx, float* topk_score, float* out,
                                 hipStream_t st);
 // scratch: prior_scratch_bytes.
 int64_t prior_scratch_bytes(const Shape& s);

@@ -171,7 +171,7 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
   const int piece = 4 * (int)blockIdx.x + wave;
   const int out0 = geo.start(piece);                      // where its survivors go in the heads' rows
   const int64_t head = head0 + (kb < G ? kb : 0);
-  const uint64_t nans = __ballot(kb < G && isnan(thr));
+  const uint64_t nans = __ballot(kb < G && isnan(thr) && !skipped);
   if (cnt == 0 || nans) {
     if (j == 0 && kb < G) seg_count[head * nseg + piece] = cnt << 16;
     return;

@@ -143,16 +143,15 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
     int n = seq_lens[b];
     n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
     const int64_t head = (int64_t)b * s.Hq + (int64_t)g * G + (kb < G ? kb : 0);
-    // NaN in thr_state = "no previous step": skip the group here, the unfiltered pass will take it
-    bool no_history = false;
-#pragma unroll
-    for (int h = 0; h < G; ++h) no_history |= isnan(thr_state[(int64_t)b * s.Hq + (int64_t)g * G + h]);
-    if (no_history) {
+    // NaN in thr_state = "no previous step": skip the group here, the unfiltered pass will take it.  (A bypassed head keeps
+    // nothing, and needs no step before this one.)
+    const float thr = thr_state[head];
+    const bool skipped = skip_if && skip_if[head] != 0;
+    if (__ballot(kb < G && !skipped && isnan(thr))) {
       if (j == 0 && kb < G) seg_count[head * nseg + seg] = 0;
       continue;
     }
-    // (a bypassed head keeps nothing)
-    const float tau = kb < G && !(skip_if && skip_if[head] != 0) ? thr_state[head] - margin : INFINITY;
+    const float tau = kb < G && !skipped ? thr - margin : INFINITY;
 
     using Rows = RowMap<kPaged>;
     using Tile = KTile<kKind>;

@@ -36,12 +36,18 @@
 
 namespace lfps {
 
-struct KeepAll {
-  int ratio, most;
-};
 // Is the k-th best of c candidates a threshold worth remembering?  (keep: c < keep.ratio * k and c <= keep.most)
 __device__ __forceinline__ bool filter_pays(int c, int ksel, const KeepAll& keep) {
   return c / keep.ratio >= ksel || c > keep.most;
+}
+
+// What a bypassed head remembers, by one thread: it has no k-th best score of this step.  -inf makes the first step in which
+// it is not bypassed keep all candidates for it (the scoring pass keeps nothing for a bypassed head) and spares that step
+// the unfiltered pass, which the score of an older step would often not.  But a head that had more candidates than half of
+// the list in its last step would be sure to take that pass then: it keeps its score.  (Here, where nobody waits for it: in
+// the gate's kernel the two loads cost each step 0.5 us.)
+__device__ __forceinline__ void remember_bypassed(float* thr_state, const KeepAll& keep, int bh) {
+  if (!(isfinite(thr_state[bh]) && keep.fits && keep.fits[bh] == 0)) thr_state[bh] = -INFINITY;
 }
 
 constexpr int kSelRowsMax = 16384;    // selected rows of a head that pass through LDS; more go through global memory
@@ -124,7 +130,10 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int bg = b * s.Hkv + g;
   const bool skipped = skip_if && skip_if[bh] != 0;  // bypassed head: its rows were written by the gate
-  if (skipped && !(kRanges && h % s.G == 0)) return;
+  if (skipped && !(kRanges && h % s.G == 0)) {
+    if (tid == 0) remember_bypassed(thr_state, keep, bh);
+    return;
+  }
   int raw[kPieces];                                  // piece counts of this head, masked once the geometry is known
 #pragma unroll
   for (int u = 0; u < kPieces; ++u) {
@@ -180,7 +189,10 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) c += ctot[w];
     if (tid == 0 && h % s.G == 0) cand_count[bg] = c;
-    if (skipped) return;
+    if (skipped) {
+      if (tid == 0) remember_bypassed(thr_state, keep, bh);
+      return;
+    }
   }
   const int ksel = kb < c ? kb : c;
   int base = 0, n_surv = 0;
@@ -212,6 +224,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     if (out && tid < kD) out[(int64_t)bh * kD + tid] = 0.f;
     return;
   }
+  if (keep.fits && tid == 0) keep.fits[bh] = c <= keep.most;
   float* thr_out = filter_pays(c, ksel, keep) ? thr_state + bh : nullptr;
   if (!thr_out && tid == 0) thr_state[bh] = -INFINITY;      // (every thread has read it before the barrier)
   float* sc = score + (int64_t)bh * score_stride;
@@ -335,7 +348,10 @@ __global__ __launch_bounds__(kSelThreads) void k_select_attend(
   const int bh = head_of_block(s, blockIdx.x);
   const int b = bh / s.Hq, h = bh % s.Hq, g = h / s.G;
   const int tid = threadIdx.x;
-  if (skip_if && skip_if[bh] != 0) return;          // bypassed head: its rows were written by the gate
+  if (skip_if && skip_if[bh] != 0) {                // bypassed head: its rows were written by the gate
+    if (thr_state && tid == 0) remember_bypassed(thr_state, keep, bh);
+    return;
+  }
   int c = cand_count[b * s.Hkv + g];
   c = c < 0 ? 0 : (c > s.cand_cap ? s.cand_cap : c);
   int kb = kk[b];
@@ -355,6 +371,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_attend(
     if (tid < kD) out[(int64_t)bh * kD + tid] = 0.f;
     return;
   }
+  if (keep.fits && tid == 0) keep.fits[bh] = c <= keep.most;
   if (thr_out && !filter_pays(c, ksel, keep)) {
     if (tid == 0) *thr_out = -INFINITY;
     thr_out = nullptr;
@@ -488,10 +505,10 @@ hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, 
                                        const int32_t* cand, int32_t* cand_count, const int64_t* group_start,
                                        int64_t* line_total, int range, const uint32_t* bitmap, int bitmap_words,
                                        const int32_t* k, int32_t* topk_idx, float* topk_score,
-                                       float* thr_state, float margin, int keep_ratio, const int32_t* skip_if, int32_t* rescored,
+                                       float* thr_state, float margin, KeepAll keep, const int32_t* skip_if, int32_t* rescored,
                                        const float* q, int32_t* flags, const KvView& kv, float* out, hipStream_t st) {
   const int nt = filter_select_threads(s);
-  const KeepAll keep{keep_ratio, filter_list_cap(s) / 2};
+  keep.most = filter_list_cap(s) / 2;
   const float scale = 0.08838834764831845f;   // 1/sqrt(128)
   const bool paged = kv.page.table != nullptr;
   // the pair (V type, K format) of this cache
@@ -526,10 +543,10 @@ hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, 
 template <typename T>
 static hipError_t launch_sa_t(const Shape& s, const float* score, int64_t score_stride, const int32_t* cand,
                               const int32_t* cand_count, const int32_t* k, int32_t* topk_idx, float* topk_score,
-                              float* thr_state, int keep_ratio, const int32_t* skip_if, const KvView& kv, float* out,
+                              float* thr_state, KeepAll keep, const int32_t* skip_if, const KvView& kv, float* out,
                               hipStream_t st) {
   const int ce = select_attend_cache(s);
-  const KeepAll keep{keep_ratio, filter_list_cap(s) / 2};
+  keep.most = filter_list_cap(s) / 2;
   const T* V = (const T*)kv.v;
 #define LFPS_LAUNCH_SA(PAGED)                                                                                         \
   hipLaunchKernelGGL((k_select_attend<T, PAGED>), dim3(s.B * s.Hq), dim3(kSelThreads), (size_t)select_attend_lds(s),  \
@@ -546,9 +563,9 @@ static hipError_t launch_sa_t(const Shape& s, const float* score, int64_t score_
 
 hipError_t launch_select_attend(const Shape& s, int dtype, const float* score, int64_t score_stride, const int32_t* cand,
                                 const int32_t* cand_count, const int32_t* k, int32_t* topk_idx, float* topk_score,
-                                float* thr_state, int keep_ratio, const int32_t* skip_if, const KvView& kv, float* out,
+                                float* thr_state, KeepAll keep, const int32_t* skip_if, const KvView& kv, float* out,
                                 hipStream_t st) {
-#define LFPS_SA_ARGS s, score, score_stride, cand, cand_count, k, topk_idx, topk_score, thr_state, keep_ratio, skip_if, kv, out, st
+#define LFPS_SA_ARGS s, score, score_stride, cand, cand_count, k, topk_idx, topk_score, thr_state, keep, skip_if, kv, out, st
   if (dtype == LFPS_BF16 && kv.v_fp8) return launch_sa_t<uint8_t>(LFPS_SA_ARGS);
   if (dtype == LFPS_F16) return launch_sa_t<_Float16>(LFPS_SA_ARGS);
   if (dtype == LFPS_BF16) return launch_sa_t<uint16_t>(LFPS_SA_ARGS);

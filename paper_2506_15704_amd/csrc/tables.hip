@@ -612,8 +612,7 @@ __global__ __launch_bounds__(64) void k_head_sparsity(Shape s, const float* __re
                                                       const float* __restrict__ sigma2_hat, int n_local, float eps,
                                                       float* __restrict__ rho_out, int32_t* __restrict__ gate_out,
                                                       const float* __restrict__ vbar, int32_t* __restrict__ topk_idx,
-                                                      float* __restrict__ topk_score, float* __restrict__ out,
-                                                      float* __restrict__ thr_state) {
+                                                      float* __restrict__ topk_score, float* __restrict__ out) {
   const int bh = blockIdx.x, b = bh / s.Hq, h = bh % s.Hq, g = h / s.G, lane = threadIdx.x;
   const int j = lane & 15, rs = lane >> 4;                    // 16 lanes per row, 8 channels each
   int n = seq_lens[b];
@@ -693,10 +692,6 @@ __global__ __launch_bounds__(64) void k_head_sparsity(Shape s, const float* __re
       topk_idx[(int64_t)bh * s.kmax + i] = -1;
       if (topk_score) topk_score[(int64_t)bh * s.kmax + i] = 0.f;
     }
-    // A bypassed head has no k-th score to remember, and a group with a NaN there would be taken as "no previous step" by
-    // the filtered scoring pass at every step.  -inf makes the first step in which it is not bypassed keep all candidates
-    // for it (the scoring pass keeps nothing for a bypassed head) and spares that step the unfiltered pass.
-    if (thr_state && lane == 0) thr_state[bh] = -INFINITY;
   }
 }
 
@@ -754,12 +749,11 @@ hipError_t launch_table_init(const Shape& s, float* tab_ver, float* tab_sla, con
 
 hipError_t launch_head_sparsity(const Shape& s, int dtype, const float* q, const KvView& kv, const float* kbar,
                                 const float* sigma2_hat, int n_local, float eps, float* rho, int32_t* gate,
-                                const float* vbar, int32_t* topk_idx, float* topk_score, float* out, float* thr_state,
-                                hipStream_t st) {
+                                const float* vbar, int32_t* topk_idx, float* topk_score, float* out, hipStream_t st) {
 #define LFPS_LAUNCH_HSP(TYPE, PAGED)                                                                             \
   hipLaunchKernelGGL((k_head_sparsity<TYPE, PAGED>), dim3(s.B * s.Hq), dim3(64), 0, st, s, q, (const TYPE*)kv.k,     \
                      kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, kbar, sigma2_hat, n_local, eps, rho, \
-                     gate, vbar, topk_idx, topk_score, out, thr_state)
+                     gate, vbar, topk_idx, topk_score, out)
   const bool paged = kv.page.table != nullptr;
   if (dtype == LFPS_BF16 && kv.k_fp8) {
     if (paged) LFPS_LAUNCH_HSP(uint8_t, true);

@@ -925,3 +925,40 @@ def test_update_of_a_step_equals_the_update_of_a_callers_list(L, k, n_sink):
         assert (cnt[0] - cnt[1]).abs().max() <= 2
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("L,k,cap,scale", [(40000, 500, 0, 1.0), (40000, 500, 39999, 1.0), (3000, 20, 0, 0.1)])
+def test_a_head_back_from_the_bypass_does_not_take_the_unfiltered_pass(L, k, cap, scale):
+    """With more candidates than the select's list holds (40000 rows) a bypassed head keeps the score it has; with few it
+    forgets it, and its first step back keeps all candidates whatever the queries are then."""
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    K = torch.randn((1, 1, L + 8, 128), device=DEV, generator=g).to(torch.bfloat16)
+    q = torch.randn((1, 4, 128), device=DEV, generator=g)
+    ctxs = [Lfps(batch=1, n_q_heads=4, n_kv_heads=1, kv_dtype="bf16", max_seq_len=L + 8, max_k=k, radius=30, n_sink=4,
+                 table_mode=True, cand_cap=cap) for _ in range(2)]
+    ctxs[1].lfps_set_filter(False)
+    # heavy tails: an entry above tau near almost every row, and more than half of the rows above some head's mean
+    phi = torch.rand((2, 1, 4, L + 8), device=DEV, generator=g).log().pow(4).contiguous()
+    for ctx in ctxs:
+        ctx.lfps_tables_import(phi[0], phi[1], torch.tensor([L], dtype=torch.int32, device=DEV))
+    kbar, vbar, s2 = (torch.zeros(x, device=DEV) for x in ((1, 1, 128), (1, 1, 128), (1, 4)))
+    ks = torch.tensor([k], dtype=torch.int32, device=DEV)
+    for t, (eps, by) in enumerate(((2.0, 1.0), (2.0, 1.0), (-1.0, 1.0), (-1.0, 1.0), (2.0, scale)), 1):
+        seq = torch.tensor([L + t], dtype=torch.int32, device=DEV)
+        res = []
+        for ctx in ctxs:
+            idx, out = torch.zeros((1, 4, k), dtype=torch.int32, device=DEV), torch.zeros((1, 4, 128), device=DEV)
+            cnt = torch.zeros((1, 1), dtype=torch.int32, device=DEV)
+            ctx.lfps_table_step_gated(by * q, ctx.kv_view(K, K, seq), ks, kbar, vbar, s2, 6, eps, idx, out)
+            ctx.lfps_copy_cand_count(cnt)
+            res.append((idx, out, cnt))
+        assert (int(res[0][2]) > 16384) == (L == 40000 and eps > 0), t
+        for x, y in zip(*res):
+            assert torch.equal(x, y), t
+        rescored = ctxs[0].lfps_poll_rescored()
+        assert rescored == 0 or t != 5, rescored
+        assert (res[0][0][0, :, 0] == -1).all() == (eps < 0)
+    for ctx in ctxs:
+        ctx.close()
