@@ -659,8 +659,9 @@ __global__ __launch_bounds__(64) void k_head_sparsity(Shape s, const float* __re
       const float top = row16_max(in ? mine : -INFINITY);
       if (top == -INFINITY) return;                            // (wave-uniform: every group holds the same rows)
       const double mx = m > (double)top ? m : (double)top;
-      const double part = row16_sum(in ? exp((double)mine - mx) : 0.0);
-      z = (z > 0.0 ? z * exp(m - mx) : 0.0) + part;
+      // (a logit of +inf is a term of weight 1 beside which all others vanish; a NaN stays)
+      const double part = row16_sum(in ? ((double)mine == mx ? 1.0 : exp((double)mine - mx)) : 0.0);
+      z = (m == mx ? z : z * exp(m - mx)) + part;
       m = mx;
     };
     add(r < ns, m_sink, z_sink);

@@ -962,3 +962,34 @@ def test_a_head_back_from_the_bypass_does_not_take_the_unfiltered_pass(L, k, cap
         assert (res[0][0][0, :, 0] == -1).all() == (eps < 0)
     for ctx in ctxs:
         ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("row,value,want", [(3, np.inf, 1.0), (18, np.inf, 1.0), (-2, np.inf, 0.0), (3, np.nan, 0.0),
+                                            (3, -np.inf, None)])
+def test_head_sparsity_of_logits_that_are_not_finite(dtype, row, value, want):
+    """More than sixteen sink and local rows.  A sink whose logit overflows takes all the weight, a local row none of it is
+    left for; a sink without a value leaves the head unbypassed, and one at -inf weighs nothing."""
+    from paper_2506_15704_amd.binding import Lfps
+    L, n_sink, n_local = 600, 20, 6
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    K = torch.randn((1, 1, L, 128), device=DEV, generator=g).to({"bf16": torch.bfloat16, "f32": torch.float32}[dtype])
+    q = torch.randn((1, 2, 128), device=DEV, generator=g)
+    q[..., :2] = 2.0
+    seq = torch.tensor([L], dtype=torch.int32, device=DEV)
+    ctx = Lfps(batch=1, n_q_heads=2, n_kv_heads=1, kv_dtype=dtype, max_seq_len=L, max_k=16, radius=1, n_sink=n_sink)
+    rho, gate = torch.zeros((1, 2), device=DEV), torch.zeros((1, 2), dtype=torch.int32, device=DEV)
+    zeros = torch.zeros((1, 1, 128), device=DEV), torch.zeros((1, 2), device=DEV)
+    K[0, 0, row] = 0
+    K[0, 0, row, :2] = {np.inf: 3e38, -np.inf: -3e38}.get(value, value)
+    ctx.lfps_head_sparsity(q, ctx.kv_view(K, K, seq), *zeros, n_local, 0.5, rho, gate)
+    for h in range(2):
+        ref = want
+        if want is None:
+            s = orc.scores(q[0, h].cpu().numpy(), K[0, 0].float().cpu().numpy())
+            sink, loc = np.exp(np.delete(s[:n_sink], row)).sum(), np.exp(s[L - n_local:]).sum()
+            ref = sink / (sink + L + loc)
+        assert float(rho[0, h]) == pytest.approx(ref, rel=1e-5)
+        assert int(gate[0, h]) == int(ref > 0.5)
+    ctx.close()
