@@ -1,5 +1,6 @@
 """Candidates and scores in one kernel (chained steps of up to a million rows): at the edges of its ranges and pieces, from
-the Top-k of the step before and from the table flags, against an unfiltered context, which takes the separate kernels."""
+the Top-k of the step before and from the table flags, against an unfiltered context, which takes other kernels.  And the
+separate kernels, which the same steps take with more rows, or with a candidate capacity below the bound, as here."""
 import pytest
 import torch
 
@@ -170,3 +171,86 @@ def test_every_head_left_short_in_a_short_context(B, Hq, Hkv, L, k, r, page):
             a.lfps_poll_rescored()
     a.close()
     b.close()
+
+
+def _capacity_below_the_bound(**kw):
+    """One candidate less than the largest set there can be: the range kernel is not taken (its bitmap is not allocated)."""
+    from paper_2506_15704_amd.binding import workspace_bytes
+    kw = dict(dict(head_dim=128, n_recent=1, n_sink=0, table_mode=0, k_fp8=0), **kw)
+    bound = kw["n_q_heads"] // kw["n_kv_heads"] * kw["max_k"] * (2 * kw["radius"] + 2) + kw["n_recent"] + kw["n_sink"]
+    bound = kw["max_seq_len"] if kw["table_mode"] else min(bound, kw["max_seq_len"])
+    kw["kv_dtype"] = {"f32": 0, "bf16": 1, "f16": 2}[kw["kv_dtype"]]
+    with_range, without = (workspace_bytes(cand_cap=c, **kw) for c in (bound, bound - 1))
+    assert with_range - without >= kw["batch"] * kw["n_kv_heads"] * -(-kw["max_seq_len"] // 32) * 4
+    return bound - 1
+
+
+# 384 groups of a few hundred rows (one wave's part crosses several groups), few groups of many rows (a group is cut into
+# many parts), one tiny group; 1, 2 and 4 heads per group
+@pytest.mark.parametrize("B,Hq,Hkv,L,k,r,dtype,page", [
+    (48, 32, 8, 700, 24, 1, "bf16", 0), (48, 32, 8, 700, 24, 1, "fp8", 16), (24, 16, 8, 900, 40, 2, "f16", 16),
+    (40, 8, 8, 650, 30, 3, "bf16", 0), (5, 16, 4, 9000, 300, 2, "bf16", 64), (3, 16, 8, 20011, 400, 3, "f16", 64),
+    (2, 4, 4, 12000, 500, 2, "fp8", 0), (1, 4, 1, 70, 5, 0, "bf16", 0)])
+def test_memoryless_steps_through_the_separate_kernels(B, Hq, Hkv, L, k, r, dtype, page):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L * 3 + k)
+    Lcap = L + 6
+    cache = _cache(B, Hkv, Lcap, dtype, page, g)
+    cfg = dict(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="bf16" if dtype == "fp8" else dtype, k_fp8=dtype == "fp8",
+               max_seq_len=Lcap, max_k=k, radius=r)
+    a, b = _pair(cand_cap=_capacity_below_the_bound(**cfg), **cfg)
+    lens = [max(1, L - 131 * i % L) for i in range(B)]
+    ks = torch.tensor([max(1, min(k, n) - i % 3) for i, n in enumerate(lens)], dtype=torch.int32, device=DEV)
+    q = torch.randn((B, Hq, 128), device=DEV, generator=g)
+    prev = torch.full((B, Hq, k), -1, dtype=torch.int32, device=DEV)
+    a.lfps_exact_topk(q, _view(a, cache, torch.tensor(lens, dtype=torch.int32, device=DEV)), ks, prev)
+    for t in range(1, 6):          # the fourth leaves every head short
+        q = q * 0.02 if t == 4 else q + 0.1 * torch.randn((B, Hq, 128), device=DEV, generator=g)
+        seq = torch.tensor([n + t for n in lens], dtype=torch.int32, device=DEV)
+        res = []
+        for ctx in (a, b):
+            idx = torch.full((B, Hq, k), -5, dtype=torch.int32, device=DEV)
+            sc, out = torch.full((B, Hq, k), -5.0, device=DEV), torch.full((B, Hq, 128), -5.0, device=DEV)
+            cnt = torch.full((B, Hkv), -5, dtype=torch.int32, device=DEV)
+            ctx.lfps_step(q, _view(ctx, cache, seq), prev, ks, idx, out, sc)
+            ctx.lfps_copy_cand_count(cnt)
+            assert ctx.lfps_poll_status() == 0
+            res.append((idx, sc, out, cnt))
+        for x, y, name in zip(*res, ("index", "score", "output", "candidate count")):
+            assert torch.equal(x, y), (name, t, int((x != y).sum()))
+        rescored = a.lfps_poll_rescored()
+        assert t != 4 or rescored > B * Hq // 2, rescored
+        prev = res[0][0]
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,k,r,dtype,page", [
+    (48, 32, 8, 700, 24, 1, "bf16", 0), (24, 16, 8, 900, 40, 2, "f16", 16), (3, 8, 8, 9000, 100, 3, "bf16", 16)])
+def test_table_steps_through_the_separate_kernels(B, Hq, Hkv, L, k, r, dtype, page):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L + k)
+    Lcap = L + 8
+    cache = _cache(B, Hkv, Lcap, dtype, page, g)
+    cfg = dict(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype=dtype, max_seq_len=Lcap, max_k=k, radius=r, n_sink=4)
+    pair = _pair(cand_cap=_capacity_below_the_bound(table_mode=1, table_decay=0.95, table_a=0.2, **cfg), table_mode=True, **cfg)
+    lens = [max(1, L - 131 * i % L) for i in range(B)]
+    ks = torch.tensor([min(k, n) for n in lens], dtype=torch.int32, device=DEV)
+    q = 3 * torch.randn((B, Hq, 128), device=DEV, generator=g)
+    for ctx in pair:
+        ctx.lfps_tables_init(q[None].contiguous(), _view(ctx, cache, torch.tensor(lens, dtype=torch.int32, device=DEV)))
+    for t in range(1, 6):
+        q = q + 0.3 * torch.randn((B, Hq, 128), device=DEV, generator=g)
+        seq = torch.tensor([n + t for n in lens], dtype=torch.int32, device=DEV)
+        res = []
+        for ctx in pair:
+            idx = torch.full((B, Hq, k), -5, dtype=torch.int32, device=DEV)
+            sc, out = torch.full((B, Hq, k), -5.0, device=DEV), torch.full((B, Hq, 128), -5.0, device=DEV)
+            cnt = torch.full((B, Hkv), -5, dtype=torch.int32, device=DEV)
+            ctx.lfps_table_step(q, _view(ctx, cache, seq), ks, idx, out, sc)
+            ctx.lfps_copy_cand_count(cnt)
+            res.append((idx, sc, out, cnt))
+        for x, y, name in zip(*res, ("index", "score", "output", "candidate count")):
+            assert torch.equal(x, y), (name, t, int((x != y).sum()))
+    for ctx in pair:
+        ctx.close()
