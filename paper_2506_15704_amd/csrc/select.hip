@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select(Shape s, const float* __
   if (done) return;
   __syncthreads();
   if (c <= cache_elems)
-    select_body<true, NT>(sm, dyn, sc, c, ksel, nullptr, cbg, oi, os, thr_out, FLT_MAX, -FLT_MAX, n_valid);
+    select_body<true, NT>(sm, dyn, sc, c, ksel, cbg, oi, os, thr_out, n_valid);
   else
     select_stream(sm, sc, c, ksel, cbg, oi, os, thr_out, n_valid);
 }

@@ -415,8 +415,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_attend(
   } else {
     float top;
     if (c <= cache_elems)
-      select_body<true, NT>(sm, reinterpret_cast<float*>(dyn), sc, c, ksel, nullptr, cbg, oi, os, thr_out, FLT_MAX,
-                            -FLT_MAX, n, &top);
+      select_body<true, NT>(sm, reinterpret_cast<float*>(dyn), sc, c, ksel, cbg, oi, os, thr_out, n, &top);
     else
       top = select_stream(sm, sc, c, ksel, cbg, oi, os, thr_out, n);
     __syncthreads();                                // this workgroup's stores of (position, score) before its loads of them

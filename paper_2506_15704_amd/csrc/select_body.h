@@ -84,19 +84,14 @@ __device__ __forceinline__ void find_bin(SelectShared<NT>& sm, uint32_t need, in
     }                                                                                 \
   }
 
-// `slot_of` (LDS, or NULL for identity) maps an element of the scored list to its candidate slot;
 // `cbg` (or NULL for identity) maps a candidate slot to its position; a position outside [0, n_valid)
 // (a bad entry of a caller's candidate list: its score is -inf, so it is taken only when fewer than k
 // valid candidates exist) is written as -1 with score 0.  `thr_out` receives the k-th largest score.
-// kHaveRange: the caller has already seen every element (it filled the cache) and passes its own
-// thread's smallest and largest in pre_lo / pre_hi, which saves the first pass over the data.
-template <bool CACHED, int NT, bool kHaveRange = false>
+template <bool CACHED, int NT>
 __device__ __forceinline__ void select_body(SelectShared<NT>& sm, float* __restrict__ cache,
                                             const float* __restrict__ sc, int c, int ksel,
-                                            const int32_t* __restrict__ slot_of, const int32_t* __restrict__ cbg,
-                                            int32_t* __restrict__ oi, float* __restrict__ os,
-                                            float* __restrict__ thr_out, float pre_lo = FLT_MAX,
-                                            float pre_hi = -FLT_MAX, int n_valid = 0x7FFFFFFF,
+                                            const int32_t* __restrict__ cbg, int32_t* __restrict__ oi,
+                                            float* __restrict__ os, float* __restrict__ thr_out, int n_valid,
                                             float* top_out = nullptr) {
   constexpr int kSelWaves = NT / 64, kBins = 2 * NT, kListCap = NT;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -105,17 +100,15 @@ __device__ __forceinline__ void select_body(SelectShared<NT>& sm, float* __restr
   const int nit = r1 > r0 ? (r1 - r0 + 63) >> 6 : 0;
 
   // ---- 1. load (once, into LDS, if the head fits) and block min / max
-  if (CACHED && sc) {                      // sc == NULL: the caller has already filled the cache
+  if (CACHED) {
 #pragma unroll 8
     for (int it = 0; it < nit; ++it) {
       const int i = r0 + 64 * it + lane;
       if (i < r1) cache[i] = sanitize(sc[i]);
     }
   }
-  float lo = pre_lo, hi = pre_hi;
-  if constexpr (!kHaveRange) {
-    LFPS_FOR_EACH(lo = in ? fminf(lo, x) : lo; hi = in ? fmaxf(hi, x) : hi;)
-  }
+  float lo = FLT_MAX, hi = -FLT_MAX;
+  LFPS_FOR_EACH(lo = in ? fminf(lo, x) : lo; hi = in ? fmaxf(hi, x) : hi;)
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     lo = fminf(lo, __shfl_xor(lo, d));
@@ -241,8 +234,7 @@ __device__ __forceinline__ void select_body(SelectShared<NT>& sm, float* __restr
       eq_run += eq ? 1u : 0u;
       if (take) {
         if (pos < (uint32_t)ksel) {
-          const int sl = slot_of ? slot_of[i] : i;
-          const int p = cbg ? cbg[sl] : sl;
+          const int p = cbg ? cbg[i] : i;
           const bool okp = (uint32_t)p < (uint32_t)n_valid;
           oi[pos] = okp ? p : -1;
           if (os) os[pos] = okp ? x : 0.f;
@@ -275,8 +267,7 @@ __device__ __forceinline__ void select_body(SelectShared<NT>& sm, float* __restr
       if (take) {
         const uint32_t pos = out_run + lanes_below(m_take);
         if (pos < (uint32_t)ksel) {
-          const int sl = slot_of ? slot_of[i] : i;
-          const int p = cbg ? cbg[sl] : sl;
+          const int p = cbg ? cbg[i] : i;
           const bool okp = (uint32_t)p < (uint32_t)n_valid;
           oi[pos] = okp ? p : -1;
           if (os) os[pos] = okp ? x : 0.f;
@@ -298,7 +289,7 @@ static __device__ __noinline__ float select_stream(SelectShared<NT>& sm, const f
                                                    const int32_t* __restrict__ cbg, int32_t* __restrict__ oi,
                                                    float* __restrict__ os, float* __restrict__ thr_out, int n_valid) {
   float top = 0.f;
-  select_body<false, NT>(sm, nullptr, sc, c, ksel, nullptr, cbg, oi, os, thr_out, FLT_MAX, -FLT_MAX, n_valid, &top);
+  select_body<false, NT>(sm, nullptr, sc, c, ksel, cbg, oi, os, thr_out, n_valid, &top);
   return top;
 }
 
