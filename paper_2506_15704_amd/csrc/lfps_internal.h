@@ -333,6 +333,10 @@ __device__ __forceinline__ int wave_inclusive_sum(int x) {
   return x;
 }
 
+// Between LDS writes of some lanes of a wave and reads of them by others: a wave's LDS operations complete in order, so this
+// only keeps the compiler from moving or reusing them across (no instruction).
+__device__ __forceinline__ void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
+
 // Sum and maximum over the 16 lanes of a row of lanes, left in every one of them (DPP rotations, no LDS).
 __device__ __forceinline__ float row16_sum(float x) {
 #define LFPS_ROT(v, n) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + (n), 0xf, 0xf, false))

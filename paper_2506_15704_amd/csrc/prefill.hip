@@ -191,6 +191,7 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
     };
     if (whole) walk(std::false_type{});
     else walk(std::true_type{});
+    wave_lds_order();                                      // wm of this tile before the other lanes read it in the next
   }
   __syncthreads();
   for (int e = tid; e < nq * G; e += kHistWaves * 64) {
@@ -301,6 +302,7 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_apply(
       if (j == 15) my_carry[jq][kb] = as[NT - 1];
       cin = next_cin;
     }
+    wave_lds_order();                                      // the carries before the other lanes read them for the next rows
   };
   auto walk_rows = [&](auto& T, int base, auto& av, auto& as) {
     constexpr int NT = sizeof(av) / sizeof(float);

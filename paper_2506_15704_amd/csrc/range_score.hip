@@ -186,6 +186,7 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
 
   // (survivors are staged so that the loop holds no global store: a wait for a load would wait for those before it)
   auto flush = [&]() {
+    wave_lds_order();
 #pragma unroll
     for (int h = 0; h < G; ++h) {
       const int cnt_h = __shfl(staged, 16 * h);
@@ -199,6 +200,7 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
     }
     run += staged;
     staged = 0;
+    wave_lds_order();
   };
   // the row of list entry e0 + lane (past the end: the last one, never kept)
   auto ids_of = [&](int e0) { return lo + list[c0 + (e0 + lane < cnt ? e0 + lane : cnt - 1)]; };

@@ -167,6 +167,7 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
     // full).  Global stores inside the loop would share the vector-memory counter with the row
     // loads, so that every wait for a load would also wait for the stores before it.
     auto flush = [&]() {
+      wave_lds_order();
 #pragma unroll
       for (int h = 0; h < G; ++h) {
         const int cnt_h = __shfl(staged, 16 * h);
@@ -180,6 +181,7 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
       }
       run += staged;
       staged = 0;
+      wave_lds_order();
     };
 
     // Two 64-row tiles are kept in flight per wave: while tile i is multiplied, the loads of tile
