@@ -52,14 +52,18 @@ __device__ __forceinline__ void remember_bypassed(float* thr_state, const KeepAl
 
 constexpr int kSelRowsMax = 16384;    // selected rows of a head that pass through LDS; more go through global memory
 
-// Threads per head (16 waves per CU: the attention's loads in flight set the registers): 1024 while every head's workgroup is
-// resident at once, else 512, unless the survivors of the largest budget need the registers of more threads.  Not 256, also
-// where that would make more than 512 heads resident at once: whole steps of 1024 heads were then 0 to 2.4 % faster (k = 512
-// 172 -> 168 us, k = 1000 to 2048 within 0.5 %, ragged budgets of 330 to 1311 630 -> 615 for four steps), but those in which a
-// change of the queries leaves 2 to 10 % of the heads short 5 to 28 % slower (k = 512 239 -> 307 us, 1000 399 -> 443, 2048
-// 649 -> 727: the unfiltered pass of a head has half the waves), and the list holds 4096 survivors instead of 8192.
+// Threads per head (16 waves per CU: the attention's loads in flight set the registers): as many as let every head's
+// workgroup be resident at once, 1024 up to 256 heads, 512 up to 512, else 256; but the list holds kRegElems survivors per
+// thread and has to hold four of the largest budget (1024 and 512 threads: two, or 7680).  Above 512 heads, steps whose
+// heads all have enough survivors, 256 threads against 512: k = 128 46 against 52 us (608 heads) and 107 against 123
+// (2048), k = 400 76 against 81 and 247 against 257, k = 1000 within 1 %; k = 1600 and 2048 equal, ragged budgets of
+// 330 to 1311 2 % faster for four steps, but there a list of 4096 overflows, for every head at once, when the scores grow
+// from one step to the next.  (The unfiltered pass of a head left short has half the waves: steps in which 2 % of the heads
+// take it, k = 400, 193 against 175 us at 1024 heads.)
 static int filter_select_threads(const Shape& s) {
-  return s.B * s.Hq <= 256 || kRegElems * 512 < 2 * s.kmax ? 1024 : 512;
+  const int heads = s.B * s.Hq;
+  if (heads > 512 && kRegElems * 256 >= 4 * s.kmax) return 256;
+  return heads <= 256 || kRegElems * 512 < 2 * s.kmax ? 1024 : 512;
 }
 
 int filter_list_cap(const Shape& s) { return kRegElems * filter_select_threads(s); }
@@ -453,6 +457,7 @@ static int select_attend_lds(const Shape& s) {
 // FP8 V with FP8 keys, fp16 V with fp16 keys), times paged or not, times the threads per head, times the form
 // of the lists.
 #define LFPS_FSA_FOR_EACH_NT(X, TYPE, PAGED, KIND)                                \
+  X(TYPE, PAGED, KIND, 256, false) X(TYPE, PAGED, KIND, 256, true)                \
   X(TYPE, PAGED, KIND, 512, false) X(TYPE, PAGED, KIND, 512, true)                \
   X(TYPE, PAGED, KIND, 1024, false) X(TYPE, PAGED, KIND, 1024, true)
 #define LFPS_FSA_FOR_EACH(X)                               \

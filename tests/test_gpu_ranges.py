@@ -138,7 +138,7 @@ def test_a_budget_of_most_candidates_keeps_them_all(L, k):
     b.close()
 
 
-# 1024 and 512 threads per head; one to a few dozen words of bitmap, so that most waves own none
+# 1024, 512 and 256 threads per head; one to a few dozen words of bitmap, so that most waves own none
 @pytest.mark.parametrize("B,Hq,Hkv,L,k,r,page", [
     (1, 4, 1, 40, 2, 0, 0), (2, 8, 2, 130, 8, 1, 16), (4, 32, 8, 301, 16, 2, 0), (8, 64, 16, 97, 5, 1, 0),
     (17, 32, 8, 260, 12, 1, 64), (17, 32, 32, 700, 20, 3, 0)])

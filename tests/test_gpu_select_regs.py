@@ -24,7 +24,7 @@ def _reference(ctx, q, kv, prev, k, seq):
     return idx, sc, out
 
 
-# heads: up to 256 -> 1024 threads, more -> 512 (unless the budget needs more); budgets that put the
+# heads: up to 256 -> 1024 threads, up to 512 -> 512, more -> 256 (unless the budget needs more); budgets that put the
 # survivors on both sides of 2, 4, 8 and 16 elements per thread; dtype f32 = the select from full score rows
 @pytest.mark.parametrize("B,Hq,Hkv,L,k,r,dtype", [
     (1, 4, 1, 3000, 63, 2, "bf16"), (1, 4, 1, 3001, 1, 0, "bf16"), (2, 8, 2, 6000, 1600, 3, "bf16"),
