@@ -77,11 +77,11 @@ static __device__ __noinline__ void attend_global(AttendShared& as, const T* V, 
 }
 
 // Entries of weight 0 behind the ksel selected rows of a list, up to a multiple of 64 (and to `room`): the request's own row
-// 0.  (Row 0 of a paged pool may belong to nobody, and 0 times what it holds need not be 0.)
-template <int NT, bool kPaged>
+// 0.  (Row 0 of a paged pool may belong to nobody, and 0 times what it holds need not be 0.)  Called by 64 threads or more.
+template <bool kPaged>
 __device__ __forceinline__ void pad_list(SelRow* list, const KvPage& page, int b, int ksel, int room) {
-  const int end = ((ksel + 63) & ~63) < room ? (ksel + 63) & ~63 : room;
-  for (int i = ksel + threadIdx.x; i < end; i += NT) list[i] = SelRow{RowMap<kPaged>::phys(page, b, 0), 0.f};
+  const int i = ksel + (int)threadIdx.x;
+  if (i < ((ksel + 63) & ~63) && i < room) list[i] = SelRow{RowMap<kPaged>::phys(page, b, 0), 0.f};
 }
 
 // The rows a workgroup has just selected into global memory (oi, os; the caller's barrier has ordered the stores), as
@@ -222,15 +222,17 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     oi[i] = -1;
     os[i] = 0.f;
   }
-  pad_list<NT, kPaged>(list, page, b, ksel, kSelRowsMax);
+  pad_list<kPaged>(list, page, b, ksel, kSelRowsMax);
   if (ksel == 0) {
     if (tid == 0) thr_state[bh] = -INFINITY;
     if (out && tid < kD) out[(int64_t)bh * kD + tid] = 0.f;
     return;
   }
-  if (keep.fits && tid == 0) keep.fits[bh] = c <= keep.most;
   float* thr_out = filter_pays(c, ksel, keep) ? thr_state + bh : nullptr;
-  if (!thr_out && tid == 0) thr_state[bh] = -INFINITY;      // (every thread has read it before the barrier)
+  if (tid == 0) {
+    if (!thr_out) thr_state[bh] = -INFINITY;                // (every thread has read it before the barrier)
+    if (keep.fits) keep.fits[bh] = c <= keep.most;
+  }
   float* sc = score + (int64_t)bh * score_stride;
   int32_t* sl = slot + (int64_t)bh * score_stride;
   const int32_t* cbg = kRanges ? sl : (cand ? cand + (int64_t)bg * s.cand_cap : nullptr);
@@ -375,7 +377,9 @@ __global__ __launch_bounds__(kSelThreads) void k_select_attend(
     if (tid < kD) out[(int64_t)bh * kD + tid] = 0.f;
     return;
   }
-  if (keep.fits && tid == 0) keep.fits[bh] = c <= keep.most;
+  if constexpr (!std::is_same<T, float>::value) {   // (no filter for fp32 caches)
+    if (keep.fits && tid == 0) keep.fits[bh] = c <= keep.most;
+  }
   if (thr_out && !filter_pays(c, ksel, keep)) {
     if (tid == 0) *thr_out = -INFINITY;
     thr_out = nullptr;
@@ -385,7 +389,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_attend(
   if (c <= kRegElems * NT) {
     for (int i = tid; i < 2 * NT; i += NT) sm.hist[i] = 0u;
     if (tid == 0) sm.list_n = 0u;
-    pad_list<NT, kPaged>(list, page, b, ksel, kSelRowsMax);
+    pad_list<kPaged>(list, page, b, ksel, kSelRowsMax);
     __syncthreads();
     auto run = [&](auto elems) {
       constexpr int E = decltype(elems)::value;
@@ -428,7 +432,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_attend(
                                         out + (int64_t)bh * kD);
       return;
     }
-    pad_list<NT, kPaged>(list, page, b, ksel, kSelRowsMax);
+    pad_list<kPaged>(list, page, b, ksel, kSelRowsMax);
     list_from_global<NT, kPaged>(list, page, b, n, ksel, oi, os, top);
   }
   __syncthreads();
