@@ -80,6 +80,7 @@ static __device__ __noinline__ void attend_global(AttendShared& as, const T* V, 
 // 0.  (Row 0 of a paged pool may belong to nobody, and 0 times what it holds need not be 0.)  Called by 64 threads or more.
 template <bool kPaged>
 __device__ __forceinline__ void pad_list(SelRow* list, const KvPage& page, int b, int ksel, int room) {
+  if ((ksel & 63) == 0) return;                     // (uniform: the look-up is waited for by all)
   const int i = ksel + (int)threadIdx.x;
   if (i < ((ksel + 63) & ~63) && i < room) list[i] = SelRow{RowMap<kPaged>::phys(page, b, 0), 0.f};
 }
