@@ -11,7 +11,7 @@
 //
 // Why one kernel: as two, a step of 8 groups x 32K rows spent 7.8 + 14.5 us here, of which the rows themselves are 5 us;
 // the rest is two launches and the round trips
-// candidates -> list -> geometry -> list -> rows.  Together: 14.6 us.
+// candidates -> list -> geometry -> list -> rows.  Together: 14.4 us.
 #include "candidates.h"
 #include "range_geometry.h"
 #include "score_mfma.h"
@@ -261,7 +261,8 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
 //   From the Top-k: every workgroup reads the Top-k rows of its group, 5 us in which it loads no rows, so all of them have
 //   to be resident at once (four per CU) and there may be no more rows than 1024 ranges of 1024.  Steps, separate ->
 //   together: 8 groups x 32K rows 34.6 -> 28 us, 24 x 20K (paged fp16) 31.9 -> 23.6; but 64 x 32K 65.4 -> 69 us, paged FP8
-//   128 x 64K 82 -> 98.  Ranges of 512 rows while that leaves at most 512 of them, else 1024 (512 to 2048 differ by 3 %).
+//   128 x 64K 82 -> 98.  Up to the line: 0.5 to 1 million rows in 8 to 256 groups, whole steps 6 to 10 us shorter (32 x 32K
+//   55.3 -> 48.8, 256 x 4K 64.0 -> 53.8, FP8 8 x 130K, k = 4000 58.2 -> 49.3).  Ranges of 512 rows while that leaves at most 512 of them, else 1024 (512 to 2048 differ by 3 %).
 //   From the table flags, a few words per range: candidates are 4 % of the rows, so ranges of 2048 give a wave 20 rows.
 //   64 x 32K: 23.6 -> 16.1 us for the two kernels.  Up to 4 million rows.
 int range_rows(const Shape& s, bool tables) {
