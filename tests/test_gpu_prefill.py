@@ -171,3 +171,35 @@ def test_means_hold_their_accuracy_for_many_groups(B):
     rms = lambda e: float(np.sqrt(np.mean(np.square(np.stack(e)))))
     assert rms(errs) <= 1.25 * rms(sims), (rms(errs), rms(sims))
     ctx.close()
+
+
+@pytest.mark.parametrize("s", [1, 6])
+def test_tables_of_many_groups_are_those_of_few(s):
+    """320 KV groups, one workgroup each: every request's tables as in a context of that request alone, in which each group is
+    cut into several.  The sums of exponentials are in fp64, so the weights differ by a rounding: 2 units of 2^-24 each."""
+    from paper_2506_15704_amd.binding import Lfps
+    B, Hkv, L = 40, 8, 2100
+    g = torch.Generator(device=DEV)
+    g.manual_seed(s)
+    K = torch.randn((B, Hkv, L, 128), device=DEV, generator=g).to(torch.bfloat16)
+    q = torch.randn((s, B, Hkv, 128), device=DEV, generator=g)
+    lens = [L - 41 * b for b in range(B)]
+
+    def tables(rows):
+        n = len(rows)
+        ctx = Lfps(batch=n, n_q_heads=Hkv, n_kv_heads=Hkv, kv_dtype="bf16", max_seq_len=L, max_k=16, radius=1, n_sink=4,
+                   table_mode=True)
+        seq = torch.tensor([lens[b] for b in rows], dtype=torch.int32, device=DEV)
+        Kr = K[rows].contiguous()
+        ctx.lfps_tables_init(q[:, rows].contiguous(), ctx.kv_view(Kr, Kr, seq))
+        out = torch.zeros((2, n, Hkv, L), dtype=torch.float64, device=DEV)
+        ctx.lfps_tables_export(out[0], out[1], seq)
+        torch.cuda.synchronize()
+        ctx.close()
+        return out
+
+    many = tables(list(range(B)))
+    for b in (0, 17, B - 1):
+        few = tables([b])
+        assert (many[:, b] - few[:, 0]).abs().max() <= 2.0**-23 * few.abs().max()
+        assert (few > 0).any()

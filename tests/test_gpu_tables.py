@@ -993,3 +993,37 @@ def test_head_sparsity_of_logits_that_are_not_finite(dtype, row, value, want):
         assert float(rho[0, h]) == pytest.approx(ref, rel=1e-5)
         assert int(gate[0, h]) == int(ref > 0.5)
     ctx.close()
+
+
+def test_table_steps_of_many_heads_whose_candidates_overflow_the_list():
+    """544 heads, lists of 4096 survivors and up to twice as many candidates per group: first steps back from a bypass, and
+    steps whose scores have grown, against the unfiltered context."""
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(9)
+    B, Hq, Hkv, L, k = 17, 32, 8, 9000, 100
+    K = torch.randn((B, Hkv, L + 8, 128), device=DEV, generator=g).to(torch.bfloat16)
+    q = torch.randn((B, Hq, 128), device=DEV, generator=g)
+    ctxs = [Lfps(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="bf16", max_seq_len=L + 8, max_k=k, radius=30, n_sink=4,
+                 table_mode=True) for _ in range(2)]
+    ctxs[1].lfps_set_filter(False)
+    phi = torch.rand((2, B, Hq, L + 8), device=DEV, generator=g).log().pow(4)
+    seq = torch.tensor([L - 300 * b for b in range(B)], dtype=torch.int32, device=DEV)
+    for ctx in ctxs:
+        ctx.lfps_tables_import(phi[0].contiguous(), phi[1].contiguous(), seq)
+    kbar, vbar, s2 = (torch.zeros(x, device=DEV) for x in ((B, Hkv, 128), (B, Hkv, 128), (B, Hq)))
+    ks = torch.full((B,), k, dtype=torch.int32, device=DEV)
+    for eps, scale in ((2.0, 1.0), (2.0, 1.0), (-1.0, 1.0), (2.0, 1.0), (2.0, 4.0), (2.0, 0.05)):
+        seq = seq + 1
+        res = []
+        for ctx in ctxs:
+            idx, out = torch.zeros((B, Hq, k), dtype=torch.int32, device=DEV), torch.zeros((B, Hq, 128), device=DEV)
+            cnt = torch.zeros((B, Hkv), dtype=torch.int32, device=DEV)
+            ctx.lfps_table_step_gated(scale * q, ctx.kv_view(K, K, seq), ks, kbar, vbar, s2, 6, eps, idx, out)
+            ctx.lfps_copy_cand_count(cnt)
+            res.append((idx, out, cnt))
+        assert eps < 0 or int(res[0][2].max()) > 4096
+        for x, y in zip(*res):
+            assert torch.equal(x, y), (eps, scale)
+    for ctx in ctxs:
+        ctx.close()
