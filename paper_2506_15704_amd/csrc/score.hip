@@ -82,6 +82,17 @@ __global__ __launch_bounds__(kScoreThreads) void k_group_score_bf16(Shape s, con
 // written when the piece is done); their number goes to seg_count[head, seg].  No atomics here:
 // the lists are ascending in position and the same from run to run.
 // A threshold of -inf keeps every row; NaN means there is no previous step.
+//
+// How the rows are fetched.  Bound by the bytes of the rows.  Candidates of more than kKeptBytes cannot be found again in the
+// memory-side cache (256 MB) by the next step, so their rows are read past the caches (StreamTile): 128 groups x 128K rows,
+// 954 MB of candidates 193 -> 175 us, 1.07 GB of all rows 185 -> 162.5 us = 6.6 TB/s; and what the select reads after it (the
+// survivors, V rows shared by the heads of a group) is no longer driven out: its kernel 40 -> 31 us.  (Non-temporal loads of
+// KTile's shape fetch every line several times, 300 us; StreamTile with ordinary loads gains nothing, 196 us.)  Up to kKeptBytes
+// ordinary loads, every lane its own channels (KTile): the next step finds nine tenths of its rows in the cache.  64 groups x
+// 32K rows, 220 MB: a step 64 us, 66 past the caches; equal at 280 to 300 MB.
+// The parts are cut at multiples of 16 slots: of 64, a part of 420 slots grew by 6 % and the last waves had nothing to do
+// (64 groups x 32K rows: 38.1 -> 37.0 us).
+constexpr int64_t kKeptBytes = 256 << 20;
 constexpr int kFilterStage = 256;   // survivors one wave can hold per head before it must write them out
 
 // kDense: the "candidates" of a group are all its rows 0..count-1 (no list is read): the exact Top-k baseline's
@@ -97,49 +108,101 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
     int32_t* __restrict__ flags) {
   __shared__ float stage_score[4][G][kFilterStage];
   __shared__ int32_t stage_slot[4][G][kFilterStage];
+  __shared__ u32x4 turn[4][StreamTile<kKind>::kLdsChunks];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform values stay in scalar registers
   const int j = lane & 15, kb = lane >> 4;
   const int n_groups = s.B * s.Hkv;
 
+  // Before the first row there is a chain of loads, each written by another kernel and a trip to memory of about 0.8 us: the
+  // line and the groups' places on it together, then row ids, threshold and length together, (the block table,) the rows.
+  // (Waits that the compiler would put in between are avoided by asking for everything of a link before any of it is used.)
+  struct Places {
+    int64_t st[4];
+    int cnt[4];
+  };
+  auto places_from = [&](int g0) {
+    Places p;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int at = g0 + 64 * u + lane;
+      p.st[u] = at < n_groups ? group_start[at] : 0;
+      p.cnt[u] = at < n_groups ? cand_count[at] : 0;
+    }
+    return p;
+  };
+  Places at_hand = places_from(0);
   // ---- the part of this wave: S slots from wave_index * S; every wave derives the same S
   const int64_t total = *line_total;
-  const int64_t n_waves = (int64_t)gridDim.x * 4;
-  int64_t S = ((total + n_waves - 1) / n_waves + 63) & ~(int64_t)63;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) asm volatile("" : "+v"(at_hand.cnt[u]));
+  const int n_waves = (int)gridDim.x * 4;
+  int64_t S = (total >> 30) == 0 ? (int64_t)(((uint32_t)total + (uint32_t)n_waves - 1u) / (uint32_t)n_waves)
+                                 : (total + n_waves - 1) / n_waves;
+  S = (S + 15) & ~(int64_t)15;
   S = S < min_seg_rows ? min_seg_rows : S;
   if (blockIdx.x == 0 && tid == 0) *seg_rows_out = (int32_t)S;      // the select reads it
   const int64_t w = (int64_t)blockIdx.x * 4 + wave;
   const int64_t part_lo = w * S;
   const int64_t part_hi = part_lo + S < total ? part_lo + S : total;
   if (part_lo >= total) return;                          // nothing left for this wave
+  const bool stream = total * (kD * KTile<kKind>::kElemBytes) > kKeptBytes;
 
   const uint32_t below = (1u << j) - 1u;                // lanes of my 16-lane group with a lower row
   float* st_s = stage_score[wave][kb < G ? kb : 0];
   int32_t* st_i = stage_slot[wave][kb < G ? kb : 0];
   constexpr int T = kRowsPerWaveIter;
 
-  // the groups that overlap my part: 64 groups are tested at a time, one per lane
-  for (int g0 = 0; g0 < n_groups; g0 += 64) {
-    int64_t st = 0;
-    int cnt_l = 0;
-    if (g0 + lane < n_groups) {
-      st = group_start[g0 + lane];
-      const int c = cand_count[g0 + lane];
-      cnt_l = c < 0 ? 0 : (c > s.cand_cap ? s.cand_cap : c);
+  // the groups that overlap my part: 256 groups are tested at a time, four per lane, all loads issued together; the place and
+  // count of the first one found stay, those of a further one are read again (scalar loads that hit the cache)
+  auto count_of = [&](int c) { return c < 0 ? 0 : (c > s.cand_cap ? s.cand_cap : c); };
+  for (int g0 = 0; g0 < n_groups; g0 += 256) {
+    if (g0 > 0) at_hand = places_from(g0);
+    uint64_t hits[4];
+    int found = -1, found_count = 0;
+    int64_t found_start = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t st = at_hand.st[u];
+      const int cnt = count_of(at_hand.cnt[u]);
+      hits[u] = __ballot(cnt > 0 && st < part_hi && st + cnt > part_lo);
+      if (found < 0 && hits[u]) {
+        const int src = __builtin_ctzll(hits[u]);
+        found = g0 + 64 * u + src;
+        found_count = __builtin_amdgcn_readlane(cnt, src);
+        found_start = ((int64_t)__builtin_amdgcn_readlane((int)(st >> 32), src) << 32) |
+                      (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)st, src);
+      }
     }
-    uint64_t hits = __ballot(cnt_l > 0 && st < part_hi && st + cnt_l > part_lo);
-  while (hits) {                                          // one piece per overlapping group
-    const int src = __builtin_ctzll(hits);
-    hits &= hits - 1;
-    const int bg = g0 + src;
-    const int64_t pg = ((int64_t)__builtin_amdgcn_readlane((int)(st >> 32), src) << 32) |
-                       (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)st, src);   // the group's place on the line
-    const int count = __builtin_amdgcn_readlane(cnt_l, src);
+  while (hits[0] | hits[1] | hits[2] | hits[3]) {         // one piece per overlapping group
+    int bg = 0;
+#pragma unroll
+    for (int u = 3; u >= 0; --u) bg = hits[u] ? g0 + 64 * u + __builtin_ctzll(hits[u]) : bg;
+#pragma unroll
+    for (int u = 3; u >= 0; --u) {
+      bool earlier = false;
+#pragma unroll
+      for (int v = 0; v < u; ++v) earlier |= hits[v] != 0;
+      if (!earlier) hits[u] &= hits[u] - 1;
+    }
+    const int64_t pg = bg == found ? found_start : group_start[bg];      // the group's place on the line
+    const int count = bg == found ? found_count : count_of(cand_count[bg]);
     const int seg_lo = part_lo > pg ? (int)(part_lo - pg) : 0;
     const int seg_hi = part_hi - pg < count ? (int)(part_hi - pg) : count;
-    const int seg = (int)(w - pg / S);
+    const int seg = (int)w - ((pg >> 31) == 0 ? (int)((uint32_t)pg / (uint32_t)S) : (int)(pg / S));
 
     const int b = bg / s.Hkv, g = bg % s.Hkv;
+    // Slots past the end of the piece read the id of its last slot (a valid row) and are never kept:
+    // no load of the loop below sits behind a branch, so the waits the compiler derives for the
+    // two tiles in flight are exact counts instead of "everything outstanding".
+    const int32_t* cbg = cand + (int64_t)bg * s.cand_cap;
+    auto fetch_ids = [&](int base_slot) {
+      const int sl = base_slot + lane;
+      const int at = sl < seg_hi ? sl : seg_hi - 1;
+      if constexpr (kDense) return at;
+      else return cbg[at];
+    };
+    int ids_first = fetch_ids(seg_lo), ids_second = fetch_ids(seg_lo + T), ids_third = fetch_ids(seg_lo + 2 * T);
     int n = seq_lens[b];
     n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
     const int64_t head = (int64_t)b * s.Hq + (int64_t)g * G + (kb < G ? kb : 0);
@@ -147,6 +210,7 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
     // nothing, and needs no step before this one.)
     const float thr = thr_state[head];
     const bool skipped = skip_if && skip_if[head] != 0;
+    asm volatile("" : "+v"(ids_first), "+v"(ids_second), "+v"(ids_third));
     if (__ballot(kb < G && !skipped && isnan(thr))) {
       if (j == 0 && kb < G) seg_count[head * nseg + seg] = 0;
       continue;
@@ -154,12 +218,10 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
     const float tau = kb < G && !skipped ? thr - margin : INFINITY;
 
     using Rows = RowMap<kPaged>;
-    using Tile = KTile<kKind>;
-    using Op = typename Tile::Operand;
+    using Op = typename KTile<kKind>::Operand;
     Op A[4];                                            // filled after the first tile's loads are on their way
-    constexpr int ES = Tile::kElemBytes;
+    constexpr int ES = KTile<kKind>::kElemBytes;
     const char* Kbg = static_cast<const char*>(K) + Rows::base(b, g, stride_b, stride_h) * ES;
-    const int32_t* cbg = cand + (int64_t)bg * s.cand_cap;
     int run = 0;                                        // survivors of my head already in global memory
     int staged = 0;                                     // survivors of my head waiting in LDS
 
@@ -186,131 +248,115 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
 
     // Two 64-row tiles are kept in flight per wave: while tile i is multiplied, the loads of tile
     // i+1 (issued before) are still arriving.
-    // ids: the row positions of the tile's 64 slots, one per lane; phys: the same rows as physical
-    // rows (paged cache only; ignored otherwise)
-    auto issue = [&](Tile& Bt, int (&rows)[4], int ids, int phys) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        int row = __shfl(ids, 16 * t + j);
-        row = (row < 0 || row >= n) ? 0 : row;          // padding slots read row 0 and are never kept
-        rows[t] = row;
-        const int prow = kPaged ? __shfl(phys, 16 * t + j) : row;
-        Bt.load_row(t, Kbg + Rows::offset(page, prow, stride_b, stride_n) * ES, kb);
-      }
+    // phys: the tile's 64 rows as physical rows, one per lane
+    auto issue = [&](auto& Bt, int phys) {
+      Bt.fetch(Kbg, phys, lane, [&](int p) { return Rows::offset(page, p, stride_b, stride_n) * ES; });
     };
-    auto lookup = [&](int ids) { return Rows::phys(page, b, (ids < 0 || ids >= n) ? 0 : ids); };
-    auto consume = [&](Tile& Bt, int (&rows)[4], int base_slot) {
+    auto lookup = [&](int ids) { return Rows::phys(page, b, ids); };
+    // ids: their row positions
+    auto consume = [&](const auto& Bt, int ids, int base_slot) {
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
+        const KSub<kKind> sub = Bt.sub(t, turn[wave], lane);
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
-          acc = mfma16(A[kk], Bt.operand(t, kk), acc);
+          acc = mfma16(A[kk], sub.operand(kk), acc);
         const float v = Split3<Op>::sum(acc) * scale;
         const int slot = base_slot + 16 * t + j;
         const bool pass = kb < G && slot < seg_hi && v >= tau;
         const uint32_t gm = (uint32_t)(__ballot(pass) >> (16 * kb)) & 0xFFFFu;   // my head's 16 rows
+        const int row = lane_value(ids, j, 16 * t);
         if (pass) {
           const int o = staged + __popc(gm & below);
           st_s[o] = v;
-          st_i[o] = rows[t];                            // the row position itself: the select needs no lookup
+          st_i[o] = row;                                // the row position itself: the select needs no lookup
         }
         staged += __popc(gm);
       }
       // room for one more tile (64 rows) in every head's stage?  (wave-uniform test)
       if (__ballot(staged > kFilterStage - kRowsPerWaveIter)) flush();
     };
-    // Slots past the end of the piece read the id of its last slot (a valid row) and are never kept:
-    // no load of the loop below sits behind a branch, so the waits the compiler derives for the
-    // two tiles in flight are exact counts instead of "everything outstanding".
-    auto fetch_ids = [&](int base_slot) {
-      const int sl = base_slot + lane;
-      const int at = sl < seg_hi ? sl : seg_hi - 1;
-      if constexpr (kDense) return at;
-      else return cbg[at];
-    };
+    auto checked = [&](int ids) { return ids < 0 || ids >= n ? 0 : ids; };   // (a bad entry of a caller's list reads row 0)
 
     // Row ids are fetched three tiles ahead, always BEFORE the loads of the tile that precedes
     // their use are issued: a wait for ids then never has to wait for a tile still in flight
     // (the vector-memory counter completes in issue order).
-    Tile Bt0, Bt1;
-    int rows0[4], rows1[4];
+    auto walk = [&](auto Bt0, auto Bt1) {               // (the two tiles in flight)
     int base_slot = seg_lo;
     if constexpr (!kPaged) {
-      const int ids_0 = fetch_ids(seg_lo);
-      int ids_b = fetch_ids(seg_lo + T);                  // ids of the next odd tile
-      int ids_a = fetch_ids(seg_lo + 2 * T);              // ids of the next even tile
-      issue(Bt0, rows0, ids_0, 0);
+      int ids_0 = checked(ids_first), ids_1;              // ids of the even tile in flight, of the odd one
+      int ids_b = ids_second;                             // ids of the next odd tile
+      int ids_a = ids_third;                              // ids of the next even tile
+      issue(Bt0, ids_0);
       report_q_range(load_query_operand(A, q, (int64_t)b * s.Hq + (int64_t)g * G, G, j, kb), flags);   // overlaps the first tile's latency
       for (; base_slot + 2 * T < seg_hi; base_slot += 2 * T) {   // at least three tiles left: no conditions inside
-        issue(Bt1, rows1, ids_b, 0);
+        issue(Bt1, ids_1 = checked(ids_b));
         ids_b = fetch_ids(base_slot + 3 * T);
-        consume(Bt0, rows0, base_slot);
-        issue(Bt0, rows0, ids_a, 0);
+        consume(Bt0, ids_0, base_slot);
+        issue(Bt0, ids_0 = checked(ids_a));
         ids_a = fetch_ids(base_slot + 4 * T);
-        consume(Bt1, rows1, base_slot + T);
+        consume(Bt1, ids_1, base_slot + T);
       }
       if (base_slot + T < seg_hi) {                       // two tiles left (wave-uniform)
-        issue(Bt1, rows1, ids_b, 0);
-        consume(Bt0, rows0, base_slot);
-        consume(Bt1, rows1, base_slot + T);
+        issue(Bt1, ids_1 = checked(ids_b));
+        consume(Bt0, ids_0, base_slot);
+        consume(Bt1, ids_1, base_slot + T);
       } else {
-        consume(Bt0, rows0, base_slot);
+        consume(Bt0, ids_0, base_slot);
       }
     } else {
       // Paged cache: a block-table lookup sits between a row id and its address.  A wait completes
       // everything older than what it waits for, so with tile i in flight every step issues, BEFORE
       // the loads of tile i+1: the ids of tile i+3 and the lookup for tile i+2 (whose ids were fetched
-      // one step earlier, before the loads of tile i).  The lane shuffles that spread ids and physical
-      // rows of tile i+1 over the wave come first, so that the registers can be refilled in place.
-      int prow[4];
-      auto aim = [&](int (&rows)[4], int ids, int phys) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int row = __shfl(ids, 16 * t + j);
-          rows[t] = (row < 0 || row >= n) ? 0 : row;
-          prow[t] = __shfl(phys, 16 * t + j);
-        }
-      };
-      auto fire = [&](Tile& Bt) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) Bt.load_row(t, Kbg + Rows::offset(page, prow[t], stride_b, stride_n) * ES, kb);
-      };
-      int ids_0 = fetch_ids(seg_lo), ids_1 = fetch_ids(seg_lo + T);
+      // one step earlier, before the loads of tile i).
+      int ids_0 = checked(ids_first), ids_1 = checked(ids_second);
       int phys_0 = lookup(ids_0), phys_1 = lookup(ids_1);
-      aim(rows0, ids_0, phys_0);
-      ids_0 = fetch_ids(seg_lo + 2 * T);
-      __builtin_amdgcn_sched_barrier(0);
-      fire(Bt0);
+      int in_0 = ids_0, in_1;                             // of the tiles in flight
+      {
+        const int at = phys_0;
+        ids_0 = ids_third;
+        issue(Bt0, at);
+      }
       report_q_range(load_query_operand(A, q, (int64_t)b * s.Hq + (int64_t)g * G, G, j, kb), flags);
       // here and at the top of every iteration: (ids_1, phys_1) describe the next odd tile, ids_0 the next even one
       for (; base_slot + 2 * T < seg_hi; base_slot += 2 * T) {
-        aim(rows1, ids_1, phys_1);
-        ids_1 = fetch_ids(base_slot + 3 * T);
-        phys_0 = lookup(ids_0);
-        __builtin_amdgcn_sched_barrier(0);      // the instruction scheduler must not move these two loads
-        fire(Bt1);                              // behind the tile's: the order is what the waits rely on
-        consume(Bt0, rows0, base_slot);
-        aim(rows0, ids_0, phys_0);
-        ids_0 = fetch_ids(base_slot + 4 * T);
-        phys_1 = lookup(ids_1);
-        __builtin_amdgcn_sched_barrier(0);
-        fire(Bt0);
-        consume(Bt1, rows1, base_slot + T);
+        {
+          const int at = phys_1;
+          in_1 = ids_1;
+          ids_1 = fetch_ids(base_slot + 3 * T);
+          ids_0 = checked(ids_0);
+          phys_0 = lookup(ids_0);
+          __builtin_amdgcn_sched_barrier(0);    // the instruction scheduler must not move these two loads
+          issue(Bt1, at);                       // behind the tile's: the order is what the waits rely on
+        }
+        consume(Bt0, in_0, base_slot);
+        {
+          const int at = phys_0;
+          in_0 = ids_0;
+          ids_0 = fetch_ids(base_slot + 4 * T);
+          ids_1 = checked(ids_1);
+          phys_1 = lookup(ids_1);
+          __builtin_amdgcn_sched_barrier(0);
+          issue(Bt0, at);
+        }
+        consume(Bt1, in_1, base_slot + T);
       }
       if (base_slot + T < seg_hi) {
-        aim(rows1, ids_1, phys_1);
-        fire(Bt1);
-        consume(Bt0, rows0, base_slot);
-        consume(Bt1, rows1, base_slot + T);
+        issue(Bt1, phys_1);
+        consume(Bt0, in_0, base_slot);
+        consume(Bt1, ids_1, base_slot + T);
       } else {
-        consume(Bt0, rows0, base_slot);
+        consume(Bt0, in_0, base_slot);
       }
       // A use of the prefetched ids on every path: without it the compiler moves the prologue's fetch of
       // ids_0 down to the loop entry, behind the first tile's loads, and the loop's first wait for it
       // becomes a wait for everything.
       asm volatile("" ::"v"(ids_0), "v"(ids_1));
     }
+    };
+    if (stream) walk(StreamTile<kKind>{}, StreamTile<kKind>{});
+    else walk(KTile<kKind>{}, KTile<kKind>{});
     flush();
     if (j == 0 && kb < G) seg_count[head * nseg + seg] = run;
   }

@@ -5,6 +5,8 @@
 #pragma once
 #include "lfps_internal.h"
 
+#include <type_traits>
+
 namespace lfps {
 
 constexpr int kScoreThreads = 256;           // 4 waves
@@ -158,14 +160,65 @@ struct KSub<kKindFp8> {
   }
 };
 
-// A 64-row K tile: sub-tile t holds the rows 16 t + j.
+// The value of x in lane `base + more` of the wave (more: known when compiled; it becomes the instruction's offset).
+__device__ __forceinline__ int lane_value(int x, int base, int more) {
+  return __builtin_amdgcn_ds_bpermute(4 * base + 4 * more, x);
+}
+
+// A 64-row K tile: sub-tile t holds the rows 16 t + j, every lane loads its own channels of its row (four loads touch every
+// cache line of a row).
 template <int kKind>
 struct KTile {
   using Operand = typename KSub<kKind>::Operand;
   static constexpr int kElemBytes = KSub<kKind>::kElemBytes;
-  KSub<kKind> sub[4];
-  __device__ __forceinline__ void load_row(int t, const char* row, int kb) { sub[t].load_row(row, kb); }
-  __device__ __forceinline__ Operand operand(int t, int kk) const { return sub[t].operand(kk); }
+  static constexpr int kLdsChunks = 1;                     // (none needed)
+  KSub<kKind> s_[4];
+  __device__ __forceinline__ void load_row(int t, const char* row, int kb) { s_[t].load_row(row, kb); }
+  __device__ __forceinline__ Operand operand(int t, int kk) const { return s_[t].operand(kk); }
+  // the rows whose addresses relative to Kbg are offset(lane's row id of that tile row)
+  template <typename Offset>
+  __device__ __forceinline__ void fetch(const char* Kbg, int phys, int lane, Offset offset) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) load_row(t, Kbg + offset(lane_value(phys, lane & 15, 16 * t)), lane >> 4);
+  }
+  __device__ __forceinline__ KSub<kKind> sub(int t, u32x4*, int) const { return s_[t]; }
+};
+
+// The same tile fetched past the caches: every load instruction of the wave covers whole rows (16 lanes a row, 8 of FP8), so
+// that a cache line is touched by one instruction only and need not be kept (non-temporal).  sub(t) turns the sixteen rows of
+// sub-tile t into operands through a wave-private piece of LDS (rows 16 bytes further apart than they are long, so that
+// neither the writes nor the reads of neighbouring lanes meet in a bank): the operands, and so the scores' bits, are KTile's.
+template <int kKind>
+struct StreamTile {
+  using Operand = typename KSub<kKind>::Operand;
+  static constexpr int kElemBytes = KSub<kKind>::kElemBytes;
+  static constexpr int kChunks = kD * kElemBytes / 16;                 // of a row
+  static constexpr int kLoadRows = 64 / kChunks;                       // rows of a load instruction
+  static constexpr int kLoads = kRowsPerWaveIter / kLoadRows;
+  static constexpr int kLdsChunks = 16 * (kChunks + 1);
+  u32x4 raw[kLoads];
+  template <typename Offset>
+  __device__ __forceinline__ void fetch(const char* Kbg, int phys, int lane, Offset offset) {
+    const u32x4* mine = reinterpret_cast<const u32x4*>(Kbg) + lane % kChunks;
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int row = lane_value(phys, lane / kChunks, i * kLoadRows);
+      raw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(mine) + offset(row)));
+    }
+  }
+  __device__ __forceinline__ KSub<kKind> sub(int t, u32x4* lds, int lane) const {
+    constexpr int kPer = kLoads / 4, kPitch = kChunks + 1;
+    u32x4* to = lds + lane / kChunks * kPitch + lane % kChunks;
+    const u32x4* from = lds + (lane & 15) * kPitch + kChunks / 4 * (lane >> 4);
+    wave_lds_order();                                                  // the reads of the sub-tile before
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) to[i * kLoadRows * kPitch] = raw[kPer * t + i];
+    wave_lds_order();
+    KSub<kKind> out;
+#pragma unroll
+    for (int c = 0; c < kChunks / 4; ++c) out.v[c] = __builtin_bit_cast(std::remove_reference_t<decltype(out.v[0])>, from[c]);
+    return out;
+  }
 };
 
 // Scores of the slots first .. first+63, first+step .. first+step+63, ... (below count) of one KV group, by one wave:

@@ -1,0 +1,62 @@
+"""Scoring passes over more rows than the memory-side cache holds (their K rows are fetched past the caches and turned into
+operands in LDS): bit for bit what the unfiltered kernels return, which other tests hold against the oracle."""
+import pytest
+import torch
+
+from tests.harness import DEV
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,page,B,L,Hq,Hkv", [
+    ("bf16", 0, 5, 40007, 32, 8), ("bf16", 16, 3, 70001, 16, 8), ("f16", 64, 5, 40013, 32, 8), ("f16", 0, 7, 33331, 8, 8),
+    ("fp8k", 0, 5, 70003, 16, 8), ("fp8kv", 16, 6, 60011, 32, 8)])
+def test_streamed_scoring_equals_the_unfiltered_kernels(dtype, page, B, L, Hq, Hkv):
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    kd = {"bf16": torch.bfloat16, "f16": torch.float16}.get(dtype, torch.float8_e4m3fn)
+    vd = torch.bfloat16 if dtype == "fp8k" else kd
+    Lcap, k, r = L + 4, L // 20, 12
+    nb = -(-Lcap // page) if page else 1
+    shape = (B * nb, Hkv, page, 128) if page else (B, Hkv, Lcap, 128)
+    K, V = (torch.empty(shape, dtype=d, device=DEV) for d in (kd, vd))
+    for T in (K, V):
+        for i in range(0, shape[0], -(-shape[0] // B)):
+            T[i:i + -(-shape[0] // B)] = torch.randn(T[i:i + -(-shape[0] // B)].shape, device=DEV, generator=g).to(T.dtype)
+    table = torch.randperm(B * nb, device=DEV, generator=g).view(B, nb).to(torch.int32)
+    lens = [L - 29 * b for b in range(B)]
+    row_bytes = 128 * K.element_size()
+    assert Hkv * sum(lens) * row_bytes > 256 << 20
+    ks = torch.tensor([k - b for b in range(B)], dtype=torch.int32, device=DEV)
+    q = torch.randn((B, Hq, 128), device=DEV, generator=g)
+    ctxs = []
+    for filtered in (True, False):
+        ctx = Lfps(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="f16" if dtype == "f16" else "bf16", max_seq_len=Lcap,
+                   max_k=k, radius=r, k_fp8=kd == torch.float8_e4m3fn, v_fp8=vd == torch.float8_e4m3fn)
+        ctx.lfps_set_filter(filtered)
+        ctxs.append(ctx)
+    prev = None
+    for t in range(3):                                            # t = 0: the exact Top-k, then two steps (the second filtered)
+        seq = torch.tensor([n + t for n in lens], dtype=torch.int32, device=DEV)
+        res = []
+        for ctx in ctxs:
+            kv = ctx.paged_kv_view(K, V, table, seq) if page else ctx.kv_view(K, V, seq)
+            idx = torch.full((B, Hq, k), -5, dtype=torch.int32, device=DEV)
+            sc = torch.full((B, Hq, k), -5.0, device=DEV)
+            out = torch.zeros((B, Hq, 128), device=DEV)
+            if t == 0:
+                ctx.lfps_exact_topk(q, kv, ks, idx, sc)
+            else:
+                ctx.lfps_step(q, kv, prev, ks, idx, out, sc)
+                cnt = torch.zeros((B, Hkv), dtype=torch.int32, device=DEV)
+                ctx.lfps_copy_cand_count(cnt)
+                assert int(cnt.sum()) * row_bytes > 256 << 20
+            res.append((idx, sc, out))
+        for x, y, name in zip(*res, ("index", "score", "output")):
+            assert torch.equal(x, y), (name, t, int((x != y).sum()))
+        prev = res[0][0]
+        q = q + 0.02 * torch.randn((B, Hq, 128), device=DEV, generator=g)
+    assert ctxs[0].lfps_poll_rescored() == 0                      # the filtered passes decided, not their fall-back
+    for ctx in ctxs:
+        ctx.close()
