@@ -85,17 +85,79 @@ int full_attn_splits(const Shape& s) {
 
 __device__ __forceinline__ int rows_per_split(int n, int n_split) { return (((n + n_split - 1) / n_split) + 15) & ~15; }
 
+// exp(x) for x <= 0 to about one unit in the last place: exp2 of the rounded product, corrected by the product's rounding
+// error, which grows with |x|.  (Results below 2^-126 are 0; a NaN stays one.)
+__device__ __forceinline__ float exp_weight(float x) {
+  constexpr double c = 1.4426950408889634;
+  constexpr float hi = (float)c, lo = (float)(c - (double)hi), ln2 = 0.6931471805599453f;
+  x = __builtin_elementwise_maximum(x, -1e30f);             // (the correction needs a finite x)
+  const float t = x * hi;
+  const float r = fmaf(x, lo, fmaf(x, hi, -t));
+  const float e = __builtin_amdgcn_exp2f(t);
+  return fmaf(e * ln2, r, e);
+}
+
+// The sums over the 16 lanes of a row of lanes of a[0 .. G-1], G = 1, 2 or 4: lane j receives that of a[j % G].  (A butterfly
+// over lane distances 1, 2, 4, 8 in which the first log2 G steps also share the G sums out: 11 instructions instead of 16.)
+template <int G>
+__device__ __forceinline__ float row16_shared_sums(float (&a)[G], int j) {
+#define LFPS_DPP(v, ctrl) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false))
+  float x;
+  if constexpr (G == 1) {
+    x = a[0];
+    x += LFPS_DPP(x, 0xB1);                                  // quad_perm 1 0 3 2
+    x += LFPS_DPP(x, 0x4E);                                  // quad_perm 2 3 0 1
+  } else {
+    const bool odd = j & 1;
+    float y[G / 2];
+#pragma unroll
+    for (int h = 0; h < G / 2; ++h) {
+      const float keep = odd ? a[2 * h + 1] : a[2 * h], give = odd ? a[2 * h] : a[2 * h + 1];
+      y[h] = keep + LFPS_DPP(give, 0xB1);
+    }
+    if constexpr (G == 2) {
+      x = y[0];
+      x += LFPS_DPP(x, 0x4E);
+    } else {
+      const bool upper = j & 2;
+      const float keep = upper ? y[1] : y[0], give = upper ? y[0] : y[1];
+      x = keep + LFPS_DPP(give, 0x4E);
+    }
+  }
+  // (lanes j and j ^ 4, then j ^ 8, by rotation: every lane of a quad holds another sum)
+  x += LFPS_DPP(x, 0x124);                                   // row_ror:4: with the next one, the pairs' sums agree
+  x += LFPS_DPP(x, 0x128);                                   // row_ror:8
+  return x;
+#undef LFPS_DPP
+}
+
 // grid (n_split, B*Hkv); part [B*Hkv, n_split, G, D+2]: acc[D], m, l
-template <typename TK, typename T, int G, bool kPaged>
+//
+// A wave takes U groups of four rows at a time, 16 lanes a row, 8 channels a lane, for K and for V.  The G sums of a row are
+// shared out over its lanes, so that a lane makes the softmax step for one head and its own rows only, once per tile; the
+// weights reach the lanes that hold the values through LDS.  The rows of K and of V are in flight in turn, those of one while
+// the other is used.  Bound by the bytes of K and V in 16 bits (64 groups x 32K rows, 1.07 GB: 174 us with the merge, 199 before),
+// by the multiply-adds in FP8 (the same rows: 132 us, 233 before): when every lane made the step for all heads and each of its
+// rows, a row cost the same whatever it took to fetch.  U = 16 for FP8 leaves two waves per SIMD: 145 us.
+// (The dot products on the matrix units were as fast, 169 to 180 us, but 1.3 times as far from 64 bits where a few rows carry
+// the weight: large scores are sums of like-signed products there.)
+// kOnce: rows past the caches, for caches larger than the memory-side cache (8 x 32K rows 195 against 207 us with the kernel as
+// it was); smaller ones are found there by the next call (2 x 32K in FP8 65 against 80).
+template <typename TK, typename T, int G, bool kPaged, bool kOnce>
 __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float* __restrict__ q,
                                                             const TK* __restrict__ K, const T* __restrict__ V,
                                                             int64_t stride_b, int64_t stride_h, int64_t stride_n,
                                                             KvPage pg, const int32_t* __restrict__ seq_lens,
                                                             float* __restrict__ part, int n_split, float scale) {
+  constexpr int U = sizeof(TK) == 4 && G > 1 ? 4 : 8, kRows = 4 * U;
+  constexpr int kShare = 16 / G;                            // lanes of a row that hold the same head's sum
+  constexpr int NV = U > kShare ? U / kShare : 1;           // (row, head) pairs of a lane
   __shared__ float red_acc[4][G][kD];
+  __shared__ float weight[4][kRows][G];
   __shared__ float red_m[4][G], red_l[4][G];
   const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv, split = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, rs = lane >> 4;
   int n = seq_lens[b];
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
@@ -114,132 +176,142 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
   using Rows = RowMap<kPaged>;
   const TK* Kbg = K + Rows::base(b, g, stride_b, stride_h) + 8 * j;
   const T* Vbg = V + Rows::base(b, g, stride_b, stride_h) + 8 * j;
-
-  float m[G], l[G], acc[G][8];
+  // row r0 + lane of a tile as a physical row (past the end: the last row, of weight 0, so that no load sits behind a branch)
+  auto rows_of = [&](int r0) { return Rows::phys(pg, b, r0 + lane < r_end ? r0 + lane : r_end - 1); };
+  auto row_value = [&](int x, int u) { return __builtin_amdgcn_ds_bpermute(4 * rs + 16 * u, x); };   // of row 4 u + rs
+  Raw8<TK> kt[U];                                           // kt[u], vt[u]: my channels of row 4 u + rs
+  Raw8<T> vt[U];
+  auto fetch_k = [&](int phys) {
 #pragma unroll
-  for (int h = 0; h < G; ++h) {
-    m[h] = -INFINITY;
-    l[h] = 0.f;
+    for (int u = 0; u < U; ++u) {
+      const TK* p = Kbg + Rows::offset(pg, row_value(phys, u), stride_b, stride_n);
+      if constexpr (kOnce) kt[u].load_once(p);
+      else kt[u].load(p);
+    }
+  };
+  auto fetch_v = [&](int phys) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const T* p = Vbg + Rows::offset(pg, row_value(phys, u), stride_b, stride_n);
+      if constexpr (kOnce) vt[u].load_once(p);
+      else vt[u].load(p);
+    }
+  };
+  // my pairs: head j % G and the rows 4 u + rs with u = t * kShare + j / G
+  const int my_u = j / G;
+  const bool mine = my_u < U;
+  float m = -INFINITY, l = 0.f;                             // of head j % G: largest score so far; the sum over my rows
+  float acc[G][8];
+#pragma unroll
+  for (int h = 0; h < G; ++h)
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[h][c] = 0.f;
-  }
 
-  constexpr int U = 4;                       // rows per lane group and tile
-  // Wave w takes rows r_begin + 16*(4*i + w) + 4*u + rs of tile i.  Two tiles are kept in flight: the loads of
-  // the next one are issued before the current one is used, as raw cache elements (half or a quarter of the
-  // registers of their fp32 form).  Rows past the end are read from the last row and weigh nothing, so no
-  // load sits behind a branch.
-  struct Tile {
-    Raw8<TK> k[U];
-    Raw8<T> v[U];
-    bool ok[U];
-  };
-  auto issue = [&](Tile& t, int r0) {
+  constexpr int kStep = 4 * kRows;                          // wave w takes tiles w, w + 4, ...
+  int r0 = r_begin + kRows * wave;
+  int phys = rows_of(r0), phys_next = rows_of(r0 + kStep);
+  fetch_k(phys);
+  fetch_v(phys);
+  for (; r0 < r_end; r0 += kStep) {
+    float v[NV];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      int r = r0 + 4 * u + rs;
-      t.ok[u] = r < r_end;
-      r = t.ok[u] ? r : r_end - 1;
-      const int64_t off = Rows::offset(pg, Rows::phys(pg, b, r), stride_b, stride_n);
-      t.k[u].load(Kbg + off);
-      t.v[u].load(Vbg + off);
-    }
-  };
-  auto consume = [&](const Tile& t) {
-    float kx[U][8], vx[U][8];
-    bool ok[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      t.k[u].get(kx[u]);
-      t.v[u].get(vx[u]);
-      ok[u] = t.ok[u];
-    }
-    float sc[U][G];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
+      float x[8], a[G];
+      kt[u].get(x);
 #pragma unroll
       for (int h = 0; h < G; ++h) {
-        float a = qr[h][0] * kx[u][0];
+        a[h] = qr[h][0] * x[0];
 #pragma unroll
-        for (int c = 1; c < 8; ++c) a = fmaf(qr[h][c], kx[u][c], a);
-        sc[u][h] = a;
+        for (int c = 1; c < 8; ++c) a[h] = fmaf(qr[h][c], x[c], a[h]);
       }
+      const float sum = row16_shared_sums<G>(a, j);
+      v[u / kShare] = u % kShare == 0 || my_u == u % kShare ? sum : v[u / kShare];
+      if (u % 2) __builtin_amdgcn_sched_barrier(0);         // (registers: two rows' elements at a time as fp32)
+    }
+    phys = phys_next;
+    phys_next = rows_of(r0 + 2 * kStep);
+    if constexpr (kPaged) __builtin_amdgcn_sched_barrier(0);      // the look-up before the rows: its wait must not include them
+    fetch_k(phys);
+    // one online-softmax step
+    bool ok[NV];
+    float mx = m;
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int t = 0; t < NV; ++t) {
+      ok[t] = mine && r0 + 4 * (t * kShare + my_u) + rs < r_end;
+      mx = ok[t] ? fmaxf(mx, v[t]) : mx;
+    }
+#define LFPS_ROT(x, n) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + (n), 0xf, 0xf, false))
+    mx = fmaxf(mx, LFPS_ROT(mx, 8));
+    mx = fmaxf(mx, LFPS_ROT(mx, 4));
+    if constexpr (G <= 2) mx = fmaxf(mx, LFPS_ROT(mx, 2));
+    if constexpr (G == 1) mx = fmaxf(mx, LFPS_ROT(mx, 1));
+#undef LFPS_ROT
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float alpha = mx == -INFINITY ? 1.f : exp_weight(m - mx);      // (0 on the first tile)
+    l *= alpha;
+    m = mx;
+    wave_lds_order();                                                // (the weights of the tile before have been read)
 #pragma unroll
-      for (int h = 0; h < G; ++h) sc[u][h] = row16_butterfly_sum(sc[u][h]);
+    for (int t = 0; t < NV; ++t) {
+      const float e = exp_weight(v[t] - mx);
+      const float p = ok[t] && v[t] != -INFINITY ? e : 0.f;
+      l += p;
+      if (mine) weight[wave][4 * (t * kShare + my_u) + rs][j % G] = p;
+    }
+    wave_lds_order();
+    if (__ballot(alpha != 1.f)) {
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      float mx = m[h];
+      for (int h = 0; h < G; ++h) {
+        const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(alpha), h));
 #pragma unroll
-      for (int u = 0; u < U; ++u) mx = ok[u] ? fmaxf(mx, sc[u][h]) : mx;
-      // a lane group whose rows all lie past the end still has mx = -inf: keep its empty state
-      const float alpha = (mx == -INFINITY) ? 1.f : __expf(m[h] - mx);   // exp(-inf) = 0 on the first tile
-      float p[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) p[u] = ok[u] ? __expf(sc[u][h] - mx) : 0.f;
-      float ls = l[h] * alpha;
-#pragma unroll
-      for (int u = 0; u < U; ++u) ls += p[u];
-      l[h] = ls;
-      m[h] = mx;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        float a = acc[h][c] * alpha;
-#pragma unroll
-        for (int u = 0; u < U; ++u) a = fmaf(p[u], vx[u][c], a);
-        acc[h][c] = a;
+        for (int c = 0; c < 8; ++c) acc[h][c] *= a;
       }
     }
-  };
-  Tile ta, tb;
-  issue(ta, r_begin + 16 * wave);
-  for (int r0 = r_begin + 16 * wave; r0 < r_end; r0 += 128) {
-    issue(tb, r0 + 64);
-    consume(ta);
-    issue(ta, r0 + 128);
-    consume(tb);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float x[8], p[G];
+      vt[u].get(x);
+#pragma unroll
+      for (int h = 0; h < G; ++h) p[h] = weight[wave][4 * u + rs][h];
+#pragma unroll
+      for (int h = 0; h < G; ++h)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[h][c] = fmaf(p[h], x[c], acc[h][c]);
+      if (u % 2) __builtin_amdgcn_sched_barrier(0);
+    }
+    fetch_v(phys);
   }
 
-  // merge the 4 lane groups of the wave, then the 4 waves
+  // the lanes of the wave, then the four waves (a wave without rows: m = -inf, weight 0)
 #pragma unroll
-  for (int h = 0; h < G; ++h) {
-    float mx = fmaxf(m[h], __shfl_xor(m[h], 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float a = (m[h] == -INFINITY) ? 0.f : __expf(m[h] - mx);   // lane groups that saw no row
-    float ls = l[h] * a;
-    ls += __shfl_xor(ls, 16);
-    ls += __shfl_xor(ls, 32);
+  for (int d = G; d < 64; d <<= 1) l += __shfl_xor(l, d);
+#pragma unroll
+  for (int h = 0; h < G; ++h)
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-      float v = acc[h][c] * a;
-      v += __shfl_xor(v, 16);
-      v += __shfl_xor(v, 32);
-      acc[h][c] = v;
+      acc[h][c] += __shfl_xor(acc[h][c], 16);
+      acc[h][c] += __shfl_xor(acc[h][c], 32);
     }
-    m[h] = mx;
-    l[h] = ls;
-  }
   if (rs == 0) {
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
+    for (int h = 0; h < G; ++h)
 #pragma unroll
       for (int c = 0; c < 8; ++c) red_acc[wave][h][8 * j + c] = acc[h][c];
-      if (j == 0) {
-        red_m[wave][h] = m[h];
-        red_l[wave][h] = l[h];
-      }
+    if (j < G) {
+      red_m[wave][j] = m;
+      red_l[wave][j] = l;
     }
   }
   __syncthreads();
   float* po = part + ((int64_t)bg * n_split + split) * G * (kD + 2);
   for (int e = tid; e < G * kD; e += kAttnThreads) {
     const int h = e / kD, c = e % kD;
-    float mx = fmaxf(fmaxf(red_m[0][h], red_m[1][h]), fmaxf(red_m[2][h], red_m[3][h]));
+    const float mx = fmaxf(fmaxf(red_m[0][h], red_m[1][h]), fmaxf(red_m[2][h], red_m[3][h]));
     float a = 0.f, ls = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const float f = (red_m[w][h] == -INFINITY) ? 0.f : __expf(red_m[w][h] - mx);
+      const float f = (red_m[w][h] == -INFINITY) ? 0.f : exp_weight(red_m[w][h] - mx);
       a = fmaf(red_acc[w][h][c], f, a);
       ls = fmaf(red_l[w][h], f, ls);
     }
@@ -284,7 +356,7 @@ __global__ __launch_bounds__(kD) void k_full_merge(Shape s, const int32_t* __res
     float mx = m;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
-    wgt[c] = __expf(m - mx);
+    wgt[c] = exp_weight(m - mx);
   }
   __syncthreads();
   float a = 0.f, l = 0.f;
@@ -306,18 +378,20 @@ __global__ __launch_bounds__(kD) void k_full_merge(Shape s, const int32_t* __res
 template <typename TK, typename T>
 static hipError_t launch_full_t(const Shape& s, const float* q, const KvView& kv, float* part, int n_split,
                                 hipStream_t st) {
-  dim3 grid(n_split, s.B * s.Hkv), block(kAttnThreads);
+  const dim3 grid(n_split, s.B * s.Hkv), block(kAttnThreads);
   const float scale = 0.08838834764831845f;
-  const TK* K = (const TK*)kv.k;
-  const T* V = (const T*)kv.v;
-#define LFPS_LAUNCH_FULL_P(GG, PAGED)                                                                           \
-  hipLaunchKernelGGL((k_full_attn<TK, T, GG, PAGED>), grid, block, 0, st, s, q, K, V, kv.stride_b, kv.stride_h, \
-                     kv.stride_n, kv.page, kv.seq_lens, part, n_split, scale)
-#define LFPS_LAUNCH_FULL(GG)          \
-  if (kv.page.table) {                \
-    LFPS_LAUNCH_FULL_P(GG, true);     \
-  } else {                            \
-    LFPS_LAUNCH_FULL_P(GG, false);    \
+  // (fp32 rows: a lane's eight channels are two loads, which would fetch the line twice)
+  const bool once = sizeof(TK) < 4 && (int64_t)s.B * s.Hkv * s.Lcap * kD * (int64_t)(sizeof(TK) + sizeof(T)) > kKeptBytes;
+#define LFPS_LAUNCH_FULL_P(GG, PAGED, ONCE)                                                                          \
+  hipLaunchKernelGGL((k_full_attn<TK, T, GG, PAGED, ONCE>), grid, block, 0, st, s, q, (const TK*)kv.k, (const T*)kv.v, \
+                     kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, part, n_split, scale)
+#define LFPS_LAUNCH_FULL(GG)                                          \
+  if (kv.page.table) {                                                \
+    if (once) LFPS_LAUNCH_FULL_P(GG, true, sizeof(TK) < 4);           \
+    else LFPS_LAUNCH_FULL_P(GG, true, false);                         \
+  } else {                                                            \
+    if (once) LFPS_LAUNCH_FULL_P(GG, false, sizeof(TK) < 4);          \
+    else LFPS_LAUNCH_FULL_P(GG, false, false);                        \
   }
   switch (s.G) {
     case 1: LFPS_LAUNCH_FULL(1); break;

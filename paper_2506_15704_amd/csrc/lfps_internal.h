@@ -9,11 +9,14 @@ namespace lfps {
 
 constexpr int kD = 128;           // head_dim the kernels are written for
 constexpr int kMaxSplits = 64;    // upper bound of split-K partials per head (full attention)
+// What the memory-side cache holds (256 MB): rows of a pass that together take more are read past the caches, see the kernels.
+constexpr int64_t kKeptBytes = 256 << 20;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // Where the rows of a request live when the cache is paged (table != nullptr): a pool of blocks of
 // 2^shift rows, table[b*table_stride + (i >> shift)] = block of row i of request b.
@@ -269,25 +272,34 @@ __device__ __forceinline__ bf16x8 fp8x8_to_bf16x8(uint32_t w0, uint32_t w1) {
 }
 
 // Eight consecutive elements of a K or V row as they are loaded (T = float, uint16_t = bf16 bits, _Float16,
-// uint8_t = E4M3), converted to fp32 when used: a row waiting in registers costs 8, 4 or 2 of them.
+// uint8_t = E4M3), converted to fp32 when used: a row waiting in registers costs 8, 4 or 2 of them.  load_once: past the
+// caches, for lines that one instruction reads whole and nobody reads again soon.
 template <typename T>
 struct Raw8;
 template <>
 struct Raw8<float> {
-  float4 a, b;
+  f32x4 a, b;
   __device__ __forceinline__ void load(const float* p) {
-    a = reinterpret_cast<const float4*>(p)[0];
-    b = reinterpret_cast<const float4*>(p)[1];
+    a = reinterpret_cast<const f32x4*>(p)[0];
+    b = reinterpret_cast<const f32x4*>(p)[1];
+  }
+  __device__ __forceinline__ void load_once(const float* p) {
+    a = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+    b = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p) + 1);
   }
   __device__ __forceinline__ void get(float x[8]) const {
-    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w;
-    x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      x[c] = a[c];
+      x[4 + c] = b[c];
+    }
   }
 };
 template <>
 struct Raw8<uint16_t> {
   u32x4 w;
   __device__ __forceinline__ void load(const uint16_t* p) { w = *reinterpret_cast<const u32x4*>(p); }
+  __device__ __forceinline__ void load_once(const uint16_t* p) { w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)); }
   __device__ __forceinline__ void get(float x[8]) const {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -300,6 +312,7 @@ template <>
 struct Raw8<_Float16> {
   f16x8 w;
   __device__ __forceinline__ void load(const _Float16* p) { w = *reinterpret_cast<const f16x8*>(p); }
+  __device__ __forceinline__ void load_once(const _Float16* p) { w = __builtin_nontemporal_load(reinterpret_cast<const f16x8*>(p)); }
   __device__ __forceinline__ void get(float x[8]) const {
 #pragma unroll
     for (int c = 0; c < 8; ++c) x[c] = (float)w[c];
@@ -307,11 +320,12 @@ struct Raw8<_Float16> {
 };
 template <>
 struct Raw8<uint8_t> {
-  uint2 w;
-  __device__ __forceinline__ void load(const uint8_t* p) { w = *reinterpret_cast<const uint2*>(p); }
+  u32x2 w;
+  __device__ __forceinline__ void load(const uint8_t* p) { w = *reinterpret_cast<const u32x2*>(p); }
+  __device__ __forceinline__ void load_once(const uint8_t* p) { w = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p)); }
   __device__ __forceinline__ void get(float x[8]) const {
-    fp8x4_to_f32(w.x, x);
-    fp8x4_to_f32(w.y, x + 4);
+    fp8x4_to_f32(w[0], x);
+    fp8x4_to_f32(w[1], x + 4);
   }
 };
 template <typename T>

@@ -92,7 +92,6 @@ __global__ __launch_bounds__(kScoreThreads) void k_group_score_bf16(Shape s, con
 // 32K rows, 220 MB: a step 64 us, 66 past the caches; equal at 280 to 300 MB.
 // The parts are cut at multiples of 16 slots: of 64, a part of 420 slots grew by 6 % and the last waves had nothing to do
 // (64 groups x 32K rows: 38.1 -> 37.0 us).
-constexpr int64_t kKeptBytes = 256 << 20;
 constexpr int kFilterStage = 256;   // survivors one wave can hold per head before it must write them out
 
 // kDense: the "candidates" of a group are all its rows 0..count-1 (no list is read): the exact Top-k baseline's

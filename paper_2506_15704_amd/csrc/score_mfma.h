@@ -79,34 +79,56 @@ __device__ __forceinline__ f32x4 mfma16(f16x8 a, f16x8 b, f32x4 c) {
 // loads issued together; a lane-dependent branch here would serialise 32 single loads.
 // Returns true if this lane met a query element beyond the fp16 range (fp16 operands only): the element is
 // clamped to +-65504 so that the scores stay finite, and the caller raises LFPS_FLAG_Q_RANGE.
-template <typename Op>
-__device__ __forceinline__ bool load_query_operand(Op (&A)[4], const float* __restrict__ q, int64_t head0, int G, int j,
-                                                   int kb) {
-  const int h = j >> 2, t = j & 3;
-  const float4* qh = reinterpret_cast<const float4*>(q + (head0 + (h < G ? h : 0)) * kD);
-  float4 x[4][2];
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    x[kk][0] = qh[2 * (kk + 4 * kb)];
-    x[kk][1] = qh[2 * (kk + 4 * kb) + 1];
+// (QueryPart is the operand of one step, in two parts for callers that have rows to request between the query's arrival and
+// its use: loads complete in order, and a query asked for behind a tile is there only after the tile.)
+struct QueryPart {
+  float4 x[2];
+  __device__ __forceinline__ void load(const float* __restrict__ q, int64_t head0, int G, int kk, int j, int kb) {
+    const int h = j >> 2;
+    const float4* qh = reinterpret_cast<const float4*>(q + (head0 + (h < G ? h : 0)) * kD);
+    x[0] = qh[2 * (kk + 4 * kb)];
+    x[1] = qh[2 * (kk + 4 * kb) + 1];
   }
-  const bool live = h < G && t < 3;
-  bool clipped = false;
+  template <typename Op>
+  __device__ __forceinline__ bool operand(Op& A, int G, int j, float factor = 1.f) const {
+    const int h = j >> 2, t = j & 3;
+    const bool live = h < G && t < 3;
+    bool clipped = false;
+    float f[8] = {x[0].x, x[0].y, x[0].z, x[0].w, x[1].x, x[1].y, x[1].z, x[1].w};
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    float f[8] = {x[kk][0].x, x[kk][0].y, x[kk][0].z, x[kk][0].w, x[kk][1].x, x[kk][1].y, x[kk][1].z, x[kk][1].w};
-    if constexpr (Split3<Op>::kHalf) {
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        if (fabsf(f[c]) > 65504.0f) {               // also +-inf; a NaN goes through as in the other formats
+    for (int c = 0; c < 8; ++c) {
+      f[c] *= factor;
+      if constexpr (Split3<Op>::kHalf) {
+        if (fabsf(f[c]) > 65504.0f) {                 // also +-inf; a NaN goes through as in the other formats
           clipped |= live;
           f[c] = copysignf(65504.0f, f[c]);
         }
       }
     }
-    A[kk] = Split3<Op>::terms(f, live ? t : 3);
+    A = Split3<Op>::terms(f, live ? t : 3);
+    return clipped;
   }
-  return clipped;
+};
+struct QueryRows {
+  QueryPart part[4];
+  __device__ __forceinline__ void load(const float* __restrict__ q, int64_t head0, int G, int j, int kb) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) part[kk].load(q, head0, G, kk, j, kb);
+  }
+  template <typename Op>
+  __device__ __forceinline__ bool operand(Op (&A)[4], int G, int j) const {
+    bool clipped = false;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) clipped |= part[kk].operand(A[kk], G, j);
+    return clipped;
+  }
+};
+template <typename Op>
+__device__ __forceinline__ bool load_query_operand(Op (&A)[4], const float* __restrict__ q, int64_t head0, int G, int j,
+                                                   int kb) {
+  QueryRows rows;
+  rows.load(q, head0, G, j, kb);
+  return rows.operand(A, G, j);
 }
 
 // One lane of the wave reports a clamped query element (fp16 caches only; compiled out otherwise).
@@ -188,7 +210,8 @@ struct KTile {
 // that a cache line is touched by one instruction only and need not be kept (non-temporal).  sub(t) turns the sixteen rows of
 // sub-tile t into operands through a wave-private piece of LDS (rows 16 bytes further apart than they are long, so that
 // neither the writes nor the reads of neighbouring lanes meet in a bank): the operands, and so the scores' bits, are KTile's.
-template <int kKind>
+// kOnce false: the same with ordinary loads.
+template <int kKind, bool kOnce = true>
 struct StreamTile {
   using Operand = typename KSub<kKind>::Operand;
   static constexpr int kElemBytes = KSub<kKind>::kElemBytes;
@@ -203,7 +226,8 @@ struct StreamTile {
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
       const int row = lane_value(phys, lane / kChunks, i * kLoadRows);
-      raw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(mine) + offset(row)));
+      const u32x4* p = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(mine) + offset(row));
+      raw[i] = kOnce ? __builtin_nontemporal_load(p) : *p;
     }
   }
   __device__ __forceinline__ KSub<kKind> sub(int t, u32x4* lds, int lane) const {
