@@ -21,8 +21,9 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 // Term t (0, 1, 2; 3: zeros) of the three-way split of eight fp32 query elements into the operand's 16-bit format, and the
 // sum of the three MFMA results that undoes the split.  Every wave of a scoring kernel splits 32 elements per lane before
 // its first product, so this is kept short: two elements per hardware conversion (round to nearest even), and the term is
-// chosen before the last one: 8 instructions an element (rounding in integer arithmetic took about 30: four steps of
-// 8 x 32K 262.5 against 260.2 us, the two passes of a hand-over with 32 queries 50 + 62 against 47 + 60.5 us).
+// chosen by factors of 0 and 1, without branches: 7 instructions an element (rounding in integer arithmetic took about 30;
+// with selects, which the compiler made branches, four steps of 1 x 32K took 109 us instead of 106, of 3 x 20K fp16 92 instead
+// of 87).  An infinite or overflowing element makes NaNs here or in the sum, as a difference of infinities does.
 template <typename Op>
 struct Split3;
 template <>
@@ -30,15 +31,17 @@ struct Split3<bf16x8> {
   static constexpr bool kHalf = false;
   __device__ static __forceinline__ bf16x8 terms(const float (&f)[8], int t) {
     bf16x8 out;
+    const float one = t >= 1 ? -1.f : 0.f, two = t >= 2 ? -1.f : 0.f;      // (no branches: the lanes of a wave make different terms)
 #pragma unroll
     for (int c = 0; c < 8; c += 2) {
-      const f32x2 x = {f[c], f[c + 1]};
-      const f32x2 r1 = x - __builtin_convertvector(__builtin_convertvector(x, bf16x2), f32x2);
-      const f32x2 r2 = r1 - __builtin_convertvector(__builtin_convertvector(r1, bf16x2), f32x2);
-      const f32x2 y = t == 0 ? x : (t == 1 ? r1 : (t == 2 ? r2 : f32x2{0.f, 0.f}));
-      const bf16x2 b = __builtin_convertvector(y, bf16x2);
-      out[c] = b[0];
-      out[c + 1] = b[1];
+      f32x2 x = {f[c], f[c + 1]};
+      f32x2 y = __builtin_convertvector(__builtin_convertvector(x, bf16x2), f32x2);
+      x = {fmaf(one, y[0], x[0]), fmaf(one, y[1], x[1])};
+      y = __builtin_convertvector(__builtin_convertvector(x, bf16x2), f32x2);
+      x = {fmaf(two, y[0], x[0]), fmaf(two, y[1], x[1])};
+      const bf16x2 b = __builtin_convertvector(x, bf16x2);
+      out[c] = t < 3 ? b[0] : (__bf16)0.f;
+      out[c + 1] = t < 3 ? b[1] : (__bf16)0.f;
     }
     return out;
   }
@@ -50,14 +53,14 @@ struct Split3<f16x8> {
   // q = t0 + t1 / 2^11 + t2 / 2^22 (11 significant bits per term; the scaling keeps t1, t2 normal)
   __device__ static __forceinline__ f16x8 terms(const float (&f)[8], int t) {
     f16x8 out;
+    const float one = t >= 1 ? -1.f : 0.f, two = t >= 2 ? -1.f / 2048.0f : 0.f;
+    const float up = t == 0 ? 1.f : (t == 1 ? 2048.0f : 4194304.0f), up1 = t >= 2 ? 2048.0f : 0.f;   // (0: a large x must not overflow)
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-      const _Float16 t0 = (_Float16)f[c];
-      const float r1 = f[c] - (float)t0;
-      const _Float16 t1 = (_Float16)(r1 * 2048.0f);
-      const float r2 = r1 - (float)t1 * (1.0f / 2048.0f);
-      const _Float16 t2 = (_Float16)(r2 * 4194304.0f);
-      out[c] = t == 0 ? t0 : (t == 1 ? t1 : (t == 2 ? t2 : (_Float16)0.0f));
+      float x = fmaf(one, (float)(_Float16)f[c], f[c]);
+      x = fmaf(two, (float)(_Float16)(x * up1), x);
+      const _Float16 h = (_Float16)(x * up);
+      out[c] = t < 3 ? h : (_Float16)0.0f;
     }
     return out;
   }
@@ -79,47 +82,37 @@ __device__ __forceinline__ f32x4 mfma16(f16x8 a, f16x8 b, f32x4 c) {
 // loads issued together; a lane-dependent branch here would serialise 32 single loads.
 // Returns true if this lane met a query element beyond the fp16 range (fp16 operands only): the element is
 // clamped to +-65504 so that the scores stay finite, and the caller raises LFPS_FLAG_Q_RANGE.
-// (QueryPart is the operand of one step, in two parts for callers that have rows to request between the query's arrival and
-// its use: loads complete in order, and a query asked for behind a tile is there only after the tile.)
-struct QueryPart {
-  float4 x[2];
-  __device__ __forceinline__ void load(const float* __restrict__ q, int64_t head0, int G, int kk, int j, int kb) {
+// (In two parts for callers that have rows to request between the query's arrival and its use.)
+struct QueryRows {
+  float4 x[4][2];
+  __device__ __forceinline__ void load(const float* __restrict__ q, int64_t head0, int G, int j, int kb) {
     const int h = j >> 2;
     const float4* qh = reinterpret_cast<const float4*>(q + (head0 + (h < G ? h : 0)) * kD);
-    x[0] = qh[2 * (kk + 4 * kb)];
-    x[1] = qh[2 * (kk + 4 * kb) + 1];
-  }
-  template <typename Op>
-  __device__ __forceinline__ bool operand(Op& A, int G, int j, float factor = 1.f) const {
-    const int h = j >> 2, t = j & 3;
-    const bool live = h < G && t < 3;
-    bool clipped = false;
-    float f[8] = {x[0].x, x[0].y, x[0].z, x[0].w, x[1].x, x[1].y, x[1].z, x[1].w};
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      f[c] *= factor;
-      if constexpr (Split3<Op>::kHalf) {
-        if (fabsf(f[c]) > 65504.0f) {                 // also +-inf; a NaN goes through as in the other formats
-          clipped |= live;
-          f[c] = copysignf(65504.0f, f[c]);
-        }
-      }
+    for (int kk = 0; kk < 4; ++kk) {
+      x[kk][0] = qh[2 * (kk + 4 * kb)];
+      x[kk][1] = qh[2 * (kk + 4 * kb) + 1];
     }
-    A = Split3<Op>::terms(f, live ? t : 3);
-    return clipped;
-  }
-};
-struct QueryRows {
-  QueryPart part[4];
-  __device__ __forceinline__ void load(const float* __restrict__ q, int64_t head0, int G, int j, int kb) {
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) part[kk].load(q, head0, G, kk, j, kb);
   }
   template <typename Op>
   __device__ __forceinline__ bool operand(Op (&A)[4], int G, int j) const {
+    const int h = j >> 2, t = j & 3;
+    const bool live = h < G && t < 3;
     bool clipped = false;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) clipped |= part[kk].operand(A[kk], G, j);
+    for (int kk = 0; kk < 4; ++kk) {
+      float f[8] = {x[kk][0].x, x[kk][0].y, x[kk][0].z, x[kk][0].w, x[kk][1].x, x[kk][1].y, x[kk][1].z, x[kk][1].w};
+      if constexpr (Split3<Op>::kHalf) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          if (fabsf(f[c]) > 65504.0f) {               // also +-inf; a NaN goes through as in the other formats
+            clipped |= live;
+            f[c] = copysignf(65504.0f, f[c]);
+          }
+        }
+      }
+      A[kk] = Split3<Op>::terms(f, live ? t : 3);
+    }
     return clipped;
   }
 };
