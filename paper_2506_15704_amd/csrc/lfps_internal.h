@@ -85,10 +85,11 @@ hipError_t launch_candidates(const Shape& s, const int32_t* prev_topk, const int
 // Scores of candidate rows (cand != NULL) or of all rows 0..n_b-1 (cand == NULL) for the G heads
 // of each KV group.  score is [B, Hq, score_stride].
 // flags: the context's status word (LFPS_FLAG_Q_RANGE is raised there).  A candidate entry outside [0, n_b)
-// scores -inf.
+// scores -inf.  tops [B, Hq, score_stride / 16] (or NULL; all rows of 16-bit and FP8 keys only) receives the largest score of
+// every 16 rows, made finite as the select does.
 hipError_t launch_group_score(const Shape& s, int dtype, const float* q, const KvView& kv, const int32_t* cand,
                               const int32_t* cand_count, float* score, int64_t score_stride, int32_t* flags,
-                              hipStream_t st);
+                              hipStream_t st, float* tops = nullptr);
 
 // Filtered scoring (bf16, fp16 or FP8 keys; the kernel keeps its first name, k_filter_score_bf16): per
 // head only rows with score >= thr_state[b,h] - margin are kept, as
@@ -167,9 +168,12 @@ hipError_t launch_select_attend(const Shape& s, int dtype, const float* score, i
 // thr_state [B,Hq] (or NULL) receives
 // each head's k-th best score.  skip_if [B,Hq] (or NULL): heads whose entry is not 0 are skipped (bypassed heads).
 // seq_lens [B] (or NULL; with cand only): a selected candidate entry outside [0, n_b) is written as -1.
+// tops (or NULL; without cand only): what launch_group_score has left there for these scores.
 hipError_t launch_select(const Shape& s, const float* score, int64_t score_stride, const int32_t* cand,
                          const int32_t* count, const int32_t* k, int32_t* topk_idx, float* topk_score,
-                         float* thr_state, const int32_t* skip_if, const int32_t* seq_lens, hipStream_t st);
+                         float* thr_state, const int32_t* skip_if, const int32_t* seq_lens, hipStream_t st,
+                         const float* tops = nullptr);
+bool select_wants_tops(const Shape& s);   // worth asking launch_group_score for?
 
 // Scores of idx[b,h,0:k_b] rows against q[b,h] (one head at a time, no group sharing).
 hipError_t launch_head_score(const Shape& s, int dtype, const float* q, const KvView& kv, const int32_t* idx,

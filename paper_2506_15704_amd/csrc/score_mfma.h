@@ -5,6 +5,8 @@
 #pragma once
 #include "lfps_internal.h"
 
+#include <float.h>
+
 #include <type_traits>
 
 namespace lfps {
@@ -244,11 +246,14 @@ struct StreamTile {
 // position.  A slot whose position lies outside [0, n) reads row 0 and scores -inf: it ranks below every row.
 // The row ids of the next visit are fetched, and the scores of the previous visit stored, right after this visit's
 // loads are issued.  sc: the score row of head kb (ignored by lanes with store == false).
-template <bool kPaged, int kKind>
+// tops (or NULL): receives the largest score of every 16 slots, as the select orders them (a NaN above all); first and step are
+// multiples of 64 then.
+template <bool kPaged, int kKind, bool kTops = false>
 __device__ __forceinline__ void score_slots_mfma(const typename KTile<kKind>::Operand (&A)[4], const char* Kbg,
                                                  const KvPage& pg, int b, int64_t stride_b, int64_t stride_n,
                                                  const int32_t* __restrict__ cbg, int n, int count, int first, int step,
-                                                 float* __restrict__ sc, bool store, float scale) {
+                                                 float* __restrict__ sc, bool store, float scale,
+                                                 float* __restrict__ tops = nullptr) {
   using Rows = RowMap<kPaged>;
   using Op = typename KTile<kKind>::Operand;
   constexpr int ES = KTile<kKind>::kElemBytes;
@@ -292,6 +297,18 @@ __device__ __forceinline__ void score_slots_mfma(const typename KTile<kKind>::Op
         acc = mfma16(A[kk], Bt.operand(t, kk), acc);
       // lane (j, kb): D rows 4*kb .. 4*kb+3 = the three terms (and a zero row) of head kb, column j
       pv[t] = ok_t[t] ? Split3<Op>::sum(acc) * scale : -INFINITY;
+    }
+    if constexpr (kTops) {
+      if (tops) {
+        float mine = 0.f;                                  // lane j: of the slots 16 j .. 16 j + 15, j < 4
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const float x = base + 16 * t + j < count ? fmaxf(fminf(pv[t], FLT_MAX), -FLT_MAX) + 0.0f : -FLT_MAX;
+          const float top = row16_max(x);
+          mine = j == t ? top : mine;
+        }
+        if (store && j < 4 && base + 16 * j < count) tops[(base >> 4) + j] = mine;
+      }
     }
     pbase = base;
     my_row = next_row;

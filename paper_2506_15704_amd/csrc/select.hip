@@ -16,7 +16,8 @@
 //     equal to it as still needed, lowest position first.  The output is ascending in position
 //     and identical from run to run.
 //
-// Heads of up to kSelRegMax scores are read from memory once and stay in registers (select_regs.h); only when a row of
+// Rows of more than 8192 scores whose scoring pass has left the largest score of every 16 are selected from the few blocks that
+// hold the k best (select_blocks).  Other heads of up to kSelRegMax scores are read from memory once and stay in registers (select_regs.h); only when a row of
 // 16384 to 32768 scores would keep more than the list of select_long holds (budgets of about 16000 and more, crowded
 // bins) is it kept in LDS as a whole, and longer ones are streamed in each pass (L2).  32 heads x 32768 scores, k = 1024:
 // 35 us with the row in LDS, 28 us with select_registers alone (32 elements a thread), 25 us this way (exact Top-k and attention of a 32K request: 57 -> 46 us).
@@ -36,7 +37,8 @@ __global__ __launch_bounds__(kSelThreads) void k_select(Shape s, const float* __
                                                         float* __restrict__ topk_score, int list_cap,
                                                         int cache_elems, float* __restrict__ thr_state,
                                                         const int32_t* __restrict__ skip_if,
-                                                        const int32_t* __restrict__ seq_lens) {
+                                                        const int32_t* __restrict__ seq_lens,
+                                                        const float* __restrict__ tops) {
   constexpr int NT = kSelThreads;
   __shared__ SelectShared<NT> sm;
   extern __shared__ float dyn[];                    // select_long's list, or the scores of a whole row
@@ -97,6 +99,10 @@ __global__ __launch_bounds__(kSelThreads) void k_select(Shape s, const float* __
   }
   bool done = false;
   float2* list = reinterpret_cast<float2*>(dyn);
+  const int n_tops = (c + 15) >> 4;
+  if (tops && ksel <= n_tops && n_tops <= kRegElems * NT)
+    done = select_blocks<NT>(sm, sc, tops + (int64_t)bh * (score_stride >> 4), c, ksel, list, list_cap, thr_out, put);
+  if (done) return;
   if (c <= 16 * NT) done = select_long<NT, 16>(sm, sc, c, ksel, list, list_cap, thr_out, put);
   else if (c <= kSelRegMax) done = select_long<NT, 32>(sm, sc, c, ksel, list, list_cap, thr_out, put);
   if (done) return;
@@ -115,6 +121,12 @@ static void select_room(const Shape& s, bool gather, int* list_cap, int* cache_e
   *list_cap = rows_max <= 8 * kSelThreads ? 0 : kSelListMax;
 }
 
+// Are the largest scores of 16 rows each worth their writing by the scoring pass?  (They save the select most of its work, but
+// where there are many heads the select's workgroups overlap and the writes do not.)  Exact Top-k of all rows, separate scores
+// -> with tops: 1 x 32K 45.8 -> 36.0 us, 1 x 64K 95 -> 55, 4 x 30K 76 -> 68, 2 x 16K 35.1 -> 32.8, 6 x 16K 61.4 -> 59.7; but 8 x 16K
+// (256 heads) 71.3 -> 72.5, 8 x 9000 49.3 -> 49.9, and rows of up to 8192 scores are selected without them.
+bool select_wants_tops(const Shape& s) { return s.Lcap > 16384 || (s.Lcap > 8 * kSelThreads && s.B * s.Hq <= 192); }
+
 // Called once per context at creation: the kernel needs more dynamic LDS than the default limit.
 hipError_t configure_select(const Shape& s, int dtype, bool k_fp8, bool v_fp8) {
   hipError_t e = hipFuncSetAttribute((const void*)k_select, hipFuncAttributeMaxDynamicSharedMemorySize, kSelListMax * 8);
@@ -124,12 +136,13 @@ hipError_t configure_select(const Shape& s, int dtype, bool k_fp8, bool v_fp8) {
 
 hipError_t launch_select(const Shape& s, const float* score, int64_t score_stride, const int32_t* cand,
                          const int32_t* count, const int32_t* k, int32_t* topk_idx, float* topk_score,
-                         float* thr_state, const int32_t* skip_if, const int32_t* seq_lens, hipStream_t st) {
+                         float* thr_state, const int32_t* skip_if, const int32_t* seq_lens, hipStream_t st,
+                         const float* tops) {
   int list_cap, cache_elems;
   select_room(s, cand != nullptr, &list_cap, &cache_elems);
   hipLaunchKernelGGL(k_select, dim3(s.B * s.Hq), dim3(kSelThreads), (size_t)(list_cap * 2 > cache_elems ? list_cap * 2 : cache_elems) * 4,
                      st, s, score, score_stride, cand, count, k, topk_idx, topk_score, list_cap, cache_elems, thr_state,
-                     skip_if, seq_lens);
+                     skip_if, seq_lens, tops);
   return hipGetLastError();
 }
 

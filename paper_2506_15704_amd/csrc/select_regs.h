@@ -165,6 +165,107 @@ __device__ __forceinline__ void select_registers(SelectShared<NT>& sm, const flo
   }
 }
 
+// The select above on kept (score, element) pairs in LDS, ascending in position, all of them >= cut: out(rank, element, score).
+// All threads call, after a barrier behind the list's last entry.
+template <int NT, typename Out>
+__device__ __forceinline__ void select_list(SelectShared<NT>& sm, const float2* list, int kept, int ksel, float cut,
+                                            float* __restrict__ thr_out, Out out) {
+  for (int i = threadIdx.x; i < 2 * NT; i += NT) sm.hist[i] = 0u;
+  if (threadIdx.x == 0) sm.list_n = 0u;
+  __syncthreads();
+  auto finish = [&](auto elems) {
+    constexpr int E2 = decltype(elems)::value;
+    float w[E2];
+    int at[E2];
+#pragma unroll
+    for (int u = 0; u < E2; ++u) {
+      const int e = u * NT + (int)threadIdx.x < kept ? u * NT + (int)threadIdx.x : kept - 1;
+      w[u] = list[e].x;
+      at[u] = __float_as_int(list[e].y);
+    }
+    select_registers<NT, E2>(sm, w, kept, ksel, cut, false, thr_out,
+                             [&](int rank, int u, float) { out(rank, at[u], w[u]); });
+  };
+  if (kept <= 2 * NT) finish(std::integral_constant<int, 2>{});
+  else if (kept <= 4 * NT) finish(std::integral_constant<int, 4>{});
+  else finish(std::integral_constant<int, kRegElems>{});
+}
+
+// The same for a row whose scoring pass has left the largest (sanitised) score of every 16 in tops[0 .. (n + 15) / 16 - 1],
+// at least ksel and at most kRegElems * NT of them.  The ksel best of these, ties to the lower block, tell the blocks
+// that hold the ksel best scores: ksel scores reach the smallest of them, t, so no smaller one is taken; every block with a
+// larger score is among them; and of scores equal to t the first ones are, because the last block chosen for a top equal to
+// t leaves enough of them before it.  What reaches t in those blocks goes to LDS, ascending, and is selected from there.
+// Bound by the latency of one CU; 32 heads x 32768 scores, k = 1024: 15.5 us, 25 with select_long, which handles every score
+// four times.  False if more than cap elements would go to the list: nothing has been written then.  sc: 16-byte aligned, readable up to
+// a multiple of 16.
+template <int NT, typename Out>
+__device__ __forceinline__ bool select_blocks(SelectShared<NT>& sm, const float* __restrict__ sc,
+                                              const float* __restrict__ tops, int n, int ksel, float2* list, int cap,
+                                              float* __restrict__ thr_out, Out out) {
+  constexpr int kWaves = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int nb = (n + 15) >> 4;
+  cap -= (ksel + 1) >> 1;                                  // the chosen blocks lie behind the list
+  uint32_t* blocks = reinterpret_cast<uint32_t*>(list + cap);
+  float* cut_at = &sm.wlo[0];                              // (not used by a select with from_min after its first barrier)
+  for (int i = tid; i < 2 * NT; i += NT) sm.hist[i] = 0u;
+  if (tid == 0) sm.list_n = 0u;
+  __syncthreads();
+  auto choose = [&](auto elems) {
+    constexpr int E = decltype(elems)::value;
+    float v[E];
+#pragma unroll
+    for (int u = 0; u < E; ++u) v[u] = tops[u * NT + tid < nb ? u * NT + tid : nb - 1];
+    select_registers<NT, E>(sm, v, nb, ksel, 0.f, true, cut_at,
+                            [&](int rank, int u, float) { blocks[rank] = (uint32_t)(u * NT + tid); });
+  };
+  if (nb <= 2 * NT) choose(std::integral_constant<int, 2>{});
+  else if (nb <= 4 * NT) choose(std::integral_constant<int, 4>{});
+  else if (nb <= 8 * NT) choose(std::integral_constant<int, 8>{});
+  else choose(std::integral_constant<int, kRegElems>{});
+  __syncthreads();
+  const float cut = *cut_at;
+  int kept = 0;
+#pragma unroll 1
+  for (int r0 = 0; r0 < ksel; r0 += NT) {                  // a block a thread
+    const bool in = r0 + tid < ksel;
+    const int base = in ? (int)blocks[r0 + tid] << 4 : 0;
+    float x[16];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const f32x4 y = reinterpret_cast<const f32x4*>(sc + base)[c];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[4 * c + i] = y[i];
+    }
+    uint32_t take = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      x[i] = sanitize(x[i]);
+      take |= (in && base + i < n && x[i] >= cut ? 1u : 0u) << i;
+    }
+    const int cnt = __popc(take), inc = wave_inclusive_sum(cnt);
+    if (lane == 63) sm.wsum[wv] = (uint32_t)inc;
+    __syncthreads();
+    int at = kept + inc - cnt, total = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const int t = (int)sm.wsum[w];
+      at += w < wv ? t : 0;
+      total += t;
+    }
+    kept += total;
+    if (kept > cap) return false;                          // (the same for the whole workgroup)
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (take >> i & 1u) list[at++] = make_float2(x[i], __int_as_float(base + i));
+    __syncthreads();
+  }
+  if (kept < ksel) return false;                           // (cannot be: tops and scores do not belong together)
+  select_list<NT>(sm, list, kept, ksel, cut, thr_out, out);
+  return true;
+}
+
 // The same for long rows.  One workgroup works on a head, so what counts is instructions per element: here about 30 (the
 // select above: about 120).  The n scores of the head (thread t: elements u*NT + t, from memory) are laid on a histogram
 // linear between the smallest and the largest (bins that follow the distance from a bound would pile the bulk of a full
@@ -251,24 +352,7 @@ __device__ __forceinline__ bool select_long(SelectShared<NT>& sm, const float* _
     if (k) list[at + lanes_below(m)] = make_float2(v[u], __int_as_float(u * NT + tid));
   }
   __syncthreads();
-  for (int i = tid; i < kBins; i += NT) sm.hist[i] = 0u;
-  __syncthreads();
-  auto finish = [&](auto elems) {
-    constexpr int E2 = decltype(elems)::value;
-    float w[E2];
-    int at[E2];
-#pragma unroll
-    for (int u = 0; u < E2; ++u) {
-      const int e = u * NT + tid < kept ? u * NT + tid : kept - 1;
-      w[u] = list[e].x;
-      at[u] = __float_as_int(list[e].y);
-    }
-    select_registers<NT, E2>(sm, w, kept, ksel, cut, false, thr_out,
-                             [&](int rank, int u, float) { out(rank, at[u], w[u]); });
-  };
-  if (kept <= 2 * NT) finish(std::integral_constant<int, 2>{});
-  else if (kept <= 4 * NT) finish(std::integral_constant<int, 4>{});
-  else finish(std::integral_constant<int, kRegElems>{});
+  select_list<NT>(sm, list, kept, ksel, cut, thr_out, out);
   return true;
 }
 
