@@ -68,8 +68,10 @@ __device__ __forceinline__ bool stage_hist_operands(Op* lds, const float* __rest
         }
       }
     }
+    Op term[3];
+    Split3<Op>::all(f, term);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) e[t] = Split3<Op>::terms(f, h < G ? t : 3);
+    for (int t = 0; t < 4; ++t) e[t] = h < G && t < 3 ? term[t < 3 ? t : 0] : Op{};
   }
   return clipped;
 }
