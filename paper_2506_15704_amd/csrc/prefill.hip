@@ -46,6 +46,8 @@ __device__ __forceinline__ float exp_scaled(float y) {
   return fmaf(e * ln2, r, e);
 }
 
+__host__ __device__ constexpr int hist_lds(int nq) { return nq * 4 * 64 * 16; }   // bytes of the operands of nq queries
+
 // MFMA A operands (layout of load_query_operand) of nq queries for the heads of group (b, g), to LDS:
 // entry (jq * 4 + kk) * 64 + lane.  A thread makes the three terms (and the zero row) of 8 channels of one head.
 // Returns true if it met an element beyond the fp16 range.
@@ -97,6 +99,25 @@ struct HistTile {
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) x[t][kk] = raw[t].operand(kk);
   }
+  // the same past the caches; turn: StreamTile's piece of LDS of this wave
+  __device__ __forceinline__ void load_once(const char* Kbg, const KvPage& pg, int b, int64_t stride_b, int64_t stride_n,
+                                            int base, int n, int lane, u32x4* turn) {
+    using Rows = RowMap<kPaged>;
+    static_assert(NT % 4 == 0, "whole stream tiles");
+    StreamTile<kKind> raw[NT / 4];
+#pragma unroll
+    for (int u = 0; u < NT / 4; ++u) {
+      const int row = base + kRowsPerWaveIter * u + lane;
+      raw[u].fetch(Kbg, Rows::phys(pg, b, row < n ? row : n - 1), lane,
+                   [&](int p) { return Rows::offset(pg, p, stride_b, stride_n) * KSub<kKind>::kElemBytes; });
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const KSub<kKind> sub = raw[t / 4].sub(t % 4, turn, lane);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) x[t][kk] = sub.operand(kk);
+    }
+  }
   // v[t] = q . K (not yet divided by sqrt(D)) of my row of sub-tile t for head kb and the query whose operands start at a
   __device__ __forceinline__ void dots(const Op* a, int lane, float (&v)[NT]) const {
     Op A[4];
@@ -123,7 +144,8 @@ __device__ __forceinline__ void wave_run(int tiles, int w, int waves, int& lo, i
 // [n_sink, n - j + 1).  part_m / part_l [bg, block, jq, h]: the largest q . K and the sum of the exponentials relative
 // to it over the rows of the block (kLeastMax and 0 when it has none).  dots (or NULL; one query only): every q . K,
 // [B, Hq, stride].
-template <int G, bool kPaged, int kKind>
+// kOnce: rows past the caches (StreamTile; its LDS lies behind the operands), see stats_once.
+template <int G, bool kPaged, int kKind, bool kOnce>
 __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
     Shape s, const float* __restrict__ q0, int64_t q_stride, int j0, int nq, const void* __restrict__ K,
     int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage pg, const int32_t* __restrict__ seq_lens,
@@ -153,7 +175,11 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
   for (int tile = lo; tile < hi; ++tile) {
     const int base = tile * kHistRows;
     Tile T;
-    T.load(Kbg, pg, b, stride_b, stride_n, base, n, j, kb);
+    if constexpr (kOnce)
+      T.load_once(Kbg, pg, b, stride_b, stride_n, base, n, lane,
+                  reinterpret_cast<u32x4*>(lds_raw + hist_lds(nq)) + wave * StreamTile<kKind>::kLdsChunks);
+    else
+      T.load(Kbg, pg, b, stride_b, stride_n, base, n, j, kb);
     // a tile of which every query sees every row needs no masks (wave-uniform)
     const bool whole = base >= s.n_sink && base + kHistRows <= n - (j0 + nq - 1) + 1;
     auto walk = [&](auto masked) {
@@ -715,7 +741,14 @@ int64_t table_init_scratch_bytes(const Shape& s) {
   return stats + moments;
 }
 
-static int hist_lds(int nq) { return nq * 4 * 64 * 16; }
+// K larger than the memory-side cache and few queries: the pass is bound by the bytes of K then.  One query, 64 groups x 32K rows
+// (537 MB): 119 -> 96 us.  Tables and one step, before -> now: 40 groups x 32K rows, 1 query 166 -> 148 us, 4 queries 264 -> 246,
+// 8 queries 275 -> 263; 96 groups x 40K rows, 4 queries 598 -> 558, in paged FP8 435 -> 420 (1 query 271 -> 269).  With 32
+// queries the matrix units bound the pass, and their operands leave no LDS for this form.
+constexpr int kOnceQueries = 8;
+static bool stats_once(const Shape& s, int nq, int elem_bytes) {
+  return nq <= kOnceQueries && (int64_t)s.B * s.Hkv * s.Lcap * kD * elem_bytes > kKeptBytes;
+}
 
 // Called once per context in table mode: the operands of 32 queries need more dynamic LDS than the default limit.
 hipError_t configure_table_history(const Shape& s, int k_kind) {
@@ -725,8 +758,10 @@ hipError_t configure_table_history(const Shape& s, int k_kind) {
   };
 #define LFPS_RAISE_HIST(GG, KIND)                                     \
   if (s.G == GG && k_kind == KIND) {                                  \
-    raise((const void*)k_hist_stats<GG, false, KIND>);                \
-    raise((const void*)k_hist_stats<GG, true, KIND>);                 \
+    raise((const void*)k_hist_stats<GG, false, KIND, false>);         \
+    raise((const void*)k_hist_stats<GG, true, KIND, false>);          \
+    raise((const void*)k_hist_stats<GG, false, KIND, true>);          \
+    raise((const void*)k_hist_stats<GG, true, KIND, true>);           \
     raise((const void*)k_hist_apply<GG, false, KIND>);                \
     raise((const void*)k_hist_apply<GG, true, KIND>);                 \
   }
@@ -749,9 +784,15 @@ static hipError_t launch_hist_t(const Shape& s, float* tab_ver, float* tab_sla, 
   float* part_m = reinterpret_cast<float*>(part_l + (int64_t)s.B * s.Hkv * bpg * kHistBatch * G);
   const dim3 grid(bpg, s.B * s.Hkv), block(kHistWaves * 64);
   const bool one = n_queries == 1;
-  hipLaunchKernelGGL((k_hist_stats<G, kPaged, kKind>), grid, block, hist_lds(nq), st, s, q0, q_stride, j0, nq, kv.k,
-                     kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, part_m, part_l,
-                     one ? dots : nullptr, dots_stride, flags);
+  constexpr int kTurns = kHistWaves * StreamTile<kKind>::kLdsChunks * 16;
+  static_assert(hist_lds(kOnceQueries) + kTurns <= hist_lds(kHistBatch), "the kernels' limit of dynamic LDS");
+#define LFPS_STATS(ONCE, LDS)                                                                                          \
+  hipLaunchKernelGGL((k_hist_stats<G, kPaged, kKind, ONCE>), grid, block, LDS, st, s, q0, q_stride, j0, nq, kv.k,      \
+                     kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, part_m, part_l, one ? dots : nullptr, \
+                     dots_stride, flags)
+  if (stats_once(s, nq, KSub<kKind>::kElemBytes)) LFPS_STATS(true, hist_lds(nq) + kTurns);
+  else LFPS_STATS(false, hist_lds(nq));
+#undef LFPS_STATS
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (one)

@@ -60,3 +60,43 @@ def test_streamed_scoring_equals_the_unfiltered_kernels(dtype, page, B, L, Hq, H
     assert ctxs[0].lfps_poll_rescored() == 0                      # the filtered passes decided, not their fall-back
     for ctx in ctxs:
         ctx.close()
+
+
+# one query (stored dot products) and the most that are read past the caches, one more; against each request on its own, whose
+# keys fit the cache: other sums of the exponentials, so entries agree to the 2e-5 of a table entry, not bit for bit
+@pytest.mark.parametrize("dtype,page,B,L,Hq,Hkv,s", [
+    ("bf16", 0, 5, 35007, 32, 8, 1), ("bf16", 16, 3, 70001, 16, 8, 4), ("f16", 64, 5, 33331, 8, 8, 8),
+    ("fp8", 0, 8, 33007, 32, 8, 1), ("fp8", 16, 8, 33011, 16, 8, 3), ("bf16", 0, 4, 33007, 32, 8, 9)])
+def test_tables_from_streamed_keys(dtype, page, B, L, Hq, Hkv, s):
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L + s)
+    kd = {"bf16": torch.bfloat16, "f16": torch.float16, "fp8": torch.float8_e4m3fn}[dtype]
+    Lcap = L + 3
+    nb = -(-Lcap // page) if page else 1
+    shape = (B * nb, Hkv, page, 128) if page else (B, Hkv, Lcap, 128)
+    K = torch.empty(shape, dtype=kd, device=DEV)
+    for i in range(0, shape[0], nb):
+        K[i:i + nb] = torch.randn(K[i:i + nb].shape, device=DEV, generator=g).to(kd)
+    V = torch.zeros(shape, dtype=torch.float16 if dtype == "f16" else torch.bfloat16, device=DEV)
+    assert B * Hkv * Lcap * 128 * K.element_size() > 256 << 20
+    table = torch.randperm(B * nb, device=DEV, generator=g).view(B, nb).to(torch.int32)
+    seq = torch.tensor([L - 127 * b for b in range(B)], dtype=torch.int32, device=DEV)
+    q = 2 * torch.randn((s, B, Hq, 128), device=DEV, generator=g)
+
+    def tables(lo, hi):
+        ctx = Lfps(batch=hi - lo, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="f16" if dtype == "f16" else "bf16",
+                   max_seq_len=Lcap, max_k=64, radius=1, k_fp8=dtype == "fp8", table_mode=True, table_decay=0.95, n_sink=4)
+        n = seq[lo:hi].contiguous()
+        kv = ctx.paged_kv_view(K, V, table[lo:hi].contiguous(), n) if page else ctx.kv_view(K[lo:hi], V[lo:hi], n)
+        ctx.lfps_tables_init(q[:, lo:hi].contiguous(), kv)
+        out = [torch.zeros((hi - lo, Hq, Lcap), dtype=torch.float64, device=DEV) for _ in range(2)]
+        ctx.lfps_tables_export(*out, n)
+        ctx.close()
+        return out
+
+    whole = tables(0, B)
+    for b in range(B):
+        for got, want in zip(whole, tables(b, b + 1)):
+            assert float(want.abs().max()) > 0
+            torch.testing.assert_close(got[b:b + 1], want, rtol=2e-5, atol=1e-12)
