@@ -697,7 +697,7 @@ int lfps_exact_topk(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int3
   }
   float* tops = select_wants_tops(s) ? (float*)ctx->slot : nullptr;   // (scratch here; NULL for fp32 keys)
   LAUNCH(ctx, LFPS_KERNEL_DENSE_SCORE, st,
-         launch_group_score(s, ctx->cfg.kv_dtype, q, v, nullptr, nullptr, ctx->score, s.score_stride, ctx->flags, st, tops));
+         launch_group_score(s, ctx->cfg.kv_dtype, q, v, nullptr, nullptr, ctx->score, s.score_stride, ctx->flags, st, tops, k));
   LAUNCH(ctx, LFPS_KERNEL_SELECT, st,
          launch_select(s, ctx->score, s.score_stride, nullptr, v.seq_lens, k, topk_idx, topk_score, nullptr, nullptr,
                        nullptr, st, tops));

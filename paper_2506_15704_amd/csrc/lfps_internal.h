@@ -86,10 +86,10 @@ hipError_t launch_candidates(const Shape& s, const int32_t* prev_topk, const int
 // of each KV group.  score is [B, Hq, score_stride].
 // flags: the context's status word (LFPS_FLAG_Q_RANGE is raised there).  A candidate entry outside [0, n_b)
 // scores -inf.  tops [B, Hq, score_stride / 16] (or NULL; all rows of 16-bit and FP8 keys only) receives the largest score of
-// every 16 rows, made finite as the select does.
+// every 16 rows, made finite as the select does, of the requests whose select reads them (k: its budgets; select_takes_tops).
 hipError_t launch_group_score(const Shape& s, int dtype, const float* q, const KvView& kv, const int32_t* cand,
                               const int32_t* cand_count, float* score, int64_t score_stride, int32_t* flags,
-                              hipStream_t st, float* tops = nullptr);
+                              hipStream_t st, float* tops = nullptr, const int32_t* k = nullptr);
 
 // Filtered scoring (bf16, fp16 or FP8 keys; the kernel keeps its first name, k_filter_score_bf16): per
 // head only rows with score >= thr_state[b,h] - margin are kept, as
@@ -174,6 +174,24 @@ hipError_t launch_select(const Shape& s, const float* score, int64_t score_strid
                          float* thr_state, const int32_t* skip_if, const int32_t* seq_lens, hipStream_t st,
                          const float* tops = nullptr);
 bool select_wants_tops(const Shape& s);   // worth asking launch_group_score for?
+
+// Is the select of n scores and a budget of kb made from the largest scores of 16 rows each?  Asked by the pass that writes
+// them and by the select.  The select reads the blocks of the budget's best maxima, and what passes the cut has to fit its list
+// beside the blocks' numbers: of independent scores 1 - (1 - p)^(1/16) pass, p the share of blocks chosen.  The line is the p at
+// which the list is full up to five standard deviations; below 32769 rows, where the select from all scores is faster, that at
+// which 4096 pass (a longer list makes the last step twice as long); never more than 31/32, where nearly all of the row passes.
+// Exact Top-k of 32 heads, from all scores -> from the blocks, us: 9000 rows, p = 7/8 19.6 -> 19.1, 1 19.8 -> 29.9; 32768 rows, 1/2
+// 38.1 -> 27.4, 27/32 38.3 -> 32.1, 7/8 38.4 -> 38.9, 1 39.6 -> 47.3; 65536 rows, 15/16 84.3 -> 61.3, 1 84 -> 100; 120000 rows, 3/4
+// 148.7 -> 90.3, 7/8 (the list overflows) 148.9 -> 176.3.
+constexpr int kTopsMinRows = 8192, kTopsMaxRows = 262144;
+__host__ __device__ inline bool select_takes_tops(const Shape& s, int n, int kb) {
+  kb = kb > s.kmax ? s.kmax : kb;
+  kb = kb > n ? n : kb;
+  const int share = n <= 19712 ? 124 : n <= 32768 ? 124 - (n - 19712) / 932                        // in 128ths
+                    : n <= 65536 ? 124 : n <= 147456 ? 124 - (n - 65536) / 2926
+                    : n <= 200704 ? 96 - (n - 147456) / 3132 : 79 - (n - 200704) / 4389;
+  return n > kTopsMinRows && n <= kTopsMaxRows && 128 * kb <= share * ((n + 15) >> 4);
+}
 
 // Scores of idx[b,h,0:k_b] rows against q[b,h] (one head at a time, no group sharing).
 hipError_t launch_head_score(const Shape& s, int dtype, const float* q, const KvView& kv, const int32_t* idx,

@@ -39,7 +39,8 @@ __global__ __launch_bounds__(kScoreThreads) void k_group_score_bf16(Shape s, con
                                                                     const int32_t* __restrict__ cand_count,
                                                                     float* __restrict__ score, int64_t score_stride,
                                                                     float scale, int32_t* __restrict__ flags,
-                                                                    float* __restrict__ tops) {
+                                                                    float* __restrict__ tops,
+                                                                    const int32_t* __restrict__ kk) {
   const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j = lane & 15, kb = lane >> 4;
@@ -61,7 +62,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_group_score_bf16(Shape s, con
   float* sc = score + ((int64_t)b * s.Hq + (int64_t)g * G + kb) * score_stride;   // lane group kb -> head kb
   float* my_tops = nullptr;
   if constexpr (!GATHER) {
-    if (tops) my_tops = tops + ((int64_t)b * s.Hq + (int64_t)g * G + kb) * (score_stride >> 4);
+    if (tops && select_takes_tops(s, n, kk[b])) my_tops = tops + ((int64_t)b * s.Hq + (int64_t)g * G + kb) * (score_stride >> 4);
   }
   score_slots_mfma<kPaged, kKind, !GATHER>(A, Kbg, pg, b, stride_b, stride_n, cbg, n, count, first,
                                            (int)gridDim.x * 4 * kRowsPerWaveIter, sc, kb < G, scale, my_tops);
@@ -393,7 +394,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_group_score_f32(Shape s, cons
                                                                    const int32_t* __restrict__ cand,
                                                                    const int32_t* __restrict__ cand_count,
                                                                    float* __restrict__ score, int64_t score_stride,
-                                                                   float scale, int32_t* __restrict__ flags, float*) {
+                                                                   float scale, int32_t* __restrict__ flags, float*, const int32_t*) {
   const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j = lane & 15, rs = lane >> 4;     // 16 lanes per row, 4 rows per wave instruction
@@ -507,7 +508,7 @@ __global__ __launch_bounds__(256) void k_head_score(Shape s, const float* __rest
 template <int G, bool GATHER>
 static hipError_t launch_gs(const Shape& s, int dtype, const float* q, const KvView& kv, const int32_t* cand,
                             const int32_t* cand_count, float* score, int64_t score_stride, int32_t* flags,
-                            hipStream_t st, float* tops) {
+                            hipStream_t st, float* tops, const int32_t* k) {
   const int rows_max = GATHER ? s.cand_cap : s.Lcap;
   const int per_block = 4 * (dtype == LFPS_F32 ? kRowsPerWaveF32 : kRowsPerWaveIter);
   int tiles = (rows_max + per_block - 1) / per_block;
@@ -521,7 +522,7 @@ static hipError_t launch_gs(const Shape& s, int dtype, const float* q, const KvV
 #define LFPS_LAUNCH_GS(KERNEL, TYPE, ...)                                                                          \
   hipLaunchKernelGGL((KERNEL<G, GATHER, __VA_ARGS__>), grid, block, 0, st, s, q, (const TYPE*)kv.k, kv.stride_b,   \
                      kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, cand, cand_count, score, score_stride, scale, \
-                     flags, tops)
+                     flags, tops, k)
   const bool paged = kv.page.table != nullptr;
   if (dtype == LFPS_BF16 && kv.k_fp8) {
     if (paged) LFPS_LAUNCH_GS(k_group_score_bf16, void, true, kKindFp8);
@@ -542,15 +543,15 @@ static hipError_t launch_gs(const Shape& s, int dtype, const float* q, const KvV
 
 hipError_t launch_group_score(const Shape& s, int dtype, const float* q, const KvView& kv, const int32_t* cand,
                               const int32_t* cand_count, float* score, int64_t score_stride, int32_t* flags,
-                              hipStream_t st, float* tops) {
+                              hipStream_t st, float* tops, const int32_t* k) {
   const bool gather = cand != nullptr;
   switch (s.G) {
-    case 1: return gather ? launch_gs<1, true>(s, dtype, q, kv, cand, cand_count, score, score_stride, flags, st, tops)
-                          : launch_gs<1, false>(s, dtype, q, kv, cand, cand_count, score, score_stride, flags, st, tops);
-    case 2: return gather ? launch_gs<2, true>(s, dtype, q, kv, cand, cand_count, score, score_stride, flags, st, tops)
-                          : launch_gs<2, false>(s, dtype, q, kv, cand, cand_count, score, score_stride, flags, st, tops);
-    case 4: return gather ? launch_gs<4, true>(s, dtype, q, kv, cand, cand_count, score, score_stride, flags, st, tops)
-                          : launch_gs<4, false>(s, dtype, q, kv, cand, cand_count, score, score_stride, flags, st, tops);
+    case 1: return gather ? launch_gs<1, true>(s, dtype, q, kv, cand, cand_count, score, score_stride, flags, st, tops, k)
+                          : launch_gs<1, false>(s, dtype, q, kv, cand, cand_count, score, score_stride, flags, st, tops, k);
+    case 2: return gather ? launch_gs<2, true>(s, dtype, q, kv, cand, cand_count, score, score_stride, flags, st, tops, k)
+                          : launch_gs<2, false>(s, dtype, q, kv, cand, cand_count, score, score_stride, flags, st, tops, k);
+    case 4: return gather ? launch_gs<4, true>(s, dtype, q, kv, cand, cand_count, score, score_stride, flags, st, tops, k)
+                          : launch_gs<4, false>(s, dtype, q, kv, cand, cand_count, score, score_stride, flags, st, tops, k);
     default: return hipErrorInvalidValue;
   }
 }

@@ -99,8 +99,8 @@ __global__ __launch_bounds__(kSelThreads) void k_select(Shape s, const float* __
   }
   bool done = false;
   float2* list = reinterpret_cast<float2*>(dyn);
-  const int n_tops = (c + 15) >> 4;
-  if (tops && ksel <= n_tops && n_tops <= kRegElems * NT)
+  static_assert(kTopsMinRows == 8 * NT && kTopsMaxRows == 16 * kRegElems * NT, "rows that select_blocks takes");
+  if (tops && select_takes_tops(s, c, kb))
     done = select_blocks<NT>(sm, sc, tops + (int64_t)bh * (score_stride >> 4), c, ksel, list, list_cap, thr_out, put);
   if (done) return;
   if (c <= 16 * NT) done = select_long<NT, 16>(sm, sc, c, ksel, list, list_cap, thr_out, put);

@@ -1,0 +1,44 @@
+"""Where a rule of a dispatch lies: a call on one side of the line costs no more than its neighbour on the other side.  Times are
+the smallest of several, both sides in turn."""
+import pytest
+import torch
+
+from tests.harness import DEV
+
+pytestmark = pytest.mark.gpu
+
+
+def least_us(*calls, rounds=12, each=20):
+    """The smallest time of a call, of each of the calls, in microseconds."""
+    least = [float("inf")] * len(calls)
+    begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    for call in calls:
+        call()
+    for _ in range(rounds):
+        for i, call in enumerate(calls):
+            begin.record()
+            for _ in range(each):
+                call()
+            end.record()
+            end.synchronize()
+            least[i] = min(least[i], 1e3 * begin.elapsed_time(end) / each)
+    return least
+
+
+# budgets of nine tenths of a row's blocks of 16 and of all of them (nearly all of the row would be read through its blocks: 1.2 to
+# 1.5 times the time of the select from all scores), and one whose blocks hold more than the select's list
+@pytest.mark.parametrize("L,budgets,from_all", [(9000, [506, 563], 564), (20000, [1120, 1250], 1251), (32768, [1835, 2048], 2049),
+                                                (120000, [6562, 7500], 7501)])
+def test_exact_topk_from_blocks_is_no_slower_than_from_all_scores(L, budgets, from_all):
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    K = torch.randn((1, 8, L, 128), device=DEV, generator=g).to(torch.bfloat16)
+    q = torch.randn((1, 32, 128), device=DEV, generator=g)
+    ctx = Lfps(batch=1, max_seq_len=L, max_k=from_all, radius=1)
+    kv = ctx.kv_view(K, K, torch.tensor([L], dtype=torch.int32, device=DEV))
+    idx = torch.zeros((1, 32, from_all), dtype=torch.int32, device=DEV)
+    ks = [torch.tensor([k], dtype=torch.int32, device=DEV) for k in [from_all] + budgets]
+    want, *got = least_us(*[lambda k=k: ctx.lfps_exact_topk(q, kv, k, idx) for k in ks])
+    assert max(got) <= 1.1 * want, (want, got)
+    ctx.close()

@@ -8,10 +8,12 @@ from tests.harness import DEV
 pytestmark = pytest.mark.gpu
 
 
-# one block more than 512; budgets of all blocks (the next one takes the other path); a thread with several blocks; rows past a
-# multiple of 16 and of 64; 2, 4, 8 and 16 blocks per thread of the choice, and more than that
+# one block more than 512; the largest budgets that are selected from blocks and the next ones (select_takes_tops); a thread with
+# several blocks; rows past a multiple of 16 and of 64; 2, 4, 8 and 16 blocks per thread of the choice, and more than that
 @pytest.mark.parametrize("L,k", [(8193, 1), (8193, 513), (8193, 514), (8207, 300), (32768, 1024), (32769, 2047), (65537, 4097),
-                                 (131073, 1500), (262144, 100), (262145, 100)])
+                                 (131073, 1500), (262144, 100), (262145, 100), (8193, 496), (8193, 497), (32768, 1760),
+                                 (32768, 1761), (32769, 1984), (32769, 1985), (131073, 6528), (131073, 6529), (262144, 8448),
+                                 (262144, 8449)])
 @pytest.mark.parametrize("values", ["normal", "ties", "equal", "runs", "special"])
 def test_select_from_block_maxima(L, k, values):
     from paper_2506_15704_amd.binding import Lfps
