@@ -8,8 +8,8 @@
 // independent row loads in flight per wave; the partial sums meet in LDS and the output row is
 // written once (no partials in global memory, no second kernel).
 //
-// Full: split-K over contiguous row ranges with the G heads of a group sharing every K and V
-// row; running (max, sum, acc) per lane group, merged with the online-softmax rule.
+// Full: split-K over contiguous row ranges with the G heads of a group sharing every K and V row; a wave keeps the running
+// (max, sum, acc) of its heads, without grouping a lane group of 16 that of its rows, merged with the online-softmax rule.
 #include "attend.h"
 
 namespace lfps {
@@ -97,32 +97,53 @@ __device__ __forceinline__ float exp_weight(float x) {
   return fmaf(e * ln2, r, e);
 }
 
-// The sums over the 16 lanes of a row of lanes of a[0 .. G-1], G = 1, 2 or 4: lane j receives that of a[j % G].  (A butterfly
+// The weight of a partial result whose largest score lies x <= 0 from the largest of all.  Without grouping the scores are held as
+// powers of two (k_full_attn_single).
+template <int G>
+__device__ __forceinline__ float part_weight(float x) { return G == 1 ? __builtin_amdgcn_exp2f(x) : exp_weight(x); }
+
+// The four waves of a workgroup (a wave without rows: m = -inf, weight 0) -> po [G, D+2]: acc[D], m, l.  All threads call, after a
+// barrier.
+template <int G>
+__device__ __forceinline__ void merge_waves(const float (&red_acc)[4][G][kD], const float (&red_m)[4][G],
+                                            const float (&red_l)[4][G], float* __restrict__ po) {
+  for (int e = threadIdx.x; e < G * kD; e += kAttnThreads) {
+    const int h = e / kD, c = e % kD;
+    const float mx = fmaxf(fmaxf(red_m[0][h], red_m[1][h]), fmaxf(red_m[2][h], red_m[3][h]));
+    float a = 0.f, ls = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float f = (red_m[w][h] == -INFINITY) ? 0.f : part_weight<G>(red_m[w][h] - mx);
+      a = fmaf(red_acc[w][h][c], f, a);
+      ls = fmaf(red_l[w][h], f, ls);
+    }
+    po[h * (kD + 2) + c] = a;
+    if (c == 0) {
+      po[h * (kD + 2) + kD] = mx;
+      po[h * (kD + 2) + kD + 1] = ls;
+    }
+  }
+}
+
+// The sums over the 16 lanes of a row of lanes of a[0 .. G-1], G = 2 or 4: lane j receives that of a[j % G].  (A butterfly
 // over lane distances 1, 2, 4, 8 in which the first log2 G steps also share the G sums out: 11 instructions instead of 16.)
 template <int G>
 __device__ __forceinline__ float row16_shared_sums(float (&a)[G], int j) {
 #define LFPS_DPP(v, ctrl) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, false))
-  float x;
-  if constexpr (G == 1) {
-    x = a[0];
-    x += LFPS_DPP(x, 0xB1);                                  // quad_perm 1 0 3 2
+  const bool odd = j & 1;
+  float x, y[G / 2];
+#pragma unroll
+  for (int h = 0; h < G / 2; ++h) {
+    const float keep = odd ? a[2 * h + 1] : a[2 * h], give = odd ? a[2 * h] : a[2 * h + 1];
+    y[h] = keep + LFPS_DPP(give, 0xB1);                      // quad_perm 1 0 3 2
+  }
+  if constexpr (G == 2) {
+    x = y[0];
     x += LFPS_DPP(x, 0x4E);                                  // quad_perm 2 3 0 1
   } else {
-    const bool odd = j & 1;
-    float y[G / 2];
-#pragma unroll
-    for (int h = 0; h < G / 2; ++h) {
-      const float keep = odd ? a[2 * h + 1] : a[2 * h], give = odd ? a[2 * h] : a[2 * h + 1];
-      y[h] = keep + LFPS_DPP(give, 0xB1);
-    }
-    if constexpr (G == 2) {
-      x = y[0];
-      x += LFPS_DPP(x, 0x4E);
-    } else {
-      const bool upper = j & 2;
-      const float keep = upper ? y[1] : y[0], give = upper ? y[0] : y[1];
-      x = keep + LFPS_DPP(give, 0x4E);
-    }
+    const bool upper = j & 2;
+    const float keep = upper ? y[1] : y[0], give = upper ? y[0] : y[1];
+    x = keep + LFPS_DPP(give, 0x4E);
   }
   // (lanes j and j ^ 4, then j ^ 8, by rotation: every lane of a quad holds another sum)
   x += LFPS_DPP(x, 0x124);                                   // row_ror:4: with the next one, the pairs' sums agree
@@ -131,7 +152,7 @@ __device__ __forceinline__ float row16_shared_sums(float (&a)[G], int j) {
 #undef LFPS_DPP
 }
 
-// grid (n_split, B*Hkv); part [B*Hkv, n_split, G, D+2]: acc[D], m, l
+// G = 2 or 4.  grid (n_split, B*Hkv); part [B*Hkv, n_split, G, D+2]: acc[D], m, l
 //
 // A wave takes U groups of four rows at a time, 16 lanes a row, 8 channels a lane, for K and for V.  The G sums of a row are
 // shared out over its lanes, so that a lane makes the softmax step for one head and its own rows only, once per tile; the
@@ -149,7 +170,7 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
                                                             int64_t stride_b, int64_t stride_h, int64_t stride_n,
                                                             KvPage pg, const int32_t* __restrict__ seq_lens,
                                                             float* __restrict__ part, int n_split, float scale) {
-  constexpr int U = sizeof(TK) == 4 && G > 1 ? 4 : 8, kRows = 4 * U;
+  constexpr int U = sizeof(TK) == 4 ? 4 : 8, kRows = 4 * U;
   constexpr int kShare = 16 / G;                            // lanes of a row that hold the same head's sum
   constexpr int NV = U > kShare ? U / kShare : 1;           // (row, head) pairs of a lane
   __shared__ float red_acc[4][G][kD];
@@ -243,8 +264,7 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
 #define LFPS_ROT(x, n) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + (n), 0xf, 0xf, false))
     mx = fmaxf(mx, LFPS_ROT(mx, 8));
     mx = fmaxf(mx, LFPS_ROT(mx, 4));
-    if constexpr (G <= 2) mx = fmaxf(mx, LFPS_ROT(mx, 2));
-    if constexpr (G == 1) mx = fmaxf(mx, LFPS_ROT(mx, 1));
+    if constexpr (G == 2) mx = fmaxf(mx, LFPS_ROT(mx, 2));
 #undef LFPS_ROT
     mx = fmaxf(mx, __shfl_xor(mx, 16));
     mx = fmaxf(mx, __shfl_xor(mx, 32));
@@ -304,23 +324,151 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
     }
   }
   __syncthreads();
-  float* po = part + ((int64_t)bg * n_split + split) * G * (kD + 2);
-  for (int e = tid; e < G * kD; e += kAttnThreads) {
-    const int h = e / kD, c = e % kD;
-    const float mx = fmaxf(fmaxf(red_m[0][h], red_m[1][h]), fmaxf(red_m[2][h], red_m[3][h]));
-    float a = 0.f, ls = 0.f;
+  merge_waves<G>(red_acc, red_m, red_l, part + ((int64_t)bg * n_split + split) * G * (kD + 2));
+}
+
+// The same without grouping (G = 1), where nothing is to be shared out: the four rows that a wave instruction covers keep a state
+// of their own (largest score, sum, values) until the end, so a tile needs no step across its rows.  A wave takes 16 rows at a
+// time, two tiles in flight.  Every lane of a row makes its exponentials: scores are kept in units of ln 2 (the query is multiplied
+// by log2(e) / sqrt(D), rounded once), so that an exponential needs no product whose rounding would have to be corrected.  In
+// k_full_attn's form the few tiles of a short row waited longer for each other: 1 x 8192 rows of 8 heads in bf16 10.9 -> 9.85 us,
+// in FP8 10.6 -> 9.7, 1 x 16384 in fp32 29.4 -> 28.6, 1 x 32768 in FP8 21.2 -> 19.7; 32 x 30000 in bf16 571 -> 567.
+template <typename TK, typename T, bool kPaged, bool kOnce>
+__global__ __launch_bounds__(kAttnThreads) void k_full_attn_single(Shape s, const float* __restrict__ q,
+                                                                   const TK* __restrict__ K, const T* __restrict__ V,
+                                                                   int64_t stride_b, int64_t stride_h, int64_t stride_n,
+                                                                   KvPage pg, const int32_t* __restrict__ seq_lens,
+                                                                   float* __restrict__ part, int n_split, float) {
+  constexpr double kLog2Scale = 0.08838834764831845 * 1.4426950408889634;
+  constexpr float kHi = (float)kLog2Scale, kLo = (float)(kLog2Scale - (double)kHi);
+  constexpr int U = 4, kRows = 4 * U;
+  __shared__ float red_acc[4][1][kD];
+  __shared__ float red_m[4][1], red_l[4][1];
+  const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv, split = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = lane & 15, rs = lane >> 4;
+  int n = seq_lens[b];
+  n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
+  const int rps = rows_per_split(n, n_split);
+  const int r_begin = split * rps;
+  const int r_end = (r_begin + rps < n) ? r_begin + rps : n;
+  if (r_begin >= n) return;
+
+  float qr[8];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const float f = (red_m[w][h] == -INFINITY) ? 0.f : exp_weight(red_m[w][h] - mx);
-      a = fmaf(red_acc[w][h][c], f, a);
-      ls = fmaf(red_l[w][h], f, ls);
+  for (int c = 0; c < 8; ++c) {
+    const float x = q[(int64_t)bg * kD + 8 * j + c];
+    qr[c] = fmaf(x, kHi, x * kLo);
+  }
+  using Rows = RowMap<kPaged>;
+  const TK* Kbg = K + Rows::base(b, g, stride_b, stride_h) + 8 * j;
+  const T* Vbg = V + Rows::base(b, g, stride_b, stride_h) + 8 * j;
+
+  // Rows past the end are read from the last row and weigh nothing, so no load sits behind a branch.
+  struct Tile {
+    Raw8<TK> k[U];                                          // my channels of row 4 u + rs
+    Raw8<T> v[U];
+  };
+  auto clamped = [&](int r) { return r < r_end ? r : r_end - 1; };
+  // paged: row r0 + j of a tile as a physical row
+  auto rows_of = [&](int r0) { return kPaged ? Rows::phys(pg, b, clamped(r0 + j)) : 0; };
+  auto issue = [&](Tile& t, int r0, int phys) {
+    int64_t off[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int p = kPaged ? __builtin_amdgcn_ds_bpermute(4 * rs + 16 * u, phys) : clamped(r0 + 4 * u + rs);
+      off[u] = Rows::offset(pg, p, stride_b, stride_n);
     }
-    po[h * (kD + 2) + c] = a;
-    if (c == 0) {
-      po[h * (kD + 2) + kD] = mx;
-      po[h * (kD + 2) + kD + 1] = ls;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if constexpr (kOnce) t.k[u].load_once(Kbg + off[u]);
+      else t.k[u].load(Kbg + off[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if constexpr (kOnce) t.v[u].load_once(Vbg + off[u]);
+      else t.v[u].load(Vbg + off[u]);
+    }
+    __builtin_amdgcn_sched_barrier(0);                      // (moved down to their uses, the loads of one tile would wait for the other's)
+  };
+  float m = -INFINITY, l = 0.f, acc[8];                     // of the rows rs mod 4
+#pragma unroll
+  for (int c = 0; c < 8; ++c) acc[c] = 0.f;
+  auto consume = [&](const Tile& t, int r0) {
+    float sc[U], p[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float x[8];
+      t.k[u].get(x);
+      float a = qr[0] * x[0];
+#pragma unroll
+      for (int c = 1; c < 8; ++c) a = fmaf(qr[c], x[c], a);
+      sc[u] = row16_butterfly_sum(a);
+    }
+    float mx = m;
+#pragma unroll
+    for (int u = 0; u < U; ++u) mx = r0 + 4 * u + rs < r_end ? fmaxf(mx, sc[u]) : mx;
+    const float from = mx == -INFINITY ? 0.f : mx;          // (no row yet, or only scores of -inf: they weigh 0)
+    const float alpha = __builtin_amdgcn_exp2f(m - from);   // (0 on the first tile)
+    l *= alpha;
+    m = mx;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float e = __builtin_amdgcn_exp2f(sc[u] - from);
+      p[u] = r0 + 4 * u + rs < r_end ? e : 0.f;
+      l += p[u];
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[c] *= alpha;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float x[8];
+      t.v[u].get(x);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) acc[c] = fmaf(p[u], x[c], acc[c]);
+    }
+  };
+
+  constexpr int kStep = 4 * kRows;                          // wave w takes tiles w, w + 4, ...
+  Tile ta, tb;
+  int r0 = r_begin + kRows * wave;
+  int phys_a = rows_of(r0), phys_b = rows_of(r0 + kStep);
+  issue(ta, r0, phys_a);
+  for (; r0 < r_end; r0 += 2 * kStep) {
+    phys_a = rows_of(r0 + 2 * kStep);
+    if constexpr (kPaged) __builtin_amdgcn_sched_barrier(0);      // the look-up before the rows: its wait must not include them
+    issue(tb, r0 + kStep, phys_b);
+    consume(ta, r0);
+    phys_b = rows_of(r0 + 3 * kStep);
+    if constexpr (kPaged) __builtin_amdgcn_sched_barrier(0);
+    issue(ta, r0 + 2 * kStep, phys_a);
+    consume(tb, r0 + kStep);
+  }
+
+  // the four lane groups of the wave (one without rows: m = -inf, weight 0), then the four waves
+  float mx = fmaxf(m, __shfl_xor(m, 16));
+  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  const float f = m == -INFINITY ? 0.f : part_weight<1>(m - mx);
+  l *= f;
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    acc[c] *= f;
+    acc[c] += __shfl_xor(acc[c], 16);
+    acc[c] += __shfl_xor(acc[c], 32);
+  }
+  if (rs == 0) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) red_acc[wave][0][8 * j + c] = acc[c];
+    if (j == 0) {
+      red_m[wave][0] = mx;
+      red_l[wave][0] = l;
     }
   }
+  __syncthreads();
+  merge_waves<1>(red_acc, red_m, red_l, part + ((int64_t)bg * n_split + split) * (kD + 2));
 }
 
 // grid B*Hq, 128 threads.  Bound by latency (1 MB of partials per 256 heads and 8 splits): the maxima and sums of all
@@ -356,7 +504,7 @@ __global__ __launch_bounds__(kD) void k_full_merge(Shape s, const int32_t* __res
     float mx = m;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
-    wgt[c] = exp_weight(m - mx);
+    wgt[c] = s.G == 1 ? part_weight<1>(m - mx) : part_weight<2>(m - mx);
   }
   __syncthreads();
   float a = 0.f, l = 0.f;
@@ -382,21 +530,21 @@ static hipError_t launch_full_t(const Shape& s, const float* q, const KvView& kv
   const float scale = 0.08838834764831845f;
   // (fp32 rows: a lane's eight channels are two loads, which would fetch the line twice)
   const bool once = sizeof(TK) < 4 && (int64_t)s.B * s.Hkv * s.Lcap * kD * (int64_t)(sizeof(TK) + sizeof(T)) > kKeptBytes;
-#define LFPS_LAUNCH_FULL_P(GG, PAGED, ONCE)                                                                          \
-  hipLaunchKernelGGL((k_full_attn<TK, T, GG, PAGED, ONCE>), grid, block, 0, st, s, q, (const TK*)kv.k, (const T*)kv.v, \
-                     kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, part, n_split, scale)
-#define LFPS_LAUNCH_FULL(GG)                                          \
-  if (kv.page.table) {                                                \
-    if (once) LFPS_LAUNCH_FULL_P(GG, true, sizeof(TK) < 4);           \
-    else LFPS_LAUNCH_FULL_P(GG, true, false);                         \
-  } else {                                                            \
-    if (once) LFPS_LAUNCH_FULL_P(GG, false, sizeof(TK) < 4);          \
-    else LFPS_LAUNCH_FULL_P(GG, false, false);                        \
+#define LFPS_LAUNCH_FULL_P(KERNEL, PAGED, ONCE, ...)                                                                    \
+  hipLaunchKernelGGL((KERNEL<TK, T, ##__VA_ARGS__, PAGED, ONCE>), grid, block, 0, st, s, q, (const TK*)kv.k,             \
+                     (const T*)kv.v, kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, part, n_split, scale)
+#define LFPS_LAUNCH_FULL(KERNEL, ...)                                                   \
+  if (kv.page.table) {                                                                  \
+    if (once) LFPS_LAUNCH_FULL_P(KERNEL, true, sizeof(TK) < 4, ##__VA_ARGS__);          \
+    else LFPS_LAUNCH_FULL_P(KERNEL, true, false, ##__VA_ARGS__);                        \
+  } else {                                                                              \
+    if (once) LFPS_LAUNCH_FULL_P(KERNEL, false, sizeof(TK) < 4, ##__VA_ARGS__);         \
+    else LFPS_LAUNCH_FULL_P(KERNEL, false, false, ##__VA_ARGS__);                       \
   }
   switch (s.G) {
-    case 1: LFPS_LAUNCH_FULL(1); break;
-    case 2: LFPS_LAUNCH_FULL(2); break;
-    case 4: LFPS_LAUNCH_FULL(4); break;
+    case 1: LFPS_LAUNCH_FULL(k_full_attn_single); break;
+    case 2: LFPS_LAUNCH_FULL(k_full_attn, 2); break;
+    case 4: LFPS_LAUNCH_FULL(k_full_attn, 4); break;
     default: return hipErrorInvalidValue;
   }
 #undef LFPS_LAUNCH_FULL

@@ -1,4 +1,4 @@
-"""Full attention at the edges of its tiles (32 rows a wave, 16 in fp32), splits and groupings, with scores that are not finite:
+"""Full attention at the edges of its tiles (32 rows a wave, 16 in fp32 and without grouping), splits and groupings, with scores that are not finite:
 against softmax and sum in fp64."""
 import pytest
 import torch
@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32", "fp8k", "fp8kv"])
 @pytest.mark.parametrize("Hq,Hkv,lens,page", [
-    (4, 1, [1, 31, 32, 33], 0), (8, 4, [64, 127, 129, 0], 16), (4, 4, [255, 256, 257, 15], 0), (16, 4, [511, 513, 17, 1030], 64)])
+    (4, 1, [1, 31, 32, 33], 0), (8, 4, [64, 127, 129, 0], 16), (4, 4, [255, 256, 257, 15], 0), (16, 4, [511, 513, 17, 1030], 64),
+    (4, 4, [1, 16, 17, 1030], 16), (2, 2, [63, 64, 65, 2113], 0)])
 def test_full_attention_against_fp64(dtype, Hq, Hkv, lens, page):
     from paper_2506_15704_amd.binding import Lfps
     g = torch.Generator(device=DEV)
@@ -51,7 +52,8 @@ def test_full_attention_against_fp64(dtype, Hq, Hkv, lens, page):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
-def test_rows_that_score_minus_infinity_weigh_nothing(dtype):
+@pytest.mark.parametrize("Hkv", [2, 4, 8])
+def test_rows_that_score_minus_infinity_weigh_nothing(dtype, Hkv):
     """Keys of -inf in one channel (positive there in every query): rows of weight 0, whole tiles of them among the others; a
     query beyond the fp16 range is no special case."""
     from paper_2506_15704_amd.binding import Lfps
@@ -59,7 +61,7 @@ def test_rows_that_score_minus_infinity_weigh_nothing(dtype):
     g.manual_seed(3)
     dt = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dtype]
     L = 900
-    K, V = (torch.randn((1, 2, L, 128), device=DEV, generator=g).to(dt) for _ in range(2))
+    K, V = (torch.randn((1, Hkv, L, 128), device=DEV, generator=g).to(dt) for _ in range(2))
     dead = torch.zeros(L, dtype=torch.bool, device=DEV)
     dead[:300] = True
     dead[400::3] = True
@@ -67,11 +69,11 @@ def test_rows_that_score_minus_infinity_weigh_nothing(dtype):
     K[:, :, dead, 5] = float("-inf")
     q = torch.randn((1, 8, 128), device=DEV, generator=g)
     q[..., 5] = 1e5
-    ctx = Lfps(batch=1, n_q_heads=8, n_kv_heads=2, kv_dtype=dtype, max_seq_len=L, max_k=1, radius=1)
+    ctx = Lfps(batch=1, n_q_heads=8, n_kv_heads=Hkv, kv_dtype=dtype, max_seq_len=L, max_k=1, radius=1)
     out = torch.zeros((1, 8, 128), device=DEV)
     ctx.lfps_full_attn_decode(q, ctx.kv_view(K, V, torch.tensor([L], dtype=torch.int32, device=DEV)), out)
     for h in range(8):
-        k, v = K[0, h // 4, ~dead].double(), V[0, h // 4, ~dead].double()
+        k, v = K[0, h * Hkv // 8, ~dead].double(), V[0, h * Hkv // 8, ~dead].double()
         ref = torch.softmax(k @ q[0, h].double() / 128 ** 0.5, 0) @ v
         assert float((out[0, h].double() - ref).abs().max()) <= 2e-5
     ctx.close()
