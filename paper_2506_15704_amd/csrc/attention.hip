@@ -97,6 +97,17 @@ __device__ __forceinline__ float exp_weight(float x) {
   return fmaf(e * ln2, r, e);
 }
 
+// x[u] = the elements at at(u), past the caches or not.  (A choice at run time between the two forms of one load is merged by the
+// compiler, into the ordinary one: the kernels hold their loops twice.)
+template <bool kOnce, typename Raw, int U, typename At>
+__device__ __forceinline__ void load_rows(Raw (&x)[U], At at) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if constexpr (kOnce) x[u].load_once(at(u));
+    else x[u].load(at(u));
+  }
+}
+
 // The weight of a partial result whose largest score lies x <= 0 from the largest of all.  Without grouping the scores are held as
 // powers of two (k_full_attn_single).
 template <int G>
@@ -162,9 +173,10 @@ __device__ __forceinline__ float row16_shared_sums(float (&a)[G], int j) {
 // rows, a row cost the same whatever it took to fetch.  U = 16 for FP8 leaves two waves per SIMD: 145 us.
 // (The dot products on the matrix units were as fast, 169 to 180 us, but 1.3 times as far from 64 bits where a few rows carry
 // the weight: large scores are sums of like-signed products there.)
-// kOnce: rows past the caches, for caches larger than the memory-side cache (8 x 32K rows 195 against 207 us with the kernel as
-// it was); smaller ones are found there by the next call (2 x 32K in FP8 65 against 80).
-template <typename TK, typename T, int G, bool kPaged, bool kOnce>
+// kMayOnce: rows past the caches where the rows that the requests hold outgrow the memory-side cache (8 x 32K rows 195 against
+// 207 us with the kernel as it was); fewer are found there by the next call, whatever the context has room for (8 x 8192 of
+// 131072 rows in bf16 52.9 -> 48.8 us, 8 x 16384 in FP8 62.3 -> 57.3, against that capacity deciding).
+template <typename TK, typename T, int G, bool kPaged, bool kMayOnce>
 __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float* __restrict__ q,
                                                             const TK* __restrict__ K, const T* __restrict__ V,
                                                             int64_t stride_b, int64_t stride_h, int64_t stride_n,
@@ -186,6 +198,7 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
   const int r_begin = split * rps;
   const int r_end = (r_begin + rps < n) ? r_begin + rps : n;
   if (r_begin >= n) return;
+  const bool once_here = kMayOnce && outgrows_cache(s, seq_lens, kD * (int)(sizeof(TK) + sizeof(T)));
 
   float qr[G][8];
 #pragma unroll
@@ -202,21 +215,11 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
   auto row_value = [&](int x, int u) { return __builtin_amdgcn_ds_bpermute(4 * rs + 16 * u, x); };   // of row 4 u + rs
   Raw8<TK> kt[U];                                           // kt[u], vt[u]: my channels of row 4 u + rs
   Raw8<T> vt[U];
-  auto fetch_k = [&](int phys) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const TK* p = Kbg + Rows::offset(pg, row_value(phys, u), stride_b, stride_n);
-      if constexpr (kOnce) kt[u].load_once(p);
-      else kt[u].load(p);
-    }
+  auto fetch_k = [&](auto once, int phys) {
+    load_rows<decltype(once)::value>(kt, [&](int u) { return Kbg + Rows::offset(pg, row_value(phys, u), stride_b, stride_n); });
   };
-  auto fetch_v = [&](int phys) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const T* p = Vbg + Rows::offset(pg, row_value(phys, u), stride_b, stride_n);
-      if constexpr (kOnce) vt[u].load_once(p);
-      else vt[u].load(p);
-    }
+  auto fetch_v = [&](auto once, int phys) {
+    load_rows<decltype(once)::value>(vt, [&](int u) { return Vbg + Rows::offset(pg, row_value(phys, u), stride_b, stride_n); });
   };
   // my pairs: head j % G and the rows 4 u + rs with u = t * kShare + j / G
   const int my_u = j / G;
@@ -229,10 +232,11 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
     for (int c = 0; c < 8; ++c) acc[h][c] = 0.f;
 
   constexpr int kStep = 4 * kRows;                          // wave w takes tiles w, w + 4, ...
+  auto walk = [&](auto once) {
   int r0 = r_begin + kRows * wave;
   int phys = rows_of(r0), phys_next = rows_of(r0 + kStep);
-  fetch_k(phys);
-  fetch_v(phys);
+  fetch_k(once, phys);
+  fetch_v(once, phys);
   for (; r0 < r_end; r0 += kStep) {
     float v[NV];
 #pragma unroll
@@ -252,7 +256,7 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
     phys = phys_next;
     phys_next = rows_of(r0 + 2 * kStep);
     if constexpr (kPaged) __builtin_amdgcn_sched_barrier(0);      // the look-up before the rows: its wait must not include them
-    fetch_k(phys);
+    fetch_k(once, phys);
     // one online-softmax step
     bool ok[NV];
     float mx = m;
@@ -300,8 +304,11 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
         for (int c = 0; c < 8; ++c) acc[h][c] = fmaf(p[h], x[c], acc[h][c]);
       if (u % 2) __builtin_amdgcn_sched_barrier(0);
     }
-    fetch_v(phys);
+    fetch_v(once, phys);
   }
+  };
+  if (once_here) walk(std::true_type{});
+  else walk(std::false_type{});
 
   // the lanes of the wave, then the four waves (a wave without rows: m = -inf, weight 0)
 #pragma unroll
@@ -333,7 +340,7 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
 // by log2(e) / sqrt(D), rounded once), so that an exponential needs no product whose rounding would have to be corrected.  In
 // k_full_attn's form the few tiles of a short row waited longer for each other: 1 x 8192 rows of 8 heads in bf16 10.9 -> 9.85 us,
 // in FP8 10.6 -> 9.7, 1 x 16384 in fp32 29.4 -> 28.6, 1 x 32768 in FP8 21.2 -> 19.7; 32 x 30000 in bf16 571 -> 567.
-template <typename TK, typename T, bool kPaged, bool kOnce>
+template <typename TK, typename T, bool kPaged, bool kMayOnce>
 __global__ __launch_bounds__(kAttnThreads) void k_full_attn_single(Shape s, const float* __restrict__ q,
                                                                    const TK* __restrict__ K, const T* __restrict__ V,
                                                                    int64_t stride_b, int64_t stride_h, int64_t stride_n,
@@ -354,6 +361,7 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn_single(Shape s, cons
   const int r_begin = split * rps;
   const int r_end = (r_begin + rps < n) ? r_begin + rps : n;
   if (r_begin >= n) return;
+  const bool once_here = kMayOnce && outgrows_cache(s, seq_lens, kD * (int)(sizeof(TK) + sizeof(T)));
 
   float qr[8];
 #pragma unroll
@@ -373,23 +381,15 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn_single(Shape s, cons
   auto clamped = [&](int r) { return r < r_end ? r : r_end - 1; };
   // paged: row r0 + j of a tile as a physical row
   auto rows_of = [&](int r0) { return kPaged ? Rows::phys(pg, b, clamped(r0 + j)) : 0; };
-  auto issue = [&](Tile& t, int r0, int phys) {
+  auto issue = [&](auto once, Tile& t, int r0, int phys) {
     int64_t off[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int p = kPaged ? __builtin_amdgcn_ds_bpermute(4 * rs + 16 * u, phys) : clamped(r0 + 4 * u + rs);
       off[u] = Rows::offset(pg, p, stride_b, stride_n);
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if constexpr (kOnce) t.k[u].load_once(Kbg + off[u]);
-      else t.k[u].load(Kbg + off[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if constexpr (kOnce) t.v[u].load_once(Vbg + off[u]);
-      else t.v[u].load(Vbg + off[u]);
-    }
+    load_rows<decltype(once)::value>(t.k, [&](int u) { return Kbg + off[u]; });
+    load_rows<decltype(once)::value>(t.v, [&](int u) { return Vbg + off[u]; });
     __builtin_amdgcn_sched_barrier(0);                      // (moved down to their uses, the loads of one tile would wait for the other's)
   };
   float m = -INFINITY, l = 0.f, acc[8];                     // of the rows rs mod 4
@@ -431,20 +431,24 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn_single(Shape s, cons
   };
 
   constexpr int kStep = 4 * kRows;                          // wave w takes tiles w, w + 4, ...
+  auto walk = [&](auto once) {
   Tile ta, tb;
   int r0 = r_begin + kRows * wave;
   int phys_a = rows_of(r0), phys_b = rows_of(r0 + kStep);
-  issue(ta, r0, phys_a);
+  issue(once, ta, r0, phys_a);
   for (; r0 < r_end; r0 += 2 * kStep) {
     phys_a = rows_of(r0 + 2 * kStep);
     if constexpr (kPaged) __builtin_amdgcn_sched_barrier(0);      // the look-up before the rows: its wait must not include them
-    issue(tb, r0 + kStep, phys_b);
+    issue(once, tb, r0 + kStep, phys_b);
     consume(ta, r0);
     phys_b = rows_of(r0 + 3 * kStep);
     if constexpr (kPaged) __builtin_amdgcn_sched_barrier(0);
-    issue(ta, r0 + 2 * kStep, phys_a);
+    issue(once, ta, r0 + 2 * kStep, phys_a);
     consume(tb, r0 + kStep);
   }
+  };
+  if (once_here) walk(std::true_type{});
+  else walk(std::false_type{});
 
   // the four lane groups of the wave (one without rows: m = -inf, weight 0), then the four waves
   float mx = fmaxf(m, __shfl_xor(m, 16));
@@ -528,7 +532,7 @@ static hipError_t launch_full_t(const Shape& s, const float* q, const KvView& kv
                                 hipStream_t st) {
   const dim3 grid(n_split, s.B * s.Hkv), block(kAttnThreads);
   const float scale = 0.08838834764831845f;
-  // (fp32 rows: a lane's eight channels are two loads, which would fetch the line twice)
+  // (the kernels ask how many rows are held; fp32 rows: a lane's eight channels are two loads, which would fetch the line twice)
   const bool once = sizeof(TK) < 4 && (int64_t)s.B * s.Hkv * s.Lcap * kD * (int64_t)(sizeof(TK) + sizeof(T)) > kKeptBytes;
 #define LFPS_LAUNCH_FULL_P(KERNEL, PAGED, ONCE, ...)                                                                    \
   hipLaunchKernelGGL((KERNEL<TK, T, ##__VA_ARGS__, PAGED, ONCE>), grid, block, 0, st, s, q, (const TK*)kv.k,             \

@@ -401,6 +401,19 @@ __device__ __forceinline__ float row16_butterfly_sum(float x) {
 #undef LFPS_DPP
   return x;
 }
+// Do the rows that the requests hold, row_bytes each in every KV head, outgrow the memory-side cache?  (The same for the whole
+// grid; all lanes of a wave call.  In fp32: requests may share rows, and B * Lcap need not fit an int.)
+__device__ __forceinline__ bool outgrows_cache(const Shape& s, const int32_t* seq_lens, int row_bytes) {
+  float rows = 0.f;
+  for (int b = threadIdx.x & 63; b < s.B; b += 64) {
+    const int n = seq_lens[b];
+    rows += (float)(n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n));
+  }
+  rows = row16_sum(rows);
+  rows += __shfl_xor(rows, 16);
+  rows += __shfl_xor(rows, 32);
+  return __builtin_amdgcn_readfirstlane(rows * (float)s.Hkv * (float)row_bytes > (float)kKeptBytes);
+}
 template <int kBy>
 __device__ __forceinline__ double row16_rotate(double x) {
   return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x120 + kBy, 0xf, 0xf, false),

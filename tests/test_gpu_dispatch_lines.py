@@ -42,3 +42,28 @@ def test_exact_topk_from_blocks_is_no_slower_than_from_all_scores(L, budgets, fr
     want, *got = least_us(*[lambda k=k: ctx.lfps_exact_topk(q, kv, k, idx) for k in ks])
     assert max(got) <= 1.1 * want, (want, got)
     ctx.close()
+
+
+# rows that fit the memory-side cache in a context with room for eight times as many, which would not: they are found there by
+# the next call (read past it, they took 1.05 to 1.07 times as long), and the splits are the same
+@pytest.mark.parametrize("dtype,n,Hq", [("bf16", 8192, 32), ("fp8", 16384, 32), ("fp8", 16384, 8)])
+def test_full_attention_with_room_to_grow(dtype, n, Hq):
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    B, Hkv, dt = 8, 8, torch.bfloat16 if dtype == "bf16" else torch.float8_e4m3fn
+    K, V = (torch.zeros((B, Hkv, 8 * n, 128), dtype=dt, device=DEV) for _ in range(2))
+    for T in (K, V):
+        T[:, :, :n] = torch.randn((B, Hkv, n, 128), device=DEV, generator=g).to(dt)
+    q = torch.randn((B, Hq, 128), device=DEV, generator=g)
+    seq = torch.full((B,), n, dtype=torch.int32, device=DEV)
+    calls, outs = [], []
+    for room in (n, 8 * n):
+        ctx = Lfps(batch=B, n_q_heads=Hq, max_seq_len=room, max_k=1, radius=1, k_fp8=dtype == "fp8", v_fp8=dtype == "fp8")
+        out = torch.zeros((B, Hq, 128), device=DEV)
+        kv = ctx.kv_view(K[:, :, :room], V[:, :, :room], seq)
+        calls.append(lambda ctx=ctx, kv=kv, out=out: ctx.lfps_full_attn_decode(q, kv, out))
+        outs.append(out)
+    tight, roomy = least_us(*calls, each=100)
+    assert torch.equal(*outs)
+    assert roomy <= 1.03 * tight, (tight, roomy)

@@ -1,5 +1,6 @@
-"""Scoring passes over more rows than the memory-side cache holds (their K rows are fetched past the caches and turned into
-operands in LDS): bit for bit what the unfiltered kernels return, which other tests hold against the oracle."""
+"""Passes over more rows than the memory-side cache holds, whose rows are fetched past the caches.  Scoring (rows turned into
+operands in LDS): bit for bit what the unfiltered kernels return, which other tests hold against the oracle.  Full attention and
+score tables: against the same rows when the call holds few."""
 import pytest
 import torch
 
@@ -100,3 +101,42 @@ def test_tables_from_streamed_keys(dtype, page, B, L, Hq, Hkv, s):
         for got, want in zip(whole, tables(b, b + 1)):
             assert float(want.abs().max()) > 0
             torch.testing.assert_close(got[b:b + 1], want, rtol=2e-5, atol=1e-12)
+
+
+# every form of the kernels that ask how much is held; a request gives the same bits whatever the others hold
+@pytest.mark.parametrize("dtype,page", [("bf16", 0), ("f16", 64), ("fp8k", 16), ("fp8kv", 0), ("fp8kv", 256), ("bf16", 16)])
+@pytest.mark.parametrize("Hq,Hkv", [(8, 8), (16, 8), (32, 8)])
+def test_full_attention_of_rows_read_once_equals_that_of_kept_rows(dtype, page, Hq, Hkv):
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(Hq + page)
+    kd = {"bf16": torch.bfloat16, "f16": torch.float16}.get(dtype, torch.float8_e4m3fn)
+    vd = torch.bfloat16 if dtype == "fp8k" else kd
+    row = 128 * (torch.empty(0, dtype=kd).element_size() + torch.empty(0, dtype=vd).element_size())
+    B = 3
+    L = (340 << 20) // (B * Hkv * row) + 5
+    nb = -(-L // page) if page else 1
+    shape = (B * nb, Hkv, page, 128) if page else (B, Hkv, L, 128)
+    K, V = (torch.empty(shape, dtype=d, device=DEV) for d in (kd, vd))
+    for T in (K, V):
+        for i in range(0, shape[0], nb):
+            T[i:i + nb] = torch.randn(T[i:i + nb].shape, device=DEV, generator=g).to(T.dtype)
+    table = torch.randperm(B * nb, device=DEV, generator=g).view(B, nb).to(torch.int32)
+    q = torch.randn((B, Hq, 128), device=DEV, generator=g)
+    ctx = Lfps(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="f16" if dtype == "f16" else "bf16", max_seq_len=L, max_k=1,
+               radius=1, k_fp8=kd == torch.float8_e4m3fn, v_fp8=vd == torch.float8_e4m3fn)
+
+    def attend(lens):
+        seq = torch.tensor(lens, dtype=torch.int32, device=DEV)
+        kv = ctx.paged_kv_view(K, V, table, seq) if page else ctx.kv_view(K, V, seq)
+        out = torch.full((B, Hq, 128), 7.0, device=DEV)
+        ctx.lfps_full_attn_decode(q, kv, out)
+        return out
+
+    lens = [L, L - 13, L - 1]
+    assert sum(lens) * Hkv * row > 288 << 20
+    whole = attend(lens)
+    for b in range(B):
+        few = attend([n if i == b else 1 for i, n in enumerate(lens)])
+        assert torch.equal(few[b], whole[b]), b
+    ctx.close()
