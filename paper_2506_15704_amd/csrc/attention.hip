@@ -198,7 +198,7 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
   const int r_begin = split * rps;
   const int r_end = (r_begin + rps < n) ? r_begin + rps : n;
   if (r_begin >= n) return;
-  const bool once_here = kMayOnce && outgrows_cache(s, seq_lens, kD * (int)(sizeof(TK) + sizeof(T)));
+  const bool once_here = kMayOnce && outgrow_cache(s, held_rows(s, seq_lens), kD * (int)(sizeof(TK) + sizeof(T)));
 
   float qr[G][8];
 #pragma unroll
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn_single(Shape s, cons
   const int r_begin = split * rps;
   const int r_end = (r_begin + rps < n) ? r_begin + rps : n;
   if (r_begin >= n) return;
-  const bool once_here = kMayOnce && outgrows_cache(s, seq_lens, kD * (int)(sizeof(TK) + sizeof(T)));
+  const bool once_here = kMayOnce && outgrow_cache(s, held_rows(s, seq_lens), kD * (int)(sizeof(TK) + sizeof(T)));
 
   float qr[8];
 #pragma unroll

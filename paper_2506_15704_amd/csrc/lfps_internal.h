@@ -401,18 +401,24 @@ __device__ __forceinline__ float row16_butterfly_sum(float x) {
 #undef LFPS_DPP
   return x;
 }
-// Do the rows that the requests hold, row_bytes each in every KV head, outgrow the memory-side cache?  (The same for the whole
-// grid; all lanes of a wave call.  In fp32: requests may share rows, and B * Lcap need not fit an int.)
-__device__ __forceinline__ bool outgrows_cache(const Shape& s, const int32_t* seq_lens, int row_bytes) {
-  float rows = 0.f;
-  for (int b = threadIdx.x & 63; b < s.B; b += 64) {
-    const int n = seq_lens[b];
-    rows += (float)(n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n));
-  }
+// Do the rows that the requests hold, row_bytes each in every KV head, take more than kept_bytes (the memory-side cache, or what a
+// pass leaves of it)?  The same for the whole grid.  In two parts, so that other loads can be asked for in between: the rows that
+// my lane counts, and their sum over the wave.  (In fp32: requests may share rows, and B * Lcap need not fit an int.)
+__device__ __forceinline__ float held_rows(const Shape& s, const int32_t* seq_lens) {
+  auto rows = [&](int b) {
+    const int n = seq_lens[b < s.B ? b : 0];
+    return b < s.B ? (float)(n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n)) : 0.f;
+  };
+  const int lane = threadIdx.x & 63;
+  float sum = rows(lane);
+  for (int b0 = 64; b0 < s.B; b0 += 64) sum += rows(b0 + lane);
+  return sum;
+}
+__device__ __forceinline__ bool outgrow_cache(const Shape& s, float rows, int row_bytes, float kept_bytes = (float)kKeptBytes) {
   rows = row16_sum(rows);
   rows += __shfl_xor(rows, 16);
   rows += __shfl_xor(rows, 32);
-  return __builtin_amdgcn_readfirstlane(rows * (float)s.Hkv * (float)row_bytes > (float)kKeptBytes);
+  return __builtin_amdgcn_readfirstlane(rows * (float)s.Hkv * (float)row_bytes > kept_bytes);
 }
 template <int kBy>
 __device__ __forceinline__ double row16_rotate(double x) {

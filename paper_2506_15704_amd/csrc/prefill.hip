@@ -144,13 +144,14 @@ __device__ __forceinline__ void wave_run(int tiles, int w, int waves, int& lo, i
 // [n_sink, n - j + 1).  part_m / part_l [bg, block, jq, h]: the largest q . K and the sum of the exponentials relative
 // to it over the rows of the block (kLeastMax and 0 when it has none).  dots (or NULL; one query only): every q . K,
 // [B, Hq, stride].
-// kOnce: rows past the caches (StreamTile; its LDS lies behind the operands), see stats_once.
-template <int G, bool kPaged, int kKind, bool kOnce>
+// kMayOnce: rows past the caches (StreamTile; its LDS lies behind the operands) where the requests hold more than kept_bytes of
+// them, see stats_kept_bytes.
+template <int G, bool kPaged, int kKind, bool kMayOnce>
 __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
     Shape s, const float* __restrict__ q0, int64_t q_stride, int j0, int nq, const void* __restrict__ K,
     int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage pg, const int32_t* __restrict__ seq_lens,
     float* __restrict__ part_m, double* __restrict__ part_l, float* __restrict__ dots, int64_t dots_stride,
-    int32_t* __restrict__ flags) {
+    int32_t* __restrict__ flags, float kept_bytes) {
   using Tile = HistTile<kPaged, kKind, kHistSub>;
   using Op = typename Tile::Op;
   extern __shared__ char lds_raw[];
@@ -162,11 +163,13 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
   const int j = lane & 15, kb = lane >> 4;
   int n = seq_lens[b];
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
+  const float held = kMayOnce ? held_rows(s, seq_lens) : 0.f;
   report_q_range(stage_hist_operands<G>(ops, q0, q_stride, (int64_t)b * s.Hq + (int64_t)g * G, nq), flags);
   for (int e = tid; e < kHistWaves * kHistBatch * 4; e += kHistWaves * 64) {
     (&wm[0][0][0])[e] = kLeastMax;
     (&wl[0][0][0])[e] = 0.0;
   }
+  const bool once = kMayOnce && outgrow_cache(s, held, kD * KSub<kKind>::kElemBytes, kept_bytes);
   __syncthreads();
   const char* Kbg = static_cast<const char*>(K) + RowMap<kPaged>::base(b, g, stride_b, stride_h) * KSub<kKind>::kElemBytes;
   float* my_dots = dots && kb < G ? dots + ((int64_t)b * s.Hq + (int64_t)g * G + kb) * dots_stride : nullptr;
@@ -175,7 +178,7 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
   for (int tile = lo; tile < hi; ++tile) {
     const int base = tile * kHistRows;
     Tile T;
-    if constexpr (kOnce)
+    if (kMayOnce && once)                                  // (a copy of the loop each: 1.5 us slower at 64 groups x 17K rows)
       T.load_once(Kbg, pg, b, stride_b, stride_n, base, n, lane,
                   reinterpret_cast<u32x4*>(lds_raw + hist_lds(nq)) + wave * StreamTile<kKind>::kLdsChunks);
     else
@@ -741,13 +744,17 @@ int64_t table_init_scratch_bytes(const Shape& s) {
   return stats + moments;
 }
 
-// K larger than the memory-side cache and few queries: the pass is bound by the bytes of K then.  One query, 64 groups x 32K rows
-// (537 MB): 119 -> 96 us.  Tables and one step, before -> now: 40 groups x 32K rows, 1 query 166 -> 148 us, 4 queries 264 -> 246,
-// 8 queries 275 -> 263; 96 groups x 40K rows, 4 queries 598 -> 558, in paged FP8 435 -> 420 (1 query 271 -> 269).  With 32
-// queries the matrix units bound the pass, and their operands leave no LDS for this form.
+// Up to how many bytes of keys the pass over K above reads with ordinary loads.  With few queries it is bound by the bytes of K, and
+// keys that will not be found in the memory-side cache again are read past it (one query, 64 groups x 32K rows, 537 MB: 119 -> 96
+// us).  With one query the next reader is the next call, and the tables, written whole in between, take their part of the cache:
+// tables of 4 x capacity, K + tables 224 MB 54.2 us kept, 58.4 past the caches, 280 MB 74.0 and 72.8, 336 MB 91.2 and 79.1.  With
+// more queries k_hist_apply reads the keys again at once, while it writes the tables: 4 queries, keys + tables of 128 + 192 MB
+// 135.9 and 153.1, 192 + 36 MB 120.7 and 122.4, 224 + 168 MB 164.6 and 163.3, 256 + 192 MB 199.3 and 186.2.  With 32 queries the
+// matrix units bound the pass, and their operands leave no LDS for this form.
 constexpr int kOnceQueries = 8;
-static bool stats_once(const Shape& s, int nq, int elem_bytes) {
-  return nq <= kOnceQueries && (int64_t)s.B * s.Hkv * s.Lcap * kD * elem_bytes > kKeptBytes;
+static float stats_kept_bytes(const Shape& s, int n_queries) {
+  const float tables = 12.f * s.B * s.Hq * s.Lcap;
+  return n_queries == 1 ? (float)kKeptBytes - tables : 280.f * (1 << 20) - 0.5f * tables;
 }
 
 // Called once per context in table mode: the operands of 32 queries need more dynamic LDS than the default limit.
@@ -789,8 +796,9 @@ static hipError_t launch_hist_t(const Shape& s, float* tab_ver, float* tab_sla, 
 #define LFPS_STATS(ONCE, LDS)                                                                                          \
   hipLaunchKernelGGL((k_hist_stats<G, kPaged, kKind, ONCE>), grid, block, LDS, st, s, q0, q_stride, j0, nq, kv.k,      \
                      kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, part_m, part_l, one ? dots : nullptr, \
-                     dots_stride, flags)
-  if (stats_once(s, nq, KSub<kKind>::kElemBytes)) LFPS_STATS(true, hist_lds(nq) + kTurns);
+                     dots_stride, flags, kept)
+  const float kept = stats_kept_bytes(s, n_queries);
+  if (nq <= kOnceQueries && (float)s.B * s.Hkv * s.Lcap * (kD * KSub<kKind>::kElemBytes) > kept) LFPS_STATS(true, hist_lds(nq) + kTurns);
   else LFPS_STATS(false, hist_lds(nq));
 #undef LFPS_STATS
   hipError_t e = hipGetLastError();

@@ -67,3 +67,20 @@ def test_full_attention_with_room_to_grow(dtype, n, Hq):
     tight, roomy = least_us(*calls, each=100)
     assert torch.equal(*outs)
     assert roomy <= 1.03 * tight, (tight, roomy)
+
+
+# eight queries are the most whose pass may read the keys past the caches: with keys that stay in the memory-side cache for the
+# second pass over them, in a context with room for four times as many, they cost no more than nine (they cost 1.08 times as much)
+def test_tables_from_eight_queries_cost_no_more_than_from_nine():
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(8)
+    B, n = 2, 32768
+    K = torch.zeros((B, 8, 4 * n, 128), dtype=torch.bfloat16, device=DEV)
+    K[:, :, :n] = torch.randn((B, 8, n, 128), device=DEV, generator=g).to(torch.bfloat16)
+    ctx = Lfps(batch=B, max_seq_len=4 * n, max_k=64, radius=1, table_mode=True, n_sink=4)
+    kv = ctx.kv_view(K, K, torch.full((B,), n, dtype=torch.int32, device=DEV))
+    q = torch.randn((9, B, 32, 128), device=DEV, generator=g)
+    eight, nine = least_us(lambda: ctx.lfps_tables_init(q[:8], kv), lambda: ctx.lfps_tables_init(q, kv))
+    assert eight <= 1.01 * nine, (eight, nine)
+    ctx.close()

@@ -140,3 +140,41 @@ def test_full_attention_of_rows_read_once_equals_that_of_kept_rows(dtype, page, 
         few = attend([n if i == b else 1 for i, n in enumerate(lens)])
         assert torch.equal(few[b], whole[b]), b
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype,page", [("bf16", 0), ("f16", 64), ("fp8", 16), ("fp8", 0), ("bf16", 16)])
+@pytest.mark.parametrize("Hq,s", [(32, 1), (32, 4), (8, 8), (16, 3)])
+def test_tables_from_rows_read_once_equal_those_from_kept_rows(dtype, page, Hq, s):
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(Hq + s)
+    kd = {"bf16": torch.bfloat16, "f16": torch.float16, "fp8": torch.float8_e4m3fn}[dtype]
+    B, Hkv = 3, 8
+    L = (300 << 20) // (B * Hkv * 128 * torch.empty(0, dtype=kd).element_size()) + 3
+    nb = -(-L // page) if page else 1
+    shape = (B * nb, Hkv, page, 128) if page else (B, Hkv, L, 128)
+    K = torch.empty(shape, dtype=kd, device=DEV)
+    for i in range(0, shape[0], nb):
+        K[i:i + nb] = torch.randn(K[i:i + nb].shape, device=DEV, generator=g).to(kd)
+    V = torch.zeros(shape, dtype=torch.float16 if dtype == "f16" else torch.bfloat16, device=DEV)
+    table = torch.randperm(B * nb, device=DEV, generator=g).view(B, nb).to(torch.int32)
+    q = 2 * torch.randn((s, B, Hq, 128), device=DEV, generator=g)
+    ctx = Lfps(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="f16" if dtype == "f16" else "bf16", max_seq_len=L, max_k=64,
+               radius=1, k_fp8=dtype == "fp8", table_mode=True, table_decay=0.95, n_sink=4)
+
+    def tables(lens):
+        seq = torch.tensor(lens, dtype=torch.int32, device=DEV)
+        kv = ctx.paged_kv_view(K, V, table, seq) if page else ctx.kv_view(K, V, seq)
+        ctx.lfps_tables_init(q, kv)
+        out = [torch.zeros((B, Hq, L), dtype=torch.float64, device=DEV) for _ in range(2)]
+        ctx.lfps_tables_export(*out, seq)
+        return out
+
+    lens = [L, L - 130, L - 1]
+    whole = tables(lens)
+    for b in range(B):
+        few = tables([n if i == b else 200 for i, n in enumerate(lens)])
+        for got, want in zip(whole, few):
+            assert float(want[b].abs().max()) > 0
+            assert torch.equal(got[b], want[b]), b
+    ctx.close()
