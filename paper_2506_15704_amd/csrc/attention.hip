@@ -173,7 +173,7 @@ __device__ __forceinline__ float row16_shared_sums(float (&a)[G], int j) {
 // rows, a row cost the same whatever it took to fetch.  U = 16 for FP8 leaves two waves per SIMD: 145 us.
 // (The dot products on the matrix units were as fast, 169 to 180 us, but 1.3 times as far from 64 bits where a few rows carry
 // the weight: large scores are sums of like-signed products there.)
-// kMayOnce: rows past the caches where the rows that the requests hold outgrow the memory-side cache (8 x 32K rows 195 against
+// kMayOnce: rows past the caches where the rows that the requests hold outgrow the memory-side cache (kKeptStreamBytes; 8 x 32K rows 195 against
 // 207 us with the kernel as it was); fewer are found there by the next call, whatever the context has room for (8 x 8192 of
 // 131072 rows in bf16 52.9 -> 48.8 us, 8 x 16384 in FP8 62.3 -> 57.3, against that capacity deciding).
 template <typename TK, typename T, int G, bool kPaged, bool kMayOnce>
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
   const int r_begin = split * rps;
   const int r_end = (r_begin + rps < n) ? r_begin + rps : n;
   if (r_begin >= n) return;
-  const bool once_here = kMayOnce && outgrow_cache(s, held_rows(s, seq_lens), kD * (int)(sizeof(TK) + sizeof(T)));
+  const bool once_here = kMayOnce && outgrow_cache(s, held_rows(s, seq_lens), kD * (int)(sizeof(TK) + sizeof(T)), kKeptStreamBytes);
 
   float qr[G][8];
 #pragma unroll
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn_single(Shape s, cons
   const int r_begin = split * rps;
   const int r_end = (r_begin + rps < n) ? r_begin + rps : n;
   if (r_begin >= n) return;
-  const bool once_here = kMayOnce && outgrow_cache(s, held_rows(s, seq_lens), kD * (int)(sizeof(TK) + sizeof(T)));
+  const bool once_here = kMayOnce && outgrow_cache(s, held_rows(s, seq_lens), kD * (int)(sizeof(TK) + sizeof(T)), kKeptStreamBytes);
 
   float qr[8];
 #pragma unroll
@@ -533,7 +533,7 @@ static hipError_t launch_full_t(const Shape& s, const float* q, const KvView& kv
   const dim3 grid(n_split, s.B * s.Hkv), block(kAttnThreads);
   const float scale = 0.08838834764831845f;
   // (the kernels ask how many rows are held; fp32 rows: a lane's eight channels are two loads, which would fetch the line twice)
-  const bool once = sizeof(TK) < 4 && (int64_t)s.B * s.Hkv * s.Lcap * kD * (int64_t)(sizeof(TK) + sizeof(T)) > kKeptBytes;
+  const bool once = sizeof(TK) < 4 && (int64_t)s.B * s.Hkv * s.Lcap * kD * (int64_t)(sizeof(TK) + sizeof(T)) > kKeptStreamBytes;
 #define LFPS_LAUNCH_FULL_P(KERNEL, PAGED, ONCE, ...)                                                                    \
   hipLaunchKernelGGL((KERNEL<TK, T, ##__VA_ARGS__, PAGED, ONCE>), grid, block, 0, st, s, q, (const TK*)kv.k,             \
                      (const T*)kv.v, kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, part, n_split, scale)

@@ -91,11 +91,13 @@ __global__ __launch_bounds__(kScoreThreads) void k_group_score_bf16(Shape s, con
 //
 // How the rows are fetched.  Bound by the bytes of the rows.  Candidates of more than kKeptBytes cannot be found again in the
 // memory-side cache (256 MB) by the next step, so their rows are read past the caches (StreamTile): 128 groups x 128K rows,
-// 954 MB of candidates 193 -> 175 us, 1.07 GB of all rows 185 -> 162.5 us = 6.6 TB/s; and what the select reads after it (the
-// survivors, V rows shared by the heads of a group) is no longer driven out: its kernel 40 -> 31 us.  (Non-temporal loads of
-// KTile's shape fetch every line several times, 300 us; StreamTile with ordinary loads gains nothing, 196 us.)  Up to kKeptBytes
-// ordinary loads, every lane its own channels (KTile): the next step finds nine tenths of its rows in the cache.  64 groups x
-// 32K rows, 220 MB: a step 64 us, 66 past the caches; equal at 280 to 300 MB.
+// 954 MB of candidates 193 -> 175 us; all rows of 64 groups x 64K (kDense), 1.07 GB 185 -> 162.5 us = 6.6 TB/s; and what the select
+// reads after it (the survivors, V rows shared by the heads of a group) is no longer driven out: its kernel 40 -> 31 us.
+// (Non-temporal loads of KTile's shape fetch every line several times, 300 us; StreamTile with ordinary loads gains nothing, 196
+// us.)  Up to kKeptBytes ordinary loads, every lane its own channels (KTile): where the same layer's steps follow each other, the
+// next one finds nine tenths of its rows in the cache.  64 groups x 32K rows, 220 MB: a step 64 us, 66 past the caches.  Two steps
+// of 16 requests, kept -> past: 260 MB of bf16 candidates 152.3 -> 152.0 us, 275 MB 161.0 -> 157.7; FP8 260 MB 168.0 -> 169.7,
+// 275 MB 176.0 -> 174.8.
 // The parts are cut at multiples of 16 slots: of 64, a part of 420 slots grew by 6 % and the last waves had nothing to do
 // (64 groups x 32K rows: 38.1 -> 37.0 us).
 constexpr int kFilterStage = 256;   // survivors one wave can hold per head before it must write them out
@@ -151,7 +153,7 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
   const int64_t part_lo = w * S;
   const int64_t part_hi = part_lo + S < total ? part_lo + S : total;
   if (part_lo >= total) return;                          // nothing left for this wave
-  const bool stream = total * (kD * KTile<kKind>::kElemBytes) > kKeptBytes;
+  const bool stream = total * (kD * KTile<kKind>::kElemBytes) > (kDense ? kKeptStreamBytes : kKeptBytes);
 
   const uint32_t below = (1u << j) - 1u;                // lanes of my 16-lane group with a lower row
   float* st_s = stage_score[wave][kb < G ? kb : 0];
