@@ -168,9 +168,11 @@ __device__ __forceinline__ float row16_shared_sums(float (&a)[G], int j) {
 // A wave takes U groups of four rows at a time, 16 lanes a row, 8 channels a lane, for K and for V.  The G sums of a row are
 // shared out over its lanes, so that a lane makes the softmax step for one head and its own rows only, once per tile; the
 // weights reach the lanes that hold the values through LDS.  The rows of K and of V are in flight in turn, those of one while
-// the other is used.  Bound by the bytes of K and V in 16 bits (64 groups x 32K rows, 1.07 GB: 174 us with the merge, 199 before),
-// by the multiply-adds in FP8 (the same rows: 132 us, 233 before): when every lane made the step for all heads and each of its
-// rows, a row cost the same whatever it took to fetch.  U = 16 for FP8 leaves two waves per SIMD: 145 us.
+// the other is used.  Bound by the bytes of K and V in 16 bits (64 groups x 32K rows, 1.07 GB: 168.5 us with the merge, 199 with an
+// earlier form), by the multiply-adds in FP8 (the same rows: 112 us, 233): when every lane made the step for all heads and each of
+// its rows, a row cost the same whatever it took to fetch.  U = 16 for FP8 leaves two waves per SIMD: 13 us slower.
+// Rows of a contiguous cache are counted, not looked up across lanes, which made every load wait for LDS: bf16 172.5 -> 168.5 us, FP8
+// 114 -> 112, 8 x 16384 in FP8 57.2 -> 56.9, 16 x 8480 60.0 -> 59.3.
 // (The dot products on the matrix units were as fast, 169 to 180 us, but 1.3 times as far from 64 bits where a few rows carry
 // the weight: large scores are sums of like-signed products there.)
 // kMayOnce: rows past the caches where the rows that the requests hold outgrow the memory-side cache (kKeptStreamBytes; 8 x 32K rows 195 against
@@ -210,9 +212,13 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
   using Rows = RowMap<kPaged>;
   const TK* Kbg = K + Rows::base(b, g, stride_b, stride_h) + 8 * j;
   const T* Vbg = V + Rows::base(b, g, stride_b, stride_h) + 8 * j;
-  // row r0 + lane of a tile as a physical row (past the end: the last row, of weight 0, so that no load sits behind a branch)
-  auto rows_of = [&](int r0) { return Rows::phys(pg, b, r0 + lane < r_end ? r0 + lane : r_end - 1); };
-  auto row_value = [&](int x, int u) { return __builtin_amdgcn_ds_bpermute(4 * rs + 16 * u, x); };   // of row 4 u + rs
+  // Rows past the end are read from the last row and weigh nothing, so no load sits behind a branch.
+  auto clamped = [&](int r) { return r < r_end ? r : r_end - 1; };
+  // the tile at r0: paged, its row r0 + lane as a physical row; else its first row
+  auto rows_of = [&](int r0) { return kPaged ? Rows::phys(pg, b, clamped(r0 + lane)) : r0; };
+  auto row_value = [&](int x, int u) {                      // of row 4 u + rs
+    return kPaged ? __builtin_amdgcn_ds_bpermute(4 * rs + 16 * u, x) : clamped(x + 4 * u + rs);
+  };
   Raw8<TK> kt[U];                                           // kt[u], vt[u]: my channels of row 4 u + rs
   Raw8<T> vt[U];
   auto fetch_k = [&](auto once, int phys) {
