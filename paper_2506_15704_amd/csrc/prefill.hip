@@ -72,8 +72,10 @@ __device__ __forceinline__ bool stage_hist_operands(Op* lds, const float* __rest
     }
     Op term[3];
     Split3<Op>::all(f, term);
+    const uint32_t live = h < G ? ~0u : 0u;                // (by bits: from a choice the compiler makes two branches)
 #pragma unroll
-    for (int t = 0; t < 4; ++t) e[t] = h < G && t < 3 ? term[t < 3 ? t : 0] : Op{};
+    for (int t = 0; t < 3; ++t) e[t] = __builtin_bit_cast(Op, __builtin_bit_cast(u32x4, term[t]) & live);
+    e[3] = Op{};
   }
   return clipped;
 }
