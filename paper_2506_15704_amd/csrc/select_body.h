@@ -20,6 +20,7 @@ struct SelectShared {
   float wlo[NT / 64], whi[NT / 64];
   uint32_t cnt_gt[NT / 64], cnt_eq[NT / 64];
   uint32_t need, bin, list_n, thr, need_eq;
+  float cut;                                               // (select_blocks)
 };
 
 __device__ __forceinline__ int lanes_below(uint64_t m) {   // set bits of m at lanes lower than mine

@@ -208,7 +208,6 @@ __device__ __forceinline__ bool select_blocks(SelectShared<NT>& sm, const float*
   const int nb = (n + 15) >> 4;
   cap -= (ksel + 1) >> 1;                                  // the chosen blocks lie behind the list
   uint32_t* blocks = reinterpret_cast<uint32_t*>(list + cap);
-  float* cut_at = &sm.wlo[0];                              // (not used by a select with from_min after its first barrier)
   for (int i = tid; i < 2 * NT; i += NT) sm.hist[i] = 0u;
   if (tid == 0) sm.list_n = 0u;
   __syncthreads();
@@ -217,7 +216,7 @@ __device__ __forceinline__ bool select_blocks(SelectShared<NT>& sm, const float*
     float v[E];
 #pragma unroll
     for (int u = 0; u < E; ++u) v[u] = tops[u * NT + tid < nb ? u * NT + tid : nb - 1];
-    select_registers<NT, E>(sm, v, nb, ksel, 0.f, true, cut_at,
+    select_registers<NT, E>(sm, v, nb, ksel, 0.f, true, &sm.cut,
                             [&](int rank, int u, float) { blocks[rank] = (uint32_t)(u * NT + tid); });
   };
   if (nb <= 2 * NT) choose(std::integral_constant<int, 2>{});
@@ -225,7 +224,7 @@ __device__ __forceinline__ bool select_blocks(SelectShared<NT>& sm, const float*
   else if (nb <= 8 * NT) choose(std::integral_constant<int, 8>{});
   else choose(std::integral_constant<int, kRegElems>{});
   __syncthreads();
-  const float cut = *cut_at;
+  const float cut = sm.cut;
   int kept = 0;
 #pragma unroll 1
   for (int r0 = 0; r0 < ksel; r0 += NT) {                  // a block a thread
