@@ -214,7 +214,6 @@ template <int kKind>
 struct KTile {
   using Operand = typename KSub<kKind>::Operand;
   static constexpr int kElemBytes = KSub<kKind>::kElemBytes;
-  static constexpr int kLdsChunks = 1;                     // (none needed)
   KSub<kKind> s_[4];
   __device__ __forceinline__ void load_row(int t, const char* row, int kb) { s_[t].load_row(row, kb); }
   __device__ __forceinline__ Operand operand(int t, int kk) const { return s_[t].operand(kk); }
@@ -231,8 +230,7 @@ struct KTile {
 // that a cache line is touched by one instruction only and need not be kept (non-temporal).  sub(t) turns the sixteen rows of
 // sub-tile t into operands through a wave-private piece of LDS (rows 16 bytes further apart than they are long, so that
 // neither the writes nor the reads of neighbouring lanes meet in a bank): the operands, and so the scores' bits, are KTile's.
-// kOnce false: the same with ordinary loads.
-template <int kKind, bool kOnce = true>
+template <int kKind>
 struct StreamTile {
   using Operand = typename KSub<kKind>::Operand;
   static constexpr int kElemBytes = KSub<kKind>::kElemBytes;
@@ -247,8 +245,7 @@ struct StreamTile {
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
       const int row = lane_value(phys, lane / kChunks, i * kLoadRows);
-      const u32x4* p = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(mine) + offset(row));
-      raw[i] = kOnce ? __builtin_nontemporal_load(p) : *p;
+      raw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(mine) + offset(row)));
     }
   }
   __device__ __forceinline__ KSub<kKind> sub(int t, u32x4* lds, int lane) const {
