@@ -85,18 +85,6 @@ int full_attn_splits(const Shape& s) {
 
 __device__ __forceinline__ int rows_per_split(int n, int n_split) { return (((n + n_split - 1) / n_split) + 15) & ~15; }
 
-// exp(x) for x <= 0 to about one unit in the last place: exp2 of the rounded product, corrected by the product's rounding
-// error, which grows with |x|.  (Results below 2^-126 are 0; a NaN stays one.)
-__device__ __forceinline__ float exp_weight(float x) {
-  constexpr double c = 1.4426950408889634;
-  constexpr float hi = (float)c, lo = (float)(c - (double)hi), ln2 = 0.6931471805599453f;
-  x = __builtin_elementwise_maximum(x, -1e30f);             // (the correction needs a finite x)
-  const float t = x * hi;
-  const float r = fmaf(x, lo, fmaf(x, hi, -t));
-  const float e = __builtin_amdgcn_exp2f(t);
-  return fmaf(e * ln2, r, e);
-}
-
 // x[u] = the elements at at(u), past the caches or not.  (A choice at run time between the two forms of one load is merged by the
 // compiler, into the ordinary one: the kernels hold their loops twice.)
 template <bool kOnce, typename Raw, int U, typename At>
@@ -111,7 +99,7 @@ __device__ __forceinline__ void load_rows(Raw (&x)[U], At at) {
 // The weight of a partial result whose largest score lies x <= 0 from the largest of all.  Without grouping the scores are held as
 // powers of two (k_full_attn_single).
 template <int G>
-__device__ __forceinline__ float part_weight(float x) { return G == 1 ? __builtin_amdgcn_exp2f(x) : exp_weight(x); }
+__device__ __forceinline__ float part_weight(float x) { return G == 1 ? __builtin_amdgcn_exp2f(x) : exp_below<false>(x); }
 
 // The four waves of a workgroup (a wave without rows: m = -inf, weight 0) -> po [G, D+2]: acc[D], m, l.  All threads call, after a
 // barrier.
@@ -157,8 +145,8 @@ __device__ __forceinline__ float row16_shared_sums(float (&a)[G], int j) {
     x = keep + LFPS_DPP(give, 0x4E);
   }
   // (lanes j and j ^ 4, then j ^ 8, by rotation: every lane of a quad holds another sum)
-  x += LFPS_DPP(x, 0x124);                                   // row_ror:4: with the next one, the pairs' sums agree
-  x += LFPS_DPP(x, 0x128);                                   // row_ror:8
+  x += row16_rotate<4>(x);                                   // with the next one, the pairs' sums agree
+  x += row16_rotate<8>(x);
   return x;
 #undef LFPS_DPP
 }
@@ -271,20 +259,18 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
       ok[t] = mine && r0 + 4 * (t * kShare + my_u) + rs < r_end;
       mx = ok[t] ? fmaxf(mx, v[t]) : mx;
     }
-#define LFPS_ROT(x, n) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + (n), 0xf, 0xf, false))
-    mx = fmaxf(mx, LFPS_ROT(mx, 8));
-    mx = fmaxf(mx, LFPS_ROT(mx, 4));
-    if constexpr (G == 2) mx = fmaxf(mx, LFPS_ROT(mx, 2));
-#undef LFPS_ROT
+    mx = fmaxf(mx, row16_rotate<8>(mx));
+    mx = fmaxf(mx, row16_rotate<4>(mx));
+    if constexpr (G == 2) mx = fmaxf(mx, row16_rotate<2>(mx));
     mx = fmaxf(mx, __shfl_xor(mx, 16));
     mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float alpha = mx == -INFINITY ? 1.f : exp_weight(m - mx);      // (0 on the first tile)
+    const float alpha = mx == -INFINITY ? 1.f : exp_below<false>(m - mx);      // (0 on the first tile)
     l *= alpha;
     m = mx;
     wave_lds_order();                                                // (the weights of the tile before have been read)
 #pragma unroll
     for (int t = 0; t < NV; ++t) {
-      const float e = exp_weight(v[t] - mx);
+      const float e = exp_below<false>(v[t] - mx);
       const float p = ok[t] && v[t] != -INFINITY ? e : 0.f;
       l += p;
       if (mine) weight[wave][4 * (t * kShare + my_u) + rs][j % G] = p;

@@ -378,22 +378,31 @@ __device__ __forceinline__ int wave_inclusive_sum(int x) {
 // only keeps the compiler from moving or reusing them across (no instruction).
 __device__ __forceinline__ void wave_lds_order() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
 
+// The value of lane (lane - kBy) mod 16 of my 16 lanes.
+template <int kBy>
+__device__ __forceinline__ float row16_rotate(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + kBy, 0xf, 0xf, false));   // row_ror
+}
+template <int kBy>
+__device__ __forceinline__ double row16_rotate(double x) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x120 + kBy, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x120 + kBy, 0xf, 0xf, false));
+}
 // Sum and maximum over the 16 lanes of a row of lanes, left in every one of them (DPP rotations, no LDS).
-__device__ __forceinline__ float row16_sum(float x) {
-#define LFPS_ROT(v, n) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + (n), 0xf, 0xf, false))
-  x += LFPS_ROT(x, 8);
-  x += LFPS_ROT(x, 4);
-  x += LFPS_ROT(x, 2);
-  x += LFPS_ROT(x, 1);
+template <typename T>
+__device__ __forceinline__ T row16_sum(T x) {
+  x += row16_rotate<8>(x);
+  x += row16_rotate<4>(x);
+  x += row16_rotate<2>(x);
+  x += row16_rotate<1>(x);
   return x;
 }
 __device__ __forceinline__ float row16_max(float x) {
-  x = fmaxf(x, LFPS_ROT(x, 8));
-  x = fmaxf(x, LFPS_ROT(x, 4));
-  x = fmaxf(x, LFPS_ROT(x, 2));
-  x = fmaxf(x, LFPS_ROT(x, 1));
+  x = fmaxf(x, row16_rotate<8>(x));
+  x = fmaxf(x, row16_rotate<4>(x));
+  x = fmaxf(x, row16_rotate<2>(x));
+  x = fmaxf(x, row16_rotate<1>(x));
   return x;
-#undef LFPS_ROT
 }
 // The same sum in the order of a butterfly over lane distances 1, 2, 4, 8 (the bits of four xor shuffles), without LDS:
 // lanes of a quad by permutation, then, all lanes of a quad (of a half) being equal, the other one by mirroring.
@@ -425,17 +434,18 @@ __device__ __forceinline__ bool outgrow_cache(const Shape& s, float rows, int ro
   rows += __shfl_xor(rows, 32);
   return __builtin_amdgcn_readfirstlane(rows * (float)s.Hkv * (float)row_bytes > kept_bytes);
 }
-template <int kBy>
-__device__ __forceinline__ double row16_rotate(double x) {
-  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x120 + kBy, 0xf, 0xf, false),
-                          __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x120 + kBy, 0xf, 0xf, false));
-}
-__device__ __forceinline__ double row16_sum(double x) {
-  x += row16_rotate<8>(x);
-  x += row16_rotate<4>(x);
-  x += row16_rotate<2>(x);
-  x += row16_rotate<1>(x);
-  return x;
+// exp(y), or kScaled exp(y / sqrt(D)), for y <= 0 to about one unit in the last place: exp2 of the rounded product, corrected by the
+// product's rounding error, which grows with |y| (seven instructions; without expf's handling of other ranges: results below
+// 2^-126 are 0).  -inf gives 0, a NaN stays one.
+template <bool kScaled>
+__device__ __forceinline__ float exp_below(float y) {
+  constexpr double c = (kScaled ? 0.08838834764831845 : 1.0) * 1.4426950408889634;
+  constexpr float hi = (float)c, lo = (float)(c - (double)hi), ln2 = 0.6931471805599453f;
+  y = __builtin_elementwise_maximum(y, -1e30f);             // (the correction needs a finite y)
+  const float t = y * hi;
+  const float r = fmaf(y, lo, fmaf(y, hi, -t));
+  const float e = __builtin_amdgcn_exp2f(t);
+  return fmaf(e * ln2, r, e);
 }
 
 // Order-preserving map fp32 -> uint32 (larger float <=> larger key).

@@ -28,24 +28,6 @@ constexpr int kHistRows = 16 * kHistSub;
 constexpr float kNoScore = -FLT_MAX;   // stands for "row not seen"
 constexpr float kLeastMax = -1.7e38f;  // the largest score is taken as at least this: a row not seen weighs 0 beside any
 
-// The value of lane (lane - 1) of my 16 lanes; lane 0 receives lane 15's.
-__device__ __forceinline__ float rotate16(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xf, 0xf, false));   // row_ror:1
-}
-
-// exp(y / sqrt(D)) for y <= 0 to about one unit in the last place: exp2 of the rounded product, corrected by the product's
-// rounding error (seven instructions; without expf's handling of other ranges: results below 2^-126 are 0).  -inf gives 0,
-// a NaN stays one.
-__device__ __forceinline__ float exp_scaled(float y) {
-  constexpr double c = 0.08838834764831845 * 1.4426950408889634;            // log2(e) / sqrt(128)
-  constexpr float hi = (float)c, lo = (float)(c - (double)hi), ln2 = 0.6931471805599453f;
-  y = __builtin_elementwise_maximum(y, -1e30f);                             // (the correction below needs a finite y)
-  const float t = y * hi;
-  const float r = fmaf(y, lo, fmaf(y, hi, -t));
-  const float e = __builtin_amdgcn_exp2f(t);
-  return fmaf(e * ln2, r, e);
-}
-
 __host__ __device__ constexpr int hist_lds(int nq) { return nq * 4 * 64 * 16; }   // bytes of the operands of nq queries
 
 // MFMA A operands (layout of load_query_operand) of nq queries for the heads of group (b, g), to LDS:
@@ -207,10 +189,10 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
         const float m = fmaxf(m_old, mx);
         double l = 0.0;
 #pragma unroll
-        for (int t = 0; t < kHistSub; ++t) l += (double)exp_scaled(v[t] - m);
+        for (int t = 0; t < kHistSub; ++t) l += (double)exp_below<true>(v[t] - m);
         l = row16_sum(l);
         if (j == 0) {
-          wl[wave][jq][kb] = wl[wave][jq][kb] * (double)exp_scaled(m_old - m) + l;
+          wl[wave][jq][kb] = wl[wave][jq][kb] * (double)exp_below<true>(m_old - m) + l;
           wm[wave][jq][kb] = m;
         }
         if (my_dots) {
@@ -234,7 +216,7 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
     for (int w = 0; w < kHistWaves; ++w) m = fmaxf(m, wm[w][jq][h]);
     double l = 0.0;
 #pragma unroll
-    for (int w = 0; w < kHistWaves; ++w) l += wl[w][jq][h] * (double)exp_scaled(wm[w][jq][h] - m);
+    for (int w = 0; w < kHistWaves; ++w) l += wl[w][jq][h] * (double)exp_below<true>(wm[w][jq][h] - m);
     const int64_t o = ((int64_t)bg * gridDim.x + blockIdx.x) * (kHistBatch * G) + e;
     part_m[o] = m;
     part_l[o] = l;
@@ -253,7 +235,7 @@ __device__ __forceinline__ void merge_hist(const float* part_m, const double* pa
   for (int d = 1; d < kPer; d <<= 1) m = fmaxf(m, __shfl_xor(m, d));
   double l = 0.0;
 #pragma unroll 8
-  for (int k = sub; k < blocks; k += kPer) l += part_l[o + k * step] * (double)exp_scaled(part_m[o + k * step] - m);
+  for (int k = sub; k < blocks; k += kPer) l += part_l[o + k * step] * (double)exp_below<true>(part_m[o + k * step] - m);
 #pragma unroll
   for (int d = 1; d < kPer; d <<= 1) l += __shfl_xor(l, d);
   norm = l > 0.0 ? 1.0 / (2.0 * (double)n_queries * (1.0 - gamma) * l) : 0.0;
@@ -320,14 +302,14 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_apply(
       const float next_cin = my_carry[jq][kb];
       float up[NT];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) up[t] = rotate16(as[t]);
+      for (int t = 0; t < NT; ++t) up[t] = row16_rotate<1>(as[t]);
 #pragma unroll
       for (int t = NT - 1; t >= 0; --t) {
         if constexpr (decltype(masked)::value) {
           const int row = base + 16 * t + j;
           v[t] = row >= s.n_sink && row < n - (j0 + jq) + 1 ? v[t] : kNoScore;
         }
-        const float w = weigh(exp_scaled(v[t] - m), hi, lo);
+        const float w = weigh(exp_below<true>(v[t] - m), hi, lo);
         av[t] += w;
         const float moved = j != 0 ? up[t] : (t == 0 ? cin : up[t > 0 ? t - 1 : 0]);
         as[t] = moved + w;
@@ -468,7 +450,7 @@ __global__ __launch_bounds__(256) void k_hist_apply_one(Shape s, float* __restri
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int i = blockIdx.x * kMomentRows + u * 256 + tid;
-    x[u] = in[u] ? weigh(exp_scaled(x[u] - m), hi, lo) : 0.f;
+    x[u] = in[u] ? weigh(exp_below<true>(x[u] - m), hi, lo) : 0.f;
     if (i < s.Lcap) {
       ver[i] = x[u];
       sla[s.Lcap + i] = x[u];
