@@ -332,6 +332,8 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn(Shape s, const float
 // by log2(e) / sqrt(D), rounded once), so that an exponential needs no product whose rounding would have to be corrected.  In
 // k_full_attn's form the few tiles of a short row waited longer for each other: 1 x 8192 rows of 8 heads in bf16 10.9 -> 9.85 us,
 // in FP8 10.6 -> 9.7, 1 x 16384 in fp32 29.4 -> 28.6, 1 x 32768 in FP8 21.2 -> 19.7; 32 x 30000 in bf16 571 -> 567.
+// Paged, one look-up serves both tiles: with one each, its wait came twice as often and the compiler kept fewer loads in flight (FP8
+// 16 x 32768 169.2 -> 166.5 us, bf16 325.9 -> 323.2, 1 x 8192 11.7 -> 11.3).
 template <typename TK, typename T, bool kPaged, bool kMayOnce>
 __global__ __launch_bounds__(kAttnThreads) void k_full_attn_single(Shape s, const float* __restrict__ q,
                                                                    const TK* __restrict__ K, const T* __restrict__ V,
@@ -371,13 +373,14 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn_single(Shape s, cons
     Raw8<T> v[U];
   };
   auto clamped = [&](int r) { return r < r_end ? r : r_end - 1; };
-  // paged: row r0 + j of a tile as a physical row
-  auto rows_of = [&](int r0) { return kPaged ? Rows::phys(pg, b, clamped(r0 + j)) : 0; };
-  auto issue = [&](auto once, Tile& t, int r0, int phys) {
+  constexpr int kStep = 4 * kRows;                          // wave w takes tiles w, w + 4, ...
+  // paged: the rows of the tiles at r0 and r0 + kStep as physical rows, in lanes 0-15 and 16-31
+  auto rows_of = [&](int r0) { return kPaged ? Rows::phys(pg, b, clamped(r0 + j + (rs & 1) * kStep)) : 0; };
+  auto issue = [&](auto once, Tile& t, int r0, int phys, int first_lane) {
     int64_t off[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int p = kPaged ? __builtin_amdgcn_ds_bpermute(4 * rs + 16 * u, phys) : clamped(r0 + 4 * u + rs);
+      const int p = kPaged ? __builtin_amdgcn_ds_bpermute(4 * rs + 16 * u + 4 * first_lane, phys) : clamped(r0 + 4 * u + rs);
       off[u] = Rows::offset(pg, p, stride_b, stride_n);
     }
     load_rows<decltype(once)::value>(t.k, [&](int u) { return Kbg + off[u]; });
@@ -422,21 +425,19 @@ __global__ __launch_bounds__(kAttnThreads) void k_full_attn_single(Shape s, cons
     }
   };
 
-  constexpr int kStep = 4 * kRows;                          // wave w takes tiles w, w + 4, ...
   auto walk = [&](auto once) {
   Tile ta, tb;
   int r0 = r_begin + kRows * wave;
-  int phys_a = rows_of(r0), phys_b = rows_of(r0 + kStep);
-  issue(once, ta, r0, phys_a);
+  int phys = rows_of(r0);
+  issue(once, ta, r0, phys, 0);
   for (; r0 < r_end; r0 += 2 * kStep) {
-    phys_a = rows_of(r0 + 2 * kStep);
+    const int phys_next = rows_of(r0 + 2 * kStep);
     if constexpr (kPaged) __builtin_amdgcn_sched_barrier(0);      // the look-up before the rows: its wait must not include them
-    issue(once, tb, r0 + kStep, phys_b);
+    issue(once, tb, r0 + kStep, phys, 16);
     consume(ta, r0);
-    phys_b = rows_of(r0 + 3 * kStep);
-    if constexpr (kPaged) __builtin_amdgcn_sched_barrier(0);
-    issue(once, ta, r0 + 2 * kStep, phys_a);
+    issue(once, ta, r0 + 2 * kStep, phys_next, 0);
     consume(tb, r0 + kStep);
+    phys = phys_next;
   }
   };
   if (once_here) walk(std::true_type{});
