@@ -46,3 +46,36 @@ def test_select_from_block_maxima(L, k, values):
     assert torch.equal(idx[0], idx[1])
     assert torch.equal(sc[0].view(torch.int32), sc[1].view(torch.int32))
     ctx.close()
+
+
+# requests of different lengths (one whose row is selected from all scores), groups with lanes that compute maxima and store none, the
+# other cache formats and pages; the last budget lies past the line
+@pytest.mark.parametrize("dtype,page", [("bf16", 16), ("f16", 0), ("f16", 64), ("fp8", 0), ("fp8", 16)])
+@pytest.mark.parametrize("Hq,Hkv", [(8, 8), (8, 4), (16, 4)])
+def test_block_maxima_of_a_ragged_batch(dtype, page, Hq, Hkv):
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(Hq + page)
+    lens, budgets = [33001, 8191, 20015, 16400], [1500, 700, 1, 1020]
+    B, L, k = len(lens), max(lens) + 2, max(budgets)
+    kd = {"bf16": torch.bfloat16, "f16": torch.float16, "fp8": torch.float8_e4m3fn}[dtype]
+    nb = -(-L // page) if page else 1
+    shape = (B * nb, Hkv, page, 128) if page else (B, Hkv, L, 128)
+    K = torch.randn(shape, device=DEV, generator=g).to(kd)
+    V = torch.zeros(shape, dtype=torch.float16 if dtype == "f16" else torch.bfloat16, device=DEV)
+    q = torch.randn((B, Hq, 128), device=DEV, generator=g)
+    ctx = Lfps(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="f16" if dtype == "f16" else "bf16", max_seq_len=L, max_k=k,
+               radius=1, cand_cap=L, k_fp8=dtype == "fp8")
+    seq, ks = (torch.tensor(x, dtype=torch.int32, device=DEV) for x in (lens, budgets))
+    table = torch.randperm(B * nb, device=DEV, generator=g).view(B, nb).to(torch.int32)
+    kv = ctx.paged_kv_view(K, V, table, seq) if page else ctx.kv_view(K, V, seq)
+    idx = [torch.full((B, Hq, k), -5, dtype=torch.int32, device=DEV) for _ in range(2)]
+    sc = [torch.full((B, Hq, k), -5.0, device=DEV) for _ in range(2)]
+    ctx.lfps_exact_topk(q, kv, ks, idx[0], sc[0])
+    cand = torch.arange(ctx.cand_cap, dtype=torch.int32, device=DEV).repeat(B, Hkv, 1)
+    ctx.lfps_score_topk(q, kv, cand, seq[:, None].repeat(1, Hkv), ks, idx[1], sc[1])
+    for b, kb in enumerate(budgets):
+        assert int(idx[0][b, :, :kb].min()) >= 0
+        assert torch.equal(idx[0][b, :, :kb], idx[1][b, :, :kb])
+        assert torch.equal(sc[0][b, :, :kb].view(torch.int32), sc[1][b, :, :kb].view(torch.int32))
+    ctx.close()
