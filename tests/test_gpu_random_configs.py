@@ -40,7 +40,7 @@ def test_random_configuration_chained_steps(i):
 
 
 # Many requests with short contexts: hundreds of (request, KV group) units, so that one wave of the filtered
-# scoring kernel crosses several groups and the group tables are read in more than one batch of 64.
+# scoring kernel crosses several groups and the group tables are read in more than one batch of 256.
 MANY = [dict(Hq=32, Hkv=8, B=48, L_range=(150, 700), kmax=40, r=2, n_recent=1, n_sink=0, kv_dtype="bf16", k_dtype="",
              v_dtype="", paged=None),
         dict(Hq=8, Hkv=8, B=70, L_range=(90, 400), kmax=24, r=1, n_recent=2, n_sink=4, kv_dtype="bf16", k_dtype="fp8",
