@@ -729,11 +729,12 @@ int lfps_tables_init(lfps_ctx* ctx, const float* q_hist, int32_t n_queries, cons
   hipStream_t st = (hipStream_t)stream;
   const Shape& s = ctx->shape;
   hipError_t e = hipSuccess;
+  int moment_parts = 0;
   const bool together = ctx->cfg.kv_dtype != LFPS_F32;   // all queries in one pass over K (fp32 keys: one at a time)
   if (together) {
     LAUNCH(ctx, LFPS_KERNEL_DENSE_SCORE, st,
            launch_table_history(s, ctx->tab_ver, ctx->tab_sla, q_hist, n_queries, (double)ctx->cfg.table_decay, v,
-                                ctx->score, s.score_stride, ctx->aux, ctx->flags, st));
+                                ctx->score, s.score_stride, ctx->aux, ctx->flags, &moment_parts, st));
   } else {
     for (int j = 1; j <= n_queries; ++j) {
       LAUNCH(ctx, LFPS_KERNEL_DENSE_SCORE, st,
@@ -744,8 +745,7 @@ int lfps_tables_init(lfps_ctx* ctx, const float* q_hist, int32_t n_queries, cons
       if (e != hipSuccess) return fail(ctx, LFPS_EHIP, "lfps_tables_init", e);
     }
   }
-  e = launch_table_state(s, ctx->tab_ver, ctx->tab_sla, ctx->tab_state, v.seq_lens, ctx->aux, together && n_queries == 1,
-                         st);
+  e = launch_table_state(s, ctx->tab_ver, ctx->tab_sla, ctx->tab_state, v.seq_lens, ctx->aux, moment_parts, st);
   if (e != hipSuccess) return fail(ctx, LFPS_EHIP, "lfps_tables_init (statistics)", e);
   ctx->tab_updates = 0;
   ctx->tab_ready = 1;

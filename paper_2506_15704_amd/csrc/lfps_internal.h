@@ -244,17 +244,17 @@ hipError_t launch_table_init(const Shape& s, float* tab_ver, float* tab_sla, con
                              hipStream_t st);
 // Eq. 4 from n_queries prefill queries, kHistBatch of them per pass over K (prefill.hip; 16-bit and FP8 keys);
 // q_hist[j - 1] = query j, the j-th most recent.  dots [B, Hq, dots_stride]: room for one query's dot products.
-// scratch: table_init_scratch_bytes.
+// scratch: table_init_scratch_bytes.  *moment_parts: how many partials per head of the tables' moments it has left there (0:
+// none).
 constexpr int kHistBatch = 32;
 int64_t table_init_scratch_bytes(const Shape& s);
 hipError_t configure_table_history(const Shape& s, int k_kind);
 hipError_t launch_table_history(const Shape& s, float* tab_ver, float* tab_sla, const float* q_hist, int n_queries,
                                 double gamma, const KvView& kv, float* dots, int64_t dots_stride, void* scratch,
-                                int32_t* flags, hipStream_t st);
-// Statistics and head state of freshly written tables; have_moments: launch_table_history was called with one query
-// and has left the moments in scratch.
+                                int32_t* flags, int* moment_parts, hipStream_t st);
+// Statistics and head state of freshly written tables.
 hipError_t launch_table_state(const Shape& s, const float* tab_ver, const float* tab_sla, double* state,
-                              const int32_t* seq_lens, void* scratch, bool have_moments, hipStream_t st);
+                              const int32_t* seq_lens, void* scratch, int moment_parts, hipStream_t st);
 // Head sparsity (Eq. 5-6) and the prefill priors it needs; gate [B,Hq] marks bypassed heads, whose output
 // row (vbar) and index row (-1) the kernel writes when out != NULL.
 hipError_t launch_head_sparsity(const Shape& s, int dtype, const float* q, const KvView& kv, const float* kbar,

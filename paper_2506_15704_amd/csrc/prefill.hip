@@ -4,15 +4,18 @@
 // Eq. 4 needs, for every one of s queries and every head, the softmax of its scores over all rows it sees.  One query
 // at a time that is s passes over K (16-bit keys at 8 groups x 32K rows: 14 us of scoring that writes every score, and
 // 30 us of softmax and accumulation that reads and writes scores and tables, per query: 1.4 ms for s = 32).  K is the
-// same for all of them, so here a wave keeps 128 rows of K in registers as MFMA operands and walks the queries:
-//   k_hist_stats   per (query, head) the largest score and the sum of exponentials, in one pass over K;
-//   k_hist_apply   the scores once more (the same bits), the weights, and the sums over the queries, which never leave
-//                  registers: every table entry is written once.
+// same for all of them, so 32 queries are taken together:
+//   k_batch_stats   per (query, head) the largest score and the sum of exponentials, in one pass over K;
+//   k_batch_apply   the scores once more (the same bits), the weights, and the sums over the queries, which never leave
+//                   the chip: every table entry is written once.
 // Two passes over K are needed because a weight needs the sum over all rows; storing the scores between them would
 // cost 4 bytes per row, query and head (8.6 times the bytes of a second pass over bf16 keys at s = 32, G = 4).
-// The kernels are bound by the matrix and vector units (per 64 rows and query 16 MFMAs of 16 cycles, and about as much
-// time again in vector instructions, most of them the exponentials and the fp64 sums): 32 queries of 8 groups x 32K rows
-// take 48 + 59 us, beside 1.42 ms one query at a time.
+// With many queries both are bound by the matrix and vector units: per 16 rows and 16 (query, head) pairs 12 products of 16
+// cycles, of which a SIMD can issue two vector instructions each for nothing, and about 22 vector instructions in the first
+// kernel, 45 in the second.  32 queries of 8 groups x 32K rows: 30 + 45 us (11 + 11 by the products alone), of 64 groups x 64K
+// rows 341 + 489; before, one wave holding 128 rows and walking the queries, 49 + 59 and 1140 together.  With few queries they
+// are bound by the bytes of K: 4 queries of 64 groups x 64K rows 200 + 265 us for 1.07 GB each and 0.2 GB of tables.
+// A single query takes k_hist_stats and k_hist_apply_one instead: its scores are few enough to store.
 #include "lfps_internal.h"
 #include "score_mfma.h"
 
@@ -27,40 +30,6 @@ constexpr int kHistSub = 8;            // 16-row sub-tiles a wave holds: 128 row
 constexpr int kHistRows = 16 * kHistSub;
 constexpr float kNoScore = -FLT_MAX;   // stands for "row not seen"
 constexpr float kLeastMax = -1.7e38f;  // the largest score is taken as at least this: a row not seen weighs 0 beside any
-
-__host__ __device__ constexpr int hist_lds(int nq) { return nq * 4 * 64 * 16; }   // bytes of the operands of nq queries
-
-// MFMA A operands (layout of load_query_operand) of nq queries for the heads of group (b, g), to LDS:
-// entry (jq * 4 + kk) * 64 + lane.  A thread makes the three terms (and the zero row) of 8 channels of one head.
-// Returns true if it met an element beyond the fp16 range.
-template <int G, typename Op>
-__device__ __forceinline__ bool stage_hist_operands(Op* lds, const float* __restrict__ q0, int64_t q_stride,
-                                                    int64_t head0, int nq) {
-  bool clipped = false;
-  for (int u = threadIdx.x; u < nq * 64; u += kHistWaves * 64) {
-    const int jq = u >> 6, h = (u >> 4) & 3, kk = (u >> 2) & 3, kb = u & 3;
-    Op* e = lds + (jq * 4 + kk) * 64 + kb * 16 + 4 * h;
-    const float4* p = reinterpret_cast<const float4*>(q0 + jq * q_stride + (head0 + (h < G ? h : 0)) * kD) + 2 * (kk + 4 * kb);
-    const float4 lo = p[0], hi = p[1];
-    float f[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-    if constexpr (Split3<Op>::kHalf) {
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        if (fabsf(f[c]) > 65504.0f) {
-          clipped |= h < G;
-          f[c] = copysignf(65504.0f, f[c]);
-        }
-      }
-    }
-    Op term[3];
-    Split3<Op>::all(f, term);
-    const uint32_t live = h < G ? ~0u : 0u;                // (by bits: from a choice the compiler makes two branches)
-#pragma unroll
-    for (int t = 0; t < 3; ++t) e[t] = __builtin_bit_cast(Op, __builtin_bit_cast(u32x4, term[t]) & live);
-    e[3] = Op{};
-  }
-  return clipped;
-}
 
 // NT sub-tiles of K rows as MFMA operands: lane (j, kb) holds its channels of the rows base + 16 t + j.  Rows past the
 // sequence read its last row.
@@ -102,11 +71,8 @@ struct HistTile {
       for (int kk = 0; kk < 4; ++kk) x[t][kk] = sub.operand(kk);
     }
   }
-  // v[t] = q . K (not yet divided by sqrt(D)) of my row of sub-tile t for head kb and the query whose operands start at a
-  __device__ __forceinline__ void dots(const Op* a, int lane, float (&v)[NT]) const {
-    Op A[4];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) A[kk] = a[kk * 64 + lane];
+  // v[t] = q . K (not yet divided by sqrt(D)) of my row of sub-tile t for head kb
+  __device__ __forceinline__ void dots(const Op (&A)[4], float (&v)[NT]) const {
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -124,110 +90,94 @@ __device__ __forceinline__ void wave_run(int tiles, int w, int waves, int& lo, i
   hi = lo + per < tiles ? lo + per : tiles;
 }
 
-// grid (blocks per group, B*Hkv).  Queries j0 .. j0 + nq - 1 (j = 1: the most recent); query j sees the offloaded rows
-// [n_sink, n - j + 1).  part_m / part_l [bg, block, jq, h]: the largest q . K and the sum of the exponentials relative
-// to it over the rows of the block (kLeastMax and 0 when it has none).  dots (or NULL; one query only): every q . K,
-// [B, Hq, stride].
-// kMayOnce: rows past the caches (StreamTile; its LDS lies behind the operands) where the requests hold more than kept_bytes of
-// them, see stats_kept_bytes.
+// One query, which sees the offloaded rows [n_sink, n).  grid (blocks per group, B*Hkv).  part_m / part_l [bg, block, jq, h]
+// (jq = 0): the largest q . K and the sum of the exponentials relative to it over the rows of the block (kLeastMax and 0 when it
+// has none).  dots [B, Hq, stride]: every q . K.
+// kMayOnce: rows past the caches (StreamTile) where the requests hold more than kept_bytes of them, see stats_kept_bytes.
 template <int G, bool kPaged, int kKind, bool kMayOnce>
 __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
-    Shape s, const float* __restrict__ q0, int64_t q_stride, int j0, int nq, const void* __restrict__ K,
-    int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage pg, const int32_t* __restrict__ seq_lens,
-    float* __restrict__ part_m, double* __restrict__ part_l, float* __restrict__ dots, int64_t dots_stride,
-    int32_t* __restrict__ flags, float kept_bytes) {
+    Shape s, const float* __restrict__ q, const void* __restrict__ K, int64_t stride_b, int64_t stride_h, int64_t stride_n,
+    KvPage pg, const int32_t* __restrict__ seq_lens, float* __restrict__ part_m, double* __restrict__ part_l,
+    float* __restrict__ dots, int64_t dots_stride, int32_t* __restrict__ flags, float kept_bytes) {
   using Tile = HistTile<kPaged, kKind, kHistSub>;
   using Op = typename Tile::Op;
-  extern __shared__ char lds_raw[];
-  Op* ops = reinterpret_cast<Op*>(lds_raw);
-  __shared__ float wm[kHistWaves][kHistBatch][4];
-  __shared__ double wl[kHistWaves][kHistBatch][4];
+  __shared__ u32x4 turn[kMayOnce ? kHistWaves : 1][StreamTile<kKind>::kLdsChunks];
+  __shared__ float wm[kHistWaves][4];
+  __shared__ double wl[kHistWaves][4];
   const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, kb = lane >> 4;
   int n = seq_lens[b];
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   const float held = kMayOnce ? held_rows(s, seq_lens) : 0.f;
-  report_q_range(stage_hist_operands<G>(ops, q0, q_stride, (int64_t)b * s.Hq + (int64_t)g * G, nq), flags);
-  for (int e = tid; e < kHistWaves * kHistBatch * 4; e += kHistWaves * 64) {
-    (&wm[0][0][0])[e] = kLeastMax;
-    (&wl[0][0][0])[e] = 0.0;
-  }
+  const int64_t head0 = (int64_t)b * s.Hq + (int64_t)g * G;
+  Op A[4];
+  report_q_range(load_query_operand(A, q, head0, G, j, kb), flags);
   const bool once = kMayOnce && outgrow_cache(s, held, kD * KSub<kKind>::kElemBytes, kept_bytes);
-  __syncthreads();
   const char* Kbg = static_cast<const char*>(K) + RowMap<kPaged>::base(b, g, stride_b, stride_h) * KSub<kKind>::kElemBytes;
-  float* my_dots = dots && kb < G ? dots + ((int64_t)b * s.Hq + (int64_t)g * G + kb) * dots_stride : nullptr;
+  float* my_dots = kb < G ? dots + (head0 + kb) * dots_stride : nullptr;
+  float m = kLeastMax;                                     // of head kb (all sixteen lanes)
+  double sum = 0.0;
   int lo, hi;
   wave_run((n + kHistRows - 1) / kHistRows, blockIdx.x * kHistWaves + wave, gridDim.x * kHistWaves, lo, hi);
   for (int tile = lo; tile < hi; ++tile) {
     const int base = tile * kHistRows;
     Tile T;
     if (kMayOnce && once)                                  // (a copy of the loop each: 1.5 us slower at 64 groups x 17K rows)
-      T.load_once(Kbg, pg, b, stride_b, stride_n, base, n, lane,
-                  reinterpret_cast<u32x4*>(lds_raw + hist_lds(nq)) + wave * StreamTile<kKind>::kLdsChunks);
+      T.load_once(Kbg, pg, b, stride_b, stride_n, base, n, lane, turn[kMayOnce ? wave : 0]);
     else
       T.load(Kbg, pg, b, stride_b, stride_n, base, n, j, kb);
-    // a tile of which every query sees every row needs no masks (wave-uniform)
-    const bool whole = base >= s.n_sink && base + kHistRows <= n - (j0 + nq - 1) + 1;
-    auto walk = [&](auto masked) {
-      for (int jq = 0; jq < nq; ++jq) {
-        float v[kHistSub];
-        T.dots(ops + jq * 256, lane, v);
-        if constexpr (decltype(masked)::value) {
-          const int seen = n - (j0 + jq) + 1;
+    __builtin_amdgcn_sched_barrier(0);                     // (all rows asked for before the first product)
+    float v[kHistSub];
+    T.dots(A, v);
+    if (!(base >= s.n_sink && base + kHistRows <= n)) {    // (wave-uniform)
 #pragma unroll
-          for (int t = 0; t < kHistSub; ++t) {
-            const int row = base + 16 * t + j;
-            v[t] = row >= s.n_sink && row < seen ? v[t] : kNoScore;
-          }
-        }
-        float mx = v[0];
-#pragma unroll
-        for (int t = 1; t < kHistSub; ++t) mx = fmaxf(mx, v[t]);
-        mx = row16_max(mx);
-        const float m_old = wm[wave][jq][kb];
-        const float m = fmaxf(m_old, mx);
-        double l = 0.0;
-#pragma unroll
-        for (int t = 0; t < kHistSub; ++t) l += (double)exp_below<true>(v[t] - m);
-        l = row16_sum(l);
-        if (j == 0) {
-          wl[wave][jq][kb] = wl[wave][jq][kb] * (double)exp_below<true>(m_old - m) + l;
-          wm[wave][jq][kb] = m;
-        }
-        if (my_dots) {
-#pragma unroll
-          for (int t = 0; t < kHistSub; ++t) {
-            const int row = base + 16 * t + j;
-            if (row < n) my_dots[row] = v[t];
-          }
-        }
+      for (int t = 0; t < kHistSub; ++t) {
+        const int row = base + 16 * t + j;
+        v[t] = row >= s.n_sink && row < n ? v[t] : kNoScore;
       }
-    };
-    if (whole) walk(std::false_type{});
-    else walk(std::true_type{});
-    wave_lds_order();                                      // wm of this tile before the other lanes read it in the next
-  }
-  __syncthreads();
-  for (int e = tid; e < nq * G; e += kHistWaves * 64) {
-    const int jq = e / G, h = e % G;
-    float m = kLeastMax;
+    }
+    float mx = v[0];
 #pragma unroll
-    for (int w = 0; w < kHistWaves; ++w) m = fmaxf(m, wm[w][jq][h]);
+    for (int t = 1; t < kHistSub; ++t) mx = fmaxf(mx, v[t]);
+    const float top = fmaxf(m, row16_max(mx));
     double l = 0.0;
 #pragma unroll
-    for (int w = 0; w < kHistWaves; ++w) l += wl[w][jq][h] * (double)exp_below<true>(wm[w][jq][h] - m);
-    const int64_t o = ((int64_t)bg * gridDim.x + blockIdx.x) * (kHistBatch * G) + e;
-    part_m[o] = m;
+    for (int t = 0; t < kHistSub; ++t) l += (double)exp_below<true>(v[t] - top);
+    sum = sum * (double)exp_below<true>(m - top) + row16_sum(l);
+    m = top;
+    if (my_dots) {
+#pragma unroll
+      for (int t = 0; t < kHistSub; ++t) {
+        const int row = base + 16 * t + j;
+        if (row < n) my_dots[row] = v[t];
+      }
+    }
+  }
+  if (j == 0) {
+    wm[wave][kb] = m;
+    wl[wave][kb] = sum;
+  }
+  __syncthreads();
+  if (tid < G) {
+    float top = kLeastMax;
+#pragma unroll
+    for (int w = 0; w < kHistWaves; ++w) top = fmaxf(top, wm[w][tid]);
+    double l = 0.0;
+#pragma unroll
+    for (int w = 0; w < kHistWaves; ++w) l += wl[w][tid] * (double)exp_below<true>(wm[w][tid] - top);
+    const int64_t o = ((int64_t)bg * gridDim.x + blockIdx.x) * (kHistBatch * G) + tid;
+    part_m[o] = top;
     part_l[o] = l;
   }
 }
 
 // The partials of one (query, head), merged by kPer neighbouring lanes (sub = 0 .. kPer - 1): the largest dot
-// product, and the factor 1 / (2 s (1 - gamma) sum) that turns an exponential into a table contribution.
-template <int kPer>
+// product, and the factor 1 / (2 s (1 - gamma) sum) that turns an exponential into a table contribution.  weight(x): the
+// exponential of a difference x of two of the partials' maxima.
+template <int kPer, typename Weight>
 __device__ __forceinline__ void merge_hist(const float* part_m, const double* part_l, int64_t o, int64_t step, int blocks,
-                                           int sub, double gamma, int n_queries, float& m, double& norm) {
+                                           int sub, double gamma, int n_queries, float& m, double& norm, Weight weight) {
   m = kLeastMax;
 #pragma unroll 8
   for (int k = sub; k < blocks; k += kPer) m = fmaxf(m, part_m[o + k * step]);
@@ -235,7 +185,7 @@ __device__ __forceinline__ void merge_hist(const float* part_m, const double* pa
   for (int d = 1; d < kPer; d <<= 1) m = fmaxf(m, __shfl_xor(m, d));
   double l = 0.0;
 #pragma unroll 8
-  for (int k = sub; k < blocks; k += kPer) l += part_l[o + k * step] * (double)exp_below<true>(part_m[o + k * step] - m);
+  for (int k = sub; k < blocks; k += kPer) l += part_l[o + k * step] * (double)weight(part_m[o + k * step] - m);
 #pragma unroll
   for (int d = 1; d < kPer; d <<= 1) l += __shfl_xor(l, d);
   norm = l > 0.0 ? 1.0 / (2.0 * (double)n_queries * (1.0 - gamma) * l) : 0.0;
@@ -244,177 +194,584 @@ __device__ __forceinline__ void merge_hist(const float* part_m, const double* pa
 // e * norm rounded once to fp32 (norm = hi + lo).
 __device__ __forceinline__ float weigh(float e, float hi, float lo) { return fmaf(e, hi, e * lo); }
 
-// The same grid and queries.  Adds  w_j(i) / (2 s (1 - gamma))  to the vertical table at i and to the slash table at
-// i + j - 1, for all nq queries at once; the first batch (j0 = 1) writes the tables whole (zeros past the sequence and
-// in the lower half of the slash frame), later batches add to them.
-// The slash sums need no scatter: walked from the oldest query of the batch to the newest, with the running sums moved
-// one row up before each query's weights are added, row p ends with sum_i w_{j0 + i}(p - i), which belongs at slash
-// position p + j0 - 1.  Lanes are consecutive rows, so the move is a rotation inside 16 lanes; the value that enters a
-// tile at its first row was left per query by the tile before (carry).  A wave starts its run of tiles with the 32
-// rows before it, for their carries alone (a batch reaches back at most 31 rows).
-template <int G, bool kPaged, int kKind>
-__global__ __launch_bounds__(kHistWaves * 64) void k_hist_apply(
-    Shape s, float* __restrict__ tab_ver, float* __restrict__ tab_sla, const float* __restrict__ q0, int64_t q_stride,
-    int j0, int nq, const void* __restrict__ K, int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage pg,
-    const int32_t* __restrict__ seq_lens, const float* __restrict__ part_m, const double* __restrict__ part_l,
-    double gamma, int n_queries) {
+// M1..M4 of a table's entries, then the smallest and the negated largest.
+struct TableMoments {
+  double m[4] = {0, 0, 0, 0};
+  float e[2] = {INFINITY, INFINITY};
+  __device__ __forceinline__ void add(float x) {
+    const double a = x;
+    m[0] += a; m[1] += a * a; m[2] += a * a * a; m[3] += a * a * a * a;
+    e[0] = fminf(e[0], x); e[1] = fminf(e[1], -x);
+  }
+  __device__ __forceinline__ void reduce_wave() {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      m[p] = row16_sum(m[p]);
+      m[p] += __shfl_xor(m[p], 16);
+      m[p] += __shfl_xor(m[p], 32);
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      e[p] = -row16_max(-e[p]);
+      e[p] = fminf(e[p], __shfl_xor(e[p], 16));
+      e[p] = fminf(e[p], __shfl_xor(e[p], 32));
+    }
+  }
+  __device__ __forceinline__ void store(double* to) const {                // six values
+#pragma unroll
+    for (int p = 0; p < 4; ++p) to[p] = m[p];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) to[4 + p] = (double)e[p];
+  }
+};
+
+// Of both tables' entries of a workgroup (256 threads, U positions each, those with in[u]): M1..M4 of the vertical and of the slash
+// table, then the smallest and the negated largest of both, to out[0:12].
+template <int U>
+__device__ __forceinline__ void moments_of_chunk(const float (&xv)[U], const float (&xs)[U], const bool (&in)[U],
+                                                 double* __restrict__ out) {
+  __shared__ double red[4][2][6];
+  const int tid = threadIdx.x;
+  TableMoments v, x;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (!in[u]) continue;
+    v.add(xv[u]);
+    x.add(xs[u]);
+  }
+  v.reduce_wave();
+  x.reduce_wave();
+  if ((tid & 63) == 0) {
+    v.store(red[tid >> 6][0]);
+    x.store(red[tid >> 6][1]);
+  }
+  __syncthreads();
+  if (tid < 12) {
+    const int table = tid < 8 ? tid >> 2 : (tid - 8) >> 1, at = tid < 8 ? tid & 3 : 4 + (tid & 1);
+    double t = red[0][table][at];
+    for (int w = 1; w < 4; ++w) t = tid < 8 ? t + red[w][table][at] : fmin(t, red[w][table][at]);
+    out[tid] = t;
+  }
+}
+
+// ----------------------------------------------------------------------------- many queries
+// Both kernels take the K rows of a workgroup in chunks through LDS (as 16-bit operands, two chunks there and one
+// more on its way in registers), and every wave keeps its queries: sixteen (query, head) pairs, a unit, are the sixteen rows
+// of an MFMA A operand, the three terms of the query one operand each.  (With the terms as rows of one operand, sixteen rows were
+// four heads of one query and four of them zeros; with the rows in registers and the queries walked, every workgroup first
+// loaded all of its rows and then computed, and each query's maximum and sum took a reduction over lanes per 128 rows.)
+// U waves (2, 4, 8) of the eight of a workgroup hold the units of a batch; where that is not all eight, the workgroup's rows are
+// cut into 8 / U spans of their own, and a chunk of R rows holds R U / 8 of each.  Row 4 i + c of an operand (D: lane group i,
+// register c) is query 4 quad + c, quad = unit * 4 / G + i / G, of head i % G.
+constexpr int kBatchThreads = 64 * kHistWaves;
+// 16-byte pieces from row to row, and the piece that lane group kb takes at step kk: a read of the wave is served 16 lanes at a
+// time, lanes 0-3 and 12-15 of an even group with 4-11 of the next odd one and the other way round, which meet in no bank so (with
+// rows 17 apart and pieces kk + 4 kb every read waited half its time again).
+constexpr int kChunkPitch = kD / 8 + 2;
+__device__ __forceinline__ constexpr int chunk_piece(int kk, int kb) { return 2 * kk + (kb & 1) + 8 * (kb >> 1); }
+template <int U, int R>
+struct BatchShape {
+  static constexpr int kRows = R;
+  static constexpr int kPieces = R * kChunkPitch;
+  static constexpr int kSpans = kHistWaves / U;
+  static constexpr int kSpanRows = R / kSpans;             // of a chunk
+  static constexpr int kSubs = kSpanRows / 16;             // sub-tiles of 16 rows a wave takes of a chunk
+};
+constexpr int kStatsRows = 64, kApplyRows = 128;
+
+// The rows of a workgroup's chunks: from memory to registers, from there to LDS, by the first kThreads of its threads.
+template <bool kPaged, int kKind, typename B, int kThreads>
+struct ChunkRows {
+  static constexpr int kPieces = kD * KSub<kKind>::kElemBytes / 16;      // of a row
+  static constexpr int kStep = kThreads / kPieces;                       // rows of one load
+  static constexpr int kLoads = B::kRows / kStep;
+  static_assert(kLoads * kStep == B::kRows, "whole loads");
+  u32x4 raw[kLoads];
+  int phys[kPaged ? kLoads : 1];                           // paged: mine of the chunk to fetch next
+  int next, span_rows, n;                                  // that chunk's first row, rows from span to span
+  __device__ __forceinline__ int phys_of(const KvPage& pg, int b, int i) const {       // (outside the sequence: a row of it)
+    const int at = (int)threadIdx.x / kPieces + i * kStep;
+    const int row = next + at / B::kSpanRows * span_rows + at % B::kSpanRows;
+    return RowMap<kPaged>::phys(pg, b, row < 0 ? 0 : (row < n ? row : n - 1));
+  }
+  __device__ __forceinline__ void start(const KvPage& pg, int b, int first, int span_rows_, int n_) {
+    n = n_;
+    next = first;
+    span_rows = span_rows_;
+    if constexpr (kPaged) {
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) phys[i] = phys_of(pg, b, i);
+    }
+  }
+  // my pieces of the next chunk; the block table is asked one chunk ahead
+  __device__ __forceinline__ void fetch(const char* Kbg, const KvPage& pg, int b, int64_t stride_b, int64_t stride_n, bool once) {
+    auto at = [&](int i) {
+      const int p = kPaged ? phys[kPaged ? i : 0] : phys_of(pg, b, i);
+      return reinterpret_cast<const u32x4*>(Kbg + RowMap<kPaged>::offset(pg, p, stride_b, stride_n) * KSub<kKind>::kElemBytes) +
+             (int)threadIdx.x % kPieces;
+    };
+    if (once) {
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) raw[i] = __builtin_nontemporal_load(at(i));
+    } else {
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) raw[i] = *at(i);
+    }
+    next += B::kSpanRows;
+    if constexpr (kPaged) {
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) phys[i] = phys_of(pg, b, i);
+    }
+  }
+  __device__ __forceinline__ void put(u32x4* chunk) const {
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      u32x4* to = chunk + ((int)threadIdx.x / kPieces + i * kStep) * kChunkPitch;
+      if constexpr (kKind == kKindFp8) {
+        to += 2 * ((int)threadIdx.x % kPieces);
+        to[0] = __builtin_bit_cast(u32x4, fp8x8_to_bf16x8(raw[i][0], raw[i][1]));
+        to[1] = __builtin_bit_cast(u32x4, fp8x8_to_bf16x8(raw[i][2], raw[i][3]));
+      } else {
+        to[(int)threadIdx.x % kPieces] = raw[i];
+      }
+    }
+  }
+};
+
+// The A operands of a unit: the terms of 4 log2(e) / sqrt(D) times the queries, so that a quarter of a product is the power of two
+// that its row weighs.  The factor is applied to more than 24 bits and the three terms hold that: a weight is then one fused
+// subtraction of the maximum and one exp2, without the product of a rounded score with a rounded factor in between (with the
+// plain queries, the factor and its rounding made good in exp_below, the vector instructions bound both kernels: 14 a product in
+// the first and 17 in the second, now 6 and 11).  (4: an element of the largest size does not overflow.)
+constexpr float kProductUnit = 0.25f;
+__device__ __forceinline__ float product_weight(float x, float top) {
+  return __builtin_amdgcn_exp2f(fmaf(x, kProductUnit, -kProductUnit * top));
+}
+template <int G, typename Op>
+struct UnitQueries {
+  Op a[3][4];
+  __device__ static __forceinline__ void terms(float f, Op (&e)[3], int c) {
+    constexpr double factor = 4.0 * 0.08838834764831845 * 1.4426950408889634;
+    constexpr float hi = (float)factor, lo = (float)(factor - (double)hi);
+    using Elem = std::remove_reference_t<decltype(e[0][0] + e[0][0])>;
+    constexpr float kUp = Split3<Op>::kHalf ? 2048.0f : 1.0f;              // as Split3's terms are scaled
+    float x = f * hi;
+    asm("" : "+v"(x));                                     // (one value: not rounded to 16 bits from the product in one place)
+    const float rest = fmaf(f, lo, fmaf(f, hi, -x));
+    const Elem t0 = (Elem)x;
+    x -= (float)t0;
+    const Elem t1 = (Elem)(x * kUp);
+    x = fmaf((float)t1, -1.0f / kUp, x) + rest;
+    e[0][c] = t0;
+    e[1][c] = t1;
+    e[2][c] = (Elem)(x * (kUp * kUp));
+  }
+  // Returns true if it met an element beyond the fp16 range.
+  __device__ __forceinline__ bool load(const float* __restrict__ q0, int64_t q_stride, int64_t head0, int nq, int unit, int lane) {
+    const int m = lane & 15, i = m >> 2;
+    const int jq = 4 * (unit * (4 / G) + i / G) + (m & 3);
+    const bool live = jq < nq;
+    const float4* p = reinterpret_cast<const float4*>(q0 + (live ? jq : 0) * q_stride + (head0 + i % G) * kD);
+    float4 x[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) x[c] = p[2 * chunk_piece(c >> 1, lane >> 4) + (c & 1)];
+    bool clipped = false;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const float4 lo = x[2 * kk], hi = x[2 * kk + 1];
+      float f[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+      if constexpr (Split3<Op>::kHalf) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          if (fabsf(f[c]) > 65504.0f) {
+            clipped |= live;
+            f[c] = copysignf(65504.0f, f[c]);
+          }
+        }
+      }
+      Op term[3];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) terms(f[c], term, c);
+      const uint32_t keep = live ? ~0u : 0u;
+#pragma unroll
+      for (int t = 0; t < 3; ++t) a[t][kk] = __builtin_bit_cast(Op, __builtin_bit_cast(u32x4, term[t]) & keep);
+    }
+    return clipped;
+  }
+  // [c]: the product of the unit's rows 4 (lane >> 4) + c with the K row of my lane & 15, whose operands are k.  bf16: all terms in
+  // one sum, the small ones first.
+  __device__ __forceinline__ f32x4 dots(const Op (&k)[4]) const {
+    f32x4 acc[3] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    constexpr bool kApart = Split3<Op>::kHalf;             // fp16 terms are scaled differently
+#pragma unroll
+    for (int t = 2; t >= 0; --t)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) acc[kApart ? t : 0] = mfma16(a[t][kk], k[kk], acc[kApart ? t : 0]);
+    if constexpr (kApart) {
+      f32x4 v;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)                          // (small ones first: the least of them alone would round away)
+        v[c] = fmaf(fmaf(acc[2][c], 1.0f / 2048.0f, acc[1][c]), 1.0f / 2048.0f, acc[0][c]);
+      return v;
+    }
+    return acc[0];
+  }
+};
+
+// The operands of a K row in a chunk (x: the first piece of my lane group).
+template <typename Op>
+__device__ __forceinline__ void read_operands(Op (&k)[4], const u32x4* x) {
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) k[kk] = __builtin_bit_cast(Op, x[chunk_piece(kk, 0)]);
+}
+
+// The products of a wave's unit with the sub-tiles kFrom .. kSubs - 1 of a chunk (x: the first piece of my row of its first
+// sub-tile), and beside those of a sub-tile what is to be done with the ones before: use(sub-tile, products), about kBeside vector
+// instructions between two products.  (The matrix unit works on while a wave issues other instructions, two for each product; left
+// to itself the compiler puts all products of a sub-tile first.)
+template <int kSubs, int kFrom, int kBeside, int kAt, int G, typename Op, typename Use>
+__device__ __forceinline__ void walk_chunk_from(const UnitQueries<G, Op>& queries, const u32x4* x, const Op (&k)[4], const f32x4& before,
+                                                Use use) {
+  Op ahead[4];
+  if constexpr (kAt + 1 < kSubs) read_operands(ahead, x + 16 * (kAt + 1) * kChunkPitch);
+  f32x4 v = before;
+  if constexpr (kAt < kSubs) v = queries.dots(k);
+  if constexpr (kAt > kFrom) use(kAt - 1, before);
+  if constexpr (kAt > kFrom && kAt < kSubs) {
+    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);     // LDS reads
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+      __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);     // a product
+      __builtin_amdgcn_sched_group_barrier(0x2, kBeside, 0);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (kAt < kSubs) walk_chunk_from<kSubs, kFrom, kBeside, kAt + 1>(queries, x, ahead, v, use);
+}
+template <int kSubs, int kFrom, int kBeside, int G, typename Op, typename Use>
+__device__ __forceinline__ void walk_chunk(const UnitQueries<G, Op>& queries, const u32x4* x, Use use) {
+  Op k[4];
+  read_operands(k, x + 16 * kFrom * kChunkPitch);
+  walk_chunk_from<kSubs, kFrom, kBeside, kFrom>(queries, x, k, f32x4{0.f, 0.f, 0.f, 0.f}, use);
+}
+
+// Where a workgroup and a wave of it work: chunks, and the rows [first, first + span_rows) of the wave's span.
+template <int U, typename B>
+struct BatchWork {
+  int chunks, wg_first, wg_rows, unit, span, span_rows, first;
+  __device__ __forceinline__ BatchWork(int n, int wave) {
+    const int tiles = (n + B::kRows - 1) / B::kRows;
+    const int per = (tiles + (int)gridDim.x - 1) / (int)gridDim.x;
+    wg_rows = per * B::kRows;
+    wg_first = (int)blockIdx.x * wg_rows;
+    chunks = wg_first < n ? per : 0;                       // (workgroup-uniform)
+    unit = wave % U;
+    span = wave / U;
+    span_rows = per * B::kSpanRows;
+    first = wg_first + span * span_rows;
+  }
+};
+
+// How far query jq of a batch of nq sees: rows below (0: no such query), and how far all queries of a unit do.
+__device__ __forceinline__ int seen_by(int jq, int j0, int nq, int n) { return jq < nq ? n - (j0 + jq) + 1 : 0; }
+template <int G>
+__device__ __forceinline__ int seen_by_all(int unit, int j0, int nq, int n) {
+  return seen_by((unit + 1) * (16 / G) - 1, j0, nq, n);
+}
+
+// grid (blocks per group, B*Hkv).  Queries j0 .. j0 + nq - 1 (j = 1: the most recent); query j sees the offloaded rows
+// [n_sink, n - j + 1).  part_m / part_l [bg, block, jq, h]: the largest product and the sum of the weights relative to it over
+// the rows of the block (kLeastMax and 0 when it has none).
+// A lane keeps the maximum and the sum of its own rows (of four queries) to the end.  Two workgroups per CU: four waves on a SIMD,
+// of which some are at their products while others are not.
+template <int G, bool kPaged, int kKind, int U>
+__global__ __launch_bounds__(kBatchThreads, 4) void k_batch_stats(
+    Shape s, const float* __restrict__ q0, int64_t q_stride, int j0, int nq, const void* __restrict__ K,
+    int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage pg, const int32_t* __restrict__ seq_lens,
+    float* __restrict__ part_m, double* __restrict__ part_l, int32_t* __restrict__ flags, float kept_bytes) {
+  using B = BatchShape<U, kStatsRows>;
   using Op = typename KSub<kKind>::Operand;
-  extern __shared__ char lds_raw[];
-  Op* ops = reinterpret_cast<Op*>(lds_raw);
-  __shared__ float ref[kHistBatch][4][3];                  // largest dot product, factor as a pair of floats
-  __shared__ float carry[kHistWaves][kHistBatch][4];
+  __shared__ u32x4 chunk[2][B::kPieces];
+  __shared__ float wm[kHistWaves][16];
+  __shared__ double wl[kHistWaves][16];
   const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, kb = lane >> 4;
   int n = seq_lens[b];
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
-  (void)stage_hist_operands<G>(ops, q0, q_stride, (int64_t)b * s.Hq + (int64_t)g * G, nq);   // (k_hist_stats reported the range)
-  {
-    static_assert(kHistWaves * 64 == kHistBatch * 4 * 4, "four lanes per query and head");
-    const int jq = tid >> 4, h = (tid >> 2) & 3, sub = tid & 3;
-    if (jq < nq && h < G) {                                // uniform over the four lanes
-      float m;
-      double norm;
-      merge_hist<4>(part_m, part_l, (int64_t)bg * gridDim.x * (kHistBatch * G) + jq * G + h, kHistBatch * G, gridDim.x,
-                    sub, gamma, n_queries, m, norm);
-      const float hi = (float)norm;
-      ref[jq][h][0] = m;
-      ref[jq][h][1] = hi;
-      ref[jq][h][2] = (float)(norm - (double)hi);
-    }
-  }
-  for (int e = tid; e < kHistWaves * kHistBatch * 4; e += kHistWaves * 64) (&carry[0][0][0])[e] = 0.f;
-  __syncthreads();
-
+  const bool once = outgrow_cache(s, held_rows(s, seq_lens), kD * KSub<kKind>::kElemBytes, kept_bytes);
+  const BatchWork<U, B> work(n, wave);
   const char* Kbg = static_cast<const char*>(K) + RowMap<kPaged>::base(b, g, stride_b, stride_h) * KSub<kKind>::kElemBytes;
-  const int64_t bh = (int64_t)b * s.Hq + (int64_t)g * G + (kb < G ? kb : 0);
-  float* ver = tab_ver + bh * s.Lcap;
-  float* sla = tab_sla + bh * 2 * s.Lcap;                  // position p of an untouched table is slot Lcap + p
-  float(*my_carry)[4] = carry[wave];
-  const int kh = kb < G ? kb : 0;
-  auto walk = [&](auto& T, int base, auto& av, auto& as, auto masked) {
-    constexpr int NT = sizeof(av) / sizeof(float);
-    float cin = 0.f;                                       // what enters at row `base` from the row before
-    for (int jq = nq - 1; jq >= 0; --jq) {
-      float v[NT];
-      T.dots(ops + jq * 256, lane, v);
-      const float m = ref[jq][kh][0], hi = ref[jq][kh][1], lo = ref[jq][kh][2];
-      const float next_cin = my_carry[jq][kb];
-      float up[NT];
+  float m[4];
+  double l[4];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) up[t] = row16_rotate<1>(as[t]);
-#pragma unroll
-      for (int t = NT - 1; t >= 0; --t) {
-        if constexpr (decltype(masked)::value) {
-          const int row = base + 16 * t + j;
-          v[t] = row >= s.n_sink && row < n - (j0 + jq) + 1 ? v[t] : kNoScore;
-        }
-        const float w = weigh(exp_below<true>(v[t] - m), hi, lo);
-        av[t] += w;
-        const float moved = j != 0 ? up[t] : (t == 0 ? cin : up[t > 0 ? t - 1 : 0]);
-        as[t] = moved + w;
-      }
-      if (j == 15) my_carry[jq][kb] = as[NT - 1];
-      cin = next_cin;
-    }
-    wave_lds_order();                                      // the carries before the other lanes read them for the next rows
-  };
-  auto walk_rows = [&](auto& T, int base, auto& av, auto& as) {
-    constexpr int NT = sizeof(av) / sizeof(float);
-    if (base >= s.n_sink && base + 16 * NT <= n - (j0 + nq - 1) + 1) walk(T, base, av, as, std::false_type{});
-    else walk(T, base, av, as, std::true_type{});
-  };
-  const int tiles = (n + kHistRows - 1) / kHistRows;
-  int lo, hi;
-  wave_run(tiles, blockIdx.x * kHistWaves + wave, gridDim.x * kHistWaves, lo, hi);
-  if (lo < hi && lo > 0 && nq > 1) {
-    HistTile<kPaged, kKind, 2> T;
-    const int base = lo * kHistRows - 32;
-    T.load(Kbg, pg, b, stride_b, stride_n, base, n, j, kb);
-    float av[2] = {0.f, 0.f}, as[2] = {0.f, 0.f};
-    walk_rows(T, base, av, as);
+  for (int c = 0; c < 4; ++c) {
+    m[c] = kLeastMax;
+    l[c] = 0.0;
   }
+  if (work.chunks > 0) {
+    ChunkRows<kPaged, kKind, B, kBatchThreads> rows;
+    rows.start(pg, b, work.wg_first, work.span_rows, n);
+    rows.fetch(Kbg, pg, b, stride_b, stride_n, once);
+    UnitQueries<G, Op> queries;
+    report_q_range(queries.load(q0, q_stride, (int64_t)b * s.Hq + (int64_t)g * G, nq, work.unit, lane), flags);
+    const int all_see = seen_by_all<G>(work.unit, j0, nq, n);
+    const bool idle = work.unit * (16 / G) >= nq;          // (wave-uniform: a unit of no query)
+    for (int at = 0; at < work.chunks; ++at) {
+      rows.put(chunk[at & 1]);
+      rows.fetch(Kbg, pg, b, stride_b, stride_n, once);
+      __syncthreads();
+      if (idle) continue;
+      const u32x4* mine = chunk[at & 1] + (work.span * B::kSpanRows + j) * kChunkPitch + chunk_piece(0, kb);
+      f32x4 x[B::kSubs];
+#pragma unroll
+      for (int t = 0; t < B::kSubs; ++t) {
+        Op k[4];
+        read_operands(k, mine + 16 * t * kChunkPitch);
+        x[t] = queries.dots(k);
+      }
+      const int base = work.first + at * B::kSpanRows;
+      if (!(base >= s.n_sink && base + B::kSpanRows <= all_see)) {         // (wave-uniform)
+        const int jq = 4 * (work.unit * (4 / G) + kb / G);
+#pragma unroll
+        for (int t = 0; t < B::kSubs; ++t)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const int row = base + 16 * t + j;
+            x[t][c] = row >= s.n_sink && row < seen_by(jq + c, j0, nq, n) ? x[t][c] : kNoScore;
+          }
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        float top = m[c];
+#pragma unroll
+        for (int t = 0; t < B::kSubs; ++t) top = __builtin_elementwise_maximum(top, x[t][c]);   // (a NaN is in the sum then, too)
+        l[c] *= (double)product_weight(m[c], top);
+        m[c] = top;
+#pragma unroll
+        for (int t = 0; t < B::kSubs; ++t) l[c] += (double)product_weight(x[t][c], top);
+      }
+    }
+  }
+  // the sixteen lanes of a row of lanes, then the spans
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const float top = row16_max(m[c]);
+    const double sum = row16_sum(l[c] * (double)product_weight(m[c], top));
+    if (j == 0) {
+      wm[wave][4 * kb + c] = top;
+      wl[wave][4 * kb + c] = sum;
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < nq * G; e += kBatchThreads) {
+    const int jq = e / G, h = e % G, quad = jq >> 2;
+    const int unit = quad / (4 / G), at = 4 * (quad % (4 / G) * G + h) + (jq & 3);
+    float top = kLeastMax;
+#pragma unroll
+    for (int w = 0; w < B::kSpans; ++w) top = fmaxf(top, wm[unit + U * w][at]);
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < B::kSpans; ++w) sum += wl[unit + U * w][at] * (double)product_weight(wm[unit + U * w][at], top);
+    const int64_t o = ((int64_t)bg * gridDim.x + blockIdx.x) * (kHistBatch * G) + e;
+    part_m[o] = top;
+    part_l[o] = sum;
+  }
+}
+
+// The same grid and queries.  Adds  w_j(i) / (2 s (1 - gamma))  to the vertical table at i and to the slash table at
+// i + j - 1, for all nq queries at once; the first batch (j0 = 1) writes the tables whole (zeros past the sequence and
+// in the lower half of the slash frame), later batches add to them.
+// A lane has the weights of four queries of a quad for its row: their sum, and the sum in which each query's weight is moved
+// one row up for every query before it in the quad (a rotation inside 16 lanes; what enters at the first row of sixteen comes
+// from the sixteen before), go to LDS per quad and head, the latter four rows further up for every quad before.  One thread per
+// row and head adds the quads up, a chunk behind the products.  A span starts with the 32 rows before it, for what reaches into
+// it (31 rows at most).
+// moments (or NULL; the only batch): the statistics of the workgroup's rows, as k_table_moments leaves them, one partial per
+// workgroup.
+template <int U>
+struct ApplyLds {
+  using B = BatchShape<U, kApplyRows>;
+  static constexpr int kQuads = 4 * U;                     // times heads
+  u32x4 chunk[2][B::kPieces];
+  float sum[2][kQuads][B::kRows];                          // [quad * G + head][row of the chunk, span by span]
+  float moved[B::kSpans][kQuads][3 * B::kSpanRows];        // per span, [row of three chunks in turn]
+  float ref[3][4][kHistBatch];                             // [largest product, factor as a pair of floats][head][query]
+};
+template <int G, bool kPaged, int kKind, int U>
+__global__ __launch_bounds__(kBatchThreads, 2) void k_batch_apply(
+    Shape s, float* __restrict__ tab_ver, float* __restrict__ tab_sla, const float* __restrict__ q0, int64_t q_stride,
+    int j0, int nq, const void* __restrict__ K, int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage pg,
+    const int32_t* __restrict__ seq_lens, const float* __restrict__ part_m, const double* __restrict__ part_l,
+    int parts, double gamma, int n_queries, double* __restrict__ moments) {
+  using B = BatchShape<U, kApplyRows>;
+  using Op = typename KSub<kKind>::Operand;
+  using Lds = ApplyLds<U>;
+  constexpr int kSpanRows = B::kSpanRows, kRing = 3 * kSpanRows;
+  extern __shared__ char lds_raw[];
+  Lds& lds = *reinterpret_cast<Lds*>(lds_raw);
+  const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = lane & 15, kb = lane >> 4;
+  int n = seq_lens[b];
+  n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
+  const BatchWork<U, B> work(n, wave);
+  const char* Kbg = static_cast<const char*>(K) + RowMap<kPaged>::base(b, g, stride_b, stride_h) * KSub<kKind>::kElemBytes;
+  const int64_t head0 = (int64_t)b * s.Hq + (int64_t)g * G;
   const bool first = j0 == 1;
-  for (int tile = lo; tile < hi; ++tile) {
-    const int base = tile * kHistRows;
-    HistTile<kPaged, kKind, kHistSub> T;
-    T.load(Kbg, pg, b, stride_b, stride_n, base, n, j, kb);
-    float av[kHistSub], as[kHistSub];
+  // The first four waves fetch the rows, the others add up and write the tables: a wait for a load would wait for the stores
+  // before it.  What a wave of the latter adds up: the rows of a chunk, of one head.
+  constexpr int kLoadThreads = kBatchThreads / 2;
+  const int my_head = wave - kHistWaves / 2;
+  TableMoments stats_v, stats_s;
+  if (work.chunks > 0) {
+    UnitQueries<G, Op> queries;                            // (k_batch_stats reported the range)
+    (void)queries.load(q0, q_stride, head0, nq, work.unit, lane);
+    {
+      static_assert(kBatchThreads == kHistBatch * 4 * 4, "four lanes per query and head");
+      const int jq = tid >> 4, h = (tid >> 2) & 3, sub = tid & 3;
+      float top = 0.f;
+      double norm = 0.0;
+      if (jq < nq && h < G)                                // uniform over the four lanes
+        merge_hist<4>(part_m, part_l, (int64_t)bg * parts * (kHistBatch * G) + jq * G + h, kHistBatch * G, parts,
+                      sub, gamma, n_queries, top, norm, [](float x) { return product_weight(x, 0.f); });
+      const float hi = (float)norm;
+      lds.ref[0][h][jq] = top;
+      lds.ref[1][h][jq] = hi;
+      lds.ref[2][h][jq] = (float)(norm - (double)hi);
+    }
+    const bool idle = work.unit * (16 / G) >= nq;          // (wave-uniform: a unit of no query)
+    const int quads = (nq + 3) >> 2;
+    const int all_see = seen_by_all<G>(work.unit, j0, nq, n);
+    const int quad = work.unit * (4 / G) + kb / G;
+    const float* my_ref = &lds.ref[0][kb % G][(4 * quad) & (kHistBatch - 1)];
+    float enter[3] = {0.f, 0.f, 0.f};                      // the rotated sums of the sixteen rows before
+    auto products = [&](auto from, auto masked, const u32x4* buf, int at, int sum_at, int moved_at) __attribute__((always_inline)) {
+      constexpr bool kMasked = decltype(masked)::value;
+      const int row0 = work.first + at * kSpanRows + j;
+      const u32x4* mine = buf + (work.span * kSpanRows + j) * kChunkPitch + chunk_piece(0, kb);
+      float* sum = &lds.sum[sum_at][work.unit * 4 + kb][work.span * kSpanRows + j];
+      float* moved = lds.moved[work.span][work.unit * 4 + kb];
+      const f32x4 top = *reinterpret_cast<const f32x4*>(my_ref), hi = *reinterpret_cast<const f32x4*>(my_ref + 4 * kHistBatch),
+                  lo = *reinterpret_cast<const f32x4*>(my_ref + 8 * kHistBatch);
+      walk_chunk<B::kSubs, decltype(from)::value, kMasked ? 5 : 3>(queries, mine, [&](int t, const f32x4& v) __attribute__((always_inline)) {
+        float w[4];
 #pragma unroll
-    for (int t = 0; t < kHistSub; ++t) av[t] = as[t] = 0.f;
-    walk_rows(T, base, av, as);
-    if (kb < G) {
+        for (int c = 0; c < 4; ++c) {
+          float x = v[c];
+          if constexpr (kMasked)
+            x = row0 + 16 * t >= s.n_sink && row0 + 16 * t < seen_by(4 * quad + c, j0, nq, n) ? x : kNoScore;
+          w[c] = weigh(product_weight(x, top[c]), hi[c], lo[c]);
+        }
+        float up = w[3];
 #pragma unroll
-      for (int t = 0; t < kHistSub; ++t) {
-        const int row = base + 16 * t + j;
-        const int pos = row + j0 - 1;
+        for (int c = 2; c >= 0; --c) {
+          const float r = row16_rotate<1>(up);
+          up = (j != 0 ? r : enter[c]) + w[c];
+          enter[c] = r;
+        }
+        sum[16 * t] = ((w[3] + w[2]) + w[1]) + w[0];
+        int to = moved_at * kSpanRows + 16 * t + 4 * quad + j;
+        if (t + 2 >= B::kSubs) to = to < kRing ? to : to - kRing;
+        moved[to] = up;
+      });
+    };
+    // the quads of a chunk, by one thread per row and head
+    auto combine = [&](int at, int sum_at, int moved_at) __attribute__((always_inline)) {
+      if (my_head >= G) return;
+      float* ver = tab_ver + (head0 + my_head) * s.Lcap;
+      float* sla = tab_sla + (head0 + my_head) * 2 * s.Lcap;               // position p of an untouched table is slot Lcap + p
+#pragma unroll
+      for (int i = 0; i < B::kRows / 64; ++i) {
+        const int my_at = 64 * i + lane, my_span = my_at / kSpanRows, my_row = my_at % kSpanRows;
+        const float* sum = &lds.sum[sum_at][my_head][my_at];
+        const float* moved = &lds.moved[my_span][my_head][moved_at * kSpanRows + my_row];
+        float av = 0.f, as = 0.f;
+#pragma unroll
+        for (int quad = Lds::kQuads / G - 1; quad >= 0; --quad) {
+          if (quad >= quads) continue;
+          av += sum[quad * G * B::kRows];
+          as += moved[quad * G * kRing];
+        }
+        const int row = work.wg_first + my_span * work.span_rows + at * kSpanRows + my_row, pos = row + j0 - 1;
         if (first) {
           if (row < s.Lcap) {                              // past the sequence the sums are zero
-            ver[row] = av[t];
-            sla[s.Lcap + row] = as[t];
+            ver[row] = av;
+            sla[s.Lcap + row] = as;
             sla[row] = 0.f;
+            if (moments && row >= s.n_sink && row < n) {
+              stats_v.add(av);
+              stats_s.add(as);
+            }
           }
         } else {
-          if (row < n) ver[row] += av[t];
-          if (pos < n) sla[s.Lcap + pos] += as[t];
+          if (row < n) ver[row] += av;
+          if (pos < n) sla[s.Lcap + pos] += as;
         }
       }
-    }
+    };
+    // (the barriers of the two kinds of waves are the same ones, in the same order)
+    auto walk = [&](auto loads) __attribute__((always_inline)) {
+      constexpr bool kLoads = decltype(loads)::value;
+      ChunkRows<kPaged, kKind, B, kLoadThreads> rows;
+      if constexpr (kLoads) {
+        rows.start(pg, b, work.wg_first - kSpanRows, work.span_rows, n);   // chunk -1: the rows before the spans
+        rows.fetch(Kbg, pg, b, stride_b, stride_n, false);
+        rows.put(lds.chunk[1]);
+        rows.fetch(Kbg, pg, b, stride_b, stride_n, false);
+      }
+      __syncthreads();
+      constexpr std::integral_constant<int, 0> kWhole{};
+      constexpr std::integral_constant<int, (B::kSubs > 2 ? B::kSubs - 2 : 0)> kLast{};    // the last 32 rows
+      if (!idle) products(kLast, std::true_type{}, lds.chunk[1], -1, 1, 2);
+      int moved_at = 0;                                    // chunk at % 3
+      for (int at = 0; at < work.chunks; ++at) {
+        if constexpr (kLoads) {
+          rows.put(lds.chunk[at & 1]);
+          rows.fetch(Kbg, pg, b, stride_b, stride_n, false);
+        }
+        __syncthreads();
+        if constexpr (!kLoads) {
+          if (at > 0) combine(at - 1, (at - 1) & 1, moved_at > 0 ? moved_at - 1 : 2);
+        }
+        const int base = work.first + at * kSpanRows;
+        if (idle) {
+        } else if (base >= s.n_sink && base + kSpanRows <= all_see) {
+          products(kWhole, std::false_type{}, lds.chunk[at & 1], at, at & 1, moved_at);
+        } else {
+          products(kWhole, std::true_type{}, lds.chunk[at & 1], at, at & 1, moved_at);
+        }
+        moved_at = moved_at < 2 ? moved_at + 1 : 0;
+      }
+      __syncthreads();
+      if constexpr (!kLoads) combine(work.chunks - 1, (work.chunks - 1) & 1, moved_at > 0 ? moved_at - 1 : 2);
+    };
+    if (wave < kHistWaves / 2) walk(std::true_type{});
+    else walk(std::false_type{});
   }
   if (first) {
+    const int reached = (n + work.wg_rows - 1) / (work.wg_rows > 0 ? work.wg_rows : 1) * work.wg_rows;
     for (int h = 0; h < G; ++h) {
-      float* vh = tab_ver + ((int64_t)b * s.Hq + (int64_t)g * G + h) * s.Lcap;
-      float* sh = tab_sla + ((int64_t)b * s.Hq + (int64_t)g * G + h) * 2 * s.Lcap;
-      for (int i = tiles * kHistRows + blockIdx.x * kHistWaves * 64 + tid; i < s.Lcap; i += gridDim.x * kHistWaves * 64) {
+      float* vh = tab_ver + (head0 + h) * s.Lcap;
+      float* sh = tab_sla + (head0 + h) * 2 * s.Lcap;
+      for (int i = reached + blockIdx.x * kBatchThreads + tid; i < s.Lcap; i += gridDim.x * kBatchThreads) {
         vh[i] = 0.f;
         sh[s.Lcap + i] = 0.f;
         sh[i] = 0.f;
       }
     }
   }
-}
-
-// M1..M4 of the vertical and of the slash entries of a workgroup (256 threads, U positions each, those with in[u]), then
-// the smallest and the negated largest of both, to out[0:12].
-template <int U>
-__device__ __forceinline__ void moments_of_chunk(const float (&xv)[U], const float (&xs)[U], const bool (&in)[U],
-                                                 double* __restrict__ out) {
-  __shared__ double red[4][12];
-  const int tid = threadIdx.x;
-  double m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  float e[4] = {INFINITY, INFINITY, INFINITY, INFINITY};
+  if (moments && my_head >= 0 && my_head < G) {
+    stats_v.reduce_wave();
+    stats_s.reduce_wave();
+    if (lane == 0) {
+      double x[12];
+      stats_v.store(x);
+      stats_s.store(x + 6);
+      double* to = moments + ((head0 + my_head) * gridDim.x + blockIdx.x) * 12;
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    if (!in[u]) continue;
-    const double a = xv[u], c = xs[u];
-    m[0] += a; m[1] += a * a; m[2] += a * a * a; m[3] += a * a * a * a;
-    m[4] += c; m[5] += c * c; m[6] += c * c * c; m[7] += c * c * c * c;
-    e[0] = fminf(e[0], xv[u]); e[1] = fminf(e[1], -xv[u]);
-    e[2] = fminf(e[2], xs[u]); e[3] = fminf(e[3], -xs[u]);
-  }
-#pragma unroll
-  for (int p = 0; p < 8; ++p) {
-    m[p] = row16_sum(m[p]);
-    m[p] += __shfl_xor(m[p], 16);
-    m[p] += __shfl_xor(m[p], 32);
-  }
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    e[p] = -row16_max(-e[p]);
-    e[p] = fminf(e[p], __shfl_xor(e[p], 16));
-    e[p] = fminf(e[p], __shfl_xor(e[p], 32));
-  }
-  if ((tid & 63) == 0) {
-#pragma unroll
-    for (int p = 0; p < 8; ++p) red[tid >> 6][p] = m[p];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) red[tid >> 6][8 + p] = (double)e[p];
-  }
-  __syncthreads();
-  if (tid < 12) {
-    double t = red[0][tid];
-    for (int w = 1; w < 4; ++w) t = tid < 8 ? t + red[w][tid] : fmin(t, red[w][tid]);
-    out[tid] = t;
+      for (int p = 0; p < 12; ++p) to[p < 4 ? p : (p < 6 ? p + 4 : (p < 10 ? p - 2 : p))] = x[p];
+    }
   }
 }
 
@@ -443,7 +800,7 @@ __global__ __launch_bounds__(256) void k_hist_apply_one(Shape s, float* __restri
   float m;
   double norm;
   merge_hist<64>(part_m, part_l, ((int64_t)b * s.Hkv + g) * blocks * (kHistBatch * s.G) + h % s.G, kHistBatch * s.G,
-                 blocks, tid & 63, gamma, 1, m, norm);
+                 blocks, tid & 63, gamma, 1, m, norm, [](float x) { return exp_below<true>(x); });
   const float hi = (float)norm, lo = (float)(norm - (double)hi);
   float* ver = tab_ver + (int64_t)bh * s.Lcap;
   float* sla = tab_sla + (int64_t)bh * 2 * s.Lcap;
@@ -708,10 +1065,8 @@ __global__ __launch_bounds__(1024) void k_prior_final(Shape s, const float* __re
 }
 
 // ----------------------------------------------------------------------------- launchers
-// Workgroups that share a KV group in the two history kernels: two rounds of one workgroup per CU over all groups
-// (lengths differ), but no more than one 128-row tile per wave needs.  One workgroup fills a CU's LDS and a tile is 128 rows,
-// so time goes in steps of 2048 waves x 128 rows: 8 groups, tables from 32 queries in all, 101 to 104 us for 16K to 32768
-// rows, 163 us for 33000, 187 to 201 us for 37K to 65K.
+// Workgroups that share a KV group in k_hist_stats: 512 over all groups (lengths differ), but no more than one 128-row tile per
+// wave needs.
 static int hist_blocks(const Shape& s) {
   const int groups = s.B * s.Hkv;
   const int most = (s.Lcap + kHistRows * kHistWaves - 1) / (kHistRows * kHistWaves);
@@ -722,88 +1077,142 @@ static int hist_blocks(const Shape& s) {
 
 static int moment_chunks(const Shape& s) { return (s.Lcap + kMomentRows - 1) / kMomentRows; }
 
+// The same in the kernels of many queries, in chunks of `rows` and with `slots` workgroups on the chip at a time: as many as make
+// the fewest chunks one after the other, a workgroup beginning with about `wait` chunks' worth of waiting for its first rows and
+// queries.
+static int batch_blocks(const Shape& s, int rows, int slots, int wait) {
+  const int64_t groups = (int64_t)s.B * s.Hkv, tiles = (s.Lcap + rows - 1) / rows;
+  int64_t best = 1, least = INT64_MAX;
+  for (int64_t n = 1; n <= tiles && n <= slots; ++n) {
+    const int64_t cost = (groups * n + slots - 1) / slots * ((tiles + n - 1) / n + wait);
+    if (cost < least) {
+      least = cost;
+      best = n;
+    }
+  }
+  return (int)best;
+}
+static int stats_blocks(const Shape& s) { return batch_blocks(s, kStatsRows, 512, 4); }   // two workgroups per CU
+static int apply_blocks(const Shape& s) { return batch_blocks(s, kApplyRows, 256, 2); }   // one
+
 int64_t table_init_scratch_bytes(const Shape& s) {
-  const int64_t stats = (int64_t)s.B * s.Hkv * hist_blocks(s) * kHistBatch * s.G * (8 + 4);
-  const int64_t moments = (int64_t)s.B * s.Hq * moment_chunks(s) * 12 * 8;
-  return stats + moments;
+  const int most = hist_blocks(s) > stats_blocks(s) ? hist_blocks(s) : stats_blocks(s);
+  const int parts = moment_chunks(s) > apply_blocks(s) ? moment_chunks(s) : apply_blocks(s);
+  return (int64_t)s.B * s.Hkv * most * kHistBatch * s.G * (8 + 4) + (int64_t)s.B * s.Hq * parts * 12 * 8;
 }
 
-// Up to how many bytes of keys the pass over K above reads with ordinary loads.  With few queries it is bound by the bytes of K, and
+// Up to how many bytes of keys the first pass over K reads with ordinary loads.  With few queries it is bound by the bytes of K, and
 // keys that will not be found in the memory-side cache again are read past it (one query, 64 groups x 32K rows, 537 MB: 119 -> 96
 // us).  With one query the next reader is the next call, and the tables, written whole in between, take their part of the cache:
 // tables of 4 x capacity, K + tables 224 MB 54.2 us kept, 58.4 past the caches, 280 MB 74.0 and 72.8, 336 MB 91.2 and 79.1.  With
-// more queries k_hist_apply reads the keys again at once, while it writes the tables: 4 queries, keys + tables of 128 + 192 MB
-// 135.9 and 153.1, 192 + 36 MB 120.7 and 122.4, 224 + 168 MB 164.6 and 163.3, 256 + 192 MB 199.3 and 186.2.  With 32 queries the
-// matrix units bound the pass, and their operands leave no LDS for this form.
-constexpr int kOnceQueries = 8;
+// more queries k_batch_apply reads the keys again at once, while it writes the tables: 4 queries, keys + tables of 128 + 192 MB
+// 135.9 and 153.1, 192 + 36 MB 120.7 and 122.4, 224 + 168 MB 164.6 and 163.3, 256 + 192 MB 199.3 and 186.2 (the two passes before
+// these).  That second pass keeps ordinary loads: past the caches 257 us instead of 251 at 268 + 100 MB, 481 instead of 476 at 537 +
+// 200 MB, both passes.
 static float stats_kept_bytes(const Shape& s, int n_queries) {
   const float tables = 12.f * s.B * s.Hq * s.Lcap;
   return n_queries == 1 ? (float)kKeptBytes - tables : 280.f * (1 << 20) - 0.5f * tables;
 }
 
-// Called once per context in table mode: the operands of 32 queries need more dynamic LDS than the default limit.
+// The units of a batch of nq queries as the kernels are built for them.  (What the quads of a chunk move up has to end in the next
+// one: 28 rows at most without grouping, where sixteen of a span's rows were too few.)
+static int batch_units(int G, int nq) {
+  const int units = ((nq + 3) / 4 * G + 3) / 4;
+  return units <= 2 && G > 1 ? 2 : (units <= 4 ? 4 : 8);
+}
+
+// X(heads per group, units, key format)
+#define LFPS_BATCH_FOR_EACH_U(X, KIND) X(4, 2, KIND) X(4, 4, KIND) X(4, 8, KIND) X(2, 2, KIND) X(2, 4, KIND) X(1, 4, KIND)
+#define LFPS_BATCH_FOR_EACH(X) \
+  LFPS_BATCH_FOR_EACH_U(X, kKindBf16) LFPS_BATCH_FOR_EACH_U(X, kKindFp8) LFPS_BATCH_FOR_EACH_U(X, kKindF16)
+
+// Called once per context in table mode: the second kernel needs more dynamic LDS than the default limit.
 hipError_t configure_table_history(const Shape& s, int k_kind) {
   hipError_t e = hipSuccess;
-  auto raise = [&](const void* kernel) {
-    if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, hist_lds(kHistBatch));
+  auto raise = [&](const void* kernel, int bytes) {
+    if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   };
-#define LFPS_RAISE_HIST(GG, KIND)                                     \
-  if (s.G == GG && k_kind == KIND) {                                  \
-    raise((const void*)k_hist_stats<GG, false, KIND, false>);         \
-    raise((const void*)k_hist_stats<GG, true, KIND, false>);          \
-    raise((const void*)k_hist_stats<GG, false, KIND, true>);          \
-    raise((const void*)k_hist_stats<GG, true, KIND, true>);           \
-    raise((const void*)k_hist_apply<GG, false, KIND>);                \
-    raise((const void*)k_hist_apply<GG, true, KIND>);                 \
+#define LFPS_RAISE_BATCH(GG, UU, KIND)                                                       \
+  if (s.G == GG && k_kind == KIND) {                                                         \
+    raise((const void*)k_batch_apply<GG, false, KIND, UU>, (int)sizeof(ApplyLds<UU>));       \
+    raise((const void*)k_batch_apply<GG, true, KIND, UU>, (int)sizeof(ApplyLds<UU>));        \
   }
-#define LFPS_RAISE_HIST_G(KIND) LFPS_RAISE_HIST(1, KIND) LFPS_RAISE_HIST(2, KIND) LFPS_RAISE_HIST(4, KIND)
-  LFPS_RAISE_HIST_G(kKindBf16)
-  LFPS_RAISE_HIST_G(kKindFp8)
-  LFPS_RAISE_HIST_G(kKindF16)
-#undef LFPS_RAISE_HIST_G
-#undef LFPS_RAISE_HIST
+  LFPS_BATCH_FOR_EACH(LFPS_RAISE_BATCH)
+#undef LFPS_RAISE_BATCH
   return e;
 }
 
-template <int G, bool kPaged, int kKind>
-static hipError_t launch_hist_t(const Shape& s, float* tab_ver, float* tab_sla, const float* q0, int64_t q_stride,
-                                int j0, int nq, int n_queries, double gamma, const KvView& kv, float* dots,
-                                int64_t dots_stride, void* scratch, int32_t* flags, hipStream_t st) {
-  const int bpg = hist_blocks(s), chunks = moment_chunks(s);
-  double* moments = static_cast<double*>(scratch);
-  double* part_l = moments + (int64_t)s.B * s.Hq * chunks * 12;
-  float* part_m = reinterpret_cast<float*>(part_l + (int64_t)s.B * s.Hkv * bpg * kHistBatch * G);
-  const dim3 grid(bpg, s.B * s.Hkv), block(kHistWaves * 64);
-  const bool one = n_queries == 1;
-  constexpr int kTurns = kHistWaves * StreamTile<kKind>::kLdsChunks * 16;
-  static_assert(hist_lds(kOnceQueries) + kTurns <= hist_lds(kHistBatch), "the kernels' limit of dynamic LDS");
-#define LFPS_STATS(ONCE, LDS)                                                                                          \
-  hipLaunchKernelGGL((k_hist_stats<G, kPaged, kKind, ONCE>), grid, block, LDS, st, s, q0, q_stride, j0, nq, kv.k,      \
-                     kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, part_m, part_l, one ? dots : nullptr, \
-                     dots_stride, flags, kept)
+// What the launches below share.  The scratch: moments, then the partials of the statistics.
+struct HistScratch {
+  double* moments;
+  double* part_l;
+  float* part_m;
+  HistScratch(const Shape& s, void* scratch, int blocks, int parts) {
+    moments = static_cast<double*>(scratch);
+    part_l = moments + (int64_t)s.B * s.Hq * parts * 12;
+    part_m = reinterpret_cast<float*>(part_l + (int64_t)s.B * s.Hkv * blocks * kHistBatch * s.G);
+  }
+};
+
+template <int G, bool kPaged, int kKind, int U>
+static hipError_t launch_batch_t(const Shape& s, float* tab_ver, float* tab_sla, const float* q0, int64_t q_stride, int j0,
+                                 int nq, int n_queries, double gamma, const KvView& kv, void* scratch, int32_t* flags,
+                                 hipStream_t st) {
+  const int parts = stats_blocks(s), blocks = apply_blocks(s);
+  const HistScratch to(s, scratch, parts, blocks);
+  const dim3 block(kBatchThreads);
   const float kept = stats_kept_bytes(s, n_queries);
-  if (nq <= kOnceQueries && (float)s.B * s.Hkv * s.Lcap * (kD * KSub<kKind>::kElemBytes) > kept) LFPS_STATS(true, hist_lds(nq) + kTurns);
-  else LFPS_STATS(false, hist_lds(nq));
-#undef LFPS_STATS
+  hipLaunchKernelGGL((k_batch_stats<G, kPaged, kKind, U>), dim3(parts, s.B * s.Hkv), block, 0, st, s, q0, q_stride, j0, nq, kv.k, kv.stride_b,
+                     kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, to.part_m, to.part_l, flags, kept);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (one)
-    hipLaunchKernelGGL(k_hist_apply_one, dim3(chunks, s.B * s.Hq), dim3(256), 0, st, s, tab_ver, tab_sla, dots,
-                       dots_stride, kv.seq_lens, part_m, part_l, bpg, gamma, moments);
-  else
-    hipLaunchKernelGGL((k_hist_apply<G, kPaged, kKind>), grid, block, hist_lds(nq), st, s, tab_ver, tab_sla, q0, q_stride,
-                       j0, nq, kv.k, kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, part_m, part_l, gamma,
-                       n_queries);
+  hipLaunchKernelGGL((k_batch_apply<G, kPaged, kKind, U>), dim3(blocks, s.B * s.Hkv), block, sizeof(ApplyLds<U>), st, s, tab_ver, tab_sla, q0, q_stride,
+                     j0, nq, kv.k, kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, to.part_m, to.part_l, parts, gamma,
+                     n_queries, n_queries <= kHistBatch ? to.moments : nullptr);
   return hipGetLastError();
 }
 
-static hipError_t launch_hist(const Shape& s, float* tab_ver, float* tab_sla, const float* q0, int64_t q_stride, int j0,
-                              int nq, int n_queries, double gamma, const KvView& kv, float* dots, int64_t dots_stride,
-                              void* scratch, int32_t* flags, hipStream_t st) {
-#define LFPS_HIST_ARGS s, tab_ver, tab_sla, q0, q_stride, j0, nq, n_queries, gamma, kv, dots, dots_stride, scratch, flags, st
+static hipError_t launch_batch(const Shape& s, float* tab_ver, float* tab_sla, const float* q0, int64_t q_stride, int j0,
+                               int nq, int n_queries, double gamma, const KvView& kv, void* scratch, int32_t* flags,
+                               hipStream_t st) {
+  const int units = batch_units(s.G, nq), kind = kv.k_fp8 ? kKindFp8 : (kv.f16 ? kKindF16 : kKindBf16);
+#define LFPS_HIST_ARGS s, tab_ver, tab_sla, q0, q_stride, j0, nq, n_queries, gamma, kv, scratch, flags, st
+#define LFPS_LAUNCH_BATCH(GG, UU, KIND)                                                      \
+  if (s.G == GG && units == UU && kind == KIND)                                              \
+    return kv.page.table ? launch_batch_t<GG, true, KIND, UU>(LFPS_HIST_ARGS)                \
+                         : launch_batch_t<GG, false, KIND, UU>(LFPS_HIST_ARGS);
+  LFPS_BATCH_FOR_EACH(LFPS_LAUNCH_BATCH)
+#undef LFPS_LAUNCH_BATCH
+#undef LFPS_HIST_ARGS
+  return hipErrorInvalidValue;
+}
+
+template <int G, bool kPaged, int kKind>
+static hipError_t launch_one_t(const Shape& s, float* tab_ver, float* tab_sla, const float* q, double gamma, const KvView& kv,
+                               float* dots, int64_t dots_stride, void* scratch, int32_t* flags, hipStream_t st) {
+  const int blocks = hist_blocks(s), chunks = moment_chunks(s);
+  const HistScratch to(s, scratch, blocks, chunks);
+  const float kept = stats_kept_bytes(s, 1);
+#define LFPS_STATS(ONCE)                                                                                                \
+  hipLaunchKernelGGL((k_hist_stats<G, kPaged, kKind, ONCE>), dim3(blocks, s.B * s.Hkv), dim3(kHistWaves * 64), 0, st, s, q, \
+                     kv.k, kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, to.part_m, to.part_l, dots,      \
+                     dots_stride, flags, kept)
+  if ((float)s.B * s.Hkv * s.Lcap * (kD * KSub<kKind>::kElemBytes) > kept) LFPS_STATS(true);
+  else LFPS_STATS(false);
+#undef LFPS_STATS
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_hist_apply_one, dim3(chunks, s.B * s.Hq), dim3(256), 0, st, s, tab_ver, tab_sla, dots, dots_stride,
+                     kv.seq_lens, to.part_m, to.part_l, blocks, gamma, to.moments);
+  return hipGetLastError();
+}
+
+static hipError_t launch_one(const Shape& s, float* tab_ver, float* tab_sla, const float* q, double gamma, const KvView& kv,
+                             float* dots, int64_t dots_stride, void* scratch, int32_t* flags, hipStream_t st) {
+#define LFPS_HIST_ARGS s, tab_ver, tab_sla, q, gamma, kv, dots, dots_stride, scratch, flags, st
 #define LFPS_HIST(GG, KIND)                                                        \
-  return kv.page.table ? launch_hist_t<GG, true, KIND>(LFPS_HIST_ARGS)             \
-                       : launch_hist_t<GG, false, KIND>(LFPS_HIST_ARGS)
+  return kv.page.table ? launch_one_t<GG, true, KIND>(LFPS_HIST_ARGS)              \
+                       : launch_one_t<GG, false, KIND>(LFPS_HIST_ARGS)
 #define LFPS_HIST_G(KIND)                       \
   switch (s.G) {                                \
     case 1: LFPS_HIST(1, KIND);                 \
@@ -821,26 +1230,32 @@ static hipError_t launch_hist(const Shape& s, float* tab_ver, float* tab_sla, co
 
 hipError_t launch_table_history(const Shape& s, float* tab_ver, float* tab_sla, const float* q_hist, int n_queries,
                                 double gamma, const KvView& kv, float* dots, int64_t dots_stride, void* scratch,
-                                int32_t* flags, hipStream_t st) {
+                                int32_t* flags, int* moment_parts, hipStream_t st) {
+  if (n_queries == 1) {
+    *moment_parts = moment_chunks(s);
+    return launch_one(s, tab_ver, tab_sla, q_hist, gamma, kv, dots, dots_stride, scratch, flags, st);
+  }
   const int64_t q_stride = (int64_t)s.B * s.Hq * kD;
   for (int j0 = 1; j0 <= n_queries; j0 += kHistBatch) {
     const int nq = n_queries - j0 + 1 < kHistBatch ? n_queries - j0 + 1 : kHistBatch;
-    const hipError_t e = launch_hist(s, tab_ver, tab_sla, q_hist + (int64_t)(j0 - 1) * q_stride, q_stride, j0, nq,
-                                     n_queries, gamma, kv, dots, dots_stride, scratch, flags, st);
+    const hipError_t e = launch_batch(s, tab_ver, tab_sla, q_hist + (int64_t)(j0 - 1) * q_stride, q_stride, j0, nq, n_queries,
+                                      gamma, kv, scratch, flags, st);
     if (e != hipSuccess) return e;
   }
+  *moment_parts = n_queries <= kHistBatch ? apply_blocks(s) : 0;
   return hipSuccess;
 }
 
 hipError_t launch_table_state(const Shape& s, const float* tab_ver, const float* tab_sla, double* state,
-                              const int32_t* seq_lens, void* scratch, bool have_moments, hipStream_t st) {
-  const int chunks = moment_chunks(s);
+                              const int32_t* seq_lens, void* scratch, int moment_parts, hipStream_t st) {
   double* part = static_cast<double*>(scratch);
-  if (!have_moments)
-    hipLaunchKernelGGL(k_table_moments, dim3(chunks, s.B * s.Hq), dim3(256), 0, st, s, tab_ver, tab_sla, seq_lens, part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_table_state, dim3(s.B * s.Hq), dim3(192), 0, st, s, part, chunks, state, seq_lens);
+  if (!moment_parts) {
+    moment_parts = moment_chunks(s);
+    hipLaunchKernelGGL(k_table_moments, dim3(moment_parts, s.B * s.Hq), dim3(256), 0, st, s, tab_ver, tab_sla, seq_lens, part);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k_table_state, dim3(s.B * s.Hq), dim3(192), 0, st, s, part, moment_parts, state, seq_lens);
   return hipGetLastError();
 }
 

@@ -203,3 +203,14 @@ def test_tables_of_many_groups_are_those_of_few(s):
         few = tables([b])
         assert (many[:, b] - few[:, 0]).abs().max() <= 2.0**-23 * few.abs().max()
         assert (few > 0).any()
+
+
+# Several queries in one pass: histories around the four queries of a quad and the units of four, eight and sixteen queries that
+# make other kernels, lengths around the 64- and 128-row chunks, the 32 rows before a span and one chunk per workgroup
+@pytest.mark.parametrize("L,s,heads,fmt,page", [
+    (63, 2, (8, 2), "bf16", 0), (65, 4, (8, 2), "fp8", 16), (129, 8, (8, 2), "bf16", 0), (191, 9, (8, 2), "f16", 0),
+    (257, 16, (8, 2), "bf16", 64), (2049, 17, (8, 2), "fp8", 0), (96, 8, (4, 2), "bf16", 16), (321, 15, (4, 2), "f16", 0),
+    (1500, 30, (4, 2), "bf16", 0), (161, 3, (2, 2), "f16", 16), (290, 16, (2, 2), "fp8", 0), (4100, 32, (2, 2), "bf16", 0),
+    (33, 32, (2, 2), "bf16", 0), (640, 40, (8, 2), "bf16", 256)])
+def test_tables_at_the_edges_of_chunks_and_units(L, s, heads, fmt, page):
+    test_tables_from_many_queries(L, s, heads, fmt, page)
