@@ -123,7 +123,7 @@ struct RangeSource {
   const uint32_t* fm;
   int flag_words;
 };
-int range_rows(const Shape& s, bool tables);   // 0: the separate kernels
+int range_rows(const Shape& s, bool tables);   // a multiple of 64; 0: the separate kernels
 hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, const RangeSource& from,
                               const float* thr_state, float margin, const int32_t* skip_if, float* score,
                               int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words,

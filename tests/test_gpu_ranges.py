@@ -115,6 +115,13 @@ def test_table_steps(B, Hq, Hkv, L, k, r, n_sink, dtype, page):
         ctx.close()
 
 
+# groups whose ranges of 1024 (2048 for the tables) rows would be more workgroups than the chip holds: five ranges of 1088, two of
+# 2112 rows
+def test_ranges_that_are_no_power_of_two():
+    test_memoryless_steps(25, 8, 8, 5194, 60, 2, 1, 0, "bf16", 0)
+    test_table_steps(43, 8, 8, 4100, 40, 2, 4, "f16", 0)
+
+
 @pytest.mark.parametrize("L,k", [(1200, 650), (3000, 1600)])
 def test_a_budget_of_most_candidates_keeps_them_all(L, k):
     """A head whose budget takes more than half of its candidates remembers no threshold: other queries do not send it
