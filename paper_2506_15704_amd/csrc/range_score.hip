@@ -79,8 +79,14 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
   if (lo >= n) return;                                   // (nobody reads the piece counts of such a range)
   const int hi = n - lo < range ? n : lo + range;
   const int r = s.radius;
+  // The query is split behind the requests for the first rows, beside their latency (four steps of 8 groups x 32K rows 105.7 ->
+  // 103.3 us, of 32 x 12K FP8 88.8 -> 88.1), where the registers allow it: not of fp16, whose split takes the most of them (beside a
+  // tile it spills), and not of paged rows (8 x 32K 114.4 -> 116.1).
+  constexpr bool kSplitLate = !Split3<Op>::kHalf && !kPaged;
   Op A[4];
-  report_q_range(load_query_operand(A, q, head0, G, j, kb), flags);
+  QueryRows query;
+  query.load(q, head0, G, j, kb);
+  if constexpr (!kSplitLate) report_q_range(query.operand(A, G, j), flags);
   __syncthreads();
 
   // ---- S1: the candidates of [lo, hi) as a bitmap
@@ -240,7 +246,7 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
   int rows[4];
   int id = ids_of(0);
   int phys = lookup(id);
-  for (int e0 = 0; e0 < cnt; e0 += T) {
+  auto request = [&](int e0) {
     const int id_now = id, phys_now = phys;
     id = ids_of(e0 + T);
     if constexpr (kPaged) {
@@ -249,7 +255,22 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
       __builtin_amdgcn_sched_barrier(0);
     }
     issue(Bt, rows, id_now, phys_now);
-    consume(Bt, rows, e0);
+  };
+  if constexpr (kSplitLate) {
+    request(0);
+    __builtin_amdgcn_sched_barrier(0);
+    (void)query.operand(A, G, j);                        // (only fp16 has a range to report)
+    for (int e0 = 0;;) {
+      consume(Bt, rows, e0);
+      e0 += T;
+      if (e0 >= cnt) break;
+      request(e0);
+    }
+  } else {
+    for (int e0 = 0; e0 < cnt; e0 += T) {
+      request(e0);
+      consume(Bt, rows, e0);
+    }
   }
   flush();
   if (j == 0 && kb < G) seg_count[head * nseg + piece] = cnt << 16 | run;
