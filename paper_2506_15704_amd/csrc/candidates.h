@@ -121,24 +121,12 @@ inline size_t candidates_lds_bytes(const Shape& s, int nt) {
   return words * 4 + ((words + 63) / 64) * 4 + (size_t)(nt / 64) * 4096;
 }
 
-// The candidate set of group bg = (b, g) from pt = the Top-k rows [G, kmax] of its heads (entries < 0 and >= n are
-// skipped), for a request of n rows and budget kb: vertical = same position, slash = position + 1, both widened by
-// the radius; the newest n_recent and the first n_sink rows are always in.  Written as an ascending list to
-// cand[bg, :] with its length in cand_count[bg]; `part` of `nparts` workgroups that share the group each build the
-// whole bitmap (cheap) and emit every nparts-th round of words.  All NT threads call; lds as sized above; wave_tot:
-// NT / 64 ints of LDS.  See emit_bitmap for group_start / line_total.
+// The candidates of a group as a bitmap bm[0 : words] of LDS (words * 32 >= n), from pt = the Top-k rows [G, kmax] of its heads
+// (entries < 0 and >= n are skipped), for a request of n rows and budget kb: vertical = same position, slash = position + 1, both
+// widened by the radius; the newest n_recent and the first n_sink rows are always in.  All NT threads call; ends with a barrier.
 template <int NT>
-__device__ __forceinline__ void candidates_from_topk(const Shape& s, uint32_t* lds, int* wave_tot,
-                                                     const int32_t* pt, int n, int kb, int bg, int part, int nparts,
-                                                     int32_t* __restrict__ cand, int32_t* __restrict__ cand_count,
-                                                     int32_t* __restrict__ flags, int64_t* __restrict__ group_start,
-                                                     unsigned long long* __restrict__ line_total) {
+__device__ __forceinline__ void bitmap_from_topk(const Shape& s, uint32_t* bm, int words, const int32_t* pt, int n, int kb) {
   const int tid = threadIdx.x;
-  uint32_t* bm = lds;
-  const int words_cap = (s.Lcap + 31) >> 5;
-  uint32_t* rcnt = lds + words_cap;
-  uint16_t* stage = reinterpret_cast<uint16_t*>(rcnt + ((words_cap + 63) >> 6));
-  const int W = (n + 31) >> 5;
   const int r = s.radius;
   // Every load of a round is issued before LDS is touched, so their latencies overlap (4 heads x kU entries per
   // thread and round).  A round is fetched up to the row length kmax, not the budget, and masked when used, and the
@@ -156,7 +144,7 @@ __device__ __forceinline__ void candidates_from_topk(const Shape& s, uint32_t* l
       }
   };
   fetch(0);
-  for (int w = tid; w < words_cap; w += NT) bm[w] = 0u;
+  for (int w = tid; w < words; w += NT) bm[w] = 0u;
   __syncthreads();
   for (int j0 = 0;;) {
 #pragma unroll
@@ -181,7 +169,23 @@ __device__ __forceinline__ void candidates_from_topk(const Shape& s, uint32_t* l
     if (s.n_sink > 0) set_bit_range(bm, 0, (s.n_sink > n ? n : s.n_sink) - 1);
   }
   __syncthreads();
-  emit_bitmap<NT>(s, bm, W, rcnt, stage, wave_tot, bg, part, nparts, cand, cand_count, flags, group_start, line_total);
+}
+
+// That set of group bg written as an ascending list to cand[bg, :] with its length in cand_count[bg]; `part` of `nparts`
+// workgroups that share the group each build the whole bitmap (cheap) and emit every nparts-th round of words.  All NT threads
+// call; lds as sized above; wave_tot: NT / 64 ints of LDS.  See emit_bitmap for group_start / line_total.
+template <int NT>
+__device__ __forceinline__ void candidates_from_topk(const Shape& s, uint32_t* lds, int* wave_tot,
+                                                     const int32_t* pt, int n, int kb, int bg, int part, int nparts,
+                                                     int32_t* __restrict__ cand, int32_t* __restrict__ cand_count,
+                                                     int32_t* __restrict__ flags, int64_t* __restrict__ group_start,
+                                                     unsigned long long* __restrict__ line_total) {
+  uint32_t* bm = lds;
+  const int words_cap = (s.Lcap + 31) >> 5;
+  uint32_t* rcnt = lds + words_cap;
+  uint16_t* stage = reinterpret_cast<uint16_t*>(rcnt + ((words_cap + 63) >> 6));
+  bitmap_from_topk<NT>(s, bm, words_cap, pt, n, kb);
+  emit_bitmap<NT>(s, bm, (n + 31) >> 5, rcnt, stage, wave_tot, bg, part, nparts, cand, cand_count, flags, group_start, line_total);
 }
 
 }  // namespace lfps

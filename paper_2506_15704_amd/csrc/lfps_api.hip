@@ -494,6 +494,11 @@ static bool next_step_filtered(const lfps_ctx* ctx) { return ctx->filter_on && !
 // ... and with them the kernel that finds the candidates and scores them at once (rows of its ranges, or 0)?
 static int next_step_range(const lfps_ctx* ctx, bool tables) { return next_step_filtered(ctx) ? ctx->range[tables] : 0; }
 
+// ... or, of fp32 keys, the one that does so without a filter?
+static bool step_fused(const lfps_ctx* ctx, const RangeSource& from) {
+  return ctx->cfg.kv_dtype == LFPS_F32 && from.prev_topk && step_fuses_f32(ctx->shape);
+}
+
 // S2 + S3 + S4 over ctx->cand / ctx->cand_count inside the chained entry points.  With the score filter on
 // (16-bit and FP8-key caches): survivors of the per-head threshold, then select and attention in one kernel, which
 // also takes the unfiltered pass for the heads the filter left short.  Without it: every score, then select and
@@ -528,9 +533,14 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
                                        ctx->thr_state, kFilterMargin, keep, skip_if, ctx->flags + 2, q, ctx->flags, v, out, st));
     return LFPS_OK;
   }
-  LAUNCH(ctx, LFPS_KERNEL_GATHER_SCORE, st,
-         launch_group_score(s, ctx->cfg.kv_dtype, q, v, ctx->cand, ctx->cand_count, ctx->score, s.score_stride,
-                            ctx->flags, st));
+  if (step_fused(ctx, from))
+    LAUNCH(ctx, LFPS_KERNEL_GATHER_SCORE, st,
+           launch_candidates_score_f32(s, q, v, from.prev_topk, from.k, ctx->cand, ctx->cand_count, ctx->score, s.score_stride,
+                                       ctx->flags, st));
+  else
+    LAUNCH(ctx, LFPS_KERNEL_GATHER_SCORE, st,
+           launch_group_score(s, ctx->cfg.kv_dtype, q, v, ctx->cand, ctx->cand_count, ctx->score, s.score_stride,
+                              ctx->flags, st));
   LAUNCH(ctx, LFPS_KERNEL_SELECT_ATTEND, st,
          launch_select_attend(s, ctx->cfg.kv_dtype, ctx->score, s.score_stride, ctx->cand, ctx->cand_count, k, topk_idx,
                               sel, ctx->thr_state, keep, skip_if, v, out, st));
@@ -554,8 +564,8 @@ int lfps_step(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int32_t* p
   float* sel = topk_score ? topk_score : ctx->sel_score;
   int64_t* line_total = ctx->group_start + (int64_t)s.B * s.Hkv;   // zero between steps: the filtered select resets it
   const RangeSource from{prev_topk, k, s.kmax % 4 == 0 && (uintptr_t)prev_topk % 16 == 0, nullptr, nullptr, 0};
-  if (next_step_range(ctx, false))
-    LAUNCH(ctx, LFPS_KERNEL_CANDIDATES, st, hipSuccess);      // (timing: S1 is part of the filter_score launch)
+  if (next_step_range(ctx, false) || step_fused(ctx, from))
+    LAUNCH(ctx, LFPS_KERNEL_CANDIDATES, st, hipSuccess);      // (timing: S1 is part of the scoring kernel's launch)
   else
     LAUNCH(ctx, LFPS_KERNEL_CANDIDATES, st,
            launch_candidates(s, prev_topk, k, v.seq_lens, ctx->cand, ctx->cand_count, ctx->flags,
@@ -825,7 +835,6 @@ int lfps_table_update(lfps_ctx* ctx, const int32_t* idx, const float* idx_score,
 
 static int table_step_impl(lfps_ctx* ctx, const float* q, const KvView& v, const int32_t* k, int32_t* topk_idx,
                            float* topk_score, float* out, const int32_t* gate, hipStream_t st) {
-  const Shape& s = ctx->shape;
   float* sel = topk_score ? topk_score : ctx->sel_score;
   int rc = table_candidates_impl(ctx, v.seq_lens, ctx->cand, ctx->cand_count, true, gate, st);
   if (rc != LFPS_OK) return rc;

@@ -96,6 +96,13 @@ hipError_t launch_group_score(const Shape& s, int dtype, const float* q, const K
                               const int32_t* cand_count, float* score, int64_t score_stride, int32_t* flags,
                               hipStream_t st, float* tops = nullptr, const int32_t* k = nullptr);
 
+// S1 and S2 of a step over fp32 keys in one kernel, where step_fuses_f32: what launch_candidates (without a line) and
+// launch_group_score leave.
+bool step_fuses_f32(const Shape& s);
+hipError_t launch_candidates_score_f32(const Shape& s, const float* q, const KvView& kv, const int32_t* prev_topk, const int32_t* k,
+                                       int32_t* cand, int32_t* cand_count, float* score, int64_t score_stride, int32_t* flags,
+                                       hipStream_t st);
+
 // Filtered scoring (bf16, fp16 or FP8 keys; the kernel keeps its first name, k_filter_score_bf16): per
 // head only rows with score >= thr_state[b,h] - margin are kept, as
 // (score, position) lists in at most filter_nseg(s) pieces per head.  The kernel runs with exactly

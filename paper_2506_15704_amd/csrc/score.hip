@@ -15,7 +15,7 @@
 //     scaled up by 2^11 and 2^22 so that they stay normal numbers, and scaled back when the three
 //     D rows are added (fp16 x fp16 products are exact in fp32 as well).  |q| must stay below 65504.
 //   fp32 cache: 16 lanes per row, 8 channels each, fp32 FMAs and a reduce by lane permutations.
-#include "lfps_internal.h"
+#include "candidates.h"
 #include "score_mfma.h"
 
 namespace lfps {
@@ -388,45 +388,19 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
 // the other waited for memory four times, and few candidates made few waves: 11.2 us for 770 candidates of 8 groups, this
 // way 3.6 us (a step of 1 x 4096: 24.1 -> 18.4).
 constexpr int kRowsPerWaveF32 = 16;
-template <int G, bool GATHER, bool kPaged>
-__global__ __launch_bounds__(kScoreThreads) void k_group_score_f32(Shape s, const float* __restrict__ q,
-                                                                   const float* __restrict__ K, int64_t stride_b,
-                                                                   int64_t stride_h, int64_t stride_n, KvPage pg,
-                                                                   const int32_t* __restrict__ seq_lens,
-                                                                   const int32_t* __restrict__ cand,
-                                                                   const int32_t* __restrict__ cand_count,
-                                                                   float* __restrict__ score, int64_t score_stride,
-                                                                   float scale, int32_t* __restrict__ flags, float*, const int32_t*) {
-  const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+
+// Scores of the slots first .. first + 15, first + step ..., below count, by one wave.  row_at(slot): the row of a slot (called
+// by the lanes 0 .. 15 of a visit); an entry outside [0, n) reads row 0 and scores -inf: it ranks below every row.  sc: the score
+// row of the group's first head.
+template <int G, bool kPaged, typename RowAt>
+__device__ __forceinline__ void score_slots_f32(const float (&qr)[G][8], const float* Kbg, const KvPage& pg, int b, int64_t stride_b,
+                                                int64_t stride_n, int n, int count, int first, int step, float* __restrict__ sc,
+                                                int64_t score_stride, float scale, RowAt row_at) {
+  const int lane = threadIdx.x & 63;
   const int j = lane & 15, rs = lane >> 4;     // 16 lanes per row, 4 rows per wave instruction
-  int n = seq_lens[b];
-  n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
-  int count = GATHER ? cand_count[bg] : n;
-  if (GATHER) count = count < 0 ? 0 : (count > s.cand_cap ? s.cand_cap : count);
-  const int first = (blockIdx.x * 4 + wave) * kRowsPerWaveF32;
-  if (first >= count) return;
-
-  float qr[G][8];
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    const float* qh = q + ((int64_t)b * s.Hq + (int64_t)g * G + h) * kD + 8 * j;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) qr[h][c] = qh[c];
-  }
   using Rows = RowMap<kPaged>;
-  const float* Kbg = K + Rows::base(b, g, stride_b, stride_h);
-  const int32_t* cbg = GATHER ? cand + (int64_t)bg * s.cand_cap : nullptr;
-  float* sc = score + ((int64_t)b * s.Hq + (int64_t)g * G) * score_stride;
-  const int step = gridDim.x * 4 * kRowsPerWaveF32;
-  // lanes 0 .. 15: the rows of a visit; an entry outside [0, n) reads row 0 and scores -inf: it ranks below every row
-  auto fetch = [&](int base) {
-    int row = -1;
-    if (lane < kRowsPerWaveF32 && base + lane < count) row = GATHER ? cbg[base + lane] : base + lane;
-    return row;
-  };
+  auto fetch = [&](int base) { return lane < kRowsPerWaveF32 && base + lane < count ? row_at(base + lane) : -1; };
   auto physical = [&](int row) { return Rows::phys(pg, b, row >= 0 && row < n ? row : 0); };
-
   int my_row = fetch(first);
   int my_phys = physical(my_row);
   for (int base = first; base < count; base += step) {
@@ -462,6 +436,111 @@ __global__ __launch_bounds__(kScoreThreads) void k_group_score_f32(Shape s, cons
       if (slot < count && j < G) sc[(int64_t)j * score_stride + slot] = ok[t] ? v * scale : -INFINITY;
     }
   }
+}
+
+template <int G, bool GATHER, bool kPaged>
+__global__ __launch_bounds__(kScoreThreads) void k_group_score_f32(Shape s, const float* __restrict__ q,
+                                                                   const float* __restrict__ K, int64_t stride_b,
+                                                                   int64_t stride_h, int64_t stride_n, KvPage pg,
+                                                                   const int32_t* __restrict__ seq_lens,
+                                                                   const int32_t* __restrict__ cand,
+                                                                   const int32_t* __restrict__ cand_count,
+                                                                   float* __restrict__ score, int64_t score_stride,
+                                                                   float scale, int32_t* __restrict__ flags, float*, const int32_t*) {
+  const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;
+  const int wave = threadIdx.x >> 6, j = threadIdx.x & 15;
+  int n = seq_lens[b];
+  n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
+  int count = GATHER ? cand_count[bg] : n;
+  if (GATHER) count = count < 0 ? 0 : (count > s.cand_cap ? s.cand_cap : count);
+  const int first = (blockIdx.x * 4 + wave) * kRowsPerWaveF32;
+  if (first >= count) return;
+
+  const int64_t head0 = (int64_t)b * s.Hq + (int64_t)g * G;
+  float qr[G][8];
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    const float* qh = q + (head0 + h) * kD + 8 * j;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) qr[h][c] = qh[c];
+  }
+  const float* Kbg = K + RowMap<kPaged>::base(b, g, stride_b, stride_h);
+  const int32_t* cbg = GATHER ? cand + (int64_t)bg * s.cand_cap : nullptr;
+  score_slots_f32<G, kPaged>(qr, Kbg, pg, b, stride_b, stride_n, n, count, first, gridDim.x * 4 * kRowsPerWaveF32,
+                             score + head0 * score_stride, score_stride, scale, [&](int slot) { return GATHER ? cbg[slot] : slot; });
+}
+
+// S1 and S2 of a step over fp32 rows in one kernel: each of the gridDim.x workgroups of a group builds the group's bitmap of
+// candidates, counts them, and lists and scores its part of them, slots [part * per, (part + 1) * per) of the ascending list.  List,
+// count and scores are those of k_candidates and k_group_score_f32, to the bit.  Bound by latency: as two
+// kernels a step of 8 groups x 4096 rows took 18.3 us in all, this way 17.0.
+template <int G, bool kPaged>
+__global__ __launch_bounds__(kScoreThreads) void k_candidates_score_f32(
+    Shape s, const float* __restrict__ q, const float* __restrict__ K, int64_t stride_b, int64_t stride_h, int64_t stride_n,
+    KvPage pg, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ prev_topk, const int32_t* __restrict__ kk,
+    int32_t* __restrict__ cand, int32_t* __restrict__ cand_count, float* __restrict__ score, int64_t score_stride, float scale,
+    int32_t* __restrict__ flags) {
+  extern __shared__ uint32_t lds[];                      // the bitmap, then the part's list
+  __shared__ int wave_tot[4];
+  const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 15;
+  const int64_t head0 = (int64_t)b * s.Hq + (int64_t)g * G;
+  int n = seq_lens[b];
+  int kb = kk[b];
+  float qr[G][8];
+#pragma unroll
+  for (int h = 0; h < G; ++h) {
+    const float* qh = q + (head0 + h) * kD + 8 * j;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) qr[h][c] = qh[c];
+  }
+  n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
+  kb = kb < 0 ? 0 : (kb > s.kmax ? s.kmax : kb);
+  const int words = (s.Lcap + 31) >> 5;
+  bitmap_from_topk<kScoreThreads>(s, lds, words, prev_topk + head0 * s.kmax, n, kb);
+  // thread t owns the words [t * each, (t + 1) * each)
+  const int each = (words + kScoreThreads - 1) / kScoreThreads, w0 = tid * each, w1 = w0 + each < words ? w0 + each : words;
+  int mine = 0;
+  for (int w = w0; w < w1; ++w) mine += __popc(lds[w]);
+  const int inc = wave_inclusive_sum(mine);
+  if (lane == 63) wave_tot[wave] = inc;
+  __syncthreads();
+  int at = inc - mine, total = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const int t = wave_tot[w];
+    at += w < wave ? t : 0;
+    total += t;
+  }
+  const int count = total < s.cand_cap ? total : s.cand_cap;
+  if (blockIdx.x == 0 && tid == 0) {
+    if (total > s.cand_cap) atomicOr(flags, LFPS_FLAG_CAND_OVERFLOW);
+    cand_count[bg] = count;
+  }
+  const int per = ((count + (int)gridDim.x - 1) / (int)gridDim.x + kRowsPerWaveF32 - 1) & ~(kRowsPerWaveF32 - 1);
+  const int s0 = (int)blockIdx.x * per, s1 = s0 + per < count ? s0 + per : count;
+  if (s0 >= s1) return;                                  // (workgroup-uniform)
+  int32_t* list = reinterpret_cast<int32_t*>(lds + words);
+  int32_t* out = cand + (int64_t)bg * s.cand_cap;
+  for (int w = w0; w < w1 && at < s1; ++w) {
+    uint32_t bits = lds[w];
+    if (at + __popc(bits) <= s0) {
+      at += __popc(bits);
+      continue;
+    }
+    for (; bits && at < s1; bits &= bits - 1, ++at) {
+      if (at < s0) continue;
+      const int row = (w << 5) + __ffs(bits) - 1;
+      list[at - s0] = row;
+      out[at] = row;
+    }
+  }
+  __syncthreads();
+  const int first = s0 + wave * kRowsPerWaveF32;
+  if (first >= s1) return;
+  score_slots_f32<G, kPaged>(qr, K + RowMap<kPaged>::base(b, g, stride_b, stride_h), pg, b, stride_b, stride_n, n, s1, first,
+                             4 * kRowsPerWaveF32, score + head0 * score_stride, score_stride, scale,
+                             [&](int slot) { return list[slot - s0]; });
 }
 
 // ----------------------------------------------------------------------------- per-head index lists
@@ -556,6 +635,46 @@ hipError_t launch_group_score(const Shape& s, int dtype, const float* q, const K
                           : launch_gs<4, false>(s, dtype, q, kv, cand, cand_count, score, score_stride, flags, st, tops, k);
     default: return hipErrorInvalidValue;
   }
+}
+
+// Workgroups of k_candidates_score_f32 that share a group, or 0 where the separate kernels are faster: every
+// workgroup reads the Top-k rows of its group and builds the whole bitmap, which the rows of a long context do not pay for.  Two
+// workgroups per CU: more of them repeat that, fewer wait longer for their rows.  Two steps, separate -> together, us: 8 groups x 2000
+// rows 34.8 -> 31.6, x 4096 36.5 -> 34.0, x 8000 43.1 -> 37.9, x 10000 42.2 -> 42.7, x 32K 74.4 -> 80.8; 128 x 4000 63.5 -> 57.5,
+// 128 x 8000 96.7 -> 90.5, 256 x 4000 103.5 -> 98.7; with 1024 workgroups 8 x 8000 40.6, with 256 256 x 4000 102.7.
+static constexpr int kFusedRowsF32 = 9216;
+static int fused_f32_parts(const Shape& s) {
+  const int64_t groups = (int64_t)s.B * s.Hkv;
+  if (s.Lcap > kFusedRowsF32) return 0;
+  const int64_t tiles = (s.cand_cap + 4 * kRowsPerWaveF32 - 1) / (4 * kRowsPerWaveF32);
+  int64_t parts = (512 + groups - 1) / groups;
+  parts = parts < tiles ? parts : tiles;
+  return (int)(parts < 1 ? 1 : parts);
+}
+bool step_fuses_f32(const Shape& s) { return fused_f32_parts(s) > 0; }
+hipError_t launch_candidates_score_f32(const Shape& s, const float* q, const KvView& kv, const int32_t* prev_topk, const int32_t* k,
+                                       int32_t* cand, int32_t* cand_count, float* score, int64_t score_stride, int32_t* flags,
+                                       hipStream_t st) {
+  const int parts = fused_f32_parts(s);
+  if (parts < 1) return hipErrorInvalidValue;
+  const size_t lds = ((size_t)(s.Lcap + 31) / 32 + (s.cand_cap + parts - 1) / parts + kRowsPerWaveF32) * 4;
+  const float scale = 0.08838834764831845f;   // 1/sqrt(128)
+#define LFPS_LAUNCH_CSF(GG, PAGED)                                                                                              \
+  hipLaunchKernelGGL((k_candidates_score_f32<GG, PAGED>), dim3(parts, s.B * s.Hkv), dim3(kScoreThreads), lds, st, s, q,          \
+                     (const float*)kv.k, kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, prev_topk, k, cand,       \
+                     cand_count, score, score_stride, scale, flags)
+#define LFPS_LAUNCH_CSF_G(GG)                      \
+  if (kv.page.table) LFPS_LAUNCH_CSF(GG, true);    \
+  else LFPS_LAUNCH_CSF(GG, false)
+  switch (s.G) {
+    case 1: LFPS_LAUNCH_CSF_G(1); break;
+    case 2: LFPS_LAUNCH_CSF_G(2); break;
+    case 4: LFPS_LAUNCH_CSF_G(4); break;
+    default: return hipErrorInvalidValue;
+  }
+#undef LFPS_LAUNCH_CSF_G
+#undef LFPS_LAUNCH_CSF
+  return hipGetLastError();
 }
 
 // Smallest part size in candidate slots, and the pieces a group can then be cut into (<= 1024).

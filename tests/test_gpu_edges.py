@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import gen
+from gen import device as gen_device
 from oracle import lfps_oracle as orc
 from tests.harness import DEV, DeviceCase, assert_out_close, assert_scores_close, assert_topk_equal_mod_ties, dev, valid_row
 
@@ -296,3 +297,44 @@ def test_host_resident_cache_gives_identical_results(fmt):
     h = 4 * 3 + 1
     ref = orc.sparse_attn(case.q[3, 1, h], K0, V0, idx3[1, h, : int(case.k[1])])
     assert_out_close(out3[1, h], ref, "host-resident step 3")
+
+
+# The kernel that finds and scores the candidates of small fp32 contexts: list, count, scores and selection are those of the separate
+# entry points, to the bit.  Lengths around words, parts and the line to the separate kernels, lists cut at cand_cap, unsorted and
+# invalid entries in the previous Top-k, windows wider than two words
+@pytest.mark.parametrize("B,Hq,Hkv,L,k,r,n_sink,page,cap", [
+    (1, 4, 1, 1, 1, 0, 0, 0, 0), (2, 8, 2, 31, 5, 1, 0, 0, 0), (1, 32, 8, 4096, 128, 2, 0, 0, 0), (3, 8, 4, 1025, 33, 20, 4, 16, 0),
+    (2, 8, 8, 8200, 300, 3, 2, 64, 0), (1, 4, 2, 9213, 2300, 1, 0, 0, 0), (1, 4, 2, 9300, 100, 1, 0, 0, 0), (2, 8, 2, 5000, 200, 4, 0, 0, 700)])
+def test_fp32_steps_equal_the_separate_entry_points(B, Hq, Hkv, L, k, r, n_sink, page, cap):
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(L + k)
+    Lcap = L + 3
+    K, V = (torch.randn((B, Hkv, Lcap, 128), device="cuda:0", generator=g) for _ in range(2))
+    ctx = Lfps(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="f32", max_seq_len=Lcap, max_k=k, radius=r, n_sink=n_sink, cand_cap=cap)
+    view = lambda seq: ctx.kv_view(K, V, seq)
+    if page:
+        Kp, Vp, table = gen_device.paginate(K, V, page, seed=5)
+        view = lambda seq: ctx.paged_kv_view(Kp, Vp, table, seq)
+    lens = [max(1, L - 37 * b) for b in range(B)]
+    ks = torch.tensor([min(k, n) for n in lens], dtype=torch.int32, device="cuda:0")
+    prev = torch.randint(-3, L, (B, Hq, k), dtype=torch.int32, device="cuda:0", generator=g)
+    for t in range(1, 4):
+        seq = torch.tensor([n + t for n in lens], dtype=torch.int32, device="cuda:0")
+        q = torch.randn((B, Hq, 128), device="cuda:0", generator=g)
+        idx, idx2 = (torch.full((B, Hq, k), -5, dtype=torch.int32, device="cuda:0") for _ in range(2))
+        sc, sc2 = (torch.full((B, Hq, k), -5.0, device="cuda:0") for _ in range(2))
+        out, out2 = (torch.zeros((B, Hq, 128), device="cuda:0") for _ in range(2))
+        cnt, cnt2 = (torch.zeros((B, Hkv), dtype=torch.int32, device="cuda:0") for _ in range(2))
+        ctx.lfps_step(q, view(seq), prev, ks, idx, out, sc)
+        ctx.lfps_copy_cand_count(cnt)
+        flags = ctx.lfps_poll_status()
+        cand = torch.zeros((B, Hkv, ctx.cand_cap), dtype=torch.int32, device="cuda:0")
+        ctx.lfps_candidates(prev, ks, seq, cand, cnt2)
+        ctx.lfps_score_topk(q, view(seq), cand, cnt2, ks, idx2, sc2)
+        ctx.lfps_sparse_attn(q, view(seq), idx2, sc2, ks, out2)
+        assert ctx.lfps_poll_status() == flags and bool(flags) == bool(cap)
+        for x, y, name in ((cnt, cnt2, "count"), (idx, idx2, "index"), (sc, sc2, "score"), (out, out2, "output")):
+            assert torch.equal(x, y), (name, t)
+        prev = idx.flip(2).contiguous() if t == 1 else idx
+    ctx.close()
