@@ -874,7 +874,7 @@ static_assert(TS_MS == TS_MV + 4, "k_table_state writes both sets of moments in 
 // ----------------------------------------------------------------------------- prefill priors
 // K mean, V mean and the variance of the scaled scores of the given query over the offloaded rows, from one pass over
 // K and V (three passes before, the means by one workgroup per KV group: 8 of 256 CUs at B = 1).  Bound by the bytes of
-// K and V: 34 + 8 us at 8 groups x 32K bf16 rows (134 MB), 600 us before.  grid (splits, B*Hkv), 256 threads; 16 lanes per row, 8 channels each, two 16-row tiles per wave in flight.
+// K and V: 27 + 4 us at 8 groups x 32K bf16 rows (134 MB), 600 us before.  grid (splits, B*Hkv), 256 threads; 16 lanes per row, 8 channels each, two 16-row tiles per wave in flight.
 // Per (bg, split) a partial: 128 sums of K, 128 of V, then (rows, mean, sum of squared deviations) of every head's
 // scores; the means and deviations of parts are merged exactly (no difference of large sums).
 constexpr int kPriorThreads = 256;
@@ -1022,29 +1022,35 @@ __global__ __launch_bounds__(kPriorThreads) void k_prior_partials(Shape s, const
   }
 }
 
-// grid B*Hkv, 1024 threads: the partials of a group.  Four threads per channel take every fourth split; wave h merges
-// the scores of head h.
+// grid (B*Hkv, 5), 1024 threads: the partials of a group.  Four workgroups take 64 channels of K or V each, sixteen threads a
+// channel (all of a thread's partials on their way at once: one workgroup for all of them took 3.9 us longer for 128 partials of
+// 8 groups: priors of 1 x 32K 34.7 -> 30.8 us), the fifth the scores of the heads, a wave each.
 __global__ __launch_bounds__(1024) void k_prior_final(Shape s, const float* __restrict__ q,
                                                       const int32_t* __restrict__ seq_lens,
                                                       const double* __restrict__ part, int splits,
                                                       float* __restrict__ kbar, float* __restrict__ vbar,
                                                       float* __restrict__ sigma2_hat) {
-  __shared__ double red[4][2 * kD];
+  __shared__ double red[16][64];
   const int bg = blockIdx.x, b = bg / s.Hkv, g = bg % s.Hkv, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int n = seq_lens[b];
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   const int cnt = n - s.n_sink;
   const int stride = prior_partial(s.G);
   const double* p = part + (int64_t)bg * splits * stride;
-  const int c = tid & (2 * kD - 1);
-  double t = 0.0;
+  if (blockIdx.y < 4) {
+    const int c = 64 * blockIdx.y + lane;
+    double t = 0.0;
 #pragma unroll 8
-  for (int k = tid / (2 * kD); k < splits; k += 4) t += p[(int64_t)k * stride + c];
-  red[tid / (2 * kD)][c] = t;
-  __syncthreads();
-  if (tid < 2 * kD) {
-    t = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
-    (c < kD ? kbar : vbar)[(int64_t)bg * kD + (c & (kD - 1))] = cnt > 0 ? (float)(t / (double)cnt) : 0.f;
+    for (int k = wave; k < splits; k += 16) t += p[(int64_t)k * stride + c];
+    red[wave][lane] = t;
+    __syncthreads();
+    if (wave == 0) {
+      t = red[0][lane];
+#pragma unroll
+      for (int w = 1; w < 16; ++w) t += red[w][lane];
+      (c < kD ? kbar : vbar)[(int64_t)bg * kD + (c & (kD - 1))] = cnt > 0 ? (float)(t / (double)cnt) : 0.f;
+    }
+    return;
   }
   if (wave < s.G) {
     const int64_t bh = (int64_t)b * s.Hq + (int64_t)g * s.G + wave;
@@ -1295,7 +1301,7 @@ static hipError_t launch_priors_t(const Shape& s, const float* q, const KvView& 
 #undef LFPS_LAUNCH_PRI
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_prior_final, dim3(s.B * s.Hkv), dim3(1024), 0, st, s, q, kv.seq_lens, part, splits, kbar, vbar,
+  hipLaunchKernelGGL(k_prior_final, dim3(s.B * s.Hkv, 5), dim3(1024), 0, st, s, q, kv.seq_lens, part, splits, kbar, vbar,
                      sigma2_hat);
   return hipGetLastError();
 }
