@@ -597,7 +597,8 @@ __global__ __launch_bounds__(1024) void k_table_init(Shape s, float* __restrict_
 
 // ----------------------------------------------------------------------------- head sparsity (Eq. 5, Eq. 6)
 // One wave per (b, h), a chain of latencies: a row at a time, 64 lanes wide, took 10.6 us at 256 heads and 10 rows; four rows
-// side by side and all of them requested at once, 5.7 us.  rho = w_sink / (w_sink + w_global + w_local):
+// side by side and all of them requested at once, 5.4 us; with one fp64 exponential for both sets and one logarithm for the
+// three, in neighbouring lanes, 5.2 (sixteen table steps 1078 -> 1073 us in all).  rho = w_sink / (w_sink + w_global + w_local):
 //   w_sink   = sum over rows [0, n_sink) of exp(q.K_i/sqrt(D)),
 //   w_global = n * exp(q.kbar/sqrt(D) + |q|^2 sigma2_hat / 2)        (log-normal mean of the weights, App. B.1),
 //   w_local  = sum over the newest n_local rows of exp(q.K_i/sqrt(D)).
@@ -654,18 +655,24 @@ __global__ __launch_bounds__(64) void k_head_sparsity(Shape s, const float* __re
       const float of_row = __shfl(d, 16 * (j & 3));           // rows r0 + 4 u + (j & 3)
       mine = (j >> 2) == u ? of_row : mine;
     }
+    // both sets in one exponential: a row is in one of them
     const int r = r0 + j;
-    auto add = [&](bool in, double& m, double& z) {
-      const float top = row16_max(in ? mine : -INFINITY);
+    const bool sink = r < ns, local = r >= ns && r < rows;
+    const float top_sink = row16_max(sink ? mine : -INFINITY), top_loc = row16_max(local ? mine : -INFINITY);
+    const double mx_sink = m_sink > (double)top_sink ? m_sink : (double)top_sink;
+    const double mx_loc = m_loc > (double)top_loc ? m_loc : (double)top_loc;
+    const double mx = sink ? mx_sink : mx_loc;
+    // (a logit of +inf is a term of weight 1 beside which all others vanish; a NaN stays)
+    const double term = sink || local ? ((double)mine == mx ? 1.0 : exp((double)mine - mx)) : 0.0;
+    auto add = [&](float top, bool in, double to, double& m, double& z) {
+      const double part = row16_sum(in ? term : 0.0);
       if (top == -INFINITY) return;                            // (wave-uniform: every group holds the same rows)
-      const double mx = m > (double)top ? m : (double)top;
-      // (a logit of +inf is a term of weight 1 beside which all others vanish; a NaN stays)
-      const double part = row16_sum(in ? ((double)mine == mx ? 1.0 : exp((double)mine - mx)) : 0.0);
-      z = (m == mx ? z : z * exp(m - mx)) + part;
-      m = mx;
+      if (r0 > 0) z = m == to ? z : z * exp(m - to);           // (nothing before the first rows)
+      z += part;
+      m = to;
     };
-    add(r < ns, m_sink, z_sink);
-    add(r >= ns && r < rows, m_loc, z_loc);
+    add(top_sink, sink, mx_sink, m_sink, z_sink);
+    add(top_loc, local, mx_loc, m_loc, z_loc);
   }
   float dk = 0.f, qq = 0.f;
 #pragma unroll
@@ -675,12 +682,17 @@ __global__ __launch_bounds__(64) void k_head_sparsity(Shape s, const float* __re
   }
   dk = row16_sum(dk);
   qq = row16_sum(qq);
-  const double l_glob = n > 0 ? log((double)n) + (double)(dk * scale) + (double)qq * (double)sigma2_hat[bh] * 0.5 : -INFINITY;
-  const double l_sink = z_sink > 0.0 ? m_sink + log(z_sink) : -INFINITY;
-  const double l_loc = z_loc > 0.0 ? m_loc + log(z_loc) : -INFINITY;
+  // the three logarithms, and then the two exponentials, by neighbouring lanes at once
+  const double ln = log(j == 0 ? (double)n : (j == 1 ? z_sink : z_loc));
+  const double l_glob = n > 0 ? __shfl(ln, 0) + (double)(dk * scale) + (double)qq * (double)sigma2_hat[bh] * 0.5 : -INFINITY;
+  const double l_sink = z_sink > 0.0 ? m_sink + __shfl(ln, 1) : -INFINITY;
+  const double l_loc = z_loc > 0.0 ? m_loc + __shfl(ln, 2) : -INFINITY;
   // rho = exp(l_sink) / (exp(l_sink) + exp(l_glob) + exp(l_loc))
   double rho = 0.0;
-  if (l_sink > -INFINITY) rho = 1.0 / (1.0 + exp(l_glob - l_sink) + exp(l_loc - l_sink));
+  if (l_sink > -INFINITY) {                                     // (uniform)
+    const double e = exp((j == 0 ? l_glob : l_loc) - l_sink);
+    rho = 1.0 / (1.0 + __shfl(e, 0) + __shfl(e, 1));
+  }
   const bool bypass = rho > (double)eps;
   if (lane == 0) {
     if (rho_out) rho_out[bh] = (float)rho;
