@@ -44,15 +44,11 @@ __device__ __forceinline__ void select_registers(SelectShared<NT>& sm, const flo
     hi = mine(u) ? fmaxf(hi, v[u]) : hi;
     mn = mine(u) ? fminf(mn, v[u]) : mn;
   }
-  hi = row16_max(hi);
-  hi = fmaxf(hi, __shfl_xor(hi, 16));
-  hi = fmaxf(hi, __shfl_xor(hi, 32));
-  if (lane == 0) sm.whi[wv] = hi;
+  hi = wave_max_in_last(hi);
+  if (lane == 63) sm.whi[wv] = hi;
   if (from_min) {
-    mn = -row16_max(-mn);
-    mn = fminf(mn, __shfl_xor(mn, 16));
-    mn = fminf(mn, __shfl_xor(mn, 32));
-    if (lane == 0) sm.wlo[wv] = mn;
+    mn = -wave_max_in_last(-mn);
+    if (lane == 63) sm.wlo[wv] = mn;
     __syncthreads();
     lo = sm.wlo[0];
 #pragma unroll
