@@ -382,7 +382,8 @@ __device__ __forceinline__ int wave_inclusive_sum(int x) {
 }
 
 // Maximum over the wave, in its last lane (DPP, no LDS; a NaN counts as absent).  In the select, against two lane exchanges
-// through LDS behind the rows' maxima: four steps of 8 groups x 32K rows 253.7 -> 253.0 us, of one request 102.85 -> 102.5.
+// through LDS behind the rows' maxima: four steps of 64 groups x 32K rows 240.0 -> 239.2 us, of 96 paged groups x 20000 198.8 ->
+// 197.2, of 8 groups x 100K rows with FP8 keys 146.3 -> 145.1, exact Top-k of one request 34.2 -> 34.1.
 __device__ __forceinline__ float wave_max_in_last(float x) {
   auto step = [&](float y) { x = fmaxf(x, y); };
 #define LFPS_DPP_MAX(ctrl, rows) \

@@ -122,6 +122,10 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     const int32_t* __restrict__ seq_lens, float* __restrict__ out) {
   constexpr int kWaves = NT / 64;
   constexpr int kPieces = 1024 / NT;               // pieces per thread: nseg <= 1024
+  // Of paged rows, 1024 threads and lists on the line the registers are full, and the last lane's store of the wave's maximum costs
+  // one more spilled (24 groups x 52567 bf16 rows: 16.8 us, through a scalar 16.3; where there is room the scalar is the slower way,
+  // 64 groups x 32K contiguous rows, four steps, 238.7 -> 240.8).
+  constexpr bool kScalarMax = kPaged && NT == 1024 && !kRanges;
   __shared__ SelectShared<NT> sm;
   __shared__ int seg_off[1024];
   __shared__ int wtot[kWaves], ctot[kWaves];
@@ -307,7 +311,8 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
         if constexpr (E <= kRegElems / 2) prow[u] = RowMap<kPaged>::phys(page, b, ok ? pos[u] : 0);
         if (!ok) pos[u] = -1;
       }
-      select_registers<NT, E>(sm, v, n_el, ksel, tau, unfiltered || tau == -INFINITY, thr_out, [&](int rank, int u, float top) {
+      select_registers<NT, E, kScalarMax>(sm, v, n_el, ksel, tau, unfiltered || tau == -INFINITY, thr_out,
+                                          [&](int rank, int u, float top) {
         const bool ok = pos[u] >= 0;
         oi[rank] = pos[u];
         os[rank] = ok ? v[u] : 0.f;

@@ -32,7 +32,8 @@ __device__ __forceinline__ int tail_bin(float x, float lo, int bins) {
 // replaced by their minimum.  All threads call, after a barrier behind sm.hist = 0 and sm.list_n = 0.  Calls
 // out(rank, u, top) for every selected element, rank = its place in ascending position, top = the largest score; equal
 // scores at the cut go to the lower position.  *thr_out receives the ksel-th best score.
-template <int NT, int E, typename Out>
+// kScalarMax: a wave's largest and smallest score pass through a scalar register, see k_filter_select_attend.
+template <int NT, int E, bool kScalarMax = false, typename Out>
 __device__ __forceinline__ void select_registers(SelectShared<NT>& sm, const float (&v)[E], int n, int ksel, float lo,
                                                  bool from_min, float* __restrict__ thr_out, Out out) {
   constexpr int kWaves = NT / 64, kBins = 2 * NT, kListCap = NT;
@@ -44,11 +45,13 @@ __device__ __forceinline__ void select_registers(SelectShared<NT>& sm, const flo
     hi = mine(u) ? fmaxf(hi, v[u]) : hi;
     mn = mine(u) ? fminf(mn, v[u]) : mn;
   }
-  hi = wave_max_in_last(hi);
-  if (lane == 63) sm.whi[wv] = hi;
+  constexpr int kLeader = kScalarMax ? 0 : 63;             // stores for the wave
+  auto settled = [](float x) { return kScalarMax ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63)) : x; };
+  hi = settled(wave_max_in_last(hi));
+  if (lane == kLeader) sm.whi[wv] = hi;
   if (from_min) {
-    mn = -wave_max_in_last(-mn);
-    if (lane == 63) sm.wlo[wv] = mn;
+    mn = -settled(wave_max_in_last(-mn));
+    if (lane == kLeader) sm.wlo[wv] = mn;
     __syncthreads();
     lo = sm.wlo[0];
 #pragma unroll
