@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "lfps.h"
+#include "range_rule.h"
 
 namespace lfps {
 
@@ -121,7 +122,6 @@ hipError_t launch_filter_score(const Shape& s, const float* q, const KvView& kv,
 // S1 + S2 of a chained step in one kernel (range_score.hip): candidates from the Top-k of the step before (prev_topk, k) or
 // from the table scan's flags (f0, fm; prev_topk == NULL), scored and filtered as above.  seg_count[b, h, 4 i + w] =
 // candidates << 16 | survivors of piece w of range i; bitmap [B, Hkv, bitmap_words] = the candidates.
-constexpr int kRangeMax = 8192;      // rows of a range at most: a word of bitmap per thread
 struct RangeSource {
   const int32_t* prev_topk;          // [B, Hq, kmax]
   const int32_t* k;                  // [B]
@@ -130,7 +130,7 @@ struct RangeSource {
   const uint32_t* fm;
   int flag_words;
 };
-int range_rows(const Shape& s, bool tables);   // a multiple of 64; 0: the separate kernels
+int range_rows(const Shape& s, bool tables);   // see range_rows_for
 hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, const RangeSource& from,
                               const float* thr_state, float margin, const int32_t* skip_if, float* score,
                               int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words,

@@ -1,0 +1,43 @@
+// How long the ranges of the range kernel are (range_score.hip): host arithmetic only, so that a test can compile it by itself.
+#pragma once
+#include <stdint.h>
+
+namespace lfps {
+
+constexpr int kRangeMax = 8192;      // rows of a range at most: a word of bitmap per thread
+
+// Rows per range for `groups` (request, KV head) pairs of up to `rows` rows, a multiple of 64, or 0 where the separate kernels are
+// faster: they cut all candidates into equal parts for two tiles in flight per wave, which wins once there is enough work to fill the
+// chip.
+//   From the Top-k: every workgroup reads the Top-k rows of its group, 5 us in which it loads no rows, so there may be no more rows
+//   than 1024 ranges of 1024.  Steps, separate -> together: 8 groups x 32K rows 34.6 -> 28 us, 24 x 20K (paged fp16) 31.9 ->
+//   23.6; but 64 x 32K 65.4 -> 69 us, paged FP8 128 x 64K 82 -> 98.  Up to the line: 0.5 to 1 million rows in 8 to 256 groups, whole
+//   steps 6 to 10 us shorter (32 x 32K 55.3 -> 48.8, 256 x 4K 64.0 -> 53.8, FP8 8 x 130K, k = 4000 58.2 -> 49.3).  Ranges of 512
+//   rows while that leaves at most 512 of them, else 1024 (512 to 2048 differ by 3 %).
+//   From the table flags, a few words per range: candidates are 4 % of the rows, so ranges of 2048 give a wave 20 rows.
+//   64 x 32K: 23.6 -> 16.1 us for the two kernels.  Up to 4 million rows.
+inline int range_rows_for(int64_t groups, int rows, int heads_per_group, bool tables) {
+  auto ranges = [&](int each) { return groups * ((rows + each - 1) / each); };
+  int range = tables ? 2048 : (ranges(512) <= 512 ? 512 : 1024);
+  if (groups * rows > (tables ? 4 << 20 : 1 << 20)) return 0;
+  while ((rows + range - 1) / range > 256) range *= 2;     // at most 1024 pieces per head
+  // No more than 1024 workgroups, whose fixed part (Top-k rows or flags, list, query) costs more than the rows they add: as many
+  // equal ranges per group as that allows.  1024 are resident at once (four per CU) with ranges of up to 3520 rows; with four heads per
+  // group LDS holds three of the longer ones, which is still the faster form.  Eight table steps with their start, ranges of 2048 ->
+  // these: 64 groups x 32777 rows 594 -> 584 us, x 65509 1033 -> 1016 (one head per group 630 -> 599), 128 x 32709 1032 -> 1019, 512 x
+  // 8109 1257 -> 1246; four steps from the Top-k, ranges of 1024 -> these: 200 x 5195 166 -> 139, 72 x 14505 170 -> 145, 600 x 1395
+  // 191 -> 165.
+  const int64_t most = 1024 / groups;
+  if (most > 0 && ranges(range) > 1024 && range < kRangeMax) {
+    int64_t parts = most;
+    // 513 to 1023 groups get one range each, and half the chip or more its share of the rows.  With four heads per group and more than
+    // 4096 rows two or three ranges are faster, ranges of 2048 -> one -> these: 520 x 8009 1333 -> 1341 -> 1322, 704 x 5909 1411 -> 1449 ->
+    // 1412, 560 x 7309 1322 -> 1333 -> 1311, 600 x 5009 1166 -> 1172 -> 1162; up to 4096 rows, and with fewer heads, one is (800 x 3659
+    // 1245 -> 1232, two 1249; one head per group 600 x 6909 723 -> 701, three 709).
+    if (parts == 1 && heads_per_group == 4 && rows > 4096) parts = (rows + 2687) / 2688;
+    range = (int)(((rows + parts - 1) / parts + 63) & ~63);
+  }
+  return range <= kRangeMax ? range : 0;
+}
+
+}  // namespace lfps

@@ -11,7 +11,7 @@
 //
 // Why one kernel: as two, a step of 8 groups x 32K rows spent 7.8 + 14.5 us here, of which the rows themselves are 5 us;
 // the rest is two launches and the round trips
-// candidates -> list -> geometry -> list -> rows.  Together: 14.4 us.
+// candidates -> list -> geometry -> list -> rows.  Together: 13.7 us.
 #include "candidates.h"
 #include "range_geometry.h"
 #include "score_mfma.h"
@@ -277,28 +277,7 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
 }
 
 // ----------------------------------------------------------------------------- launcher
-// Rows per range, or 0 where the separate kernels are faster: they cut all candidates into equal parts for two tiles in
-// flight per wave, which wins once there is enough work to fill the chip.
-//   From the Top-k: every workgroup reads the Top-k rows of its group, 5 us in which it loads no rows, so all of them have
-//   to be resident at once (four per CU) and there may be no more rows than 1024 ranges of 1024.  Steps, separate ->
-//   together: 8 groups x 32K rows 34.6 -> 28 us, 24 x 20K (paged fp16) 31.9 -> 23.6; but 64 x 32K 65.4 -> 69 us, paged FP8
-//   128 x 64K 82 -> 98.  Up to the line: 0.5 to 1 million rows in 8 to 256 groups, whole steps 6 to 10 us shorter (32 x 32K
-//   55.3 -> 48.8, 256 x 4K 64.0 -> 53.8, FP8 8 x 130K, k = 4000 58.2 -> 49.3).  Ranges of 512 rows while that leaves at most 512 of them, else 1024 (512 to 2048 differ by 3 %).
-//   From the table flags, a few words per range: candidates are 4 % of the rows, so ranges of 2048 give a wave 20 rows.
-//   64 x 32K: 23.6 -> 16.1 us for the two kernels.  Up to 4 million rows.
-int range_rows(const Shape& s, bool tables) {
-  const int64_t groups = (int64_t)s.B * s.Hkv;
-  auto ranges = [&](int rows) { return groups * ((s.Lcap + rows - 1) / rows); };
-  int range = tables ? 2048 : (ranges(512) <= 512 ? 512 : 1024);
-  if (groups * s.Lcap > (tables ? 4 << 20 : 1 << 20)) return 0;
-  while ((s.Lcap + range - 1) / range > 256) range *= 2;   // at most 1024 pieces per head
-  // No more workgroups than the chip holds at once (four per CU): a few rows more than the ranges cover would make one more for
-  // every group, and the last of them begin when the first end.  Table form, 64 groups x 32785 rows: 17 ranges of 2048 a group
-  // 14.0 us, 16 of 2112 11.9.
-  const int64_t most = 1024 / groups;
-  if (most > 0 && ranges(range) > 1024 && range < kRangeMax) range = (int)(((s.Lcap + most - 1) / most + 63) & ~63);
-  return range <= kRangeMax ? range : 0;
-}
+int range_rows(const Shape& s, bool tables) { return range_rows_for((int64_t)s.B * s.Hkv, s.Lcap, s.G, tables); }
 
 hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, const RangeSource& from,
                               const float* thr_state, float margin, const int32_t* skip_if, float* score,

@@ -122,6 +122,13 @@ def test_ranges_that_are_no_power_of_two():
     test_table_steps(43, 8, 8, 4100, 40, 2, 4, "f16", 0)
 
 
+# more than 512 groups, which get one range each (of 5056 rows: 32 bits of the bitmap to a thread, threads past the range), or with
+# four heads per group two of 2560
+@pytest.mark.parametrize("Hq", [8, 32])
+def test_one_range_per_group(Hq):
+    test_table_steps(65, Hq, 8, 5000, 40, 2, 4, "bf16", 0)
+
+
 @pytest.mark.parametrize("L,k", [(1200, 650), (3000, 1600)])
 def test_a_budget_of_most_candidates_keeps_them_all(L, k):
     """A head whose budget takes more than half of its candidates remembers no threshold: other queries do not send it
