@@ -498,10 +498,8 @@ __global__ __launch_bounds__(kScoreThreads) void k_candidates_score_f32(
   kb = kb < 0 ? 0 : (kb > s.kmax ? s.kmax : kb);
   const int words = (s.Lcap + 31) >> 5;
   bitmap_from_topk<kScoreThreads>(s, lds, words, prev_topk + head0 * s.kmax, n, kb);
-  // thread t owns the words [t * each, (t + 1) * each)
-  const int each = (words + kScoreThreads - 1) / kScoreThreads, w0 = tid * each, w1 = w0 + each < words ? w0 + each : words;
-  int mine = 0;
-  for (int w = w0; w < w1; ++w) mine += __popc(lds[w]);
+  uint32_t bits = tid < words ? lds[tid] : 0u;           // a word per thread, see kFusedRowsF32
+  const int mine = __popc(bits);
   const int inc = wave_inclusive_sum(mine);
   if (lane == 63) wave_tot[wave] = inc;
   __syncthreads();
@@ -522,18 +520,12 @@ __global__ __launch_bounds__(kScoreThreads) void k_candidates_score_f32(
   if (s0 >= s1) return;                                  // (workgroup-uniform)
   int32_t* list = reinterpret_cast<int32_t*>(lds + words);
   int32_t* out = cand + (int64_t)bg * s.cand_cap;
-  for (int w = w0; w < w1 && at < s1; ++w) {
-    uint32_t bits = lds[w];
-    if (at + __popc(bits) <= s0) {
-      at += __popc(bits);
-      continue;
-    }
-    for (; bits && at < s1; bits &= bits - 1, ++at) {
-      if (at < s0) continue;
-      const int row = (w << 5) + __ffs(bits) - 1;
-      list[at - s0] = row;
-      out[at] = row;
-    }
+  if (at + mine <= s0) bits = 0u;
+  for (; bits && at < s1; bits &= bits - 1, ++at) {
+    if (at < s0) continue;
+    const int row = (tid << 5) + __ffs(bits) - 1;
+    list[at - s0] = row;
+    out[at] = row;
   }
   __syncthreads();
   const int first = s0 + wave * kRowsPerWaveF32;
@@ -638,11 +630,13 @@ hipError_t launch_group_score(const Shape& s, int dtype, const float* q, const K
 }
 
 // Workgroups of k_candidates_score_f32 that share a group, or 0 where the separate kernels are faster: every
-// workgroup reads the Top-k rows of its group and builds the whole bitmap, which the rows of a long context do not pay for.  Two
-// workgroups per CU: more of them repeat that, fewer wait longer for their rows.  Two steps, separate -> together, us: 8 groups x 2000
-// rows 34.8 -> 31.6, x 4096 36.5 -> 34.0, x 8000 43.1 -> 37.9, x 10000 42.2 -> 42.7, x 32K 74.4 -> 80.8; 128 x 4000 63.5 -> 57.5,
-// 128 x 8000 96.7 -> 90.5, 256 x 4000 103.5 -> 98.7; with 1024 workgroups 8 x 8000 40.6, with 256 256 x 4000 102.7.
-static constexpr int kFusedRowsF32 = 9216;
+// workgroup reads the Top-k rows of its group and builds the whole bitmap, which the rows of a long context do not pay for.  The line
+// is a word of bitmap per thread (beyond, half the threads count and list two words each and the others none).  Two
+// workgroups per CU: more of them repeat the bitmap, fewer wait longer for their rows.  Two steps, separate -> together, us: 8 groups x
+// 2000 rows 34.8 -> 31.6, x 4096 36.5 -> 34.0, x 8180 45.5 -> 40.0 (k = 2250 98.2 -> 97.0), x 9000 43.1 -> 43.7 (105.1 -> 107.3), x
+// 32K 74.4 -> 80.8; 128 x 4000 63.5 -> 57.5, 128 x 8000 96.7 -> 90.5, 256 x 4000 103.5 -> 98.7; with 1024 workgroups 8 x 8000 40.6,
+// with 256 256 x 4000 102.7.
+static constexpr int kFusedRowsF32 = 32 * kScoreThreads;
 static int fused_f32_parts(const Shape& s) {
   const int64_t groups = (int64_t)s.B * s.Hkv;
   if (s.Lcap > kFusedRowsF32) return 0;

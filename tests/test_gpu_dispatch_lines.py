@@ -88,3 +88,28 @@ def test_tables_from_eight_queries_cost_no_more_than_from_nine():
     eight, nine = least_us(lambda: ctx.lfps_tables_init(q[:8], kv), lambda: ctx.lfps_tables_init(q, kv))
     assert eight <= 1.01 * nine, (eight, nine)
     ctx.close()
+
+
+# fp32 steps find and score their candidates in one kernel up to a capacity of 8192 rows: the same step costs no more there than in a
+# context of one row more, which takes two (8100 rows: 0.88 times as much with a budget of 250, 0.99 with 2250).  With the line at 9216
+# the last thousand rows cost 1.02 times as much with the large budget.
+@pytest.mark.parametrize("line,k", [(8192, 250), (8192, 2250), (9216, 250), (9216, 2250)])
+def test_fp32_steps_in_one_kernel_cost_no_more_than_in_two(line, k):
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(line + k)
+    n = line - 92
+    K = torch.randn((1, 8, line + 1, 128), device=DEV, generator=g)
+    q = torch.randn((1, 32, 128), device=DEV, generator=g)
+    prev = torch.stack([torch.randperm(n, device=DEV, generator=g)[:k].sort().values for _ in range(32)])[None].to(torch.int32)
+    seq, ks = (torch.tensor([x], dtype=torch.int32, device=DEV) for x in (n, k))
+    calls, outs = [], []
+    for room in (line, line + 1):
+        ctx = Lfps(batch=1, kv_dtype="f32", max_seq_len=room, max_k=k, radius=4)
+        kv = ctx.kv_view(K[:, :, :room], K[:, :, :room], seq)
+        idx, out = torch.zeros((1, 32, k), dtype=torch.int32, device=DEV), torch.zeros((1, 32, 128), device=DEV)
+        calls.append(lambda ctx=ctx, kv=kv, idx=idx, out=out: ctx.lfps_step(q, kv, prev, ks, idx, out))
+        outs.append(out)
+    within, beyond = least_us(*calls, each=100)
+    assert torch.equal(*outs)
+    assert within <= 1.01 * beyond, (within, beyond)
