@@ -1022,35 +1022,36 @@ __global__ __launch_bounds__(kPriorThreads) void k_prior_partials(Shape s, const
   }
 }
 
-// grid (B*Hkv, 5), 1024 threads: the partials of a group.  Four workgroups take 64 channels of K or V each, sixteen threads a
-// channel (all of a thread's partials on their way at once: one workgroup for all of them took 3.9 us longer for 128 partials of
-// 8 groups: priors of 1 x 32K 34.7 -> 30.8 us), the fifth the scores of the heads, a wave each.
-__global__ __launch_bounds__(1024) void k_prior_final(Shape s, const float* __restrict__ q,
-                                                      const int32_t* __restrict__ seq_lens,
-                                                      const double* __restrict__ part, int splits,
-                                                      float* __restrict__ kbar, float* __restrict__ vbar,
-                                                      float* __restrict__ sigma2_hat) {
-  __shared__ double red[16][64];
+// The partials of a group: the sums of K and V in four blocks of 64 channels, W waves to a block, a thread every W-th partial of a
+// channel with all of them on their way at once, and the scores of the heads, a wave each.  grid (B*Hkv, 5): a workgroup to
+// each block and one to the scores (one workgroup for everything took 3.9 us longer for 128 partials of 8 groups: priors of 1 x 32K
+// 34.7 -> 30.8 us), or kTogether: grid (B*Hkv), everything by one.
+template <int W, bool kTogether>
+__global__ __launch_bounds__(64 * W * (kTogether ? 4 : 1)) void k_prior_final(
+    Shape s, const float* __restrict__ q, const int32_t* __restrict__ seq_lens, const double* __restrict__ part, int splits,
+    float* __restrict__ kbar, float* __restrict__ vbar, float* __restrict__ sigma2_hat) {
+  __shared__ double red[kTogether ? 4 : 1][W][64];
   const int bg = blockIdx.x, b = bg / s.Hkv, g = bg % s.Hkv, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int n = seq_lens[b];
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   const int cnt = n - s.n_sink;
   const int stride = prior_partial(s.G);
   const double* p = part + (int64_t)bg * splits * stride;
-  if (blockIdx.y < 4) {
-    const int c = 64 * blockIdx.y + lane;
+  const int mine = kTogether ? wave / W : 0, first = kTogether ? wave % W : wave;
+  if (kTogether || blockIdx.y < 4) {
+    const int c = 64 * (kTogether ? mine : blockIdx.y) + lane;
     double t = 0.0;
 #pragma unroll 8
-    for (int k = wave; k < splits; k += 16) t += p[(int64_t)k * stride + c];
-    red[wave][lane] = t;
+    for (int k = first; k < splits; k += W) t += p[(int64_t)k * stride + c];
+    red[mine][first][lane] = t;
     __syncthreads();
-    if (wave == 0) {
-      t = red[0][lane];
+    if (first == 0) {
+      t = red[mine][0][lane];
 #pragma unroll
-      for (int w = 1; w < 16; ++w) t += red[w][lane];
+      for (int w = 1; w < W; ++w) t += red[mine][w][lane];
       (c < kD ? kbar : vbar)[(int64_t)bg * kD + (c & (kD - 1))] = cnt > 0 ? (float)(t / (double)cnt) : 0.f;
     }
-    return;
+    if (!kTogether) return;
   }
   if (wave < s.G) {
     const int64_t bh = (int64_t)b * s.Hq + (int64_t)g * s.G + wave;
@@ -1301,8 +1302,15 @@ static hipError_t launch_priors_t(const Shape& s, const float* q, const KvView& 
 #undef LFPS_LAUNCH_PRI
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_prior_final, dim3(s.B * s.Hkv, 5), dim3(1024), 0, st, s, q, kv.seq_lens, part, splits, kbar, vbar,
-                     sigma2_hat);
+#define LFPS_LAUNCH_FINAL(W, TOGETHER)                                                                                  \
+  hipLaunchKernelGGL((k_prior_final<W, TOGETHER>), dim3(s.B * s.Hkv, TOGETHER ? 1 : 5), dim3(64 * W * (TOGETHER ? 4 : 1)), 0, \
+                     st, s, q, kv.seq_lens, part, splits, kbar, vbar, sigma2_hat)
+  // From 256 groups on (four partials each) as many workgroups as groups: 1024 groups x 1000 rows 109.7 us, with five of sixteen waves
+  // each 116.1, five of four 112.3; 512 x 2000 103.4, 109.1.  Up to sixteen partials four waves: 64 x 4000 30.9 -> 29.9.
+  if (s.B * s.Hkv >= 256) LFPS_LAUNCH_FINAL(4, true);
+  else if (splits > 16) LFPS_LAUNCH_FINAL(16, false);
+  else LFPS_LAUNCH_FINAL(4, false);
+#undef LFPS_LAUNCH_FINAL
   return hipGetLastError();
 }
 

@@ -102,6 +102,34 @@ def test_priors_at_split_edges(L, heads, fmt, page, n_sink):
     ctx.close()
 
 
+# four partials a group merged by one workgroup (256 groups and more) and by five, sixteen, seventeen and 128 partials; requests with
+# no rows, with fewer than there are parts, with all.  The bounds of the test above: 24-bit sums over n / 64 rows at most.
+@pytest.mark.parametrize("B,Hq,Hkv,L", [(300, 1, 1, 70), (32, 32, 8, 300), (255, 2, 1, 513), (64, 4, 1, 4090), (61, 4, 1, 4353), (1, 8, 8, 32768)])
+def test_priors_however_the_partials_are_merged(B, Hq, Hkv, L):
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    K, V = (torch.randn((B, Hkv, L, 128), device=DEV, generator=g).to(torch.bfloat16) for _ in range(2))
+    q = torch.randn((B, Hq, 128), device=DEV, generator=g)
+    lens = [max(0, L - 17 * b) for b in range(B)]
+    ctx = Lfps(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, max_seq_len=L, max_k=4, radius=1, n_sink=3)
+    kbar, vbar = (torch.full((B, Hkv, 128), 9.0, device=DEV) for _ in range(2))
+    s2 = torch.full((B, Hq), 9.0, device=DEV)
+    ctx.lfps_priors(q, ctx.kv_view(K, V, torch.tensor(lens, dtype=torch.int32, device=DEV)), kbar, vbar, s2)
+    G = Hq // Hkv
+    for b in range(B):
+        rows = K[b, :, 3:lens[b]].double(), V[b, :, 3:lens[b]].double()
+        if lens[b] <= 3:
+            assert not (kbar[b].any() or vbar[b].any() or s2[b].any())
+            continue
+        for got, x in ((kbar, rows[0]), (vbar, rows[1])):
+            torch.testing.assert_close(got[b].double(), x.mean(1), rtol=0, atol=2e-6)
+        qb = q[b].double().view(Hkv, G, 128)
+        want = (rows[0] @ qb.transpose(1, 2).contiguous() / 128**0.5).var(1, unbiased=False) / qb.square().sum(-1)
+        torch.testing.assert_close(s2[b].double().view(Hkv, G), want, rtol=2e-5, atol=1e-9)
+    ctx.close()
+
+
 # one query (from stored dot products), one batch of queries, two; rows in whole 128-row tiles and in the ones cut by the
 # sinks and by the end
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
