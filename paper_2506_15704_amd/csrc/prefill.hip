@@ -688,10 +688,10 @@ __global__ __launch_bounds__(kBatchThreads, 2) void k_batch_apply(
         const float* moved = &lds.moved[my_span][my_head][moved_at * kSpanRows + my_row];
         float av = 0.f, as = 0.f;
 #pragma unroll
-        for (int quad = Lds::kQuads / G - 1; quad >= 0; --quad) {
-          if (quad >= quads) continue;
-          av += sum[quad * G * B::kRows];
-          as += moved[quad * G * kRing];
+        for (int quad = Lds::kQuads / G - 1; quad >= 0; --quad) {          // (all reads at once: no branch at a quad that is not there)
+          const float v = sum[quad * G * B::kRows], x = moved[quad * G * kRing];
+          av += quad < quads ? v : 0.f;
+          as += quad < quads ? x : 0.f;
         }
         const int row = work.wg_first + my_span * work.span_rows + at * kSpanRows + my_row, pos = row + j0 - 1;
         if (first) {
@@ -710,44 +710,37 @@ __global__ __launch_bounds__(kBatchThreads, 2) void k_batch_apply(
         }
       }
     };
-    // (the barriers of the two kinds of waves are the same ones, in the same order)
-    auto walk = [&](auto loads) __attribute__((always_inline)) {
-      constexpr bool kLoads = decltype(loads)::value;
-      ChunkRows<kPaged, kKind, B, kLoadThreads> rows;
-      if constexpr (kLoads) {
-        rows.start(pg, b, work.wg_first - kSpanRows, work.span_rows, n);   // chunk -1: the rows before the spans
-        rows.fetch(Kbg, pg, b, stride_b, stride_n, false);
-        rows.put(lds.chunk[1]);
+    const bool loads = wave < kHistWaves / 2;              // (wave-uniform; the barriers stand outside of what it decides)
+    ChunkRows<kPaged, kKind, B, kLoadThreads> rows;
+    if (loads) {
+      rows.start(pg, b, work.wg_first - kSpanRows, work.span_rows, n);     // chunk -1: the rows before the spans
+      rows.fetch(Kbg, pg, b, stride_b, stride_n, false);
+      rows.put(lds.chunk[1]);
+      rows.fetch(Kbg, pg, b, stride_b, stride_n, false);
+    }
+    __syncthreads();
+    constexpr std::integral_constant<int, 0> kWhole{};
+    constexpr std::integral_constant<int, (B::kSubs > 2 ? B::kSubs - 2 : 0)> kLast{};      // the last 32 rows
+    if (!idle) products(kLast, std::true_type{}, lds.chunk[1], -1, 1, 2);
+    int moved_at = 0;                                      // chunk at % 3
+    for (int at = 0; at < work.chunks; ++at) {
+      if (loads) {
+        rows.put(lds.chunk[at & 1]);
         rows.fetch(Kbg, pg, b, stride_b, stride_n, false);
       }
       __syncthreads();
-      constexpr std::integral_constant<int, 0> kWhole{};
-      constexpr std::integral_constant<int, (B::kSubs > 2 ? B::kSubs - 2 : 0)> kLast{};    // the last 32 rows
-      if (!idle) products(kLast, std::true_type{}, lds.chunk[1], -1, 1, 2);
-      int moved_at = 0;                                    // chunk at % 3
-      for (int at = 0; at < work.chunks; ++at) {
-        if constexpr (kLoads) {
-          rows.put(lds.chunk[at & 1]);
-          rows.fetch(Kbg, pg, b, stride_b, stride_n, false);
-        }
-        __syncthreads();
-        if constexpr (!kLoads) {
-          if (at > 0) combine(at - 1, (at - 1) & 1, moved_at > 0 ? moved_at - 1 : 2);
-        }
-        const int base = work.first + at * kSpanRows;
-        if (idle) {
-        } else if (base >= s.n_sink && base + kSpanRows <= all_see) {
-          products(kWhole, std::false_type{}, lds.chunk[at & 1], at, at & 1, moved_at);
-        } else {
-          products(kWhole, std::true_type{}, lds.chunk[at & 1], at, at & 1, moved_at);
-        }
-        moved_at = moved_at < 2 ? moved_at + 1 : 0;
+      if (!loads && at > 0) combine(at - 1, (at - 1) & 1, moved_at > 0 ? moved_at - 1 : 2);
+      const int base = work.first + at * kSpanRows;
+      if (idle) {
+      } else if (base >= s.n_sink && base + kSpanRows <= all_see) {
+        products(kWhole, std::false_type{}, lds.chunk[at & 1], at, at & 1, moved_at);
+      } else {
+        products(kWhole, std::true_type{}, lds.chunk[at & 1], at, at & 1, moved_at);
       }
-      __syncthreads();
-      if constexpr (!kLoads) combine(work.chunks - 1, (work.chunks - 1) & 1, moved_at > 0 ? moved_at - 1 : 2);
-    };
-    if (wave < kHistWaves / 2) walk(std::true_type{});
-    else walk(std::false_type{});
+      moved_at = moved_at < 2 ? moved_at + 1 : 0;
+    }
+    __syncthreads();
+    if (!loads) combine(work.chunks - 1, (work.chunks - 1) & 1, moved_at > 0 ? moved_at - 1 : 2);
   }
   if (first) {
     const int reached = (n + work.wg_rows - 1) / (work.wg_rows > 0 ? work.wg_rows : 1) * work.wg_rows;
