@@ -260,7 +260,7 @@ __device__ __forceinline__ void moments_of_chunk(const float (&xv)[U], const flo
 // of an MFMA A operand, the three terms of the query one operand each.  (With the terms as rows of one operand, sixteen rows were
 // four heads of one query and four of them zeros; with the rows in registers and the queries walked, every workgroup first
 // loaded all of its rows and then computed, and each query's maximum and sum took a reduction over lanes per 128 rows.)
-// U waves (2, 4, 8) of the eight of a workgroup hold the units of a batch; where that is not all eight, the workgroup's rows are
+// U waves (1, 2, 4, 8) of the eight of a workgroup hold the units of a batch; where that is not all eight, the workgroup's rows are
 // cut into 8 / U spans of their own, and a chunk of R rows holds R U / 8 of each.  Row 4 i + c of an operand (D: lane group i,
 // register c) is query 4 quad + c, quad = unit * 4 / G + i / G, of head i % G.
 constexpr int kBatchThreads = 64 * kHistWaves;
@@ -277,7 +277,8 @@ struct BatchShape {
   static constexpr int kSpanRows = R / kSpans;             // of a chunk
   static constexpr int kSubs = kSpanRows / 16;             // sub-tiles of 16 rows a wave takes of a chunk
 };
-constexpr int kStatsRows = 64, kApplyRows = 128;
+constexpr int kApplyRows = 128;
+constexpr int stats_rows(int U) { return U == 1 ? 128 : 64; }   // (a wave's span of a chunk is sixteen rows at least)
 
 // The rows of a workgroup's chunks: from memory to registers, from there to LDS, by the first kThreads of its threads.
 template <bool kPaged, int kKind, typename B, int kThreads>
@@ -489,7 +490,7 @@ __global__ __launch_bounds__(kBatchThreads, 4) void k_batch_stats(
     Shape s, const float* __restrict__ q0, int64_t q_stride, int j0, int nq, const void* __restrict__ K,
     int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage pg, const int32_t* __restrict__ seq_lens,
     float* __restrict__ part_m, double* __restrict__ part_l, int32_t* __restrict__ flags, float kept_bytes) {
-  using B = BatchShape<U, kStatsRows>;
+  using B = BatchShape<U, stats_rows(U)>;
   using Op = typename KSub<kKind>::Operand;
   __shared__ u32x4 chunk[2][B::kPieces];
   __shared__ float wm[kHistWaves][16];
@@ -608,6 +609,9 @@ __global__ __launch_bounds__(kBatchThreads, 2) void k_batch_apply(
   using Op = typename KSub<kKind>::Operand;
   using Lds = ApplyLds<U>;
   constexpr int kSpanRows = B::kSpanRows, kRing = 3 * kSpanRows;
+  constexpr int kMostQuads = 4 * U / G;
+  static_assert(4 * (kMostQuads - 1) + 15 < 2 * kSpanRows, "what is moved up ends in the next chunk");
+  static_assert(4 * kMostQuads <= (kSpanRows < 32 ? kSpanRows : 32), "what reaches into a span comes from the rows before it that are taken");
   extern __shared__ char lds_raw[];
   Lds& lds = *reinterpret_cast<Lds*>(lds_raw);
   const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;
@@ -1092,11 +1096,12 @@ static int batch_blocks(const Shape& s, int rows, int slots, int wait) {
   }
   return (int)best;
 }
-static int stats_blocks(const Shape& s) { return batch_blocks(s, kStatsRows, 512, 4); }   // two workgroups per CU
+static int stats_blocks(const Shape& s, int U) { return batch_blocks(s, stats_rows(U), 512, 4); }   // two workgroups per CU
 static int apply_blocks(const Shape& s) { return batch_blocks(s, kApplyRows, 256, 2); }   // one
 
 int64_t table_init_scratch_bytes(const Shape& s) {
-  const int most = hist_blocks(s) > stats_blocks(s) ? hist_blocks(s) : stats_blocks(s);
+  int most = hist_blocks(s);
+  for (int U = 1; U <= 2; ++U) most = stats_blocks(s, U) > most ? stats_blocks(s, U) : most;
   const int parts = moment_chunks(s) > apply_blocks(s) ? moment_chunks(s) : apply_blocks(s);
   return (int64_t)s.B * s.Hkv * most * kHistBatch * s.G * (8 + 4) + (int64_t)s.B * s.Hq * parts * 12 * 8;
 }
@@ -1114,15 +1119,15 @@ static float stats_kept_bytes(const Shape& s, int n_queries) {
   return n_queries == 1 ? (float)kKeptBytes - tables : 280.f * (1 << 20) - 0.5f * tables;
 }
 
-// The units of a batch of nq queries as the kernels are built for them.  (What the quads of a chunk move up has to end in the next
-// one: 28 rows at most without grouping, where sixteen of a span's rows were too few.)
+// The units of a batch of nq queries as the kernels are built for them.  (What the quads of a chunk move up, 4 rows for each before
+// the last and 15 for the rows, has to end in the next one.)
 static int batch_units(int G, int nq) {
   const int units = ((nq + 3) / 4 * G + 3) / 4;
-  return units <= 2 && G > 1 ? 2 : (units <= 4 ? 4 : 8);
+  return units == 1 && G > 1 ? 2 : (units == 3 ? 4 : (units > 4 ? 8 : units));
 }
 
 // X(heads per group, units, key format)
-#define LFPS_BATCH_FOR_EACH_U(X, KIND) X(4, 2, KIND) X(4, 4, KIND) X(4, 8, KIND) X(2, 2, KIND) X(2, 4, KIND) X(1, 4, KIND)
+#define LFPS_BATCH_FOR_EACH_U(X, KIND) X(4, 2, KIND) X(4, 4, KIND) X(4, 8, KIND) X(2, 2, KIND) X(2, 4, KIND) X(1, 1, KIND) X(1, 2, KIND)
 #define LFPS_BATCH_FOR_EACH(X) \
   LFPS_BATCH_FOR_EACH_U(X, kKindBf16) LFPS_BATCH_FOR_EACH_U(X, kKindFp8) LFPS_BATCH_FOR_EACH_U(X, kKindF16)
 
@@ -1158,7 +1163,7 @@ template <int G, bool kPaged, int kKind, int U>
 static hipError_t launch_batch_t(const Shape& s, float* tab_ver, float* tab_sla, const float* q0, int64_t q_stride, int j0,
                                  int nq, int n_queries, double gamma, const KvView& kv, void* scratch, int32_t* flags,
                                  hipStream_t st) {
-  const int parts = stats_blocks(s), blocks = apply_blocks(s);
+  const int parts = stats_blocks(s, U), blocks = apply_blocks(s);
   const HistScratch to(s, scratch, parts, blocks);
   const dim3 block(kBatchThreads);
   const float kept = stats_kept_bytes(s, n_queries);

@@ -113,3 +113,25 @@ def test_fp32_steps_in_one_kernel_cost_no_more_than_in_two(line, k):
     within, beyond = least_us(*calls, each=100)
     assert torch.equal(*outs)
     assert within <= 1.01 * beyond, (within, beyond)
+
+
+# over the same keys, ungrouped heads cost no more than twice as many heads in groups of two: their queries make half the units, and
+# the waves of a workgroup hold those there are (0.75 to 0.95 times as much; up to 1.4 times with four units for any number)
+@pytest.mark.parametrize("B,L,fp8,s", [(32, 4000, True, 2), (32, 4000, True, 16), (32, 4000, True, 32), (2, 20000, False, 4)])
+def test_tables_of_ungrouped_heads_cost_no_more_than_of_twice_as_many(B, L, fp8, s):
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L + s)
+    K = torch.randn((B, 8, L, 128), device=DEV, generator=g).to(torch.float8_e4m3fn if fp8 else torch.bfloat16)
+    V = torch.zeros((B, 8, L, 128), dtype=torch.bfloat16, device=DEV)
+    seq = torch.full((B,), L, dtype=torch.int32, device=DEV)
+    ctxs, calls = [], []
+    for Hq in (8, 16):
+        ctx = Lfps(batch=B, n_q_heads=Hq, n_kv_heads=8, max_seq_len=L, max_k=64, radius=1, table_mode=True, n_sink=4, k_fp8=fp8)
+        kv, q = ctx.kv_view(K, V, seq), torch.randn((s, B, Hq, 128), device=DEV, generator=g)
+        ctxs.append(ctx)
+        calls.append(lambda ctx=ctx, kv=kv, q=q: ctx.lfps_tables_init(q, kv))
+    one, two = least_us(*calls)
+    assert one <= two, (one, two)
+    for ctx in ctxs:
+        ctx.close()

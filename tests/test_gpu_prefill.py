@@ -76,6 +76,15 @@ def test_tables_from_many_queries(L, s, heads, fmt, page):
     ctx.close()
 
 
+# ungrouped heads: one unit of sixteen queries (spans of sixteen rows, which all sixteen queries reach across), two, and both in
+# turn; lengths around a span, a chunk of 128 rows and a workgroup
+@pytest.mark.parametrize("L,s,fmt,page", [
+    (17, 16, "bf16", 0), (127, 16, "bf16", 0), (129, 15, "fp8", 16), (1041, 9, "f16", 0), (2111, 16, "bf16", 64), (300, 17, "bf16", 0),
+    (1024, 48, "fp8", 0), (640, 2, "bf16", 16)])
+def test_tables_of_ungrouped_heads(L, s, fmt, page):
+    test_tables_from_many_queries(L, s, (2, 2), fmt, page)
+
+
 @pytest.mark.parametrize("L,heads,fmt,page,n_sink", [
     (255, (8, 2), "bf16", 0, 4), (257, (4, 2), "fp8kv", 16, 0), (1030, (2, 2), "fp8", 0, 4), (777, (8, 2), "f16", 64, 4),
     (513, (8, 2), "f32", 0, 1), (17, (8, 2), "bf16", 0, 4), (3, (8, 2), "bf16", 0, 4)])
