@@ -1081,14 +1081,17 @@ static int hist_blocks(const Shape& s) {
 
 static int moment_chunks(const Shape& s) { return (s.Lcap + kMomentRows - 1) / kMomentRows; }
 
-// The same in the kernels of many queries, in chunks of `rows` and with `slots` workgroups on the chip at a time: as many as make
-// the fewest chunks one after the other, a workgroup beginning with about `wait` chunks' worth of waiting for its first rows and
-// queries.
-static int batch_blocks(const Shape& s, int rows, int slots, int wait) {
-  const int64_t groups = (int64_t)s.B * s.Hkv, tiles = (s.Lcap + rows - 1) / rows;
+// The same in the kernels of many queries, in chunks of `rows`: as many workgroups as make the least of the chunks one after the
+// other, a workgroup beginning with about `wait` chunks' worth of waiting for its first rows and queries.  A CU takes one workgroup at a
+// time, or with `pairs` two, which together take 1.75 times as long.  merge: twentieths of a chunk that 32 workgroups of a group
+// cost whoever reads their results (merge_hist: eight loads of each of four lanes at a time).
+static int batch_blocks(const Shape& s, int rows, int wait, bool pairs, int merge) {
+  const int64_t groups = (int64_t)s.B * s.Hkv, tiles = (s.Lcap + rows - 1) / rows, slots = pairs ? 512 : 256;
   int64_t best = 1, least = INT64_MAX;
   for (int64_t n = 1; n <= tiles && n <= slots; ++n) {
-    const int64_t cost = (groups * n + slots - 1) / slots * ((tiles + n - 1) / n + wait);
+    const int64_t all = groups * n, rest = all % slots;
+    const int64_t rounds = all / slots * (pairs ? 35 : 20) + (rest > 256 ? 35 : (rest > 0 ? 20 : 0));     // in twentieths
+    const int64_t cost = rounds * ((tiles + n - 1) / n + wait) + (n + 31) / 32 * merge;
     if (cost < least) {
       least = cost;
       best = n;
@@ -1096,8 +1099,11 @@ static int batch_blocks(const Shape& s, int rows, int slots, int wait) {
   }
   return (int)best;
 }
-static int stats_blocks(const Shape& s, int U) { return batch_blocks(s, stats_rows(U), 512, 4); }   // two workgroups per CU
-static int apply_blocks(const Shape& s) { return batch_blocks(s, kApplyRows, 256, 2); }   // one
+// Every workgroup of the second kernel reads all partials of its group before its first product: 32 queries of one group (four heads) x
+// 128K rows with 512 of them 85.3 us, 256 61.6, 192 59.3, 128 58.4 (two queries 39.4, 31.1, 32.1, 33.1), of 8 groups x 32K with 64 71.6,
+// 32 65.6, of 8 x 128K with 64 208, 32 219.
+static int stats_blocks(const Shape& s, int U) { return batch_blocks(s, stats_rows(U), 4, true, 62); }
+static int apply_blocks(const Shape& s) { return batch_blocks(s, kApplyRows, 2, false, 0); }
 
 int64_t table_init_scratch_bytes(const Shape& s) {
   int most = hist_blocks(s);

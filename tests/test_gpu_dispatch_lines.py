@@ -135,3 +135,23 @@ def test_tables_of_ungrouped_heads_cost_no_more_than_of_twice_as_many(B, L, fp8,
     assert one <= two, (one, two)
     for ctx in ctxs:
         ctx.close()
+
+
+# the second kernel of a table start merges what every workgroup of the first has left: of one long group the first is cut so that this
+# does not outweigh it (four times the rows cost 1.6 times as much; 1.27 with 512 parts for either number of rows)
+def test_tables_of_a_shorter_group_cost_much_less():
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(4)
+    K = torch.randn((1, 1, 131072, 128), device=DEV, generator=g).to(torch.bfloat16)
+    q = torch.randn((32, 1, 4, 128), device=DEV, generator=g)
+    ctxs, calls = [], []
+    for L in (32768, 131072):
+        ctx = Lfps(batch=1, n_q_heads=4, n_kv_heads=1, max_seq_len=L, max_k=64, radius=1, table_mode=True, n_sink=4)
+        kv = ctx.kv_view(K[:, :, :L], K[:, :, :L], torch.full((1,), L, dtype=torch.int32, device=DEV))
+        ctxs.append(ctx)
+        calls.append(lambda ctx=ctx, kv=kv: ctx.lfps_tables_init(q, kv))
+    short, long = least_us(*calls)
+    assert short <= 0.7 * long, (short, long)
+    for ctx in ctxs:
+        ctx.close()
