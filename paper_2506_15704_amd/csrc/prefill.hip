@@ -473,11 +473,12 @@ struct BatchWork {
   }
 };
 
-// How far query jq of a batch of nq sees: rows below (0: no such query), and how far all queries of a unit do.
+// How far query jq of a batch of nq sees: rows below (0: no such query), and how far all queries of a unit that there are do.
 __device__ __forceinline__ int seen_by(int jq, int j0, int nq, int n) { return jq < nq ? n - (j0 + jq) + 1 : 0; }
 template <int G>
 __device__ __forceinline__ int seen_by_all(int unit, int j0, int nq, int n) {
-  return seen_by((unit + 1) * (16 / G) - 1, j0, nq, n);
+  const int last = (unit + 1) * (16 / G) - 1;
+  return seen_by(last < nq ? last : nq - 1, j0, nq, n);
 }
 
 // grid (blocks per group, B*Hkv).  Queries j0 .. j0 + nq - 1 (j = 1: the most recent); query j sees the offloaded rows
@@ -650,22 +651,29 @@ __global__ __launch_bounds__(kBatchThreads, 2) void k_batch_apply(
     const int quad = work.unit * (4 / G) + kb / G;
     const float* my_ref = &lds.ref[0][kb % G][(4 * quad) & (kHistBatch - 1)];
     float enter[3] = {0.f, 0.f, 0.f};                      // the rotated sums of the sixteen rows before
+    // masked 0: every row is seen by all queries of the unit, 1: by those that there are, 2: a row may not be seen.  (A query that is
+    // not there has to be left out: its products are zeros, but not with a row that is not finite.)
+    constexpr std::integral_constant<int, 0> kFull{};
+    constexpr std::integral_constant<int, 1> kPart{};
+    constexpr std::integral_constant<int, 2> kRows{};
+    const bool full = (work.unit + 1) * (16 / G) <= nq;    // (wave-uniform)
     auto products = [&](auto from, auto masked, const u32x4* buf, int at, int sum_at, int moved_at) __attribute__((always_inline)) {
-      constexpr bool kMasked = decltype(masked)::value;
+      constexpr int kMasked = decltype(masked)::value;
       const int row0 = work.first + at * kSpanRows + j;
       const u32x4* mine = buf + (work.span * kSpanRows + j) * kChunkPitch + chunk_piece(0, kb);
       float* sum = &lds.sum[sum_at][work.unit * 4 + kb][work.span * kSpanRows + j];
       float* moved = lds.moved[work.span][work.unit * 4 + kb];
       const f32x4 top = *reinterpret_cast<const f32x4*>(my_ref), hi = *reinterpret_cast<const f32x4*>(my_ref + 4 * kHistBatch),
                   lo = *reinterpret_cast<const f32x4*>(my_ref + 8 * kHistBatch);
-      walk_chunk<B::kSubs, decltype(from)::value, kMasked ? 5 : 3>(queries, mine, [&](int t, const f32x4& v) __attribute__((always_inline)) {
+      walk_chunk<B::kSubs, decltype(from)::value, kMasked == 2 ? 5 : 3>(queries, mine, [&](int t, const f32x4& v) __attribute__((always_inline)) {
         float w[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           float x = v[c];
-          if constexpr (kMasked)
+          if constexpr (kMasked == 2)
             x = row0 + 16 * t >= s.n_sink && row0 + 16 * t < seen_by(4 * quad + c, j0, nq, n) ? x : kNoScore;
           w[c] = weigh(product_weight(x, top[c]), hi[c], lo[c]);
+          if constexpr (kMasked == 1) w[c] = 4 * quad + c < nq ? w[c] : 0.f;
         }
         float up = w[3];
 #pragma unroll
@@ -725,7 +733,7 @@ __global__ __launch_bounds__(kBatchThreads, 2) void k_batch_apply(
     __syncthreads();
     constexpr std::integral_constant<int, 0> kWhole{};
     constexpr std::integral_constant<int, (B::kSubs > 2 ? B::kSubs - 2 : 0)> kLast{};      // the last 32 rows
-    if (!idle) products(kLast, std::true_type{}, lds.chunk[1], -1, 1, 2);
+    if (!idle) products(kLast, kRows, lds.chunk[1], -1, 1, 2);
     int moved_at = 0;                                      // chunk at % 3
     for (int at = 0; at < work.chunks; ++at) {
       if (loads) {
@@ -736,10 +744,12 @@ __global__ __launch_bounds__(kBatchThreads, 2) void k_batch_apply(
       if (!loads && at > 0) combine(at - 1, (at - 1) & 1, moved_at > 0 ? moved_at - 1 : 2);
       const int base = work.first + at * kSpanRows;
       if (idle) {
-      } else if (base >= s.n_sink && base + kSpanRows <= all_see) {
-        products(kWhole, std::false_type{}, lds.chunk[at & 1], at, at & 1, moved_at);
+      } else if (!(base >= s.n_sink && base + kSpanRows <= all_see)) {
+        products(kWhole, kRows, lds.chunk[at & 1], at, at & 1, moved_at);
+      } else if (full) {
+        products(kWhole, kFull, lds.chunk[at & 1], at, at & 1, moved_at);
       } else {
-        products(kWhole, std::true_type{}, lds.chunk[at & 1], at, at & 1, moved_at);
+        products(kWhole, kPart, lds.chunk[at & 1], at, at & 1, moved_at);
       }
       moved_at = moved_at < 2 ? moved_at + 1 : 0;
     }

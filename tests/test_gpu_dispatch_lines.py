@@ -155,3 +155,20 @@ def test_tables_of_a_shorter_group_cost_much_less():
     assert short <= 0.7 * long, (short, long)
     for ctx in ctxs:
         ctx.close()
+
+
+# a batch whose last unit lacks queries costs no more than a full one (0.97 to 0.99 times as much; 1.02 to 1.03 times while every row
+# of such a unit was looked at one by one)
+@pytest.mark.parametrize("few,full", [(13, 16), (30, 32)])
+def test_tables_from_an_incomplete_unit_cost_no_more_than_from_a_full_one(few, full):
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(few)
+    L = 32768
+    K = torch.randn((1, 8, L, 128), device=DEV, generator=g).to(torch.bfloat16)
+    q = torch.randn((full, 1, 32, 128), device=DEV, generator=g)
+    ctx = Lfps(batch=1, max_seq_len=L, max_k=64, radius=1, table_mode=True, n_sink=4)
+    kv = ctx.kv_view(K, K, torch.full((1,), L, dtype=torch.int32, device=DEV))
+    part, whole = least_us(lambda: ctx.lfps_tables_init(q[:few], kv), lambda: ctx.lfps_tables_init(q, kv))
+    assert part <= 1.01 * whole, (part, whole)
+    ctx.close()
