@@ -312,8 +312,10 @@ struct ChunkRows {
              (int)threadIdx.x % kPieces;
     };
     if (once) {
+      asm volatile("; past the caches");                   // (or the compiler makes ordinary loads of both branches)
 #pragma unroll
       for (int i = 0; i < kLoads; ++i) raw[i] = __builtin_nontemporal_load(at(i));
+      asm volatile("; past the caches");
     } else {
 #pragma unroll
       for (int i = 0; i < kLoads; ++i) raw[i] = *at(i);
@@ -1122,17 +1124,18 @@ int64_t table_init_scratch_bytes(const Shape& s) {
   return (int64_t)s.B * s.Hkv * most * kHistBatch * s.G * (8 + 4) + (int64_t)s.B * s.Hq * parts * 12 * 8;
 }
 
-// Up to how many bytes of keys the first pass over K reads with ordinary loads.  With few queries it is bound by the bytes of K, and
-// keys that will not be found in the memory-side cache again are read past it (one query, 64 groups x 32K rows, 537 MB: 119 -> 96
-// us).  With one query the next reader is the next call, and the tables, written whole in between, take their part of the cache:
-// tables of 4 x capacity, K + tables 224 MB 54.2 us kept, 58.4 past the caches, 280 MB 74.0 and 72.8, 336 MB 91.2 and 79.1.  With
-// more queries k_batch_apply reads the keys again at once, while it writes the tables: 4 queries, keys + tables of 128 + 192 MB
-// 135.9 and 153.1, 192 + 36 MB 120.7 and 122.4, 224 + 168 MB 164.6 and 163.3, 256 + 192 MB 199.3 and 186.2 (the two passes before
-// these).  That second pass keeps ordinary loads: past the caches 257 us instead of 251 at 268 + 100 MB, 481 instead of 476 at 537 +
+// Up to how many bytes of keys the first pass over K reads with ordinary loads.  Keys that will not be found in the memory-side cache
+// again are read past it (one query, 64 groups x 32K rows, 537 MB: 119 -> 96 us).  With one query the next reader is the next call, and
+// the tables, written whole in between, take their part of the cache: tables of 4 x capacity, K + tables 224 MB 54.2 us kept, 58.4 past
+// the caches, 280 MB 74.0 and 72.8, 336 MB 91.2 and 79.1.  With more queries k_batch_apply reads the keys again at once, while it writes
+// the tables.  Kept and past the caches, 4 queries (16 and 32 much the same), MiB of keys + tables: bf16 256 + 48 101.6 and 125.6, 320 +
+// 60 143.5 and 139.3, 512 + 96 244.2 and 218.8; fp16, two heads per group, 320 + 30 132.9 and 135.2, 448 + 42 189.6 and 187.0; bf16, one
+// head, 384 + 18 152.0 and 155.0, 512 + 24 223.1 and 214.8; FP8 keys 224 + 84 146.9 and 146.1, 256 + 96 145.6 and 146.0, 320 + 120 195.8
+// and 183.7.  That second pass keeps ordinary loads: past the caches 257 us instead of 251 at 268 + 100 MB, 481 instead of 476 at 537 +
 // 200 MB, both passes.
 static float stats_kept_bytes(const Shape& s, int n_queries) {
   const float tables = 12.f * s.B * s.Hq * s.Lcap;
-  return n_queries == 1 ? (float)kKeptBytes - tables : 280.f * (1 << 20) - 0.5f * tables;
+  return n_queries == 1 ? (float)kKeptBytes - tables : 440.f * (1 << 20) - 2.4f * tables;
 }
 
 // The units of a batch of nq queries as the kernels are built for them.  (What the quads of a chunk move up, 4 rows for each before

@@ -72,9 +72,9 @@ def test_full_attention_with_room_to_grow(dtype, n, Hq):
         assert roomy <= 1.05 * tight, (tight, roomy)
 
 
-# eight queries are the most whose pass may read the keys past the caches: with keys that stay in the memory-side cache for the
-# second pass over them, in a context with room for four times as many, they cost no more than nine (0.975 times as much; 1.04 times
-# when they were read past the caches)
+# keys that stay in the memory-side cache for the second pass over them, in a context with room for four times as many: the first pass
+# reads them past the caches by what is held, not by the capacity, and eight queries cost no more than nine (0.975 times as much; 1.04
+# times when eight were the most that could be read past the caches, and were)
 def test_tables_from_eight_queries_cost_no_more_than_from_nine():
     from paper_2506_15704_amd.binding import Lfps
     g = torch.Generator(device=DEV)
