@@ -35,6 +35,7 @@ struct lfps_ctx {
   uint32_t* tab_f0;    // [B, Hq, flag_words]
   uint32_t* tab_fm;    // [B, Hq, flag_words]
   int flag_words;
+  HistPlan hist;       // of the table start from many queries
   int tab_updates;     // update calls since the last import / init (graph replays are not seen here: the kernel checks too)
   int tab_ready;
   int32_t* gate;       // [B, Hq] bypass marks of the current gated step
@@ -81,6 +82,7 @@ namespace {
 
 struct Sizes {
   int32_t G, cand_cap, score_stride, n_split_full, nseg, flag_words, range[2], bitmap_words;
+  HistPlan hist;
   int64_t score_b, cand_b, count_b, sel_b, part_b, slot_b, seg_b, thr_b, line_b, tver_b, tsla_b, tstate_b, tflag_b, x_b, aux_b, bitmap_b, total;
 };
 
@@ -175,7 +177,8 @@ int check_config(const lfps_config* c, Sizes* z, char* err, size_t errn) {
   z->tflag_b = c->table_mode ? align256(heads * z->flag_words * 4) : 0;
   z->x_b = 3 * z->count_b + 2 * align256((int64_t)c->batch * 4) + align256(((int64_t)c->batch * c->n_kv_heads + 1) * 8) + z->thr_b;
   z->aux_b = prior_scratch_bytes(s);
-  if (c->table_mode && table_init_scratch_bytes(s) > z->aux_b) z->aux_b = table_init_scratch_bytes(s);
+  z->hist = c->table_mode ? plan_table_history(s) : HistPlan{};
+  if (c->table_mode && table_init_scratch_bytes(s, z->hist) > z->aux_b) z->aux_b = table_init_scratch_bytes(s, z->hist);
   z->aux_b = align256(z->aux_b);
   z->total = z->score_b + z->cand_b + z->count_b + z->sel_b + z->part_b + z->slot_b + z->seg_b + z->thr_b +
              z->line_b + 256 + z->x_b + z->aux_b + z->bitmap_b + z->tver_b + z->tsla_b + z->tstate_b + 2 * z->tflag_b +
@@ -381,6 +384,7 @@ int lfps_create(const lfps_config* cfg, lfps_ctx** out) {
     c->tab_fm = (uint32_t*)p;
     p += z.tflag_b;
     c->flag_words = z.flag_words;
+    c->hist = z.hist;
   }
   c->gate = (int32_t*)p;
   p += z.thr_b;
@@ -743,7 +747,7 @@ int lfps_tables_init(lfps_ctx* ctx, const float* q_hist, int32_t n_queries, cons
   const bool together = ctx->cfg.kv_dtype != LFPS_F32;   // all queries in one pass over K (fp32 keys: one at a time)
   if (together) {
     LAUNCH(ctx, LFPS_KERNEL_DENSE_SCORE, st,
-           launch_table_history(s, ctx->tab_ver, ctx->tab_sla, q_hist, n_queries, (double)ctx->cfg.table_decay, v,
+           launch_table_history(s, ctx->hist, ctx->tab_ver, ctx->tab_sla, q_hist, n_queries, (double)ctx->cfg.table_decay, v,
                                 ctx->score, s.score_stride, ctx->aux, ctx->flags, &moment_parts, st));
   } else {
     for (int j = 1; j <= n_queries; ++j) {

@@ -254,9 +254,15 @@ hipError_t launch_table_init(const Shape& s, float* tab_ver, float* tab_sla, con
 // scratch: table_init_scratch_bytes.  *moment_parts: how many partials per head of the tables' moments it has left there (0:
 // none).
 constexpr int kHistBatch = 32;
-int64_t table_init_scratch_bytes(const Shape& s);
+// How many workgroups share a KV group: those kernels' first with two and more units of queries and with one, and their second.  Made
+// once per context (the search takes the host 2 us).
+struct HistPlan {
+  int parts[2], blocks;
+};
+HistPlan plan_table_history(const Shape& s);
+int64_t table_init_scratch_bytes(const Shape& s, const HistPlan& plan);
 hipError_t configure_table_history(const Shape& s, int k_kind);
-hipError_t launch_table_history(const Shape& s, float* tab_ver, float* tab_sla, const float* q_hist, int n_queries,
+hipError_t launch_table_history(const Shape& s, const HistPlan& plan, float* tab_ver, float* tab_sla, const float* q_hist, int n_queries,
                                 double gamma, const KvView& kv, float* dots, int64_t dots_stride, void* scratch,
                                 int32_t* flags, int* moment_parts, hipStream_t st);
 // Statistics and head state of freshly written tables.

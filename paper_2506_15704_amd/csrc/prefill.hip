@@ -1114,13 +1114,17 @@ static int batch_blocks(const Shape& s, int rows, int wait, bool pairs, int merg
 // Every workgroup of the second kernel reads all partials of its group before its first product: 32 queries of one group (four heads) x
 // 128K rows with 512 of them 85.3 us, 256 61.6, 192 59.3, 128 58.4 (two queries 39.4, 31.1, 32.1, 33.1), of 8 groups x 32K with 64 71.6,
 // 32 65.6, of 8 x 128K with 64 208, 32 219.
-static int stats_blocks(const Shape& s, int U) { return batch_blocks(s, stats_rows(U), 4, true, 62); }
-static int apply_blocks(const Shape& s) { return batch_blocks(s, kApplyRows, 2, false, 0); }
+HistPlan plan_table_history(const Shape& s) {
+  HistPlan plan;
+  for (int one = 0; one < 2; ++one) plan.parts[one] = batch_blocks(s, stats_rows(one ? 1 : 2), 4, true, 62);
+  plan.blocks = batch_blocks(s, kApplyRows, 2, false, 0);
+  return plan;
+}
 
-int64_t table_init_scratch_bytes(const Shape& s) {
+int64_t table_init_scratch_bytes(const Shape& s, const HistPlan& plan) {
   int most = hist_blocks(s);
-  for (int U = 1; U <= 2; ++U) most = stats_blocks(s, U) > most ? stats_blocks(s, U) : most;
-  const int parts = moment_chunks(s) > apply_blocks(s) ? moment_chunks(s) : apply_blocks(s);
+  for (int p : plan.parts) most = p > most ? p : most;
+  const int parts = moment_chunks(s) > plan.blocks ? moment_chunks(s) : plan.blocks;
   return (int64_t)s.B * s.Hkv * most * kHistBatch * s.G * (8 + 4) + (int64_t)s.B * s.Hq * parts * 12 * 8;
 }
 
@@ -1179,10 +1183,10 @@ struct HistScratch {
 };
 
 template <int G, bool kPaged, int kKind, int U>
-static hipError_t launch_batch_t(const Shape& s, float* tab_ver, float* tab_sla, const float* q0, int64_t q_stride, int j0,
+static hipError_t launch_batch_t(const Shape& s, const HistPlan& plan, float* tab_ver, float* tab_sla, const float* q0, int64_t q_stride, int j0,
                                  int nq, int n_queries, double gamma, const KvView& kv, void* scratch, int32_t* flags,
                                  hipStream_t st) {
-  const int parts = stats_blocks(s, U), blocks = apply_blocks(s);
+  const int parts = plan.parts[U == 1], blocks = plan.blocks;
   const HistScratch to(s, scratch, parts, blocks);
   const dim3 block(kBatchThreads);
   const float kept = stats_kept_bytes(s, n_queries);
@@ -1196,11 +1200,11 @@ static hipError_t launch_batch_t(const Shape& s, float* tab_ver, float* tab_sla,
   return hipGetLastError();
 }
 
-static hipError_t launch_batch(const Shape& s, float* tab_ver, float* tab_sla, const float* q0, int64_t q_stride, int j0,
+static hipError_t launch_batch(const Shape& s, const HistPlan& plan, float* tab_ver, float* tab_sla, const float* q0, int64_t q_stride, int j0,
                                int nq, int n_queries, double gamma, const KvView& kv, void* scratch, int32_t* flags,
                                hipStream_t st) {
   const int units = batch_units(s.G, nq), kind = kv.k_fp8 ? kKindFp8 : (kv.f16 ? kKindF16 : kKindBf16);
-#define LFPS_HIST_ARGS s, tab_ver, tab_sla, q0, q_stride, j0, nq, n_queries, gamma, kv, scratch, flags, st
+#define LFPS_HIST_ARGS s, plan, tab_ver, tab_sla, q0, q_stride, j0, nq, n_queries, gamma, kv, scratch, flags, st
 #define LFPS_LAUNCH_BATCH(GG, UU, KIND)                                                      \
   if (s.G == GG && units == UU && kind == KIND)                                              \
     return kv.page.table ? launch_batch_t<GG, true, KIND, UU>(LFPS_HIST_ARGS)                \
@@ -1252,7 +1256,7 @@ static hipError_t launch_one(const Shape& s, float* tab_ver, float* tab_sla, con
 #undef LFPS_HIST_ARGS
 }
 
-hipError_t launch_table_history(const Shape& s, float* tab_ver, float* tab_sla, const float* q_hist, int n_queries,
+hipError_t launch_table_history(const Shape& s, const HistPlan& plan, float* tab_ver, float* tab_sla, const float* q_hist, int n_queries,
                                 double gamma, const KvView& kv, float* dots, int64_t dots_stride, void* scratch,
                                 int32_t* flags, int* moment_parts, hipStream_t st) {
   if (n_queries == 1) {
@@ -1262,11 +1266,11 @@ hipError_t launch_table_history(const Shape& s, float* tab_ver, float* tab_sla, 
   const int64_t q_stride = (int64_t)s.B * s.Hq * kD;
   for (int j0 = 1; j0 <= n_queries; j0 += kHistBatch) {
     const int nq = n_queries - j0 + 1 < kHistBatch ? n_queries - j0 + 1 : kHistBatch;
-    const hipError_t e = launch_batch(s, tab_ver, tab_sla, q_hist + (int64_t)(j0 - 1) * q_stride, q_stride, j0, nq, n_queries,
+    const hipError_t e = launch_batch(s, plan, tab_ver, tab_sla, q_hist + (int64_t)(j0 - 1) * q_stride, q_stride, j0, nq, n_queries,
                                       gamma, kv, scratch, flags, st);
     if (e != hipSuccess) return e;
   }
-  *moment_parts = n_queries <= kHistBatch ? apply_blocks(s) : 0;
+  *moment_parts = n_queries <= kHistBatch ? plan.blocks : 0;
   return hipSuccess;
 }
 
