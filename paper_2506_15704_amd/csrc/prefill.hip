@@ -25,16 +25,17 @@
 
 namespace lfps {
 
-constexpr int kHistWaves = 8;          // one workgroup per CU: the query operands fill its LDS, the rows its registers
-constexpr int kHistSub = 8;            // 16-row sub-tiles a wave holds: 128 rows
+constexpr int kHistWaves = 8;          // of a workgroup
+constexpr int kHistSub = 8;            // 16-row sub-tiles a wave of k_hist_stats holds: 128 rows, which fill its registers
 constexpr int kHistRows = 16 * kHistSub;
 constexpr float kNoScore = -FLT_MAX;   // stands for "row not seen"
 constexpr float kLeastMax = -1.7e38f;  // the largest score is taken as at least this: a row not seen weighs 0 beside any
 
-// NT sub-tiles of K rows as MFMA operands: lane (j, kb) holds its channels of the rows base + 16 t + j.  Rows past the
+// kHistSub sub-tiles of K rows as MFMA operands: lane (j, kb) holds its channels of the rows base + 16 t + j.  Rows past the
 // sequence read its last row.
-template <bool kPaged, int kKind, int NT>
+template <bool kPaged, int kKind>
 struct HistTile {
+  static constexpr int NT = kHistSub;
   using Op = typename KSub<kKind>::Operand;
   Op x[NT][4];
   __device__ __forceinline__ void load(const char* Kbg, const KvPage& pg, int b, int64_t stride_b, int64_t stride_n,
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
     Shape s, const float* __restrict__ q, const void* __restrict__ K, int64_t stride_b, int64_t stride_h, int64_t stride_n,
     KvPage pg, const int32_t* __restrict__ seq_lens, float* __restrict__ part_m, double* __restrict__ part_l,
     float* __restrict__ dots, int64_t dots_stride, int32_t* __restrict__ flags, float kept_bytes) {
-  using Tile = HistTile<kPaged, kKind, kHistSub>;
+  using Tile = HistTile<kPaged, kKind>;
   using Op = typename Tile::Op;
   __shared__ u32x4 turn[kMayOnce ? kHistWaves : 1][StreamTile<kKind>::kLdsChunks];
   __shared__ float wm[kHistWaves][4];
@@ -883,7 +884,8 @@ static_assert(TS_MS == TS_MV + 4, "k_table_state writes both sets of moments in 
 // ----------------------------------------------------------------------------- prefill priors
 // K mean, V mean and the variance of the scaled scores of the given query over the offloaded rows, from one pass over
 // K and V (three passes before, the means by one workgroup per KV group: 8 of 256 CUs at B = 1).  Bound by the bytes of
-// K and V: 27 + 4 us at 8 groups x 32K bf16 rows (134 MB), 600 us before.  grid (splits, B*Hkv), 256 threads; 16 lanes per row, 8 channels each, two 16-row tiles per wave in flight.
+// K and V: 28 + 5 us at 8 groups x 32K bf16 rows (134 MB), 600 us before.  grid (splits, B*Hkv), 256 threads; 16 lanes per row, 8
+// channels each, two 16-row tiles per wave in flight.
 // Per (bg, split) a partial: 128 sums of K, 128 of V, then (rows, mean, sum of squared deviations) of every head's
 // scores; the means and deviations of parts are merged exactly (no difference of large sums).
 constexpr int kPriorThreads = 256;

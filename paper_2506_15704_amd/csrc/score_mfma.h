@@ -47,20 +47,6 @@ struct Split3<bf16x8> {
     }
     return out;
   }
-  // all three terms, for callers whose lanes make them all
-  __device__ static __forceinline__ void all(const float (&f)[8], bf16x8 (&e)[3]) {
-#pragma unroll
-    for (int c = 0; c < 8; c += 2) {
-      f32x2 x = {f[c], f[c + 1]};
-#pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        const bf16x2 b = __builtin_convertvector(x, bf16x2);
-        e[t][c] = b[0];
-        e[t][c + 1] = b[1];
-        x -= __builtin_convertvector(b, f32x2);
-      }
-    }
-  }
   __device__ static __forceinline__ float sum(const f32x4& acc) { return (acc[0] + acc[1]) + acc[2]; }
 };
 template <>
@@ -79,18 +65,6 @@ struct Split3<f16x8> {
       out[c] = t < 3 ? h : (_Float16)0.0f;
     }
     return out;
-  }
-  __device__ static __forceinline__ void all(const float (&f)[8], f16x8 (&e)[3]) {
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-      const _Float16 t0 = (_Float16)f[c];
-      const float r1 = f[c] - (float)t0;
-      const _Float16 t1 = (_Float16)(r1 * 2048.0f);
-      const float r2 = r1 - (float)t1 * (1.0f / 2048.0f);
-      e[0][c] = t0;
-      e[1][c] = t1;
-      e[2][c] = (_Float16)(r2 * 4194304.0f);
-    }
   }
   __device__ static __forceinline__ float sum(const f32x4& acc) {
     return (acc[0] + acc[1] * (1.0f / 2048.0f)) + acc[2] * (1.0f / 4194304.0f);
