@@ -338,3 +338,36 @@ def test_fp32_steps_equal_the_separate_entry_points(B, Hq, Hkv, L, k, r, n_sink,
             assert torch.equal(x, y), (name, t)
         prev = idx.flip(2).contiguous() if t == 1 else idx
     ctx.close()
+
+
+# ... and every entry of the list and every score of that kernel, by a budget that takes all candidates: in parts, one part of a group
+# and of 512 and more groups, paged rows of four heads, a bitmap of exactly a word per thread
+@pytest.mark.parametrize("B,Hq,Hkv,L,k,filled,page", [
+    (2, 8, 2, 5000, 400, 20, 0), (1, 4, 1, 8189, 1000, 60, 16), (65, 32, 8, 300, 200, 12, 0), (129, 16, 4, 260, 200, 12, 64), (1, 2, 2, 33, 33, 5, 0)])
+def test_fp32_steps_score_every_candidate_of_the_list(B, Hq, Hkv, L, k, filled, page):
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(L + filled)
+    Lcap, G = L + 3, Hq // Hkv
+    K, V = (torch.randn((B, Hkv, Lcap, 128), device="cuda:0", generator=g) for _ in range(2))
+    ctx = Lfps(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="f32", max_seq_len=Lcap, max_k=k, radius=1)
+    seq = torch.tensor([max(1, Lcap - 3 * (b % 50)) for b in range(B)], dtype=torch.int32, device="cuda:0")
+    view = ctx.kv_view(K, V, seq) if not page else ctx.paged_kv_view(*gen_device.paginate(K, V, page, seed=5), seq)
+    ks = torch.minimum(seq, torch.full_like(seq, k))
+    prev = torch.full((B, Hq, k), -1, dtype=torch.int32, device="cuda:0")
+    prev[:, :, :filled] = torch.randint(0, L, (B, Hq, filled), dtype=torch.int32, device="cuda:0", generator=g)
+    q = torch.randn((B, Hq, 128), device="cuda:0", generator=g)
+    idx, idx2 = (torch.full((B, Hq, k), -5, dtype=torch.int32, device="cuda:0") for _ in range(2))
+    sc, sc2 = (torch.full((B, Hq, k), -5.0, device="cuda:0") for _ in range(2))
+    ctx.lfps_step(q, view, prev, ks, idx, torch.zeros((B, Hq, 128), device="cuda:0"), sc)
+    cand = torch.zeros((B, Hkv, ctx.cand_cap), dtype=torch.int32, device="cuda:0")
+    cnt = torch.zeros((B, Hkv), dtype=torch.int32, device="cuda:0")
+    ctx.lfps_candidates(prev, ks, seq, cand, cnt)
+    ctx.lfps_score_topk(q, view, cand, cnt, ks, idx2, sc2)
+    assert torch.equal(sc, sc2)
+    for b in range(B):
+        for h in range(Hq):
+            n = int(cnt[b, h // G])
+            assert n <= int(ks[b]), "the budget takes all candidates"
+            assert torch.equal(idx[b, h, :n], cand[b, h // G, :n]) and bool((idx[b, h, n:] == -1).all())
+    ctx.close()
