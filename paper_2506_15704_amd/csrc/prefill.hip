@@ -12,9 +12,9 @@
 // cost 4 bytes per row, query and head (8.6 times the bytes of a second pass over bf16 keys at s = 32, G = 4).
 // With many queries both are bound by the matrix and vector units: per 16 rows and 16 (query, head) pairs 12 products of 16
 // cycles, of which a SIMD can issue two vector instructions each for nothing, and about 22 vector instructions in the first
-// kernel, 45 in the second.  32 queries of 8 groups x 32K rows: 30 + 45 us (11 + 11 by the products alone), of 64 groups x 64K
-// rows 341 + 489; before, one wave holding 128 rows and walking the queries, 49 + 59 and 1140 together.  With few queries they
-// are bound by the bytes of K: 4 queries of 64 groups x 64K rows 200 + 265 us for 1.07 GB each and 0.2 GB of tables.
+// kernel, 45 in the second.  32 queries of 8 groups x 32K rows: 31 + 41 us (11 + 11 by the products alone), of 64 groups x 64K
+// rows 331 + 453; before, one wave holding 128 rows and walking the queries, 49 + 59 and 1140 together.  With few queries they
+// are bound by the bytes of K: 4 queries of 64 groups x 64K rows 157 + 265 us for 1.07 GB each and 0.2 GB of tables.
 // A single query takes k_hist_stats and k_hist_apply_one instead: its scores are few enough to store.
 #include "lfps_internal.h"
 #include "score_mfma.h"
