@@ -254,10 +254,11 @@ hipError_t launch_table_init(const Shape& s, float* tab_ver, float* tab_sla, con
 // scratch: table_init_scratch_bytes.  *moment_parts: how many partials per head of the tables' moments it has left there (0:
 // none).
 constexpr int kHistBatch = 32;
-// How many workgroups share a KV group: those kernels' first with two and more units of queries and with one, and their second.  Made
-// once per context (the search takes the host 2 us).
+// How many workgroups share a KV group: in those kernels' first, by the form of its chunks, and in their second.  Made once per
+// context (the search takes the host 2 us).
+enum { kPartsShort = 0, kPartsFp8 = 1, kPartsOneUnit = 2 };
 struct HistPlan {
-  int parts[2], blocks;
+  int parts[3], blocks;
 };
 HistPlan plan_table_history(const Shape& s);
 int64_t table_init_scratch_bytes(const Shape& s, const HistPlan& plan);

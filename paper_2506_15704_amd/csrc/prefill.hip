@@ -279,7 +279,13 @@ struct BatchShape {
   static constexpr int kSubs = kSpanRows / 16;             // sub-tiles of 16 rows a wave takes of a chunk
 };
 constexpr int kApplyRows = 128;
-constexpr int stats_rows(int U) { return U == 1 ? 128 : 64; }   // (a wave's span of a chunk is sixteen rows at least)
+// Rows of a chunk in the first kernel: 128 where a wave's span would be less than sixteen (one unit), and of FP8 keys where the
+// registers of a wave allow it, 64 being few bytes on their way: 2 queries of one group (four heads) x 128K rows 32.9 -> 30.9 us, of
+// 8 groups x 32K 34.6 -> 32.6, of 128 x 32K 274 -> 260, 16 of 64 x 16000 with two heads each 92.1 -> 86.1.
+constexpr int stats_form(int U, int kind) {
+  return U <= 2 && kind == kKindFp8 ? kPartsFp8 : (U == 1 ? kPartsOneUnit : kPartsShort);
+}
+constexpr int stats_rows(int form) { return form == kPartsShort ? 64 : 128; }
 
 // The rows of a workgroup's chunks: from memory to registers, from there to LDS, by the first kThreads of its threads.
 template <bool kPaged, int kKind, typename B, int kThreads>
@@ -494,7 +500,7 @@ __global__ __launch_bounds__(kBatchThreads, 4) void k_batch_stats(
     Shape s, const float* __restrict__ q0, int64_t q_stride, int j0, int nq, const void* __restrict__ K,
     int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage pg, const int32_t* __restrict__ seq_lens,
     float* __restrict__ part_m, double* __restrict__ part_l, int32_t* __restrict__ flags, float kept_bytes) {
-  using B = BatchShape<U, stats_rows(U)>;
+  using B = BatchShape<U, stats_rows(stats_form(U, kKind))>;
   using Op = typename KSub<kKind>::Operand;
   __shared__ u32x4 chunk[2][B::kPieces];
   __shared__ float wm[kHistWaves][16];
@@ -1097,14 +1103,14 @@ static int moment_chunks(const Shape& s) { return (s.Lcap + kMomentRows - 1) / k
 
 // The same in the kernels of many queries, in chunks of `rows`: as many workgroups as make the least of the chunks one after the
 // other, a workgroup beginning with about `wait` chunks' worth of waiting for its first rows and queries.  A CU takes one workgroup at a
-// time, or with `pairs` two, which together take 1.75 times as long.  merge: twentieths of a chunk that 32 workgroups of a group
-// cost whoever reads their results (merge_hist: eight loads of each of four lanes at a time).
-static int batch_blocks(const Shape& s, int rows, int wait, bool pairs, int merge) {
-  const int64_t groups = (int64_t)s.B * s.Hkv, tiles = (s.Lcap + rows - 1) / rows, slots = pairs ? 512 : 256;
+// time (pair 0), or two, which together take pair / 20 times as long.  merge: twentieths of a chunk that 32 workgroups of a group cost
+// whoever reads their results (merge_hist: eight loads of each of four lanes at a time).
+static int batch_blocks(const Shape& s, int rows, int wait, int pair, int merge) {
+  const int64_t groups = (int64_t)s.B * s.Hkv, tiles = (s.Lcap + rows - 1) / rows, slots = pair ? 512 : 256;
   int64_t best = 1, least = INT64_MAX;
   for (int64_t n = 1; n <= tiles && n <= slots; ++n) {
     const int64_t all = groups * n, rest = all % slots;
-    const int64_t rounds = all / slots * (pairs ? 35 : 20) + (rest > 256 ? 35 : (rest > 0 ? 20 : 0));     // in twentieths
+    const int64_t rounds = all / slots * (pair ? pair : 20) + (rest > 256 ? pair : (rest > 0 ? 20 : 0));  // in twentieths
     const int64_t cost = rounds * ((tiles + n - 1) / n + wait) + (n + 31) / 32 * merge;
     if (cost < least) {
       least = cost;
@@ -1118,8 +1124,10 @@ static int batch_blocks(const Shape& s, int rows, int wait, bool pairs, int merg
 // 32 65.6, of 8 x 128K with 64 208, 32 219.
 HistPlan plan_table_history(const Shape& s) {
   HistPlan plan;
-  for (int one = 0; one < 2; ++one) plan.parts[one] = batch_blocks(s, stats_rows(one ? 1 : 2), 4, true, 62);
-  plan.blocks = batch_blocks(s, kApplyRows, 2, false, 0);
+  plan.parts[kPartsShort] = batch_blocks(s, 64, 4, 35, 62);
+  plan.parts[kPartsOneUnit] = batch_blocks(s, 128, 4, 35, 62);
+  plan.parts[kPartsFp8] = batch_blocks(s, 128, 2, 35, 31);             // (the same waits in chunks of twice the rows)
+  plan.blocks = batch_blocks(s, kApplyRows, 2, 0, 0);
   return plan;
 }
 
@@ -1188,7 +1196,7 @@ template <int G, bool kPaged, int kKind, int U>
 static hipError_t launch_batch_t(const Shape& s, const HistPlan& plan, float* tab_ver, float* tab_sla, const float* q0, int64_t q_stride, int j0,
                                  int nq, int n_queries, double gamma, const KvView& kv, void* scratch, int32_t* flags,
                                  hipStream_t st) {
-  const int parts = plan.parts[U == 1], blocks = plan.blocks;
+  const int parts = plan.parts[stats_form(U, kKind)], blocks = plan.blocks;
   const HistScratch to(s, scratch, parts, blocks);
   const dim3 block(kBatchThreads);
   const float kept = stats_kept_bytes(s, n_queries);
