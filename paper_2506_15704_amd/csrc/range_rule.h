@@ -31,9 +31,9 @@ inline int range_rows_for(int64_t groups, int rows, int heads_per_group, bool ta
   if (most > 0 && ranges(range) > 1024 && range < kRangeMax) {
     int64_t parts = most;
     // 513 to 1023 groups get one range each, and half the chip or more its share of the rows.  With four heads per group and more than
-    // 4096 rows two or three ranges are faster, ranges of 2048 -> one -> these: 520 x 8009 1333 -> 1341 -> 1322, 704 x 5909 1411 -> 1449 ->
-    // 1412, 560 x 7309 1322 -> 1333 -> 1311, 600 x 5009 1166 -> 1172 -> 1162; up to 4096 rows, and with fewer heads, one is (800 x 3659
-    // 1245 -> 1232, two 1249; one head per group 600 x 6909 723 -> 701, three 709).
+    // 4096 rows two or three ranges are faster (from 8065 rows on four, of 2048), ranges of 2048 -> one -> these: 520 x 8009 1333 ->
+    // 1341 -> 1322, 704 x 5909 1411 -> 1449 -> 1412, 560 x 7309 1322 -> 1333 -> 1311, 600 x 5009 1166 -> 1172 -> 1162; up to 4096 rows,
+    // and with fewer heads, one is (800 x 3659 1245 -> 1232, two 1249; one head per group 600 x 6909 723 -> 701, three 709).
     if (parts == 1 && heads_per_group == 4 && rows > 4096) parts = (rows + 2687) / 2688;
     range = (int)(((rows + parts - 1) / parts + 63) & ~63);
   }
