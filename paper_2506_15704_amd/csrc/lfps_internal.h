@@ -53,10 +53,19 @@ struct RowMap {
     if constexpr (!kPaged) {
       return i;
     } else {
-      int blk = pg.table[(int64_t)b * pg.table_stride + (i >> pg.shift)];
-      blk = blk < 0 ? 0 : (blk >= pg.n_blocks ? pg.n_blocks - 1 : blk);   // a bad entry reads a wrong block, never outside the pool
-      return (blk << pg.shift) | (i & ((1 << pg.shift) - 1));
+      return (kept_in_pool(pg, block(pg, b, i)) << pg.shift) | (i & ((1 << pg.shift) - 1));
     }
+  }
+  // A row's entry of the block table as it is there, and the offset that follows from it, for who asks for the entry long before it is
+  // used (with phys the wait for the load comes right behind it).
+  __device__ __forceinline__ static int block(const KvPage& pg, int b, int i) {
+    return kPaged ? pg.table[(int64_t)b * pg.table_stride + (i >> pg.shift)] : 0;
+  }
+  __device__ __forceinline__ static int64_t offset_in(const KvPage& pg, int blk, int i, int64_t stride_b, int64_t stride_n) {
+    return kPaged ? kept_in_pool(pg, blk) * stride_b + (i & ((1 << pg.shift) - 1)) * stride_n : i * stride_n;
+  }
+  __device__ __forceinline__ static int kept_in_pool(const KvPage& pg, int blk) {       // a bad entry reads a wrong block, never outside
+    return blk < 0 ? 0 : (blk >= pg.n_blocks ? pg.n_blocks - 1 : blk);
   }
   // element offset of the start of (b, g)'s rows, to which offset(p) is added
   __device__ __forceinline__ static int64_t base(int b, int g, int64_t stride_b, int64_t stride_h) {
