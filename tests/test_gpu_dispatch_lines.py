@@ -240,3 +240,25 @@ def test_tables_from_few_queries_over_pages_cost_little_more(fp8, most):
     assert pages <= most * rows, (pages, rows)
     for ctx in ctxs:
         ctx.close()
+
+
+# one query over fp16 keys: its split, the longest of the formats, stands behind the requests for the first rows, and tables from it cost
+# no more than over bf16 keys (0.97 times as much; 1.03 with the split before the requests)
+def test_tables_from_one_query_cost_no_more_over_fp16_keys():
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(7)
+    L, page = 32768, 64
+    K = torch.randn((L // page, 8, page, 128), device=DEV, generator=g)
+    q, seq = torch.randn((1, 1, 32, 128), device=DEV, generator=g), torch.full((1,), L, dtype=torch.int32, device=DEV)
+    table = torch.randperm(L // page, device=DEV, generator=g).view(1, -1).to(torch.int32)
+    ctxs, calls = [], []
+    for name, dtype in (("f16", torch.float16), ("bf16", torch.bfloat16)):
+        ctx = Lfps(batch=1, kv_dtype=name, max_seq_len=L, max_k=64, radius=1, table_mode=True, n_sink=4)
+        kv = ctx.paged_kv_view(K.to(dtype), K.to(dtype), table, seq)
+        ctxs.append(ctx)
+        calls.append(lambda ctx=ctx, kv=kv: ctx.lfps_tables_init(q, kv))
+    half, brain = least_us(*calls, each=50)
+    assert half <= 1.01 * brain, (half, brain)
+    for ctx in ctxs:
+        ctx.close()
