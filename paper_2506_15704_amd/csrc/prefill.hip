@@ -113,8 +113,7 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
   const float held = kMayOnce ? held_rows(s, seq_lens) : 0.f;
   const int64_t head0 = (int64_t)b * s.Hq + (int64_t)g * G;
   // fp16: the query is split behind the requests for the first rows, beside their latency, as the compiler does by itself where there is
-  // no range to report (8 groups x 32K
-  // rows 24.9 -> 23.8 us, x 128K 75.4 -> 72.9; of FP8 keys it takes 2.5 % longer).
+  // no range to report (8 groups x 32K rows 24.9 -> 23.8 us, x 128K 75.4 -> 72.9; of FP8 keys it takes 2.5 % longer).
   constexpr bool kSplitLate = Split3<Op>::kHalf;
   Op A[4] = {};
   QueryRows query;
@@ -1163,16 +1162,21 @@ static float stats_kept_bytes(const Shape& s, int n_queries) {
 }
 
 // The units of a batch of nq queries as the kernels are built for them.  (What the quads of a chunk move up, 4 rows for each before
-// the last and 15 for the rows, has to end in the next one.)
-static int batch_units(int G, int nq) {
+// the last and 15 for the rows, has to end in the next one.)  One unit of grouped heads: over FP8 keys, where a wave's products then
+// take half as long beside the conversion of the rows, 2 queries with one unit instead of two (one of them without a query): 64 groups
+// (two heads each) x 16000 rows 79.6 -> 67.5 us, 8 x 32K 32.8 -> 28.7, four heads each 74.6 -> 68.3 and 32.6 -> 30.2.  (128 x
+// 32K, past the caches, 265 -> 280.)  Over 16-bit keys the longer chunks that one unit needs in the first kernel cost more: 8 x 32K bf16
+// 36.4 -> 39.0, 64 x 16000 96.7 -> 102.7.
+static int batch_units(int G, int nq, int kind) {
   const int units = ((nq + 3) / 4 * G + 3) / 4;
-  return units == 1 && G > 1 ? 2 : (units == 3 ? 4 : (units > 4 ? 8 : units));
+  return units == 1 && G > 1 && kind != kKindFp8 ? 2 : (units == 3 ? 4 : (units > 4 ? 8 : units));
 }
 
 // X(heads per group, units, key format)
 #define LFPS_BATCH_FOR_EACH_U(X, KIND) X(4, 2, KIND) X(4, 4, KIND) X(4, 8, KIND) X(2, 2, KIND) X(2, 4, KIND) X(1, 1, KIND) X(1, 2, KIND)
-#define LFPS_BATCH_FOR_EACH(X) \
-  LFPS_BATCH_FOR_EACH_U(X, kKindBf16) LFPS_BATCH_FOR_EACH_U(X, kKindFp8) LFPS_BATCH_FOR_EACH_U(X, kKindF16)
+#define LFPS_BATCH_FOR_EACH(X)                                                                                            \
+  LFPS_BATCH_FOR_EACH_U(X, kKindBf16) LFPS_BATCH_FOR_EACH_U(X, kKindFp8) LFPS_BATCH_FOR_EACH_U(X, kKindF16)               \
+  X(4, 1, kKindFp8) X(2, 1, kKindFp8)
 
 // Called once per context in table mode: the second kernel needs more dynamic LDS than the default limit.
 hipError_t configure_table_history(const Shape& s, int k_kind) {
@@ -1223,7 +1227,7 @@ static hipError_t launch_batch_t(const Shape& s, const HistPlan& plan, float* ta
 static hipError_t launch_batch(const Shape& s, const HistPlan& plan, float* tab_ver, float* tab_sla, const float* q0, int64_t q_stride, int j0,
                                int nq, int n_queries, double gamma, const KvView& kv, void* scratch, int32_t* flags,
                                hipStream_t st) {
-  const int units = batch_units(s.G, nq), kind = kv.k_fp8 ? kKindFp8 : (kv.f16 ? kKindF16 : kKindBf16);
+  const int kind = kv.k_fp8 ? kKindFp8 : (kv.f16 ? kKindF16 : kKindBf16), units = batch_units(s.G, nq, kind);
 #define LFPS_HIST_ARGS s, plan, tab_ver, tab_sla, q0, q_stride, j0, nq, n_queries, gamma, kv, scratch, flags, st
 #define LFPS_LAUNCH_BATCH(GG, UU, KIND)                                                      \
   if (s.G == GG && units == UU && kind == KIND)                                              \

@@ -85,6 +85,14 @@ def test_tables_of_ungrouped_heads(L, s, fmt, page):
     test_tables_from_many_queries(L, s, (2, 2), fmt, page)
 
 
+# one unit of grouped heads over FP8 keys (four queries of four heads, eight of two), and a last batch of one behind a full one
+@pytest.mark.parametrize("L,s,heads,page", [
+    (17, 4, (8, 2), 0), (127, 3, (8, 2), 16), (1041, 8, (4, 2), 0), (129, 5, (4, 2), 64), (2111, 4, (8, 2), 0), (640, 2, (8, 2), 16),
+    (1025, 36, (8, 2), 0), (300, 40, (4, 2), 16)])
+def test_tables_of_one_unit_over_fp8_keys(L, s, heads, page):
+    test_tables_from_many_queries(L, s, heads, "fp8", page)
+
+
 @pytest.mark.parametrize("L,heads,fmt,page,n_sink", [
     (255, (8, 2), "bf16", 0, 4), (257, (4, 2), "fp8kv", 16, 0), (1030, (2, 2), "fp8", 0, 4), (777, (8, 2), "f16", 64, 4),
     (513, (8, 2), "f32", 0, 1), (17, (8, 2), "bf16", 0, 4), (3, (8, 2), "bf16", 0, 4)])
