@@ -187,13 +187,59 @@ template <int kPer, typename Weight>
 __device__ __forceinline__ void merge_hist(const float* part_m, const double* part_l, int64_t o, int64_t step, int blocks,
                                            int sub, double gamma, int n_queries, float& m, double& norm, Weight weight) {
   m = kLeastMax;
-#pragma unroll 8
-  for (int k = sub; k < blocks; k += kPer) m = fmaxf(m, part_m[o + k * step]);
-#pragma unroll
-  for (int d = 1; d < kPer; d <<= 1) m = fmaxf(m, __shfl_xor(m, d));
   double l = 0.0;
+  if constexpr (kPer > 4) {
 #pragma unroll 8
-  for (int k = sub; k < blocks; k += kPer) l += part_l[o + k * step] * (double)weight(part_m[o + k * step] - m);
+    for (int k = sub; k < blocks; k += kPer) m = fmaxf(m, part_m[o + k * step]);
+#pragma unroll
+    for (int d = 1; d < kPer; d <<= 1) m = fmaxf(m, __shfl_xor(m, d));
+#pragma unroll 8
+    for (int k = sub; k < blocks; k += kPer) l += part_l[o + k * step] * (double)weight(part_m[o + k * step] - m);
+  } else {
+    // Eight loads of a lane at a time, also of the last ones (one by one, up to seven of them in turn: 8 queries of 8 groups x 3600 FP8
+    // rows 20.6 us instead of 16.9).  The conditions on first are the same for all lanes; past the end a lane reads partial 0 and counts
+    // nothing.
+    constexpr int kAtOnce = 8;
+    auto batches = [&](auto batch) {
+      int first = 0;
+      for (; first + kAtOnce * kPer <= blocks; first += kAtOnce * kPer) batch(std::true_type{}, first);
+      if (first < blocks) batch(std::false_type{}, first);
+    };
+    batches([&](auto whole, int first) __attribute__((always_inline)) {
+      constexpr bool kWhole = decltype(whole)::value;
+      float x[kAtOnce];
+#pragma unroll
+      for (int u = 0; u < kAtOnce; ++u) {
+        const int k = first + u * kPer + sub;
+        x[u] = kLeastMax;
+        if (kWhole || first + u * kPer < blocks) x[u] = part_m[o + (kWhole || k < blocks ? k : 0) * step];
+      }
+#pragma unroll
+      for (int u = 0; u < kAtOnce; ++u) m = fmaxf(m, x[u]);
+    });
+#pragma unroll
+    for (int d = 1; d < kPer; d <<= 1) m = fmaxf(m, __shfl_xor(m, d));
+    batches([&](auto whole, int first) __attribute__((always_inline)) {
+      constexpr bool kWhole = decltype(whole)::value;
+      float x[kAtOnce];
+      double part[kAtOnce];
+#pragma unroll
+      for (int u = 0; u < kAtOnce; ++u) {
+        const int k = first + u * kPer + sub;
+        x[u] = kLeastMax;
+        part[u] = 0.0;
+        if (kWhole || first + u * kPer < blocks) {
+          const int64_t at = o + (kWhole || k < blocks ? k : 0) * step;
+          x[u] = part_m[at];
+          part[u] = part_l[at];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kAtOnce; ++u)
+        if (kWhole || first + u * kPer < blocks)
+          l += kWhole || first + u * kPer + sub < blocks ? part[u] * (double)weight(x[u] - m) : 0.0;
+    });
+  }
 #pragma unroll
   for (int d = 1; d < kPer; d <<= 1) l += __shfl_xor(l, d);
   norm = l > 0.0 ? 1.0 / (2.0 * (double)n_queries * (1.0 - gamma) * l) : 0.0;
