@@ -286,3 +286,23 @@ def test_tables_from_one_unit_cost_much_less_over_fp8_keys(s):
     assert one <= 0.78 * two, (one, two)
     for ctx in ctxs:
         ctx.close()
+
+
+# the last partials of a (query, head) are merged together: a context of 3600 rows, whose partials are few and no multiple of 32, costs
+# much less than one of 12000, whose partials are 32 (0.83 times as much; 1.02 when the last ones came one by one)
+def test_tables_of_a_short_context_cost_much_less():
+    from paper_2506_15704_amd.binding import Lfps
+    g = torch.Generator(device=DEV)
+    g.manual_seed(9)
+    K = torch.randn((1, 8, 12000, 128), device=DEV, generator=g).to(torch.float8_e4m3fn)
+    V, q = torch.zeros((1, 8, 12000, 128), dtype=torch.bfloat16, device=DEV), torch.randn((8, 1, 8, 128), device=DEV, generator=g)
+    ctxs, calls = [], []
+    for L in (3600, 12000):
+        ctx = Lfps(batch=1, n_q_heads=8, n_kv_heads=8, max_seq_len=L, max_k=64, radius=1, table_mode=True, n_sink=4, k_fp8=True)
+        kv = ctx.kv_view(K[:, :, :L], V[:, :, :L], torch.full((1,), L, dtype=torch.int32, device=DEV))
+        ctxs.append(ctx)
+        calls.append(lambda ctx=ctx, kv=kv: ctx.lfps_tables_init(q, kv))
+    short, long = least_us(*calls, each=50)
+    assert short <= 0.93 * long, (short, long)
+    for ctx in ctxs:
+        ctx.close()
