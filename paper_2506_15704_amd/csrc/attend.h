@@ -2,16 +2,21 @@
 #pragma once
 #include "lfps_internal.h"
 
+#include <type_traits>
+
 namespace lfps {
 
 // Workgroups are dealt to the 8 XCDs round-robin (workgroup i runs on XCD i % 8) and every XCD has
 // its own L2.  The heads of a KV group select largely the same rows, so the G workgroups of a group
 // are given ids that differ by multiples of 8: they run on one XCD at about the same time and a V
-// row fetched for one head is an L2 hit for the others.  Returns the head (b * Hq + h) of a workgroup.
-__device__ __forceinline__ int head_of_block(const Shape& s, int block) {
+// row fetched for one head is an L2 hit for the others.  Returns the head (b * Hq + h) of a workgroup, and which kParts-th of the
+// output row's channels it makes.
+template <int kParts = 1>
+__device__ __forceinline__ int head_of_block(const Shape& s, int block, int* part = nullptr) {
   const int n_kvg = s.B * s.Hkv;                   // KV groups in the launch
-  if (n_kvg % 8 != 0) return block;
-  const int xcd = block & 7, slot = block >> 3;
+  if (part) *part = (n_kvg % 8 != 0 ? block : block >> 3) % kParts;
+  if (n_kvg % 8 != 0) return block / kParts;
+  const int xcd = block & 7, slot = (block >> 3) / kParts;
   return ((slot / s.G) * 8 + xcd) * s.G + slot % s.G;
 }
 
@@ -19,6 +24,37 @@ __device__ __forceinline__ int head_of_block(const Shape& s, int block) {
 // sum is formed by one wave in list order and the chunks are added in chunk order, whatever the number of waves
 // (a wave takes kAttendChunks / NW consecutive chunks): the output row does not depend on the launch shape.
 constexpr int kAttendChunks = 16;
+
+// Workgroups per head, each for its part of the channels: one CU takes rows in at 64 bytes a cycle, and few heads leave most of the
+// chip idle.  Four, while every one has a CU of its own.  Each makes the head's list, which costs no time, and the sums of a channel
+// are made as by one workgroup: the same bits.  One -> four, us: steps of 1 x 32K, k = 1024 25.5 -> 24.2, exact Top-k with its
+// attention 34.6 -> 33.2; steps of 1 x 128K, k = 4096 74.8 -> 66.0, 2 x 8000 FP8, k = 128 16.7 -> 16.3.  Two for 128 heads: bf16 4 x
+// 32K 54.7 -> 55.0, 4 x 64K 61.9 -> 61.3, FP8 35.1 -> 34.5, not worth the kernels.
+inline int attend_parts(const Shape& s) { return s.B * s.Hq <= 64 ? 4 : 1; }
+
+// N consecutive elements of a row, as Raw8.
+template <typename T, int N>
+struct RawPart {
+  typedef T Vec __attribute__((ext_vector_type(N)));
+  Vec w;
+  __device__ __forceinline__ void load(const T* p) { w = *reinterpret_cast<const Vec*>(p); }
+  __device__ __forceinline__ void get(float x[N]) const {
+    if constexpr (std::is_same<T, uint8_t>::value) {
+      uint32_t bits;
+      if constexpr (N == 4) bits = __builtin_bit_cast(uint32_t, w);
+      else bits = __builtin_bit_cast(uint16_t, w);
+      float all[4];
+      fp8x4_to_f32(bits, all);
+#pragma unroll
+      for (int c = 0; c < N; ++c) x[c] = all[c];
+    } else {
+#pragma unroll
+      for (int c = 0; c < N; ++c) x[c] = std::is_same<T, uint16_t>::value ? __uint_as_float((uint32_t)w[c] << 16) : (float)w[c];
+    }
+  }
+};
+template <typename T>
+struct RawPart<T, 8> : Raw8<T> {};
 
 struct AttendShared {
   float red[kAttendChunks][kD];
@@ -31,11 +67,12 @@ struct AttendShared {
 // no entry is valid).  The scores are known, so the softmax reference (their maximum over the valid entries) is
 // fixed before any V row is read and the partial sums add; a caller that already knows it passes it
 // (have_m, m_known) and saves the pass over the scores.  16 lanes per V row, 16-byte loads.
-template <typename T, int NW, bool kPaged>
+// kParts: the channels [part * D / kParts, (part + 1) * D / kParts) only.
+template <typename T, int NW, bool kPaged, int kParts = 1>
 __device__ __forceinline__ void attend_rows(AttendShared& sm, const T* __restrict__ V, int64_t stride_b,
                                             int64_t stride_h, int64_t stride_n, const KvPage& pg, int b, int g, int n,
                                             int kb, const int32_t* ih, const float* sh, bool have_m, float m_known,
-                                            float* __restrict__ out_row) {
+                                            float* __restrict__ out_row, int part = 0) {
   static_assert(kAttendChunks % NW == 0, "a wave takes a whole number of chunks");
   constexpr int kPerWave = kAttendChunks / NW;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -84,7 +121,8 @@ __device__ __forceinline__ void attend_rows(AttendShared& sm, const T* __restric
     for (int w = 1; w < NW; ++w) m = fmaxf(m, sm.redm[w]);
   }
 
-  const T* Vbg = V + Rows::base(b, g, stride_b, stride_h) + 8 * j;
+  constexpr int kEach = 8 / kParts;                          // channels of a lane
+  const T* Vbg = V + Rows::base(b, g, stride_b, stride_h) + part * (kD / kParts) + kEach * j;
   // A tile = 64 entries of the list, one per lane (row, weight); the entries of the next tile are fetched
   // before the rows of the current one.  The rows of a tile are read in two batches of eight loads per lane
   // (32 rows per wave), every load of a batch issued before the first is used: the compiler, left alone,
@@ -99,7 +137,7 @@ __device__ __forceinline__ void attend_rows(AttendShared& sm, const T* __restric
   for (int cc = 0; cc < kPerWave; ++cc) {
     const int ck = wave * kPerWave + cc;
     const int c0 = ck * chunk, c1 = c0 + chunk < kb ? c0 + chunk : kb;
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float acc[kEach] = {};
     float l = 0.f;
     for (int base = c0; base < c1; base += 64) {          // the prefetched entries run on across chunk boundaries
       l += my_p;
@@ -111,7 +149,7 @@ __device__ __forceinline__ void attend_rows(AttendShared& sm, const T* __restric
       else next_row = -1;
 #pragma unroll
       for (int half = 0; half < 16 / kBatch; ++half) {
-        Raw8<T> rw[kBatch];
+        RawPart<T, kEach> rw[kBatch];
         float pw[kBatch];
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
@@ -124,10 +162,10 @@ __device__ __forceinline__ void attend_rows(AttendShared& sm, const T* __restric
         __builtin_amdgcn_sched_barrier(0);                    // keep the batch's loads ahead of its arithmetic
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-          float x[8];
+          float x[kEach];
           rw[u].get(x);
 #pragma unroll
-          for (int c = 0; c < 8; ++c) acc[c] = fmaf(pw[u], x[c], acc[c]);
+          for (int c = 0; c < kEach; ++c) acc[c] = fmaf(pw[u], x[c], acc[c]);
         }
       }
     }
@@ -135,65 +173,66 @@ __device__ __forceinline__ void attend_rows(AttendShared& sm, const T* __restric
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) l += __shfl_xor(l, d);
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
+    for (int c = 0; c < kEach; ++c) {
       acc[c] += __shfl_xor(acc[c], 16);
       acc[c] += __shfl_xor(acc[c], 32);
     }
     if (rs == 0) {
 #pragma unroll
-      for (int c = 0; c < 8; ++c) sm.red[ck][8 * j + c] = acc[c];
+      for (int c = 0; c < kEach; ++c) sm.red[ck][kEach * j + c] = acc[c];
     }
     if (lane == 0) sm.redl[ck] = l;
   }
   __syncthreads();
-  if (tid < kD) {
+  if (tid < kD / kParts) {
     float a = 0.f, ls = 0.f;
 #pragma unroll
     for (int w = 0; w < kAttendChunks; ++w) {
       a += sm.red[w][tid];
       ls += sm.redl[w];
     }
-    out_row[tid] = ls > 0.f ? a / ls : 0.f;
+    out_row[part * (kD / kParts) + tid] = ls > 0.f ? a / ls : 0.f;
   }
 }
 
 // The same sum over the first ksel entries of a list in LDS (physical row, weight relative to the largest score), which
 // the caller has filled up to a multiple of 64 with entries of weight 0 (pad_list), for a head of budget kb: the chunks, the
 // order of the additions and therefore the bits are those of attend_rows.  A wave issues the rows of a whole 64-entry
-// tile (16 loads per lane; 8 for fp32 rows, which take twice the registers) before it uses the first.
-template <typename T, int NW, bool kPaged, typename Entry>
+// tile (16 loads per lane; 8 of 32 bytes, which take twice the registers) before it uses the first.
+template <typename T, int NW, bool kPaged, int kParts, typename Entry>
 __device__ __forceinline__ void attend_list(AttendShared& sm, const T* __restrict__ Vbg, const KvPage& pg,
                                             int64_t stride_b, int64_t stride_n, int kb, int ksel,
-                                            const Entry* list, float* __restrict__ out_row) {
+                                            const Entry* list, float* __restrict__ out_row, int part) {
   constexpr int kPerWave = kAttendChunks / NW;
-  constexpr int kBatch = sizeof(T) == 4 ? 8 : 16;
+  constexpr int kEach = 8 / kParts;                          // channels of a lane
+  constexpr int kBatch = kEach * sizeof(T) == 32 ? 8 : 16;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int j = lane & 15, rs = lane >> 4;
   const int chunk = (((kb + kAttendChunks - 1) / kAttendChunks) + 63) & ~63;
-  const T* Vj = Vbg + 8 * j;
+  const T* Vj = Vbg + part * (kD / kParts) + kEach * j;
   auto offset = [&](int row) { return RowMap<kPaged>::offset(pg, row, stride_b, stride_n); };
 #pragma unroll 1
   for (int cc = 0; cc < kPerWave; ++cc) {
     const int ck = wave * kPerWave + cc;
     const int c0 = ck * chunk, c1 = c0 + chunk < ksel ? c0 + chunk : ksel;
-    float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float acc[kEach] = {};
     float l = 0.f;
     for (int base = c0; base < c1; base += 64) {
       l += list[base + lane].p;
 #pragma unroll
-      for (int part = 0; part < 16 / kBatch; ++part) {
-        Raw8<T> rw[kBatch];
-        const Entry* e = list + base + 4 * kBatch * part + rs;
+      for (int step = 0; step < 16 / kBatch; ++step) {
+        RawPart<T, kEach> rw[kBatch];
+        const Entry* e = list + base + 4 * kBatch * step + rs;
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) rw[u].load(Vj + offset(e[4 * u].row));
         __builtin_amdgcn_sched_barrier(0);                    // keep the batch's loads ahead of its arithmetic
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
           const float p = e[4 * u].p;
-          float x[8];
+          float x[kEach];
           rw[u].get(x);
 #pragma unroll
-          for (int c = 0; c < 8; ++c) acc[c] = fmaf(p, x[c], acc[c]);
+          for (int c = 0; c < kEach; ++c) acc[c] = fmaf(p, x[c], acc[c]);
         }
       }
     }
@@ -201,25 +240,25 @@ __device__ __forceinline__ void attend_list(AttendShared& sm, const T* __restric
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) l += __shfl_xor(l, d);
 #pragma unroll
-    for (int c = 0; c < 8; ++c) {
+    for (int c = 0; c < kEach; ++c) {
       acc[c] += __shfl_xor(acc[c], 16);
       acc[c] += __shfl_xor(acc[c], 32);
     }
     if (rs == 0) {
 #pragma unroll
-      for (int c = 0; c < 8; ++c) sm.red[ck][8 * j + c] = acc[c];
+      for (int c = 0; c < kEach; ++c) sm.red[ck][kEach * j + c] = acc[c];
     }
     if (lane == 0) sm.redl[ck] = l;
   }
   __syncthreads();
-  if (tid < kD) {
+  if (tid < kD / kParts) {
     float a = 0.f, ls = 0.f;
 #pragma unroll
     for (int w = 0; w < kAttendChunks; ++w) {
       a += sm.red[w][tid];
       ls += sm.redl[w];
     }
-    out_row[tid] = ls > 0.f ? a / ls : 0.f;
+    out_row[part * (kD / kParts) + tid] = ls > 0.f ? a / ls : 0.f;
   }
 }
 

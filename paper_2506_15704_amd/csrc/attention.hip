@@ -16,8 +16,8 @@ namespace lfps {
 
 constexpr int kAttnThreads = 256;       // full attention
 
-// grid B*Hq, kSparseWaves waves per workgroup
-template <typename T, int kSparseWaves, bool kPaged>
+// grid B*Hq * kParts, kSparseWaves waves per workgroup
+template <typename T, int kSparseWaves, bool kPaged, int kParts>
 __global__ __launch_bounds__(kSparseWaves * 64) void k_sparse_attn(Shape s, const T* __restrict__ V, int64_t stride_b,
                                                                 int64_t stride_h, int64_t stride_n, KvPage pg,
                                                                 const int32_t* __restrict__ seq_lens,
@@ -27,16 +27,17 @@ __global__ __launch_bounds__(kSparseWaves * 64) void k_sparse_attn(Shape s, cons
                                                                 float* __restrict__ out,
                                                                 const int32_t* __restrict__ skip_if) {
   __shared__ AttendShared sm;
-  const int bh = head_of_block(s, blockIdx.x);
+  int part;
+  const int bh = head_of_block<kParts>(s, blockIdx.x, &part);
   if (skip_if && skip_if[bh] != 0) return;            // bypassed head: the gate wrote its output row
   const int b = bh / s.Hq, h = bh % s.Hq, g = h / s.G;
   int n = seq_lens[b];
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   int kb = kk[b];
   kb = kb < 0 ? 0 : (kb > s.kmax ? s.kmax : kb);
-  attend_rows<T, kSparseWaves, kPaged>(sm, V, stride_b, stride_h, stride_n, pg, b, g, n, kb,
-                                       idx + (int64_t)bh * s.kmax, idx_score + (int64_t)bh * s.kmax, false, 0.f,
-                                       out + (int64_t)bh * kD);
+  attend_rows<T, kSparseWaves, kPaged, kParts>(sm, V, stride_b, stride_h, stride_n, pg, b, g, n, kb,
+                                               idx + (int64_t)bh * s.kmax, idx_score + (int64_t)bh * s.kmax, false, 0.f,
+                                               out + (int64_t)bh * kD, part);
 }
 
 template <typename T>
@@ -45,21 +46,23 @@ static hipError_t launch_sparse_t(const Shape& s, const KvView& kv, const int32_
   // as many waves per head as keep every head's workgroup resident at once (256 CUs x 32 waves)
   const int heads = s.B * s.Hq;
   const T* V = (const T*)kv.v;
-#define LFPS_LAUNCH_SPARSE_P(NW, PAGED)                                                                        \
-  hipLaunchKernelGGL((k_sparse_attn<T, NW, PAGED>), dim3(heads), dim3(NW * 64), 0, st, s, V, kv.stride_b,      \
+#define LFPS_LAUNCH_SPARSE_P(NW, PAGED, PARTS)                                                                           \
+  hipLaunchKernelGGL((k_sparse_attn<T, NW, PAGED, PARTS>), dim3(heads * PARTS), dim3(NW * 64), 0, st, s, V, kv.stride_b, \
                      kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, idx, idx_score, k, out, skip_if)
-#define LFPS_LAUNCH_SPARSE(NW)          \
-  if (kv.page.table) {                  \
-    LFPS_LAUNCH_SPARSE_P(NW, true);     \
-  } else {                              \
-    LFPS_LAUNCH_SPARSE_P(NW, false);    \
+#define LFPS_LAUNCH_SPARSE(NW, PARTS)          \
+  if (kv.page.table) {                         \
+    LFPS_LAUNCH_SPARSE_P(NW, true, PARTS);     \
+  } else {                                     \
+    LFPS_LAUNCH_SPARSE_P(NW, false, PARTS);    \
   }
-  if (heads * 16 <= 4096) {
-    LFPS_LAUNCH_SPARSE(16)
+  if (attend_parts(s) == 4) {
+    LFPS_LAUNCH_SPARSE(16, 4)
+  } else if (heads * 16 <= 4096) {
+    LFPS_LAUNCH_SPARSE(16, 1)
   } else if (heads * 8 <= 4096) {
-    LFPS_LAUNCH_SPARSE(8)
+    LFPS_LAUNCH_SPARSE(8, 1)
   } else {
-    LFPS_LAUNCH_SPARSE(4)
+    LFPS_LAUNCH_SPARSE(4, 1)
   }
 #undef LFPS_LAUNCH_SPARSE
 #undef LFPS_LAUNCH_SPARSE_P

@@ -23,6 +23,7 @@ struct lfps_ctx {
   int32_t* slot;       // [B, Hq, score_stride] candidate slots of the filtered survivors
   int32_t* seg_count;  // [B, Hq, nseg]
   float* thr_state;    // [B, Hq] k-th best score of the previous step
+  float* tau;          // [B, Hq] what the rows have reached that the scoring pass of this step kept
   int32_t* keep_fits;  // [B, Hq] 1: the candidates of the head's last step fitted half of the select's list (table mode, else NULL)
   int range[2];        // rows of a range when a step (0 memoryless, 1 table form) takes the range kernel, else 0
   uint32_t* bitmap;    // [B, Hkv, bitmap_words] the candidates of such a step
@@ -182,7 +183,7 @@ int check_config(const lfps_config* c, Sizes* z, char* err, size_t errn) {
   z->aux_b = align256(z->aux_b);
   z->total = z->score_b + z->cand_b + z->count_b + z->sel_b + z->part_b + z->slot_b + z->seg_b + z->thr_b +
              z->line_b + 256 + z->x_b + z->aux_b + z->bitmap_b + z->tver_b + z->tsla_b + z->tstate_b + 2 * z->tflag_b +
-             z->thr_b /* gate marks */ + (c->table_mode ? z->thr_b : 0) /* keep_fits */;
+             2 * z->thr_b /* gate marks, tau */ + (c->table_mode ? z->thr_b : 0) /* keep_fits */;
   return LFPS_OK;
 }
 
@@ -388,6 +389,8 @@ int lfps_create(const lfps_config* cfg, lfps_ctx** out) {
   }
   c->gate = (int32_t*)p;
   p += z.thr_b;
+  c->tau = (float*)p;
+  p += z.thr_b;
   if (cfg->table_mode) c->keep_fits = (int32_t*)p;
   c->nseg = z.nseg;
   // The filtered pass pays off only if a head's survivors (about 1.25 x its budget) fit the select's list; with a
@@ -521,12 +524,12 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
   ctx->no_history = 0;                       // either form leaves every selecting head's k-th best score behind
   if (range) {
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
-           launch_range_score(s, q, v, from, ctx->thr_state, kFilterMargin, skip_if, ctx->score, ctx->slot,
+           launch_range_score(s, q, v, from, ctx->thr_state, kFilterMargin, ctx->tau, skip_if, ctx->score, ctx->slot,
                               s.score_stride, ctx->seg_count, ctx->nseg, ctx->bitmap, ctx->bitmap_words, range, ctx->flags, st));
   } else if (filtered) {
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
            launch_filter_score(s, q, v, ctx->cand, ctx->cand_count, ctx->group_start, line_total, ctx->thr_state,
-                               kFilterMargin, skip_if, ctx->score, ctx->slot, s.score_stride, ctx->seg_count, ctx->flags + 1,
+                               kFilterMargin, ctx->tau, skip_if, ctx->score, ctx->slot, s.score_stride, ctx->seg_count, ctx->flags + 1,
                                ctx->filter_blocks[v.page.table ? 1 : 0], ctx->flags, false, ctx->nseg, st));
   }
   if (filtered) {
@@ -534,7 +537,7 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
            launch_filter_select_attend(s, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
                                        ctx->flags + 1, ctx->nseg, ctx->cand, ctx->cand_count, ctx->group_start,
                                        line_total, range, ctx->bitmap, ctx->bitmap_words, k, topk_idx, sel,
-                                       ctx->thr_state, kFilterMargin, keep, skip_if, ctx->flags + 2, q, ctx->flags, v, out, st));
+                                       ctx->thr_state, ctx->tau, keep, skip_if, ctx->flags + 2, q, ctx->flags, v, out, st));
     return LFPS_OK;
   }
   if (step_fused(ctx, from))
@@ -699,13 +702,13 @@ int lfps_exact_topk(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int3
            launch_select(s, ctx->score, s.score_stride, nullptr, ctx->x_ns, ctx->x_rank, ctx->slot, nullptr, ctx->thr_x,
                          nullptr, nullptr, st));
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
-           launch_filter_score(sd, q, v, nullptr, ctx->x_cnt, ctx->x_start, x_total, ctx->thr_x, 0.f, nullptr, ctx->score,
+           launch_filter_score(sd, q, v, nullptr, ctx->x_cnt, ctx->x_start, x_total, ctx->thr_x, 0.f, ctx->tau, nullptr, ctx->score,
                                ctx->slot, s.score_stride, ctx->seg_count, ctx->flags + 1,
                                ctx->filter_blocks[v.page.table ? 1 : 0], ctx->flags, true, ctx->nseg, st));
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SELECT_ATTEND, st,
            launch_filter_select_attend(sd, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
                                        ctx->flags + 1, ctx->nseg, nullptr, ctx->x_cnt, ctx->x_start, x_total, 0, nullptr, 0, k, topk_idx,
-                                       topk_score ? topk_score : ctx->sel_score, ctx->thr_x, 0.f, KeepAll{kKeepRatio, nullptr, 0}, nullptr, nullptr,
+                                       topk_score ? topk_score : ctx->sel_score, ctx->thr_x, ctx->tau, KeepAll{kKeepRatio, nullptr, 0}, nullptr, nullptr,
                                        q, ctx->flags, v, nullptr, st));
     return LFPS_OK;
   }

@@ -114,7 +114,7 @@ hipError_t launch_candidates_score_f32(const Shape& s, const float* q, const KvV
                                        hipStream_t st);
 
 // Filtered scoring (bf16, fp16 or FP8 keys; the kernel keeps its first name, k_filter_score_bf16): per
-// head only rows with score >= thr_state[b,h] - margin are kept, as
+// head only rows with score >= thr_state[b,h] - margin (left in tau_out[b,h] where rows are kept: the select replaces thr_state) are kept, as
 // (score, position) lists in at most filter_nseg(s) pieces per head.  The kernel runs with exactly
 // n_blocks workgroups (filter_score_blocks: what the device holds at once) and cuts the candidate
 // slots of all groups (placed on one line by the candidates kernel: group_start, line_total) into
@@ -125,7 +125,7 @@ int filter_list_cap(const Shape& s);   // survivors per head the filtered select
 hipError_t filter_score_blocks(const Shape& s, int k_kind, int out[2]);
 hipError_t launch_filter_score(const Shape& s, const float* q, const KvView& kv, const int32_t* cand,
                                const int32_t* cand_count, const int64_t* group_start, const int64_t* line_total,
-                               const float* thr_state, float margin, const int32_t* skip_if, float* score,
+                               const float* thr_state, float margin, float* tau_out, const int32_t* skip_if, float* score,
                                int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int32_t* seg_rows_out,
                                int n_blocks, int32_t* flags, bool dense, int nseg, hipStream_t st);
 // S1 + S2 of a chained step in one kernel (range_score.hip): candidates from the Top-k of the step before (prev_topk, k) or
@@ -141,7 +141,7 @@ struct RangeSource {
 };
 int range_rows(const Shape& s, bool tables);   // see range_rows_for
 hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, const RangeSource& from,
-                              const float* thr_state, float margin, const int32_t* skip_if, float* score,
+                              const float* thr_state, float margin, float* tau_out, const int32_t* skip_if, float* score,
                               int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words,
                               int range, int32_t* flags, hipStream_t st);
 
@@ -165,7 +165,7 @@ hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, 
                                        const int32_t* cand, int32_t* cand_count, const int64_t* group_start,
                                        int64_t* line_total, int range, const uint32_t* bitmap, int bitmap_words,
                                        const int32_t* k, int32_t* topk_idx, float* topk_score,
-                                       float* thr_state, float margin, KeepAll keep, const int32_t* skip_if, int32_t* rescored,
+                                       float* thr_state, const float* tau, KeepAll keep, const int32_t* skip_if, int32_t* rescored,
                                        const float* q, int32_t* flags, const KvView& kv, float* out,
                                        hipStream_t st);   // out == NULL: select only
 

@@ -24,8 +24,8 @@ template <int G, bool kPaged, int kKind, bool kTables>
 __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
     Shape s, const float* __restrict__ q, const void* __restrict__ K, int64_t stride_b, int64_t stride_h,
     int64_t stride_n, KvPage page, const int32_t* __restrict__ seq_lens, RangeSource from,
-    const float* __restrict__ thr_state, float margin, const int32_t* __restrict__ skip_if, float* __restrict__ score,
-    int32_t* __restrict__ slot_out,
+    const float* __restrict__ thr_state, float margin, float* __restrict__ tau_out, const int32_t* __restrict__ skip_if,
+    float* __restrict__ score, int32_t* __restrict__ slot_out,
     int64_t score_stride, int32_t* __restrict__ seg_count, int nseg, uint32_t* __restrict__ bitmap, int bitmap_words,
     int range, float scale, int32_t* __restrict__ flags) {
   __shared__ float stage_score[4][G][kRangeStage];
@@ -147,7 +147,6 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
     if (sinks > lo) set_bit_range(bm, 0, sinks - 1 - lo);
   }
   __syncthreads();
-  if (tid < words && (lo >> 5) + tid < bitmap_words) bitmap[(int64_t)bg * bitmap_words + (lo >> 5) + tid] = bm[tid];
 
   // ---- the list: thread t owns the bits [t * nb, (t + 1) * nb), nb = the power of two that 256 threads cover the range with
   const int nb = range <= kScoreThreads ? 1 : 1 << (32 - __builtin_clz((uint32_t)(range - 1) / kScoreThreads)), bit0 = tid * nb;
@@ -178,8 +177,15 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
   const int out0 = geo.start(piece);                      // where its survivors go in the heads' rows
   const int64_t head = head0 + (kb < G ? kb : 0);
   const uint64_t nans = __ballot(kb < G && isnan(thr) && !skipped);
+  auto leave = [&](int kept) {                           // (no store before the last load: a wait for that would wait for the store)
+    if (tid < words && (lo >> 5) + tid < bitmap_words) bitmap[(int64_t)bg * bitmap_words + (lo >> 5) + tid] = bm[tid];
+    if (j == 0 && kb < G) {
+      seg_count[head * nseg + piece] = cnt << 16 | kept;
+      if (piece == 0) tau_out[head] = thr - margin;
+    }
+  };
   if (cnt == 0 || nans) {
-    if (j == 0 && kb < G) seg_count[head * nseg + piece] = cnt << 16;
+    leave(0);
     return;
   }
   const float tau = kb < G && !skipped ? thr - margin : INFINITY;
@@ -273,14 +279,14 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
     }
   }
   flush();
-  if (j == 0 && kb < G) seg_count[head * nseg + piece] = cnt << 16 | run;
+  leave(run);
 }
 
 // ----------------------------------------------------------------------------- launcher
 int range_rows(const Shape& s, bool tables) { return range_rows_for((int64_t)s.B * s.Hkv, s.Lcap, s.G, tables); }
 
 hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, const RangeSource& from,
-                              const float* thr_state, float margin, const int32_t* skip_if, float* score,
+                              const float* thr_state, float margin, float* tau_out, const int32_t* skip_if, float* score,
                               int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words,
                               int range, int32_t* flags, hipStream_t st) {
   dim3 grid((s.Lcap + range - 1) / range, s.B * s.Hkv), block(kScoreThreads);
@@ -291,7 +297,7 @@ hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, 
 #define LFPS_LAUNCH_RANGE(GG, PAGED, KIND, TABLES)                                                                      \
   if (!launched && s.G == GG && paged == PAGED && kind == KIND && tables == TABLES) {                                  \
     hipLaunchKernelGGL((k_range_score<GG, PAGED, KIND, TABLES>), grid, block, (size_t)range * 2, st, s, q, kv.k,        \
-                       kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, from, thr_state, margin, skip_if,  \
+                       kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, from, thr_state, margin, tau_out, skip_if,  \
                        score, slot_out, score_stride, seg_count, nseg, bitmap, bitmap_words, range, sc, flags);                \
     launched = true;                                                                                                    \
   }

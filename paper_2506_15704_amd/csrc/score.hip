@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
     Shape s, const float* __restrict__ q, const void* __restrict__ K, int64_t stride_b, int64_t stride_h,
     int64_t stride_n, KvPage page, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ cand,
     const int32_t* __restrict__ cand_count, const int64_t* __restrict__ group_start,
-    const int64_t* __restrict__ line_total, const float* __restrict__ thr_state, float margin,
+    const int64_t* __restrict__ line_total, const float* __restrict__ thr_state, float margin, float* __restrict__ tau_out,
     const int32_t* __restrict__ skip_if, float* __restrict__ score, int32_t* __restrict__ slot_out, int64_t score_stride,
     int32_t* __restrict__ seg_count, int32_t* __restrict__ seg_rows_out, int min_seg_rows, int nseg, float scale,
     int32_t* __restrict__ flags) {
@@ -374,7 +374,10 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
     if (stream) walk(StreamTile<kKind>{}, StreamTile<kKind>{});
     else walk(KTile<kKind>{}, KTile<kKind>{});
     flush();
-    if (j == 0 && kb < G) seg_count[head * nseg + seg] = run;
+    if (j == 0 && kb < G) {
+      seg_count[head * nseg + seg] = run;
+      if (seg == 0) tau_out[head] = thr - margin;
+    }
   }
     g0 += 256;
     if (g0 >= n_groups) break;
@@ -716,7 +719,7 @@ hipError_t filter_score_blocks(const Shape& s, int k_kind, int out[2]) {
 
 hipError_t launch_filter_score(const Shape& s, const float* q, const KvView& kv, const int32_t* cand,
                                const int32_t* cand_count, const int64_t* group_start, const int64_t* line_total,
-                               const float* thr_state, float margin, const int32_t* skip_if, float* score,
+                               const float* thr_state, float margin, float* tau_out, const int32_t* skip_if, float* score,
                                int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int32_t* seg_rows_out,
                                int n_blocks, int32_t* flags, bool dense, int nseg, hipStream_t st) {
   if (n_blocks < 1) return hipErrorInvalidValue;
@@ -726,7 +729,7 @@ hipError_t launch_filter_score(const Shape& s, const float* q, const KvView& kv,
 #define LFPS_LAUNCH_FILTER_D(GG, PAGED, FP8, DENSE)                                                                \
   hipLaunchKernelGGL((k_filter_score_bf16<GG, PAGED, FP8, DENSE>), grid, block, 0, st, s, q, kv.k, kv.stride_b,    \
                      kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, cand, cand_count, group_start, line_total,    \
-                     thr_state, margin, skip_if, score, slot_out, score_stride, seg_count, seg_rows_out,                    \
+                     thr_state, margin, tau_out, skip_if, score, slot_out, score_stride, seg_count, seg_rows_out,                    \
                      filter_min_seg_rows(s), nseg, scale, flags)
 #define LFPS_LAUNCH_FILTER_P(GG, PAGED, FP8)       \
   if (dense) {                                     \
