@@ -11,14 +11,17 @@
 //
 // Why one kernel: as two, a step of 8 groups x 32K rows spent 7.8 + 14.5 us here, of which the rows themselves are 5 us;
 // the rest is two launches and the round trips
-// candidates -> list -> geometry -> list -> rows.  Together: 13.7 us.
+// candidates -> list -> geometry -> list -> rows.  Together: 13.7 us, 12.2 with the rows through LDS:
+// every load instruction covers whole rows (StreamTile, here with ordinary loads).  With a lane's own 64 bytes of a row in four
+// loads, each of these touches 32 cache lines instead of 8, and with one tile per wave and eight to sixteen waves per CU all asking at
+// once the address unit was what the first rows waited for.  (A stage of 160 survivors makes room for it at four workgroups per CU.)
 #include "candidates.h"
 #include "range_geometry.h"
 #include "score_mfma.h"
 
 namespace lfps {
 
-constexpr int kRangeStage = 256;        // survivors a wave holds per head before it writes them out
+constexpr int kRangeStage = 160;        // survivors a wave holds per head before it writes them out
 
 template <int G, bool kPaged, int kKind, bool kTables>
 __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
@@ -29,7 +32,8 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
     int64_t score_stride, int32_t* __restrict__ seg_count, int nseg, uint32_t* __restrict__ bitmap, int bitmap_words,
     int range, float scale, int32_t* __restrict__ flags) {
   __shared__ float stage_score[4][G][kRangeStage];
-  __shared__ int32_t stage_slot[4][G][kRangeStage];
+  __shared__ uint16_t stage_slot[4][G][kRangeStage];     // relative to the range's first row
+  __shared__ u32x4 turn[4][StreamTile<kKind, false>::kLdsChunks];
   __shared__ uint32_t bm[kRangeMax / 32];
   __shared__ int wave_tot[4];
   extern __shared__ uint16_t list[];                     // the range's candidates, relative to its first row
@@ -41,7 +45,7 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
   const int words = range >> 5;
 
   using Rows = RowMap<kPaged>;
-  using Tile = KTile<kKind>;
+  using Tile = StreamTile<kKind, false>;
   using Op = typename Tile::Operand;
 
   // ---- what the workgroup needs is requested before anything is waited for
@@ -191,7 +195,7 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
   const float tau = kb < G && !skipped ? thr - margin : INFINITY;
   const uint32_t below = (1u << j) - 1u;                 // lanes of my 16-lane group with a lower row
   float* st_s = stage_score[wave][kb < G ? kb : 0];
-  int32_t* st_i = stage_slot[wave][kb < G ? kb : 0];
+  uint16_t* st_i = stage_slot[wave][kb < G ? kb : 0];
   constexpr int ES = Tile::kElemBytes, T = kRowsPerWaveIter;
   const char* Kbg = static_cast<const char*>(K) + Rows::base(b, g, stride_b, stride_h) * ES;
   int run = 0, staged = 0;                               // my head's survivors in global memory, and waiting in LDS
@@ -207,38 +211,30 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
       int32_t* dsl = slot_out + (head0 + h) * score_stride + out0 + run_h;
       for (int e = lane; e < cnt_h; e += 64) {
         dsc[e] = stage_score[wave][h][e];
-        dsl[e] = stage_slot[wave][h][e];
+        dsl[e] = lo + stage_slot[wave][h][e];
       }
     }
     run += staged;
     staged = 0;
     wave_lds_order();
   };
-  // the row of list entry e0 + lane (past the end: the last one, never kept)
-  auto ids_of = [&](int e0) { return lo + list[c0 + (e0 + lane < cnt ? e0 + lane : cnt - 1)]; };
-  auto issue = [&](Tile& Bt, int (&rows)[4], int id, int phys) {
-    int prow[4];
+  // list entry e0 + lane (past the end: the last one, never kept), relative to the range
+  auto ids_of = [&](int e0) { return (int)list[c0 + (e0 + lane < cnt ? e0 + lane : cnt - 1)]; };
+  auto consume = [&](const Tile& Bt, int ids, int e0) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      rows[t] = __shfl(id, 16 * t + j);
-      prow[t] = kPaged ? __shfl(phys, 16 * t + j) : rows[t];
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t) Bt.load_row(t, Kbg + Rows::offset(page, prow[t], stride_b, stride_n) * ES, kb);
-  };
-  auto consume = [&](Tile& Bt, int (&rows)[4], int e0) {
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
+      const KSub<kKind> sub = Bt.sub(t, turn[wave], lane);
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) acc = mfma16(A[kk], Bt.operand(t, kk), acc);
+      for (int kk = 0; kk < 4; ++kk) acc = mfma16(A[kk], sub.operand(kk), acc);
       const float v = Split3<Op>::sum(acc) * scale;
       const bool pass = kb < G && e0 + 16 * t + j < cnt && v >= tau;
       const uint32_t gm = (uint32_t)(__ballot(pass) >> (16 * kb)) & 0xFFFFu;   // my head's 16 rows
+      const int row = lane_value(ids, j, 16 * t);
       if (pass) {
         const int o = staged + __popc(gm & below);
         st_s[o] = v;
-        st_i[o] = rows[t];
+        st_i[o] = (uint16_t)row;
       }
       staged += __popc(gm);
     }
@@ -247,27 +243,29 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
   // One tile in flight per wave and sixteen waves per CU (two tiles in flight do not fit the registers of that many).
   // Paged cache: the block-table lookup of the next tile is issued before the loads of this one, so that the wait for it
   // does not wait for them (memory operations complete in order).
-  auto lookup = [&](int id) { return Rows::phys(page, b, id); };
+  auto lookup = [&](int id) { return Rows::phys(page, b, lo + id); };
   Tile Bt;
-  int rows[4];
-  int id = ids_of(0);
+  int id = ids_of(0), in_flight;                          // of the next tile, of the one in flight
   int phys = lookup(id);
   auto request = [&](int e0) {
-    const int id_now = id, phys_now = phys;
+    const int phys_now = phys;
+    in_flight = id;
     id = ids_of(e0 + T);
     if constexpr (kPaged) {
       asm volatile("" ::"v"(phys_now));
       phys = lookup(id);
       __builtin_amdgcn_sched_barrier(0);
+    } else {
+      phys = lookup(id);
     }
-    issue(Bt, rows, id_now, phys_now);
+    Bt.fetch(Kbg, phys_now, lane, [&](int p) { return Rows::offset(page, p, stride_b, stride_n) * ES; });
   };
   if constexpr (kSplitLate) {
     request(0);
     __builtin_amdgcn_sched_barrier(0);
     (void)query.operand(A, G, j);                        // (only fp16 has a range to report)
     for (int e0 = 0;;) {
-      consume(Bt, rows, e0);
+      consume(Bt, in_flight, e0);
       e0 += T;
       if (e0 >= cnt) break;
       request(e0);
@@ -275,7 +273,7 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
   } else {
     for (int e0 = 0; e0 < cnt; e0 += T) {
       request(e0);
-      consume(Bt, rows, e0);
+      consume(Bt, in_flight, e0);
     }
   }
   flush();

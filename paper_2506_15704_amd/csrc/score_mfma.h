@@ -204,7 +204,8 @@ struct KTile {
 // that a cache line is touched by one instruction only and need not be kept (non-temporal).  sub(t) turns the sixteen rows of
 // sub-tile t into operands through a wave-private piece of LDS (rows 16 bytes further apart than they are long, so that
 // neither the writes nor the reads of neighbouring lanes meet in a bank): the operands, and so the scores' bits, are KTile's.
-template <int kKind>
+// kOnce false: the same instructions with ordinary loads.
+template <int kKind, bool kOnce = true>
 struct StreamTile {
   using Operand = typename KSub<kKind>::Operand;
   static constexpr int kElemBytes = KSub<kKind>::kElemBytes;
@@ -219,7 +220,8 @@ struct StreamTile {
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
       const int row = lane_value(phys, lane / kChunks, i * kLoadRows);
-      raw[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(mine) + offset(row)));
+      const u32x4* at = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(mine) + offset(row));
+      raw[i] = kOnce ? __builtin_nontemporal_load(at) : *at;
     }
   }
   __device__ __forceinline__ KSub<kKind> sub(int t, u32x4* lds, int lane) const {
