@@ -570,7 +570,7 @@ int lfps_step(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int32_t* p
   hipStream_t st = (hipStream_t)stream;
   float* sel = topk_score ? topk_score : ctx->sel_score;
   int64_t* line_total = ctx->group_start + (int64_t)s.B * s.Hkv;   // zero between steps: the filtered select resets it
-  const RangeSource from{prev_topk, k, s.kmax % 4 == 0 && (uintptr_t)prev_topk % 16 == 0, nullptr, nullptr, 0};
+  const RangeSource from{prev_topk, k, nullptr, nullptr, 0};
   if (next_step_range(ctx, false) || step_fused(ctx, from))
     LAUNCH(ctx, LFPS_KERNEL_CANDIDATES, st, hipSuccess);      // (timing: S1 is part of the scoring kernel's launch)
   else
@@ -845,7 +845,7 @@ static int table_step_impl(lfps_ctx* ctx, const float* q, const KvView& v, const
   float* sel = topk_score ? topk_score : ctx->sel_score;
   int rc = table_candidates_impl(ctx, v.seq_lens, ctx->cand, ctx->cand_count, true, gate, st);
   if (rc != LFPS_OK) return rc;
-  const RangeSource from{nullptr, nullptr, 0, ctx->tab_f0, ctx->tab_fm, ctx->flag_words};
+  const RangeSource from{nullptr, nullptr, ctx->tab_f0, ctx->tab_fm, ctx->flag_words};
   rc = score_select_attend(ctx, q, v, from, k, topk_idx, sel, out, gate, st);
   if (rc != LFPS_OK) return rc;
   return table_update_impl(ctx, topk_idx, sel, k, v.seq_lens, gate, true, st);   // the select's rows are distinct

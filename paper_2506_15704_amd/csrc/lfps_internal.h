@@ -134,7 +134,6 @@ hipError_t launch_filter_score(const Shape& s, const float* q, const KvView& kv,
 struct RangeSource {
   const int32_t* prev_topk;          // [B, Hq, kmax]
   const int32_t* k;                  // [B]
-  int vec;                           // rows of prev_topk are 16-byte aligned
   const uint32_t* f0;                // [B, Hq, flag_words]
   const uint32_t* fm;
   int flag_words;
