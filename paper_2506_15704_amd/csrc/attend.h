@@ -9,15 +9,25 @@ namespace lfps {
 // Workgroups are dealt to the 8 XCDs round-robin (workgroup i runs on XCD i % 8) and every XCD has
 // its own L2.  The heads of a KV group select largely the same rows, so the G workgroups of a group
 // are given ids that differ by multiples of 8: they run on one XCD at about the same time and a V
-// row fetched for one head is an L2 hit for the others.  Returns the head (b * Hq + h) of a workgroup, and which kParts-th of the
-// output row's channels it makes.
-template <int kParts = 1>
-__device__ __forceinline__ int head_of_block(const Shape& s, int block, int* part = nullptr) {
-  const int n_kvg = s.B * s.Hkv;                   // KV groups in the launch
-  if (part) *part = (n_kvg % 8 != 0 ? block : block >> 3) % kParts;
-  if (n_kvg % 8 != 0) return block / kParts;
-  const int xcd = block & 7, slot = (block >> 3) / kParts;
-  return ((slot / s.G) * 8 + xcd) * s.G + slot % s.G;
+// row fetched for one head is an L2 hit for the others.
+struct HeadPlace {
+  int bg, b, g, bh;                                // KV group, request, KV head, query head (b * Hq + h)
+  int in_group;                                    // which of the group's heads
+  int part;                                        // which kParts-th of the output row's channels the workgroup makes
+};
+template <int kParts>
+__device__ __forceinline__ HeadPlace place_of_block(const Shape& s, uint32_t block) {
+  const int shift = s.G >> 1;                      // log2 of 1, 2 or 4 heads
+  const bool dealt = (s.B * s.Hkv) % 8 == 0;       // KV groups in the launch
+  const uint32_t slot = dealt ? block >> 3 : block, head = slot / kParts;
+  HeadPlace p;
+  p.part = (int)(slot % kParts);
+  p.in_group = (int)(head & (uint32_t)(s.G - 1));
+  p.bg = (int)(dealt ? (head >> shift) * 8 + (block & 7) : head >> shift);
+  p.b = (int)((uint32_t)p.bg / (uint32_t)s.Hkv);
+  p.g = p.bg - p.b * s.Hkv;
+  p.bh = (p.bg << shift) + p.in_group;
+  return p;
 }
 
 // The list of a head is cut into kAttendChunks equal chunks (a multiple of 64 entries each); every chunk's partial

@@ -27,17 +27,17 @@ __global__ __launch_bounds__(kSparseWaves * 64) void k_sparse_attn(Shape s, cons
                                                                 float* __restrict__ out,
                                                                 const int32_t* __restrict__ skip_if) {
   __shared__ AttendShared sm;
-  int part;
-  const int bh = head_of_block<kParts>(s, blockIdx.x, &part);
+  request_arguments<decltype(&k_sparse_attn<T, kSparseWaves, kPaged, kParts>)>();
+  const HeadPlace at = place_of_block<kParts>(s, blockIdx.x);
+  const int bh = at.bh, b = at.b, g = at.g;
   if (skip_if && skip_if[bh] != 0) return;            // bypassed head: the gate wrote its output row
-  const int b = bh / s.Hq, h = bh % s.Hq, g = h / s.G;
   int n = seq_lens[b];
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   int kb = kk[b];
   kb = kb < 0 ? 0 : (kb > s.kmax ? s.kmax : kb);
   attend_rows<T, kSparseWaves, kPaged, kParts>(sm, V, stride_b, stride_h, stride_n, pg, b, g, n, kb,
                                                idx + (int64_t)bh * s.kmax, idx_score + (int64_t)bh * s.kmax, false, 0.f,
-                                               out + (int64_t)bh * kD, part);
+                                               out + (int64_t)bh * kD, at.part);
 }
 
 template <typename T>

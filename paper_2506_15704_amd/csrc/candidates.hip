@@ -26,6 +26,7 @@ __global__ __launch_bounds__(kCandThreads) void k_candidates(Shape s, const int3
                                                              unsigned long long* __restrict__ line_total) {
   extern __shared__ uint32_t lds[];
   __shared__ int wave_tot[kCandThreads / 64];
+  request_arguments<decltype(&k_candidates)>();
   const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;
   int n = seq_lens[b];
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
@@ -50,6 +51,7 @@ __global__ __launch_bounds__(kCandThreads) void k_table_candidates(Shape s, cons
                                                                    int32_t* __restrict__ flags,
                                                                    int64_t* __restrict__ group_start,
                                                                    unsigned long long* __restrict__ line_total) {
+  request_arguments<decltype(&k_table_candidates)>();
   extern __shared__ uint32_t lds[];
   __shared__ int wave_tot[kCandThreads / 64];
   const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;

@@ -100,6 +100,7 @@ __global__ __launch_bounds__(kHistWaves * 64) void k_hist_stats(
     Shape s, const float* __restrict__ q, const void* __restrict__ K, int64_t stride_b, int64_t stride_h, int64_t stride_n,
     KvPage pg, const int32_t* __restrict__ seq_lens, float* __restrict__ part_m, double* __restrict__ part_l,
     float* __restrict__ dots, int64_t dots_stride, int32_t* __restrict__ flags, float kept_bytes) {
+  request_arguments<decltype(&k_hist_stats<G, kPaged, kKind, kMayOnce>)>();
   using Tile = HistTile<kPaged, kKind>;
   using Op = typename Tile::Op;
   __shared__ u32x4 turn[kMayOnce ? kHistWaves : 1][StreamTile<kKind>::kLdsChunks];
@@ -856,6 +857,7 @@ __global__ __launch_bounds__(256) void k_hist_apply_one(Shape s, float* __restri
                                                         const float* __restrict__ part_m,
                                                         const double* __restrict__ part_l, int blocks, double gamma,
                                                         double* __restrict__ part) {
+  request_arguments<decltype(&k_hist_apply_one)>();
   const int bh = blockIdx.y, b = bh / s.Hq, h = bh % s.Hq, g = h / s.G, tid = threadIdx.x;
   int n = seq_lens[b];
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);

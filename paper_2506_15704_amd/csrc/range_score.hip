@@ -38,10 +38,11 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
   __shared__ uint32_t bm[kRangeMax / 32];
   __shared__ int wave_tot[4];
   extern __shared__ uint16_t list[];                     // the range's candidates, relative to its first row
+  request_arguments<decltype(&k_range_score<G, kPaged, kKind, kTables>)>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, kb = lane >> 4;
-  const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;
+  const int bg = blockIdx.y, b = (int)((uint32_t)bg / (uint32_t)s.Hkv), g = bg - b * s.Hkv;
   const int lo = blockIdx.x * range;
   const int words = range >> 5;
 

@@ -41,6 +41,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_group_score_bf16(Shape s, con
                                                                     float scale, int32_t* __restrict__ flags,
                                                                     float* __restrict__ tops,
                                                                     const int32_t* __restrict__ kk) {
+  request_arguments<decltype(&k_group_score_bf16<G, GATHER, kPaged, kKind>)>();
   const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j = lane & 15, kb = lane >> 4;
@@ -116,6 +117,7 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_filter_score_bf16(
   __shared__ float stage_score[4][G][kFilterStage];
   __shared__ int32_t stage_slot[4][G][kFilterStage];
   __shared__ u32x4 turn[4][StreamTile<kKind>::kLdsChunks];
+  request_arguments<decltype(&k_filter_score_bf16<G, kPaged, kKind, kDense>)>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform values stay in scalar registers
   const int j = lane & 15, kb = lane >> 4;
@@ -483,6 +485,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_candidates_score_f32(
     KvPage pg, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ prev_topk, const int32_t* __restrict__ kk,
     int32_t* __restrict__ cand, int32_t* __restrict__ cand_count, float* __restrict__ score, int64_t score_stride, float scale,
     int32_t* __restrict__ flags) {
+  request_arguments<decltype(&k_candidates_score_f32<G, kPaged>)>();
   extern __shared__ uint32_t lds[];                      // the bitmap, then the part's list
   __shared__ int wave_tot[4];
   const int bg = blockIdx.y, b = bg / s.Hkv, g = bg % s.Hkv;

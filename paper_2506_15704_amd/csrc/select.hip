@@ -39,6 +39,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select(Shape s, const float* __
                                                         const int32_t* __restrict__ skip_if,
                                                         const int32_t* __restrict__ seq_lens,
                                                         const float* __restrict__ tops) {
+  request_arguments<decltype(&k_select)>();
   constexpr int NT = kSelThreads;
   __shared__ SelectShared<NT> sm;
   extern __shared__ float dyn[];                    // select_long's list, or the scores of a whole row

@@ -39,7 +39,7 @@ namespace lfps {
 
 // Is the k-th best of c candidates a threshold worth remembering?  (keep: c < keep.ratio * k and c <= keep.most)
 __device__ __forceinline__ bool filter_pays(int c, int ksel, const KeepAll& keep) {
-  return c / keep.ratio >= ksel || c > keep.most;
+  return c >= keep.ratio * ksel || c > keep.most;
 }
 
 // What a bypassed head remembers, by one thread: it has no k-th best score of this step.  -inf makes the first step in which
@@ -134,14 +134,14 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   AttendShared& as = *reinterpret_cast<AttendShared*>(dyn);
   SelRow* list = reinterpret_cast<SelRow*>(dyn + sizeof(AttendShared));
   if (!kRanges && blockIdx.x == 0 && threadIdx.x == 0) *line_total = 0;   // the scoring pass that read it has finished
-  int part;
-  const int bh = head_of_block<kParts>(s, blockIdx.x, &part);     // the heads of a KV group on one XCD: they share V rows in its L2
+  request_arguments<decltype(&k_filter_select_attend<T, kPaged, kKind, NT, kRanges, kParts>)>();
+  const HeadPlace at = place_of_block<kParts>(s, blockIdx.x);     // the heads of a KV group on one XCD: they share V rows in its L2
+  const int bh = at.bh, b = at.b, g = at.g, bg = at.bg, part = at.part;
   const bool writes = kParts == 1 || part == 0;
-  const int b = bh / s.Hq, h = bh % s.Hq, g = h / s.G;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int bg = b * s.Hkv + g;
+  const bool leads = writes && at.in_group == 0;     // leaves what the group's heads have in common
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool skipped = skip_if && skip_if[bh] != 0;  // bypassed head: its rows were written by the gate
-  if (skipped && !(kRanges && h % s.G == 0 && writes)) {
+  if (skipped && !(kRanges && leads)) {
     if (tid == 0 && writes) remember_bypassed(thr_state, keep, bh);
     return;
   }
@@ -197,22 +197,17 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   }
   __syncthreads();
   if (kRanges) {
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) c += ctot[w];
-    if (tid == 0 && h % s.G == 0 && writes) cand_count[bg] = c;
+    c += __builtin_amdgcn_readlane(wave_inclusive_sum(lane < kWaves ? ctot[lane] : 0), 63);
+    if (tid == 0 && leads) cand_count[bg] = c;
     if (skipped) {
       if (tid == 0) remember_bypassed(thr_state, keep, bh);
       return;
     }
   }
   const int ksel = kb < c ? kb : c;
-  int base = 0, n_surv = 0;
-#pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    const int t = wtot[w];
-    base += w < wv ? t : 0;
-    n_surv += t;
-  }
+  const int of_wave = lane < kWaves ? wtot[lane] : 0, upto_wave = wave_inclusive_sum(of_wave);
+  const int base = __builtin_amdgcn_readlane(upto_wave, wv) - __builtin_amdgcn_readlane(of_wave, wv);
+  const int n_surv = __builtin_amdgcn_readlane(upto_wave, 63);
   {
     int off = base + inc - cnt;
 #pragma unroll
@@ -268,7 +263,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     report_q_range(load_query_operand(A, q, (int64_t)b * s.Hq + (int64_t)g * s.G, s.G, lane & 15, lane >> 4), flags);
     const char* Kbg = static_cast<const char*>(K) + Rows::base(b, g, stride_b, stride_h) * KTile<kKind>::kElemBytes;
     score_slots_mfma<kPaged, kKind>(A, Kbg, page, b, stride_b, stride_n, cbg, n, c, wv * kRowsPerWaveIter,
-                                    kWaves * kRowsPerWaveIter, sc, (lane >> 4) == h - g * s.G, scale);
+                                    kWaves * kRowsPerWaveIter, sc, (lane >> 4) == at.in_group, scale);
   }
   __syncthreads();                                  // seg_off, or the score row, is complete before anyone reads it
   const int n_el = unfiltered ? c : n_surv;
@@ -366,16 +361,16 @@ __global__ __launch_bounds__(kSelThreads) void k_select_attend(
   __shared__ AttendShared as;
   extern __shared__ char dyn[];                     // the list of selected rows, or before it the scores of a long row
   SelRow* list = reinterpret_cast<SelRow*>(dyn);
-  int part;
-  const int bh = head_of_block<kParts>(s, blockIdx.x, &part);
+  request_arguments<decltype(&k_select_attend<T, kPaged, kParts>)>();
+  const HeadPlace at = place_of_block<kParts>(s, blockIdx.x);
+  const int bh = at.bh, b = at.b, g = at.g, part = at.part;
   const bool writes = kParts == 1 || part == 0;
-  const int b = bh / s.Hq, h = bh % s.Hq, g = h / s.G;
   const int tid = threadIdx.x;
   if (skip_if && skip_if[bh] != 0) {                // bypassed head: its rows were written by the gate
     if (thr_state && tid == 0 && writes) remember_bypassed(thr_state, keep, bh);
     return;
   }
-  int c = cand_count[b * s.Hkv + g];
+  int c = cand_count[at.bg];
   c = c < 0 ? 0 : (c > s.cand_cap ? s.cand_cap : c);
   int kb = kk[b];
   kb = kb < 0 ? 0 : (kb > s.kmax ? s.kmax : kb);
@@ -404,7 +399,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_attend(
     thr_out = nullptr;
   }
   const float* sc = score + (int64_t)bh * score_stride;
-  const int32_t* cbg = cand + ((int64_t)b * s.Hkv + g) * s.cand_cap;
+  const int32_t* cbg = cand + (int64_t)at.bg * s.cand_cap;
   if (in_registers) {
     for (int i = tid; i < 2 * NT; i += NT) sm.hist[i] = 0u;
     if (tid == 0) sm.list_n = 0u;

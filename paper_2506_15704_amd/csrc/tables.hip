@@ -96,6 +96,7 @@ __global__ __launch_bounds__(kTabThreads) void k_table_flags(Shape s, const floa
                                                              uint32_t* __restrict__ f0, uint32_t* __restrict__ fm,
                                                              int flag_words, int rows_per_block, double a,
                                                              const int32_t* __restrict__ gate) {
+  request_arguments<decltype(&k_table_flags)>();
   __shared__ uint32_t w0[kFlagIters * kTabThreads / 32], wm[kFlagIters * kTabThreads / 32];
   const int bh = blockIdx.y, b = bh / s.Hq;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -340,6 +341,7 @@ __global__ __launch_bounds__(kUpdateThreads) void k_table_update_own(Shape s, fl
                                                                      const int32_t* __restrict__ kk, double gamma,
                                                                      const int32_t* __restrict__ gate,
                                                                      int32_t* __restrict__ flags) {
+  request_arguments<decltype(&k_table_update_own<kEach>)>();
   constexpr int NT = kUpdateThreads, NW = NT / 64;
   __shared__ float top[NW];
   __shared__ double red[NW][8];
@@ -614,6 +616,7 @@ __global__ __launch_bounds__(64) void k_head_sparsity(Shape s, const float* __re
                                                       float* __restrict__ rho_out, int32_t* __restrict__ gate_out,
                                                       const float* __restrict__ vbar, int32_t* __restrict__ topk_idx,
                                                       float* __restrict__ topk_score, float* __restrict__ out) {
+  request_arguments<decltype(&k_head_sparsity<T, kPaged>)>();
   const int bh = blockIdx.x, b = bh / s.Hq, h = bh % s.Hq, g = h / s.G, lane = threadIdx.x;
   const int j = lane & 15, rs = lane >> 4;                    // 16 lanes per row, 8 channels each
   int n = seq_lens[b];
