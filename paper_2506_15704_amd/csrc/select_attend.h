@@ -61,8 +61,12 @@ constexpr int kSelRowsMax = 16384;    // selected rows of a head that pass throu
 // 330 to 1311 2 % faster for four steps, but there a list of 4096 overflows, for every head at once, when the scores grow
 // from one step to the next.  (The unfiltered pass of a head left short has half the waves: steps in which 2 % of the heads
 // take it, k = 400, 193 against 175 us at 1024 heads.)
+// Up to 64 heads with budgets of at most 512: 512 threads (with four workgroups a head).  A head's uniform work is done by every wave
+// on its own, and there are half as many; steps with 1024 -> 512, us: 1 x 3000, k = 48 16.5 -> 15.4, 1 x 16000, k = 256 17.3 -> 17.0,
+// 1 x 32K, k = 512 21.2 -> 20.7, FP8 2 x 8000, k = 250 16.7 -> 16.4; k = 1024 27.0 -> 27.7, and with one workgroup a head within 1 %.
 inline int filter_select_threads(const Shape& s) {
   const int heads = s.B * s.Hq;
+  if (heads <= 64 && s.kmax <= 512) return 512;
   if (heads > 512 && kRegElems * 256 >= 4 * s.kmax) return 256;
   return heads <= 256 || kRegElems * 512 < 2 * s.kmax ? 1024 : 512;
 }
@@ -525,6 +529,7 @@ void each_filter_select(Use use) {
     use(&k_filter_select_attend<T, kPaged, kKind, 256, kRanges, 1>, kPaged, 256, kRanges, 1);
     use(&k_filter_select_attend<T, kPaged, kKind, 512, kRanges, 1>, kPaged, 512, kRanges, 1);
     use(&k_filter_select_attend<T, kPaged, kKind, 1024, kRanges, 1>, kPaged, 1024, kRanges, 1);
+    use(&k_filter_select_attend<T, kPaged, kKind, 512, kRanges, 4>, kPaged, 512, kRanges, 4);
     use(&k_filter_select_attend<T, kPaged, kKind, 1024, kRanges, 4>, kPaged, 1024, kRanges, 4);
   };
   of(std::false_type{}, std::false_type{});
