@@ -536,7 +536,7 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SELECT_ATTEND, st,
            launch_filter_select_attend(s, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
                                        ctx->flags + 1, ctx->nseg, ctx->cand, ctx->cand_count, ctx->group_start,
-                                       line_total, range, ctx->bitmap, ctx->bitmap_words, k, topk_idx, sel,
+                                       line_total, range, range_parts(s, from.prev_topk == nullptr), ctx->bitmap, ctx->bitmap_words, k, topk_idx, sel,
                                        ctx->thr_state, ctx->tau, keep, skip_if, ctx->flags + 2, q, ctx->flags, v, out, st));
     return LFPS_OK;
   }
@@ -707,7 +707,7 @@ int lfps_exact_topk(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int3
                                ctx->filter_blocks[v.page.table ? 1 : 0], ctx->flags, true, ctx->nseg, st));
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SELECT_ATTEND, st,
            launch_filter_select_attend(sd, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
-                                       ctx->flags + 1, ctx->nseg, nullptr, ctx->x_cnt, ctx->x_start, x_total, 0, nullptr, 0, k, topk_idx,
+                                       ctx->flags + 1, ctx->nseg, nullptr, ctx->x_cnt, ctx->x_start, x_total, 0, 0, nullptr, 0, k, topk_idx,
                                        topk_score ? topk_score : ctx->sel_score, ctx->thr_x, ctx->tau, KeepAll{kKeepRatio, nullptr, 0}, nullptr, nullptr,
                                        q, ctx->flags, v, nullptr, st));
     return LFPS_OK;

@@ -138,7 +138,8 @@ struct RangeSource {
   const uint32_t* fm;
   int flag_words;
 };
-int range_rows(const Shape& s, bool tables);   // see range_rows_for
+int range_rows(const Shape& s, bool tables);   // see range_rows_for and wide_rows_for
+int range_parts(const Shape& s, bool tables);  // wide ranges: every request's rows are cut into so many equal ones; else 0
 hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, const RangeSource& from,
                               const float* thr_state, float margin, float* tau_out, const int32_t* skip_if, float* score,
                               int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words,
@@ -162,7 +163,7 @@ hipError_t configure_select_attend(const Shape& s, int dtype, bool k_fp8, bool v
 hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, int32_t* slot,
                                        int64_t score_stride, const int32_t* seg_count, const int32_t* seg_rows, int nseg,
                                        const int32_t* cand, int32_t* cand_count, const int64_t* group_start,
-                                       int64_t* line_total, int range, const uint32_t* bitmap, int bitmap_words,
+                                       int64_t* line_total, int range, int range_parts, const uint32_t* bitmap, int bitmap_words,
                                        const int32_t* k, int32_t* topk_idx, float* topk_score,
                                        float* thr_state, const float* tau, KeepAll keep, const int32_t* skip_if, int32_t* rescored,
                                        const float* q, int32_t* flags, const KvView& kv, float* out,

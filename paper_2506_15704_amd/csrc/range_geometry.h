@@ -7,10 +7,15 @@ namespace lfps {
 // A group's rows [0, n) are cut into ranges of `range` rows and the candidates of a range into four pieces.  Piece p
 // belongs to range p / 4 and keeps its survivors from start(p) on: a range's pieces stand a quarter of the range apart
 // (of the last range: a quarter of its rows, rounded up to 16, which stays below n rounded up to 64).
+__device__ __forceinline__ int equal_ranges(int n, int parts) {
+  const int rows = (int)(((uint32_t)n + (uint32_t)parts - 1u) / (uint32_t)parts + 63u) & ~63;
+  return rows > 64 ? rows : 64;
+}
 struct RangePieces {
   int range, last, apart_last, count;
-  __device__ __forceinline__ RangePieces(int n, int range_) : range(range_) {
-    const int ranges = n > 0 ? (n - 1) / range + 1 : 0;
+  // parts > 0: that many ranges of equal length, a multiple of 64 rows, whatever range_ is.
+  __device__ __forceinline__ RangePieces(int n, int range_, int parts) : range(parts > 0 ? equal_ranges(n, parts) : range_) {
+    const int ranges = n > 0 ? (int)((uint32_t)(n - 1) / (uint32_t)range) + 1 : 0;
     last = ranges - 1;
     const int rows = n - last * range;                   // of the last range
     apart_last = (((rows + 3) >> 2) + 15) & ~15;

@@ -204,8 +204,8 @@ struct KTile {
 // that a cache line is touched by one instruction only and need not be kept (non-temporal).  sub(t) turns the sixteen rows of
 // sub-tile t into operands through a wave-private piece of LDS (rows 16 bytes further apart than they are long, so that
 // neither the writes nor the reads of neighbouring lanes meet in a bank): the operands, and so the scores' bits, are KTile's.
-// kOnce false: the same instructions with ordinary loads.
-template <int kKind, bool kOnce = true>
+// once false: the same instructions with ordinary loads.
+template <int kKind>
 struct StreamTile {
   using Operand = typename KSub<kKind>::Operand;
   static constexpr int kElemBytes = KSub<kKind>::kElemBytes;
@@ -215,13 +215,20 @@ struct StreamTile {
   static constexpr int kLdsChunks = 16 * (kChunks + 1);
   u32x4 raw[kLoads];
   template <typename Offset>
-  __device__ __forceinline__ void fetch(const char* Kbg, int phys, int lane, Offset offset) {
+  __device__ __forceinline__ void fetch(const char* Kbg, int phys, int lane, Offset offset, bool once = true) {
     const u32x4* mine = reinterpret_cast<const u32x4*>(Kbg) + lane % kChunks;
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i) {
+    auto at = [&](int i) {
       const int row = lane_value(phys, lane / kChunks, i * kLoadRows);
-      const u32x4* at = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(mine) + offset(row));
-      raw[i] = kOnce ? __builtin_nontemporal_load(at) : *at;
+      return reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(mine) + offset(row));
+    };
+    if (once) {
+      asm volatile("; past the caches");                               // (or the compiler makes ordinary loads of both branches)
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) raw[i] = __builtin_nontemporal_load(at(i));
+      asm volatile("; past the caches");
+    } else {
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) raw[i] = *at(i);
     }
   }
   __device__ __forceinline__ KSub<kKind> sub(int t, u32x4* lds, int lane) const {
