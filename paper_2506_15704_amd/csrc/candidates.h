@@ -136,27 +136,31 @@ __device__ __forceinline__ void bitmap_from_topk(const Shape& s, uint32_t* bm, i
   int ids[4 * kU];
   auto fetch = [&](int j0) {
 #pragma unroll
-    for (int h = 0; h < 4; ++h)
+    for (int u = 0; u < kU; ++u) {
+      const int j = j0 + tid + u * NT;
+      if (j0 + u * NT >= s.kmax) break;                    // (uniform)
 #pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int j = j0 + tid + u * NT;
-        ids[h * kU + u] = (h < s.G && j < s.kmax) ? pt[(int64_t)h * s.kmax + j] : -1;
-      }
+      for (int h = 0; h < 4; ++h) ids[u * 4 + h] = (h < s.G && j < s.kmax) ? pt[(int64_t)h * s.kmax + j] : -1;
+    }
   };
   fetch(0);
   for (int w = tid; w < words; w += NT) bm[w] = 0u;
   __syncthreads();
   for (int j0 = 0;;) {
 #pragma unroll
-    for (int e = 0; e < 4 * kU; ++e) {
-      const int i = (j0 + tid + (e % kU) * NT < kb) ? ids[e] : -1;
-      if (i >= 0 && i < n) {
-        const int lo = i - r < 0 ? 0 : i - r;
-        if (r <= kWindowRadius) {
-          set_bit_window(bm, lo, i + r + 1 > n - 1 ? n - 1 : i + r + 1);
-        } else {
-          const int64_t hi64 = (int64_t)i + r + 1;
-          set_bit_range(bm, lo, hi64 > n - 1 ? n - 1 : (int)hi64);
+    for (int u = 0; u < kU; ++u) {
+      if (j0 + u * NT >= kb) break;                        // (uniform)
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        const int i = (j0 + tid + u * NT < kb) ? ids[u * 4 + h] : -1;
+        if (i >= 0 && i < n) {
+          const int lo = i - r < 0 ? 0 : i - r;
+          if (r <= kWindowRadius) {
+            set_bit_window(bm, lo, i + r + 1 > n - 1 ? n - 1 : i + r + 1);
+          } else {
+            const int64_t hi64 = (int64_t)i + r + 1;
+            set_bit_range(bm, lo, hi64 > n - 1 ? n - 1 : (int)hi64);
+          }
         }
       }
     }

@@ -88,12 +88,12 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
   auto fetch = [&](int j0) {
     if constexpr (!kTables) {
 #pragma unroll
-      for (int u = 0; u < kEach; ++u)
+      for (int u = 0; u < kEach; ++u) {
+        const int at = j0 + kScoreThreads * u;
+        if (at >= s.kmax) break;                           // (uniform)
 #pragma unroll
-        for (int h = 0; h < G; ++h) {
-          const int at = j0 + kScoreThreads * u + tid;
-          ids[u][h] = at < s.kmax ? pt[(int64_t)h * s.kmax + at] : -1;
-        }
+        for (int h = 0; h < G; ++h) ids[u][h] = at + tid < s.kmax ? pt[(int64_t)h * s.kmax + at + tid] : -1;
+      }
     }
   };
   fetch(0);
