@@ -47,9 +47,10 @@ __device__ __forceinline__ void find_bin(SelectShared<NT>& sm, uint32_t need, in
   const uint32_t inc = all - upto + mine;    // inclusive suffix sum within the wave
   if (lane == 0) sm.wsum[wv] = all;
   __syncthreads();
-  uint32_t above_waves = 0;
-#pragma unroll
-  for (int w = 0; w < kSelWaves; ++w) above_waves += w > wv ? sm.wsum[w] : 0u;
+  // (every wave adds the waves' sums up, in its lanes: with a loop over sixteen of them this took as many instructions as the rest)
+  const uint32_t upto_wave = (uint32_t)wave_inclusive_sum(lane < kSelWaves ? (int)sm.wsum[lane] : 0);
+  const uint32_t above_waves = (uint32_t)__builtin_amdgcn_readlane((int)upto_wave, 63) -
+                               (uint32_t)__builtin_amdgcn_readlane((int)upto_wave, __builtin_amdgcn_readfirstlane(wv));
   const uint32_t suffix_incl = above_waves + inc;    // count in bins >= 2t
   const uint32_t suffix_excl = suffix_incl - mine;   // count in bins >  2t+1
   if (suffix_incl >= need && suffix_excl < need) {   // exactly one thread

@@ -37,7 +37,8 @@ template <int NT, int E, bool kScalarMax = false, typename Out>
 __device__ __forceinline__ void select_registers(SelectShared<NT>& sm, const float (&v)[E], int n, int ksel, float lo,
                                                  bool from_min, float* __restrict__ thr_out, Out out) {
   constexpr int kWaves = NT / 64, kBins = 2 * NT, kListCap = NT;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  static_assert(kWaves <= 16, "the waves' values are merged in a row of lanes");
   auto mine = [&](int u) { return u * NT + tid < n; };
   float hi = -FLT_MAX, mn = FLT_MAX;
 #pragma unroll
@@ -53,18 +54,14 @@ __device__ __forceinline__ void select_registers(SelectShared<NT>& sm, const flo
     mn = -settled(wave_max_in_last(-mn));
     if (lane == kLeader) sm.wlo[wv] = mn;
     __syncthreads();
-    lo = sm.wlo[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) lo = fminf(lo, sm.wlo[w]);
+    lo = -__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(row16_max(lane < kWaves ? -sm.wlo[lane] : -FLT_MAX))));
   }
   // (bins are computed where they are needed: held for all elements they would cost E registers)
 #pragma unroll
   for (int u = 0; u < E; ++u)
     if (mine(u)) atomicAdd(&sm.hist[tail_bin(v[u], lo, kBins)], 1u);
   __syncthreads();
-  float top = sm.whi[0];
-#pragma unroll
-  for (int w = 1; w < kWaves; ++w) top = fmaxf(top, sm.whi[w]);
+  const float top = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(row16_max(lane < kWaves ? sm.whi[lane] : -FLT_MAX))));
   find_bin(sm, (uint32_t)ksel, tid, lane, wv);
   const int tb = (int)sm.bin;
   uint32_t need = sm.need;                                 // elements still to take from bin tb (>= 1)
