@@ -7,47 +7,14 @@
 //   2. the filtered scoring kernel streams all rows once and keeps only those that reach the threshold;
 //   3. the select picks the exact k best from the survivors; a head whose survivors are fewer than k (or too many
 //      for the on-chip list) is rescored the plain way, so the result is always the exact Top-k.
-#include "lfps_internal.h"
+#include "score_mfma.h"
 
 namespace lfps {
 
-// grid B*Hkv, 256 threads.
-__global__ __launch_bounds__(256) void k_dense_prep(Shape s, const int32_t* __restrict__ seq_lens,
-                                                    const int32_t* __restrict__ kk, int ns_max, int list_cap,
-                                                    int32_t* __restrict__ x_cnt, int64_t* __restrict__ x_start,
-                                                    int32_t* __restrict__ x_nsg, int32_t* __restrict__ x_ns,
-                                                    int32_t* __restrict__ x_rank, int32_t* __restrict__ sample) {
-  __shared__ long long part[256];
-  const int bg = blockIdx.x, b = bg / s.Hkv, g = bg % s.Hkv, tid = threadIdx.x;
-  const int n_groups = s.B * s.Hkv;
-  auto len = [&](int bb) {
-    int n = seq_lens[bb];
-    return n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
-  };
-  // my place on the line: rows of the groups before mine (and, for the last group, the line's length)
-  long long before = 0, all = 0;
-  for (int i = tid; i < n_groups; i += 256) {
-    const long long n_i = len(i / s.Hkv);
-    before += i < bg ? n_i : 0;
-    all += n_i;
-  }
-  part[tid] = before;
-  __syncthreads();
-  for (int d = 128; d >= 1; d >>= 1) {
-    if (tid < d) part[tid] += part[tid + d];
-    __syncthreads();
-  }
-  const long long my_start = part[0];
-  __syncthreads();
-  part[tid] = all;
-  __syncthreads();
-  for (int d = 128; d >= 1; d >>= 1) {
-    if (tid < d) part[tid] += part[tid + d];
-    __syncthreads();
-  }
-  const long long total = part[0];
-  const int n = len(b);
-  int kb = kk[b];
+struct SamplePlan {
+  int ns, rank;
+};
+__device__ __forceinline__ SamplePlan plan_sample(const Shape& s, int n, int kb, int ns_max, int list_cap) {
   kb = kb < 0 ? 0 : (kb > s.kmax ? s.kmax : kb);
   kb = kb < n ? kb : n;
   // The sample and the rank r of the sample score that becomes the threshold.  With p = k / n the rows of the whole
@@ -84,26 +51,95 @@ __global__ __launch_bounds__(256) void k_dense_prep(Shape s, const int32_t* __re
   r = r < 1 ? 1 : r;
   r = r > s.kmax ? s.kmax : r;
   r = r > ns ? ns : r;
-  if (tid == 0) {
-    x_cnt[bg] = n;
-    x_start[bg] = my_start;
-    if (bg == n_groups - 1) x_start[n_groups] = total;
-    x_nsg[bg] = ns;
-    if (g == 0) {
-      x_ns[b] = ns;
-      x_rank[b] = r;
-    }
-  }
-  int32_t* out = sample + (int64_t)bg * s.cand_cap;
-  for (int i = tid; i < ns; i += 256) out[i] = (int)(((long long)i * n) / ns);
+  return SamplePlan{ns, r};
 }
 
-hipError_t launch_dense_prep(const Shape& s, const int32_t* seq_lens, const int32_t* k, int ns_max, int list_cap, int32_t* x_cnt,
-                             int64_t* x_start, int32_t* x_nsg, int32_t* x_ns, int32_t* x_rank, int32_t* sample,
-                             hipStream_t st) {
-  hipLaunchKernelGGL(k_dense_prep, dim3(s.B * s.Hkv), dim3(256), 0, st, s, seq_lens, k, ns_max, list_cap, x_cnt, x_start, x_nsg,
-                     x_ns, x_rank, sample);
-  return hipGetLastError();
+// Step 1, the scores [B, Hq, ns] of the samples, and with them, by the first workgroup of every group, what the next steps need: its
+// rows (x_cnt) and its place on the line of all rows (x_start, with the line's length behind), of every request the length of its
+// samples and the rank (x_ns, x_rank).  grid (workgroups per group, B*Hkv).  (As a kernel before, which listed the sample rows, the
+// set-up took 5.2 us and a boundary: exact Top-k of 8 x 64K with its attention 207.4 -> 203.4.)
+template <int G, bool kPaged, int kKind>
+__global__ __launch_bounds__(kScoreThreads) void k_sample_score(
+    Shape s, const float* __restrict__ q, const void* __restrict__ K, int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage pg,
+    const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ kk, int ns_max, int list_cap, int32_t* __restrict__ x_cnt,
+    int64_t* __restrict__ x_start, int32_t* __restrict__ x_ns, int32_t* __restrict__ x_rank, float* __restrict__ score,
+    int64_t score_stride, float scale, int32_t* __restrict__ flags) {
+  request_arguments<decltype(&k_sample_score<G, kPaged, kKind>)>();
+  const int bg = blockIdx.y, b = (int)((uint32_t)bg / (uint32_t)s.Hkv), g = bg - b * s.Hkv;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int j = lane & 15, kb = lane >> 4;
+  auto len = [&](int bb) {
+    const int n = seq_lens[bb];
+    return n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
+  };
+  const int n = len(b);
+  const SamplePlan plan = plan_sample(s, n, kk[b], ns_max, list_cap);
+  if (blockIdx.x == 0 && wave == 0) {
+    int64_t before = 0, all = 0;                            // rows of a head
+    for (int bb = lane; bb < s.B; bb += 64) {
+      const int64_t n_b = len(bb);
+      before += bb < b ? n_b : 0;
+      all += n_b;
+    }
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      before += __shfl_xor(before, d);
+      all += __shfl_xor(all, d);
+    }
+    if (lane == 0) {
+      x_cnt[bg] = n;
+      x_start[bg] = before * s.Hkv + (int64_t)g * n;
+      if (bg == 0) x_start[s.B * s.Hkv] = all * s.Hkv;
+      if (g == 0) {
+        x_ns[b] = plan.ns;
+        x_rank[b] = plan.rank;
+      }
+    }
+  }
+  const int first = ((int)blockIdx.x * 4 + wave) * kRowsPerWaveIter;
+  if (first >= plan.ns) return;
+  using Op = typename KTile<kKind>::Operand;
+  Op A[4];
+  report_q_range(load_query_operand(A, q, (int64_t)b * s.Hq + (int64_t)g * G, G, j, kb), flags);
+  const char* Kbg = static_cast<const char*>(K) + RowMap<kPaged>::base(b, g, stride_b, stride_h) * KTile<kKind>::kElemBytes;
+  // row i of the sample: i n / ns, rounded down (the product is exact, and no quotient lies so near below a whole number that it would
+  // be rounded up to it)
+  score_slots_mfma<kPaged, kKind>(A, Kbg, pg, b, stride_b, stride_n, [&](int i) { return (int)((double)i * (double)n / (double)plan.ns); }, n,
+                                  plan.ns, first, (int)gridDim.x * 4 * kRowsPerWaveIter,
+                                  score + ((int64_t)b * s.Hq + (int64_t)g * G + kb) * score_stride, kb < G, scale);
+}
+
+hipError_t launch_sample_score(const Shape& s, const float* q, const KvView& kv, const int32_t* k, int ns_max, int list_cap,
+                               int32_t* x_cnt, int64_t* x_start, int32_t* x_ns, int32_t* x_rank, float* score, int64_t score_stride,
+                               int32_t* flags, hipStream_t st) {
+  const int most = ns_max < s.cand_cap ? ns_max : s.cand_cap, groups = s.B * s.Hkv;
+  const int tiles = (most + 4 * kRowsPerWaveIter - 1) / (4 * kRowsPerWaveIter), want = (1024 + groups - 1) / groups;   // as launch_group_score
+  const dim3 grid(tiles < want ? tiles : want, groups);
+  const int kind = kv.k_fp8 ? kKindFp8 : (kv.f16 ? kKindF16 : kKindBf16);
+  const bool paged = kv.page.table != nullptr;
+  hipError_t e = hipErrorInvalidValue;
+  auto launch = [&](auto heads, auto pages, auto form) {
+    constexpr int G = decltype(heads)::value, kKind = decltype(form)::value;
+    constexpr bool kPaged = decltype(pages)::value;
+    if (s.G != G || paged != kPaged || kind != kKind) return;
+    hipLaunchKernelGGL((k_sample_score<G, kPaged, kKind>), grid, dim3(kScoreThreads), 0, st, s, q, kv.k, kv.stride_b, kv.stride_h,
+                       kv.stride_n, kv.page, kv.seq_lens, k, ns_max, list_cap, x_cnt, x_start, x_ns, x_rank, score, score_stride,
+                       0.08838834764831845f /* 1/sqrt(128) */, flags);
+    e = hipGetLastError();
+  };
+  auto of_kinds = [&](auto heads, auto pages) {
+    launch(heads, pages, std::integral_constant<int, kKindBf16>{});
+    launch(heads, pages, std::integral_constant<int, kKindFp8>{});
+    launch(heads, pages, std::integral_constant<int, kKindF16>{});
+  };
+  auto of_heads = [&](auto heads) {
+    of_kinds(heads, std::false_type{});
+    of_kinds(heads, std::true_type{});
+  };
+  of_heads(std::integral_constant<int, 1>{});
+  of_heads(std::integral_constant<int, 2>{});
+  of_heads(std::integral_constant<int, 4>{});
+  return e;
 }
 
 }  // namespace lfps

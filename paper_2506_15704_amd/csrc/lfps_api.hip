@@ -47,7 +47,6 @@ struct lfps_ctx {
   // exact Top-k baseline in its filtered form (x_fast): the dense rows on the line, the sample and its rank
   int x_fast;
   int32_t* x_cnt;      // [B, Hkv] rows of each group
-  int32_t* x_nsg;      // [B, Hkv] sample rows of each group
   int32_t* x_ns;       // [B] the same per request
   int32_t* x_rank;     // [B] rank of the sample score taken as threshold
   int64_t* x_start;    // [B*Hkv + 1] place of each group on the line of all rows, then the line's length
@@ -176,7 +175,7 @@ int check_config(const lfps_config* c, Sizes* z, char* err, size_t errn) {
   z->tsla_b = c->table_mode ? align256(heads * c->max_seq_len * 8) : 0;
   z->tstate_b = c->table_mode ? align256(heads * kTableStateDoubles * 8) : 0;
   z->tflag_b = c->table_mode ? align256(heads * z->flag_words * 4) : 0;
-  z->x_b = 3 * z->count_b + 2 * align256((int64_t)c->batch * 4) + align256(((int64_t)c->batch * c->n_kv_heads + 1) * 8) + z->thr_b;
+  z->x_b = z->count_b + 2 * align256((int64_t)c->batch * 4) + align256(((int64_t)c->batch * c->n_kv_heads + 1) * 8) + z->thr_b;
   z->aux_b = prior_scratch_bytes(s);
   z->hist = c->table_mode ? plan_table_history(s) : HistPlan{};
   if (c->table_mode && table_init_scratch_bytes(s, z->hist) > z->aux_b) z->aux_b = table_init_scratch_bytes(s, z->hist);
@@ -359,11 +358,10 @@ int lfps_create(const lfps_config* cfg, lfps_ctx** out) {
   {
     const int64_t per_b = align256((int64_t)cfg->batch * 4);
     c->x_cnt = (int32_t*)p;
-    c->x_nsg = (int32_t*)(p + z.count_b);
-    c->x_ns = (int32_t*)(p + 2 * z.count_b);
-    c->x_rank = (int32_t*)(p + 2 * z.count_b + per_b);
-    c->x_start = (int64_t*)(p + 2 * z.count_b + 2 * per_b);
-    c->thr_x = (float*)(p + 2 * z.count_b + 2 * per_b + align256(((int64_t)cfg->batch * cfg->n_kv_heads + 1) * 8));
+    c->x_ns = (int32_t*)(p + z.count_b);
+    c->x_rank = (int32_t*)(p + z.count_b + per_b);
+    c->x_start = (int64_t*)(p + z.count_b + 2 * per_b);
+    c->thr_x = (float*)(p + z.count_b + 2 * per_b + align256(((int64_t)cfg->batch * cfg->n_kv_heads + 1) * 8));
     p += z.x_b;
   }
   c->aux = p;
@@ -692,12 +690,9 @@ int lfps_exact_topk(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int3
     Shape sd = s;
     sd.cand_cap = s.Lcap;                 // the "candidates" of the dense pass are all rows of a group
     int64_t* x_total = ctx->x_start + (int64_t)s.B * s.Hkv;
-    hipError_t e = launch_dense_prep(s, v.seq_lens, k, kExactSampleRows, filter_list_cap(s), ctx->x_cnt, ctx->x_start, ctx->x_nsg, ctx->x_ns,
-                                     ctx->x_rank, ctx->cand, st);
-    if (e != hipSuccess) return fail(ctx, LFPS_EHIP, "lfps_exact_topk (set-up)", e);
     LAUNCH(ctx, LFPS_KERNEL_GATHER_SCORE, st,
-           launch_group_score(s, ctx->cfg.kv_dtype, q, v, ctx->cand, ctx->x_nsg, ctx->score, s.score_stride, ctx->flags,
-                              st));
+           launch_sample_score(s, q, v, k, kExactSampleRows, filter_list_cap(s), ctx->x_cnt, ctx->x_start, ctx->x_ns, ctx->x_rank, ctx->score,
+                               s.score_stride, ctx->flags, st));
     LAUNCH(ctx, LFPS_KERNEL_SELECT, st,      // the rank-th best sample score of every head -> thr_x (the rows go to scratch)
            launch_select(s, ctx->score, s.score_stride, nullptr, ctx->x_ns, ctx->x_rank, ctx->slot, nullptr, ctx->thr_x,
                          nullptr, nullptr, st));

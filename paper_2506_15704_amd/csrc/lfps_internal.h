@@ -169,15 +169,13 @@ hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, 
                                        const float* q, int32_t* flags, const KvView& kv, float* out,
                                        hipStream_t st);   // out == NULL: select only
 
-// Exact Top-k baseline, set-up of its filtered dense pass (exact_topk.hip): every group's rows 0..n_b-1 laid on the
-// line (x_cnt, x_start, x_start[B*Hkv] = the line's length), a strided sample of at most ns_max rows per group
-// (sized for the select's list capacity list_cap)
-// (sample [B, Hkv, cand_cap], x_nsg [B*Hkv] / x_ns [B] its length) and the rank x_rank [B] whose sample score is
-// taken as the threshold.
-hipError_t launch_dense_prep(const Shape& s, const int32_t* seq_lens, const int32_t* k, int ns_max, int list_cap,
-                             int32_t* x_cnt,
-                             int64_t* x_start, int32_t* x_nsg, int32_t* x_ns, int32_t* x_rank, int32_t* sample,
-                             hipStream_t st);
+// Exact Top-k baseline, the first step of its filtered form (exact_topk.hip): a strided sample of at most ns_max rows per group (and
+// no more than cand_cap; sized for the select's list capacity list_cap) is scored (score [B, Hq, score_stride]; x_ns [B] its
+// length), every group's rows 0..n_b-1 are laid on the line (x_cnt, x_start, x_start[B*Hkv] = the line's length), and x_rank [B] is
+// the rank whose sample score is taken as the threshold.
+hipError_t launch_sample_score(const Shape& s, const float* q, const KvView& kv, const int32_t* k, int ns_max, int list_cap,
+                               int32_t* x_cnt, int64_t* x_start, int32_t* x_ns, int32_t* x_rank, float* score, int64_t score_stride,
+                               int32_t* flags, hipStream_t st);
 // From the full score rows [B, Hq, score_stride] over cand, every head.
 hipError_t launch_select_attend(const Shape& s, int dtype, const float* score, int64_t score_stride, const int32_t* cand,
                                 const int32_t* cand_count, const int32_t* k, int32_t* topk_idx, float* topk_score,

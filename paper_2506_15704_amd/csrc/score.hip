@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_group_score_bf16(Shape s, con
   if constexpr (!GATHER) {
     if (tops && select_takes_tops(s, n, kk[b])) my_tops = tops + ((int64_t)b * s.Hq + (int64_t)g * G + kb) * (score_stride >> 4);
   }
-  score_slots_mfma<kPaged, kKind, !GATHER>(A, Kbg, pg, b, stride_b, stride_n, cbg, n, count, first,
+  score_slots_mfma<kPaged, kKind, !GATHER>(A, Kbg, pg, b, stride_b, stride_n, [&](int slot) { return GATHER ? cbg[slot] : slot; }, n, count, first,
                                            (int)gridDim.x * 4 * kRowsPerWaveIter, sc, kb < G, scale, my_tops);
 }
 

@@ -248,16 +248,15 @@ struct StreamTile {
 
 // Scores of the slots first .. first+63, first+step .. first+step+63, ... (below count) of one KV group, by one wave:
 // lane (j, kb) = (lane & 15, lane >> 4) loads the chunks of K that lane group kb owns and ends up holding head kb's
-// score of slot base + 16 t + j.  cbg: the group's candidate list (slot -> row position), or NULL when slot = row
-// position.  A slot whose position lies outside [0, n) reads row 0 and scores -inf: it ranks below every row.
+// score of slot base + 16 t + j.  row_at(slot): its row position.  A slot whose position lies outside [0, n) reads row 0 and scores -inf: it ranks below every row.
 // The row ids of the next visit are fetched, and the scores of the previous visit stored, right after this visit's
 // loads are issued.  sc: the score row of head kb (ignored by lanes with store == false).
 // tops (or NULL): receives the largest score of every 16 slots, as the select orders them (a NaN above all); first and step are
 // multiples of 64 then.
-template <bool kPaged, int kKind, bool kTops = false>
+template <bool kPaged, int kKind, bool kTops = false, typename RowAt>
 __device__ __forceinline__ void score_slots_mfma(const typename KTile<kKind>::Operand (&A)[4], const char* Kbg,
                                                  const KvPage& pg, int b, int64_t stride_b, int64_t stride_n,
-                                                 const int32_t* __restrict__ cbg, int n, int count, int first, int step,
+                                                 RowAt row_at, int n, int count, int first, int step,
                                                  float* __restrict__ sc, bool store, float scale,
                                                  float* __restrict__ tops = nullptr) {
   using Rows = RowMap<kPaged>;
@@ -271,7 +270,7 @@ __device__ __forceinline__ void score_slots_mfma(const typename KTile<kKind>::Op
   float pv[4] = {0.f, 0.f, 0.f, 0.f};   // scores of the previous visit, not yet stored
   int pbase = -1;
   int my_row = -1;
-  if (first + lane < count) my_row = cbg ? cbg[first + lane] : first + lane;
+  if (first + lane < count) my_row = row_at(first + lane);
   int my_ok = valid(my_row);
   my_row = physical(my_row);
   for (int base = first; base < count; base += step) {
@@ -285,7 +284,7 @@ __device__ __forceinline__ void score_slots_mfma(const typename KTile<kKind>::Op
     }
     const int nb = base + step;
     int next_row = -1;
-    if (nb + lane < count) next_row = cbg ? cbg[nb + lane] : nb + lane;
+    if (nb + lane < count) next_row = row_at(nb + lane);
     const int next_ok = valid(next_row);
     next_row = physical(next_row);
     if (pbase >= 0) {

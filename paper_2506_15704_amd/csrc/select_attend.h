@@ -266,7 +266,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     Op A[4];
     report_q_range(load_query_operand(A, q, (int64_t)b * s.Hq + (int64_t)g * s.G, s.G, lane & 15, lane >> 4), flags);
     const char* Kbg = static_cast<const char*>(K) + Rows::base(b, g, stride_b, stride_h) * KTile<kKind>::kElemBytes;
-    score_slots_mfma<kPaged, kKind>(A, Kbg, page, b, stride_b, stride_n, cbg, n, c, wv * kRowsPerWaveIter,
+    score_slots_mfma<kPaged, kKind>(A, Kbg, page, b, stride_b, stride_n, [&](int e) { return cbg ? cbg[e] : e; }, n, c, wv * kRowsPerWaveIter,
                                     kWaves * kRowsPerWaveIter, sc, (lane >> 4) == at.in_group, scale);
   }
   __syncthreads();                                  // seg_off, or the score row, is complete before anyone reads it
