@@ -88,7 +88,10 @@ __device__ __forceinline__ float float_below(double t) {
 
 // grid (chunks, B*Hq).  Each wave tests 64 consecutive positions per iteration; the ballots are the
 // flag words.  A table entry is g * A(i); the comparison  g * A > threshold  is made as  A > threshold / g
-// with the quotient (fp64) rounded down to fp32 once per head.
+// with the quotient (fp64) rounded down to fp32 once per workgroup: by one wave, the vertical table's in its even lanes
+// and the slash table's in its odd ones, behind the requests for the first rows.  Bound by the bytes of both tables, of
+// which 256 heads x 32K rows (a fifth of the heads bypassed) take 54 MB: 11.8 us = 4.6 TB/s.  14.8 us with the quotients
+// found by every wave, one table after the other and before the requests, and a branch around each load and comparison.
 __global__ __launch_bounds__(kTabThreads) void k_table_flags(Shape s, const float* __restrict__ tab_ver,
                                                              const float* __restrict__ tab_sla,
                                                              const double* __restrict__ state,
@@ -98,12 +101,25 @@ __global__ __launch_bounds__(kTabThreads) void k_table_flags(Shape s, const floa
                                                              const int32_t* __restrict__ gate) {
   request_arguments<decltype(&k_table_flags)>();
   __shared__ uint32_t w0[kFlagIters * kTabThreads / 32], wm[kFlagIters * kTabThreads / 32];
+  __shared__ float limits[4];                             // threshold and mean of the vertical, then of the slash table
   const int bh = blockIdx.y, b = bh / s.Hq;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const double* st = state + (int64_t)bh * kTableStateDoubles;
+  // everything that depends on the head alone in one round trip (the gate's word, too: without a gate any other is read)
+  const int gate_word = *(gate ? gate + bh : seq_lens + b);
+  const double moves = st[TS_CNT], g = st[TS_G], flat_n = st[TS_FLAT_N];
   int n = seq_lens[b];
+  const bool slash = lane & 1;
+  double M[4], flat = 0.0;
+  if (wave == 0) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) M[p] = st[(slash ? TS_MS : TS_MV) + p];
+    flat = st[slash ? TS_FLAT_S : TS_FLAT_V];
+  }
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   const int n_round = (n + 63) & ~63;                     // whole flag words up to the end of the sequence
-  if (gate && gate[bh] != 0) {                            // bypassed head: it proposes no candidates
+  asm volatile("" ::"s"(moves), "s"(g), "s"(flat_n));     // (the compiler would ask for them behind the branch)
+  if (gate && gate_word != 0) {                           // bypassed head: it proposes no candidates
     const int w_begin = (blockIdx.x * rows_per_block) >> 5;
     const int w_end = ((blockIdx.x + 1) * rows_per_block < n_round ? (blockIdx.x + 1) * rows_per_block : n_round) >> 5;
     for (int w = w_begin + tid; w < w_end; w += kTabThreads) {
@@ -112,30 +128,29 @@ __global__ __launch_bounds__(kTabThreads) void k_table_flags(Shape s, const floa
     }
     return;
   }
-  const double* st = state + (int64_t)bh * kTableStateDoubles;
-  const double g = st[TS_G];
-  const int cnt = clamp_count(st[TS_CNT], s.Lcap);
-  float tau_v, tau_s, mean_v, mean_s;
-  {
-    const double N = (double)(n - s.n_sink > 0 ? n - s.n_sink : 0);
-    double Mv[4], Ms[4], t, m;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      Mv[p] = st[TS_MV + p];
-      Ms[p] = st[TS_MS + p];
-    }
-    const bool same_n = st[TS_FLAT_N] == N;
-    thresholds_from_moments(Mv, N, a, st[TS_FLAT_V] != 0.0 && (same_n || Mv[1] == 0.0), &t, &m);
-    tau_v = float_below(t / g);
-    mean_v = float_below(m / g);
-    thresholds_from_moments(Ms, N, a, st[TS_FLAT_S] != 0.0 && (same_n || Ms[1] == 0.0), &t, &m);
-    tau_s = float_below(t / g);
-    mean_s = float_below(m / g);
-  }
+  const int cnt = clamp_count(moves, s.Lcap);
   const float* ver = tab_ver + (int64_t)bh * s.Lcap;
   const float* sla = tab_sla + (int64_t)bh * 2 * s.Lcap + (s.Lcap - cnt);
   uint32_t* o0 = f0 + (int64_t)bh * flag_words;
   uint32_t* om = fm + (int64_t)bh * flag_words;
+  float tau_v = 0.f, tau_s = 0.f, mean_v = 0.f, mean_s = 0.f;
+  auto find_limits = [&]() {
+    if (wave == 0) {
+      const double N = (double)(n - s.n_sink > 0 ? n - s.n_sink : 0);
+      double t, m;
+      thresholds_from_moments(M, N, a, flat != 0.0 && (flat_n == N || M[1] == 0.0), &t, &m);
+      const float tau = float_below(t / g), mean = float_below(m / g);
+      if (lane < 2) {
+        limits[2 * lane] = tau;
+        limits[2 * lane + 1] = mean;
+      }
+    }
+    __syncthreads();
+    tau_v = limits[0];
+    mean_v = limits[1];
+    tau_s = limits[2];
+    mean_s = limits[3];
+  };
   // A workgroup covers rows_per_block consecutive positions in passes of kFlagIters * 256; in a pass wave w
   // takes every fourth 64-position word pair, and all its loads are issued before the first comparison
   // (fixed trip count, fully unrolled).  The flag words of a pass meet in LDS and leave as two coalesced stores.
@@ -146,18 +161,21 @@ __global__ __launch_bounds__(kTabThreads) void k_table_flags(Shape s, const floa
     const int begin = pass + wave * 64;
     float av[kFlagIters], as[kFlagIters];
 #pragma unroll
-    for (int it = 0; it < kFlagIters; ++it) {
-      const int i = begin + it * kTabThreads + lane;
-      const bool in = i >= s.n_sink && i < n;
-      av[it] = in ? ver[i] : 0.f;
-      as[it] = in ? sla[i] : 0.f;
+    for (int it = 0; it < kFlagIters; ++it) {             // (n >= 1 here; what lies outside [n_sink, n) is masked below)
+      const int i = begin + it * kTabThreads + lane, at = i < n ? i : n - 1;
+      av[it] = ver[at];
+      as[it] = sla[at];
+    }
+    if (pass == block_begin) {
+      __builtin_amdgcn_sched_barrier(0);
+      find_limits();
     }
 #pragma unroll
     for (int it = 0; it < kFlagIters; ++it) {
       const int i = begin + it * kTabThreads + lane;
-      const bool in = i >= s.n_sink && i < n;
-      const uint64_t m0 = __ballot(in && (av[it] > tau_v || as[it] > tau_s));
-      const uint64_t mm = __ballot(in && (av[it] > mean_v || as[it] > mean_s));
+      const uint64_t in = __ballot(i >= s.n_sink) & __ballot(i < n);
+      const uint64_t m0 = (__ballot(av[it] > tau_v) | __ballot(as[it] > tau_s)) & in;
+      const uint64_t mm = (__ballot(av[it] > mean_v) | __ballot(as[it] > mean_s)) & in;
       if (lane == 0) {
         const int w = (it * kTabThreads + wave * 64) >> 5;
         w0[w] = (uint32_t)m0;

@@ -123,6 +123,35 @@ def test_table_candidates_from_imported_tables(r, n_recent, n_sink, a):
     ctx.close()
 
 
+@pytest.mark.parametrize("B,Lcap,n_sink", [(6, 2112, 0), (6, 2112, 7), (64, 40000, 4)])
+def test_scan_at_the_edges_of_words_and_passes(B, Lcap, n_sink):
+    """Lengths around a flag word, a pass of the scan (2048 rows) and, with many heads, a workgroup's several passes; a scan
+    reads nothing behind a request's rows and flags nothing there."""
+    from paper_2506_15704_amd.binding import Lfps
+    rng = np.random.default_rng(Lcap + n_sink)
+    Hq, Hkv, a, r = 32, 8, 0.2, 1
+    edges = [1, 8, 63, 64, 65, 2048] if B == 6 else [40000, 20479, 20481, 6145] + [1] * (B - 4)
+    n = np.array(edges, dtype=np.int32)
+    ver, sla = (np.zeros((B, Hq, Lcap), dtype=np.float32) for _ in range(2))
+    for b in range(min(B, 6)):
+        for T in (ver, sla):
+            T[b, :, n_sink:n[b]] = rng.gamma(0.05, size=(Hq, max(0, n[b] - n_sink))).astype(np.float32)
+    ctx = Lfps(batch=B, max_seq_len=Lcap, max_k=32, radius=r, n_recent=0, n_sink=n_sink, table_mode=True, table_decay=0.95,
+               table_a=a, cand_cap=Lcap)
+    ctx.lfps_tables_import(dev(ver), dev(sla), dev(n))
+    cand = torch.full((B, Hkv, ctx.cand_cap), -7, dtype=torch.int32, device=DEV)
+    cnt = torch.zeros((B, Hkv), dtype=torch.int32, device=DEV)
+    ctx.lfps_table_candidates(dev(n), cand, cnt)
+    torch.cuda.synchronize()
+    cand, cnt = cand.cpu().numpy(), cnt.cpu().numpy()
+    for b in range(6):
+        for g in (0, Hkv - 1):
+            t64 = [(ver[b, 4 * g + h].astype(np.float64), sla[b, 4 * g + h].astype(np.float64)) for h in range(4)]
+            want = tor.group_candidates(t64, int(n[b]), a, r, 0, n_sink)
+            _assert_candidates(cand[b, g, : cnt[b, g]], want, t64, int(n[b]), a, r, n_sink, f"b={b} g={g}")
+    ctx.close()
+
+
 def _oracle_update_all(ver, sla, n, idx, sc, k, gamma, n_sink):
     B, Hq, Lcap = ver.shape
     nv, ns = np.zeros((B, Hq, Lcap)), np.zeros((B, Hq, Lcap))
