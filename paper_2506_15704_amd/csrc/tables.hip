@@ -347,8 +347,44 @@ __global__ __launch_bounds__(kTabThreads) void k_table_update(Shape s, float* __
 // The same for the library's own Top-k (distinct positions, at most kUpdateThreads * kUpdateEach of them): a thread reads
 // its entries and the table values they change at once and keeps them, a plain store replaces the atomic addition, and
 // the eight moments meet in one reduction.  The kernel is a chain of latencies (256 heads, k = 1024): 17.4 us with four
-// entries per thread read three times and ten reductions one after the other, 8.2 us this way.
+// entries per thread read three times and ten reductions one after the other, 8.2 us with eight sums each over all lanes of a
+// wave, 6.7 us with the lanes sharing the sums out (wave_sum_of_8) and the old moments asked for at the start.
 constexpr int kUpdateThreads = 1024, kUpdateEach = 4;
+
+// The value of lane ^ 4 (DPP: lanes 4 to 7 and 12 to 15 from below, the others from above).
+__device__ __forceinline__ double lane_xor4(double x) {
+  auto half = [](int v) {
+    const int t = __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xa, false);      // row_shr:4
+    return __builtin_amdgcn_update_dpp(t, v, 0x104, 0xf, 0x5, false);             // row_shl:4
+  };
+  return __hiloint2double(half(__double2hiint(x)), half(__double2loint(x)));
+}
+__device__ __forceinline__ double lane_xor2(double x) {
+  auto half = [](int v) { return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, false); };      // quad_perm [2,3,0,1]
+  return __hiloint2double(half(__double2hiint(x)), half(__double2loint(x)));
+}
+// Eight sums over a wave; lanes 2 p and 2 p + 1 of every sixteen return sum p.  Lanes 8, 4 and 2 apart share the values out while they
+// add, so there are ten additions instead of 48, in the order of wave_sum.
+__device__ __forceinline__ double wave_sum_of_8(const double (&d)[8], int lane) {
+  double a[4], c[2];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const double keep = lane & 8 ? d[4 + p] : d[p], give = lane & 8 ? d[p] : d[4 + p];
+    a[p] = keep + row16_rotate<8>(give);
+  }
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const double keep = lane & 4 ? a[2 + p] : a[p], give = lane & 4 ? a[p] : a[2 + p];
+    c[p] = keep + lane_xor4(give);
+  }
+  const double keep = lane & 2 ? c[1] : c[0], give = lane & 2 ? c[0] : c[1];
+  double v = keep + lane_xor2(give);
+  auto swap = [](int x) { return __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xf, 0xf, false); };      // quad_perm [1,0,3,2]
+  v += __hiloint2double(swap(__double2hiint(v)), swap(__double2loint(v)));
+  v += __shfl_xor(v, 16);
+  return v + __shfl_xor(v, 32);
+}
+
 template <int kEach>
 __global__ __launch_bounds__(kUpdateThreads) void k_table_update_own(Shape s, float* __restrict__ tab_ver,
                                                                      float* __restrict__ tab_sla,
@@ -377,6 +413,8 @@ __global__ __launch_bounds__(kUpdateThreads) void k_table_update_own(Shape s, fl
   }
   double* st = state + (int64_t)bh * kTableStateDoubles;
   const double g = st[TS_G], moves = st[TS_CNT];
+  const int at_moment = (tid & 4 ? TS_MS : TS_MV) + (tid & 3);
+  const double old_moment = st[at_moment];                   // (of threads 0 to 7)
   int n = seq_lens[b];
   int kb = kk[b];
   if (gate && gate[bh] != 0) return;                        // bypassed head: Eq. 10 is skipped for it
@@ -461,20 +499,15 @@ __global__ __launch_bounds__(kUpdateThreads) void k_table_update_own(Shape s, fl
       }
     }
   }
-#pragma unroll
-  for (int p = 0; p < 8; ++p) d[p] = wave_sum(d[p]);
+  const double moment = wave_sum_of_8(d, lane);
   __syncthreads();                                           // everybody has read red[][0]
-  if (lane == 0) {
-#pragma unroll
-    for (int p = 0; p < 8; ++p) red[wave][p] = d[p];
-  }
+  if (lane < 16 && !(lane & 1)) red[wave][lane >> 1] = moment;
   __syncthreads();
   if (tid < 8) {                                             // thread p: moment p & 3 of the vertical, then of the slash table
     double sum = 0.0, gp = 1.0;
     for (int w = 0; w < NW; ++w) sum += red[w][tid];
     for (int p = 0; p <= (tid & 3); ++p) gp *= gamma;
-    double* M = st + (tid < 4 ? TS_MV + tid : TS_MS + tid - 4);
-    *M = gp * *M + sum;
+    st[at_moment] = gp * old_moment + sum;
     if (tid == 0) {
       st[TS_G] = g1;
       st[TS_CNT] = (double)(cnt + 1);
