@@ -849,7 +849,9 @@ __global__ __launch_bounds__(kBatchThreads, 2) void k_batch_apply(
 
 // One query (s = 1): its dot products are few enough to store (4 bytes per row and head beside 2 D / G of K), so the
 // second pass over K is replaced by this one over them.  Vertical and slash table are equal then.  Writes the tables
-// whole, and the moments of its rows as k_table_moments does.  grid (chunks, B*Hq), 256 threads.
+// whole, and the moments of its rows as k_table_moments does.  Bound by the stores (12 bytes per row and head) and, nearly as much, by
+// its instructions: 256 heads x 32K rows 28.2 us = 4.8 TB/s, 32.7 with a branch around every load and store also where a chunk lies in
+// the tables whole.  grid (chunks, B*Hq), 256 threads.
 constexpr int kMomentRows = 2048;
 __global__ __launch_bounds__(256) void k_hist_apply_one(Shape s, float* __restrict__ tab_ver, float* __restrict__ tab_sla,
                                                         const float* __restrict__ dots, int64_t dots_stride,
@@ -862,31 +864,41 @@ __global__ __launch_bounds__(256) void k_hist_apply_one(Shape s, float* __restri
   int n = seq_lens[b];
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   constexpr int U = kMomentRows / 256;
+  const int row0 = blockIdx.x * kMomentRows;
+  const bool whole = row0 >= s.n_sink && row0 + kMomentRows <= n;     // (then n <= Lcap covers the stores, too)
   float x[U];
   bool in[U];
+  const float* from = dots + (int64_t)bh * dots_stride + row0;
+  float* ver = tab_ver + (int64_t)bh * s.Lcap + row0;
+  float* sla = tab_sla + (int64_t)bh * 2 * s.Lcap + row0;
+  float* fresh = sla + s.Lcap;
+  auto rest = [&](auto all) {
+    constexpr bool kAll = decltype(all)::value;
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int i = blockIdx.x * kMomentRows + u * 256 + tid;
-    in[u] = i >= s.n_sink && i < n;
-    x[u] = in[u] ? dots[(int64_t)bh * dots_stride + i] : kNoScore;
-  }
-  float m;
-  double norm;
-  merge_hist<64>(part_m, part_l, ((int64_t)b * s.Hkv + g) * blocks * (kHistBatch * s.G) + h % s.G, kHistBatch * s.G,
-                 blocks, tid & 63, gamma, 1, m, norm, [](float x) { return exp_below<true>(x); });
-  const float hi = (float)norm, lo = (float)(norm - (double)hi);
-  float* ver = tab_ver + (int64_t)bh * s.Lcap;
-  float* sla = tab_sla + (int64_t)bh * 2 * s.Lcap;
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int i = blockIdx.x * kMomentRows + u * 256 + tid;
-    x[u] = in[u] ? weigh(exp_below<true>(x[u] - m), hi, lo) : 0.f;
-    if (i < s.Lcap) {
-      ver[i] = x[u];
-      sla[s.Lcap + i] = x[u];
-      sla[i] = 0.f;
+    for (int u = 0; u < U; ++u) {
+      const uint32_t e = u * 256 + tid;
+      const int i = row0 + (int)e;
+      in[u] = kAll || (i >= s.n_sink && i < n);
+      x[u] = in[u] ? from[e] : kNoScore;
     }
-  }
+    float m;
+    double norm;
+    merge_hist<64>(part_m, part_l, ((int64_t)b * s.Hkv + g) * blocks * (kHistBatch * s.G) + h % s.G, kHistBatch * s.G,
+                   blocks, tid & 63, gamma, 1, m, norm, [](float x) { return exp_below<true>(x); });
+    const float hi = (float)norm, lo = (float)(norm - (double)hi);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t e = u * 256 + tid;
+      x[u] = in[u] ? weigh(exp_below<true>(x[u] - m), hi, lo) : 0.f;
+      if (kAll || row0 + (int)e < s.Lcap) {
+        ver[e] = x[u];
+        fresh[e] = x[u];
+        sla[e] = 0.f;
+      }
+    }
+  };
+  if (whole) rest(std::true_type{});
+  else rest(std::false_type{});
   moments_of_chunk<U>(x, x, in, part + ((int64_t)bh * gridDim.x + blockIdx.x) * 12);
 }
 
