@@ -52,7 +52,7 @@ __device__ __forceinline__ float candidate_rows(const Shape& s, const int32_t* s
 template <int G, bool kPaged, int kKind, bool kTables, bool kWide>
 __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
     Shape s, const float* __restrict__ q, const void* __restrict__ K, int64_t stride_b, int64_t stride_h,
-    int64_t stride_n, KvPage page, const int32_t* __restrict__ seq_lens, RangeSource from,
+    int64_t stride_n, KvPage page, const int32_t* __restrict__ seq_lens, RangeSource from, const int32_t* __restrict__ kk,
     const float* __restrict__ thr_state, float margin, float* __restrict__ tau_out, const int32_t* __restrict__ skip_if,
     float* __restrict__ score, int32_t* __restrict__ slot_out,
     int64_t score_stride, int32_t* __restrict__ seg_count, int nseg, uint32_t* __restrict__ bitmap, int bitmap_words,
@@ -92,22 +92,24 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
         const int at = j0 + kScoreThreads * u;
         if (at >= s.kmax) break;                           // (uniform)
 #pragma unroll
-        for (int h = 0; h < G; ++h) ids[u][h] = at + tid < s.kmax ? pt[(int64_t)h * s.kmax + at + tid] : -1;
+        for (int h = 0; h < G; ++h) ids[u][h] = (pt + (int64_t)h * s.kmax)[at + tid < s.kmax ? at + tid : s.kmax - 1];
       }
     }
   };
   fetch(0);
   int n = seq_lens[b];
-  const int k_raw = kTables ? 0 : from.k[b];
-  const int64_t head0 = (int64_t)b * s.Hq + (int64_t)g * G;
-  const float thr = thr_state[head0 + (kb < G ? kb : 0)];
-  const bool skipped = skip_if && skip_if[head0 + (kb < G ? kb : 0)] != 0;     // bypassed head: nothing is kept for it
+  const int k_raw = kTables ? 0 : kk[b];
+  // (Scalar loads beside the entries.  Behind them, the budget as a vector load, each was a trip to memory of its own.)
+  asm volatile("" ::"s"(n), "s"(k_raw));
+  const int64_t head0 = (int64_t)b * s.Hq + (int64_t)g * G, my_head = head0 + (kb < G ? kb : 0);
+  const float thr = thr_state[my_head];
+  const int skip_word = *(skip_if ? skip_if + my_head : seq_lens);             // (no gate: any word)
   for (int w = tid; w < range_arg >> 5; w += kScoreThreads) {
     bm[w] = 0u;
     if constexpr (!kWide) break;
   }
   float all_rows = 0.f;
-  if (kWide && may_once) all_rows = candidate_rows(s, seq_lens, from.k);
+  if (kWide && may_once) all_rows = candidate_rows(s, seq_lens, kk);
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   // (a wide range is the request's part, not the context's: a batch of mixed lengths, or far below its capacity, keeps the chip full)
   const int range = kWide ? equal_ranges(n, gridDim.y) : range_arg, words = range >> 5;
@@ -135,10 +137,15 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
 #pragma unroll
       for (int h = 0; h < G; ++h) {
         const int64_t row = (head0 + h) * from.flag_words;
-        before[h] = w > 0 ? from.f0[row + w - 1] : 0u;
+        before[h] = from.f0[row + (w > 0 ? w - 1 : 0)];
         mid[h] = from.f0[row + w];
-        after[h] = w + 1 < W ? from.f0[row + w + 1] : 0u;
+        after[h] = from.f0[row + (w + 1 < W ? w + 1 : w)];
         mean[h] = from.fm[row + w];
+      }
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        before[h] = w > 0 ? before[h] : 0u;
+        after[h] = w + 1 < W ? after[h] : 0u;
       }
       uint32_t acc = 0u;
 #pragma unroll
@@ -230,7 +237,7 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
   const int cnt = __builtin_amdgcn_readfirstlane(total - c0 < per ? (total - c0 > 0 ? total - c0 : 0) : per);
   const int piece = 4 * (int)blockIdx.y + wave;
   const int out0 = geo.start(piece);                      // where its survivors go in the heads' rows
-  const int64_t head = head0 + (kb < G ? kb : 0);
+  const bool skipped = skip_if && skip_word != 0;         // bypassed head: nothing is kept for it
   const uint64_t nans = __ballot(kb < G && isnan(thr) && !skipped);
   auto leave = [&](int kept) {                           // (no store before the last load: a wait for that would wait for the store)
     for (int w = tid; w < words && (lo >> 5) + w < bitmap_words; w += kScoreThreads) {
@@ -238,8 +245,8 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
       if constexpr (!kWide) break;
     }
     if (j == 0 && kb < G) {
-      seg_count[head * nseg + piece] = cnt << 16 | kept;
-      if (piece == 0) tau_out[head] = thr - margin;
+      seg_count[my_head * nseg + piece] = cnt << 16 | kept;
+      if (piece == 0) tau_out[my_head] = thr - margin;
     }
   };
   if (cnt == 0 || nans) {
@@ -258,8 +265,8 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
   auto flush = [&]() {
     wave_lds_order();
     if (kb < G) {                                         // sixteen lanes write for a head
-      float* dsc = score + head * score_stride + out0 + run;
-      int32_t* dsl = slot_out + head * score_stride + out0 + run;
+      float* dsc = score + my_head * score_stride + out0 + run;
+      int32_t* dsl = slot_out + my_head * score_stride + out0 + run;
       for (int e = j; e < staged; e += 16) {
         dsc[e] = st_s[e];
         dsl[e] = lo + st_i[e];
@@ -409,7 +416,7 @@ hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, 
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(beside, (s.Lcap + range - 1) / range, groups / beside), dim3(kScoreThreads),
                        (size_t)(wide ? range / 8 : range * 2), st, s, q, kv.k, kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens,
-                       from, thr_state, margin, tau_out, skip_if, score, slot_out, score_stride, seg_count, nseg, bitmap, bitmap_words,
+                       from, from.k, thr_state, margin, tau_out, skip_if, score, slot_out, score_stride, seg_count, nseg, bitmap, bitmap_words,
                        range, 0.08838834764831845f /* 1/sqrt(128) */, flags, may_once);
     e = hipGetLastError();
   };
