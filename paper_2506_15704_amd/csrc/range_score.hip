@@ -17,7 +17,7 @@
 // every load instruction covers whole rows (StreamTile, here with ordinary loads).  With a lane's own 64 bytes of a row in four
 // loads, each of these touches 32 cache lines instead of 8, and with one tile per wave and eight to sixteen waves per CU all asking at
 // once the address unit was what the first rows waited for.  11.4 us with the entries of a Top-k row strided over the lanes and the
-// survivors of all heads written side by side.  (A stage of 160 survivors makes room for it at four workgroups per CU.)
+// survivors of all heads written side by side, 9.2 with length and budget asked for beside the Top-k entries.  (A stage of 160 survivors makes room for it at four workgroups per CU.)
 #include "candidates.h"
 #include "range_geometry.h"
 #include "score_mfma.h"
