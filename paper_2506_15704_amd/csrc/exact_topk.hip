@@ -57,7 +57,9 @@ __device__ __forceinline__ SamplePlan plan_sample(const Shape& s, int n, int kb,
 // Step 1, the scores [B, Hq, ns] of the samples, and with them, by the first workgroup of every group, what the next steps need: its
 // rows (x_cnt) and its place on the line of all rows (x_start, with the line's length behind), of every request the length of its
 // samples and the rank (x_ns, x_rank).  grid (workgroups per group, B*Hkv).  (As a kernel before, which listed the sample rows, the
-// set-up took 5.2 us and a boundary: exact Top-k of 8 x 64K with its attention 207.4 -> 203.4.)
+// set-up took 5.2 us and a boundary: exact Top-k of 8 x 64K with its attention 207.4 -> 203.4.)  One tile a wave, so what bounds it is
+// the time to the first rows: with whole rows an instruction (StreamTile) and the query split behind the requests 16.8 -> 13.9 us, 42 MB of
+// rows 6 KB apart, 204.9 -> 202.2 in all.  (Contiguous rows are better read the other way: exact Top-k of 1 x 32K 32.0 -> 32.4.)
 template <int G, bool kPaged, int kKind>
 __global__ __launch_bounds__(kScoreThreads) void k_sample_score(
     Shape s, const float* __restrict__ q, const void* __restrict__ K, int64_t stride_b, int64_t stride_h, int64_t stride_n, KvPage pg,
@@ -99,14 +101,17 @@ __global__ __launch_bounds__(kScoreThreads) void k_sample_score(
   const int first = ((int)blockIdx.x * 4 + wave) * kRowsPerWaveIter;
   if (first >= plan.ns) return;
   using Op = typename KTile<kKind>::Operand;
+  __shared__ u32x4 turn[kScoreThreads / 64][StreamTile<kKind>::kLdsChunks];
   Op A[4];
-  report_q_range(load_query_operand(A, q, (int64_t)b * s.Hq + (int64_t)g * G, G, j, kb), flags);
+  QueryRows query;
+  query.load(q, (int64_t)b * s.Hq + (int64_t)g * G, G, j, kb);
   const char* Kbg = static_cast<const char*>(K) + RowMap<kPaged>::base(b, g, stride_b, stride_h) * KTile<kKind>::kElemBytes;
   // row i of the sample: i n / ns, rounded down (the product is exact, and no quotient lies so near below a whole number that it would
   // be rounded up to it)
-  score_slots_mfma<kPaged, kKind>(A, Kbg, pg, b, stride_b, stride_n, [&](int i) { return (int)((double)i * (double)n / (double)plan.ns); }, n,
+  score_slots_mfma<kPaged, kKind, false, true>(A, Kbg, pg, b, stride_b, stride_n, [&](int i) { return (int)((double)i * (double)n / (double)plan.ns); }, n,
                                   plan.ns, first, (int)gridDim.x * 4 * kRowsPerWaveIter,
-                                  score + ((int64_t)b * s.Hq + (int64_t)g * G + kb) * score_stride, kb < G, scale);
+                                  score + ((int64_t)b * s.Hq + (int64_t)g * G + kb) * score_stride, kb < G, scale, nullptr, turn[wave], &query,
+                                  G, flags);
 }
 
 hipError_t launch_sample_score(const Shape& s, const float* q, const KvView& kv, const int32_t* k, int ns_max, int list_cap,

@@ -253,12 +253,15 @@ struct StreamTile {
 // loads are issued.  sc: the score row of head kb (ignored by lanes with store == false).
 // tops (or NULL): receives the largest score of every 16 slots, as the select orders them (a NaN above all); first and step are
 // multiples of 64 then.
-template <bool kPaged, int kKind, bool kTops = false, typename RowAt>
-__device__ __forceinline__ void score_slots_mfma(const typename KTile<kKind>::Operand (&A)[4], const char* Kbg,
+// turn (or NULL, see kStream): a wave-private piece of LDS, through which the rows come as whole ones (StreamTile, ordinary loads; the
+// same bits).  query (or NULL): the rows A is made from, here, behind the requests for the first tile.  (k_sample_score.)
+template <bool kPaged, int kKind, bool kTops = false, bool kStream = false, typename RowAt>
+__device__ __forceinline__ void score_slots_mfma(typename KTile<kKind>::Operand (&A)[4], const char* Kbg,
                                                  const KvPage& pg, int b, int64_t stride_b, int64_t stride_n,
                                                  RowAt row_at, int n, int count, int first, int step,
                                                  float* __restrict__ sc, bool store, float scale,
-                                                 float* __restrict__ tops = nullptr) {
+                                                 float* __restrict__ tops = nullptr, u32x4* turn = nullptr,
+                                                 const QueryRows* query = nullptr, int G = 0, int32_t* flags = nullptr) {
   using Rows = RowMap<kPaged>;
   using Op = typename KTile<kKind>::Operand;
   constexpr int ES = KTile<kKind>::kElemBytes;
@@ -274,13 +277,16 @@ __device__ __forceinline__ void score_slots_mfma(const typename KTile<kKind>::Op
   int my_ok = valid(my_row);
   my_row = physical(my_row);
   for (int base = first; base < count; base += step) {
-    KTile<kKind> Bt;
+    std::conditional_t<kStream, StreamTile<kKind>, KTile<kKind>> Bt;
     bool ok_t[4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int row = __shfl(my_row, 16 * t + j);
-      ok_t[t] = __shfl(my_ok, 16 * t + j) != 0;
-      Bt.load_row(t, Kbg + Rows::offset(pg, row, stride_b, stride_n) * ES, kb);
+    for (int t = 0; t < 4; ++t) ok_t[t] = __shfl(my_ok, 16 * t + j) != 0;
+    auto offset = [&](int row) { return Rows::offset(pg, row, stride_b, stride_n) * ES; };
+    if constexpr (kStream) Bt.fetch(Kbg, my_row, lane, offset, false);
+    else Bt.fetch(Kbg, my_row, lane, offset);
+    if (query && base == first) {
+      __builtin_amdgcn_sched_barrier(0);
+      report_q_range(query->operand(A, G, j), flags);
     }
     const int nb = base + step;
     int next_row = -1;
@@ -296,10 +302,11 @@ __device__ __forceinline__ void score_slots_mfma(const typename KTile<kKind>::Op
     }
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
+      const KSub<kKind> sub = Bt.sub(t, turn, lane);
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk)
-        acc = mfma16(A[kk], Bt.operand(t, kk), acc);
+        acc = mfma16(A[kk], sub.operand(kk), acc);
       // lane (j, kb): D rows 4*kb .. 4*kb+3 = the three terms (and a zero row) of head kb, column j
       pv[t] = ok_t[t] ? Split3<Op>::sum(acc) * scale : -INFINITY;
     }
