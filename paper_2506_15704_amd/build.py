@@ -11,7 +11,7 @@ PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
 INCLUDE = os.path.join(os.path.dirname(PKG_DIR), "include")
 LIB_PATH = os.path.join(PKG_DIR, "liblfps.so")
-SOURCES = ["lfps_api.hip", "candidates.hip", "score.hip", "range_score.hip", "select.hip",
+SOURCES = ["lfps_api.hip", "candidates.hip", "score.hip", "range_score.hip", "wide_score.hip", "select.hip",
            "select_attend_bf16.hip", "select_attend_bf16_fp8.hip", "select_attend_fp8.hip",
            "select_attend_f16.hip", "select_attend.hip", "attention.hip", "tables.hip", "prefill.hip", "exact_topk.hip"]
 

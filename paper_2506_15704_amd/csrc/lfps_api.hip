@@ -159,9 +159,12 @@ int check_config(const lfps_config* c, Sizes* z, char* err, size_t errn) {
   z->bitmap_words = (s.Lcap + 31) / 32;
   z->bitmap_b = 0;
   for (int t = 0; t < 2; ++t) {
-    z->range[t] = filt && z->cand_cap >= bound && (t == 0 || c->table_mode) ? range_rows(s, t == 1) : 0;
+    z->range[t] = 0;
+    if (!filt || z->cand_cap < bound || (t == 1 && !c->table_mode)) continue;
+    const WidePlan wide = t == 0 ? wide_plan(s) : WidePlan{0, 0};
+    z->range[t] = wide.rows ? wide.rows : range_rows(s, t == 1);
     if (!z->range[t]) continue;
-    const int np = 4 * ((s.Lcap + z->range[t] - 1) / z->range[t]);
+    const int np = 4 * (wide.rows ? 2 * wide.parts : (s.Lcap + z->range[t] - 1) / z->range[t]);
     z->nseg = np > z->nseg ? np : z->nseg;
     z->bitmap_b = align256((int64_t)c->batch * c->n_kv_heads * z->bitmap_words * 4);
   }
@@ -496,7 +499,7 @@ int lfps_sparse_attn(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int
 // Does the next chained step take the filtered kernels?  (Decides, too, whether its candidates kernel lays the
 // groups on the line: only the filtered select clears the line's length again.)
 static bool next_step_filtered(const lfps_ctx* ctx) { return ctx->filter_on && !ctx->no_history; }
-// ... and with them the kernel that finds the candidates and scores them at once (rows of its ranges, or 0)?
+// ... and with them a kernel that finds the candidates and scores them at once (rows of a workgroup, or 0)?
 static int next_step_range(const lfps_ctx* ctx, bool tables) { return next_step_filtered(ctx) ? ctx->range[tables] : 0; }
 
 // ... or, of fp32 keys, the one that does so without a filter?
@@ -520,7 +523,12 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
   const int range = next_step_range(ctx, from.prev_topk == nullptr);
   const KeepAll keep{from.prev_topk ? kKeepRatio : kKeepRatioTables, ctx->keep_fits, 0};
   ctx->no_history = 0;                       // either form leaves every selecting head's k-th best score behind
-  if (range) {
+  const WidePlan wide = range && from.prev_topk ? wide_plan(s) : WidePlan{0, 0};
+  if (wide.rows) {
+    LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
+           launch_wide_score(s, q, v, from.prev_topk, from.k, ctx->thr_state, kFilterMargin, ctx->tau, skip_if, ctx->score, ctx->slot,
+                             s.score_stride, ctx->seg_count, ctx->nseg, ctx->bitmap, ctx->bitmap_words, ctx->flags, st));
+  } else if (range) {
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
            launch_range_score(s, q, v, from, ctx->thr_state, kFilterMargin, ctx->tau, skip_if, ctx->score, ctx->slot,
                               s.score_stride, ctx->seg_count, ctx->nseg, ctx->bitmap, ctx->bitmap_words, range, ctx->flags, st));
@@ -534,7 +542,7 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SELECT_ATTEND, st,
            launch_filter_select_attend(s, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
                                        ctx->flags + 1, ctx->nseg, ctx->cand, ctx->cand_count, ctx->group_start,
-                                       line_total, range, range_parts(s, from.prev_topk == nullptr), ctx->bitmap, ctx->bitmap_words, k, topk_idx, sel,
+                                       line_total, range, 2 * wide.parts, ctx->bitmap, ctx->bitmap_words, k, topk_idx, sel,
                                        ctx->thr_state, ctx->tau, keep, skip_if, ctx->flags + 2, q, ctx->flags, v, out, st));
     return LFPS_OK;
   }

@@ -138,18 +138,23 @@ struct RangeSource {
   const uint32_t* fm;
   int flag_words;
 };
-int range_rows(const Shape& s, bool tables);   // see range_rows_for and wide_rows_for
-int range_parts(const Shape& s, bool tables);  // wide ranges: every request's rows are cut into so many equal ones; else 0
+int range_rows(const Shape& s, bool tables);   // see range_rows_for
 hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, const RangeSource& from,
                               const float* thr_state, float margin, float* tau_out, const int32_t* skip_if, float* score,
                               int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words,
                               int range, int32_t* flags, hipStream_t st);
+// The same from the Top-k for larger contexts (wide_score.hip), those with a wide_plan: a piece is a wave's part of a strip.
+WidePlan wide_plan(const Shape& s);
+hipError_t launch_wide_score(const Shape& s, const float* q, const KvView& kv, const int32_t* prev_topk, const int32_t* k,
+                             const float* thr_state, float margin, float* tau_out, const int32_t* skip_if, float* score, int32_t* slot_out,
+                             int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words, int32_t* flags,
+                             hipStream_t st);
 
 // S3 + S4 of the chained steps in one kernel (select_attend.hip).  From the survivor lists of the filtered scoring
 // pass: every head gets its Top-k rows (topk_idx, topk_score: both required) and its output row; a head whose list
 // is short or overfull takes the unfiltered pass inside the kernel (counted in *rescored), which needs q, the K rows
 // and the group's candidate list (cand; NULL = all rows 0 .. cand_count-1) and overwrites the head's score row.
-// range > 0: the lists are those of launch_range_score with that range (cand, seg_rows, group_start, line_total unused;
+// range > 0: the lists are those of launch_range_score with that range, or with range_parts of launch_wide_score (cand, seg_rows, group_start, line_total unused;
 // the candidates are in bitmap), and cand_count is written.
 // keep: a head with fewer than keep.ratio * k candidates, and no more than keep.most, leaves -inf in thr_state instead of its
 // k-th best score; keep.fits [B, Hq] (or NULL) receives whether it had no more than keep.most, and a bypassed head (skip_if)

@@ -1,16 +1,13 @@
 // Where the pieces of the range kernel's survivors lie in a head's score / position rows.
 #pragma once
 #include "lfps_internal.h"
+#include "wide_cut.h"
 
 namespace lfps {
 
 // A group's rows [0, n) are cut into ranges of `range` rows and the candidates of a range into four pieces.  Piece p
 // belongs to range p / 4 and keeps its survivors from start(p) on: a range's pieces stand a quarter of the range apart
 // (of the last range: a quarter of its rows, rounded up to 16, which stays below n rounded up to 64).
-__device__ __forceinline__ int equal_ranges(int n, int parts) {
-  const int rows = (int)(((uint32_t)n + (uint32_t)parts - 1u) / (uint32_t)parts + 63u) & ~63;
-  return rows > 64 ? rows : 64;
-}
 struct RangePieces {
   int range, last, apart_last, count;
   // parts > 0: that many ranges of equal length, a multiple of 64 rows, whatever range_ is.

@@ -2,6 +2,8 @@
 #pragma once
 #include <stdint.h>
 
+#include "wide_cut.h"
+
 namespace lfps {
 
 constexpr int kRangeMax = 8192;      // rows of a range at most: a word of bitmap per thread
@@ -40,20 +42,25 @@ inline int range_rows_for(int64_t groups, int rows, int heads_per_group, bool ta
   return range <= kRangeMax ? range : 0;
 }
 
-constexpr int kWideMax = 65536;      // rows of a wide range at most
+constexpr int kWideMax = 65536;      // rows of a workgroup of the wide form at most: their places are 16 bits
 
-// Rows of the longest wide range (a multiple of 64) of contexts from the Top-k that range_rows_for does not take, or 0 where the
-// separate kernels are.  Every workgroup reads the Top-k rows of its group once and keeps two tiles per wave in flight, so there are as
-// many as the chip holds at once, 512: 1024 take 5 to 12 % longer (64 groups x 32K rows 228 -> 240 us for four steps, 128 x 128K 810 ->
-// 853, FP8 128 x 64K 286 -> 320), 2048 still more.  257 to 384 groups get two workgroups each, half the chip standing empty with one
-// costs more than a second generation: 264 x 20000 444 -> 418, 320 x 30000 668 -> 624, 384 x 32K 783 -> 759 (480 x 20000 with two 576
-// -> 600).  Four steps, separate kernels -> these: 64 groups x 32K rows 253 -> 228, 128 x 128K 884 -> 810, 16 x 66000 FP8 145 -> 108, 800
-// x 8000 514 -> 461.  Up to 2^20 rows the ranges above are the better ones (1 x 32K 72 against 74, 8 x 8000 76 against 80).
-inline int wide_rows_for(int64_t groups, int rows) {
+// The wide form (wide_score.hip) of contexts from the Top-k that range_rows_for does not take.
+struct WidePlan {
+  int rows;        // of a workgroup at most, a multiple of 64; 0: the separate kernels
+  int parts;       // workgroups per group
+};
+
+// Every workgroup reads the Top-k rows of its group once and keeps two tiles per wave in flight, so there are as many as the chip holds
+// at once, 512: 1024 take 5 to 12 % longer (64 groups x 32K rows 228 -> 240 us for four steps, 128 x 128K 810 -> 853, FP8 128 x 64K 286
+// -> 320), 2048 still more.  257 to 384 groups get two workgroups each, half the chip standing empty with one costs more than a second
+// generation: 264 x 20000 444 -> 418, 320 x 30000 668 -> 624, 384 x 32K 783 -> 759 (480 x 20000 with two 576 -> 600).
+// Four steps, separate kernels -> these: 64 groups x 32K rows 253 -> 228, 128 x 128K 884 -> 810, 16 x 66000 FP8 145 -> 108, 800 x 8000
+// 514 -> 461.  Up to 2^20 rows the ranges above are the better ones (1 x 32K 72 against 74, 8 x 8000 76 against 80).
+inline WidePlan wide_plan_for(int64_t groups, int rows) {
   int64_t parts = groups <= 384 && groups > 256 ? 2 : 512 / groups;
-  parts = parts < 1 ? 1 : (parts > 256 ? 256 : parts);                    // (at most 1024 pieces per head)
-  const int64_t range = ((rows + parts - 1) / parts + 63) & ~(int64_t)63;
-  return range <= kWideMax ? (int)range : 0;
+  parts = parts < 1 ? 1 : (parts > 128 ? 128 : parts);                      // (two strips of four pieces, 1024 per head)
+  const int64_t most = 2 * (int64_t)equal_ranges(rows, 2 * (int)parts);
+  return most <= kWideMax ? WidePlan{(int)most, (int)parts} : WidePlan{0, 0};
 }
 
 }  // namespace lfps

@@ -9,7 +9,7 @@
 // in position, with the numbers of survivors and candidates of every piece in seg_count.  The bitmap goes to memory too,
 // for the heads that need that unfiltered pass.
 //
-// Larger contexts from the Top-k have wide ranges, of which every workgroup keeps one: see k_range_score and wide_rows_for.
+// Larger contexts from the Top-k take the wide form, a kernel of its own (wide_score.hip).
 //
 // Why one kernel: as two, a step of 8 groups x 32K rows spent 7.8 + 14.5 us here, of which the rows themselves are 5 us;
 // the rest is two launches and the round trips
@@ -24,50 +24,23 @@
 
 namespace lfps {
 
-// Survivors a wave holds per head before it writes them out.
-constexpr int range_stage(bool wide) { return wide ? 256 : 160; }
-constexpr int kRangeRing = 512;         // list entries of a wave of a wide range
+constexpr int kRangeStage = 160;        // survivors a wave holds per head before it writes them out
 
-// Bytes of K that the candidates of all requests take, about: windows of 2 r + 2 rows around the Top-k rows of a group's heads, which
-// have a part of them in common.  (Whether rows are read past the caches hangs on it, nothing else.)
-__device__ __forceinline__ float candidate_rows(const Shape& s, const int32_t* seq_lens, const int32_t* kk) {
-  const float heads = s.G == 4 ? 1.6f : (s.G == 2 ? 1.3f : 1.f), window = heads * (float)(2 * s.radius + 2);
-  auto rows = [&](int b) {
-    const int n = seq_lens[b < s.B ? b : 0], k = kk[b < s.B ? b : 0];
-    const float nf = (float)(n < 1 ? 1 : (n > s.Lcap ? s.Lcap : n)), kf = (float)(k < 0 ? 0 : (k > s.kmax ? s.kmax : k));
-    return b < s.B ? nf * (1.f - __expf(-window * kf / nf)) : 0.f;
-  };
-  const int lane = threadIdx.x & 63;
-  float sum = rows(lane);
-  for (int b0 = 64; b0 < s.B; b0 += 64) sum += rows(b0 + lane);
-  return sum;
-}
-
-// kWide: ranges of up to 65536 rows, two workgroups per CU, two tiles per wave in flight; bound by the bytes of the rows.  The
-// candidates are not listed: a wave expands the bitmap from where its quarter of them begins, 256 positions at a time, into a ring of its
-// own.  may_once: the candidates may take more than the memory-side cache holds; rows are then read past it, see k_filter_score_bf16.
-// Against a kernel that lists the candidates of a group in memory and one that reads them back in equal parts, a step of 64 groups x 32K
-// rows: 7.9 + 36.2 us and a boundary -> 38; of 128 x 128K 13.1 + 174 -> 168, of FP8 128 x 64K pages 9.6 + 47.4 -> 48.  With four
-// workgroups per CU and one tile each, 911 us for four steps of 128 x 128K instead of 810 (884 separately).
-template <int G, bool kPaged, int kKind, bool kTables, bool kWide>
-__global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
+template <int G, bool kPaged, int kKind, bool kTables>
+__global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
     Shape s, const float* __restrict__ q, const void* __restrict__ K, int64_t stride_b, int64_t stride_h,
     int64_t stride_n, KvPage page, const int32_t* __restrict__ seq_lens, RangeSource from, const int32_t* __restrict__ kk,
     const float* __restrict__ thr_state, float margin, float* __restrict__ tau_out, const int32_t* __restrict__ skip_if,
     float* __restrict__ score, int32_t* __restrict__ slot_out,
     int64_t score_stride, int32_t* __restrict__ seg_count, int nseg, uint32_t* __restrict__ bitmap, int bitmap_words,
-    int range_arg, float scale, int32_t* __restrict__ flags, int may_once) {
-  constexpr int kStage = range_stage(kWide);
-  __shared__ float stage_score[4][G][kStage];
-  __shared__ uint16_t stage_slot[4][G][kStage];          // relative to the range's first row
+    int range, float scale, int32_t* __restrict__ flags) {
+  __shared__ float stage_score[4][G][kRangeStage];
+  __shared__ uint16_t stage_slot[4][G][kRangeStage];          // relative to the range's first row
   __shared__ u32x4 turn[4][StreamTile<kKind>::kLdsChunks];
-  __shared__ uint32_t bm_narrow[kWide ? 1 : kRangeMax / 32];
-  __shared__ uint16_t ring[kWide ? 4 : 1][kRangeRing];
-  __shared__ int wave_tot[4], first_word[4], skip_of[4];
-  extern __shared__ uint32_t dyn[];                      // wide: the bitmap; else the range's candidates, relative to its first row
-  uint32_t* bm = kWide ? dyn : bm_narrow;
-  uint16_t* list = reinterpret_cast<uint16_t*>(dyn);
-  request_arguments<decltype(&k_range_score<G, kPaged, kKind, kTables, kWide>)>();
+  __shared__ uint32_t bm[kRangeMax / 32];
+  __shared__ int wave_tot[4];
+  extern __shared__ uint16_t list[];                     // the range's candidates, relative to its first row
+  request_arguments<decltype(&k_range_score<G, kPaged, kKind, kTables>)>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, kb = lane >> 4;
@@ -104,15 +77,9 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
   const int64_t head0 = (int64_t)b * s.Hq + (int64_t)g * G, my_head = head0 + (kb < G ? kb : 0);
   const float thr = thr_state[my_head];
   const int skip_word = *(skip_if ? skip_if + my_head : seq_lens);             // (no gate: any word)
-  for (int w = tid; w < range_arg >> 5; w += kScoreThreads) {
-    bm[w] = 0u;
-    if constexpr (!kWide) break;
-  }
-  float all_rows = 0.f;
-  if (kWide && may_once) all_rows = candidate_rows(s, seq_lens, kk);
+  const int words = range >> 5;
+  if (tid < words) bm[tid] = 0u;
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
-  // (a wide range is the request's part, not the context's: a batch of mixed lengths, or far below its capacity, keeps the chip full)
-  const int range = kWide ? equal_ranges(n, gridDim.y) : range_arg, words = range >> 5;
   const int lo = blockIdx.y * range;
   if (lo >= n) return;                                   // (nobody reads the piece counts of such a range)
   const int hi = n - lo < range ? n : lo + range;
@@ -120,16 +87,14 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
   // The query is split behind the requests for the first rows, beside their latency (four steps of 8 groups x 32K rows 105.7 ->
   // 103.3 us, of 32 x 12K FP8 88.8 -> 88.1), where the registers allow it: not of fp16, whose split takes the most of them (beside a
   // tile it spills), and not of paged rows (8 x 32K 114.4 -> 116.1).
-  constexpr bool kSplitLate = kWide || (!Split3<Op>::kHalf && !kPaged);
+  constexpr bool kSplitLate = !Split3<Op>::kHalf && !kPaged;
   Op A[4];
   QueryRows query;
   query.load(q, head0, G, j, kb);
   if constexpr (!kSplitLate) report_q_range(query.operand(A, G, j), flags);
-  const bool once = kWide && may_once && outgrow_cache(s, all_rows, kD * Tile::kElemBytes, (float)kKeptBytes);
   __syncthreads();
 
   // ---- S1: the candidates of [lo, hi) as a bitmap
-  static_assert(!(kTables && kWide), "the table form has no wide ranges");
   if constexpr (kTables) {
     const int w = (lo >> 5) + tid, W = (n + 31) >> 5;
     if (tid < words && w < W) {
@@ -187,52 +152,29 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
   }
   __syncthreads();
 
-  int total = 0;
-  auto places = [&](int mine) {                           // of the thread's candidates in the list; total
-    const int inc = wave_inclusive_sum(mine);
-    if (lane == 63) wave_tot[wave] = inc;
-    __syncthreads();
-    int at = inc - mine;
+  // ---- the list: thread t owns the bits [t * nb, (t + 1) * nb), nb = the power of two that 256 threads cover the range with
+  const int nb = range <= kScoreThreads ? 1 : 1 << (32 - __builtin_clz((uint32_t)(range - 1) / kScoreThreads)), bit0 = tid * nb;
+  uint32_t bits = bit0 < range ? (bm[bit0 >> 5] >> (bit0 & 31)) & (nb == 32 ? 0xFFFFFFFFu : (1u << nb) - 1u) : 0u;
+  const int mine = __popc(bits);
+  const int inc = wave_inclusive_sum(mine);
+  if (lane == 63) wave_tot[wave] = inc;
+  __syncthreads();
+  int at = inc - mine, total = 0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int t = wave_tot[w];
-      at += w < wave ? t : 0;
-      total += t;
-    }
-    return at;
-  };
-  auto per_wave = [&]() { return (((total + 3) >> 2) + 15) & ~15; };
-  if constexpr (kWide) {
-    // ---- thread t owns `own` words; the one in whose words a wave's quarter begins says where
-    const int own = (words + kScoreThreads - 1) / kScoreThreads, w0 = tid * own;
-    int mine = 0;
-#pragma unroll
-    for (int i = 0; i < kWideMax / 32 / kScoreThreads; ++i)
-      if (i < own) mine += w0 + i < words ? __popc(bm[w0 + i]) : 0;
-    const int at = places(mine);
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int c = w * per_wave();
-      if (at <= c && c < at + mine) {
-        first_word[w] = w0;
-        skip_of[w] = c - at;
-      }
-    }
-  } else {
-    // ---- the list: thread t owns the bits [t * nb, (t + 1) * nb), nb = the power of two that 256 threads cover the range with
-    const int nb = range <= kScoreThreads ? 1 : 1 << (32 - __builtin_clz((uint32_t)(range - 1) / kScoreThreads)), bit0 = tid * nb;
-    uint32_t bits = bit0 < range ? (bm[bit0 >> 5] >> (bit0 & 31)) & (nb == 32 ? 0xFFFFFFFFu : (1u << nb) - 1u) : 0u;
-    int at = places(__popc(bits));
-    while (bits) {
-      list[at++] = (uint16_t)(bit0 + __ffs(bits) - 1);
-      bits &= bits - 1;
-    }
+  for (int w = 0; w < 4; ++w) {
+    const int t = wave_tot[w];
+    at += w < wave ? t : 0;
+    total += t;
+  }
+  while (bits) {
+    list[at++] = (uint16_t)(bit0 + __ffs(bits) - 1);
+    bits &= bits - 1;
   }
   __syncthreads();
 
   // ---- S2: the piece of this wave, entries [c0, c0 + cnt) of the list
   const RangePieces geo(n, range, 0);
-  const int per = per_wave();
+  const int per = (((total + 3) >> 2) + 15) & ~15;
   const int c0 = wave * per;
   const int cnt = __builtin_amdgcn_readfirstlane(total - c0 < per ? (total - c0 > 0 ? total - c0 : 0) : per);
   const int piece = 4 * (int)blockIdx.y + wave;
@@ -240,10 +182,7 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
   const bool skipped = skip_if && skip_word != 0;         // bypassed head: nothing is kept for it
   const uint64_t nans = __ballot(kb < G && isnan(thr) && !skipped);
   auto leave = [&](int kept) {                           // (no store before the last load: a wait for that would wait for the store)
-    for (int w = tid; w < words && (lo >> 5) + w < bitmap_words; w += kScoreThreads) {
-      bitmap[(int64_t)bg * bitmap_words + (lo >> 5) + w] = bm[w];
-      if constexpr (!kWide) break;
-    }
+    if (tid < words && (lo >> 5) + tid < bitmap_words) bitmap[(int64_t)bg * bitmap_words + (lo >> 5) + tid] = bm[tid];
     if (j == 0 && kb < G) {
       seg_count[my_head * nseg + piece] = cnt << 16 | kept;
       if (piece == 0) tau_out[my_head] = thr - margin;
@@ -277,32 +216,7 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
     wave_lds_order();
   };
   // list entry e0 + lane (past the end: the last one, never kept), relative to the range
-  int word = kWide ? __builtin_amdgcn_readfirstlane(first_word[wave]) : 0;      // of the bitmap, to expand next
-  const int skip = kWide ? __builtin_amdgcn_readfirstlane(skip_of[wave]) : 0;   // entries of the ring before the wave's first
-  int filled = 0;
-  auto ids_of = [&](int e0) {
-    const int e = e0 + lane < cnt ? e0 + lane : cnt - 1;
-    if constexpr (!kWide) return (int)list[c0 + e];
-    const int need = skip + (e0 + T < cnt ? e0 + T : cnt);
-    uint16_t* mine = ring[wave];
-    wave_lds_order();
-    while (filled < need) {                               // (ends: the range holds cnt candidates from the wave's first on)
-      const int w = word + (lane >> 3), bit = 4 * (lane & 7);
-      const uint32_t four = w < words ? bm[w] >> bit & 15u : 0u;
-      const int here = __popc(four), upto = wave_inclusive_sum(here);
-      int to = filled + upto - here;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        if (four >> c & 1u) mine[to & (kRangeRing - 1)] = (uint16_t)((w << 5) + bit + c);
-        to += four >> c & 1u;
-      }
-      filled += __builtin_amdgcn_readlane(upto, 63);
-      word += 8;
-      if (word >= words) break;
-    }
-    wave_lds_order();
-    return (int)mine[(skip + e) & (kRangeRing - 1)];
-  };
+  auto ids_of = [&](int e0) { return (int)list[c0 + (e0 + lane < cnt ? e0 + lane : cnt - 1)]; };
   auto consume = [&](const Tile& Bt, int ids, int e0) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -321,7 +235,7 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
       }
       staged += __popc(gm);
     }
-    if (__ballot(staged > kStage - T)) flush();      // no room for one more tile
+    if (__ballot(staged > kRangeStage - T)) flush();      // no room for one more tile
   };
   // One tile in flight per wave and sixteen waves per CU (two tiles in flight do not fit the registers of that many).
   // Paged cache: the block-table lookup of the next tile is issued before the loads of this one, so that the wait for it
@@ -340,32 +254,11 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
     } else {
       phys = lookup(id);
     }
-    Bt.fetch(Kbg, phys_now, lane, [&](int p) { return Rows::offset(page, p, stride_b, stride_n) * ES; }, once);
+    Bt.fetch(Kbg, phys_now, lane, [&](int p) { return Rows::offset(page, p, stride_b, stride_n) * ES; }, false);
   };
   Tile B0;
   int f0;
-  if constexpr (kWide) {
-    Tile B1;
-    int f1, e0 = 0;
-    request(B0, f0, 0);
-    if constexpr (kSplitLate) {
-      __builtin_amdgcn_sched_barrier(0);
-      report_q_range(query.operand(A, G, j), flags);
-    }
-    for (; e0 + 2 * T < cnt; e0 += 2 * T) {
-      request(B1, f1, e0 + T);
-      consume(B0, f0, e0);
-      request(B0, f0, e0 + 2 * T);
-      consume(B1, f1, e0 + T);
-    }
-    if (e0 + T < cnt) {
-      request(B1, f1, e0 + T);
-      consume(B0, f0, e0);
-      consume(B1, f1, e0 + T);
-    } else {
-      consume(B0, f0, e0);
-    }
-  } else if constexpr (kSplitLate) {
+  if constexpr (kSplitLate) {
     request(B0, f0, 0);
     __builtin_amdgcn_sched_barrier(0);
     (void)query.operand(A, G, j);                        // (only fp16 has a range to report)
@@ -386,21 +279,10 @@ __global__ __launch_bounds__(kScoreThreads, kWide ? 2 : 4) void k_range_score(
 }
 
 // ----------------------------------------------------------------------------- launcher
-int range_rows(const Shape& s, bool tables) {
-  const int64_t groups = (int64_t)s.B * s.Hkv;
-  const int rows = range_rows_for(groups, s.Lcap, s.G, tables);
-  return rows || tables ? rows : wide_rows_for(groups, s.Lcap);
-}
+int range_rows(const Shape& s, bool tables) { return range_rows_for((int64_t)s.B * s.Hkv, s.Lcap, s.G, tables); }
 
-int range_parts(const Shape& s, bool tables) {
-  const int64_t groups = (int64_t)s.B * s.Hkv;
-  if (tables || range_rows_for(groups, s.Lcap, s.G, false)) return 0;
-  const int rows = wide_rows_for(groups, s.Lcap);
-  return rows ? (s.Lcap + rows - 1) / rows : 0;
-}
-
-template <int G, bool kPaged, int kKind, bool kTables, bool kWide>
-static constexpr auto range_kernel = &k_range_score<G, kPaged, kKind, kTables, kWide>;
+template <int G, bool kPaged, int kKind, bool kTables>
+static constexpr auto range_kernel = &k_range_score<G, kPaged, kKind, kTables>;
 
 hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, const RangeSource& from,
                               const float* thr_state, float margin, float* tau_out, const int32_t* skip_if, float* score,
@@ -409,27 +291,20 @@ hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, 
   const int groups = s.B * s.Hkv, beside = groups % 8 == 0 ? 8 : 1;
   const int kind = kv.k_fp8 ? kKindFp8 : (kv.f16 ? kKindF16 : kKindBf16);
   const bool paged = kv.page.table != nullptr, tables = from.prev_topk == nullptr;
-  const bool wide = range_parts(s, tables) > 0;
-  // (cand_cap is at least what the windows can cover)
-  const int may_once = wide && (int64_t)groups * s.cand_cap * kD * (kind == kKindFp8 ? 1 : 2) > kKeptBytes;
   hipError_t e = hipErrorInvalidValue;
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(beside, (s.Lcap + range - 1) / range, groups / beside), dim3(kScoreThreads),
-                       (size_t)(wide ? range / 8 : range * 2), st, s, q, kv.k, kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens,
+                       (size_t)range * 2, st, s, q, kv.k, kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens,
                        from, from.k, thr_state, margin, tau_out, skip_if, score, slot_out, score_stride, seg_count, nseg, bitmap, bitmap_words,
-                       range, 0.08838834764831845f /* 1/sqrt(128) */, flags, may_once);
+                       range, 0.08838834764831845f /* 1/sqrt(128) */, flags);
     e = hipGetLastError();
   };
   auto of_kind = [&](auto heads, auto pages, auto form) {
     constexpr int G = decltype(heads)::value;
     constexpr bool kPaged = decltype(pages)::value;
-    if (wide) {
-      if (kind == form.value) launch(range_kernel<G, kPaged, decltype(form)::value, false, true>);
-    } else if (tables) {
-      if (kind == form.value) launch(range_kernel<G, kPaged, decltype(form)::value, true, false>);
-    } else {
-      if (kind == form.value) launch(range_kernel<G, kPaged, decltype(form)::value, false, false>);
-    }
+    if (kind != form.value) return;
+    if (tables) launch(range_kernel<G, kPaged, decltype(form)::value, true>);
+    else launch(range_kernel<G, kPaged, decltype(form)::value, false>);
   };
   auto of_pages = [&](auto heads, auto pages) {
     if (paged != pages.value) return;

@@ -1,0 +1,45 @@
+// Which rows of a group a workgroup of the wide kernel (wide_score.hip) has: arithmetic only, for the host and the device, so that a
+// test can compile it by itself.
+#pragma once
+#include <stdint.h>
+
+#ifdef __HIPCC__
+#define LFPS_BOTH __host__ __device__ __forceinline__
+#else
+#define LFPS_BOTH inline
+#endif
+
+namespace lfps {
+
+// Rows [0, n) in at most `parts` ranges of equal length, a multiple of 64.
+LFPS_BOTH int equal_ranges(int n, int parts) {
+  const int rows = (int)(((uint32_t)n + (uint32_t)parts - 1u) / (uint32_t)parts + 63u) & ~63;
+  return rows > 64 ? rows : 64;
+}
+
+// The rows [0, n) of a group are cut into 2 * parts strips of equal length, and workgroup `part` of `parts` has the strips part and
+// parts + part.  It counts its rows through: place i is row i of the first strip, place rows + i is row i of the second.
+struct Strips {
+  int rows;                                  // of a strip
+  int first, second;                         // row where they begin
+  LFPS_BOTH Strips(int n, int parts, int part) : rows(equal_ranges(n, 2 * parts)), first(part * rows), second((parts + part) * rows) {}
+  LFPS_BOTH int row_of(int place) const { return place + (place < rows ? first : second - rows); }
+};
+
+// The strip [begin, begin + rows) of a request of n rows, and which windows [i - r, i + r + 1] touch it: those with touches(i).
+// (i is any int32; r is at most 2^20.)
+struct StripWindows {
+  int begin, end, lowest;
+  uint32_t span;
+  LFPS_BOTH StripWindows(int n, int begin_, int rows, int r) : begin(begin_), end(n - begin_ < rows ? n : begin_ + rows) {
+    const int highest = end - 1 + r < n - 1 ? end - 1 + r : n - 1;
+    lowest = begin - 1 - r > 0 ? begin - 1 - r : 0;
+    span = begin < n ? (uint32_t)(highest - lowest + 1) : 0u;
+  }
+  LFPS_BOTH bool touches(int i) const { return (uint32_t)i - (uint32_t)lowest < span; }
+  // ... and the rows of the strip, counted from its first, that such a window covers
+  LFPS_BOTH int from(int i, int r) const { return i - r > begin ? i - r - begin : 0; }
+  LFPS_BOTH int to(int i, int r) const { return (i + r + 1 < end ? i + r + 1 : end - 1) - begin; }
+};
+
+}  // namespace lfps
