@@ -26,6 +26,7 @@ struct lfps_ctx {
   float* tau;          // [B, Hq] what the rows have reached that the scoring pass of this step kept
   int32_t* keep_fits;  // [B, Hq] 1: the candidates of the head's last step fitted half of the select's list (table mode, else NULL)
   int range[2];        // rows of a range when a step (0 memoryless, 1 table form) takes the range kernel, else 0
+  int32_t* wide_parts; // [B, Hkv] workgroups that share a group's rows in the wide form of such a step
   uint32_t* bitmap;    // [B, Hkv, bitmap_words] the candidates of such a step
   int bitmap_words;
   int64_t* group_start; // [B, Hkv] place of each group on the line of all candidate slots; [B*Hkv] = the line's length
@@ -161,10 +162,10 @@ int check_config(const lfps_config* c, Sizes* z, char* err, size_t errn) {
   for (int t = 0; t < 2; ++t) {
     z->range[t] = 0;
     if (!filt || z->cand_cap < bound || (t == 1 && !c->table_mode)) continue;
-    const WidePlan wide = t == 0 ? wide_plan(s) : WidePlan{0, 0};
+    const WidePlan wide = t == 0 ? wide_plan(s) : WidePlan{0, 0, 0, 0};
     z->range[t] = wide.rows ? wide.rows : range_rows(s, t == 1);
     if (!z->range[t]) continue;
-    const int np = 4 * (wide.rows ? 2 * wide.parts : (s.Lcap + z->range[t] - 1) / z->range[t]);
+    const int np = 4 * (wide.rows ? 2 * wide.most : (s.Lcap + z->range[t] - 1) / z->range[t]);
     z->nseg = np > z->nseg ? np : z->nseg;
     z->bitmap_b = align256((int64_t)c->batch * c->n_kv_heads * z->bitmap_words * 4);
   }
@@ -185,7 +186,7 @@ int check_config(const lfps_config* c, Sizes* z, char* err, size_t errn) {
   z->aux_b = align256(z->aux_b);
   z->total = z->score_b + z->cand_b + z->count_b + z->sel_b + z->part_b + z->slot_b + z->seg_b + z->thr_b +
              z->line_b + 256 + z->x_b + z->aux_b + z->bitmap_b + z->tver_b + z->tsla_b + z->tstate_b + 2 * z->tflag_b +
-             2 * z->thr_b /* gate marks, tau */ + (c->table_mode ? z->thr_b : 0) /* keep_fits */;
+             2 * z->thr_b /* gate marks, tau */ + z->count_b /* wide_parts */ + (c->table_mode ? z->thr_b : 0) /* keep_fits */;
   return LFPS_OK;
 }
 
@@ -392,6 +393,8 @@ int lfps_create(const lfps_config* cfg, lfps_ctx** out) {
   p += z.thr_b;
   c->tau = (float*)p;
   p += z.thr_b;
+  c->wide_parts = (int32_t*)p;
+  p += z.count_b;
   if (cfg->table_mode) c->keep_fits = (int32_t*)p;
   c->nseg = z.nseg;
   // The filtered pass pays off only if a head's survivors (about 1.25 x its budget) fit the select's list; with a
@@ -523,11 +526,11 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
   const int range = next_step_range(ctx, from.prev_topk == nullptr);
   const KeepAll keep{from.prev_topk ? kKeepRatio : kKeepRatioTables, ctx->keep_fits, 0};
   ctx->no_history = 0;                       // either form leaves every selecting head's k-th best score behind
-  const WidePlan wide = range && from.prev_topk ? wide_plan(s) : WidePlan{0, 0};
+  const WidePlan wide = range && from.prev_topk ? wide_plan(s) : WidePlan{0, 0, 0, 0};
   if (wide.rows) {
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
            launch_wide_score(s, q, v, from.prev_topk, from.k, ctx->thr_state, kFilterMargin, ctx->tau, skip_if, ctx->score, ctx->slot,
-                             s.score_stride, ctx->seg_count, ctx->nseg, ctx->bitmap, ctx->bitmap_words, ctx->flags, st));
+                             s.score_stride, ctx->seg_count, ctx->nseg, ctx->wide_parts, ctx->bitmap, ctx->bitmap_words, ctx->flags, st));
   } else if (range) {
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
            launch_range_score(s, q, v, from, ctx->thr_state, kFilterMargin, ctx->tau, skip_if, ctx->score, ctx->slot,
@@ -542,7 +545,7 @@ static int score_select_attend(lfps_ctx* ctx, const float* q, const KvView& v, c
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SELECT_ATTEND, st,
            launch_filter_select_attend(s, ctx->cfg.kv_dtype, ctx->score, ctx->slot, s.score_stride, ctx->seg_count,
                                        ctx->flags + 1, ctx->nseg, ctx->cand, ctx->cand_count, ctx->group_start,
-                                       line_total, range, 2 * wide.parts, ctx->bitmap, ctx->bitmap_words, k, topk_idx, sel,
+                                       line_total, range, wide.rows ? ctx->wide_parts : nullptr, ctx->bitmap, ctx->bitmap_words, k, topk_idx, sel,
                                        ctx->thr_state, ctx->tau, keep, skip_if, ctx->flags + 2, q, ctx->flags, v, out, st));
     return LFPS_OK;
   }

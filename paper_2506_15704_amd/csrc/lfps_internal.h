@@ -143,18 +143,19 @@ hipError_t launch_range_score(const Shape& s, const float* q, const KvView& kv, 
                               const float* thr_state, float margin, float* tau_out, const int32_t* skip_if, float* score,
                               int32_t* slot_out, int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words,
                               int range, int32_t* flags, hipStream_t st);
-// The same from the Top-k for larger contexts (wide_score.hip), those with a wide_plan: a piece is a wave's part of a strip.
+// The same from the Top-k for larger contexts (wide_score.hip), those with a wide_plan: a piece is a wave's part of a strip,
+// and parts_of [B, Hkv] receives the workgroups of a group, with two strips each.
 WidePlan wide_plan(const Shape& s);
 hipError_t launch_wide_score(const Shape& s, const float* q, const KvView& kv, const int32_t* prev_topk, const int32_t* k,
                              const float* thr_state, float margin, float* tau_out, const int32_t* skip_if, float* score, int32_t* slot_out,
-                             int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words, int32_t* flags,
-                             hipStream_t st);
+                             int64_t score_stride, int32_t* seg_count, int nseg, int32_t* parts_of, uint32_t* bitmap, int bitmap_words,
+                             int32_t* flags, hipStream_t st);
 
 // S3 + S4 of the chained steps in one kernel (select_attend.hip).  From the survivor lists of the filtered scoring
 // pass: every head gets its Top-k rows (topk_idx, topk_score: both required) and its output row; a head whose list
 // is short or overfull takes the unfiltered pass inside the kernel (counted in *rescored), which needs q, the K rows
 // and the group's candidate list (cand; NULL = all rows 0 .. cand_count-1) and overwrites the head's score row.
-// range > 0: the lists are those of launch_range_score with that range, or with range_parts of launch_wide_score (cand, seg_rows, group_start, line_total unused;
+// range > 0: the lists are those of launch_range_score with that range, or with parts_of those of launch_wide_score (cand, seg_rows, group_start, line_total unused;
 // the candidates are in bitmap), and cand_count is written.
 // keep: a head with fewer than keep.ratio * k candidates, and no more than keep.most, leaves -inf in thr_state instead of its
 // k-th best score; keep.fits [B, Hq] (or NULL) receives whether it had no more than keep.most, and a bypassed head (skip_if)
@@ -168,7 +169,7 @@ hipError_t configure_select_attend(const Shape& s, int dtype, bool k_fp8, bool v
 hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, int32_t* slot,
                                        int64_t score_stride, const int32_t* seg_count, const int32_t* seg_rows, int nseg,
                                        const int32_t* cand, int32_t* cand_count, const int64_t* group_start,
-                                       int64_t* line_total, int range, int range_parts, const uint32_t* bitmap, int bitmap_words,
+                                       int64_t* line_total, int range, const int32_t* parts_of, const uint32_t* bitmap, int bitmap_words,
                                        const int32_t* k, int32_t* topk_idx, float* topk_score,
                                        float* thr_state, const float* tau, KeepAll keep, const int32_t* skip_if, int32_t* rescored,
                                        const float* q, int32_t* flags, const KvView& kv, float* out,

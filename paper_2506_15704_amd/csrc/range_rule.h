@@ -42,12 +42,13 @@ inline int range_rows_for(int64_t groups, int rows, int heads_per_group, bool ta
   return range <= kRangeMax ? range : 0;
 }
 
-constexpr int kWideMax = 65536;      // rows of a workgroup of the wide form at most: their places are 16 bits
 
 // The wide form (wide_score.hip) of contexts from the Top-k that range_rows_for does not take.
 struct WidePlan {
-  int rows;        // of a workgroup at most, a multiple of 64; 0: the separate kernels
-  int parts;       // workgroups per group
+  int rows;        // of a workgroup at most in an even cut, a multiple of 64; 0: the separate kernels
+  int parts;       // workgroups per group, where all requests have about as much work
+  int slots;       // workgroups per KV head where they have not; 0: one request
+  int most;        // of these, for one request
 };
 
 // Every workgroup reads the Top-k rows of its group once and keeps two tiles per wave in flight, so there are as many as the chip holds
@@ -56,11 +57,21 @@ struct WidePlan {
 // generation: 264 x 20000 444 -> 418, 320 x 30000 668 -> 624, 384 x 32K 783 -> 759 (480 x 20000 with two 576 -> 600).
 // Four steps, separate kernels -> these: 64 groups x 32K rows 253 -> 228, 128 x 128K 884 -> 810, 16 x 66000 FP8 145 -> 108, 800 x 8000
 // 514 -> 461.  Up to 2^20 rows the ranges above are the better ones (1 x 32K 72 against 74, 8 x 8000 76 against 80).
-inline WidePlan wide_plan_for(int64_t groups, int rows) {
+// Requests of uneven work share the workgroups out by it.  Where they have the fewest already there are 256 more, which else return at once.
+// Four steps of 8 KV heads, separate kernels (which cut the candidates of all requests into equal parts) -> the same number for every
+// request -> by their work: one request of 100000 rows and 31 of 2000 317 -> 803 -> 306 us, FP8 pages 288 -> 826 -> 247, one of 131072 and
+// 15 of 4096 286 -> 515 -> 265, one of 32768 and 127 of 1000 474 -> 848 -> 437, 32 x 64K with one budget of 4096 and 31 of 64 518 -> 1077 ->
+// 538, 64 whose lengths fall from 32768 by a tenth each 462 -> 680 -> 500.  512 more instead of 256: 131072 and 15 x 4096 293, the
+// budgets 623.
+// heads: KV heads; pieces: what a head's row of piece counts holds.
+inline WidePlan wide_plan_for(int batch, int heads, int rows, int pieces) {
+  const int64_t groups = (int64_t)batch * heads;
   int64_t parts = groups <= 384 && groups > 256 ? 2 : 512 / groups;
   parts = parts < 1 ? 1 : (parts > 128 ? 128 : parts);                      // (two strips of four pieces, 1024 per head)
   const int64_t most = 2 * (int64_t)equal_ranges(rows, 2 * (int)parts);
-  return most <= kWideMax ? WidePlan{(int)most, (int)parts} : WidePlan{0, 0};
+  if (most > kWideMax) return WidePlan{0, 0, 0, 0};
+  const int shared = batch * (int)parts, extra = batch * fewest_parts(rows) + (256 + heads - 1) / heads, of_one = pieces / 8 < 128 ? pieces / 8 : 128;
+  return WidePlan{(int)most, (int)parts, batch == 1 ? 0 : (shared > extra ? shared : extra), of_one > (int)parts ? of_one : (int)parts};
 }
 
 }  // namespace lfps

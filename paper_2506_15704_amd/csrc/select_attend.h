@@ -117,7 +117,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     Shape s, float* score, int32_t* slot, int64_t score_stride,
     const int32_t* __restrict__ seg_count, const int32_t* __restrict__ seg_rows_in, int nseg,
     const int32_t* __restrict__ cand, int32_t* __restrict__ cand_count, const int64_t* __restrict__ group_start,
-    int64_t* __restrict__ line_total, int range_arg, int range_parts, const uint32_t* __restrict__ bitmap, int bitmap_words,
+    int64_t* __restrict__ line_total, int range_arg, const int32_t* __restrict__ parts_of, const uint32_t* __restrict__ bitmap, int bitmap_words,
     const int32_t* __restrict__ kk, int32_t* topk_idx, float* topk_score,
     float* __restrict__ thr_state, const float* __restrict__ tau_in, KeepAll keep, const int32_t* __restrict__ skip_if,
     int32_t* __restrict__ rescored,
@@ -157,6 +157,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   }
   const float tau = tau_in[bh];                       // what the survivors have reached
   int c = kRanges ? 0 : cand_count[bg];
+  const int strips = kRanges && parts_of ? 2 * parts_of[bg] : 0;
   int kb = kk[b];
   int n = seq_lens[b];
   int S = kRanges ? 64 : *seg_rows_in;                // chosen by the scoring pass of this step
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   S = S < 64 ? 64 : S;
   // the group's slots relative to the part it starts in: piece sgm is [sgm * S - r0, (sgm + 1) * S - r0)
   const int r0 = (pg >> 32) == 0 ? (int)((uint32_t)pg % (uint32_t)S) : (int)(pg % S);
-  const RangePieces geo(n, kRanges ? range_arg : 64, kRanges ? range_parts : 0);
+  const RangePieces geo(n, kRanges ? range_arg : 64, strips);
   int np = kRanges ? geo.count : (c > 0 ? (r0 + c - 1) / S + 1 : 0);         // pieces my group was cut into
   np = np > nseg ? nseg : np;
   auto piece_lo = [&](int sgm) { return kRanges ? geo.start(sgm) : (sgm > 0 ? sgm * S - r0 : 0); };
@@ -488,7 +489,8 @@ struct FilterSelectArgs {
   int32_t* cand_count;
   const int64_t* group_start;
   int64_t* line_total;
-  int range, range_parts;
+  int range;
+  const int32_t* parts_of;
   const uint32_t* bitmap;
   int bitmap_words;
   const int32_t* k;
@@ -581,7 +583,7 @@ hipError_t launch_filter_select(const FilterSelectArgs& a, hipStream_t st) {
     if (paged != of_pages || nt != threads || (a.range > 0) != ranges || parts != of_head) return;
     hipLaunchKernelGGL(kernel, dim3(a.s.B * a.s.Hq * parts), dim3(nt), (size_t)(sizeof(AttendShared) + sel_list_bytes(a.s)), st, a.s,
                        a.score, a.slot, a.score_stride, a.seg_count, a.seg_rows, a.nseg, a.cand, a.cand_count, a.group_start,
-                       a.line_total, a.range, a.range_parts, a.bitmap, a.bitmap_words, a.k, a.topk_idx, a.topk_score, a.thr_state, a.tau, keep,
+                       a.line_total, a.range, a.parts_of, a.bitmap, a.bitmap_words, a.k, a.topk_idx, a.topk_score, a.thr_state, a.tau, keep,
                        a.skip_if, a.rescored, a.q, kv.k, 0.08838834764831845f /* 1/sqrt(128) */, a.flags, (const T*)kv.v, kv.stride_b,
                        kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, a.out);
     launched = true;

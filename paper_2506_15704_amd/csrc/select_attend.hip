@@ -37,11 +37,11 @@ hipError_t configure_select_attend(const Shape& s, int dtype, bool k_fp8, bool v
 hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, int32_t* slot,
                                        int64_t score_stride, const int32_t* seg_count, const int32_t* seg_rows, int nseg,
                                        const int32_t* cand, int32_t* cand_count, const int64_t* group_start,
-                                       int64_t* line_total, int range, int range_parts, const uint32_t* bitmap, int bitmap_words,
+                                       int64_t* line_total, int range, const int32_t* parts_of, const uint32_t* bitmap, int bitmap_words,
                                        const int32_t* k, int32_t* topk_idx, float* topk_score,
                                        float* thr_state, const float* tau, KeepAll keep, const int32_t* skip_if, int32_t* rescored,
                                        const float* q, int32_t* flags, const KvView& kv, float* out, hipStream_t st) {
-  const FilterSelectArgs a{s, score, slot, score_stride, seg_count, seg_rows, nseg, cand, cand_count, group_start, line_total, range, range_parts, bitmap,
+  const FilterSelectArgs a{s, score, slot, score_stride, seg_count, seg_rows, nseg, cand, cand_count, group_start, line_total, range, parts_of, bitmap,
                            bitmap_words, k, topk_idx, topk_score, thr_state, tau, keep, skip_if, rescored, q, flags, &kv, out};
   if (dtype == LFPS_F16) return launch_filter_select<_Float16, kKindF16>(a, st);
   if (dtype != LFPS_BF16) return hipErrorInvalidValue;          // the filtered pass exists for 16-bit and FP8 caches only

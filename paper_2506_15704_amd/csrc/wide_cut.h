@@ -42,4 +42,16 @@ struct StripWindows {
   LFPS_BOTH int to(int i, int r) const { return (i + r + 1 < end ? i + r + 1 : end - 1) - begin; }
 };
 
+constexpr int kWideMax = 65536;      // rows of a workgroup at most: their places are 16 bits
+LFPS_BOTH int fewest_parts(int n) { return n > kWideMax ? (n - 1) / kWideMax + 1 : 1; }
+
+// How many of the workgroups of a KV head a request gets.  `rows`: of its candidates, about; `all`: of those of all requests; `spare`: the
+// workgroups beyond the fewest that each request can do with.  (No more than there are: what the quotients' errors add up to, below 1e-3 of
+// a spare one, is less than what rounding down leaves.)  A batch is cut evenly unless a request has more than twice its share.
+LFPS_BOTH bool uneven(float largest, float all, int batch) { return largest * (float)batch > 2.f * all; }
+LFPS_BOTH int parts_of_request(int n, float rows, float all, int spare, int most) {
+  const int parts = fewest_parts(n) + (int)((float)spare * (rows / all));
+  return parts < most ? parts : most;
+}
+
 }  // namespace lfps

@@ -26,19 +26,14 @@ constexpr int kWideStage = 256;        // survivors a wave holds per head before
 constexpr int kWideRing = 512;         // candidates of a wave, expanded
 constexpr int kWideSpare = 16;
 
-// K rows that the candidates of all requests are, about (a lane's share of them): windows of 2 r + 2 rows around the Top-k rows of a
-// group's heads, which have a part of them in common.  Whether rows are read past the caches hangs on it, nothing else.
-__device__ __forceinline__ float candidate_rows(const Shape& s, const int32_t* seq_lens, const int32_t* kk) {
-  const float heads = s.G == 4 ? 1.6f : (s.G == 2 ? 1.3f : 1.f), window = heads * (float)(2 * s.radius + 2);
-  auto rows = [&](int b) {
-    const int n = seq_lens[b < s.B ? b : 0], k = kk[b < s.B ? b : 0];
-    const float nf = (float)(n < 1 ? 1 : (n > s.Lcap ? s.Lcap : n)), kf = (float)(k < 0 ? 0 : (k > s.kmax ? s.kmax : k));
-    return b < s.B ? nf * (1.f - __expf(-window * kf / nf)) : 0.f;
-  };
-  const int lane = threadIdx.x & 63;
-  float sum = rows(lane);
-  for (int b0 = 64; b0 < s.B; b0 += 64) sum += rows(b0 + lane);
-  return sum;
+// K rows that the candidates of a request of n rows and budget k are, about: windows of 2 r + 2 rows around the Top-k rows of a group's
+// heads, which have a part of them in common, and the recent rows and sinks.  How many workgroups a request gets hangs on it, and whether
+// rows are read past the caches.
+__device__ __forceinline__ float candidate_rows(const Shape& s, int n, int k) {
+  const float heads = s.G == 4 ? 1.6f : (s.G == 2 ? 1.3f : 1.f), window = heads * (2.f * (float)s.radius + 2.f);
+  const float nf = (float)(n < 1 ? 1 : (n > s.Lcap ? s.Lcap : n)), kf = (float)(k < 0 ? 0 : (k > s.kmax ? s.kmax : k));
+  const float others = nf - (float)s.n_recent - (float)s.n_sink;
+  return nf - (others > 0.f ? others : 0.f) * __expf(-window * kf / nf);
 }
 
 // may_once: the candidates may take more than the memory-side cache holds; rows are then read past it, see k_filter_score_bf16.
@@ -48,8 +43,8 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_wide_score(
     int64_t stride_n, KvPage page, const int32_t* __restrict__ seq_lens, const int32_t* __restrict__ prev_topk,
     const int32_t* __restrict__ kk, const float* __restrict__ thr_state, float margin, float* __restrict__ tau_out,
     const int32_t* __restrict__ skip_if, float* __restrict__ score, int32_t* __restrict__ slot_out,
-    int64_t score_stride, int32_t* __restrict__ seg_count, int nseg, uint32_t* __restrict__ bitmap, int bitmap_words,
-    WidePlan plan, float scale, int32_t* __restrict__ flags, int may_once) {
+    int64_t score_stride, int32_t* __restrict__ seg_count, int nseg, int32_t* __restrict__ parts_out, uint32_t* __restrict__ bitmap,
+    int bitmap_words, WidePlan plan, float scale, int32_t* __restrict__ flags, int may_once) {
   __shared__ float stage_score[4][G][kWideStage];
   __shared__ uint16_t stage_place[4][G][kWideStage];
   __shared__ u32x4 turn[4][StreamTile<kKind>::kLdsChunks];
@@ -59,8 +54,13 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_wide_score(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, kb = lane >> 4;
-  // grid (8 groups side by side, parts, the other groups): workgroups are dealt to the XCDs in turn, and those of a group share an L2
-  const int bg = blockIdx.z * gridDim.x + blockIdx.x, b = (int)((uint32_t)bg / (uint32_t)s.Hkv), g = bg - b * s.Hkv;
+  // grid (8 groups side by side, parts, the other groups and, behind them, workgroups for batches of uneven requests): workgroups are
+  // dealt to the XCDs in turn, and those of a group share an L2
+  const int at_z = blockIdx.z * gridDim.x + blockIdx.x;
+  const bool extra = at_z >= s.B * s.Hkv;
+  const int at_extra = ((int)blockIdx.z * (int)gridDim.x - s.B * s.Hkv) * (int)gridDim.y + (int)(blockIdx.y * gridDim.x + blockIdx.x);
+  int b = extra ? 0 : (int)((uint32_t)at_z / (uint32_t)s.Hkv);
+  const int g = extra ? (int)((uint32_t)at_extra % (uint32_t)s.Hkv) : at_z - b * s.Hkv;
 
   using Rows = RowMap<kPaged>;
   using Tile = StreamTile<kKind>;
@@ -68,9 +68,17 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_wide_score(
 
   // ---- what the workgroup needs is requested before anything is waited for
   // The entries tid, tid + 256, ... of every head's Top-k row, eight at a time, as in the range kernel.
+  // Before them the lengths and budgets of the first 64 requests, one to a lane.
+  const bool weigh = plan.slots > 0 || may_once;
+  const int b_lane = lane < s.B ? lane : 0;
+  int n_lane = 0, k_lane = 0;
+  if (weigh) {
+    n_lane = seq_lens[b_lane];
+    k_lane = kk[b_lane];
+  }
   constexpr int kEach = 8;
   int ids[kEach][G];
-  const int32_t* pt = prev_topk + ((int64_t)b * s.Hq + (int64_t)g * G) * s.kmax;
+  const int32_t* pt;
   auto fetch = [&](int j0) {
 #pragma unroll
     for (int u = 0; u < kEach; ++u) {
@@ -80,29 +88,77 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_wide_score(
       for (int h = 0; h < G; ++h) ids[u][h] = (pt + (int64_t)h * s.kmax)[at + tid < s.kmax ? at + tid : s.kmax - 1];
     }
   };
-  fetch(0);
-  int n = seq_lens[b];
-  const int k_raw = kk[b];
-  asm volatile("" ::"s"(n), "s"(k_raw));                   // (beside the entries)
+  int n, k_raw;
+  auto ask_for = [&](int request) {
+    pt = prev_topk + ((int64_t)request * s.Hq + (int64_t)g * G) * s.kmax;
+    fetch(0);
+    n = seq_lens[request];
+    k_raw = kk[request];
+    asm volatile("" ::"s"(n), "s"(k_raw));                 // (beside the entries)
+  };
+  ask_for(b);
+
+  // ---- whose rows: part `part` of `parts` of request b
+  // (256 workgroups take a CU each, and the next 256 share them: theirs are other parts, so that where the candidates crowd in one strip,
+  // that of all groups, two workgroups that have them don't share a CU.)
+  int parts = plan.parts, part = (int)((blockIdx.y + (blockIdx.z * gridDim.y * gridDim.x >> 8) * (gridDim.y / 2)) % gridDim.y);
+  float all_rows = 0.f;
+  if (weigh) {
+    auto length = [&](int request) {
+      const int of = request < 64 ? n_lane : seq_lens[request < s.B ? request : 0];
+      return of < 0 ? 0 : (of > s.Lcap ? s.Lcap : of);
+    };
+    auto rows_of = [&](int request) { return candidate_rows(s, length(request), request < 64 ? k_lane : kk[request < s.B ? request : 0]); };
+    float largest = 0.f;
+    int fewest = 0;
+    for (int c0 = 0; c0 < s.B; c0 += 64) {
+      const bool is = c0 + lane < s.B;
+      const float rows = is ? rows_of(c0 + lane) : 0.f;
+      all_rows += rows;
+      largest = fmaxf(largest, rows);
+      fewest += is ? fewest_parts(length(c0 + lane)) : 0;
+    }
+    all_rows = row16_sum(all_rows);
+    all_rows += __shfl_xor(all_rows, 16);
+    all_rows += __shfl_xor(all_rows, 32);
+    all_rows = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(all_rows)));
+    largest = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_max_in_last(largest)), 63));
+    if (plan.slots > 0 && uneven(largest, all_rows, s.B)) {
+      const int spare = plan.slots - __builtin_amdgcn_readlane(wave_inclusive_sum(fewest), 63);
+      int slot = extra ? s.B * parts + at_extra / s.Hkv : b * parts + part;
+      parts = 0;
+      for (int c0 = 0; c0 < s.B; c0 += 64) {               // (every wave of every workgroup finds the same numbers)
+        const int mine = c0 + lane < s.B ? parts_of_request(length(c0 + lane), rows_of(c0 + lane), all_rows, spare, plan.most) : 0;
+        const int upto = wave_inclusive_sum(mine), total = __builtin_amdgcn_readlane(upto, 63);
+        if (slot < total) {
+          const int at = __builtin_ctzll(__ballot(slot < upto));
+          b = c0 + at;
+          parts = __builtin_amdgcn_readlane(mine, at);
+          part = slot - (__builtin_amdgcn_readlane(upto, at) - parts);
+          break;
+        }
+        slot -= total;
+      }
+      if (parts == 0) return;
+      ask_for(b);
+    } else if (extra) {
+      return;
+    }
+  }
+  const int bg = b * s.Hkv + g;
   const int64_t head0 = (int64_t)b * s.Hq + (int64_t)g * G, my_head = head0 + (kb < G ? kb : 0);
   const float thr = thr_state[my_head];
   const int skip_word = *(skip_if ? skip_if + my_head : seq_lens);             // (no gate: any word)
-  for (int w = tid; w < plan.rows >> 5; w += kScoreThreads) bm[w] = 0u;
-  float all_rows = 0.f;
-  if (may_once) all_rows = candidate_rows(s, seq_lens, kk);
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
-  // (The strips are of the request's rows, not of the context's.  256 workgroups take a CU each, and the next 256 share them: theirs are
-  // other parts, so that where the candidates crowd in one strip, that of all groups, two workgroups that have them don't share a CU.)
-  const uint32_t round = blockIdx.z * gridDim.y * gridDim.x >> 8;
-  const int part = (int)((blockIdx.y + round * (gridDim.y / 2)) % gridDim.y);
-  const Strips mine(n, plan.parts, part);
+  const Strips mine(n, parts, part);                      // (of the request's rows, not of the context's)
   if (mine.first >= n) return;                            // (nobody reads the piece counts of such a strip)
   const int strip_words = mine.rows >> 5;
+  for (int w = tid; w < 2 * strip_words; w += kScoreThreads) bm[w] = 0u;
   const int r = s.radius;
   Op A[4];
   QueryRows query;                                         // split behind the requests for the first rows
   query.load(q, head0, G, j, kb);
-  const bool once = may_once && outgrow_cache(s, all_rows, kD * Tile::kElemBytes, (float)kKeptBytes);
+  const bool once = may_once && all_rows * (float)s.Hkv * (float)(kD * Tile::kElemBytes) > (float)kKeptBytes;
   __syncthreads();
 
   // ---- S1: my candidates as a bitmap of places
@@ -184,8 +240,8 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_wide_score(
   }
   const Piece a = piece[0], z = piece[1];                  // (places of empty pieces are not used)
   const int cnt = a.count + z.count;
-  const RangePieces geo(n, 0, 2 * plan.parts);
-  const int piece_a = 4 * part + wave, piece_z = 4 * (plan.parts + part) + wave;
+  const RangePieces geo(n, 0, 2 * parts);
+  const int piece_a = 4 * part + wave, piece_z = 4 * (parts + part) + wave;
   const bool skipped = skip_if && skip_word != 0;         // bypassed head: nothing is kept for it
   const uint64_t nans = __ballot(kb < G && isnan(thr) && !skipped);
   auto leave = [&](int kept_a, int kept) {                 // (no store before the last load: a wait for that would wait for the store)
@@ -196,6 +252,7 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_wide_score(
     if (j < 2 && kb < G && (j == 0 || mine.second < n))
       seg_count[my_head * nseg + (j == 0 ? piece_a : piece_z)] = j == 0 ? a.count << 16 | kept_a : z.count << 16 | (kept - kept_a);
     if (j == 0 && kb < G && piece_a == 0) tau_out[my_head] = thr - margin;
+    if (lane == 0 && piece_a == 0) parts_out[bg] = parts;
   };
   if (cnt == 0 || nans) {
     leave(0, 0);
@@ -326,8 +383,10 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_wide_score(
 // ----------------------------------------------------------------------------- launcher
 WidePlan wide_plan(const Shape& s) {
   const int64_t groups = (int64_t)s.B * s.Hkv;
-  if (range_rows_for(groups, s.Lcap, s.G, false)) return WidePlan{0, 0};
-  return wide_plan_for(groups, s.Lcap);
+  if (range_rows_for(groups, s.Lcap, s.G, false)) return WidePlan{0, 0, 0, 0};
+  Shape dense = s;                                          // (the counts of the exact Top-k, which has all rows for candidates)
+  dense.cand_cap = s.Lcap;
+  return wide_plan_for(s.B, s.Hkv, s.Lcap, filter_nseg(dense));
 }
 
 template <int G, bool kPaged, int kKind>
@@ -335,8 +394,8 @@ static constexpr auto wide_kernel = &k_wide_score<G, kPaged, kKind>;
 
 hipError_t launch_wide_score(const Shape& s, const float* q, const KvView& kv, const int32_t* prev_topk, const int32_t* k,
                              const float* thr_state, float margin, float* tau_out, const int32_t* skip_if, float* score, int32_t* slot_out,
-                             int64_t score_stride, int32_t* seg_count, int nseg, uint32_t* bitmap, int bitmap_words, int32_t* flags,
-                             hipStream_t st) {
+                             int64_t score_stride, int32_t* seg_count, int nseg, int32_t* parts_of, uint32_t* bitmap, int bitmap_words,
+                             int32_t* flags, hipStream_t st) {
   const int groups = s.B * s.Hkv, beside = groups % 8 == 0 ? 8 : 1;
   const int kind = kv.k_fp8 ? kKindFp8 : (kv.f16 ? kKindF16 : kKindBf16);
   const bool paged = kv.page.table != nullptr;
@@ -344,14 +403,15 @@ hipError_t launch_wide_score(const Shape& s, const float* q, const KvView& kv, c
   if (plan.rows <= 0) return hipErrorInvalidValue;
   // (cand_cap is at least what the windows can cover)
   const int may_once = (int64_t)groups * s.cand_cap * kD * (kind == kKindFp8 ? 1 : 2) > kKeptBytes;
+  const int over = (plan.slots - s.B * plan.parts) * s.Hkv, row = beside * plan.parts, more = over > 0 ? (over + row - 1) / row : 0;
   hipError_t e = hipErrorInvalidValue;
   auto launch = [&](auto heads, auto pages, auto form) {
     constexpr int G = decltype(heads)::value, kKind = decltype(form)::value;
     constexpr bool kPaged = decltype(pages)::value;
     if (s.G != G || paged != kPaged || kind != kKind) return;
-    hipLaunchKernelGGL((wide_kernel<G, kPaged, kKind>), dim3(beside, plan.parts, groups / beside), dim3(kScoreThreads), (size_t)plan.rows / 8 + kWideSpare * 4,
+    hipLaunchKernelGGL((wide_kernel<G, kPaged, kKind>), dim3(beside, plan.parts, groups / beside + more), dim3(kScoreThreads), (size_t)(plan.slots ? kWideMax : plan.rows) / 8 + kWideSpare * 4,
                        st, s, q, kv.k, kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, prev_topk, k, thr_state, margin, tau_out,
-                       skip_if, score, slot_out, score_stride, seg_count, nseg, bitmap, bitmap_words, plan,
+                       skip_if, score, slot_out, score_stride, seg_count, nseg, parts_of, bitmap, bitmap_words, plan,
                        0.08838834764831845f /* 1/sqrt(128) */, flags, may_once);
     e = hipGetLastError();
   };

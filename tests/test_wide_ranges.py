@@ -18,11 +18,25 @@ using namespace lfps;
 int main() {
   char what[16];
   while (scanf("%15s", what) == 1) {
-    if (!strcmp(what, "plan")) {                    // groups, rows, heads per group -> rows of a narrow range; the wide plan
-      long long groups; int rows, heads;
-      if (scanf("%lld %d %d", &groups, &rows, &heads) != 3) return 1;
-      const WidePlan p = wide_plan_for(groups, rows);
-      printf("%d %d %d\n", range_rows_for(groups, rows, heads, false), p.rows, p.parts);
+    if (!strcmp(what, "plan")) {                    // requests, KV heads, rows, heads per group, pieces -> rows of a narrow range; the wide plan
+      int batch, heads, rows, of_group, pieces;
+      if (scanf("%d %d %d %d %d", &batch, &heads, &rows, &of_group, &pieces) != 5) return 1;
+      const WidePlan p = wide_plan_for(batch, heads, rows, pieces);
+      printf("%d %d %d %d %d\n", range_rows_for((long long)batch * heads, rows, of_group, false), p.rows, p.parts, p.slots, p.most);
+    } else if (!strcmp(what, "share")) {            // slots, most, requests, then (rows, candidates) of each -> 0, or the parts of each
+      int slots, most, batch, spare; float all = 0.f, largest = 0.f;
+      if (scanf("%d %d %d", &slots, &most, &batch) != 3) return 1;
+      std::vector<int> n(batch); std::vector<float> rows(batch);
+      spare = slots;
+      for (int i = 0; i < batch; ++i) {
+        if (scanf("%d %f", &n[i], &rows[i]) != 2) return 1;
+        all += rows[i];
+        largest = largest > rows[i] ? largest : rows[i];
+        spare -= fewest_parts(n[i]);
+      }
+      if (!uneven(largest, all, batch)) printf("0");
+      else for (int i = 0; i < batch; ++i) printf("%d ", parts_of_request(n[i], rows[i], all, spare, most));
+      printf("\n");
     } else if (!strcmp(what, "rows")) {             // rows, parts: which rows are not one workgroup's, or not found again
       int n, parts; long long bad = 0;
       if (scanf("%d %d", &n, &parts) != 2) return 1;
@@ -62,7 +76,7 @@ def cut(tmp_path_factory):
     subprocess.run([compiler, "-std=c++17", "-O1", "-I", build.CSRC, str(where / "main.cpp"), "-o", str(where / "cut")], check=True)
 
     def ask(what, cases):
-        text = "\n".join(what + " " + " ".join(str(int(x)) for x in c) for c in cases)
+        text = "\n".join(what + " " + " ".join(str(x) for x in c) for c in cases)
         res = subprocess.run([str(where / "cut")], input=text, capture_output=True, text=True, check=True)
         return [[int(x) for x in line.split()] for line in res.stdout.splitlines()]
     return ask
@@ -72,16 +86,66 @@ def _strip_rows(n, parts):
     return max(64, (-(-n // (2 * parts)) + 63) // 64 * 64)
 
 
+def _pieces(L):
+    """Piece counts that a head has room for whatever the form: of the exact Top-k's pass over all rows."""
+    return L // ((-(-L // 1000) + 63) // 64 * 64) + 2
+
+
 def test_plans_are_what_the_kernel_can_take(cut):
     rows = sorted({x + d for e in range(21) for x in (1 << e, 3 << e) for d in (-65, -1, 0, 1, 63) if 0 < x + d <= 88 * 1024 * 8})
-    cases = [(g, n, 4) for g in list(range(1, 70)) + [127, 128, 170, 171, 256, 257, 384, 385, 512, 513, 1024, 4096, 65535] for n in rows]
-    for (groups, n, _), (_, r, parts) in zip(cases, cut("plan", cases)):
+    cases = [(B, h, n, 4, _pieces(n)) for B, h in [(g, 1) for g in list(range(1, 70)) + [127, 171, 256, 4096, 65535]] +
+             [(1, 8), (2, 8), (16, 8), (21, 8), (32, 8), (33, 8), (48, 8), (49, 8), (64, 8), (65, 8), (1024, 8), (5, 3)] for n in rows]
+    for (B, heads, n, _, pieces), (_, r, parts, slots, most) in zip(cases, cut("plan", cases)):
+        groups = B * heads
         if r == 0:
             assert n > 65536 - 128 and groups > 8, (groups, n)
             continue
         assert r <= 65536 and r % 128 == 0 and 1 <= parts <= 128, (groups, n, r, parts)       # eight pieces each, 1024 per head
+        assert parts <= most <= 128 and 8 * most <= max(pieces, 8 * parts)
+        fewest = -(-n // 65536)
+        assert fewest <= parts and (slots >= max(B * parts, B * fewest + 256 // heads) if B > 1 else slots == 0), (B, heads, n, slots)
         for m in {x for x in (1, 63, 64, 65, n // 3 + 1, n - 1, n) if 0 < x <= n}:     # a request's own strips: no longer ones
             assert 2 * _strip_rows(m, parts) <= r, (groups, n, m)
+            assert 2 * _strip_rows(m, -(-m // 65536)) <= 65536
+
+
+def _candidates(n, k, r):
+    """As the kernel estimates them, of four heads a group."""
+    return n * (1 - np.exp(-1.6 * (2 * r + 2) * k / n))
+
+
+# requests of uneven work, by length or by budget: none of the workgroups has more than its share many times over (cut evenly, the long
+# request's would have 15 to 33), and there are as many as the launch has
+@pytest.mark.parametrize("B,Hkv,L,lens,ks", [
+    (32, 8, 100000, [100000] + [2000] * 31, [2000] + [40] * 31), (16, 8, 131072, [131072] + [4096] * 15, [2048] + [64] * 15),
+    (128, 8, 32768, [1000] * 127 + [32768], [32] * 127 + [1024]), (32, 8, 65536, [65536] * 32, [64] * 9 + [4096] + [64] * 22),
+    (8, 8, 65536, [1000] * 7 + [65536], [32] * 7 + [2048]),
+    (64, 8, 32768, [max(1000, int(32768 * 0.9 ** i)) for i in range(64)], [max(16, int(655 * 0.9 ** i)) for i in range(64)])])
+def test_uneven_requests_share_the_workgroups(cut, B, Hkv, L, lens, ks):
+    ((narrow, r, parts, slots, most),) = cut("plan", [(B, Hkv, L, 4, _pieces(L))])
+    assert narrow == 0 and r > 0
+    rows = [_candidates(n, k, 4) for n, k in zip(lens, ks)]
+    (got,) = cut("share", [[slots, most, B] + [x for nr in zip(lens, rows) for x in nr]])
+    assert len(got) == B and sum(got) <= slots and min(got) >= 1
+    load = max(x / p for x, p in zip(rows, got)) * 512 / Hkv / sum(rows)      # in shares of the chip's 512
+    even = max(rows) / parts * 512 / Hkv / sum(rows)
+    assert load < 0.5 * even and load < 4.5, (load, even)
+
+
+def test_shares_are_never_more_than_there_are(cut):
+    rng = np.random.default_rng(3)
+    cases = []
+    for _ in range(500):
+        B, Hkv, L = int(rng.integers(2, 400)), int(rng.choice([1, 2, 4, 8])), int(64 * 11000 ** rng.random())
+        cases.append((B, Hkv, L, [max(1, int(L * x)) for x in rng.random(B) ** rng.integers(1, 9)], rng.random(B) ** rng.integers(1, 20)))
+    plans = cut("plan", [(B, Hkv, L, 4, _pieces(L)) for B, Hkv, L, _, _ in cases])
+    took = [(c, p) for c, p in zip(cases, plans) if p[1]]
+    shares = cut("share", [[p[3], p[4], c[0]] + [x for nr in zip(c[3], (n * f for n, f in zip(c[3], c[4]))) for x in nr] for c, p in took])
+    assert len(took) > 100 and sum(len(x) > 1 for x in shares) > 50
+    for (c, p), got in zip(took, shares):
+        if len(got) > 1:
+            assert sum(got) <= p[3] and max(got) <= p[4]
+            assert all(2 * _strip_rows(n, parts) <= 65536 for n, parts in zip(c[3], got))
 
 
 @pytest.mark.parametrize("n,parts", [(1, 64), (70, 4), (4096, 1), (33006, 4), (140006, 64), (65024, 1), (131076, 4), (720896, 128), (5000, 3),
@@ -102,7 +166,7 @@ def test_every_row_is_one_workgroups(cut, n, parts):
 @pytest.mark.parametrize("B,Hkv,L,part", [(8, 8, 32768, 0.125), (16, 8, 131072, 0.125), (16, 8, 131072, 0.25), (2, 8, 131072, 0.125),
                                           (32, 8, 65536, 0.125), (1, 8, 140000, 0.25)])
 def test_crowded_rows_are_shared(cut, B, Hkv, L, part):
-    ((narrow, r, parts),) = cut("plan", [(B * Hkv, L, 4)])
+    ((narrow, r, parts, _, _),) = cut("plan", [(B, Hkv, L, 4, _pieces(L))])
     assert narrow == 0 and r > 0
     crowd = np.arange(int(L * (1 - part)), L)
     load = np.bincount(crowd // _strip_rows(L, parts) % parts, minlength=parts)
@@ -118,9 +182,9 @@ STEPS = [
 
 
 def test_the_steps_below_are_wide(cut):
-    got = cut("plan", [(B * Hkv, L + 6, Hq // Hkv) for B, Hq, Hkv, L, *_ in STEPS])
-    assert all(narrow == 0 and r > 0 for narrow, r, _ in got)
-    assert {p for _, _, p in got} >= {1, 2, 4, 32, 64, 128} and max(r for _, r, _ in got) == 65024
+    got = cut("plan", [(B, Hkv, L + 6, Hq // Hkv, _pieces(L + 6)) for B, Hq, Hkv, L, *_ in STEPS])
+    assert all(narrow == 0 and r > 0 for narrow, r, *_ in got)
+    assert {x[2] for x in got} >= {1, 2, 4, 32, 64, 128} and max(x[1] for x in got) == 65024
     # of the last one the candidates outgrow 256 MiB: heads' windows of 2 r + 2 rows around k random rows, 256 bytes each
     B, Hq, Hkv, L, k, r = STEPS[-1][:6]
     assert B * Hkv * L * (1 - np.exp(-(2 * r + 2) * k / L)) * 256 > 256 << 20
@@ -131,6 +195,52 @@ def test_the_steps_below_are_wide(cut):
 def test_steps(B, Hq, Hkv, L, k, r, n_recent, n_sink, dtype, page):
     from tests.test_gpu_ranges import test_memoryless_steps as steps
     steps(B, Hq, Hkv, L, k, r, n_recent, n_sink, dtype, page)
+
+
+# one long request among short ones and of one row, one large budget among small ones, a request that needs two workgroups for its places,
+# more requests than a wave has lanes: against an unfiltered context, and the same bits when the batch changes between steps
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hq,Hkv,L,lens,ks,dtype,page", [
+    (8, 8, 100000, [100000, 1, 2000, 64, 65] + [700] * 7, [1500, 1, 40, 5, 64] + [30] * 7, "bf16", 0),
+    (32, 8, 140000, [300, 139000, 20000], [20, 1000, 300], "fp8", 16), (16, 8, 16500, [16500] * 9, [30] * 8 + [900], "f16", 64),
+    (4, 4, 6000, [100] * 69 + [6000] + [33] * 7, [9] * 69 + [400] + [3] * 7, "bf16", 16)])
+def test_uneven_steps(Hq, Hkv, L, lens, ks, dtype, page, cut):
+    import torch
+    from tests.harness import DEV
+    from tests.test_gpu_ranges import _cache, _pair, _view
+    B, k = len(lens), max(ks)
+    ((narrow, r, parts, slots, most),) = cut("plan", [(B, Hkv, L, Hq // Hkv, _pieces(L))])
+    assert narrow == 0 and r > 0
+    heads = {1: 1.0, 2: 1.3, 4: 1.6}[Hq // Hkv]
+    rows = [n - (n - 1) * np.exp(-heads * 10 * x / n) for n, x in zip(lens, ks)]
+    assert len(cut("share", [[slots, most, B] + [x for nr in zip(lens, rows) for x in nr]])[0]) == B          # (uneven)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L + k)
+    cache = _cache(B, Hkv, L, dtype, page, g)
+    a, b = _pair(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="bf16" if dtype == "fp8" else dtype, k_fp8=dtype == "fp8", max_seq_len=L,
+                 max_k=k, radius=4)
+    q = torch.randn((B, Hq, 128), device=DEV, generator=g)
+    prev = torch.full((B, Hq, k), -1, dtype=torch.int32, device=DEV)
+    kt = torch.tensor(ks, dtype=torch.int32, device=DEV)
+    a.lfps_exact_topk(q, _view(a, cache, torch.tensor(lens, dtype=torch.int32, device=DEV)), kt, prev)
+    for t in range(4):
+        q = q * 0.02 if t == 3 else q + 0.1 * torch.randn((B, Hq, 128), device=DEV, generator=g)
+        seq = torch.tensor(lens if t != 2 else [min(lens)] * B, dtype=torch.int32, device=DEV)        # (an even batch in between)
+        res = []
+        for ctx in (a, b):
+            idx = torch.full((B, Hq, k), -5, dtype=torch.int32, device=DEV)
+            sc, out = torch.full((B, Hq, k), -5.0, device=DEV), torch.full((B, Hq, 128), -5.0, device=DEV)
+            cnt = torch.full((B, Hkv), -5, dtype=torch.int32, device=DEV)
+            ctx.lfps_step(q, _view(ctx, cache, seq), prev, kt, idx, out, sc)
+            ctx.lfps_copy_cand_count(cnt)
+            assert ctx.lfps_poll_status() == 0
+            res.append((idx, sc, out, cnt))
+        for x, y, name in zip(*res, ("index", "score", "output", "candidate count")):
+            assert torch.equal(x, y), (name, t, int((x != y).sum()))
+        if t != 2:
+            prev = res[0][0]
+    a.close()
+    b.close()
 
 
 # requests that are far below the context's capacity have strips of their own length: the same bits as in a context without that room
