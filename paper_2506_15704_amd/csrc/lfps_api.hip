@@ -702,7 +702,7 @@ int lfps_exact_topk(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int3
     sd.cand_cap = s.Lcap;                 // the "candidates" of the dense pass are all rows of a group
     int64_t* x_total = ctx->x_start + (int64_t)s.B * s.Hkv;
     LAUNCH(ctx, LFPS_KERNEL_GATHER_SCORE, st,
-           launch_sample_score(s, q, v, k, kExactSampleRows, filter_list_cap(s), ctx->x_cnt, ctx->x_start, ctx->x_ns, ctx->x_rank, ctx->score,
+           launch_sample_score(s, q, v, k, kExactSampleRows, filter_list_cap(sd), ctx->x_cnt, ctx->x_start, ctx->x_ns, ctx->x_rank, ctx->score,
                                s.score_stride, ctx->flags, st));
     LAUNCH(ctx, LFPS_KERNEL_SELECT, st,      // the rank-th best sample score of every head -> thr_x (the rows go to scratch)
            launch_select(s, ctx->score, s.score_stride, nullptr, ctx->x_ns, ctx->x_rank, ctx->slot, nullptr, ctx->thr_x,

@@ -159,7 +159,8 @@ hipError_t launch_wide_score(const Shape& s, const float* q, const KvView& kv, c
 // the candidates are in bitmap), and cand_count is written.
 // keep: a head with fewer than keep.ratio * k candidates, and no more than keep.most, leaves -inf in thr_state instead of its
 // k-th best score; keep.fits [B, Hq] (or NULL) receives whether it had no more than keep.most, and a bypassed head (skip_if)
-// leaves -inf unless it has a score and had more.  The launchers set most: half of filter_list_cap.
+// leaves -inf unless it has a score and had more.  The launchers set most: half of filter_list_cap,
+// or all of it where it holds the candidates of any step.
 struct KeepAll {
   int ratio;
   int32_t* fits;

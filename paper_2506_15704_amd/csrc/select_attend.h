@@ -61,12 +61,16 @@ constexpr int kSelRowsMax = 16384;    // selected rows of a head that pass throu
 // 330 to 1311 2 % faster for four steps, but there a list of 4096 overflows, for every head at once, when the scores grow
 // from one step to the next.  (The unfiltered pass of a head left short has half the waves: steps in which 2 % of the heads
 // take it, k = 400, 193 against 175 us at 1024 heads.)
-// Up to 64 heads with budgets of at most 512: 512 threads (with four workgroups a head).  A head's uniform work is done by every wave
-// on its own, and there are half as many; steps with 1024 -> 512, us: 1 x 3000, k = 48 16.5 -> 15.4, 1 x 16000, k = 256 17.3 -> 17.0,
-// 1 x 32K, k = 512 21.2 -> 20.7, FP8 2 x 8000, k = 250 16.7 -> 16.4; k = 1024 27.0 -> 27.7, and with one workgroup a head within 1 %.
+// Up to 64 heads with budgets of at most 512, whose candidates all fit the list of 512 threads: 512 (with four workgroups a head).  A
+// head's uniform work is done by every wave on its own, and there are half as many; steps with 1024 -> 512, us: 1 x 3000, k = 48 16.5 ->
+// 15.4, 1 x 16000, k = 256 17.3 -> 17.0, FP8 2 x 8000, k = 250 16.7 -> 16.4; k = 1024 27.0 -> 27.7, and with one workgroup a head within 1 %.
+// With more candidates the unfiltered pass, of half the waves, costs what the other steps gain (four steps of 1 x 32K, k = 512, all heads
+// of two of them short 356 -> 390), and a list half as long overflows where scores grow (2 x 120000, 34 rows around each of 512, scores
+// times three 1280 -> 2620).
+inline bool few_heads_short_lists(const Shape& s) { return s.B * s.Hq <= 64 && s.kmax <= 512 && s.cand_cap <= kRegElems * 512; }
 inline int filter_select_threads(const Shape& s) {
   const int heads = s.B * s.Hq;
-  if (heads <= 64 && s.kmax <= 512) return 512;
+  if (few_heads_short_lists(s)) return 512;
   if (heads > 512 && kRegElems * 256 >= 4 * s.kmax) return 256;
   return heads <= 256 || kRegElems * 512 < 2 * s.kmax ? 1024 : 512;
 }
@@ -476,6 +480,8 @@ inline int select_attend_cache(const Shape& s) {
   return ce > kRegElems * kSelThreads ? ce : 0;
 }
 
+inline int most_kept(const Shape& s) { return few_heads_short_lists(s) ? filter_list_cap(s) : filter_list_cap(s) / 2; }
+
 // What the launches below are made from.
 struct FilterSelectArgs {
   Shape s;
@@ -554,10 +560,12 @@ inline hipError_t raise_lds(const void* kernel, int bytes) {
 }
 template <typename T, int kKind>
 hipError_t configure_filter_select(const Shape& s) {
-  const int nt = filter_select_threads(s), parts = attend_parts(s);
+  const int parts = attend_parts(s);
+  Shape dense = s;                                         // (the exact Top-k, with all rows for candidates)
+  dense.cand_cap = s.Lcap;
   hipError_t e = hipSuccess;
   each_filter_select<T, kKind>([&](auto kernel, bool, int threads, bool, int of_head) {
-    if (e == hipSuccess && threads == nt && (of_head == parts || of_head == 1))
+    if (e == hipSuccess && (threads == filter_select_threads(s) || threads == filter_select_threads(dense)) && (of_head == parts || of_head == 1))
       e = raise_lds((const void*)kernel, (int)sizeof(AttendShared) + kSelRowsMax * (int)sizeof(SelRow));
   });
   return e;
@@ -577,7 +585,7 @@ hipError_t launch_filter_select(const FilterSelectArgs& a, hipStream_t st) {
   const bool paged = a.kv->page.table != nullptr;
   const KvView& kv = *a.kv;
   KeepAll keep = a.keep;
-  keep.most = filter_list_cap(a.s) / 2;
+  keep.most = most_kept(a.s);
   bool launched = false;
   each_filter_select<T, kKind>([&](auto kernel, bool of_pages, int threads, bool ranges, int of_head) {
     if (paged != of_pages || nt != threads || (a.range > 0) != ranges || parts != of_head) return;
@@ -597,7 +605,7 @@ hipError_t launch_select_only(const SelectArgs& a, hipStream_t st) {
   const bool paged = a.kv->page.table != nullptr;
   const KvView& kv = *a.kv;
   KeepAll keep = a.keep;
-  keep.most = filter_list_cap(a.s) / 2;
+  keep.most = most_kept(a.s);
   each_select<T>([&](auto kernel, bool of_pages, int of_head) {
     if (paged != of_pages || parts != of_head) return;
     hipLaunchKernelGGL(kernel, dim3(a.s.B * a.s.Hq * parts), dim3(kSelThreads), (size_t)lds, st, a.s, a.score, a.score_stride, a.cand,

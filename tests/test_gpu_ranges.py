@@ -268,3 +268,32 @@ def test_table_steps_through_the_separate_kernels(B, Hq, Hkv, L, k, r, dtype, pa
             assert torch.equal(x, y), (name, t, int((x != y).sum()))
     for ctx in pair:
         ctx.close()
+
+
+def test_scores_that_grow_do_not_overflow_the_list():
+    """Few heads with a small budget but many candidates: of the rows that reach the threshold of a step with smaller scores there may be
+    more than 512 threads can hold, and as many as 1024 can: no head is rescored."""
+    L, k, r = 65536, 512, 20
+    g = torch.Generator(device=DEV)
+    g.manual_seed(9)
+    cache = _cache(1, 8, L, "bf16", 0, g)
+    a, b = _pair(batch=1, n_q_heads=32, n_kv_heads=8, kv_dtype="bf16", max_seq_len=L, max_k=k, radius=r)
+    seq, ks = (torch.tensor([x], dtype=torch.int32, device=DEV) for x in (L, k))
+    q = torch.randn((1, 32, 128), device=DEV, generator=g)
+    idx = [torch.full((1, 32, k), -1, dtype=torch.int32, device=DEV) for _ in range(4)]
+    sc, out = torch.zeros((1, 32, k), device=DEV), torch.zeros((2, 1, 32, 128), device=DEV)
+    a.lfps_exact_topk(q, _view(a, cache, seq), ks, idx[0])
+    a.lfps_step(q, _view(a, cache, seq), idx[0], ks, idx[1], out[0], sc)
+    scores = 4 * torch.einsum("hgd,hnd->hgn", q.view(8, 4, 128), cache[0][0].float()) / 128 ** 0.5
+    near = torch.zeros((8, L + 2 * r + 1), dtype=torch.bool, device=DEV)      # candidates: the windows of a group's heads
+    for d in range(2 * r + 2):
+        near.scatter_(1, idx[1].view(8, -1).long() + d, True)
+    survivors = ((scores >= sc.min(dim=2).values.view(8, 4, 1) - 0.125) & near[:, None, r:L + r]).sum(dim=2)
+    assert 8192 < int(survivors.min()) and int(survivors.max()) < 16384, (int(survivors.min()), int(survivors.max()))
+    assert a.lfps_poll_rescored() in (0, 32)                                     # (the first step may have kept everything)
+    for ctx, at in ((a, 2), (b, 3)):
+        ctx.lfps_step(4 * q, _view(ctx, cache, seq), idx[1], ks, idx[at], out[at - 2])
+    assert a.lfps_poll_rescored() == 0
+    assert torch.equal(idx[2], idx[3]) and torch.equal(out[0], out[1])
+    a.close()
+    b.close()
