@@ -1,46 +1,19 @@
 // Device code shared by the kernels that end in sparse attention (Eq. 1 over a head's selected rows).
 #pragma once
+#include "head_place.h"
 #include "lfps_internal.h"
 
 #include <type_traits>
 
 namespace lfps {
 
-// Workgroups are dealt to the 8 XCDs round-robin (workgroup i runs on XCD i % 8) and every XCD has
-// its own L2.  The heads of a KV group select largely the same rows, so the G workgroups of a group
-// are given ids that differ by multiples of 8: they run on one XCD at about the same time and a V
-// row fetched for one head is an L2 hit for the others.
-struct HeadPlace {
-  int bg, b, g, bh;                                // KV group, request, KV head, query head (b * Hq + h)
-  int in_group;                                    // which of the group's heads
-  int part;                                        // which kParts-th of the output row's channels the workgroup makes
-};
-template <int kParts>
-__device__ __forceinline__ HeadPlace place_of_block(const Shape& s, uint32_t block) {
-  const int shift = s.G >> 1;                      // log2 of 1, 2 or 4 heads
-  const bool dealt = (s.B * s.Hkv) % 8 == 0;       // KV groups in the launch
-  const uint32_t slot = dealt ? block >> 3 : block, head = slot / kParts;
-  HeadPlace p;
-  p.part = (int)(slot % kParts);
-  p.in_group = (int)(head & (uint32_t)(s.G - 1));
-  p.bg = (int)(dealt ? (head >> shift) * 8 + (block & 7) : head >> shift);
-  p.b = (int)((uint32_t)p.bg / (uint32_t)s.Hkv);
-  p.g = p.bg - p.b * s.Hkv;
-  p.bh = (p.bg << shift) + p.in_group;
-  return p;
-}
-
 // The list of a head is cut into kAttendChunks equal chunks (a multiple of 64 entries each); every chunk's partial
 // sum is formed by one wave in list order and the chunks are added in chunk order, whatever the number of waves
 // (a wave takes kAttendChunks / NW consecutive chunks): the output row does not depend on the launch shape.
 constexpr int kAttendChunks = 16;
 
-// Workgroups per head, each for its part of the channels: one CU takes rows in at 64 bytes a cycle, and few heads leave most of the
-// chip idle.  Four, while every one has a CU of its own.  Each makes the head's list, which costs no time, and the sums of a channel
-// are made as by one workgroup: the same bits.  One -> four, us: steps of 1 x 32K, k = 1024 25.5 -> 24.2, exact Top-k with its
-// attention 34.6 -> 33.2; steps of 1 x 128K, k = 4096 74.8 -> 66.0, 2 x 8000 FP8, k = 128 16.7 -> 16.3.  Two for 128 heads: bf16 4 x
-// 32K 54.7 -> 55.0, 4 x 64K 61.9 -> 61.3, FP8 35.1 -> 34.5, not worth the kernels.
-inline int attend_parts(const Shape& s) { return s.B * s.Hq <= 64 ? 4 : 1; }
+inline int attend_parts(const Shape& s) { return attend_parts_for(s.B * s.Hq); }
+inline int attend_blocks(const Shape& s, int parts) { return attend_blocks_for(s.B * s.Hkv, s.G, parts); }
 
 // N consecutive elements of a row, as Raw8.
 template <typename T, int N>

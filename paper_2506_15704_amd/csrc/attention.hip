@@ -28,8 +28,9 @@ __global__ __launch_bounds__(kSparseWaves * 64) void k_sparse_attn(Shape s, cons
                                                                 const int32_t* __restrict__ skip_if) {
   __shared__ AttendShared sm;
   request_arguments<decltype(&k_sparse_attn<T, kSparseWaves, kPaged, kParts>)>();
-  const HeadPlace at = place_of_block<kParts>(s, blockIdx.x);
+  const HeadPlace at = place_of_block_for<kParts>(s.B, s.Hkv, s.G, blockIdx.x);
   const int bh = at.bh, b = at.b, g = at.g;
+  if (at.none) return;
   if (skip_if && skip_if[bh] != 0) return;            // bypassed head: the gate wrote its output row
   int n = seq_lens[b];
   n = n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
@@ -47,7 +48,7 @@ static hipError_t launch_sparse_t(const Shape& s, const KvView& kv, const int32_
   const int heads = s.B * s.Hq;
   const T* V = (const T*)kv.v;
 #define LFPS_LAUNCH_SPARSE_P(NW, PAGED, PARTS)                                                                           \
-  hipLaunchKernelGGL((k_sparse_attn<T, NW, PAGED, PARTS>), dim3(heads * PARTS), dim3(NW * 64), 0, st, s, V, kv.stride_b, \
+  hipLaunchKernelGGL((k_sparse_attn<T, NW, PAGED, PARTS>), dim3(attend_blocks(s, PARTS)), dim3(NW * 64), 0, st, s, V, kv.stride_b, \
                      kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, idx, idx_score, k, out, skip_if)
 #define LFPS_LAUNCH_SPARSE(NW, PARTS)          \
   if (kv.page.table) {                         \

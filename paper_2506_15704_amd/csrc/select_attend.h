@@ -143,8 +143,9 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   SelRow* list = reinterpret_cast<SelRow*>(dyn + sizeof(AttendShared));
   if (!kRanges && blockIdx.x == 0 && threadIdx.x == 0) *line_total = 0;   // the scoring pass that read it has finished
   request_arguments<decltype(&k_filter_select_attend<T, kPaged, kKind, NT, kRanges, kParts>)>();
-  const HeadPlace at = place_of_block<kParts>(s, blockIdx.x);     // the heads of a KV group on one XCD: they share V rows in its L2
+  const HeadPlace at = place_of_block_for<kParts>(s.B, s.Hkv, s.G, blockIdx.x);     // the heads of a KV group on one XCD: they share V rows in its L2
   const int bh = at.bh, b = at.b, g = at.g, bg = at.bg, part = at.part;
+  if (at.none) return;
   const bool writes = kParts == 1 || part == 0;
   const bool leads = writes && at.in_group == 0;     // leaves what the group's heads have in common
   const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -386,8 +387,9 @@ __global__ __launch_bounds__(kSelThreads) void k_select_attend(
   extern __shared__ char dyn[];                     // the list of selected rows, or before it the scores of a long row
   SelRow* list = reinterpret_cast<SelRow*>(dyn);
   request_arguments<decltype(&k_select_attend<T, kPaged, kParts>)>();
-  const HeadPlace at = place_of_block<kParts>(s, blockIdx.x);
+  const HeadPlace at = place_of_block_for<kParts>(s.B, s.Hkv, s.G, blockIdx.x);
   const int bh = at.bh, b = at.b, g = at.g, part = at.part;
+  if (at.none) return;
   const bool writes = kParts == 1 || part == 0;
   const int tid = threadIdx.x;
   if (skip_if && skip_if[bh] != 0) {                // bypassed head: its rows were written by the gate
@@ -604,7 +606,7 @@ hipError_t launch_filter_select(const FilterSelectArgs& a, hipStream_t st) {
   bool launched = false;
   each_filter_select<T, kKind>([&](auto kernel, bool of_pages, int threads, bool ranges, int of_head) {
     if (paged != of_pages || nt != threads || (a.range > 0) != ranges || parts != of_head) return;
-    hipLaunchKernelGGL(kernel, dim3(a.s.B * a.s.Hq * parts), dim3(nt), (size_t)(sizeof(AttendShared) + sel_list_bytes(a.s)), st, a.s,
+    hipLaunchKernelGGL(kernel, dim3(attend_blocks(a.s, parts)), dim3(nt), (size_t)(sizeof(AttendShared) + sel_list_bytes(a.s)), st, a.s,
                        a.score, a.slot, a.score_stride, a.seg_count, a.seg_rows, a.nseg, a.cand, a.cand_count, a.group_start,
                        a.line_total, a.range, a.parts_of, a.bitmap, a.bitmap_words, a.k, a.topk_idx, a.topk_score, a.thr_state, a.tau, keep,
                        a.skip_if, a.rescored, a.q, kv.k, 0.08838834764831845f /* 1/sqrt(128) */, a.flags, (const T*)kv.v, kv.stride_b,
@@ -623,7 +625,7 @@ hipError_t launch_select_only(const SelectArgs& a, hipStream_t st) {
   keep.most = most_kept(a.s);
   each_select<T>([&](auto kernel, bool of_pages, int of_head) {
     if (paged != of_pages || parts != of_head) return;
-    hipLaunchKernelGGL(kernel, dim3(a.s.B * a.s.Hq * parts), dim3(kSelThreads), (size_t)lds, st, a.s, a.score, a.score_stride, a.cand,
+    hipLaunchKernelGGL(kernel, dim3(attend_blocks(a.s, parts)), dim3(kSelThreads), (size_t)lds, st, a.s, a.score, a.score_stride, a.cand,
                        a.cand_count, a.k, a.topk_idx, a.topk_score, cache, a.thr_state, keep, a.skip_if, (const T*)kv.v, kv.stride_b,
                        kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, a.out);
   });

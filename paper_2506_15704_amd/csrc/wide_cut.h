@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #ifdef __HIPCC__
+#include <hip/hip_runtime.h>
 #define LFPS_BOTH __host__ __device__ __forceinline__
 #else
 #define LFPS_BOTH inline
