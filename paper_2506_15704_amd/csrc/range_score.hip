@@ -14,7 +14,7 @@
 // Why one kernel: as two, a step of 8 groups x 32K rows spent 7.8 + 14.5 us here, of which the rows themselves are 5 us;
 // the rest is two launches and the round trips
 // candidates -> list -> geometry -> list -> rows.  Together: 13.7 us, 12.2 with the rows through LDS:
-// every load instruction covers whole rows (StreamTile, here with ordinary loads).  With a lane's own 64 bytes of a row in four
+// every load instruction covers whole rows (StreamTile, here with ordinary loads; 16-bit keys).  With a lane's own 64 bytes of a row in four
 // loads, each of these touches 32 cache lines instead of 8, and with one tile per wave and eight to sixteen waves per CU all asking at
 // once the address unit was what the first rows waited for.  11.4 us with the entries of a Top-k row strided over the lanes and the
 // survivors of all heads written side by side, 9.2 with length and budget asked for beside the Top-k entries.  (A stage of 160 survivors makes room for it at four workgroups per CU.)
@@ -36,7 +36,7 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
     int range, float scale, int32_t* __restrict__ flags) {
   __shared__ float stage_score[4][G][kRangeStage];
   __shared__ uint16_t stage_slot[4][G][kRangeStage];          // relative to the range's first row
-  __shared__ u32x4 turn[4][StreamTile<kKind>::kLdsChunks];
+  __shared__ u32x4 turn[4][kKind == kKindFp8 ? 1 : StreamTile<kKind>::kLdsChunks];
   __shared__ uint32_t bm[kRangeMax / 32];
   __shared__ int wave_tot[4];
   extern __shared__ uint16_t list[];                     // the range's candidates, relative to its first row
@@ -48,7 +48,9 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
   const int bg = blockIdx.z * gridDim.x + blockIdx.x, b = (int)((uint32_t)bg / (uint32_t)s.Hkv), g = bg - b * s.Hkv;
 
   using Rows = RowMap<kPaged>;
-  using Tile = StreamTile<kKind>;
+  // (FP8 rows, a line each, come in two loads of a lane's own bytes: four steps of 1 x 32K, k = 400 71.4 -> 69.0 us, of 8 x 16000 110.6 ->
+  // 106.7; with the cache in host memory 1288 -> 1126.)
+  using Tile = std::conditional_t<kKind == kKindFp8, KTile<kKind>, StreamTile<kKind>>;
   using Op = typename Tile::Operand;
 
   // ---- what the workgroup needs is requested before anything is waited for
@@ -254,7 +256,9 @@ __global__ __launch_bounds__(kScoreThreads, 4) void k_range_score(
     } else {
       phys = lookup(id);
     }
-    Bt.fetch(Kbg, phys_now, lane, [&](int p) { return Rows::offset(page, p, stride_b, stride_n) * ES; }, false);
+    auto offset = [&](int p) { return Rows::offset(page, p, stride_b, stride_n) * ES; };
+    if constexpr (kKind == kKindFp8) Bt.fetch(Kbg, phys_now, lane, offset);
+    else Bt.fetch(Kbg, phys_now, lane, offset, false);
   };
   Tile B0;
   int f0;
