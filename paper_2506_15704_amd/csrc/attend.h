@@ -12,7 +12,7 @@ namespace lfps {
 // (a wave takes kAttendChunks / NW consecutive chunks): the output row does not depend on the launch shape.
 constexpr int kAttendChunks = 16;
 
-inline int attend_parts(const Shape& s) { return attend_parts_for(s.B * s.Hq); }
+inline int attend_parts(const Shape& s, const KvView& kv) { return attend_parts_for(s.B * s.Hq, kv.v_on_device); }
 inline int attend_blocks(const Shape& s, int parts) { return attend_blocks_for(s.B * s.Hkv, s.G, parts); }
 
 // N consecutive elements of a row, as Raw8.

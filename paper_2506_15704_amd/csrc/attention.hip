@@ -56,7 +56,7 @@ static hipError_t launch_sparse_t(const Shape& s, const KvView& kv, const int32_
   } else {                                     \
     LFPS_LAUNCH_SPARSE_P(NW, false, PARTS);    \
   }
-  if (attend_parts(s) == 4) {
+  if (attend_parts(s, kv) == 4) {
     LFPS_LAUNCH_SPARSE(16, 4)
   } else if (heads * 16 <= 4096) {
     LFPS_LAUNCH_SPARSE(16, 1)

@@ -11,7 +11,9 @@ namespace lfps {
 // 32K 54.7 -> 55.0, 4 x 64K 61.9 -> 61.3, FP8 35.1 -> 34.5, not worth the kernels.  Numbers of groups that are no multiple of 8, four steps,
 // one -> four on any XCD -> four on one: 12 groups x 32K, k = 1024 113.8 -> 118.9 -> 111.8, x 128K, k = 4096 384 -> 369 -> 353, FP8 97.7 ->
 // 104.7 -> 95.0 and 237 -> 265 -> 227; 4 groups x 32K 80.6 -> 78.5 -> 77.0, x 128K 197.5 -> 180.6 -> 178.2, FP8 163 -> 155 -> 149.5.
-inline int attend_parts_for(int heads) { return heads <= 64 ? 4 : 1; }
+// With values in host memory one: parts of a row are requests of their own over the host link (1 x 32K bf16, k = 1024, select and attention
+// 152 us with one, 197 with four).
+inline int attend_parts_for(int heads, bool v_on_device) { return heads <= 64 && v_on_device ? 4 : 1; }
 
 // Workgroups are dealt to the 8 XCDs round-robin (workgroup i runs on XCD i % 8) and every XCD has its own L2.  The heads of a KV group
 // select largely the same rows, so the heads * kParts workgroups of a group are given ids that differ by multiples of 8: they run on

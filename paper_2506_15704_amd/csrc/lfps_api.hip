@@ -6,6 +6,7 @@
 #include <mutex>
 #include <new>
 
+#include "head_place.h"
 #include "lfps_internal.h"
 
 using namespace lfps;
@@ -223,6 +224,13 @@ int check_kv_cfg(const lfps_config& cfg, char* err, size_t errn, const lfps_kv* 
   out->k_fp8 = cfg.k_fp8 != 0;
   out->v_fp8 = cfg.v_fp8 != 0;
   out->f16 = cfg.kv_dtype == LFPS_F16;
+  out->v_on_device = true;
+  if (need_v && attend_parts_for(cfg.batch * cfg.n_q_heads, true) > 1) {     // (asked only where something hangs on it)
+    hipPointerAttribute_t at;
+    const hipError_t e = hipPointerGetAttributes(&at, kv->v);
+    if (e != hipSuccess) (void)hipGetLastError();
+    out->v_on_device = e == hipSuccess && at.type == hipMemoryTypeDevice;
+  }
   if (kv->block_table) {
     const int64_t bs = kv->block_size;
     if (bs < 1 || bs > 65536 || (bs & (bs - 1))) BAD("paged kv: block_size must be a power of two in [1, 65536]");

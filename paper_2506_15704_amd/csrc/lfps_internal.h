@@ -41,6 +41,7 @@ struct KvView {
   bool k_fp8;   // K elements are one byte (OCP FP8 E4M3)
   bool v_fp8;   // V elements are one byte; otherwise V has the cache dtype
   bool f16;     // the cache dtype is fp16 (K and V)
+  bool v_on_device;   // the values are known to be in device memory
 };
 
 // Row addressing of the two cache layouts, chosen at compile time.  A logical row i of request b

@@ -577,12 +577,11 @@ inline hipError_t raise_lds(const void* kernel, int bytes) {
 }
 template <typename T, int kKind>
 hipError_t configure_filter_select(const Shape& s) {
-  const int parts = attend_parts(s);
   Shape dense = s;                                         // (the exact Top-k, with all rows for candidates)
   dense.cand_cap = s.Lcap;
   hipError_t e = hipSuccess;
-  each_filter_select<T, kKind>([&](auto kernel, bool, int threads, bool, int of_head) {
-    if (e == hipSuccess && (threads == filter_select_threads(s) || threads == filter_select_threads(dense)) && (of_head == parts || of_head == 1))
+  each_filter_select<T, kKind>([&](auto kernel, bool, int threads, bool, int) {
+    if (e == hipSuccess && (threads == filter_select_threads(s) || threads == filter_select_threads(dense)))
       e = raise_lds((const void*)kernel, (int)sizeof(AttendShared) + kSelRowsMax * (int)sizeof(SelRow));
   });
   return e;
@@ -590,15 +589,15 @@ hipError_t configure_filter_select(const Shape& s) {
 template <typename T>
 hipError_t configure_select_only(const Shape& s) {
   hipError_t e = hipSuccess;
-  each_select<T>([&](auto kernel, bool, int of_head) {
-    if (e == hipSuccess && of_head == attend_parts(s)) e = raise_lds((const void*)kernel, kCacheElems * 4);
+  each_select<T>([&](auto kernel, bool, int) {
+    if (e == hipSuccess) e = raise_lds((const void*)kernel, kCacheElems * 4);
   });
   return e;
 }
 
 template <typename T, int kKind>
 hipError_t launch_filter_select(const FilterSelectArgs& a, hipStream_t st) {
-  const int nt = filter_select_threads(a.s), parts = a.out ? attend_parts(a.s) : 1;
+  const int nt = filter_select_threads(a.s), parts = a.out ? attend_parts(a.s, *a.kv) : 1;
   const bool paged = a.kv->page.table != nullptr;
   const KvView& kv = *a.kv;
   KeepAll keep = a.keep;
@@ -617,7 +616,7 @@ hipError_t launch_filter_select(const FilterSelectArgs& a, hipStream_t st) {
 }
 template <typename T>
 hipError_t launch_select_only(const SelectArgs& a, hipStream_t st) {
-  const int cache = select_attend_cache(a.s), parts = attend_parts(a.s);
+  const int cache = select_attend_cache(a.s), parts = attend_parts(a.s, *a.kv);
   const int lds = cache * 4 > sel_list_bytes(a.s) ? cache * 4 : sel_list_bytes(a.s);
   const bool paged = a.kv->page.table != nullptr;
   const KvView& kv = *a.kv;

@@ -19,7 +19,14 @@ void all(int requests, int kv_heads, int heads) {
     if (!p.none) printf("%d %d %d %d %d %d %d\n", i, p.bg, p.b, p.g, p.bh, p.in_group, p.part);
   }
 }
-int main(int, char** v) {
+int main(int n, char** v) {
+  if (n == 3) {                      // heads, are the values on the device?
+    int heads, on;
+    sscanf(v[1], "%d", &heads);
+    sscanf(v[2], "%d", &on);
+    printf("%d\n", attend_parts_for(heads, on));
+    return 0;
+  }
   int x[4];
   for (int i = 0; i < 4; ++i) sscanf(v[i + 1], "%d", x + i);
   if (x[3] == 4) all<4>(x[0], x[1], x[2]);
@@ -50,3 +57,10 @@ def test_every_part_once_and_a_groups_parts_on_one_xcd(program, B, Hkv, G, parts
             assert len(set(block[bg == x] % 8)) == 1, x            # (workgroup i runs on XCD i % 8)
         per_xcd = np.bincount(block % 8, minlength=8)
         assert parts == 1 or per_xcd.max() <= 32                       # a CU for each
+
+
+def test_values_in_host_memory_have_one_workgroup_a_head(program):
+    def parts(heads, on_device):
+        return int(subprocess.run([program, str(heads), str(int(on_device))], capture_output=True, text=True, check=True).stdout)
+    assert [parts(h, True) for h in (1, 64, 65, 4096)] == [4, 4, 1, 1]
+    assert [parts(h, False) for h in (1, 64, 65)] == [1, 1, 1]
