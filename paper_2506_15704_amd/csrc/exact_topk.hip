@@ -7,52 +7,10 @@
 //   2. the filtered scoring kernel streams all rows once and keeps only those that reach the threshold;
 //   3. the select picks the exact k best from the survivors; a head whose survivors are fewer than k (or too many
 //      for the on-chip list) is rescored the plain way, so the result is always the exact Top-k.
+#include "sample_plan.h"
 #include "score_mfma.h"
 
 namespace lfps {
-
-struct SamplePlan {
-  int ns, rank;
-};
-__device__ __forceinline__ SamplePlan plan_sample(const Shape& s, int n, int kb, int ns_max, int list_cap) {
-  kb = kb < 0 ? 0 : (kb > s.kmax ? s.kmax : kb);
-  kb = kb < n ? kb : n;
-  // The sample and the rank r of the sample score that becomes the threshold.  With p = k / n the rows of the whole
-  // context above the r-th best of ns sampled scores number about n r / ns, with a relative spread of 1 / sqrt(r).
-  // That count must land between k (else too few survive) and the select's list capacity: it is aimed at t k with
-  // t = min(2, (1 + cap / k) / 2), the middle of the two limits, and r is made large enough for both to lie
-  // z = 4.5 standard deviations away (a miss costs a rescoring of that head, never a wrong result); the sample
-  // size follows as ns = (r / t) n / k.  A context no larger than that is sampled whole, with r = k.
-  int ns = n, r = kb;
-  if (kb > 0 && n > kb) {
-    const float c = (float)list_cap / (float)kb;
-    const float t = fminf(2.f, 0.5f * (1.f + c));
-    if (t > 1.05f) {
-      const float sr = 4.5f * t / (t - 1.f);
-      r = (int)ceilf(sr * sr);
-      const float want = ((float)r / t) * ((float)n / (float)kb);
-      int cap_ns = ns_max < s.cand_cap ? ns_max : s.cand_cap;
-      cap_ns = cap_ns < n ? cap_ns : n;
-      if (want < (float)cap_ns) {
-        ns = (int)ceilf(want);
-      } else {                                   // no room for the wanted sample: what fits, with the rank that aims at t k
-        ns = cap_ns;
-        r = ns < n ? (int)(t * (float)ns * (float)kb / (float)n) : kb;
-      }
-      if (ns >= n) {
-        ns = n;
-        r = kb;
-      }
-    } else {                                     // the list barely holds the budget: no room to aim, sample everything
-      ns = n < s.cand_cap ? n : s.cand_cap;
-      r = ns == n ? kb : 1;
-    }
-  }
-  r = r < 1 ? 1 : r;
-  r = r > s.kmax ? s.kmax : r;
-  r = r > ns ? ns : r;
-  return SamplePlan{ns, r};
-}
 
 // Step 1, the scores [B, Hq, ns] of the samples, and with them, by the first workgroup of every group, what the next steps need: its
 // rows (x_cnt) and its place on the line of all rows (x_start, with the line's length behind), of every request the length of its
@@ -75,7 +33,8 @@ __global__ __launch_bounds__(kScoreThreads) void k_sample_score(
     return n < 0 ? 0 : (n > s.Lcap ? s.Lcap : n);
   };
   const int n = len(b);
-  const SamplePlan plan = plan_sample(s, n, kk[b], ns_max, list_cap);
+  const int k = kk[b] < 0 ? 0 : (kk[b] > s.kmax ? s.kmax : kk[b]);
+  const SamplePlan plan = plan_sample(n, k, s.kmax > kSampleRanks ? s.kmax : kSampleRanks, ns_max, list_cap);
   if (blockIdx.x == 0 && wave == 0) {
     int64_t before = 0, all = 0;                            // rows of a head
     for (int bb = lane; bb < s.B; bb += 64) {
@@ -117,7 +76,7 @@ __global__ __launch_bounds__(kScoreThreads) void k_sample_score(
 hipError_t launch_sample_score(const Shape& s, const float* q, const KvView& kv, const int32_t* k, int ns_max, int list_cap,
                                int32_t* x_cnt, int64_t* x_start, int32_t* x_ns, int32_t* x_rank, float* score, int64_t score_stride,
                                int32_t* flags, hipStream_t st) {
-  const int most = ns_max < s.cand_cap ? ns_max : s.cand_cap, groups = s.B * s.Hkv;
+  const int most = ns_max < s.Lcap ? ns_max : s.Lcap, groups = s.B * s.Hkv;
   const int tiles = (most + 4 * kRowsPerWaveIter - 1) / (4 * kRowsPerWaveIter), want = (1024 + groups - 1) / groups;   // as launch_group_score
   const dim3 grid(tiles < want ? tiles : want, groups);
   const int kind = kv.k_fp8 ? kKindFp8 : (kv.f16 ? kKindF16 : kKindBf16);

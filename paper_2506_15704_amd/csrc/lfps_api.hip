@@ -7,6 +7,7 @@
 #include <new>
 
 #include "head_place.h"
+#include "sample_plan.h"
 #include "lfps_internal.h"
 
 using namespace lfps;
@@ -708,12 +709,14 @@ int lfps_exact_topk(lfps_ctx* ctx, const float* q, const lfps_kv* kv, const int3
     // its survivors (exact_topk.hip); a head left short takes the plain pass inside the select kernel.
     Shape sd = s;
     sd.cand_cap = s.Lcap;                 // the "candidates" of the dense pass are all rows of a group
+    Shape ranks = s;                      // of the select from the sample (its rows fit the scratch: they are at least 64 long)
+    ranks.kmax = s.kmax > kSampleRanks ? s.kmax : kSampleRanks;
     int64_t* x_total = ctx->x_start + (int64_t)s.B * s.Hkv;
     LAUNCH(ctx, LFPS_KERNEL_GATHER_SCORE, st,
            launch_sample_score(s, q, v, k, kExactSampleRows, filter_list_cap(sd), ctx->x_cnt, ctx->x_start, ctx->x_ns, ctx->x_rank, ctx->score,
                                s.score_stride, ctx->flags, st));
     LAUNCH(ctx, LFPS_KERNEL_SELECT, st,      // the rank-th best sample score of every head -> thr_x (the rows go to scratch)
-           launch_select(s, ctx->score, s.score_stride, nullptr, ctx->x_ns, ctx->x_rank, ctx->slot, nullptr, ctx->thr_x,
+           launch_select(ranks, ctx->score, s.score_stride, nullptr, ctx->x_ns, ctx->x_rank, ctx->slot, nullptr, ctx->thr_x,
                          nullptr, nullptr, st));
     LAUNCH(ctx, LFPS_KERNEL_FILTER_SCORE, st,
            launch_filter_score(sd, q, v, nullptr, ctx->x_cnt, ctx->x_start, x_total, ctx->thr_x, 0.f, ctx->tau, nullptr, ctx->score,

@@ -177,8 +177,8 @@ hipError_t launch_filter_select_attend(const Shape& s, int dtype, float* score, 
                                        const float* q, int32_t* flags, const KvView& kv, float* out,
                                        hipStream_t st);   // out == NULL: select only
 
-// Exact Top-k baseline, the first step of its filtered form (exact_topk.hip): a strided sample of at most ns_max rows per group (and
-// no more than cand_cap; sized for the select's list capacity list_cap) is scored (score [B, Hq, score_stride]; x_ns [B] its
+// Exact Top-k baseline, the first step of its filtered form (exact_topk.hip): a strided sample of at most ns_max rows per group (or
+// all; sized for the select's list capacity list_cap, see plan_sample) is scored (score [B, Hq, score_stride]; x_ns [B] its
 // length), every group's rows 0..n_b-1 are laid on the line (x_cnt, x_start, x_start[B*Hkv] = the line's length), and x_rank [B] is
 // the rank whose sample score is taken as the threshold.
 hipError_t launch_sample_score(const Shape& s, const float* q, const KvView& kv, const int32_t* k, int ns_max, int list_cap,
