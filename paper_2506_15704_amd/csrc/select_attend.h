@@ -253,7 +253,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
     // A wave has consecutive words and expands eight at a time, so that its lanes store side by side.  (With a thread for consecutive words
     // of its own this took 25 us more for the 90000 candidates of a head, 575 us in all.)
     const uint32_t* bm = bitmap + (int64_t)bg * bitmap_words;
-    const int W = (n + 31) >> 5, own = ((W + kWaves - 1) / kWaves + 63) & ~63;
+    const int W = (n + 31) >> 5, own = ((W + kWaves - 1) / kWaves + 7) & ~7;
     const int w0 = wv * own < W ? wv * own : W, w1 = w0 + own < W ? w0 + own : W;
     int mine = 0;
     for (int w = w0 + lane; w < w1; w += 64) mine += __popc(bm[w]);
