@@ -103,7 +103,10 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_wide_score(
   // that of all groups, two workgroups that have them don't share a CU.)
   int parts = plan.parts, part = (int)((blockIdx.y + (blockIdx.z * gridDim.y * gridDim.x >> 8) * (gridDim.y / 2)) % gridDim.y);
   float all_rows = 0.f;
-  if (weigh) {
+  if (weigh && s.B <= 64 && !__ballot(n_lane != n || k_lane != k_raw)) {      // (all alike: 0.5 us for a step of 144 groups)
+    if (extra) return;
+    all_rows = (float)s.B * candidate_rows(s, n, k_raw);
+  } else if (weigh) {
     auto length = [&](int request) {
       const int of = request < 64 ? n_lane : seq_lens[request < s.B ? request : 0];
       return of < 0 ? 0 : (of > s.Lcap ? s.Lcap : of);
