@@ -297,9 +297,10 @@ int lfps_poll_rescored(lfps_ctx* ctx, int32_t* n_heads, void* stream);
  * the summed milliseconds to ms[i] and the number of timed launches to launches[i] (host
  * arrays of LFPS_N_KERNELS), then resets the accumulators. */
 enum {
-  LFPS_KERNEL_CANDIDATES = 0,   /* steps that find their candidates inside the filter_score launch (contexts of up to a million
-                                   rows, table form four million) or the gather_score launch (fp32 caches of up to 8192 rows)
-                                   count it here too, with next to no time; so TABLE_CANDIDATES */
+  LFPS_KERNEL_CANDIDATES = 0,   /* steps that find their candidates inside the filter_score launch (but for the longest contexts of large
+                                   batches and capacities below the bound; table form up to four million rows) or the
+                                   gather_score launch (fp32 caches of up to 8192 rows) count it here too, with next to no time; so
+                                   TABLE_CANDIDATES */
   LFPS_KERNEL_GATHER_SCORE = 1,
   LFPS_KERNEL_SELECT = 2,
   LFPS_KERNEL_SPARSE_ATTN = 3,

@@ -56,7 +56,9 @@ struct WidePlan {
 // -> 320), 2048 still more.  257 to 384 groups get two workgroups each, half the chip standing empty with one costs more than a second
 // generation: 264 x 20000 444 -> 418, 320 x 30000 668 -> 624, 384 x 32K 783 -> 759 (480 x 20000 with two 576 -> 600).
 // Four steps, separate kernels -> these: 64 groups x 32K rows 253 -> 228, 128 x 128K 884 -> 810, 16 x 66000 FP8 145 -> 108, 800 x 8000
-// 514 -> 461.  Up to 2^20 rows the ranges above are the better ones (1 x 32K 72 against 74, 8 x 8000 76 against 80).
+// 514 -> 461; between 171 and 255 groups, with two workgroups each, 176 x 40000 868 -> 846, 200 x 40000 934 -> 892, 240 x 40000 1071 -> 1016.
+// Up to 2^20 rows the ranges above are the better ones (1 x 32K 72 against 74, 8 x 8000 76 against 80).  More than 65536 rows a workgroup
+// there cannot be (256 groups and more of longer contexts): their places have 16 bits.  Such contexts have the separate kernels.
 // Requests of uneven work share the workgroups out by it.  Where they have the fewest already there are 256 more, which else return at once.
 // Four steps of 8 KV heads, separate kernels (which cut the candidates of all requests into equal parts) -> the same number for every
 // request -> by their work: one request of 100000 rows and 31 of 2000 317 -> 803 -> 306 us, FP8 pages 288 -> 826 -> 247, one of 131072 and

@@ -265,8 +265,7 @@ __device__ __forceinline__ void score_slots_mfma(typename KTile<kKind>::Operand 
   using Rows = RowMap<kPaged>;
   using Op = typename KTile<kKind>::Operand;
   constexpr int ES = KTile<kKind>::kElemBytes;
-  const int lane = threadIdx.x & 63;
-  const int j = lane & 15, kb = lane >> 4;
+  const int lane = threadIdx.x & 63, j = lane & 15;
   auto valid = [&](int row) { return row >= 0 && row < n; };
   auto physical = [&](int row) { return Rows::phys(pg, b, valid(row) ? row : 0); };
 

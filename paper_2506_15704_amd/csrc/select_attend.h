@@ -243,7 +243,7 @@ __global__ __launch_bounds__(NT, 4) void k_filter_select_attend(
   }
   float* thr_out = writes && filter_pays(c, ksel, keep) ? thr_state + bh : nullptr;
   if (tid == 0 && writes) {
-    if (!thr_out) thr_state[bh] = -INFINITY;                // (every thread has read it before the barrier)
+    if (!thr_out) thr_state[bh] = -INFINITY;                // (nobody in this launch reads it: what the survivors reached is tau_in)
     if (keep.fits) keep.fits[bh] = c <= keep.most;
   }
   float* sc = score + (int64_t)bh * score_stride;

@@ -1,6 +1,6 @@
 """Candidates and scores in one kernel (chained steps of up to a million rows): at the edges of its ranges and pieces, from
-the Top-k of the step before and from the table flags, against an unfiltered context, which takes other kernels.  And the
-separate kernels, which the same steps take with more rows, or with a candidate capacity below the bound, as here."""
+the Top-k of the step before and from the table flags, against an unfiltered context, which takes other kernels.  (Larger contexts:
+tests/test_wide_ranges.py.)  And the separate kernels, which the same steps take with a candidate capacity below the bound, as here."""
 import pytest
 import torch
 

@@ -243,6 +243,49 @@ def test_uneven_steps(Hq, Hkv, L, lens, ks, dtype, page, cut):
     b.close()
 
 
+# a NaN query and infinite ones: rows of the request, distinct and as many as the budget, for their groups; what a clean step gives for the others
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hkv,L,dtype", [(8, 66000, "bf16"), (8, 66000, "f16"), (4, 140000, "fp8")])
+def test_non_finite_queries(Hkv, L, dtype, cut):
+    import torch
+    from tests.harness import DEV
+    from tests.test_gpu_ranges import _cache, _pair, _view
+    B, Hq, k = 2, 4 * Hkv, 300
+    ((narrow, r, *_),) = cut("plan", [(B, Hkv, L, 4, _pieces(L))])
+    assert narrow == 0 and r > 0
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    cache = _cache(B, Hkv, L, dtype, 0, g)
+    clean, dirty = _pair(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, kv_dtype="bf16" if dtype == "fp8" else dtype, k_fp8=dtype == "fp8",
+                         max_seq_len=L, max_k=k, radius=3)
+    dirty.lfps_set_filter(True)
+    seq, ks = (torch.tensor([x] * B, dtype=torch.int32, device=DEV) for x in (L, k))
+    q = torch.randn((B, Hq, 128), device=DEV, generator=g)
+    prev = torch.full((B, Hq, k), -1, dtype=torch.int32, device=DEV)
+    clean.lfps_exact_topk(q, _view(clean, cache, seq), ks, prev)
+    before = [prev, prev]
+    for t in range(3):
+        q = q + 0.1 * torch.randn((B, Hq, 128), device=DEV, generator=g)
+        bad = q.clone()
+        bad[0, 1, 5], bad[0, Hq - 1, :], bad[1, 6, 100] = float("nan"), float("inf"), float("-inf")
+        res = []
+        for ctx, query, last in ((clean, q, before[0]), (dirty, bad, before[1])):
+            idx, out = torch.full((B, Hq, k), -5, dtype=torch.int32, device=DEV), torch.zeros((B, Hq, 128), device=DEV)
+            ctx.lfps_step(query, _view(ctx, cache, seq), last, ks, idx, out)
+            res.append((idx, out))
+        before = [res[0][0], res[1][0]]
+        groups = {(0, 0), (0, Hkv - 1), (1, 1)}
+        for b in range(B):
+            for h in range(Hq):
+                mine = res[1][0][b, h]
+                if (b, h // 4) in groups:
+                    assert int(mine.min()) >= 0 and int(mine.max()) < L and len(torch.unique(mine)) == k, (t, b, h)
+                else:
+                    assert torch.equal(mine, res[0][0][b, h]) and torch.equal(res[1][1][b, h], res[0][1][b, h]), (t, b, h)
+    clean.close()
+    dirty.close()
+
+
 # requests that are far below the context's capacity have strips of their own length: the same bits as in a context without that room
 @pytest.mark.gpu
 def test_room_to_grow():
