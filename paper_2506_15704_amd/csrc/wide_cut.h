@@ -39,8 +39,8 @@ struct StripWindows {
   }
   LFPS_BOTH bool touches(int i) const { return (uint32_t)i - (uint32_t)lowest < span; }
   // ... and the rows of the strip, counted from its first, that such a window covers
-  LFPS_BOTH int from(int i, int r) const { return i - r > begin ? i - r - begin : 0; }
-  LFPS_BOTH int to(int i, int r) const { return (i + r + 1 < end ? i + r + 1 : end - 1) - begin; }
+  LFPS_BOTH static int from(int i, int r, int begin) { return i - r > begin ? i - r - begin : 0; }
+  LFPS_BOTH static int to(int i, int r, int begin, int end) { return (i + r + 1 < end ? i + r + 1 : end - 1) - begin; }
 };
 
 constexpr int kWideMax = 65536;      // rows of a workgroup at most: their places are 16 bits

@@ -58,7 +58,7 @@ int main() {
         const Strips s(n, parts, part);
         for (int x = 0; x < 2; ++x) {
           const StripWindows in(n, x ? s.second : s.first, s.rows, r);
-          if (in.touches(i)) for (int y = in.from(i, r); y <= in.to(i, r); ++y) printf("%d ", s.row_of(x * s.rows + y));
+          if (in.touches(i)) for (int y = in.from(i, r, in.begin); y <= in.to(i, r, in.begin, in.end); ++y) printf("%d ", s.row_of(x * s.rows + y));
         }
       }
       printf("\n");
