@@ -76,4 +76,14 @@ inline WidePlan wide_plan_for(int batch, int heads, int rows, int pieces) {
   return WidePlan{(int)most, (int)parts, batch == 1 ? 0 : (shared > extra ? shared : extra), of_one > (int)parts ? of_one : (int)parts};
 }
 
+// Its grid, see WideBlock.
+struct WideGrid {
+  int beside, parts, deep;
+};
+inline WideGrid wide_grid(const WidePlan& plan, int batch, int heads) {
+  const int groups = batch * heads, beside = groups % 8 == 0 || plan.parts == 1 ? 8 : 1, row = beside * plan.parts;
+  const int over = plan.slots > batch * plan.parts ? (plan.slots - batch * plan.parts) * heads : 0;
+  return WideGrid{beside, plan.parts, (groups + beside - 1) / beside + (over + row - 1) / row};
+}
+
 }  // namespace lfps

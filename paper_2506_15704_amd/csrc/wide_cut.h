@@ -46,6 +46,27 @@ struct StripWindows {
 constexpr int kWideMax = 65536;      // rows of a workgroup at most: their places are 16 bits
 LFPS_BOTH int fewest_parts(int n) { return n > kWideMax ? (n - 1) / kWideMax + 1 : 1; }
 
+// Which work workgroup (x, y, z) of a grid of `beside` x `parts` x any has.  Workgroups are dealt to the XCDs in turn, and those of a
+// group share an L2, so eight groups lie side by side, where they are a multiple of eight or have one workgroup each: without that
+// 65535 groups and what is behind them would be more than the 65535 that a grid may be deep.
+// Of an even cut it is part `part` of request b's KV head g; behind those the grid has workgroups for batches of uneven requests (`extra`).
+// 256 workgroups take a CU each, and the next 256 share them: theirs are other parts, so that where the candidates crowd in one strip,
+// that of all groups, two workgroups that have them don't share a CU.
+struct WideBlock {
+  bool extra;
+  int at_extra, b, g, part;
+  LFPS_BOTH WideBlock(int groups, int heads, int beside, int parts, int x, int y, int z) {
+    const int at = z * beside + x;
+    extra = at >= groups;
+    at_extra = (z * beside - groups) * parts + (y * beside + x);
+    b = extra ? 0 : (int)((uint32_t)at / (uint32_t)heads);
+    g = extra ? (int)((uint32_t)at_extra % (uint32_t)heads) : at - b * heads;
+    part = (int)(((uint32_t)y + ((uint32_t)(z * parts * beside) >> 8) * (uint32_t)(parts / 2)) % (uint32_t)parts);
+  }
+  // ... and of an uneven one the slot of that KV head, request by request.
+  LFPS_BOTH int slot(int batch, int heads, int parts) const { return extra ? batch * parts + (int)((uint32_t)at_extra / (uint32_t)heads) : b * parts + part; }
+};
+
 // How many of the workgroups of a KV head a request gets.  `rows`: of its candidates, about; `all`: of those of all requests; `spare`: the
 // workgroups beyond the fewest that each request can do with.  (No more than there are: what the quotients' errors add up to, below 1e-3 of
 // a spare one, is less than what rounding down leaves.)  A batch is cut evenly unless a request has more than twice its share.

@@ -54,13 +54,10 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_wide_score(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, kb = lane >> 4;
-  // grid (8 groups side by side, parts, the other groups and, behind them, workgroups for batches of uneven requests): workgroups are
-  // dealt to the XCDs in turn, and those of a group share an L2
-  const int at_z = blockIdx.z * gridDim.x + blockIdx.x;
-  const bool extra = at_z >= s.B * s.Hkv;
-  const int at_extra = ((int)blockIdx.z * (int)gridDim.x - s.B * s.Hkv) * (int)gridDim.y + (int)(blockIdx.y * gridDim.x + blockIdx.x);
-  int b = extra ? 0 : (int)((uint32_t)at_z / (uint32_t)s.Hkv);
-  const int g = extra ? (int)((uint32_t)at_extra % (uint32_t)s.Hkv) : at_z - b * s.Hkv;
+  const WideBlock at_block(s.B * s.Hkv, s.Hkv, gridDim.x, gridDim.y, blockIdx.x, blockIdx.y, blockIdx.z);
+  const bool extra = at_block.extra;
+  int b = at_block.b;
+  const int g = at_block.g;
 
   using Rows = RowMap<kPaged>;
   using Tile = StreamTile<kKind>;
@@ -99,9 +96,7 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_wide_score(
   ask_for(b);
 
   // ---- whose rows: part `part` of `parts` of request b
-  // (256 workgroups take a CU each, and the next 256 share them: theirs are other parts, so that where the candidates crowd in one strip,
-  // that of all groups, two workgroups that have them don't share a CU.)
-  int parts = plan.parts, part = (int)((blockIdx.y + (blockIdx.z * gridDim.y * gridDim.x >> 8) * (gridDim.y / 2)) % gridDim.y);
+  int parts = plan.parts, part = at_block.part;
   float all_rows = 0.f;
   if (weigh && s.B <= 64 && !__ballot(n_lane != n || k_lane != k_raw)) {      // (all alike: 0.5 us for a step of 144 groups)
     if (extra) return;
@@ -128,7 +123,7 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_wide_score(
     largest = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_max_in_last(largest)), 63));
     if (plan.slots > 0 && uneven(largest, all_rows, s.B)) {
       const int spare = plan.slots - __builtin_amdgcn_readlane(wave_inclusive_sum(fewest), 63);
-      int slot = extra ? s.B * parts + at_extra / s.Hkv : b * parts + part;
+      int slot = at_block.slot(s.B, s.Hkv, parts);
       parts = 0;
       for (int c0 = 0; c0 < s.B; c0 += 64) {               // (every wave of every workgroup finds the same numbers)
         const int mine = c0 + lane < s.B ? parts_of_request(length(c0 + lane), rows_of(c0 + lane), all_rows, spare, plan.most) : 0;
@@ -147,6 +142,8 @@ __global__ __launch_bounds__(kScoreThreads, 2) void k_wide_score(
     } else if (extra) {
       return;
     }
+  } else if (extra) {
+    return;
   }
   const int bg = b * s.Hkv + g;
   const int64_t head0 = (int64_t)b * s.Hq + (int64_t)g * G, my_head = head0 + (kb < G ? kb : 0);
@@ -412,21 +409,21 @@ hipError_t launch_wide_score(const Shape& s, const float* q, const KvView& kv, c
                              const float* thr_state, float margin, float* tau_out, const int32_t* skip_if, float* score, int32_t* slot_out,
                              int64_t score_stride, int32_t* seg_count, int nseg, int32_t* parts_of, uint32_t* bitmap, int bitmap_words,
                              int32_t* flags, hipStream_t st) {
-  const int groups = s.B * s.Hkv, beside = groups % 8 == 0 ? 8 : 1;
+  const int groups = s.B * s.Hkv;
   const int kind = kv.k_fp8 ? kKindFp8 : (kv.f16 ? kKindF16 : kKindBf16);
   const bool paged = kv.page.table != nullptr;
   const WidePlan plan = wide_plan(s);
   if (plan.rows <= 0) return hipErrorInvalidValue;
   // (cand_cap is at least what the windows can cover)
   const int may_once = (int64_t)groups * s.cand_cap * kD * (kind == kKindFp8 ? 1 : 2) > kKeptBytes;
-  const int over = (plan.slots - s.B * plan.parts) * s.Hkv, row = beside * plan.parts, more = over > 0 ? (over + row - 1) / row : 0;
+  const WideGrid grid = wide_grid(plan, s.B, s.Hkv);
   hipError_t e = hipErrorInvalidValue;
   auto launch = [&](auto heads, auto pages, auto form) {
     constexpr int G = decltype(heads)::value, kKind = decltype(form)::value;
     constexpr bool kPaged = decltype(pages)::value;
     if (s.G != G || paged != kPaged || kind != kKind) return;
-    hipLaunchKernelGGL((wide_kernel<G, kPaged, kKind>), dim3(beside, plan.parts, groups / beside + more), dim3(kScoreThreads), (size_t)(plan.slots ? kWideMax : plan.rows) / 8 + kWideSpare * 4,
-                       st, s, q, kv.k, kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, prev_topk, k, thr_state, margin, tau_out,
+    hipLaunchKernelGGL((wide_kernel<G, kPaged, kKind>), dim3(grid.beside, grid.parts, grid.deep), dim3(kScoreThreads),
+                       (size_t)(plan.slots ? kWideMax : plan.rows) / 8 + kWideSpare * 4, st, s, q, kv.k, kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, prev_topk, k, thr_state, margin, tau_out,
                        skip_if, score, slot_out, score_stride, seg_count, nseg, parts_of, bitmap, bitmap_words, plan,
                        0.08838834764831845f /* 1/sqrt(128) */, flags, may_once);
     e = hipGetLastError();

@@ -37,6 +37,23 @@ int main() {
       if (!uneven(largest, all, batch)) printf("0");
       else for (int i = 0; i < batch; ++i) printf("%d ", parts_of_request(n[i], rows[i], all, spare, most));
       printf("\n");
+    } else if (!strcmp(what, "grid")) {             // requests, KV heads, rows, pieces -> its depth; slots and parts that are not one workgroup's
+      int batch, heads, rows, pieces; long long bad = 0;
+      if (scanf("%d %d %d %d", &batch, &heads, &rows, &pieces) != 4) return 1;
+      const WidePlan p = wide_plan_for(batch, heads, rows, pieces);
+      if (!p.rows) { printf("0 0\n"); continue; }
+      const WideGrid grid = wide_grid(p, batch, heads);
+      const int slots = p.slots > batch * p.parts ? p.slots : batch * p.parts;
+      std::vector<int> even((size_t)batch * heads * p.parts), uneven((size_t)heads * slots);
+      for (int z = 0; z < grid.deep; ++z) for (int y = 0; y < grid.parts; ++y) for (int x = 0; x < grid.beside; ++x) {
+        const WideBlock block(batch * heads, heads, grid.beside, grid.parts, x, y, z);
+        const int slot = block.slot(batch, heads, p.parts);
+        if (!block.extra) ++even[((size_t)block.b * heads + block.g) * p.parts + block.part];
+        if (slot < slots) ++uneven[(size_t)block.g * slots + slot];
+      }
+      for (int n : even) bad += n != 1;
+      for (int n : uneven) bad += n != 1 && p.slots > 0;
+      printf("%d %lld\n", grid.deep, bad);
     } else if (!strcmp(what, "rows")) {             // rows, parts: which rows are not one workgroup's, or not found again
       int n, parts; long long bad = 0;
       if (scanf("%d %d", &n, &parts) != 2) return 1;
@@ -107,6 +124,15 @@ def test_plans_are_what_the_kernel_can_take(cut):
         for m in {x for x in (1, 63, 64, 65, n // 3 + 1, n - 1, n) if 0 < x <= n}:     # a request's own strips: no longer ones
             assert 2 * _strip_rows(m, parts) <= r, (groups, n, m)
             assert 2 * _strip_rows(m, -(-m // 65536)) <= 65536
+
+
+# (a grid may be 65535 deep; a batch has up to 65535 groups)
+def test_grids_have_every_part_once(cut):
+    cases = [(B, h, n, _pieces(n)) for B, h in [(g, 1) for g in (1, 2, 7, 8, 9, 63, 100, 257, 264, 385, 513, 700, 65528, 65529, 65535)] +
+             [(1, 8), (1, 601), (1, 65535), (3, 5), (13, 5), (16, 8), (32, 8), (33, 8), (65, 8), (107, 5), (1024, 8), (4681, 14), (2, 32767), (9362, 7)]
+             for n in (18, 33000, 65536, 140000)]
+    for case, (deep, bad) in zip(cases, cut("grid", cases)):
+        assert bad == 0 and deep <= 65535, (case, deep, bad)
 
 
 def _candidates(n, k, r):
@@ -197,10 +223,21 @@ def test_steps(B, Hq, Hkv, L, k, r, n_recent, n_sink, dtype, page):
     steps(B, Hq, Hkv, L, k, r, n_recent, n_sink, dtype, page)
 
 
+# many groups, no multiple of eight: of one request, and of many
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,Hq,Hkv,L,k,r,n_recent,n_sink,dtype,page", [(1, 601, 601, 2100, 40, 2, 0, 4, "bf16", 0),
+                                                                       (171, 6, 3, 2100, 40, 2, 0, 4, "fp8", 16)])
+def test_many_groups(B, Hq, Hkv, L, k, r, n_recent, n_sink, dtype, page, cut):
+    ((narrow, rows, parts, *_),) = cut("plan", [(B, Hkv, L, Hq // Hkv, _pieces(L))])
+    assert narrow == 0 and rows > 0 and parts == 1
+    test_steps(B, Hq, Hkv, L, k, r, n_recent, n_sink, dtype, page)
+
+
 # one long request among short ones and of one row, one large budget among small ones, a request that needs two workgroups for its places,
-# more requests than a wave has lanes: against an unfiltered context, and the same bits when the batch changes between steps
+# more requests than a wave has lanes, many groups, no multiple of eight: against an unfiltered context, and the same bits when the batch changes between steps
 @pytest.mark.gpu
 @pytest.mark.parametrize("Hq,Hkv,L,lens,ks,dtype,page", [
+    (3, 3, 6000, [100] * 150 + [6000] + [33] * 20, [9] * 150 + [400] + [3] * 20, "bf16", 0),
     (8, 8, 100000, [100000, 1, 2000, 64, 65] + [700] * 7, [1500, 1, 40, 5, 64] + [30] * 7, "bf16", 0),
     (32, 8, 140000, [300, 139000, 20000], [20, 1000, 300], "fp8", 16), (16, 8, 16500, [16500] * 9, [30] * 8 + [900], "f16", 64),
     (4, 4, 6000, [100] * 69 + [6000] + [33] * 7, [9] * 69 + [400] + [3] * 7, "bf16", 16)])
