@@ -13,7 +13,8 @@
 // Why two strips: Top-k rows crowd, and of rows in one piece either all or none are candidates then.  Four steps with the Top-k in the
 // last eighth (quarter) of the rows, separate kernels -> one piece -> two strips: 64 groups x 32K rows 172 (212) -> 225 (226) -> 147
 // (178), 16 x 128K 178 (206) -> 222 (217) -> 150 (178), 128 x 128K 625 (940) -> 915 (1465) -> 692 (870), 256 x 64K 630 (940) -> 630 (980)
-// -> 570 (843).  Spread rows pay 2 % for it (the select finds twice the pieces).  With four or eight strips the waves' quarters become
+// -> 570 (843).  Spread rows pay 2 to 4 % for it (the select finds twice the pieces), up to 6 % where a workgroup has few (four steps of 152 x
+// 10072, separate kernels 148, one piece 110, two strips 117).  With four or eight strips the waves' quarters become
 // short and the pieces many: 64 x 32K 43 and 45 us here and 15.0 and 16.0 in the select, instead of 40 and 14.6.
 #include "candidates.h"
 #include "range_geometry.h"
@@ -423,8 +424,8 @@ hipError_t launch_wide_score(const Shape& s, const float* q, const KvView& kv, c
     constexpr bool kPaged = decltype(pages)::value;
     if (s.G != G || paged != kPaged || kind != kKind) return;
     hipLaunchKernelGGL((wide_kernel<G, kPaged, kKind>), dim3(grid.beside, grid.parts, grid.deep), dim3(kScoreThreads),
-                       (size_t)(plan.slots ? kWideMax : plan.rows) / 8 + kWideSpare * 4, st, s, q, kv.k, kv.stride_b, kv.stride_h, kv.stride_n, kv.page, kv.seq_lens, prev_topk, k, thr_state, margin, tau_out,
-                       skip_if, score, slot_out, score_stride, seg_count, nseg, parts_of, bitmap, bitmap_words, plan,
+                       (size_t)(plan.slots ? kWideMax : plan.rows) / 8 + kWideSpare * 4, st, s, q, kv.k, kv.stride_b, kv.stride_h,
+                       kv.stride_n, kv.page, kv.seq_lens, prev_topk, k, thr_state, margin, tau_out, skip_if, score, slot_out, score_stride, seg_count, nseg, parts_of, bitmap, bitmap_words, plan,
                        0.08838834764831845f /* 1/sqrt(128) */, flags, may_once);
     e = hipGetLastError();
   };
